@@ -227,3 +227,58 @@ def tolerance(case):
     if case["kind"] == "backward":
         return {"rel": 5e-4, "max": 3.2e-2}
     return {"rel": 1e-2, "max": 8e-2}
+
+
+def exact(case, seed):
+    """What the first `run` on these inputs returns, in 64 bits (whole results: no value of their own, None)."""
+    st = prepare(case, seed)
+    S, H, H_kv, d = (case[n] for n in ("S", "H", "H_kv", "d"))
+    rows = max(1, (1 << 26) // S)
+
+    def probabilities(h, r0, r1, tokens, exclude_self):
+        """Rows r0..r1 of softmax(Q K^T / sqrt(d)) of query head h over `tokens` (all if None)."""
+        q, k = (st[n] if tokens is None else st[n][tokens] for n in ("Q", "K"))
+        q, k = q[r0:r1, h].double(), k[:, h * H_kv // H].double()
+        x = q @ k.t().contiguous() / math.sqrt(d)
+        i = torch.arange(r0, r1, device="cuda").unsqueeze(1)
+        j = torch.arange(k.shape[0], device="cuda").unsqueeze(0)
+        if case["causal"]:
+            x.masked_fill_(j > i, -math.inf)
+        x = torch.softmax(x, dim=1)
+        return x.masked_fill_(j == i, 0.0) if exclude_self else x
+
+    if case["kind"] == "eliminate":
+        scores = torch.zeros(S, dtype=torch.float64, device="cuda")
+        for h in range(H):
+            for r in range(0, S, rows):
+                scores += probabilities(h, r, min(S, r + rows), None, True).sum(0)
+        return scores / H, None
+    if case["kind"] == "blocks":
+        b = case["b"]
+        nb = -(-S // b)
+        score_blocks = torch.zeros((nb, nb), dtype=torch.float64, device="cuda")
+        rows = max(b, rows // b * b)
+        for r in range(0, S, rows):
+            n = min(rows, S - r)
+            mean = torch.zeros((-(-n // b) * b, nb * b), dtype=torch.float64, device="cuda")
+            for h in range(H):
+                mean[:n, :S] += probabilities(h, r, r + n, None, True)
+            score_blocks[r // b:r // b + mean.shape[0] // b] = mean.view(-1, b, nb, b).amax(dim=(1, 3)) / H
+        token_blocks = score_blocks.sum(0)
+        return score_blocks, token_blocks, token_blocks.mean().reshape(1), None, None
+    kept = st["kept"].long()
+    M = kept.numel()
+    if case["kind"] == "forward":
+        O = st["O"].double()
+        if case["dtype"] == "bf16":
+            for h in range(H):
+                v = st["V"][kept, h * H_kv // H].double()
+                for r in range(0, M, rows):
+                    O[r:r + rows, h] = probabilities(h, r, min(M, r + rows), kept, False) @ v
+        R = st["R"].double()
+        R[kept] += O.view(M, -1) @ st["W_out"].double().t().contiguous()
+        return O, R, R[kept] @ st["W_up"].double().t().contiguous()
+    dY = st["dY"].double()
+    dX = st["dX"].double()
+    dX[kept] += dY @ st["W"].double() + st["G"].double()
+    return dX, dY.t().contiguous() @ st["X"][kept].double()
