@@ -3,14 +3,13 @@
 // indexed load is as coalesced as a dense one and no compacted copy of X ever exists.
 //
 // 256 x 256 output tile per workgroup, 4 waves in a 2 x 2 grid, each wave 128 x 128 = 4 x 4 MFMA tiles
-// of 32 x 32 (256 accumulator registers per lane).  K advances 128 bytes per stage (64 bf16 / 32 fp32)
+// of 32 x 32 (256 accumulator registers per lane).  K advances 128 bytes per stage (64 bf16 elements)
 // through two LDS stages; the next stage's global loads are issued before the current stage's MFMAs.
 // Both operands are K-contiguous in memory (X rows, nn.Linear weight rows), which is exactly the
 // per-lane 16-byte fragment the 32x32 MFMAs take, so neither needs a transpose.
 #include <mutex>
-#include <type_traits>
 
-#include "lemo_common.hpp"
+#include "gather_gemm.hpp"
 
 namespace lemo {
 
@@ -31,23 +30,10 @@ constexpr int GG_NLD = GG_BM * GG_CPR / GG_THREADS;  // 8 loads per thread per o
 #endif
 constexpr int GG_GROUP_M = LEMO_GG_GROUP_M;  // tile rows walked together (4 keeps a die's 32 tiles to a 4 x 8 patch)
 
-// How the operands lie in memory (an MFMA lane always wants 8 consecutive contraction elements of one operand row):
-//   GG_NT  A rows and B rows run along the contraction (X[idx] [M,C] against an nn.Linear weight [N,C]); 16-byte reads.
-//   GG_NN  A as above; B is stored contraction-major, [C, N] (the same weight used the other way round, as the input
-//          gradient needs it).  Its slabs go to LDS as they are, 64 contraction rows x 256 columns, and the fragments
-//          come out through the transposing LDS read (ds_read_b64_tr_b16: inside a group of 16 lanes, lane l receives
-//          element l % 4 of the 8 bytes addressed by lanes l / 4, 4 + l / 4, 8 + l / 4 and 12 + l / 4 -- with lane
-//          4 j + q pointed at row j, column quad q of a 4-row x 16-column block, lane l gets 4 consecutive rows of
-//          column l).  Two such reads make one 16-byte fragment: the same bytes from LDS as before, no transposed copy
-//          anywhere.
-//   GG_TN  both operands contraction-major: A [C, M], B [C, N] with B's rows picked by idx (the weight gradient: the
-//          contraction runs over the kept tokens).  bf16 only for GG_NN and GG_TN.
-enum { GG_NT = 0, GG_NN = 1, GG_TN = 2 };
 constexpr int GG_KROWS = 64;             // contraction rows per slab of a contraction-major operand
 constexpr int GG_KPITCH = 512 + 32;      // LDS pitch of such a row (256 columns + pad): 136 dwords, so the 4 rows x 4 column
                                          // quads one 16-lane group reads fall into 32 distinct banks
 static_assert(GG_KROWS * GG_KPITCH <= GG_BM * GG_STRIDE, "a contraction-major slab must fit the operand's LDS region");
-typedef __attribute__((ext_vector_type(4))) short s16x4;
 
 // exchange with the neighbouring lane (l ^ 1) inside a quad: DPP quad_perm [1,0,3,2]
 __device__ __forceinline__ float swap_with_neighbour(float v) {
@@ -66,22 +52,12 @@ __global__ __launch_bounds__(GG_THREADS, 1) void gather_gemm_kernel(const T* __r
                                                                     long long ldy, int C, int N, int tiles_m, int tiles_n,
                                                                     unsigned x_bytes, const int* __restrict__ oidx,
                                                                     long long out_rows, unsigned r_bytes, unsigned w_bytes_all) {
-    static_assert(LAYOUT == GG_NT || sizeof(T) == 2, "the contraction-major layouts are built for 16-bit elements");
+    static_assert(sizeof(T) == 2, "built for 16-bit elements");
     constexpr bool A_KMAJOR = LAYOUT == GG_TN, B_KMAJOR = LAYOUT != GG_NT;
     extern __shared__ __attribute__((aligned(16))) char smem[];
 
-    // tile assignment: die x = b % 8 takes a contiguous run of tiles in grouped order (GROUP_M tile rows
-    // at a time, column by column), so the tiles resident on one die share X rows and W rows through L2
-    const int total = tiles_m * tiles_n;
-    const int per_xcd = (total + NUM_XCD - 1) / NUM_XCD;
-    const int b = blockIdx.x;
-    const int tile = (b % NUM_XCD) * per_xcd + b / NUM_XCD;
-    if (b / NUM_XCD >= per_xcd || tile >= total) return;
-    const int group = tile / (GG_GROUP_M * tiles_n);
-    const int first_m = group * GG_GROUP_M;
-    const int rows_in_group = min(GG_GROUP_M, tiles_m - first_m);
-    const int within = tile - group * GG_GROUP_M * tiles_n;
-    const int tm = first_m + within % rows_in_group, tn = within / rows_in_group;
+    int tm, tn;
+    if (!gg_tile(blockIdx.x, tiles_m, tiles_n, GG_GROUP_M, tm, tn)) return;
     const long long m0 = (long long)tm * GG_BM;
     const int n0 = tn * GG_BN;
 
@@ -335,123 +311,100 @@ __global__ __launch_bounds__(GG_THREADS, 1) void gather_gemm_kernel(const T* __r
     // epilogue of the in-place-add form.  Output row of result row m: oidx[m] (m itself without a list); rows whose
     // index falls outside [0, out_rows) are dropped.
     auto add_epilogue = [&]() {
-        if constexpr (sizeof(T) == 2) {
-            // The wave's 128 x 128 block goes through LDS in two halves of 64 rows, as binary32 (the residual is
-            // added before the only rounding).  A lane then owns 8 consecutive columns of a row (16 lanes cover a
-            // row's 256 bytes): two 16-byte LDS reads, the residual's 16 bytes, one 16-byte store.  The residual
-            // rows are requested ahead -- half 0 before anything is staged, half 1 before half 0 is consumed -- so
-            // that their latency is covered by the staging.
-            constexpr int EPF = 128 * 4 + 16;  // LDS pitch of one staged row of 128 floats
-            char* region = smem + wave * 64 * EPF;
-            const bool vec_ok = ((ldy & 7) == 0) && ((reinterpret_cast<uintptr_t>(Y) & 15u) == 0);
-            const int piece = lane & 15, rsub = lane >> 4;
-            const int ncol = n0 + wn * 128 + piece * 8;
-            const bool col_vec = vec_ok && ncol + 8 <= N;
-            float bv[4];
+        // The wave's 128 x 128 block goes through LDS in two halves of 64 rows, as binary32 (the residual is
+        // added before the only rounding).  A lane then owns 8 consecutive columns of a row (16 lanes cover a
+        // row's 256 bytes): two 16-byte LDS reads, the residual's 16 bytes, one 16-byte store.  The residual
+        // rows are requested ahead -- half 0 before anything is staged, half 1 before half 0 is consumed -- so
+        // that their latency is covered by the staging.
+        constexpr int EPF = 128 * 4 + 16;  // LDS pitch of one staged row of 128 floats
+        char* region = smem + wave * 64 * EPF;
+        const bool vec_ok = ((ldy & 7) == 0) && ((reinterpret_cast<uintptr_t>(Y) & 15u) == 0);
+        const int piece = lane & 15, rsub = lane >> 4;
+        const int ncol = n0 + wn * 128 + piece * 8;
+        const bool col_vec = vec_ok && ncol + 8 <= N;
+        float bv[4];
 #pragma unroll
-            for (int j = 0; j < 4; ++j) {
-                const int n = n0 + wn * 128 + j * 32 + l32;
-                bv[j] = (bias && n < N) ? bf16_to_f32(reinterpret_cast<const uint16_t*>(bias)[n]) : 0.f;
-            }
-            // Byte offset in R of this lane's piece of row (ih*64 + rr*4 + rsub), or NONE if it is not to be written.
-            // All 32 row indices are fetched in one batch, and the residual is read through a range-checked buffer
-            // descriptor (a NONE offset lies past its end and reads as zero), so nothing here branches or waits
-            // between the loads.
-            const unsigned NONE = r_bytes;
-            const int ldy_bytes = (int)ldy * 2;
-            const __amdgpu_buffer_rsrc_t r_rsrc = __builtin_amdgcn_make_buffer_rsrc(reinterpret_cast<char*>(Y), 0, (int)r_bytes, 0x00020000);
-            int orow[2][16];
-#pragma unroll
-            for (int ih = 0; ih < 2; ++ih)
-#pragma unroll
-                for (int rr = 0; rr < 16; ++rr) {
-                    const long long m = min(m0 + wm * 128 + ih * 64 + rr * 4 + rsub, M - 1);
-                    orow[ih][rr] = oidx ? oidx[m] : (int)m;
-                }
-            unsigned roff[2][16];
-#pragma unroll
-            for (int ih = 0; ih < 2; ++ih)
-#pragma unroll
-                for (int rr = 0; rr < 16; ++rr) {
-                    const long long m = m0 + wm * 128 + ih * 64 + rr * 4 + rsub;
-                    const bool ok = (m < M) & (ncol < N) & (orow[ih][rr] >= 0) & (orow[ih][rr] < out_rows);  // no short circuit: no branches
-                    roff[ih][rr] = ok ? (unsigned)orow[ih][rr] * (unsigned)ldy_bytes + (unsigned)ncol * 2u : NONE;
-                }
-            auto prefetch = [&](int ih, u32x4 (&old)[16]) {
-#pragma unroll
-                for (int rr = 0; rr < 16; ++rr)
-                    old[rr] = __builtin_amdgcn_raw_buffer_load_b128(r_rsrc, (int)(col_vec ? roff[ih][rr] : NONE), 0, 0);
-            };
-            auto stage = [&](int ih) {
-#pragma unroll
-                for (int j = 0; j < 4; ++j) {
-                    char* colp = region + (4 * half) * EPF + (j * 32 + l32) * 4;
-#pragma unroll
-                    for (int ii = 0; ii < 2; ++ii)
-#pragma unroll
-                        for (int r = 0; r < 16; ++r)
-                            *reinterpret_cast<float*>(colp + (ii * 32 + 8 * (r >> 2) + (r & 3)) * EPF) = acc[ih * 2 + ii][j][r] + bv[j];
-                }
-            };
-            auto consume = [&](int ih, const u32x4 (&old)[16]) {
-#pragma unroll
-                for (int rr = 0; rr < 16; ++rr) {
-                    const int row = rr * 4 + rsub;
-                    const f32x4 lo = *reinterpret_cast<const f32x4*>(region + row * EPF + piece * 32);
-                    const f32x4 hi = *reinterpret_cast<const f32x4*>(region + row * EPF + piece * 32 + 16);
-                    if (roff[ih][rr] == NONE) continue;
-                    uint16_t* dst = reinterpret_cast<uint16_t*>(reinterpret_cast<char*>(Y) + roff[ih][rr]);
-                    const float v[8] = {lo[0], lo[1], lo[2], lo[3], hi[0], hi[1], hi[2], hi[3]};
-                    if (col_vec) {
-                        u32x4 out;
-#pragma unroll
-                        for (int e = 0; e < 4; ++e)
-                            out[e] = pack_bf16x2_hw(v[2 * e] + __uint_as_float(old[rr][e] << 16),
-                                                    v[2 * e + 1] + __uint_as_float(old[rr][e] & 0xffff0000u));
-                        *reinterpret_cast<u32x4*>(dst) = out;
-                    } else {  // ragged right edge or unaligned rows: element by element
-#pragma unroll
-                        for (int e = 0; e < 8; ++e)
-                            if (ncol + e < N) dst[e] = (uint16_t)(pack_bf16x2_hw(v[e] + bf16_to_f32(dst[e]), 0.f) & 0xffffu);
-                    }
-                }
-            };
-            u32x4 old0[16], old1[16];
-            prefetch(0, old0);
-            stage(0);
-            prefetch(1, old1);
-            consume(0, old0);
-            stage(1);
-            consume(1, old1);
-        } else {
-#pragma unroll
-            for (int j = 0; j < 4; ++j) {
-                const int n = n0 + wn * 128 + j * 32 + l32;
-                const float bv = (bias && n < N) ? reinterpret_cast<const float*>(bias)[n] : 0.f;
-#pragma unroll
-                for (int i = 0; i < 4; ++i) {
-                    const long long mbase = m0 + wm * 128 + i * 32;
-#pragma unroll
-                    for (int r = 0; r < 16; ++r) {
-                        const long long m = mbase + acc_row(r, lane);
-                        if (m < M && n < N) {
-                            const long long orow = oidx ? (long long)oidx[m] : m;
-                            if (orow >= 0 && orow < out_rows) {
-                                float* dst = reinterpret_cast<float*>(Y) + orow * ldy + n;
-                                *dst = *dst + (acc[i][j][r] + bv);
-                            }
-                        }
-                    }
-                }
-            }
+        for (int j = 0; j < 4; ++j) {
+            const int n = n0 + wn * 128 + j * 32 + l32;
+            bv[j] = (bias && n < N) ? bf16_to_f32(reinterpret_cast<const uint16_t*>(bias)[n]) : 0.f;
         }
+        // Byte offset in R of this lane's piece of row (ih*64 + rr*4 + rsub), or NONE if it is not to be written.
+        // All 32 row indices are fetched in one batch, and the residual is read through a range-checked buffer
+        // descriptor (a NONE offset lies past its end and reads as zero), so nothing here branches or waits
+        // between the loads.
+        const unsigned NONE = r_bytes;
+        const int ldy_bytes = (int)ldy * 2;
+        const __amdgpu_buffer_rsrc_t r_rsrc = __builtin_amdgcn_make_buffer_rsrc(reinterpret_cast<char*>(Y), 0, (int)r_bytes, 0x00020000);
+        int orow[2][16];
+#pragma unroll
+        for (int ih = 0; ih < 2; ++ih)
+#pragma unroll
+            for (int rr = 0; rr < 16; ++rr) {
+                const long long m = min(m0 + wm * 128 + ih * 64 + rr * 4 + rsub, M - 1);
+                orow[ih][rr] = oidx ? oidx[m] : (int)m;
+            }
+        unsigned roff[2][16];
+#pragma unroll
+        for (int ih = 0; ih < 2; ++ih)
+#pragma unroll
+            for (int rr = 0; rr < 16; ++rr) {
+                const long long m = m0 + wm * 128 + ih * 64 + rr * 4 + rsub;
+                const bool ok = (m < M) & (ncol < N) & (orow[ih][rr] >= 0) & (orow[ih][rr] < out_rows);  // no short circuit: no branches
+                roff[ih][rr] = ok ? (unsigned)orow[ih][rr] * (unsigned)ldy_bytes + (unsigned)ncol * 2u : NONE;
+            }
+        auto prefetch = [&](int ih, u32x4 (&old)[16]) {
+#pragma unroll
+            for (int rr = 0; rr < 16; ++rr)
+                old[rr] = __builtin_amdgcn_raw_buffer_load_b128(r_rsrc, (int)(col_vec ? roff[ih][rr] : NONE), 0, 0);
+        };
+        auto stage = [&](int ih) {
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                char* colp = region + (4 * half) * EPF + (j * 32 + l32) * 4;
+#pragma unroll
+                for (int ii = 0; ii < 2; ++ii)
+#pragma unroll
+                    for (int r = 0; r < 16; ++r)
+                        *reinterpret_cast<float*>(colp + (ii * 32 + 8 * (r >> 2) + (r & 3)) * EPF) = acc[ih * 2 + ii][j][r] + bv[j];
+            }
+        };
+        auto consume = [&](int ih, const u32x4 (&old)[16]) {
+#pragma unroll
+            for (int rr = 0; rr < 16; ++rr) {
+                const int row = rr * 4 + rsub;
+                const f32x4 lo = *reinterpret_cast<const f32x4*>(region + row * EPF + piece * 32);
+                const f32x4 hi = *reinterpret_cast<const f32x4*>(region + row * EPF + piece * 32 + 16);
+                if (roff[ih][rr] == NONE) continue;
+                uint16_t* dst = reinterpret_cast<uint16_t*>(reinterpret_cast<char*>(Y) + roff[ih][rr]);
+                const float v[8] = {lo[0], lo[1], lo[2], lo[3], hi[0], hi[1], hi[2], hi[3]};
+                if (col_vec) {
+                    u32x4 out;
+#pragma unroll
+                    for (int e = 0; e < 4; ++e)
+                        out[e] = pack_bf16x2_hw(v[2 * e] + __uint_as_float(old[rr][e] << 16),
+                                                v[2 * e + 1] + __uint_as_float(old[rr][e] & 0xffff0000u));
+                    *reinterpret_cast<u32x4*>(dst) = out;
+                } else {  // ragged right edge or unaligned rows: element by element
+#pragma unroll
+                    for (int e = 0; e < 8; ++e)
+                        if (ncol + e < N) dst[e] = (uint16_t)(pack_bf16x2_hw(v[e] + bf16_to_f32(dst[e]), 0.f) & 0xffffu);
+                }
+            }
+        };
+        u32x4 old0[16], old1[16];
+        prefetch(0, old0);
+        stage(0);
+        prefetch(1, old1);
+        consume(0, old0);
+        stage(1);
+        consume(1, old1);
     };
 
     // epilogue: acc[i][j][r] is Y[m0 + wm*128 + i*32 + acc_row(r), n0 + wn*128 + j*32 + l32]
     if constexpr (ADD) {
         add_epilogue();
-    } else if constexpr (sizeof(T) == 2) {
-        // bf16: a lane holds ONE column of 16 rows, so storing from the accumulators would write 2-4 bytes per
+    } else {
+        // A lane holds ONE column of 16 rows, so storing from the accumulators would write 2-4 bytes per
         // lane into many rows.  Each wave instead lays its 128 x 128 block out in LDS (its own region; the
         // main loop's stages are dead after the last barrier) and writes whole 256-byte row segments.
         constexpr int EP = 128 * 2 + 16;  // LDS pitch of one staged row
@@ -495,58 +448,130 @@ __global__ __launch_bounds__(GG_THREADS, 1) void gather_gemm_kernel(const T* __r
                 }
             }
         }
-    } else {
-#pragma unroll
-        for (int j = 0; j < 4; ++j) {
-            const int n = n0 + wn * 128 + j * 32 + l32;
-            const float bv = (bias && n < N) ? reinterpret_cast<const float*>(bias)[n] : 0.f;
-#pragma unroll
-            for (int i = 0; i < 4; ++i) {
-                const long long mbase = m0 + wm * 128 + i * 32;
-#pragma unroll
-                for (int r = 0; r < 16; ++r) {
-                    const long long m = mbase + acc_row(r, lane);
-                    if (m < M && n < N) reinterpret_cast<float*>(Y)[m * ldy + n] = acc[i][j][r] + bv;
-                }
-            }
-        }
     }
 }
 
-template <typename T, bool ADD, int LAYOUT = GG_NT>
-static int launch_gg_t(const void* X, long long S, long long ldx, const int* idx, long long M, const void* W, long long ldw,
-                       const void* bias, void* Y, long long ldy, int C, int N, const int* oidx, long long out_rows, hipStream_t st,
-                       unsigned w_bytes_all = 0) {
-    const unsigned x_bytes = (unsigned)(((S - 1) * ldx + (LAYOUT == GG_TN ? M : (long long)C)) * (long long)sizeof(T));  // host checked: fits 32 bits
-    const unsigned r_bytes = ADD ? (unsigned)(((out_rows - 1) * ldy + N) * (long long)sizeof(T)) : 0u;  // likewise
+template <bool ADD, int LAYOUT>
+static int launch_t256(const GgParams& p, hipStream_t st) {
     static std::once_flag once;
     static hipError_t attr_err = hipSuccess;
     std::call_once(once, [] {
-        attr_err = hipFuncSetAttribute(reinterpret_cast<const void*>(&gather_gemm_kernel<T, ADD, LAYOUT>),
+        attr_err = hipFuncSetAttribute(reinterpret_cast<const void*>(&gather_gemm_kernel<bf16_t, ADD, LAYOUT>),
                                        hipFuncAttributeMaxDynamicSharedMemorySize, GG_LDS);
     });
     if (attr_err != hipSuccess) return (int)attr_err;
-    const int tiles_m = (int)((M + GG_BM - 1) / GG_BM), tiles_n = (N + GG_BN - 1) / GG_BN;
+    const int tiles_m = (int)((p.M + GG_BM - 1) / GG_BM), tiles_n = (p.N + GG_BN - 1) / GG_BN;
     const int per_xcd = (tiles_m * tiles_n + NUM_XCD - 1) / NUM_XCD;
-    hipLaunchKernelGGL((gather_gemm_kernel<T, ADD, LAYOUT>), dim3((unsigned)(per_xcd * NUM_XCD)), dim3(GG_THREADS), GG_LDS, st,
-                       static_cast<const T*>(X), ldx, idx, M, static_cast<const T*>(W), ldw, static_cast<const T*>(bias),
-                       static_cast<T*>(Y), ldy, C, N, tiles_m, tiles_n, x_bytes, oidx, out_rows, r_bytes, w_bytes_all);
+    hipLaunchKernelGGL((gather_gemm_kernel<bf16_t, ADD, LAYOUT>), dim3((unsigned)(per_xcd * NUM_XCD)), dim3(GG_THREADS), GG_LDS, st,
+                       static_cast<const bf16_t*>(p.A), p.lda, p.idx, p.M, static_cast<const bf16_t*>(p.B), p.ldb,
+                       static_cast<const bf16_t*>(p.bias), static_cast<bf16_t*>(p.Y), p.ldy, p.K, p.N, tiles_m, tiles_n, p.a_bytes, p.oidx,
+                       p.out_rows, p.y_bytes, p.b_bytes);
     return (int)hipGetLastError();
+}
+
+// Which tiles a product is cut into: the first `cols256` columns into 256 x 256 tiles, the others into `rest` tiles.
+//
+// The large tile is the fastest per flop but comes in rounds of 256, one per CU, and a round lasts as long for one tile
+// as for (nearly) all: with few tiles, or just past a full round, smaller ones win although they move more bytes per
+// flop.  The choice is the least of these times, in us, for a contraction of k slabs of 128 bytes; the constants are
+// fits to M = 64 ... 9856, N = 256 ... 14336, K = 256 ... 11008 (within a fifth of what was measured):
+//   256 x 256  6 + k (1.5 per full round + 1.5 for a last one over half full, 1.15 otherwise)
+//   128 x 128  4 + (k + 3) (0.6 up to 256 tiles -- one per CU --, then n/512 + 0.25, at least 0.95)
+//   64 x 64    4 + (2 + 0.25 k) per 256 tiles
+//   256 x 256 for the columns that fill whole rounds, 128 x 128 for the rest: the sum (the launches follow each other)
+// e.g. M = 256, N = K = 4096: 80 / 32 / 17.5 us; M = 256, N = 11008, K = 4096: 82 / 45 / 58; M = 1500, N = K = 4096: 85 /
+// 59 / 97; M = 3280, N = 11008, K = 4096: 282 / 292 / 565, and 9856 rows of it 705 / 815 / 1610.
+// Weight gradients (GG_TN): both operands pass the transposing read, which the 128 x 128 tile pays twice as often; it
+// takes over where the large tiles leave half the CUs idle (N = 4096, C = 1024, 700 tokens: 28 / 14.5 us; N = 11008, C =
+// 4096, 9856 tokens: 862 / 1317).
+// binary32: the products are bound by MFMA issue at any tile size, so only the fill counts and the 256 x 256 tile has
+// nothing to offer (M = 1500, N = 11008, K = 4096: 1852 / 1187 / 1147 us; M = 2000, N = 3072, K = 768: 203 / 97 / 103).
+struct GgPlan { int cols256; GgTile rest; };
+static GgPlan gg_plan(long long M, int N, int K, int layout, lemo_dtype_t dt) {
+    auto tiles = [&](int b, int n) { return (double)((M + b - 1) / b) * (double)((n + b - 1) / b); };
+    const double n256 = tiles(256, N), n128 = tiles(128, N), n64 = tiles(64, N);
+    if (dt == LEMO_F32) return {0, n128 <= 192 ? GG_T64 : GG_T128};
+    const double k = K / 64.;
+    auto t256 = [&](double n) {
+        const double full = (double)(long long)(n / 256), rem = n - 256 * full;
+        return 6 + k * (1.5 * full + (rem == 0 ? 0. : rem <= 128 ? 1.15 : 1.5));
+    };
+    auto t128 = [&](double n) { return 4 + (k + 3) * (n <= 256 ? 0.6 : n / 512 + 0.25 > 0.95 ? n / 512 + 0.25 : 0.95); };
+    auto t64 = [&](double n) { return 4 + (2 + 0.25 * k) * (double)((long long)(n + 255) / 256); };
+    if (layout == GG_TN) {
+        if (n256 > 128) return {N, GG_T128};
+        return {0, t64(n64) < t128(n128) ? GG_T64 : GG_T128};
+    }
+    GgPlan best{N, GG_T128};
+    double t = t256(n256);
+    const long long tm = (M + 255) / 256, rounds = (long long)n256 / 256;
+    const long long cols = rounds * 256 / tm * 256;  // columns whose tiles fit whole rounds
+    if (rounds > 0 && cols > 0 && cols < N) {
+        const double mixed = t256((double)tm * (double)(cols / 256)) + t128(tiles(128, N - (int)cols));
+        if (mixed < t) { t = mixed; best = {(int)cols, GG_T128}; }
+    }
+    if (t128(n128) < t) { t = t128(n128); best = {0, GG_T128}; }
+    if (t64(n64) < t) best = {0, GG_T64};
+    return best;
+}
+
+template <bool ADD, int LAYOUT>
+static int launch_gg(const GgParams& p, lemo_dtype_t dt, hipStream_t st) {
+    constexpr long long ROWS = 1ll << 24;  // a launch holds 2^32 threads: more rows than this are taken in turns
+    if (LAYOUT != GG_TN && p.M > ROWS) {
+        const int esz = dt == LEMO_BF16 ? 2 : 4;
+        for (long long m = 0; m < p.M; m += ROWS) {
+            GgParams part = p;
+            part.M = p.M - m < ROWS ? p.M - m : ROWS;
+            if (p.idx) part.idx = p.idx + m;
+            else { part.A = static_cast<const char*>(p.A) + m * p.lda * esz; part.a_bytes -= (unsigned)(m * p.lda * esz); }
+            if (ADD && p.oidx) {
+                part.oidx = p.oidx + m;
+            } else {
+                part.Y = static_cast<char*>(p.Y) + m * p.ldy * esz;
+                if (ADD) { part.out_rows -= m; part.y_bytes -= (unsigned)(m * p.ldy * esz); }
+            }
+            const int rc = launch_gg<ADD, LAYOUT>(part, dt, st);
+            if (rc) return rc;
+        }
+        return 0;
+    }
+    const GgPlan plan = gg_plan(p.M, p.N, p.K, LAYOUT, dt);
+    if (plan.cols256 >= p.N) return launch_t256<ADD, LAYOUT>(p, st);
+    GgParams rest = p;
+    if (plan.cols256 > 0) {
+        GgParams head = p;
+        head.N = plan.cols256;
+        const int rc = launch_t256<ADD, LAYOUT>(head, st);
+        if (rc) return rc;
+        // the same product on the columns behind: bases move by cols256 columns, the output's span shrinks by as much
+        // (bf16, and not GG_TN, whose b_bytes would move as well)
+        const long long c = plan.cols256;
+        rest.N -= plan.cols256;
+        rest.B = static_cast<const bf16_t*>(p.B) + (LAYOUT == GG_NT ? c * p.ldb : c);
+        rest.Y = static_cast<bf16_t*>(p.Y) + c;
+        if (p.bias) rest.bias = static_cast<const bf16_t*>(p.bias) + c;
+        if (ADD) rest.y_bytes -= (unsigned)c * 2u;
+    }
+    return launch_gather_gemm_small(rest, dt, ADD, LAYOUT, plan.rest, st);
+}
+
+static unsigned span_bytes(long long rows, long long ld, long long cols, lemo_dtype_t dt) {  // host checked: fits 32 bits
+    return (unsigned)(((rows - 1) * ld + cols) * (dt == LEMO_BF16 ? 2 : 4));
 }
 
 int launch_gather_gemm(const void* X, long long S, long long ldx, const int* idx, long long M, const void* W, long long ldw,
                        const void* bias, void* Y, long long ldy, int C, int N, lemo_dtype_t dt, hipStream_t st) {
     if (M == 0) return 0;
-    if (dt == LEMO_BF16) return launch_gg_t<bf16_t, false>(X, S, ldx, idx, M, W, ldw, bias, Y, ldy, C, N, nullptr, 0, st);
-    return launch_gg_t<float, false>(X, S, ldx, idx, M, W, ldw, bias, Y, ldy, C, N, nullptr, 0, st);
+    return launch_gg<false, GG_NT>({X, W, bias, Y, idx, nullptr, ldx, ldw, ldy, M, 0, C, N, 0, 0, span_bytes(S, ldx, C, dt), 0, 0}, dt, st);
 }
 
 int launch_gather_gemm_add(const void* X, long long S, long long ldx, const int* idx, long long M, const void* W, long long ldw,
                            const void* bias, void* R, long long ldr, long long out_rows, const int* oidx, int C, int N,
                            lemo_dtype_t dt, hipStream_t st) {
     if (M == 0) return 0;
-    if (dt == LEMO_BF16) return launch_gg_t<bf16_t, true>(X, S, ldx, idx, M, W, ldw, bias, R, ldr, C, N, oidx, out_rows, st);
-    return launch_gg_t<float, true>(X, S, ldx, idx, M, W, ldw, bias, R, ldr, C, N, oidx, out_rows, st);
+    return launch_gg<true, GG_NT>({X, W, bias, R, idx, oidx, ldx, ldw, ldr, M, out_rows, C, N, 0, 0, span_bytes(S, ldx, C, dt), 0,
+                                   span_bytes(out_rows, ldr, N, dt)}, dt, st);
 }
 
 // Input gradient of Y = X[idx] W^T:  dX[oidx[m], c] += sum_n dY[m, n] W[n, c], W as stored ([N, C], contraction-major
@@ -554,16 +579,16 @@ int launch_gather_gemm_add(const void* X, long long S, long long ldx, const int*
 int launch_gather_gemm_dx(const void* dY, long long ldy, long long M, const void* W, long long ldw, void* dX, long long lddx, long long out_rows,
                           const int* oidx, int C, int N, hipStream_t st) {
     if (M == 0) return 0;
-    return launch_gg_t<bf16_t, true, GG_NN>(dY, M, ldy, nullptr, M, W, ldw, nullptr, dX, lddx, /*contraction*/ N, /*columns*/ C, oidx, out_rows, st);
+    return launch_gg<true, GG_NN>({dY, W, nullptr, dX, nullptr, oidx, ldy, ldw, lddx, M, out_rows, /*contraction*/ N, /*columns*/ C, 0, 0,
+                                   span_bytes(M, ldy, N, LEMO_BF16), 0, span_bytes(out_rows, lddx, C, LEMO_BF16)}, LEMO_BF16, st);
 }
 
 // Weight gradient dW[n, c] = sum_m dY[m, n] X[idx[m], c], both operands read as they are stored (contraction-major),
 // the kept rows of X picked inside the B-tile load.  bf16.
 int launch_gather_gemm_dw_direct(const void* dY, long long ldy, const void* X, long long S, long long ldx, const int* idx, long long M, void* dW,
                                  long long lddw, int C, int N, hipStream_t st) {
-    const unsigned x_span = (unsigned)(((S - 1) * ldx + C) * 2);  // host checked: fits 32 bits
-    return launch_gg_t<bf16_t, false, GG_TN>(dY, M, ldy, idx, /*output rows*/ N, X, ldx, nullptr, dW, lddw, /*contraction*/ (int)M, /*columns*/ C, nullptr, 0, st,
-                                             x_span);
+    return launch_gg<false, GG_TN>({dY, X, nullptr, dW, idx, nullptr, ldy, ldx, lddw, /*output rows*/ N, 0, /*contraction*/ (int)M, /*columns*/ C, 0, 0,
+                                    span_bytes(M, ldy, N, LEMO_BF16), span_bytes(S, ldx, C, LEMO_BF16), 0}, LEMO_BF16, st);
 }
 
 }  // namespace lemo

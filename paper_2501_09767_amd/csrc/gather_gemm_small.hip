@@ -1,0 +1,388 @@
+// The selective-load GEMM (and its in-place-add and gradient forms, see gather_gemm.hip) on smaller output tiles, for
+// products whose 256 x 256 tiles do not fill the chip's 256 CUs or leave a nearly empty last round.
+//
+// One wave always computes a 64 x 64 block (2 x 2 MFMA tiles) from slabs of 128 bytes of the contraction; two shapes:
+//   GW = 4  the four waves of a workgroup share a slab: 128 x 128 output tile, two workgroups per CU (70 KB of LDS each).
+//           Bound by LDS: 32 KB written and 64 KB read per slab are 768 of its cycles against 512 of MFMAs.
+//   GW = 1  every wave has its own slabs: 64 x 64 output tile, the four waves take every fourth slab of the contraction
+//           each and their partial tiles are added, in wave order, through LDS at the end.  No barrier in the main loop.
+//           Bound by the latency of the loads: 128 KB per CU are in flight, all its LDS holds.
+// Slabs arrive by LDS-direct loads, two per group in flight, and the registers are the third buffer: the MFMA fragments
+// of the next slab are read during the first MFMAs of the current one, which frees its LDS stage for the slab after next.
+// Measured beside this (M = 256, N = K = 4096 with 64 x 64 tiles: 17.5 us; M = 9856, N = 11008, K = 4096 with 128 x 128
+// tiles: 815 us): a ring of four half-slabs with the loads spread over all MFMAs 21.6 / 1033 us (64-byte row segments
+// halve what an L2 delivers), a ring of two slabs without the registers' lookahead 19.1 / 863 us, the contraction of a
+// 128 x 128 tile split over two groups of four waves no faster than one group (LDS is what it waits for).
+#include <mutex>
+
+#include "gather_gemm.hpp"
+
+namespace lemo {
+
+constexpr int SG_THREADS = 256;
+constexpr int SG_KB = 128;          // bytes of the contraction per slab
+constexpr int SG_EP = 64 * 4 + 16;  // LDS pitch of a row of 64 floats in the epilogue
+
+template <int GW> struct SgGeo {
+    static constexpr int W = GW == 4 ? 2 : 1;       // waves of a group per output direction
+    static constexpr int BM = 64 * W, BN = 64 * W;  // output tile
+    static constexpr int GROUPS = 4 / GW;           // the slabs are dealt out to the groups in turn
+    static constexpr int OPER = 64 * W * SG_KB;     // bytes of one operand's slab
+    static constexpr int STAGE = 2 * OPER;
+    static constexpr int NLD = OPER / (GW * 1024);  // LDS-direct loads per thread, operand and slab
+    static constexpr int TOK = GROUPS * 2 * STAGE;  // (GG_TN) token rings: per wave 4 slabs of 64 indices
+    static constexpr int EPI = 4 * 64 * SG_EP;      // epilogue: a 64 x 64 block of floats per wave
+    static constexpr int LDS = TOK + 4096 > EPI ? TOK + 4096 : EPI;
+    static constexpr int PIECES = 64 * W / 8;       // contraction-major slab: 16-byte pieces per row
+    // position of 16-byte piece p of row r (the loads fill consecutive LDS bytes, so conflicts are avoided by exchanging
+    // pieces inside a row).  Rows along the contraction, 128 bytes: p ^ (r / 2 % 8) spreads one piece of 16 rows over all
+    // banks.  Contraction-major rows: the transposing read takes 4 rows x 4 pieces at a time.
+    __device__ static constexpr int swz(int r) { return (r >> 1) & 7; }
+    __device__ static constexpr int kswz(int r) { return GW == 4 ? (r & 3) << 2 : ((r >> 1) & 1) << 2; }
+};
+
+template <typename T, bool ADD, int LAYOUT, int GW>
+__global__ __launch_bounds__(SG_THREADS, GW == 4 ? 2 : 1) void gather_gemm_small_kernel(GgParams p) {
+    static_assert(LAYOUT == GG_NT || sizeof(T) == 2, "the contraction-major layouts are built for 16-bit elements");
+    constexpr bool A_KMAJOR = LAYOUT == GG_TN, B_KMAJOR = LAYOUT != GG_NT;
+    using G = SgGeo<GW>;
+    constexpr int GROUPS = G::GROUPS, NLD = G::NLD, ESZ = (int)sizeof(T);
+    extern __shared__ __attribute__((aligned(16))) char smem[];
+
+    int tm, tn;
+    if (!gg_tile(blockIdx.x, p.tiles_m, p.tiles_n, 8, tm, tn)) return;
+    const long long m0 = (long long)tm * G::BM;
+    const int n0 = tn * G::BN;
+    const int tid = threadIdx.x, lane = tid & 63, half = lane >> 5, l32 = lane & 31;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int group = wave / GW, wg = wave % GW, gtid = tid % (64 * GW);
+    const int wm = wg >> 1, wn = wg & 1;
+    const T* A = static_cast<const T*>(p.A);
+    const T* B = static_cast<const T*>(p.B);
+    const unsigned lda_bytes = (unsigned)p.lda * ESZ, ldb_bytes = (unsigned)p.ldb * ESZ;  // host: both < 2^23
+    const int K = p.K, kbytes = K * ESZ;  // (along-the-contraction operands: bytes of a row)
+    const int nk = A_KMAJOR ? (K + 63) / 64 : (kbytes + SG_KB - 1) / SG_KB;
+
+    // Per-thread byte offsets of the loads.  The hardware range check sees the per-thread offset only: rows past an
+    // operand's end fail it (or are clamped to the last one, A), pieces past the end of the contraction are given an
+    // offset at the descriptor's size in both operands and arrive as zeros; the scalar offset moves along a row.
+    auto kpos = [&](int i) { return ((gtid & 7) ^ G::swz(i * 8 * GW + (gtid >> 3))) * 16; };  // of piece i in a row's slab
+    unsigned a_voff[NLD], b_voff[NLD];
+#pragma unroll
+    for (int i = 0; i < NLD; ++i) {
+        const int u = i * 64 * GW + gtid, krow = u / G::PIECES, kcol = ((u % G::PIECES) ^ G::kswz(krow)) * 16;
+        if constexpr (A_KMAJOR) {
+            a_voff[i] = krow * lda_bytes + kcol;
+        } else {
+            const long long m = min(m0 + u / 8, p.M - 1);
+            const unsigned row = p.idx ? (unsigned)p.idx[m] : (unsigned)m;
+            a_voff[i] = row * lda_bytes + kpos(i);  // host: the operand spans < 2^32 bytes
+        }
+        if constexpr (LAYOUT == GG_NT) b_voff[i] = (u / 8) * ldb_bytes + kpos(i);
+        else if constexpr (LAYOUT == GG_NN) b_voff[i] = krow * ldb_bytes + kcol;
+        else b_voff[i] = (unsigned)n0 * 2u + kcol;  // + the token's row, per slab
+    }
+    const int b_rows = min(G::BN, p.N - n0);
+    const unsigned bn_bytes = (b_rows - 1) * ldb_bytes + kbytes;  // (GG_NT) this tile's rows of B
+    // contraction-major operand: from the slab's first row (and the tile's first column) to the operand's end, which
+    // refuses the rows past it (host: the operand spans < 2^31 bytes)
+    auto kmajor_rsrc = [&](const T* col0, unsigned ld_bytes, unsigned cols, int kt) {
+        const bool live = kt < nk;
+        const unsigned off = live ? (unsigned)kt * 64u * ld_bytes : 0u;
+        const unsigned size = live ? (unsigned)(K - 1) * ld_bytes + cols * ESZ - off : 0u;
+        return raw_rsrc(reinterpret_cast<const char*>(col0) + off, size);
+    };
+    const unsigned lds_g = lds_offset_of(smem) + group * 2 * G::STAGE + wg * 1024;
+    const unsigned lds_tok = lds_offset_of(smem) + G::TOK + wave * 1024;
+    const u32x4 idx_rsrc = raw_rsrc(p.idx, p.idx ? (long long)K * 4 : 0);
+    auto issue_tokens = [&](int it) {  // indices of the group's slab `it` into its ring entry
+        if constexpr (LAYOUT == GG_TN) lds_direct_b32(idx_rsrc, lds_tok + (it & 3) * 256, (it * GROUPS + group) * 256 + lane * 4);
+    };
+    // one of the 2 * NLD loads of the group's slab `it`: A pieces first, then B pieces
+    struct Slab { u32x4 a, b; int soff, left; unsigned a_none, b_none, stage; };
+    auto slab_of = [&](int it) {
+        const int kt = it * GROUPS + group;
+        Slab s;
+        const bool live = kt < nk;
+        s.soff = live ? kt * SG_KB : 0;
+        s.left = kbytes - s.soff;
+        s.stage = lds_g + (it & 1) * G::STAGE;
+        s.a_none = live ? p.a_bytes : 0u;
+        s.b_none = !live ? 0u : LAYOUT == GG_NT ? bn_bytes : p.b_bytes;
+        s.a = A_KMAJOR ? kmajor_rsrc(A + m0, lda_bytes, (unsigned)(p.M - m0), kt) : raw_rsrc(A, s.a_none);
+        s.b = LAYOUT == GG_NN ? kmajor_rsrc(B + n0, ldb_bytes, (unsigned)(p.N - n0), kt) : raw_rsrc(LAYOUT == GG_NT ? B + (long long)n0 * p.ldb : B, s.b_none);
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {  // uniform values; the assembly wants them in scalar registers
+            s.a[e] = __builtin_amdgcn_readfirstlane(s.a[e]);
+            s.b[e] = __builtin_amdgcn_readfirstlane(s.b[e]);
+        }
+        s.soff = __builtin_amdgcn_readfirstlane(s.soff);
+        s.stage = __builtin_amdgcn_readfirstlane(s.stage);
+        return s;
+    };
+    auto load_a = [&](const Slab& s, int i) {
+        if constexpr (A_KMAJOR) lds_direct_b128(s.a, s.stage + i * GW * 1024, (int)a_voff[i]);
+        else lds_direct_b128(s.a, s.stage + i * GW * 1024, (int)(kpos(i) < s.left ? a_voff[i] : s.a_none), s.soff);
+    };
+    unsigned tok[LAYOUT == GG_TN ? NLD : 1];
+    auto read_tokens = [&](int it) {  // the rows of B of slab `it`: their byte offsets, past the end for tokens past the end
+        if constexpr (LAYOUT == GG_TN) {
+#pragma unroll
+            for (int i = 0; i < NLD; ++i) {
+                const int krow = (i * 64 * GW + gtid) / G::PIECES, k = (it * GROUPS + group) * 64 + krow;
+                const unsigned row = p.idx ? *reinterpret_cast<const unsigned*>(smem + G::TOK + wave * 1024 + (it & 3) * 256 + krow * 4) : (unsigned)k;
+                tok[i] = k < K ? row * ldb_bytes + b_voff[i] : p.b_bytes;
+            }
+        }
+    };
+    auto load_b = [&](const Slab& s, int i) {
+        if constexpr (LAYOUT == GG_TN) lds_direct_b128(s.b, s.stage + G::OPER + i * GW * 1024, (int)tok[i]);
+        else if constexpr (LAYOUT == GG_NN) lds_direct_b128(s.b, s.stage + G::OPER + i * GW * 1024, (int)b_voff[i]);
+        else lds_direct_b128(s.b, s.stage + G::OPER + i * GW * 1024, (int)(kpos(i) < s.left ? b_voff[i] : s.b_none), s.soff);
+    };
+    constexpr int BATCH = 2 * NLD + (LAYOUT == GG_TN ? 1 : 0);  // vector-memory operations per slab
+    // after a wait: every wave of the group has come this far, and no access to LDS moves across
+    auto group_barrier = [&]() {
+        asm volatile("" ::: "memory");
+        __builtin_amdgcn_sched_barrier(0);
+        if constexpr (GW == 4) __builtin_amdgcn_s_barrier();
+        asm volatile("" ::: "memory");
+        __builtin_amdgcn_sched_barrier(0);
+    };
+
+    // fragment (32-row subtile i of the wave's 64 rows, chunk c of the slab) of an operand
+    const int trow = 8 * half + ((l32 & 15) >> 2);
+    auto frag = [&](const char* region, bool kmajor, int w, int i, int c) {
+        if (!kmajor) {
+            const int row = w * 64 + i * 32 + l32;
+            return *reinterpret_cast<const u32x4*>(region + row * SG_KB + (((2 * c + half) ^ G::swz(row)) << 4));
+        }
+        const int piece = (w * 8 + i * 4 + (l32 >> 4) * 2 + ((l32 & 3) >> 1)) ^ G::kswz(trow);
+        const char* at = region + (trow + c * 16) * (G::PIECES * 16) + piece * 16 + (l32 & 1) * 8;
+        const s16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((s16x4 __attribute__((address_space(3)))*)(at));
+        const s16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((s16x4 __attribute__((address_space(3)))*)(at + 4 * G::PIECES * 16));
+        const uint2 l2 = __builtin_bit_cast(uint2, lo), h2 = __builtin_bit_cast(uint2, hi);
+        return u32x4{l2.x, l2.y, h2.x, h2.y};
+    };
+    char* const stages = smem + group * 2 * G::STAGE;
+    auto a_frag = [&](int st, int i, int c) { return frag(stages + st * G::STAGE, A_KMAJOR, wm, i, c); };
+    auto b_frag = [&](int st, int i, int c) { return frag(stages + st * G::STAGE + G::OPER, B_KMAJOR, wn, i, c); };
+
+    f32x16 acc[2][2];
+#pragma unroll
+    for (int i = 0; i < 2; ++i)
+#pragma unroll
+        for (int j = 0; j < 2; ++j) acc[i][j] = f32x16{0};
+    u32x4 fa[2][4][2], fb[2][4][2];  // fragments of two slabs
+
+    const int nit = (nk + GROUPS - 1) / GROUPS;  // slabs per group; the last may lie past the end (zeros)
+    issue_tokens(0);
+    issue_tokens(1);
+    if constexpr (LAYOUT == GG_TN) {  // (the ring is the wave's own)
+        __builtin_amdgcn_s_waitcnt(vmcnt_imm(0));
+        asm volatile("" ::: "memory");
+    }
+#pragma unroll
+    for (int it = 0; it < 2; ++it) {
+        const Slab s = slab_of(it);
+        read_tokens(it);
+#pragma unroll
+        for (int i = 0; i < NLD; ++i) load_a(s, i);
+#pragma unroll
+        for (int i = 0; i < NLD; ++i) load_b(s, i);
+        issue_tokens(it + 2);
+    }
+    __builtin_amdgcn_s_waitcnt(vmcnt_imm(BATCH));  // slab 0 (and the indices of slab 2)
+    group_barrier();
+#pragma unroll
+    for (int c = 0; c < 4; ++c)
+#pragma unroll
+        for (int i = 0; i < 2; ++i) {
+            fa[0][c][i] = a_frag(0, i, c);
+            fb[0][c][i] = b_frag(0, i, c);
+        }
+    __builtin_amdgcn_s_waitcnt(LGKMCNT0);
+    group_barrier();
+    {
+        const Slab s = slab_of(2);
+        read_tokens(2);
+#pragma unroll
+        for (int i = 0; i < NLD; ++i) load_a(s, i);
+#pragma unroll
+        for (int i = 0; i < NLD; ++i) load_b(s, i);
+        issue_tokens(4);
+    }
+    // Slab `it` of the group (it & 1 == PAR), its fragments in set PAR; slab it+1 has been asked for into stage PAR^1,
+    // slab it+2 into stage PAR.  First half of the MFMAs: read slab it+1's fragments; then, every wave of the group
+    // having read them, the second half: ask for slab it+3 into the same stage.
+    auto step = [&](int it, auto par_tag) {
+        constexpr int PAR = decltype(par_tag)::value, NXT = PAR ^ 1;
+        __builtin_amdgcn_s_waitcnt(vmcnt_imm(BATCH));
+        group_barrier();
+        const Slab s = slab_of(it + 3);
+#pragma unroll
+        for (int q = 0; q < 16; ++q) {  // MFMA q of the slab: chunk q / 4
+            const int c = q >> 2, i = (q >> 1) & 1, j = q & 1;
+            __builtin_amdgcn_sched_barrier(0);
+            mma_chunk<T>(acc[i][j], fa[PAR][c][i], fb[PAR][c][j]);
+            if (q < 8) {
+                const int cc = q >> 1, ii = q & 1;
+                fa[NXT][cc][ii] = a_frag(NXT, ii, cc);
+                fb[NXT][cc][ii] = b_frag(NXT, ii, cc);
+            }
+            if (q == 8) {
+                read_tokens(it + 3);
+                __builtin_amdgcn_s_waitcnt(LGKMCNT0);
+                group_barrier();
+            }
+            if (q >= 8) {
+#pragma unroll
+                for (int k = (q - 8) * 2 * NLD / 8; k < (q - 7) * 2 * NLD / 8; ++k) {
+                    if (k < NLD) load_a(s, k);
+                    else load_b(s, k - NLD);
+                }
+                if (q == 15) issue_tokens(it + 5);
+            }
+        }
+        __builtin_amdgcn_sched_barrier(0);
+    };
+    using I0 = std::integral_constant<int, 0>;
+    using I1 = std::integral_constant<int, 1>;
+    int it = 0;
+    for (; it + 1 < nit; it += 2) {
+        step(it, I0{});
+        step(it + 1, I1{});
+    }
+    if (it < nit) step(it, I0{});
+    __builtin_amdgcn_s_waitcnt(vmcnt_imm(0));  // requests past the end write (zeros) to the stages, too
+    __syncthreads();
+
+    // Epilogue.  Every wave lays its 64 x 64 block out in LDS as binary32; rows are then put together (GW = 1: the four
+    // partial blocks are added in wave order, each wave finishing 16 rows; GW = 4: each wave its own 64 rows), eight
+    // consecutive columns of a row per lane, and stored in whole 16-byte pieces.
+    constexpr int PARTS = GROUPS, PASSES = 64 / PARTS / 8;
+    const int piece = lane & 7, rsub = lane >> 3;
+    const int row0 = group * (64 / PARTS);
+    const int ncol = n0 + wn * 64 + piece * 8;
+    const char* first = smem + wg * 64 * SG_EP;  // + part * GW blocks
+    constexpr int NV = 8 * ESZ / 16;  // 16-byte pieces of a lane's 8 columns
+    const bool vec = p.ldy % (16 / ESZ) == 0 && (reinterpret_cast<uintptr_t>(p.Y) & 15u) == 0 && ncol + 8 <= p.N;
+    float bv[8];
+#pragma unroll
+    for (int e = 0; e < 8; ++e) {
+        bv[e] = 0.f;
+        if (p.bias && ncol + e < p.N) {
+            if constexpr (ESZ == 2) bv[e] = bf16_to_f32(static_cast<const uint16_t*>(p.bias)[ncol + e]);
+            else bv[e] = static_cast<const float*>(p.bias)[ncol + e];
+        }
+    }
+    // output rows (ADD: picked by oidx, dropped outside [0, out_rows)), and what they hold already
+    long long orow[PASSES];
+    u32x4 old[PASSES][NV];
+#pragma unroll
+    for (int q = 0; q < PASSES; ++q) {
+        const long long m = m0 + wm * 64 + row0 + q * 8 + rsub;
+        orow[q] = ADD && p.oidx ? (long long)p.oidx[min(m, p.M - 1)] : m;
+        if (m >= p.M || ncol >= p.N || (ADD && (orow[q] < 0 || orow[q] >= p.out_rows))) orow[q] = -1;
+    }
+    if constexpr (ADD) {
+        const __amdgpu_buffer_rsrc_t y_rsrc = __builtin_amdgcn_make_buffer_rsrc(p.Y, 0, (int)p.y_bytes, 0x00020000);
+#pragma unroll
+        for (int q = 0; q < PASSES; ++q)
+#pragma unroll
+            for (int v = 0; v < NV; ++v) {
+                const unsigned off = vec && orow[q] >= 0 ? (unsigned)orow[q] * (unsigned)p.ldy * ESZ + (unsigned)ncol * ESZ + v * 16 : p.y_bytes;
+                old[q][v] = __builtin_amdgcn_raw_buffer_load_b128(y_rsrc, (int)off, 0, 0);
+            }
+    }
+    char* mine = smem + wave * 64 * SG_EP;
+#pragma unroll
+    for (int i = 0; i < 2; ++i)
+#pragma unroll
+        for (int j = 0; j < 2; ++j)
+#pragma unroll
+            for (int r = 0; r < 16; ++r)
+                *reinterpret_cast<float*>(mine + (i * 32 + acc_row(r, lane)) * SG_EP + (j * 32 + l32) * 4) = acc[i][j][r];
+    if constexpr (PARTS > 1) __syncthreads();  // (one group: a wave reads back its own block only)
+#pragma unroll
+    for (int q = 0; q < PASSES; ++q) {
+        float v[8];
+        const char* at = first + (row0 + q * 8 + rsub) * SG_EP + piece * 32;
+#pragma unroll
+        for (int part = 0; part < PARTS; ++part) {
+            const f32x4 lo = *reinterpret_cast<const f32x4*>(at + part * GW * 64 * SG_EP);
+            const f32x4 hi = *reinterpret_cast<const f32x4*>(at + part * GW * 64 * SG_EP + 16);
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                v[e] = part ? v[e] + lo[e] : lo[e];
+                v[e + 4] = part ? v[e + 4] + hi[e] : hi[e];
+            }
+        }
+        if (orow[q] < 0) continue;
+#pragma unroll
+        for (int e = 0; e < 8; ++e) v[e] += bv[e];
+        T* dst = static_cast<T*>(p.Y) + orow[q] * p.ldy + ncol;
+        if (vec) {
+            if constexpr (ESZ == 2) {
+                u32x4 out;
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    const float o0 = ADD ? bf16lo_to_f32(old[q][0][e]) : 0.f, o1 = ADD ? bf16hi_to_f32(old[q][0][e]) : 0.f;
+                    out[e] = ADD ? pack_bf16x2_hw(v[2 * e] + o0, v[2 * e + 1] + o1) : pack_bf16x2_hw(v[2 * e], v[2 * e + 1]);
+                }
+                *reinterpret_cast<u32x4*>(dst) = out;
+            } else {
+#pragma unroll
+                for (int w = 0; w < 2; ++w) {
+                    f32x4 out;
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) out[e] = ADD ? __uint_as_float(old[q][w % NV][e]) + v[w * 4 + e] : v[w * 4 + e];
+                    *reinterpret_cast<f32x4*>(dst + w * 4) = out;
+                }
+            }
+        } else {  // ragged right edge or unaligned rows: element by element
+#pragma unroll
+            for (int e = 0; e < 8; ++e) {
+                if (ncol + e >= p.N) continue;
+                if constexpr (ESZ == 2) {
+                    uint16_t* d = reinterpret_cast<uint16_t*>(dst) + e;
+                    *d = (uint16_t)(pack_bf16x2_hw(ADD ? v[e] + bf16_to_f32(*d) : v[e], 0.f) & 0xffffu);
+                } else {
+                    float* d = reinterpret_cast<float*>(dst) + e;
+                    *d = ADD ? *d + v[e] : v[e];
+                }
+            }
+        }
+    }
+}
+
+template <typename T, bool ADD, int LAYOUT, int GW>
+static int launch_small(GgParams p, hipStream_t st) {
+    using G = SgGeo<GW>;
+    static std::once_flag once;
+    static hipError_t attr_err = hipSuccess;
+    std::call_once(once, [] {
+        attr_err = hipFuncSetAttribute(reinterpret_cast<const void*>(&gather_gemm_small_kernel<T, ADD, LAYOUT, GW>),
+                                       hipFuncAttributeMaxDynamicSharedMemorySize, G::LDS);
+    });
+    if (attr_err != hipSuccess) return (int)attr_err;
+    p.tiles_m = (int)((p.M + G::BM - 1) / G::BM);
+    p.tiles_n = (p.N + G::BN - 1) / G::BN;
+    const int per_xcd = (p.tiles_m * p.tiles_n + NUM_XCD - 1) / NUM_XCD;
+    hipLaunchKernelGGL((gather_gemm_small_kernel<T, ADD, LAYOUT, GW>), dim3((unsigned)(per_xcd * NUM_XCD)), dim3(SG_THREADS), G::LDS, st, p);
+    return (int)hipGetLastError();
+}
+
+template <int GW>
+static int launch_small_form(const GgParams& p, lemo_dtype_t dt, bool add, int layout, hipStream_t st) {
+    if (dt == LEMO_F32) return add ? launch_small<float, true, GG_NT, GW>(p, st) : launch_small<float, false, GG_NT, GW>(p, st);
+    if (layout == GG_NN) return launch_small<bf16_t, true, GG_NN, GW>(p, st);
+    if (layout == GG_TN) return launch_small<bf16_t, false, GG_TN, GW>(p, st);
+    return add ? launch_small<bf16_t, true, GG_NT, GW>(p, st) : launch_small<bf16_t, false, GG_NT, GW>(p, st);
+}
+
+int launch_gather_gemm_small(const GgParams& p, lemo_dtype_t dt, bool add, int layout, GgTile tile, hipStream_t st) {
+    return tile == GG_T128 ? launch_small_form<4>(p, dt, add, layout, st) : launch_small_form<1>(p, dt, add, layout, st);
+}
+
+}  // namespace lemo

@@ -639,6 +639,62 @@ def test_gather_gemm_add_exact_cases(lemo):
     np.testing.assert_array_equal(wl.to_bf16_bits(same), wl.to_bf16_bits(R0[:, :C].contiguous()))
 
 
+@pytest.mark.parametrize("form,M,N,K,dtype", [
+    # 64 x 64 tiles: one tile and less, remainders, more slabs than a wave's share and fewer
+    ("nt", 1, 1, 8, "bf16"), ("nt", 65, 63, 264, "bf16"), ("add", 64, 129, 1000, "bf16"), ("dx", 70, 72, 200, "bf16"), ("dw", 72, 264, 65, "bf16"),
+    ("nt", 63, 66, 36, "f32"), ("add", 129, 65, 516, "f32"), ("dw", 68, 260, 131, "f32"),
+    # 128 x 128 tiles
+    ("nt", 1000, 1500, 200, "bf16"), ("add", 1023, 1409, 136, "bf16"), ("dx", 1025, 1416, 72, "bf16"), ("dw", 2056, 3080, 300, "bf16"),
+    ("nt", 2049, 1537, 20, "f32"), ("add", 1700, 1931, 132, "f32"),
+    # 256 x 256 tiles, and their whole rounds with 128 x 128 tiles behind them
+    ("nt", 4000, 4090, 520, "bf16"), ("nt", 2817, 5701, 1032, "bf16"), ("add", 2817, 5703, 1096, "bf16"), ("dx", 2817, 5704, 1096, "bf16")])
+def test_gather_gemm_tiles_exact(lemo, form, M, N, K, dtype):
+    """Every tile shape at its edges, in all four forms: small whole numbers, so that every partial sum is exact in
+    binary32 in any order and the result is the exact product rounded once."""
+    say(f"[gemm] tiles {form} M={M} N={N} K={K} {dtype}")
+    dt = torch.bfloat16 if dtype == "bf16" else torch.float32
+    gen = torch.Generator().manual_seed(M + N + K)
+    whole = lambda *s: torch.randint(-3, 4, s, generator=gen).to(dt).cuda()
+    S = M + 37 if form != "dw" else K + 37
+    order = torch.randperm(S, generator=gen)
+    product = lambda a, b: (a.double() @ b.double())  # |entries| < 2^14
+    if form == "dw":  # contraction over K kept tokens
+        idx = order[:K].int().cuda()
+        dY, X = whole(K, M), whole(S, N)
+        got = torch.full((M, N + 3), 9.0, dtype=dt, device="cuda")
+        lemo.lemo_gather_gemm_dw(dY, X, idx, dW=got[:, :N])
+        want = product(dY.t().contiguous(), X[idx.long()])
+    elif form == "nt":
+        idx = order[:M].int().cuda()
+        X, W, b = whole(S, K), whole(N, K), whole(N)
+        got = torch.full((M, N + 3), 9.0, dtype=dt, device="cuda")
+        lemo.lemo_gather_gemm(X, idx, W, b, Y=got[:, :N])
+        want = product(X[idx.long()], W.t().contiguous()) + b.double()
+        aligned = lemo.lemo_gather_gemm(X[idx.long()].contiguous(), None, W, b)  # no list, rows packed: the 16-byte stores where N allows
+        assert torch.equal(aligned, got[:, :N])
+    else:
+        out_idx = order[:M].int().cuda()
+        out_idx[::5] = S + 2  # dropped
+        dY, before = whole(M, K), whole(S, N + 3 if M % 2 else N)
+        got = before.clone()
+        if form == "dx":
+            W = whole(K, N)
+            lemo.lemo_gather_gemm_dx(dY, W, got[:, :N], out_idx)
+            prod = product(dY, W)
+        else:
+            W = whole(N, K)
+            lemo.lemo_gather_gemm_add(dY, None, W, got[:, :N], out_idx)
+            prod = product(dY, W.t().contiguous())
+        want = before[:, :N].double()
+        live = out_idx < S
+        want[out_idx[live].long()] += prod[live]
+        assert torch.equal(got[:, N:], before[:, N:])
+    torch.cuda.synchronize()
+    if form in ("nt", "dw"):
+        assert (got[:, N:] == 9.0).all()
+    assert torch.equal(got[:, :N], want.float().to(dt))
+
+
 def test_gather_gemm_add_as_backward_of_the_selective_load(lemo):
     """Backward of Y = X[idx] W^T with respect to X: dX[idx[m],:] += dY[m,:] W.  With the weight's transpose stored as a
     [C,N] matrix this is the same call (compact rows in, indexed rows out); bit-exact against the oracle on a dyadic grid."""
