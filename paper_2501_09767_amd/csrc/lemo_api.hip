@@ -116,7 +116,6 @@ static int check_qk(const void* Q, const void* K, int64_t S, int32_t H, int32_t 
     p.k_hs = k_hs;
     const double sc = scale > 0.f ? (double)scale : 1.0 / std::sqrt((double)d);
     p.c2 = (float)(sc * 1.4426950408889634);  // log2(e): probabilities are formed with exp2
-    p.L = 1;
     p.flags = flags;
     return LEMO_OK;
 }
@@ -143,7 +142,6 @@ int lemo_score_colsums(const void* Q, const void* K, int64_t S, int32_t H, int32
     if (rc != LEMO_OK) return rc;
     if (!lse2 || !colsum_per_head || !diag_per_head) return LEMO_ERR_NULL;
     if (L <= 0) return LEMO_ERR_SHAPE;
-    p.L = L;
     p.lse2 = const_cast<float*>(lse2);
     p.colsum = colsum_per_head;
     p.diag = diag_per_head;
@@ -158,7 +156,6 @@ int lemo_score_head_mean(const float* colsum_per_head, const float* diag_per_hea
     p.S = (int)S;
     p.H = H;
     p.H_kv = H;
-    p.L = 1;
     p.flags = flags;
     p.colsum = const_cast<float*>(colsum_per_head);
     p.diag = const_cast<float*>(diag_per_head);
@@ -181,7 +178,6 @@ int lemo_score_segments(const void* Q, const void* K, int64_t S, int32_t H, int3
     if (workspace_bytes < need) return LEMO_ERR_WORKSPACE;
     const size_t plane = need / 3;
     char* ws = static_cast<char*>(workspace);
-    p.L = L;
     p.lse2 = reinterpret_cast<float*>(ws);
     p.colsum = colsum_per_head ? colsum_per_head : reinterpret_cast<float*>(ws + plane);
     p.diag = diag_per_head ? diag_per_head : reinterpret_cast<float*>(ws + 2 * plane);
@@ -205,7 +201,6 @@ int lemo_score_segments_static(const void* Q, const void* K, int64_t S, int32_t 
     // for all S queries, column sums and diagonals for all S keys), so nothing has to be cleared between calls.
     const size_t plane = round_up((size_t)H * (size_t)S * sizeof(float), 256);
     char* ws = static_cast<char*>(base);
-    p.L = L;
     p.lse2 = reinterpret_cast<float*>(ws);
     p.colsum = reinterpret_cast<float*>(ws + plane);
     p.diag = reinterpret_cast<float*>(ws + 2 * plane);

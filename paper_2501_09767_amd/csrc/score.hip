@@ -47,10 +47,14 @@ constexpr int SC_THREADS = 64 * SC_WAVES;
 // Measured on the 32K-token bf16 d=128 layer: NRT = 2 4.20 / 4.25 ms (sweep 1 / sweep 2), NRT = 4 4.45 / 4.57 ms; with
 // the stages filled by LDS-direct loads NRT = 2 4.06 ms (sweep 1) against 4.93 ms for NRT = 4 (4.23 ms when NRT = 4 is
 // squeezed into half the register file for two workgroups per CU).
-template <typename T, int D, int NRT_> struct Geo {
-    static constexpr int NRT = NRT_;
+//
+// KS = waves that share resident rows: KS consecutive waves hold the same rows and take every stage's streamed subtiles
+// in shares; their statistics are put together through LDS at the end.  A block is then 1/KS as many rows and takes 1/KS
+// as long, at KS times the loads into LDS per flop.
+template <typename T, int D, int NRT_, int KS_> struct Geo {
+    static constexpr int NRT = NRT_, KS = KS_;
     static constexpr int RES = 32 * NRT;             // resident rows per wave
-    static constexpr int BLOCK = SC_WAVES * RES;     // resident rows per workgroup
+    static constexpr int BLOCK = SC_WAVES / KS * RES; // resident rows per workgroup
     static constexpr int ROWB = D * (int)sizeof(T);  // bytes per head row
     static constexpr int NCH = ROWB / 32;            // MFMA chunks per row
     static constexpr int CPR = ROWB / 16;            // 16-byte pieces per row
@@ -62,26 +66,17 @@ template <typename T, int D, int NRT_> struct Geo {
     __device__ static constexpr int frag(int row, int c, int half) { return row * ROWB + (((2 * c + half) ^ swz(row)) << 4); }
     static constexpr int TILE = ROWB > 256 ? 64 : 128; // streamed rows per LDS stage (two stages; long enough to hide a global load)
     static constexpr int NSUB = TILE / 32;           // 32-row MFMA subtiles per stage
+    static constexpr int SHARE = NSUB / KS;          // of them, those a wave takes
     static constexpr int NLOAD = TILE * CPR / SC_THREADS;  // 16-byte global loads per thread per stage
     static constexpr int ROWS_PER_LOAD = SC_THREADS / CPR; // rows covered by one load of the whole workgroup
     static constexpr int STAGE_BYTES = TILE * STRIDE;
-    static constexpr int LDS_ROWSTATS = 2 * STAGE_BYTES;
-    static constexpr int LDS_COLSUM = 2 * STAGE_BYTES + 2 * TILE * (int)sizeof(float);
-    static constexpr int MIN_WG = (ROWB > 256 || NRT > 2 || SC_WAVES > 4) ? 1 : 2;  // workgroups per CU the register budget is set for
+    static constexpr int MERGE_BYTES = KS > 1 ? SC_WAVES * RES * 16 : 0;  // two floats per half-wave and resident row
+    static constexpr int LDS_ROWSTATS = 2 * STAGE_BYTES + MERGE_BYTES;
+    static constexpr int LDS_COLSUM = 2 * STAGE_BYTES + 2 * TILE * (int)sizeof(float) + MERGE_BYTES;
+    static constexpr int MIN_WG = (ROWB > 256 || NRT > 2 || SC_WAVES > 4) ? 1 : ROWB > 128 ? 2 : 3;  // workgroups per CU the register budget is set for
     static_assert(TILE * CPR % SC_THREADS == 0, "tile must split evenly over the workgroup");
+    static_assert(SC_WAVES % KS == 0 && NSUB % KS == 0, "the shares must be whole subtiles");
 };
-
-// block index -> (head, block-within-head).  Workgroup b runs on die b % 8; a die gets a contiguous
-// range of heads (so the query heads of one GQA group share the die's L2 with their KV head) and
-// walks one head's blocks in order before moving to its next head.
-__device__ __forceinline__ bool decode_block(int nblk, int heads_per_xcd, int H, int& h, int& blk) {
-    int b = blockIdx.x;
-    int x = b % NUM_XCD, w = b / NUM_XCD;
-    int slot = w / nblk;
-    blk = w - slot * nblk;
-    h = x * heads_per_xcd + slot;
-    return h < H;
-}
 
 // 16 bytes at byte offset `byte_off` of row `row` of a [rows, heads, D] tensor, zero beyond `nrows`
 template <typename T>
@@ -202,24 +197,26 @@ __device__ __forceinline__ void rowstat_frozen_slice(int c, const f32x16& raw, f
 // exponent range the sum overflows and lse2 comes out non-finite.  A workgroup that finds such a row among its own
 // (normally none does) goes through its keys a second time with the running maximum everywhere, before it stores
 // anything: no second launch, no extra traffic when there is nothing to repair.
-template <typename T, int D, int NRT>
-__global__ __launch_bounds__(SC_THREADS, (Geo<T, D, NRT>::MIN_WG)) void rowstats_kernel(ScoreParams p) {
-    using G = Geo<T, D, NRT>;
+template <typename T, int D, int NRT, int KS>
+__global__ __launch_bounds__(SC_THREADS, (Geo<T, D, NRT, KS>::MIN_WG)) void rowstats_kernel(ScoreParams p) {
+    using G = Geo<T, D, NRT, KS>;
     extern __shared__ __attribute__((aligned(16))) char smem[];
 
     int h, qb;
-    if (!decode_block(p.n_query_blocks, p.heads_per_xcd, p.H, h, qb)) return;
+    decode_block(p.heads_per_xcd, p.H, h, qb);
     const bool causal = (p.flags & LEMO_CAUSAL) != 0;
     if (causal) qb = p.n_query_blocks - 1 - qb;  // late query blocks see the most keys: start them first
     const int g = (int)(((long long)h * p.H_kv) / p.H);
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, half = lane >> 5, l32 = lane & 31;
+    const int tid = threadIdx.x, lane = tid & 63, half = lane >> 5, l32 = lane & 31;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const T* Qb = static_cast<const T*>(p.Q);
     const T* Kb = static_cast<const T*>(p.K);
     const long long q_off = (long long)h * p.q_hs, k_off = (long long)g * p.k_hs;
     const int S = p.S;
     const float c2 = p.c2;
     const int q0 = qb * G::BLOCK;        // first query of the workgroup
-    const int qw0 = q0 + wave * G::RES;  // first query of this wave
+    const int part = wave % KS, sub0 = part * G::SHARE;  // this wave's share of a stage: subtiles [sub0, sub0 + SHARE)
+    const int qw0 = q0 + wave / KS * G::RES;  // first query of this wave
 
     // resident operand: this wave's queries as MFMA B fragments
     u32x4 qf[NRT][G::NCH];
@@ -236,7 +233,7 @@ __global__ __launch_bounds__(SC_THREADS, (Geo<T, D, NRT>::MIN_WG)) void rowstats
     const int k_row_bytes = (int)p.k_ts * (int)sizeof(T);           // host guarantees < 2^24
     int st_voff[G::NLOAD];
     stage_offsets<G>(st_voff, k_row_bytes, tid);
-    const unsigned lds_w = lds_offset_of(smem) + (unsigned)__builtin_amdgcn_readfirstlane(wave) * 1024u;
+    const unsigned lds_w = lds_offset_of(smem) + (unsigned)wave * 1024u;
 
     float lse[NRT];       // the result: lse2 of query qw0 + qt*32 + l32
     bool frozen = true;   // wave-uniform (in fact workgroup-uniform): which pass this is
@@ -259,9 +256,10 @@ __global__ __launch_bounds__(SC_THREADS, (Geo<T, D, NRT>::MIN_WG)) void rowstats
         const u32x4 next_desc = stage_desc<G>(k_head, k_row_bytes, (t + 1) * G::TILE, S, more);
         const unsigned next_lds = lds_w + ((t + 1) & 1) * G::STAGE_BYTES;
         const int k0 = t * G::TILE;
-        // wave-uniform classification of this stage of keys against the wave's queries [qw0, qw0+RES-1]
-        const bool skip = causal && k0 > qw0 + G::RES - 1;  // every key lies after every query
-        const bool clean = causal ? (k0 + G::TILE - 1 <= qw0) : (k0 + G::TILE <= S);
+        // wave-uniform classification of this share of keys against the wave's queries [qw0, qw0+RES-1]
+        const int ka = k0 + sub0 * 32, kz = ka + G::SHARE * 32 - 1;  // keys of this wave's share
+        const bool skip = causal && ka > qw0 + G::RES - 1;  // every key lies after every query
+        const bool clean = causal ? (kz <= qw0) : (kz < S);
         const char* sbuf = smem + (t & 1) * G::STAGE_BYTES;
         const bool hot = clean && frozen && t > 0;
         if (more && !hot) stage_load<G>(st_voff, next_desc, next_lds);  // (the hot path spreads them over its tiles)
@@ -276,9 +274,9 @@ __global__ __launch_bounds__(SC_THREADS, (Geo<T, D, NRT>::MIN_WG)) void rowstats
                 l2[q] = 0.f;
             }
             u32x4 kf[G::NCH];
-            read_frags<G>(kf, sbuf, 0, l32, half);
+            read_frags<G>(kf, sbuf, sub0, l32, half);
 #pragma unroll
-            for (int ks = 0; ks < G::NSUB; ++ks) {
+            for (int ks = 0; ks < G::SHARE; ++ks) {
                 u32x4 kn[G::NCH];
                 f32x16 prev = carry;
 #pragma unroll
@@ -290,15 +288,15 @@ __global__ __launch_bounds__(SC_THREADS, (Geo<T, D, NRT>::MIN_WG)) void rowstats
                     for (int c = 0; c < G::NCH; ++c) {
                         rowstat_frozen_slice<G::NCH>(c, prev, c2, nm[pq], l[pq], l2[pq]);
                         mma_chunk<T>(acc, kf[c], qf[qt][c]);  // acc[key row][query col]
-                        if (c == 1) stage_load_slot<G>(st_voff, next_desc, next_lds, ks * NRT + qt, G::NSUB * NRT);
-                        if (qt == NRT - 1 && ks + 1 < G::NSUB)
-                            kn[c] = *reinterpret_cast<const u32x4*>(&sbuf[G::frag((ks + 1) * 32 + l32, c, half)]);
+                        if (c == 1) stage_load_slot<G>(st_voff, next_desc, next_lds, ks * NRT + qt, G::SHARE * NRT);
+                        if (qt == NRT - 1 && ks + 1 < G::SHARE)
+                            kn[c] = *reinterpret_cast<const u32x4*>(&sbuf[G::frag((sub0 + ks + 1) * 32 + l32, c, half)]);
                         slot_fence();
                     }
                     prev = acc;
                 }
                 carry = prev;
-                if (ks + 1 < G::NSUB) {
+                if (ks + 1 < G::SHARE) {
 #pragma unroll
                     for (int c = 0; c < G::NCH; ++c) kf[c] = kn[c];
                 }
@@ -309,9 +307,9 @@ __global__ __launch_bounds__(SC_THREADS, (Geo<T, D, NRT>::MIN_WG)) void rowstats
             // pipelined, running maximum: the statistics update of the previous tile is issued slice by slice
             // between the MFMAs of tile (ks, qt); fragments of the next key subtile are read during the last chain
             u32x4 kf[G::NCH];
-            read_frags<G>(kf, sbuf, 0, l32, half);
+            read_frags<G>(kf, sbuf, sub0, l32, half);
 #pragma unroll
-            for (int ks = 0; ks < G::NSUB; ++ks) {
+            for (int ks = 0; ks < G::SHARE; ++ks) {
                 u32x4 kn[G::NCH];
                 f32x16 prev = carry;
 #pragma unroll
@@ -324,15 +322,15 @@ __global__ __launch_bounds__(SC_THREADS, (Geo<T, D, NRT>::MIN_WG)) void rowstats
                     for (int c = 0; c < G::NCH; ++c) {
                         rowstat_slice<G::NCH>(c, prev, c2, m[pq], st);
                         mma_chunk<T>(acc, kf[c], qf[qt][c]);
-                        if (qt == NRT - 1 && ks + 1 < G::NSUB)
-                            kn[c] = *reinterpret_cast<const u32x4*>(&sbuf[G::frag((ks + 1) * 32 + l32, c, half)]);
+                        if (qt == NRT - 1 && ks + 1 < G::SHARE)
+                            kn[c] = *reinterpret_cast<const u32x4*>(&sbuf[G::frag((sub0 + ks + 1) * 32 + l32, c, half)]);
                         slot_fence();
                     }
                     rowstat_finish(st, m[pq], l[pq]);
                     prev = acc;
                 }
                 carry = prev;
-                if (ks + 1 < G::NSUB) {
+                if (ks + 1 < G::SHARE) {
 #pragma unroll
                     for (int c = 0; c < G::NCH; ++c) kf[c] = kn[c];
                 }
@@ -342,13 +340,13 @@ __global__ __launch_bounds__(SC_THREADS, (Geo<T, D, NRT>::MIN_WG)) void rowstats
 #pragma unroll
             for (int r = 0; r < 16; ++r) carry[r] = -INFINITY;
 #pragma unroll
-            for (int ks = 0; ks < G::NSUB; ++ks) {
+            for (int ks = 0; ks < G::SHARE; ++ks) {
                 u32x4 kf[G::NCH];
-                read_frags<G>(kf, sbuf, ks, l32, half);
+                read_frags<G>(kf, sbuf, sub0 + ks, l32, half);
 #pragma unroll
                 for (int qt = 0; qt < NRT; ++qt) {
                     // this 32x32 tile: keys [kmin, kmin+31] against queries [qmin, qmin+31] (wave-uniform tests)
-                    const int kmin = k0 + ks * 32, qmin = qw0 + qt * 32;
+                    const int kmin = ka + ks * 32, qmin = qw0 + qt * 32;
                     if (causal && kmin > qmin + 31) continue;  // every key lies after every query
                     f32x16 acc = {0};
 #pragma unroll
@@ -372,14 +370,36 @@ __global__ __launch_bounds__(SC_THREADS, (Geo<T, D, NRT>::MIN_WG)) void rowstats
     rowstat_update(carry, c2, m[NRT - 1], l[NRT - 1]);
 
     // the two half-waves hold disjoint key rows of the same queries: merge, then lse2 = m + log2(l)
+    // (with KS > 1, so do the KS waves: every partial sum is rescaled once, to the largest reference of all)
+    float2* const shares = reinterpret_cast<float2*>(smem + 2 * G::STAGE_BYTES);  // [wave][half][RES]
+    if constexpr (KS > 1) {
+#pragma unroll
+        for (int qt = 0; qt < NRT; ++qt) shares[(wave * 2 + half) * G::RES + qt * 32 + l32] = make_float2(m[qt], l[qt]);
+        __syncthreads();
+    }
+#pragma unroll
+    for (int qt = 0; qt < NRT; ++qt) {
+        constexpr int N = KS > 1 ? 2 * KS : 2;
+        float2 v[N];
+        if constexpr (KS > 1) {
+#pragma unroll
+            for (int w = 0; w < N; ++w) v[w] = shares[((wave - part) * 2 + w) * G::RES + qt * 32 + l32];  // the same order in every wave
+        } else {
+            v[0] = make_float2(m[qt], l[qt]);
+            v[1] = make_float2(__shfl_xor(m[qt], 32), __shfl_xor(l[qt], 32));
+        }
+        m[qt] = v[0].x;
+#pragma unroll
+        for (int w = 1; w < N; ++w) m[qt] = fmaxf(m[qt], v[w].x);
+        const float ms = m[qt] == -INFINITY ? 0.f : m[qt];
+        l[qt] = 0.f;
+#pragma unroll
+        for (int w = 0; w < N; ++w) l[qt] += v[w].y * __builtin_amdgcn_exp2f(v[w].x - ms);
+    }
     bool bad = false;
 #pragma unroll
     for (int qt = 0; qt < NRT; ++qt) {
-        const float mo = __shfl_xor(m[qt], 32), lo = __shfl_xor(l[qt], 32);
-        const float mt = fmaxf(m[qt], mo);
-        const float ms = mt == -INFINITY ? 0.f : mt;
-        const float lt = l[qt] * __builtin_amdgcn_exp2f(m[qt] - ms) + lo * __builtin_amdgcn_exp2f(mo - ms);
-        lse[qt] = mt + __builtin_amdgcn_logf(lt);
+        lse[qt] = m[qt] + __builtin_amdgcn_logf(l[qt]);
         bad |= qw0 + qt * 32 + l32 < S && !isfinite(lse[qt]);
     }
     // every wave is past its last read of the stages here as well, so a second pass may refill them
@@ -389,7 +409,7 @@ __global__ __launch_bounds__(SC_THREADS, (Geo<T, D, NRT>::MIN_WG)) void rowstats
 #pragma unroll
     for (int qt = 0; qt < NRT; ++qt) {
         const int q = qw0 + qt * 32 + l32;
-        if (half == 0 && q < S) p.lse2[(size_t)h * S + q] = lse[qt];
+        if (half == 0 && part == 0 && q < S) p.lse2[(size_t)h * S + q] = lse[qt];
     }
 }
 
@@ -423,32 +443,29 @@ __device__ __forceinline__ void read_nl(float (&nl)[16], const float* lbuf, int 
     }
 }
 
-template <typename T, int D, int NRT>
-__global__ __launch_bounds__(SC_THREADS, (Geo<T, D, NRT>::MIN_WG)) void colsum_kernel(ScoreParams p) {
-    using G = Geo<T, D, NRT>;
+template <typename T, int D, int NRT, int KS>
+__global__ __launch_bounds__(SC_THREADS, (Geo<T, D, NRT, KS>::MIN_WG)) void colsum_kernel(ScoreParams p) {
+    using G = Geo<T, D, NRT, KS>;
     extern __shared__ __attribute__((aligned(16))) char smem[];
     float* const sLbase = reinterpret_cast<float*>(smem + 2 * G::STAGE_BYTES);
 
     int h, kb;
-    if (!decode_block(p.n_key_blocks, p.heads_per_xcd, p.H, h, kb)) return;
+    decode_block(p.heads_per_xcd, p.H, h, kb);
     const bool causal = (p.flags & LEMO_CAUSAL) != 0;
     const int S = p.S;
     const float c2 = p.c2;
-    // key block -> (segment, block inside the segment); blocks never straddle a segment boundary
-    const int seg = kb / p.blocks_per_seg, bis = kb - seg * p.blocks_per_seg;
-    const long long seg0 = (long long)seg * p.L;
-    const long long key0_ll = seg0 + (long long)bis * G::BLOCK;
-    if (key0_ll >= S) return;
-    const int key0 = (int)key0_ll;
-    const int kend = (int)min((long long)S, min(seg0 + p.L, key0_ll + G::BLOCK));  // exclusive
+    const int key0 = kb * G::BLOCK;
+    const int kend = (int)min((long long)S, (long long)key0 + G::BLOCK);  // exclusive
 
     const int g = (int)(((long long)h * p.H_kv) / p.H);
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, half = lane >> 5, l32 = lane & 31;
+    const int tid = threadIdx.x, lane = tid & 63, half = lane >> 5, l32 = lane & 31;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const T* Qb = static_cast<const T*>(p.Q);
     const T* Kb = static_cast<const T*>(p.K);
     const long long q_off = (long long)h * p.q_hs, k_off = (long long)g * p.k_hs;
     const float* lse = p.lse2 + (size_t)h * S;
-    const int kw0 = key0 + wave * G::RES;  // first key of this wave
+    const int part = wave % KS, sub0 = part * G::SHARE;  // this wave's share of a stage: subtiles [sub0, sub0 + SHARE)
+    const int kw0 = key0 + wave / KS * G::RES;  // first key of this wave
 
     // resident operand: this wave's keys as MFMA B fragments (zero beyond the block's end)
     u32x4 kf[NRT][G::NCH];
@@ -470,7 +487,7 @@ __global__ __launch_bounds__(SC_THREADS, (Geo<T, D, NRT>::MIN_WG)) void colsum_k
     const int q_row_bytes = (int)p.q_ts * (int)sizeof(T);           // host guarantees < 2^24
     int st_voff[G::NLOAD];
     stage_offsets<G>(st_voff, q_row_bytes, tid);
-    const unsigned lds_w = lds_offset_of(smem) + (unsigned)__builtin_amdgcn_readfirstlane(wave) * 1024u;
+    const unsigned lds_w = lds_offset_of(smem) + (unsigned)wave * 1024u;
     float pre_l = 0.f;
     // row statistics of a stage: thread tid < TILE owns row tid; beyond the end +inf, so that p = exp2(-inf) = 0
     auto fetch_l = [&](int t) { return tid < G::TILE ? lse[min(t * G::TILE + tid, S - 1)] : 0.f; };
@@ -494,8 +511,9 @@ __global__ __launch_bounds__(SC_THREADS, (Geo<T, D, NRT>::MIN_WG)) void colsum_k
         const unsigned next_lds = lds_w + (buf ^ 1) * G::STAGE_BYTES;
         if (more) pre_l = fetch_l(t - 1);
         const int i0 = t * G::TILE;
-        const bool on_diag = i0 <= kw0 + G::RES - 1 && i0 + G::TILE - 1 >= kw0;  // stage meets the diagonal band of this wave
-        const bool skip = causal && i0 + G::TILE - 1 < kw0;                     // every query lies before every key
+        const int ia = i0 + sub0 * 32, iz = ia + G::SHARE * 32 - 1;   // queries of this wave's share
+        const bool on_diag = ia <= kw0 + G::RES - 1 && iz >= kw0;    // they meet the diagonal band of this wave
+        const bool skip = causal && iz < kw0;                        // every query lies before every key
         const char* sbuf = smem + buf * G::STAGE_BYTES;
         const float* lbuf = sLbase + buf * G::TILE;
         const bool hot = !on_diag && !skip;
@@ -505,10 +523,10 @@ __global__ __launch_bounds__(SC_THREADS, (Geo<T, D, NRT>::MIN_WG)) void colsum_k
             // (qs, kt); fragments and row statistics of the next query subtile are read during the last chain
             u32x4 qf[G::NCH];
             float nl[16];
-            read_frags<G>(qf, sbuf, 0, l32, half);
-            read_nl(nl, lbuf, 0, half);
+            read_frags<G>(qf, sbuf, sub0, l32, half);
+            read_nl(nl, lbuf, sub0, half);
 #pragma unroll
-            for (int qs = 0; qs < G::NSUB; ++qs) {
+            for (int qs = 0; qs < G::SHARE; ++qs) {
                 u32x4 qn[G::NCH];
                 float nn[16];
                 f32x16 prev = carry;
@@ -522,11 +540,11 @@ __global__ __launch_bounds__(SC_THREADS, (Geo<T, D, NRT>::MIN_WG)) void colsum_k
                         if (kt == 0) colsum_slice<G::NCH>(c, prev, carry_nl, c2, col[pk], col2[pk]);  // the carried tile has its own rows
                         else colsum_slice<G::NCH>(c, prev, nl, c2, col[pk], col2[pk]);
                         mma_chunk<T>(acc, qf[c], kf[kt][c]);  // acc[query row][key col]
-                        if (c == 1) stage_load_slot<G>(st_voff, next_desc, next_lds, qs * NRT + kt, G::NSUB * NRT);
-                        if (kt == NRT - 1 && qs + 1 < G::NSUB) {
-                            qn[c] = *reinterpret_cast<const u32x4*>(&sbuf[G::frag((qs + 1) * 32 + l32, c, half)]);
+                        if (c == 1) stage_load_slot<G>(st_voff, next_desc, next_lds, qs * NRT + kt, G::SHARE * NRT);
+                        if (kt == NRT - 1 && qs + 1 < G::SHARE) {
+                            qn[c] = *reinterpret_cast<const u32x4*>(&sbuf[G::frag((sub0 + qs + 1) * 32 + l32, c, half)]);
                             if (c < 4) {
-                                const f32x4 v = *reinterpret_cast<const f32x4*>(&lbuf[(qs + 1) * 32 + c * 8 + half * 4]);
+                                const f32x4 v = *reinterpret_cast<const f32x4*>(&lbuf[(sub0 + qs + 1) * 32 + c * 8 + half * 4]);
                                 nn[c * 4 + 0] = v[0]; nn[c * 4 + 1] = v[1]; nn[c * 4 + 2] = v[2]; nn[c * 4 + 3] = v[3];
                             }
                         }
@@ -537,7 +555,7 @@ __global__ __launch_bounds__(SC_THREADS, (Geo<T, D, NRT>::MIN_WG)) void colsum_k
                 carry = prev;
 #pragma unroll
                 for (int r = 0; r < 16; ++r) carry_nl[r] = nl[r];
-                if (qs + 1 < G::NSUB) {
+                if (qs + 1 < G::SHARE) {
 #pragma unroll
                     for (int c = 0; c < G::NCH; ++c) qf[c] = qn[c];
 #pragma unroll
@@ -549,15 +567,15 @@ __global__ __launch_bounds__(SC_THREADS, (Geo<T, D, NRT>::MIN_WG)) void colsum_k
 #pragma unroll
             for (int r = 0; r < 16; ++r) carry_nl[r] = -INFINITY;
 #pragma unroll
-            for (int qs = 0; qs < G::NSUB; ++qs) {
+            for (int qs = 0; qs < G::SHARE; ++qs) {
                 u32x4 qf[G::NCH];
                 float nl[16];
-                read_frags<G>(qf, sbuf, qs, l32, half);
-                read_nl(nl, lbuf, qs, half);
+                read_frags<G>(qf, sbuf, sub0 + qs, l32, half);
+                read_nl(nl, lbuf, sub0 + qs, half);
 #pragma unroll
                 for (int kt = 0; kt < NRT; ++kt) {
                     // this 32x32 tile: queries [qmin, qmin+31] against keys [kmin, kmin+31] (wave-uniform tests)
-                    const int qmin = i0 + qs * 32, kmin = kw0 + kt * 32;
+                    const int qmin = ia + qs * 32, kmin = kw0 + kt * 32;
                     if (causal && qmin + 31 < kmin) continue;  // every query lies before every key
                     f32x16 acc = {0};
 #pragma unroll
@@ -585,15 +603,30 @@ __global__ __launch_bounds__(SC_THREADS, (Geo<T, D, NRT>::MIN_WG)) void colsum_k
     }
     col[NRT - 1] += colsum_tile(carry, carry_nl, c2);
 
+    float2* const shares = reinterpret_cast<float2*>(smem + 2 * G::STAGE_BYTES + 2 * G::TILE * (int)sizeof(float));  // [wave][RES]
 #pragma unroll
     for (int kt = 0; kt < NRT; ++kt) {
         col[kt] += col2[kt];
-        const float c = col[kt] + __shfl_xor(col[kt], 32);
-        const float dd = dg[kt] + __shfl_xor(dg[kt], 32);
+        col[kt] += __shfl_xor(col[kt], 32);
+        dg[kt] += __shfl_xor(dg[kt], 32);
+        if constexpr (KS > 1) shares[wave * G::RES + kt * 32 + l32] = make_float2(col[kt], dg[kt]);
+    }
+    if constexpr (KS > 1) {
+        __syncthreads();
+        if (part != 0) return;
+    }
+#pragma unroll
+    for (int kt = 0; kt < NRT; ++kt) {
+#pragma unroll
+        for (int w = 1; w < KS; ++w) {
+            const float2 v = shares[(wave + w) * G::RES + kt * 32 + l32];
+            col[kt] += v.x;
+            dg[kt] += v.y;
+        }
         const int key = kw0 + kt * 32 + l32;
         if (half == 0 && key < kend) {
-            p.colsum[(size_t)h * S + key] = c;
-            p.diag[(size_t)h * S + key] = dd;
+            p.colsum[(size_t)h * S + key] = col[kt];
+            p.diag[(size_t)h * S + key] = dg[kt];
         }
     }
 }
@@ -601,65 +634,86 @@ __global__ __launch_bounds__(SC_THREADS, (Geo<T, D, NRT>::MIN_WG)) void colsum_k
 // ------------------------------------------------------------------------------------------------
 // Head mean (Eq. 2's 1/N_head) with the self term optionally removed (Eq. 1's i != j).
 // ------------------------------------------------------------------------------------------------
-__global__ __launch_bounds__(256) void head_mean_kernel(const float* __restrict__ colsum, const float* __restrict__ diag,
+// Bound by the latency of the loads (2 H of them per token): they are asked for eight heads at a time, and 64-thread
+// workgroups spread short sequences over more CUs.  S = 32768, H = 32: 15.4 us with one head at a time.
+constexpr int HM_THREADS = 64;
+__global__ __launch_bounds__(HM_THREADS) void head_mean_kernel(const float* __restrict__ colsum, const float* __restrict__ diag,
                                                         float* __restrict__ scores, int S, int H, int exclude_self) {
-    const int j = blockIdx.x * blockDim.x + threadIdx.x;
+    const int j = blockIdx.x * HM_THREADS + threadIdx.x;
     if (j >= S) return;
     float acc = 0.f;
-    for (int h = 0; h < H; ++h) {
-        float v = colsum[(size_t)h * S + j];
-        if (exclude_self) v -= diag[(size_t)h * S + j];
-        acc += v;
+    for (int h0 = 0; h0 < H; h0 += 8) {
+        float c[8], d[8];
+#pragma unroll
+        for (int e = 0; e < 8; ++e) {
+            const size_t at = (size_t)min(h0 + e, H - 1) * S + j;
+            c[e] = colsum[at];
+            d[e] = exclude_self ? diag[at] : 0.f;
+        }
+#pragma unroll
+        for (int e = 0; e < 8; ++e)
+            if (h0 + e < H) acc += exclude_self ? c[e] - d[e] : c[e];
     }
     scores[j] = acc / (float)H;
 }
 
 // which: bit 0 = sweep 1 (row statistics), bit 1 = sweep 2 (column sums)
-template <typename T, int D, int NRT>
+template <typename T, int D, int NRT, int KS>
 static int launch_sweeps(const ScoreParams& p_in, int which, hipStream_t st) {
-    using G = Geo<T, D, NRT>;
+    using G = Geo<T, D, NRT, KS>;
     ScoreParams p = p_in;
     p.n_query_blocks = (p.S + G::BLOCK - 1) / G::BLOCK;
-    // Key blocks never straddle a segment boundary.  Segments shorter than a block are grouped: a block
-    // then covers as many WHOLE segments as fit, which is the same as working with that longer unit.
-    long long Leff = p.L;
-    if (Leff < G::BLOCK) Leff = (G::BLOCK / Leff) * Leff;
-    if (Leff > p.S) Leff = p.S;
-    p.L = (int)Leff;
-    p.blocks_per_seg = (int)((Leff + G::BLOCK - 1) / G::BLOCK);
-    const long long nseg = ((long long)p.S + Leff - 1) / Leff;
-    p.n_key_blocks = (int)(nseg * p.blocks_per_seg);
     static std::once_flag once;
     static hipError_t attr_err = hipSuccess;
     std::call_once(once, [] {  // the kernels use more dynamic LDS than the default limit
-        const void* ks[2] = {reinterpret_cast<const void*>(&rowstats_kernel<T, D, NRT>),
-                             reinterpret_cast<const void*>(&colsum_kernel<T, D, NRT>)};
+        const void* ks[2] = {reinterpret_cast<const void*>(&rowstats_kernel<T, D, NRT, KS>),
+                             reinterpret_cast<const void*>(&colsum_kernel<T, D, NRT, KS>)};
         const int bytes[2] = {G::LDS_ROWSTATS, G::LDS_COLSUM};
         for (int i = 0; i < 2 && attr_err == hipSuccess; ++i)
             attr_err = hipFuncSetAttribute(ks[i], hipFuncAttributeMaxDynamicSharedMemorySize, bytes[i]);
     });
     if (attr_err != hipSuccess) return (int)attr_err;
-    const unsigned g1 = (unsigned)(NUM_XCD * p.heads_per_xcd * p.n_query_blocks);
-    const unsigned g2 = (unsigned)(NUM_XCD * p.heads_per_xcd * p.n_key_blocks);
-    if (which & 1) hipLaunchKernelGGL((rowstats_kernel<T, D, NRT>), dim3(g1), dim3(SC_THREADS), G::LDS_ROWSTATS, st, p);
-    if (which & 2) hipLaunchKernelGGL((colsum_kernel<T, D, NRT>), dim3(g2), dim3(SC_THREADS), G::LDS_COLSUM, st, p);
+    const unsigned grid = (unsigned)(p.H * p.n_query_blocks);  // as many key blocks
+    if (which & 1) hipLaunchKernelGGL((rowstats_kernel<T, D, NRT, KS>), dim3(grid), dim3(SC_THREADS), G::LDS_ROWSTATS, st, p);
+    if (which & 2) hipLaunchKernelGGL((colsum_kernel<T, D, NRT, KS>), dim3(grid), dim3(SC_THREADS), G::LDS_COLSUM, st, p);
     return (int)hipGetLastError();
+}
+
+// How many waves share resident rows (KS).  Large launches take 1: the fewest loads into LDS per flop (32K tokens, 32
+// heads, d = 128: 4.04 / 4.50 / 5.46 ms a sweep for KS = 1 / 2 / 4).  With fewer than about two blocks per resident
+// workgroup slot the launch is as long as its longest block, and smaller blocks win: by number n of 256-row blocks,
+//   d = 128  n = 512 (4096 tokens, 32 heads) 89 / 87 / 108 us, n = 384 (6000, 16 heads) 101 / 86 / 94, n = 256 40 / 30 / 33,
+//            n = 128 (1000, 32 heads) 22 / 15 / 14, n = 704 (5500, 32 heads) 134 / 136 / 161
+//   d = 64   the vector work per logit weighs twice as much against the loads: n = 2048 (32K tokens, 16 heads) 1.26 / 1.34 /
+//            1.50 ms, n = 756 (16000, 12 heads) 289 / 254 / 292 us, n = 240 (5000, 12 heads) 70 / 48 / 43, n = 96 30 / 19 / 16.5
+//   binary32 the MFMAs take 16 times as long and the loads never show: always the most shares (d = 64, n = 576, full
+//            attention: 1750 / 1491 / 1380 us)
+template <typename T, int D, int NRT>
+static int launch_sweeps_ks(const ScoreParams& p, int which, hipStream_t st) {
+    if constexpr (sizeof(T) == 4) {
+        return launch_sweeps<T, D, NRT, Geo<T, D, NRT, 1>::NSUB>(p, which, st);
+    } else {
+        const long long n = (long long)p.H * ((p.S + 255) / 256);
+        if (n <= (D > 64 ? 128 : 256)) return launch_sweeps<T, D, NRT, 4>(p, which, st);
+        if (n <= (D > 64 ? 640 : 1024)) return launch_sweeps<T, D, NRT, 2>(p, which, st);
+        return launch_sweeps<T, D, NRT, 1>(p, which, st);
+    }
 }
 
 int launch_score(const ScoreParams& p_in, lemo_dtype_t dt, int d, int which, hipStream_t st) {
     ScoreParams p = p_in;
-    p.heads_per_xcd = (p.H + NUM_XCD - 1) / NUM_XCD;
+    p.heads_per_xcd = p.H % NUM_XCD == 0 ? p.H / NUM_XCD : 0;
     int rc = 0;
     if (which & 3) {
-        if (dt == LEMO_BF16 && d == 128) rc = launch_sweeps<bf16_t, 128, LEMO_NRT_BF16_128>(p, which, st);
-        else if (dt == LEMO_BF16 && d == 64) rc = launch_sweeps<bf16_t, 64, 2>(p, which, st);
-        else if (dt == LEMO_F32 && d == 128) rc = launch_sweeps<float, 128, 2>(p, which, st);
-        else if (dt == LEMO_F32 && d == 64) rc = launch_sweeps<float, 64, 2>(p, which, st);
+        if (dt == LEMO_BF16 && d == 128) rc = launch_sweeps_ks<bf16_t, 128, LEMO_NRT_BF16_128>(p, which, st);
+        else if (dt == LEMO_BF16 && d == 64) rc = launch_sweeps_ks<bf16_t, 64, 2>(p, which, st);
+        else if (dt == LEMO_F32 && d == 128) rc = launch_sweeps_ks<float, 128, 2>(p, which, st);
+        else if (dt == LEMO_F32 && d == 64) rc = launch_sweeps_ks<float, 64, 2>(p, which, st);
         else return (int)hipErrorInvalidValue;
         if (rc) return rc;
     }
     if (which & 4) {
-        hipLaunchKernelGGL(head_mean_kernel, dim3((p.S + 255) / 256), dim3(256), 0, st, p.colsum, p.diag, p.scores, p.S, p.H,
+        hipLaunchKernelGGL(head_mean_kernel, dim3((p.S + HM_THREADS - 1) / HM_THREADS), dim3(HM_THREADS), 0, st, p.colsum, p.diag, p.scores, p.S, p.H,
                            (p.flags & LEMO_EXCLUDE_SELF) ? 1 : 0);
         rc = (int)hipGetLastError();
     }

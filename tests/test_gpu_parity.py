@@ -196,6 +196,22 @@ def test_score_reference_overflow_is_repaired(lemo, dominant):
             assert want[dominant] > 5  # the dominant key really collects the later queries
 
 
+@pytest.mark.parametrize("S,H,Hkv,d", [(700, 70, 35, 128), (333, 330, 110, 128), (700, 104, 52, 64), (300, 520, 130, 64)])
+def test_score_larger_blocks(lemo, S, H, Hkv, d):
+    """Launches with more 256-row blocks share rows between two waves (first and third case) or none; the other scoring
+    tests run with four.  Head counts that divide over the dies and that do not; one key whose logits overtake the frozen
+    reference of sweep 1 for half the queries of a head group."""
+    say(f"[score] larger blocks S={S} H={H}/{Hkv} d={d}")
+    Q, K = wl.tiny_qk(S, H, Hkv, d, "bf16", seed=S + H + d, heavy=4)
+    K[S // 2 + 40, 1] = K[S // 2 + 40, 1] * 40
+    for flags in (3, 0):
+        got, col, dg = run_score(lemo, Q, K, 256, flags)
+        want, wcol, wdg = oracle.score(wl.as_numpy(Q), wl.as_numpy(K), flags=flags, per_head=True)
+        assert_scores_close(col.ravel(), wcol.ravel(), "colsum_per_head")
+        assert_scores_close(dg.ravel(), wdg.ravel(), "diag_per_head")
+        assert_scores_close(got, want, "scores")
+
+
 def test_score_config_C2_full(lemo):
     """Llama2-7B-shaped layer, S=4096, all 32 heads, against the full oracle."""
     cfg = wl.CONFIGS["C2"]
