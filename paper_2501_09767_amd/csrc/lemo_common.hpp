@@ -94,14 +94,14 @@ __device__ __forceinline__ uint32_t pack_bf16x2_hw(float lo, float hi) {
 // Block index -> (head, block rank); ranks are walked for all heads at once, so that the longest blocks of EVERY head
 // start first and the launch ends on short ones.  Workgroup b runs on die b % 8; when the heads divide evenly a die gets a
 // contiguous range of them (the query heads of one GQA group share the die's L2 with their KV head), otherwise
-// (heads_per_xcd = 0) blocks are dealt out over all dies.  Head by head instead, a sweep of the score took: 8192 tokens, 32
+// (heads_per_xcd = 0) blocks are dealt out over all dies.  nblk > 0 (blocks of equal length): head by head on each die.  Head by head instead, a sweep of the score took: 8192 tokens, 32
 // heads 310 us against 280, 16384 tokens 1096 against 1036; and a 12-head layer left two dies idle.
-__device__ __forceinline__ void decode_block(int heads_per_xcd, int H, int& h, int& rank) {
+__device__ __forceinline__ void decode_block(int heads_per_xcd, int H, int nblk, int& h, int& rank) {
     const int b = blockIdx.x;
     if (heads_per_xcd > 0) {
-        const int w = b / NUM_XCD;
-        rank = w / heads_per_xcd;
-        h = b % NUM_XCD * heads_per_xcd + (w - rank * heads_per_xcd);
+        const int w = b / NUM_XCD, inner = nblk > 0 ? nblk : heads_per_xcd, outer = w / inner;
+        rank = nblk > 0 ? w - outer * inner : outer;
+        h = b % NUM_XCD * heads_per_xcd + (nblk > 0 ? outer : w - outer * inner);
     } else {
         rank = b / H;
         h = b - rank * H;

@@ -73,7 +73,7 @@ template <typename T, int D, int NRT_, int KS_> struct Geo {
     static constexpr int MERGE_BYTES = KS > 1 ? SC_WAVES * RES * 16 : 0;  // two floats per half-wave and resident row
     static constexpr int LDS_ROWSTATS = 2 * STAGE_BYTES + MERGE_BYTES;
     static constexpr int LDS_COLSUM = 2 * STAGE_BYTES + 2 * TILE * (int)sizeof(float) + MERGE_BYTES;
-    static constexpr int MIN_WG = (ROWB > 256 || NRT > 2 || SC_WAVES > 4) ? 1 : ROWB > 128 ? 2 : 3;  // workgroups per CU the register budget is set for
+    static constexpr int MIN_WG = (ROWB * NRT > 512 || NRT > 2 || SC_WAVES > 4) ? 1 : ROWB > 128 ? 2 : 3;  // workgroups per CU the register budget is set for
     static_assert(TILE * CPR % SC_THREADS == 0, "tile must split evenly over the workgroup");
     static_assert(SC_WAVES % KS == 0 && NSUB % KS == 0, "the shares must be whole subtiles");
 };
@@ -203,7 +203,7 @@ __global__ __launch_bounds__(SC_THREADS, (Geo<T, D, NRT, KS>::MIN_WG)) void rows
     extern __shared__ __attribute__((aligned(16))) char smem[];
 
     int h, qb;
-    decode_block(p.heads_per_xcd, p.H, h, qb);
+    decode_block(p.heads_per_xcd, p.H, 0, h, qb);
     const bool causal = (p.flags & LEMO_CAUSAL) != 0;
     if (causal) qb = p.n_query_blocks - 1 - qb;  // late query blocks see the most keys: start them first
     const int g = (int)(((long long)h * p.H_kv) / p.H);
@@ -450,7 +450,7 @@ __global__ __launch_bounds__(SC_THREADS, (Geo<T, D, NRT, KS>::MIN_WG)) void cols
     float* const sLbase = reinterpret_cast<float*>(smem + 2 * G::STAGE_BYTES);
 
     int h, kb;
-    decode_block(p.heads_per_xcd, p.H, h, kb);
+    decode_block(p.heads_per_xcd, p.H, 0, h, kb);
     const bool causal = (p.flags & LEMO_CAUSAL) != 0;
     const int S = p.S;
     const float c2 = p.c2;
@@ -686,29 +686,27 @@ static int launch_sweeps(const ScoreParams& p_in, int which, hipStream_t st) {
 //            n = 128 (1000, 32 heads) 22 / 15 / 14, n = 704 (5500, 32 heads) 134 / 136 / 161
 //   d = 64   the vector work per logit weighs twice as much against the loads: n = 2048 (32K tokens, 16 heads) 1.26 / 1.34 /
 //            1.50 ms, n = 756 (16000, 12 heads) 289 / 254 / 292 us, n = 240 (5000, 12 heads) 70 / 48 / 43, n = 96 30 / 19 / 16.5
-//   binary32 the MFMAs take 16 times as long and the loads never show: always the most shares (d = 64, n = 576, full
-//            attention: 1750 / 1491 / 1380 us)
 template <typename T, int D, int NRT>
-static int launch_sweeps_ks(const ScoreParams& p, int which, hipStream_t st) {
-    if constexpr (sizeof(T) == 4) {
-        return launch_sweeps<T, D, NRT, Geo<T, D, NRT, 1>::NSUB>(p, which, st);
-    } else {
-        const long long n = (long long)p.H * ((p.S + 255) / 256);
-        if (n <= (D > 64 ? 128 : 256)) return launch_sweeps<T, D, NRT, 4>(p, which, st);
-        if (n <= (D > 64 ? 640 : 1024)) return launch_sweeps<T, D, NRT, 2>(p, which, st);
-        return launch_sweeps<T, D, NRT, 1>(p, which, st);
-    }
+static int launch_sweeps_ks(const ScoreParams& p, long long n, int which, hipStream_t st) {
+    if (n <= (D > 64 ? 128 : 256)) return launch_sweeps<T, D, NRT, 4>(p, which, st);
+    if (n <= (D > 64 ? 640 : 1024)) return launch_sweeps<T, D, NRT, 2>(p, which, st);
+    return launch_sweeps<T, D, NRT, 1>(p, which, st);
 }
 
+// binary32: the MFMAs take 16 times as long and the loads never show, so the most shares are best at any size (d = 64, n =
+// 576, full attention: 1750 / 1491 / 1380 us for KS = 1 / 2 / 4), and one resident subtile per wave instead of two where
+// blocks are few (d = 64, n = 16: 15.8 against 24.2 us, n = 48: 47 / 63, n = 288: 263 / 247) or its registers allow a second
+// workgroup per CU (d = 128, n = 192: 175 / 208, n = 768: 1173 / 1255).
 int launch_score(const ScoreParams& p_in, lemo_dtype_t dt, int d, int which, hipStream_t st) {
     ScoreParams p = p_in;
     p.heads_per_xcd = p.H % NUM_XCD == 0 ? p.H / NUM_XCD : 0;
     int rc = 0;
+    const long long blocks256 = (long long)p.H * ((p.S + 255) / 256);
     if (which & 3) {
-        if (dt == LEMO_BF16 && d == 128) rc = launch_sweeps_ks<bf16_t, 128, LEMO_NRT_BF16_128>(p, which, st);
-        else if (dt == LEMO_BF16 && d == 64) rc = launch_sweeps_ks<bf16_t, 64, 2>(p, which, st);
-        else if (dt == LEMO_F32 && d == 128) rc = launch_sweeps_ks<float, 128, 2>(p, which, st);
-        else if (dt == LEMO_F32 && d == 64) rc = launch_sweeps_ks<float, 64, 2>(p, which, st);
+        if (dt == LEMO_BF16 && d == 128) rc = launch_sweeps_ks<bf16_t, 128, LEMO_NRT_BF16_128>(p, blocks256, which, st);
+        else if (dt == LEMO_BF16 && d == 64) rc = launch_sweeps_ks<bf16_t, 64, 2>(p, blocks256, which, st);
+        else if (dt == LEMO_F32 && d == 128) rc = launch_sweeps<float, 128, 1, 2>(p, which, st);
+        else if (dt == LEMO_F32 && d == 64) rc = blocks256 <= 192 ? launch_sweeps<float, 64, 1, 4>(p, which, st) : launch_sweeps<float, 64, 2, 4>(p, which, st);
         else return (int)hipErrorInvalidValue;
         if (rc) return rc;
     }
