@@ -33,12 +33,8 @@ namespace lemo {
 #ifndef LEMO_AT_NQ
 #define LEMO_AT_NQ 1
 #endif
-#ifndef LEMO_AT_PIPE
-#define LEMO_AT_PIPE 1
-#endif
-constexpr int AT_THREADS = LEMO_AT_THREADS;
+constexpr int AT_THREADS = LEMO_AT_THREADS, AT_WAVES = AT_THREADS / 64;
 constexpr int AT_NQ = LEMO_AT_NQ;                   // 32-query subtiles per wave
-constexpr int AT_BQ = (AT_THREADS / 64) * 32 * AT_NQ;  // queries per workgroup
 constexpr int AT_KT = 128;                          // keys per LDS stage
 constexpr int AT_MPAD = 128;         // the transposed V is padded to a multiple of this many kept tokens
 
@@ -109,25 +105,84 @@ __global__ __launch_bounds__(256) void gather_vt_kernel(const uint16_t* __restri
     }
 }
 
-template <int D>
+// Several waves may hold the same queries and take the key subtiles of every stage in shares (KS consecutive waves); a
+// block is then 1/KS as many queries and as much shorter, which is what a launch with few blocks needs.  At the end the
+// shares of a query are brought to the largest reference of all, laid out in LDS as binary32 (the stages are dead: a
+// barrier must stand before the call), and added in wave order; each wave finishes its part of the group's queries, whole
+// rows of 16-byte pieces.  o, ref, l: a wave's outputs, their reference and their normaliser (of both half-waves).
+template <int NQ, int D> constexpr int share_lds(int waves) { return waves * 32 * NQ * ((D + 4) * 4 + 8); }
+template <int KS, int NQ, int D>
+__device__ __forceinline__ void finish_shares(const f32x16 (&o)[NQ][D / 32], const float (&ref)[NQ], const float (&l)[NQ], char* smem, int waves,
+                                              int wave, int lane, int mw0, int h, const AttnParams& p) {
+    constexpr int QW = 32 * NQ, PITCH = D + 4, LPR = D / 8;  // queries per wave, floats per row in LDS, lanes per row
+    const int part = wave % KS, first = wave - part, half = lane >> 5, l32 = lane & 31;
+    float* const blocks = reinterpret_cast<float*>(smem);                             // [wave][QW][PITCH]
+    float2* const stats = reinterpret_cast<float2*>(smem + waves * QW * PITCH * 4);  // [wave][QW]: reference, normaliser
+#pragma unroll
+    for (int qs = 0; qs < NQ; ++qs) stats[wave * QW + qs * 32 + l32] = make_float2(ref[qs], l[qs]);
+    __syncthreads();
+#pragma unroll
+    for (int qs = 0; qs < NQ; ++qs) {
+        float mt = -INFINITY;
+#pragma unroll
+        for (int w = 0; w < KS; ++w) mt = fmaxf(mt, stats[(first + w) * QW + qs * 32 + l32].x);
+        const float f = ref[qs] == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(ref[qs] - mt);
+#pragma unroll
+        for (int dv = 0; dv < D / 32; ++dv)
+#pragma unroll
+            for (int gq = 0; gq < 4; ++gq) {
+                f32x4 v;
+#pragma unroll
+                for (int e = 0; e < 4; ++e) v[e] = o[qs][dv][gq * 4 + e] * f;
+                *reinterpret_cast<f32x4*>(blocks + (wave * QW + qs * 32 + l32) * PITCH + dv * 32 + gq * 8 + half * 4) = v;
+            }
+    }
+    __syncthreads();
+    const int c0 = lane % LPR * 8;
+#pragma unroll
+    for (int r = 0; r < QW / KS; r += 64 / LPR) {
+        const int row = part * (QW / KS) + r + lane / LPR, m = mw0 + row;
+        float mt = -INFINITY, lt = 0.f, v[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int w = 0; w < KS; ++w) mt = fmaxf(mt, stats[(first + w) * QW + row].x);
+#pragma unroll
+        for (int w = 0; w < KS; ++w) {
+            const int at = (first + w) * QW + row;
+            const float2 st = stats[at];
+            lt += st.x == -INFINITY ? 0.f : st.y * __builtin_amdgcn_exp2f(st.x - mt);
+            const f32x4 lo = *reinterpret_cast<const f32x4*>(blocks + at * PITCH + c0);
+            const f32x4 hi = *reinterpret_cast<const f32x4*>(blocks + at * PITCH + c0 + 4);
+#pragma unroll
+            for (int e = 0; e < 4; ++e) { v[e] += lo[e]; v[e + 4] += hi[e]; }
+        }
+        const float inv = lt > 0.f ? 1.f / lt : 0.f;
+        if (m < p.M) {
+            u32x4 out;
+#pragma unroll
+            for (int e = 0; e < 4; ++e) out[e] = pack_bf16x2_hw(v[2 * e] * inv, v[2 * e + 1] * inv);
+            *reinterpret_cast<u32x4*>(p.O + (long long)m * p.o_ts + (long long)h * p.o_hs + c0) = out;  // host: rows are 16-byte aligned
+        }
+    }
+}
+
+template <int D, int KS>
 __global__ __launch_bounds__(AT_THREADS, 1) void kept_attention_kernel(AttnParams p) {
     using G = AGeo<D>;
     using T = bf16_t;
     extern __shared__ __attribute__((aligned(16))) char smem[];
 
-    // block -> (head, query block): die b % 8 gets a contiguous range of heads; late query blocks (most keys) first
-    const int b = blockIdx.x, x = b % NUM_XCD, w_ = b / NUM_XCD;
-    const int slot = w_ / p.n_qblocks;
-    int qb = w_ - slot * p.n_qblocks;
-    const int h = x * p.heads_per_xcd + slot;
-    if (h >= p.H) return;
+    int h, qb;
     const bool causal = (p.flags & LEMO_CAUSAL) != 0;
+    decode_block(p.heads_per_xcd, p.H, causal ? 0 : p.n_qblocks, h, qb);  // causal: late query blocks (most keys) first
     if (causal) qb = p.n_qblocks - 1 - qb;
     const int g = (int)(((long long)h * p.H_kv) / p.H);
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, half = lane >> 5, l32 = lane & 31;
+    const int tid = threadIdx.x, lane = tid & 63, half = lane >> 5, l32 = lane & 31;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int M = p.M;
     const float c2 = p.c2;
-    const int m0 = qb * AT_BQ, mw0 = m0 + wave * 32 * AT_NQ;
+    constexpr int AT_BQ = AT_WAVES / KS * 32 * AT_NQ, SHARE = AT_KT / 32 / KS;  // queries per workgroup, key subtiles of a stage per wave
+    const int m0 = qb * AT_BQ, mw0 = m0 + wave / KS * 32 * AT_NQ;
+    const int sub0 = wave % KS * SHARE;
 
     // resident operand: this wave's 64 queries (rows gathered through idx), as MFMA B fragments
     u32x4 qf[AT_NQ][G::NCH];
@@ -207,7 +262,7 @@ __global__ __launch_bounds__(AT_THREADS, 1) void kept_attention_kernel(AttnParam
         const char* sv = sk + AT_KT * G::KSTRIDE;
         if (!(causal && k0 > mw0 + 32 * AT_NQ - 1)) {  // otherwise every key of the stage lies after every query of the wave
 #pragma unroll 1
-            for (int ks = 0; ks < AT_KT / 32; ++ks) {
+            for (int ks = sub0; ks < sub0 + SHARE; ++ks) {
                 const int kmin = k0 + ks * 32;
                 if (kmin >= M || (causal && kmin > mw0 + 32 * AT_NQ - 1)) break;
                 u32x4 kf[G::NCH];
@@ -280,6 +335,13 @@ __global__ __launch_bounds__(AT_THREADS, 1) void kept_attention_kernel(AttnParam
         if (more) stash((t + 1) & 1);
     }
 
+    if constexpr (KS > 1) {
+#pragma unroll
+        for (int qs = 0; qs < AT_NQ; ++qs) lrun[qs] += __shfl_xor(lrun[qs], 32);
+        __syncthreads();
+        finish_shares<KS, AT_NQ, D>(o, mrun, lrun, smem, AT_WAVES, wave, lane, mw0, h, p);
+        return;
+    }
     // normalise and store: lane (query l32, half) holds value rows 8*(r/4) + 4*half + r%4 of every 32-row tile
 #pragma unroll
     for (int qs = 0; qs < AT_NQ; ++qs) {
@@ -334,10 +396,10 @@ __global__ __launch_bounds__(AT_THREADS, 1) void kept_attention_kernel(AttnParam
 // arithmetic): the file is compiled with -mllvm -amdgpu-mfma-vgpr-form, without which a kernel that may use the whole
 // register file gets its MFMA results in the accumulation registers and a copy around every use.
 constexpr int AP_THREADS = 256;
-constexpr int AP_BQ = 256;                 // queries per workgroup
 constexpr int AP_TILE = 128 * 256;         // bytes of a K tile (128 keys x 256 B) and of a V^T tile (128 value rows x 128 keys)
 constexpr int AP_STAGE = 2 * AP_TILE;
-constexpr int AP_LDS = 2 * AP_STAGE;
+constexpr int ap_lds(int ks) { return ks == 1 ? 2 * AP_STAGE : share_lds<2, 128>(4); }  // (the shares take more than the stages)
+static_assert(share_lds<2, 128>(4) >= 2 * AP_STAGE && share_lds<2, 128>(4) <= 160 * 1024, "");
 constexpr int AP_NLD = 8;                  // 16-byte loads per thread, tile and stage
 
 __device__ __forceinline__ void ap_fence() { __builtin_amdgcn_sched_barrier(0); }
@@ -350,24 +412,25 @@ __device__ __forceinline__ void ap_settle() {
     __builtin_amdgcn_s_waitcnt(LGKMCNT0);
 }
 
+template <int KS>  // waves that share queries (see finish_shares)
 __global__ __launch_bounds__(AP_THREADS, 1) void kept_attention_pipe_kernel(AttnParams p) {
     using T = bf16_t;
     constexpr int NCH = 8;
+    constexpr int AP_BQ = 256 / KS;  // queries per workgroup
+    constexpr int SHARE = 4 / KS;    // key subtiles of a stage that a wave takes
     extern __shared__ __attribute__((aligned(16))) char smem[];
 
-    const int b = blockIdx.x, x = b % NUM_XCD, w_ = b / NUM_XCD;
-    const int slot = w_ / p.n_qblocks;
-    int qb = w_ - slot * p.n_qblocks;
-    const int h = x * p.heads_per_xcd + slot;
-    if (h >= p.H) return;
+    int h, qb;
     const bool causal = (p.flags & LEMO_CAUSAL) != 0;
+    decode_block(p.heads_per_xcd, p.H, causal ? 0 : p.n_qblocks, h, qb);  // causal: late query blocks (most keys) first
     if (causal) qb = p.n_qblocks - 1 - qb;
     const int g = (int)(((long long)h * p.H_kv) / p.H);
     const int tid = threadIdx.x, lane = tid & 63, half = lane >> 5, l32 = lane & 31;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);  // wave-uniform, and known to be: what follows from it stays scalar
     const int M = p.M;
     const float c2 = p.c2;
-    const int m0 = qb * AP_BQ, mw0 = m0 + wave * 64;
+    const int m0 = qb * AP_BQ, mw0 = m0 + wave / KS * 64;
+    const int part = wave % KS, sub0 = part * SHARE;  // the wave takes subtiles [sub0, sub0 + SHARE)
 
     // resident operand: this wave's 64 queries (rows gathered through idx), as MFMA B fragments
     u32x4 qf[2][NCH];
@@ -423,7 +486,7 @@ __global__ __launch_bounds__(AP_THREADS, 1) void kept_attention_pipe_kernel(Attn
 
     bool frozen = true;  // workgroup-uniform: which pass this is
     f32x16 o[2][4];      // O^T accumulators: o[qs][dv][r] = element (value row dv*32 + acc_row(r), query column l32 of subtile qs)
-    float ltot[2];
+    float ltot[2], o_ref[2];  // normaliser, and the reference it and o are relative to
     for (;;) {
 #pragma unroll
     for (int qs = 0; qs < 2; ++qs)
@@ -525,7 +588,7 @@ __global__ __launch_bounds__(AP_THREADS, 1) void kept_attention_pipe_kernel(Attn
             }
             if (active && !(causal && k0 > mw0 + 63)) {  // otherwise every key of the stage lies after every query of the wave
 #pragma unroll 1
-                for (int ks = 0; ks < 4; ++ks) {
+                for (int ks = sub0; ks < sub0 + SHARE; ++ks) {
                     const int kmin = k0 + ks * 32;
                     if (kmin >= M || (causal && kmin > mw0 + 63)) break;
                     u32x4 kfr[NCH], vfr[8];
@@ -602,16 +665,16 @@ __global__ __launch_bounds__(AP_THREADS, 1) void kept_attention_pipe_kernel(Attn
         bool more; int k0, nbuf, n_next; const char* sk; const char* sv; u32x4 kd, vd;
         stage_head(t, more, k0, nbuf, n_next, sk, sv, kd, vd);
 #pragma unroll
-        for (int c = 0; c < NCH; ++c) kf[c] = k_frag(sk, 0, c);
+        for (int c = 0; c < NCH; ++c) kf[c] = k_frag(sk, sub0, c);
         // the next stage's sixteen loads ride on the stage's first group, one per slot, so that they have the other seven
         // groups' time to land before the stage's closing wait
         auto ride = [&](int n) { stage_load_one(n, nbuf, n_next, kd, vd); };
         auto no_ride = [&](int) {};
-        group(OddT{}, sk, sv, 0, false, ride);      // ODD(4t - 1): logits of a(4t), product of a(4t-1), exponentials of b(4t-1)
+        group(OddT{}, sk, sv, sub0, false, ride);   // ODD(4t - 1): logits of a(4t), product of a(4t-1), exponentials of b(4t-1)
 #pragma unroll
-        for (int ks = 0; ks < 4; ++ks) {
-            group(EvenT{}, sk, sv, ks, ks < 3, no_ride);
-            if (ks < 3) group(OddT{}, sk, sv, ks, false, no_ride);
+        for (int ks = 0; ks < SHARE; ++ks) {
+            group(EvenT{}, sk, sv, sub0 + ks, ks < SHARE - 1, no_ride);
+            if (ks < SHARE - 1) group(OddT{}, sk, sv, sub0 + ks, false, no_ride);
         }
         stage_tail(t, more);
     };
@@ -626,7 +689,10 @@ __global__ __launch_bounds__(AP_THREADS, 1) void kept_attention_pipe_kernel(Attn
 #pragma unroll
         for (int n = 0; n < 8; ++n) vf[n] = u32x4{0u, 0u, 0u, 0u};
 #pragma unroll
-        for (int qs = 0; qs < 2; ++qs) nm[qs] = -(mrun[qs] == -INFINITY ? 0.f : mrun[qs]);
+        for (int qs = 0; qs < 2; ++qs) {
+            mrun[qs] = mrun[qs] == -INFINITY ? 0.f : mrun[qs];
+            nm[qs] = -mrun[qs];
+        }
         for (int t = 1; t < t_hot; ++t) hot_stage(t);
         // ... and ends by finishing the two that are left: a(last) has its probabilities, b(last) its logits
         consume(h0, 15, 0);
@@ -647,6 +713,7 @@ __global__ __launch_bounds__(AP_THREADS, 1) void kept_attention_pipe_kernel(Attn
     for (int qs = 0; qs < 2; ++qs) {
         const float l = la[qs] + lb[qs];
         ltot[qs] = l + __shfl_xor(l, 32);
+        o_ref[qs] = mrun[qs];
         bad |= !(ltot[qs] < 0x1p100f);
     }
     if (!frozen || !__syncthreads_or(bad)) break;
@@ -654,51 +721,73 @@ __global__ __launch_bounds__(AP_THREADS, 1) void kept_attention_pipe_kernel(Attn
     }
 
     // normalise and store: lane (query l32, half) holds value rows 8*(r/4) + 4*half + r%4 of every 32-row tile
+    if constexpr (KS == 1) {
 #pragma unroll
-    for (int qs = 0; qs < 2; ++qs) {
-        const float inv = ltot[qs] > 0.f ? 1.f / ltot[qs] : 0.f;
-        const int m = mw0 + qs * 32 + l32;
-        if (m >= M) continue;
-        uint16_t* orow = p.O + (long long)m * p.o_ts + (long long)h * p.o_hs;
+        for (int qs = 0; qs < 2; ++qs) {
+            const float inv = ltot[qs] > 0.f ? 1.f / ltot[qs] : 0.f;
+            const int m = mw0 + qs * 32 + l32;
+            if (m >= M) continue;
+            uint16_t* orow = p.O + (long long)m * p.o_ts + (long long)h * p.o_hs;
 #pragma unroll
-        for (int dv = 0; dv < 4; ++dv)
+            for (int dv = 0; dv < 4; ++dv)
 #pragma unroll
-            for (int gq = 0; gq < 4; ++gq) {
-                const int c0 = dv * 32 + gq * 8 + half * 4;
-                uint2 v;
-                v.x = pack_bf16x2_hw(o[qs][dv][gq * 4 + 0] * inv, o[qs][dv][gq * 4 + 1] * inv);
-                v.y = pack_bf16x2_hw(o[qs][dv][gq * 4 + 2] * inv, o[qs][dv][gq * 4 + 3] * inv);
-                *reinterpret_cast<uint2*>(orow + c0) = v;  // host guarantees 8-byte alignment of every output row
-            }
+                for (int gq = 0; gq < 4; ++gq) {
+                    const int c0 = dv * 32 + gq * 8 + half * 4;
+                    uint2 v;
+                    v.x = pack_bf16x2_hw(o[qs][dv][gq * 4 + 0] * inv, o[qs][dv][gq * 4 + 1] * inv);
+                    v.y = pack_bf16x2_hw(o[qs][dv][gq * 4 + 2] * inv, o[qs][dv][gq * 4 + 3] * inv);
+                    *reinterpret_cast<uint2*>(orow + c0) = v;  // host guarantees 8-byte alignment of every output row
+                }
+        }
+    } else {
+        __syncthreads();
+        finish_shares<KS, 2, 128>(o, o_ref, ltot, smem, 4, wave, lane, mw0, h, p);
     }
 }
 
-template <int D>
-static int launch_attn_t(AttnParams p, hipStream_t st) {
-    using G = AGeo<D>;
+template <int KS>
+static int launch_pipe(AttnParams p, hipStream_t st) {
     static std::once_flag once;
     static hipError_t attr_err = hipSuccess;
     std::call_once(once, [] {
-        attr_err = hipFuncSetAttribute(reinterpret_cast<const void*>(&kept_attention_kernel<D>), hipFuncAttributeMaxDynamicSharedMemorySize, G::LDS);
+        attr_err = hipFuncSetAttribute(reinterpret_cast<const void*>(&kept_attention_pipe_kernel<KS>), hipFuncAttributeMaxDynamicSharedMemorySize, ap_lds(KS));
     });
     if (attr_err != hipSuccess) return (int)attr_err;
-    p.heads_per_xcd = (p.H + NUM_XCD - 1) / NUM_XCD;
-#if LEMO_AT_PIPE
-    if (D == 128) {
-        static std::once_flag once2;
-        static hipError_t attr_err2 = hipSuccess;
-        std::call_once(once2, [] {
-            attr_err2 = hipFuncSetAttribute(reinterpret_cast<const void*>(&kept_attention_pipe_kernel), hipFuncAttributeMaxDynamicSharedMemorySize, AP_LDS);
-        });
-        if (attr_err2 != hipSuccess) return (int)attr_err2;
-        p.n_qblocks = (p.M + AP_BQ - 1) / AP_BQ;
-        hipLaunchKernelGGL(kept_attention_pipe_kernel, dim3((unsigned)(NUM_XCD * p.heads_per_xcd * p.n_qblocks)), dim3(AP_THREADS), AP_LDS, st, p);
-        return (int)hipGetLastError();
-    }
-#endif
-    p.n_qblocks = (p.M + AT_BQ - 1) / AT_BQ;
-    hipLaunchKernelGGL((kept_attention_kernel<D>), dim3((unsigned)(NUM_XCD * p.heads_per_xcd * p.n_qblocks)), dim3(AT_THREADS), G::LDS, st, p);
+    p.n_qblocks = (p.M + 256 / KS - 1) / (256 / KS);
+    hipLaunchKernelGGL(kept_attention_pipe_kernel<KS>, dim3((unsigned)(p.H * p.n_qblocks)), dim3(AP_THREADS), ap_lds(KS), st, p);
     return (int)hipGetLastError();
+}
+
+template <int D, int KS>
+static int launch_waves(AttnParams p, hipStream_t st) {
+    using G = AGeo<D>;
+    constexpr int LDS = KS > 1 && share_lds<AT_NQ, D>(AT_WAVES) > G::LDS ? share_lds<AT_NQ, D>(AT_WAVES) : G::LDS;
+    static std::once_flag once;
+    static hipError_t attr_err = hipSuccess;
+    std::call_once(once, [] {
+        attr_err = hipFuncSetAttribute(reinterpret_cast<const void*>(&kept_attention_kernel<D, KS>), hipFuncAttributeMaxDynamicSharedMemorySize, LDS);
+    });
+    if (attr_err != hipSuccess) return (int)attr_err;
+    constexpr int BQ = AT_WAVES / KS * 32 * AT_NQ;
+    p.n_qblocks = (p.M + BQ - 1) / BQ;
+    hipLaunchKernelGGL((kept_attention_kernel<D, KS>), dim3((unsigned)(p.H * p.n_qblocks)), dim3(AT_THREADS), LDS, st, p);
+    return (int)hipGetLastError();
+}
+
+// How many waves share queries, by the number n of 256-query blocks (one workgroup per CU, so up to 256 run at once):
+//   d = 128  1 keeps the hot stream's pace (9856 kept, 32 heads: 751 / 852 / 1279 us for 1 / 2 / 4); fewer blocks than CUs are
+//            cut in two or four, under the causal mask, where most blocks are short, up to n = 200: n = 32 (256 kept, 32
+//            heads) 23 / 20 / 18 us, n = 64 39 / 28 / 24, n = 144 62 / 46 / 59, n = 192 61 / 53 / 68, n = 416 118 / 137 / 194;
+//            full attention n = 160 72 / 95 / 104, n = 192 85 / 109 / 122
+//   d = 64   4 up to n = 480: n = 48 27 / 20.5 / 18, n = 192 69 / 47 / 46, n = 320 full 182 / 193 / 168, n = 432 208 / 208 / 198;
+//            n = 816 456 / 547 / 544, full 961 / 1080 / 1043
+static int launch_attn(AttnParams p, int d, hipStream_t st) {
+    p.heads_per_xcd = p.H % NUM_XCD == 0 ? p.H / NUM_XCD : 0;
+    const long long n = (long long)p.H * ((p.M + 255) / 256);
+    if (d == 64) return n <= 480 ? launch_waves<64, 4>(p, st) : launch_waves<64, 1>(p, st);
+    if (n <= 64) return launch_pipe<4>(p, st);
+    if (n <= ((p.flags & LEMO_CAUSAL) ? 200 : 128)) return launch_pipe<2>(p, st);
+    return launch_pipe<1>(p, st);
 }
 
 // V [S,H_kv,d] element strides v_ts, v_hs; workspace holds V^T of the kept rows: H_kv * d * Mpad bf16
@@ -727,7 +816,7 @@ int launch_kept_attention(const void* Q, const void* K, const void* V, long long
     p.k_bytes = (unsigned)(((S - 1) * k_ts + (long long)(H_kv - 1) * k_hs + d) * 2);
     p.c2 = c2;
     p.flags = flags;
-    return d == 128 ? launch_attn_t<128>(p, st) : launch_attn_t<64>(p, st);
+    return launch_attn(p, d, st);
 }
 
 }  // namespace lemo

@@ -966,6 +966,24 @@ def test_kept_attention_stage_and_block_edges(lemo, M, causal):
     assert_attention_close(wl.to_bf16_bits(O), want, wl.as_numpy(V)[idx])
 
 
+@pytest.mark.parametrize("causal", [True, False])
+@pytest.mark.parametrize("M,H,Hkv", [(385, 50, 25), (300, 104, 26), (641, 72, 24)])
+def test_kept_attention_larger_blocks(lemo, M, H, Hkv, causal):
+    """128-wide heads in launches with more blocks, where two waves or none share queries (the other tests run with four);
+    head counts that divide over the dies and that do not, one key that overtakes the frozen reference of its head group."""
+    say(f"[attention] larger blocks M={M} H={H}/{Hkv} causal={causal}")
+    S, d = M + 11, 128
+    Q, K = wl.tiny_qk(S, H, Hkv, d, "bf16", seed=M + H, heavy=3)
+    K[M // 2 + 5, 1] = K[M // 2 + 5, 1] * 40
+    V = torch.from_numpy(np.random.default_rng(M).standard_normal((S, Hkv, d)).astype(np.float32)).to(torch.bfloat16)
+    idx = np.sort(np.random.default_rng(M + 1).permutation(S)[:M]).astype(np.int32)
+    flags = lemo.CAUSAL if causal else 0
+    O = lemo.lemo_kept_attention(Q.cuda(), K.cuda(), V.cuda(), torch.from_numpy(idx).cuda(), flags=flags)
+    torch.cuda.synchronize()
+    want = oracle.kept_attention(wl.as_numpy(Q), wl.as_numpy(K), wl.as_numpy(V), idx, flags=flags)
+    assert_attention_close(wl.to_bf16_bits(O), want, wl.as_numpy(V)[idx])
+
+
 @pytest.mark.parametrize("dominant", [500, 840, 30])
 def test_kept_attention_reference_overflow_is_repaired(lemo, dominant):
     """With 128-wide heads the attention kernel freezes the reference of its exponentials in the stages of keys that need
