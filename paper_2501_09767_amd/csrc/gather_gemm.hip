@@ -537,7 +537,7 @@ static int launch_gg(const GgParams& p, lemo_dtype_t dt, hipStream_t st) {
         return 0;
     }
     const GgPlan plan = gg_plan(p.M, p.N, p.K, LAYOUT, dt);
-    if (plan.cols256 >= p.N) return launch_t256<ADD, LAYOUT>(p, st);
+    if (plan.cols256 >= p.N) return launch_t256<ADD, LAYOUT>(p, st);  // (never binary32)
     GgParams rest = p;
     if (plan.cols256 > 0) {
         GgParams head = p;
@@ -584,11 +584,11 @@ int launch_gather_gemm_dx(const void* dY, long long ldy, long long M, const void
 }
 
 // Weight gradient dW[n, c] = sum_m dY[m, n] X[idx[m], c], both operands read as they are stored (contraction-major),
-// the kept rows of X picked inside the B-tile load.  bf16.
+// the kept rows of X picked inside the B-tile load.
 int launch_gather_gemm_dw_direct(const void* dY, long long ldy, const void* X, long long S, long long ldx, const int* idx, long long M, void* dW,
-                                 long long lddw, int C, int N, hipStream_t st) {
+                                 long long lddw, int C, int N, lemo_dtype_t dt, hipStream_t st) {
     return launch_gg<false, GG_TN>({dY, X, nullptr, dW, idx, nullptr, ldy, ldx, lddw, /*output rows*/ N, 0, /*contraction*/ (int)M, /*columns*/ C, 0, 0,
-                                    span_bytes(M, ldy, N, LEMO_BF16), span_bytes(S, ldx, C, LEMO_BF16), 0}, LEMO_BF16, st);
+                                    span_bytes(M, ldy, N, dt), span_bytes(S, ldx, C, dt), 0}, dt, st);
 }
 
 }  // namespace lemo

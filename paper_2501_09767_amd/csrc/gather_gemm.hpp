@@ -16,7 +16,8 @@ namespace lemo {
 //          column l).  Two such reads make one 16-byte fragment: the same bytes from LDS as before, no transposed copy
 //          anywhere.
 //   GG_TN  both operands contraction-major: A [C, M], B [C, N] with B's rows picked by idx (the weight gradient: the
-//          contraction runs over the kept tokens).  bf16 only for GG_NN and GG_TN.
+//          contraction runs over the kept tokens).  GG_NN is bf16 only; binary32 fragments of GG_TN are read element by
+//          element, which is what its MFMAs take.
 enum { GG_NT = 0, GG_NN = 1, GG_TN = 2 };
 typedef __attribute__((ext_vector_type(4))) short s16x4;
 

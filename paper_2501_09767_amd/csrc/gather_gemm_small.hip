@@ -23,7 +23,7 @@ constexpr int SG_THREADS = 256;
 constexpr int SG_KB = 128;          // bytes of the contraction per slab
 constexpr int SG_EP = 64 * 4 + 16;  // LDS pitch of a row of 64 floats in the epilogue
 
-template <int GW> struct SgGeo {
+template <int GW, int ESZ> struct SgGeo {
     static constexpr int W = GW == 4 ? 2 : 1;       // waves of a group per output direction
     static constexpr int BM = 64 * W, BN = 64 * W;  // output tile
     static constexpr int GROUPS = 4 / GW;           // the slabs are dealt out to the groups in turn
@@ -33,20 +33,22 @@ template <int GW> struct SgGeo {
     static constexpr int TOK = GROUPS * 2 * STAGE;  // (GG_TN) token rings: per wave 4 slabs of 64 indices
     static constexpr int EPI = 4 * 64 * SG_EP;      // epilogue: a 64 x 64 block of floats per wave
     static constexpr int LDS = TOK + 4096 > EPI ? TOK + 4096 : EPI;
-    static constexpr int PIECES = 64 * W / 8;       // contraction-major slab: 16-byte pieces per row
+    static constexpr int KROWS = SG_KB / ESZ;       // contraction-major slab: rows,
+    static constexpr int PIECES = 4 * W * ESZ;      // 16-byte pieces per row
     // position of 16-byte piece p of row r (the loads fill consecutive LDS bytes, so conflicts are avoided by exchanging
     // pieces inside a row).  Rows along the contraction, 128 bytes: p ^ (r / 2 % 8) spreads one piece of 16 rows over all
-    // banks.  Contraction-major rows: the transposing read takes 4 rows x 4 pieces at a time.
+    // banks.  Contraction-major rows: the transposing read (16 bit) takes 4 rows x 4 pieces at a time; of binary32 rows, which
+    // are read element by element, the two half-waves take rows 4 apart, 8 pieces each.
     __device__ static constexpr int swz(int r) { return (r >> 1) & 7; }
-    __device__ static constexpr int kswz(int r) { return GW == 4 ? (r & 3) << 2 : ((r >> 1) & 1) << 2; }
+    __device__ static constexpr int kswz(int r) { return ESZ == 4 ? ((r >> 2) & 1) << 3 : GW == 4 ? (r & 3) << 2 : ((r >> 1) & 1) << 2; }
 };
 
 template <typename T, bool ADD, int LAYOUT, int GW>
 __global__ __launch_bounds__(SG_THREADS, GW == 4 ? 2 : 1) void gather_gemm_small_kernel(GgParams p) {
-    static_assert(LAYOUT == GG_NT || sizeof(T) == 2, "the contraction-major layouts are built for 16-bit elements");
     constexpr bool A_KMAJOR = LAYOUT == GG_TN, B_KMAJOR = LAYOUT != GG_NT;
-    using G = SgGeo<GW>;
-    constexpr int GROUPS = G::GROUPS, NLD = G::NLD, ESZ = (int)sizeof(T);
+    constexpr int ESZ = (int)sizeof(T);
+    using G = SgGeo<GW, ESZ>;
+    constexpr int GROUPS = G::GROUPS, NLD = G::NLD;
     extern __shared__ __attribute__((aligned(16))) char smem[];
 
     int tm, tn;
@@ -61,7 +63,7 @@ __global__ __launch_bounds__(SG_THREADS, GW == 4 ? 2 : 1) void gather_gemm_small
     const T* B = static_cast<const T*>(p.B);
     const unsigned lda_bytes = (unsigned)p.lda * ESZ, ldb_bytes = (unsigned)p.ldb * ESZ;  // host: both < 2^23
     const int K = p.K, kbytes = K * ESZ;  // (along-the-contraction operands: bytes of a row)
-    const int nk = A_KMAJOR ? (K + 63) / 64 : (kbytes + SG_KB - 1) / SG_KB;
+    const int nk = A_KMAJOR ? (K + G::KROWS - 1) / G::KROWS : (kbytes + SG_KB - 1) / SG_KB;
 
     // Per-thread byte offsets of the loads.  The hardware range check sees the per-thread offset only: rows past an
     // operand's end fail it (or are clamped to the last one, A), pieces past the end of the contraction are given an
@@ -80,7 +82,7 @@ __global__ __launch_bounds__(SG_THREADS, GW == 4 ? 2 : 1) void gather_gemm_small
         }
         if constexpr (LAYOUT == GG_NT) b_voff[i] = (u / 8) * ldb_bytes + kpos(i);
         else if constexpr (LAYOUT == GG_NN) b_voff[i] = krow * ldb_bytes + kcol;
-        else b_voff[i] = (unsigned)n0 * 2u + kcol;  // + the token's row, per slab
+        else b_voff[i] = (unsigned)n0 * ESZ + kcol;  // + the token's row, per slab
     }
     const int b_rows = min(G::BN, p.N - n0);
     const unsigned bn_bytes = (b_rows - 1) * ldb_bytes + kbytes;  // (GG_NT) this tile's rows of B
@@ -88,7 +90,7 @@ __global__ __launch_bounds__(SG_THREADS, GW == 4 ? 2 : 1) void gather_gemm_small
     // refuses the rows past it (host: the operand spans < 2^31 bytes)
     auto kmajor_rsrc = [&](const T* col0, unsigned ld_bytes, unsigned cols, int kt) {
         const bool live = kt < nk;
-        const unsigned off = live ? (unsigned)kt * 64u * ld_bytes : 0u;
+        const unsigned off = live ? (unsigned)(kt * G::KROWS) * ld_bytes : 0u;
         const unsigned size = live ? (unsigned)(K - 1) * ld_bytes + cols * ESZ - off : 0u;
         return raw_rsrc(reinterpret_cast<const char*>(col0) + off, size);
     };
@@ -96,7 +98,7 @@ __global__ __launch_bounds__(SG_THREADS, GW == 4 ? 2 : 1) void gather_gemm_small
     const unsigned lds_tok = lds_offset_of(smem) + G::TOK + wave * 1024;
     const u32x4 idx_rsrc = raw_rsrc(p.idx, p.idx ? (long long)K * 4 : 0);
     auto issue_tokens = [&](int it) {  // indices of the group's slab `it` into its ring entry
-        if constexpr (LAYOUT == GG_TN) lds_direct_b32(idx_rsrc, lds_tok + (it & 3) * 256, (it * GROUPS + group) * 256 + lane * 4);
+        if constexpr (LAYOUT == GG_TN) lds_direct_b32(idx_rsrc, lds_tok + (it & 3) * 256, (it * GROUPS + group) * (G::KROWS * 4) + lane * 4);
     };
     // one of the 2 * NLD loads of the group's slab `it`: A pieces first, then B pieces
     struct Slab { u32x4 a, b; int soff, left; unsigned a_none, b_none, stage; };
@@ -129,7 +131,7 @@ __global__ __launch_bounds__(SG_THREADS, GW == 4 ? 2 : 1) void gather_gemm_small
         if constexpr (LAYOUT == GG_TN) {
 #pragma unroll
             for (int i = 0; i < NLD; ++i) {
-                const int krow = (i * 64 * GW + gtid) / G::PIECES, k = (it * GROUPS + group) * 64 + krow;
+                const int krow = (i * 64 * GW + gtid) / G::PIECES, k = (it * GROUPS + group) * G::KROWS + krow;
                 const unsigned row = p.idx ? *reinterpret_cast<const unsigned*>(smem + G::TOK + wave * 1024 + (it & 3) * 256 + krow * 4) : (unsigned)k;
                 tok[i] = k < K ? row * ldb_bytes + b_voff[i] : p.b_bytes;
             }
@@ -156,6 +158,14 @@ __global__ __launch_bounds__(SG_THREADS, GW == 4 ? 2 : 1) void gather_gemm_small
         if (!kmajor) {
             const int row = w * 64 + i * 32 + l32;
             return *reinterpret_cast<const u32x4*>(region + row * SG_KB + (((2 * c + half) ^ G::swz(row)) << 4));
+        }
+        if constexpr (ESZ == 4) {  // binary32: an MFMA takes one element per lane, rows 8c + 4 * half + {0..3} of its own column
+            const int col = w * 64 + i * 32 + l32, row = 8 * c + 4 * half;
+            const char* at = region + row * (G::PIECES * 16) + (((col >> 2) ^ G::kswz(row)) << 4) + (col & 3) * 4;
+            u32x4 v;
+#pragma unroll
+            for (int e = 0; e < 4; ++e) v[e] = *reinterpret_cast<const unsigned*>(at + e * G::PIECES * 16);
+            return v;
         }
         const int piece = (w * 8 + i * 4 + (l32 >> 4) * 2 + ((l32 & 3) >> 1)) ^ G::kswz(trow);
         const char* at = region + (trow + c * 16) * (G::PIECES * 16) + piece * 16 + (l32 & 1) * 8;
@@ -358,7 +368,7 @@ __global__ __launch_bounds__(SG_THREADS, GW == 4 ? 2 : 1) void gather_gemm_small
 
 template <typename T, bool ADD, int LAYOUT, int GW>
 static int launch_small(GgParams p, hipStream_t st) {
-    using G = SgGeo<GW>;
+    using G = SgGeo<GW, (int)sizeof(T)>;
     static std::once_flag once;
     static hipError_t attr_err = hipSuccess;
     std::call_once(once, [] {
@@ -375,7 +385,10 @@ static int launch_small(GgParams p, hipStream_t st) {
 
 template <int GW>
 static int launch_small_form(const GgParams& p, lemo_dtype_t dt, bool add, int layout, hipStream_t st) {
-    if (dt == LEMO_F32) return add ? launch_small<float, true, GG_NT, GW>(p, st) : launch_small<float, false, GG_NT, GW>(p, st);
+    if (dt == LEMO_F32) {
+        if (layout == GG_TN) return launch_small<float, false, GG_TN, GW>(p, st);
+        return add ? launch_small<float, true, GG_NT, GW>(p, st) : launch_small<float, false, GG_NT, GW>(p, st);
+    }
     if (layout == GG_NN) return launch_small<bf16_t, true, GG_NN, GW>(p, st);
     if (layout == GG_TN) return launch_small<bf16_t, false, GG_TN, GW>(p, st);
     return add ? launch_small<bf16_t, true, GG_NT, GW>(p, st) : launch_small<bf16_t, false, GG_NT, GW>(p, st);

@@ -407,10 +407,11 @@ int lemo_gather_gemm_dx(const void* dY, int64_t ldy, int64_t M, const void* W, i
     return hip_rc(launch_gather_gemm_dx(dY, ldy, M, W, ldw, dX, lddx, S_out, out_idx, C, N, static_cast<hipStream_t>(stream)));
 }
 
-// bf16 takes the kernel that reads both operands as they are stored when their spans fit its 32-bit offsets
+// the kernels that read both operands as they are stored take them when their spans fit the 32-bit offsets
 static bool dw_direct(int64_t ldy, int64_t S, int64_t ldx, int64_t M, int32_t C, int32_t N, lemo_dtype_t dt) {
-    return dt == LEMO_BF16 && ldy * 2 < (1 << 23) && ldx * 2 < (1 << 23) && ((M - 1) * ldy + N) * 2 < ((int64_t)1 << 31) &&
-           ((S - 1) * ldx + C) * 2 < ((int64_t)1 << 32) - 16;
+    const int64_t esz = dt == LEMO_BF16 ? 2 : 4;
+    return ldy * esz < (1 << 23) && ldx * esz < (1 << 23) && ((M - 1) * ldy + N) * esz < ((int64_t)1 << 31) &&
+           ((S - 1) * ldx + C) * esz < ((int64_t)1 << 32) - 16;
 }
 
 int lemo_gather_gemm_dw_workspace_bytes(int64_t M, int32_t C, int32_t N, lemo_dtype_t dt, size_t* bytes) {
@@ -435,10 +436,10 @@ int lemo_gather_gemm_dw(const void* dY, int64_t ldy, const void* X, int64_t S, i
     if ((M > 0 && (!aligned16(dY) || !aligned16(X))) || ldy % e16 || ldx % e16) return LEMO_ERR_ALIGN;
     if (reinterpret_cast<uintptr_t>(dW) % (dt == LEMO_BF16 ? 2 : 4)) return LEMO_ERR_ALIGN;
     if (kept_idx && (reinterpret_cast<uintptr_t>(kept_idx) & 3u)) return LEMO_ERR_ALIGN;
-    if (M > 0 && dw_direct(ldy, S, ldx, M, C, N, dt)) {  // both operands read where they lie: no workspace
+    if (M > 0 && dt == LEMO_BF16 && dw_direct(ldy, S, ldx, M, C, N, dt)) {  // both operands read where they lie: no workspace
         const int64_t tiles = (((int64_t)N + 255) / 256) * (((int64_t)C + 255) / 256);
         if (tiles >= (int64_t)1 << 28) return LEMO_ERR_UNSUPPORTED;
-        return hip_rc(launch_gather_gemm_dw_direct(dY, ldy, X, S, ldx, kept_idx, M, dW, lddw, C, N, static_cast<hipStream_t>(stream)));
+        return hip_rc(launch_gather_gemm_dw_direct(dY, ldy, X, S, ldx, kept_idx, M, dW, lddw, C, N, dt, static_cast<hipStream_t>(stream)));
     }
     if (M == 0) return hip_rc(launch_zero_matrix(dW, lddw, C, N, dt, static_cast<hipStream_t>(stream)));  // an empty sum: dW = 0
     if (dt == LEMO_BF16) return LEMO_ERR_UNSUPPORTED;  // operands beyond the 32-bit offsets of the kernel
@@ -451,6 +452,9 @@ int lemo_gather_gemm_dw(const void* dY, int64_t ldy, const void* X, int64_t S, i
     if (Mpad * esz >= (1 << 23) || (int64_t)N * Mpad * esz >= ((int64_t)1 << 32)) return LEMO_ERR_UNSUPPORTED;  // limits of the GEMM on the transposed operands
     const int64_t tiles = (((int64_t)N + 255) / 256) * (((int64_t)C + 255) / 256);
     if (tiles >= (int64_t)1 << 28) return LEMO_ERR_UNSUPPORTED;
+    // binary32 reads its operands where they lie as well; the workspace is for operands beyond the 32-bit offsets
+    if (dw_direct(ldy, S, ldx, M, C, N, dt))
+        return hip_rc(launch_gather_gemm_dw_direct(dY, ldy, X, S, ldx, kept_idx, M, dW, lddw, C, N, dt, static_cast<hipStream_t>(stream)));
     return hip_rc(launch_gather_gemm_dw(dY, ldy, X, S, ldx, kept_idx, M, dW, lddw, C, N, dt, workspace, static_cast<hipStream_t>(stream)));
 }
 

@@ -661,7 +661,7 @@ def test_gather_gemm_add_exact_cases(lemo):
     ("nt", 63, 66, 36, "f32"), ("add", 129, 65, 516, "f32"), ("dw", 68, 260, 131, "f32"),
     # 128 x 128 tiles
     ("nt", 1000, 1500, 200, "bf16"), ("add", 1023, 1409, 136, "bf16"), ("dx", 1025, 1416, 72, "bf16"), ("dw", 2056, 3080, 300, "bf16"),
-    ("nt", 2049, 1537, 20, "f32"), ("add", 1700, 1931, 132, "f32"),
+    ("nt", 2049, 1537, 20, "f32"), ("add", 1700, 1931, 132, "f32"), ("dw", 1924, 2060, 70, "f32"),
     # 256 x 256 tiles, and their whole rounds with 128 x 128 tiles behind them
     ("nt", 4000, 4090, 520, "bf16"), ("nt", 2817, 5701, 1032, "bf16"), ("add", 2817, 5703, 1096, "bf16"), ("dx", 2817, 5704, 1096, "bf16")])
 def test_gather_gemm_tiles_exact(lemo, form, M, N, K, dtype):
