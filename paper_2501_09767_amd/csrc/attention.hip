@@ -13,8 +13,12 @@
 //                     registers 8c..8c+7 of the logit tile are keys 16c + 4*half + {0..3} and 16c + 8 + 4*half + {0..3},
 //                     and since a dot product does not care in which order its terms are paired, the A operand (V^T)
 //                     simply supplies the same keys in the same slots.
-// V^T needs the keys contiguous per value column, which the [token, head, d] layout does not offer; a small kernel first
-// writes the kept rows of V transposed ([H_kv, d, M] in the workspace; 2 bytes per kept element, once per call).
+// V^T needs the keys contiguous per value column, which the [token, head, d] layout does not offer: the kept rows of V go
+// to LDS as they are and the A fragments come out through the transposing LDS read (ds_read_b64_tr_b16: a 16-lane group
+// pointed at 4 rows x 16 columns hands every lane 4 consecutive rows of its own column; lane 4 j + q points at row j, column
+// quad q).  Its rows are free to choose, so the two reads of a fragment take just the keys the lane's registers hold.
+// (Writing the kept rows of V transposed into the workspace first took 5 us at 256 kept tokens, 14 us at 3280, 34 us at
+// 9856, all with 32 heads.)
 // P is rounded to bf16 for the second product (as in every flash-attention kernel); the normaliser is summed from the
 // unrounded values.
 #include <mutex>
@@ -36,73 +40,52 @@ namespace lemo {
 constexpr int AT_THREADS = LEMO_AT_THREADS, AT_WAVES = AT_THREADS / 64;
 constexpr int AT_NQ = LEMO_AT_NQ;                   // 32-query subtiles per wave
 constexpr int AT_KT = 128;                          // keys per LDS stage
-constexpr int AT_MPAD = 128;         // the transposed V is padded to a multiple of this many kept tokens
+typedef __attribute__((ext_vector_type(4))) short s16x4;
 
 template <int D> struct AGeo {
     static constexpr int ROWB = D * 2;            // bytes per head row (bf16)
     static constexpr int NCH = ROWB / 32;         // MFMA chunks per K / Q row
     static constexpr int CPR = ROWB / 16;         // 16-byte pieces per K row
     static constexpr int KSTRIDE = ROWB + 16;     // LDS pitch of a K row
-    static constexpr int VSTRIDE = AT_KT * 2 + 16;  // LDS pitch of a V^T row (128 keys)
+    static constexpr int VSTRIDE = ROWB;          // V rows are unpadded: piece p of row r sits at p ^ vswz(r), so that the 4 rows x 4
+    __device__ static constexpr int vswz(int r) { return D == 64 ? ((r >> 1) & 1) << 2 : (r & 3) << 2; }  // pieces of a transposing read fill all banks
     static constexpr int NDV = D / 32;            // 32-row tiles of the value dimension
     static constexpr int NLK = AT_KT * CPR / AT_THREADS;  // K loads per thread and stage
     static constexpr int K_RPL = AT_THREADS / CPR;        // K rows covered by one load of the workgroup
-    static constexpr int VCPR = AT_KT * 2 / 16;           // 16-byte pieces per V^T row of a stage
-    static constexpr int NLV = D * VCPR / AT_THREADS;     // V^T loads per thread and stage
-    static constexpr int V_RPL = AT_THREADS / VCPR;       // V^T rows covered by one load of the workgroup
-    static constexpr int STAGE = AT_KT * KSTRIDE + D * VSTRIDE;
+    static constexpr int STAGE = AT_KT * (KSTRIDE + VSTRIDE);
     static constexpr int LDS = 2 * STAGE;
 };
 
 struct AttnParams {
     const uint16_t* Q;
     const uint16_t* K;
-    const uint16_t* Vt;  // [H_kv, D, Mpad]
+    const uint16_t* V;
     const int* idx;      // [M] or null
     uint16_t* O;
-    int M, Mpad, H, H_kv;
-    long long q_ts, q_hs, k_ts, k_hs, o_ts, o_hs;  // element strides
-    unsigned q_bytes, k_bytes;                     // spans of Q and K (32-bit buffer offsets)
+    int M, H, H_kv;
+    int v_compact;       // V holds the kept rows only (row n belongs to kept token n)
+    long long q_ts, q_hs, k_ts, k_hs, v_ts, v_hs, o_ts, o_hs;  // element strides
+    unsigned q_bytes, k_bytes, v_bytes;            // spans of Q, of K, of one head of V (32-bit buffer offsets)
     float c2;
     unsigned flags;
     int n_qblocks, heads_per_xcd;
 };
 
-// Inside every group of 16 kept tokens the transposed V is stored with its two middle quads exchanged (tokens 0-3, 8-11,
-// 4-7, 12-15): the 8 key slots a lane feeds to the second MFMA are keys 4*half + {0..3} and 8 + 4*half + {0..3} of a
-// 16-key chunk, and in this order they are 16 contiguous bytes.  The permutation is its own inverse.
-__device__ __forceinline__ int vt_src(int pos) { return (pos & ~12) | ((pos & 4) << 1) | ((pos & 8) >> 1); }
+// The kept rows of V, compact: [H_kv, M, D].  Only for a V that 32-bit offsets do not reach across.
+__global__ __launch_bounds__(256) void gather_v_kernel(const uint16_t* __restrict__ V, long long v_ts, long long v_hs, const int* __restrict__ idx,
+                                                       int M, int D, uint16_t* __restrict__ out) {
+    const int lpr = D / 8, m = blockIdx.x * (256 / lpr) + threadIdx.x / lpr, g = blockIdx.y, c0 = threadIdx.x % lpr * 8;
+    if (m >= M) return;
+    const long long tok = idx ? idx[m] : m;
+    *reinterpret_cast<u32x4*>(out + ((long long)g * M + m) * D + c0) = *reinterpret_cast<const u32x4*>(V + tok * v_ts + (long long)g * v_hs + c0);
+}
 
-// kept rows of V, transposed: Vt[g][c][pos] = V[idx[vt_src(pos)], g, c] for kept tokens below M, zero up to Mpad
-__global__ __launch_bounds__(256) void gather_vt_kernel(const uint16_t* __restrict__ V, long long v_ts, long long v_hs, const int* __restrict__ idx,
-                                                        int M, int Mpad, int D, uint16_t* __restrict__ Vt) {
-    __shared__ uint16_t tile[64][128 + 2];
-    const int m0 = blockIdx.x * 64, g = blockIdx.y, tid = threadIdx.x;
-    // load 64 kept rows x D values: thread -> (row = tid / 16 + 16 * i, 8 values at (tid % 16) * 8)
-    for (int i = 0; i < 4; ++i) {
-        const int row = tid / 16 + 16 * i, c0 = (tid % 16) * 8, m = m0 + row;
-        u32x4 v = {0u, 0u, 0u, 0u};
-        if (m < M && c0 < D) {
-            const long long tok = idx ? idx[m] : m;
-            v = *reinterpret_cast<const u32x4*>(V + tok * v_ts + (long long)g * v_hs + c0);
-        }
-        if (c0 < D) {
-            const uint32_t w[4] = {v.x, v.y, v.z, v.w};
-#pragma unroll
-            for (int e = 0; e < 8; ++e) tile[row][c0 + e] = (uint16_t)(w[e >> 1] >> ((e & 1) * 16));
-        }
-    }
-    __syncthreads();
-    // store: value column c, 64 consecutive kept tokens = 128 bytes; thread -> (c = tid / 8 + 32 * i, 8 tokens at (tid % 8) * 8)
-    for (int i = 0; i < 4; ++i) {
-        const int c = tid / 8 + 32 * i, r0 = (tid % 8) * 8;
-        if (c < D) {
-            uint32_t w[4];
-#pragma unroll
-            for (int e = 0; e < 4; ++e) w[e] = (uint32_t)tile[vt_src(r0 + 2 * e)][c] | ((uint32_t)tile[vt_src(r0 + 2 * e + 1)][c] << 16);
-            *reinterpret_cast<u32x4*>(Vt + ((long long)g * D + c) * Mpad + m0 + r0) = u32x4{w[0], w[1], w[2], w[3]};
-        }
-    }
+// One fragment of V^T: 16 bytes = this lane's value column, 4 keys from `at` on and 4 keys 8 rows further (byte pitch PITCH)
+template <int PITCH> __device__ __forceinline__ u32x4 v_fragment(const char* at) {
+    const s16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((s16x4 __attribute__((address_space(3)))*)(at));
+    const s16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((s16x4 __attribute__((address_space(3)))*)(at + 8 * PITCH));
+    const uint2 l2 = __builtin_bit_cast(uint2, lo), h2 = __builtin_bit_cast(uint2, hi);
+    return u32x4{l2.x, l2.y, h2.x, h2.y};
 }
 
 // Several waves may hold the same queries and take the key subtiles of every stage in shares (KS consecutive waves); a
@@ -211,14 +194,16 @@ __global__ __launch_bounds__(AT_THREADS, 1) void kept_attention_kernel(AttnParam
     const int nstage = k_last / AT_KT + 1;
 
     // staging.  K rows are gathered through idx (32-bit offsets into a range-checked descriptor of the whole K tensor);
-    // V^T rows are contiguous in the workspace.
+    // the V rows of the same tokens likewise (or from the compact copy).
     const int k_row = tid / G::CPR, k_cc = tid % G::CPR;
     const int k_row_bytes = (int)p.k_ts * 2;
     const __amdgpu_buffer_rsrc_t k_rsrc = __builtin_amdgcn_make_buffer_rsrc(
         const_cast<char*>(reinterpret_cast<const char*>(p.K + (long long)g * p.k_hs)), 0, (int)(p.k_bytes - (unsigned)(g * p.k_hs * 2)), 0x00020000);
-    const int v_row = tid / G::VCPR, v_cc = tid % G::VCPR;
-    const uint16_t* vt_head = p.Vt + (long long)g * D * p.Mpad;
-    u32x4 prek[G::NLK], prev_[G::NLV];
+    const __amdgpu_buffer_rsrc_t v_rsrc = __builtin_amdgcn_make_buffer_rsrc(
+        const_cast<char*>(reinterpret_cast<const char*>(p.V + (long long)g * p.v_hs)), 0, (int)p.v_bytes, 0x00020000);
+    const unsigned v_row_bytes = (unsigned)p.v_ts * 2u;
+    u32x4 prek[G::NLK], prev_[G::NLK];
+    const int v_row = 4 * half + ((l32 & 15) >> 2), v_col = (l32 >> 4) * 32 + (l32 & 3) * 8;  // this lane's corner of a transposing read
     // Row indices run one stage ahead of the rows (tok holds the K rows of the stage about to be fetched), so a row load
     // never waits behind its own index; rows past the end repeat the last kept row (masked later).
     unsigned tok[G::NLK];
@@ -238,8 +223,10 @@ __global__ __launch_bounds__(AT_THREADS, 1) void kept_attention_kernel(AttnParam
         for (int i = 0; i < G::NLK; ++i)
             prek[i] = __builtin_amdgcn_raw_buffer_load_b128(k_rsrc, (int)(tok[i] * (unsigned)k_row_bytes + (unsigned)k_cc * 16u), 0, 0);
 #pragma unroll
-        for (int i = 0; i < G::NLV; ++i)  // the padded length is a multiple of the stage length: always in range
-            prev_[i] = *reinterpret_cast<const u32x4*>(vt_head + (long long)(v_row + i * G::V_RPL) * p.Mpad + n0 + v_cc * 8);
+        for (int i = 0; i < G::NLK; ++i) {
+            const unsigned row = p.v_compact ? (unsigned)min(n0 + k_row + i * G::K_RPL, M - 1) : tok[i];
+            prev_[i] = __builtin_amdgcn_raw_buffer_load_b128(v_rsrc, (int)(row * v_row_bytes + (unsigned)k_cc * 16u), 0, 0);
+        }
         fetch_idx(t + 1);  // clamped to the last kept row, so any t is fine
     };
     auto stash = [&](int buf) {
@@ -247,7 +234,7 @@ __global__ __launch_bounds__(AT_THREADS, 1) void kept_attention_kernel(AttnParam
 #pragma unroll
         for (int i = 0; i < G::NLK; ++i) *reinterpret_cast<u32x4*>(s + (k_row + i * G::K_RPL) * G::KSTRIDE + k_cc * 16) = prek[i];
 #pragma unroll
-        for (int i = 0; i < G::NLV; ++i) *reinterpret_cast<u32x4*>(s + AT_KT * G::KSTRIDE + (v_row + i * G::V_RPL) * G::VSTRIDE + v_cc * 16) = prev_[i];
+        for (int i = 0; i < G::NLK; ++i) *reinterpret_cast<u32x4*>(s + AT_KT * G::KSTRIDE + (k_row + i * G::K_RPL) * G::VSTRIDE + ((k_cc ^ G::vswz(k_row + i * G::K_RPL)) << 4)) = prev_[i];
     };
 
     fetch_idx(0);
@@ -269,14 +256,12 @@ __global__ __launch_bounds__(AT_THREADS, 1) void kept_attention_kernel(AttnParam
 #pragma unroll
                 for (int c = 0; c < G::NCH; ++c) kf[c] = *reinterpret_cast<const u32x4*>(&sk[(ks * 32 + l32) * G::KSTRIDE + c * 32 + half * 16]);
                 // V^T fragments of this key subtile: value row dv*32 + l32, keys 16c + 4*half + {0..3} and 16c + 8 + 4*half + {0..3}
-                // (contiguous in the quad-exchanged layout)
                 u32x4 vf[G::NDV][2];
 #pragma unroll
                 for (int dv = 0; dv < G::NDV; ++dv)
 #pragma unroll
-                    for (int c = 0; c < 2; ++c) {
-                        vf[dv][c] = *reinterpret_cast<const u32x4*>(&sv[(dv * 32 + l32) * G::VSTRIDE + (ks * 32 + 16 * c + 8 * half) * 2]);
-                    }
+                    for (int c = 0; c < 2; ++c)
+                        vf[dv][c] = v_fragment<G::VSTRIDE>(&sv[(ks * 32 + 16 * c + v_row) * G::VSTRIDE + ((dv * 4 ^ G::vswz(v_row)) << 4) + v_col]);
 #pragma unroll
                 for (int qs = 0; qs < AT_NQ; ++qs) {
                     const int qmin = mw0 + qs * 32;
@@ -390,13 +375,13 @@ __global__ __launch_bounds__(AT_THREADS, 1) void kept_attention_kernel(AttnParam
 // transcendental unit, and every running sum is pinned where it is written (the compiler would otherwise postpone the
 // additions and park each exponential in a spare register).  A wave's stages come in three runs -- the first stage,
 // the hot stages, the rest -- each a loop of its own, which keeps the register allocator's view of the hot stream clean.
-// Stages (128 keys: K rows and V^T rows, 64 KB) are filled by LDS-direct loads that ride on the first key subtile of
-// the stage before, with the rows' indices fetched two stages ahead; rows are unpadded and piece p of row r sits at
-// position p ^ (r mod 16).  The MFMAs of this file must write ordinary vector registers (their results feed vector
+// Stages (128 keys: K rows and V rows, 64 KB) are filled by LDS-direct loads that ride on the first key subtile of
+// the stage before, with the rows' indices fetched two stages ahead; rows are unpadded and piece p of a K row r sits
+// at position p ^ (r mod 16), of a V row at p ^ 4 (r mod 4).  The MFMAs of this file must write ordinary vector registers (their results feed vector
 // arithmetic): the file is compiled with -mllvm -amdgpu-mfma-vgpr-form, without which a kernel that may use the whole
 // register file gets its MFMA results in the accumulation registers and a copy around every use.
 constexpr int AP_THREADS = 256;
-constexpr int AP_TILE = 128 * 256;         // bytes of a K tile (128 keys x 256 B) and of a V^T tile (128 value rows x 128 keys)
+constexpr int AP_TILE = 128 * 256;         // bytes of a K tile and of a V tile (128 keys x 256 B)
 constexpr int AP_STAGE = 2 * AP_TILE;
 constexpr int ap_lds(int ks) { return ks == 1 ? 2 * AP_STAGE : share_lds<2, 128>(4); }  // (the shares take more than the stages)
 static_assert(share_lds<2, 128>(4) >= 2 * AP_STAGE && share_lds<2, 128>(4) <= 160 * 1024, "");
@@ -412,7 +397,10 @@ __device__ __forceinline__ void ap_settle() {
     __builtin_amdgcn_s_waitcnt(LGKMCNT0);
 }
 
-template <int KS>  // waves that share queries (see finish_shares)
+// KS: waves that share queries (see finish_shares).  SAME_ROWS: K and V have the same token stride and are picked by the
+// same list, so a V row's offset is its K row's plus a constant (8 registers less, which is what keeps the hot stream from
+// spilling); otherwise it has registers of its own.
+template <int KS, bool SAME_ROWS>
 __global__ __launch_bounds__(AP_THREADS, 1) void kept_attention_pipe_kernel(AttnParams p) {
     using T = bf16_t;
     constexpr int NCH = 8;
@@ -454,25 +442,34 @@ __global__ __launch_bounds__(AP_THREADS, 1) void kept_attention_pipe_kernel(Attn
     const int s_row = tid >> 4, s_piece = (tid & 15) ^ (s_row & 15);
     const int k_row_bytes = (int)p.k_ts * 2;
     const u32x4 k_rsrc = raw_rsrc(reinterpret_cast<const char*>(p.K + (long long)g * p.k_hs), (long long)p.k_bytes - (long long)g * p.k_hs * 2);
-    const u32x4 v_rsrc = raw_rsrc(reinterpret_cast<const char*>(p.Vt + (long long)g * 128 * p.Mpad), (long long)128 * p.Mpad * 2);
-    int v_voff[AP_NLD];
-#pragma unroll
-    for (int i = 0; i < AP_NLD; ++i) v_voff[i] = (i * 16 + s_row) * p.Mpad * 2 + s_piece * 16;
-    unsigned tok[AP_NLD], tok_next[AP_NLD];  // byte offsets of the K rows of the stage being requested / of the one after it
-    auto fetch_tok = [&](int t, unsigned (&dst)[AP_NLD]) {  // rows past the end repeat the last kept row (masked later)
-        const int n0 = t * AT_KT;
+    const u32x4 v_rsrc = raw_rsrc(reinterpret_cast<const char*>(p.V + (long long)g * p.v_hs), (long long)p.v_bytes);
+    const int v_row_bytes = (int)p.v_ts * 2, v_piece = (tid & 15) ^ ((s_row & 3) << 2);  // V rows: position tid%16 holds piece (tid%16) ^ 4*(row%4)
+    const unsigned v_delta = (unsigned)(v_piece - s_piece) * 16u;
+    unsigned k_voff[AP_NLD], v_voff[SAME_ROWS ? 1 : AP_NLD];  // byte offsets of the K and V rows of the stage being requested
+    int tok[AP_NLD];                          // the tokens of the stage after it
+    auto fetch_tok = [&](int t) {  // rows past the end repeat the last kept row (masked later)
 #pragma unroll
         for (int i = 0; i < AP_NLD; ++i) {
-            const int n = min(n0 + i * 16 + s_row, M - 1);
-            dst[i] = (unsigned)(p.idx ? p.idx[n] : n) * (unsigned)k_row_bytes + (unsigned)s_piece * 16u;
+            const int n = min(t * AT_KT + i * 16 + s_row, M - 1);
+            tok[i] = p.idx ? p.idx[n] : n;
+        }
+    };
+    auto take_tok = [&](int t) {  // tok holds stage t's tokens
+#pragma unroll
+        for (int i = 0; i < AP_NLD; ++i) {
+            k_voff[i] = (unsigned)tok[i] * (unsigned)k_row_bytes + (unsigned)s_piece * 16u;
+            if constexpr (!SAME_ROWS) {
+                const int vn = p.v_compact ? min(t * AT_KT + i * 16 + s_row, M - 1) : tok[i];
+                v_voff[i] = (unsigned)vn * (unsigned)v_row_bytes + (unsigned)v_piece * 16u;
+            }
         }
     };
     const unsigned lds_w = lds_offset_of(smem) + (unsigned)wave * 1024u;
-    // load n (0..15) of the stage that starts at key n0, into stage buffer `buf`: K rows first, then V^T rows
-    auto stage_load_one = [&](int n, int buf, int n0, const u32x4& kd, const u32x4& vd) {
+    // load n (0..15) of the stage whose offsets are set, into stage buffer `buf`: K rows first, then V rows
+    auto stage_load_one = [&](int n, int buf, const u32x4& kd, const u32x4& vd) {
         const unsigned dst = lds_w + (unsigned)buf * AP_STAGE + (unsigned)(n & 7) * 4096u;
-        if (n < 8) lds_direct_b128(kd, dst, (int)tok[n & 7]);
-        else lds_direct_b128(vd, dst + AP_TILE, v_voff[n & 7], n0 * 2);
+        if (n < 8) lds_direct_b128(kd, dst, (int)k_voff[n & 7]);
+        else lds_direct_b128(vd, dst + AP_TILE, (int)(SAME_ROWS ? k_voff[n & 7] + v_delta : v_voff[SAME_ROWS ? 0 : n & 7]));
     };
 
     // ---- fragments
@@ -480,8 +477,11 @@ __global__ __launch_bounds__(AP_THREADS, 1) void kept_attention_pipe_kernel(Attn
     auto k_frag = [&](const char* sk, int ks, int c) {
         return *reinterpret_cast<const u32x4*>(sk + (ks * 32 + l32) * 256 + (((2 * c + half) ^ f_swz) << 4));
     };
-    auto v_frag = [&](const char* sv, int ks, int n) {  // n = dv*2 + c: value rows dv*32.., keys 16c + 8*half .. of the subtile (quad-exchanged order)
-        return *reinterpret_cast<const u32x4*>(sv + ((n >> 1) * 32 + l32) * 256 + (((ks * 4 + 2 * (n & 1) + half) ^ f_swz) << 4));
+    // n = dv*2 + c: value rows dv*32 + l32, keys 16c + 4*half + {0..3} and 16c + 8 + 4*half + {0..3} of the subtile; the piece
+    // exchange of a row (4 * (row%4) = 4 * ((l32 % 16) / 4)) only touches dv's bits of the position
+    const int v_lane = (4 * half + ((l32 & 15) >> 2)) * 256 + (l32 >> 4) * 32 + (l32 & 3) * 8;
+    auto v_frag = [&](const char* sv, int ks, int n) {
+        return v_fragment<256>(sv + v_lane + (((n >> 1) ^ ((l32 & 15) >> 2)) << 6) + (ks * 32 + (n & 1) * 16) * 256);
     };
 
     bool frozen = true;  // workgroup-uniform: which pass this is
@@ -551,19 +551,21 @@ __global__ __launch_bounds__(AP_THREADS, 1) void kept_attention_pipe_kernel(Attn
     u32x4 kf[NCH], vf[8];
     float nm[2];  // minus the (finite) reference of each query subtile
 
-    fetch_tok(0, tok);
+    fetch_tok(0);
+    take_tok(0);
 #pragma unroll
-    for (int n = 0; n < 16; ++n) stage_load_one(n, 0, 0, k_rsrc, v_rsrc);
-    fetch_tok(1, tok);
-    fetch_tok(2, tok_next);
+    for (int n = 0; n < 16; ++n) stage_load_one(n, 0, k_rsrc, v_rsrc);
+    fetch_tok(1);
+    take_tok(1);
+    fetch_tok(2);
     ap_settle();
     // A wave's stages come in three runs: the first stage (ordinary softmax: it sets the reference), then the stages that
     // need no mask (hot), then the rest (masked, or past the wave's last query).  Each run is a loop of its own, so that
     // the register allocator sees the hot stream alone.  Every wave passes one barrier per stage, whichever loop it is in.
-    auto stage_head = [&](int t, bool& more, int& k0, int& nbuf, int& n_next, const char*& sk, const char*& sv, u32x4& kd, u32x4& vd) {
+    auto stage_head = [&](int t, bool& more, int& k0, int& nbuf, const char*& sk, const char*& sv, u32x4& kd, u32x4& vd) {
         __syncthreads();  // stage t is complete; every wave is done reading stage t-1
         more = t + 1 < nstage;
-        k0 = t * AT_KT; nbuf = (t + 1) & 1; n_next = (t + 1) * AT_KT;
+        k0 = t * AT_KT; nbuf = (t + 1) & 1;
         sk = smem + (t & 1) * AP_STAGE;
         sv = sk + AP_TILE;
         // the next stage's loads: through descriptors of size zero when there is no next stage (nothing is read then)
@@ -574,17 +576,16 @@ __global__ __launch_bounds__(AP_THREADS, 1) void kept_attention_pipe_kernel(Attn
     auto stage_tail = [&](int t, bool more) {
         ap_settle();
         if (more) {  // after the wait, so that these index loads have the whole next stage to arrive
-#pragma unroll
-            for (int i = 0; i < AP_NLD; ++i) tok[i] = tok_next[i];
-            fetch_tok(t + 3, tok_next);
+            take_tok(t + 2);
+            fetch_tok(t + 3);
         }
     };
     auto slow_stage = [&](int t) {
-        bool more; int k0, nbuf, n_next; const char* sk; const char* sv; u32x4 kd, vd;
-        stage_head(t, more, k0, nbuf, n_next, sk, sv, kd, vd);
+        bool more; int k0, nbuf; const char* sk; const char* sv; u32x4 kd, vd;
+        stage_head(t, more, k0, nbuf, sk, sv, kd, vd);
             if (more) {
 #pragma unroll
-                for (int n = 0; n < 16; ++n) stage_load_one(n, nbuf, n_next, k_rsrc, v_rsrc);
+                for (int n = 0; n < 16; ++n) stage_load_one(n, nbuf, k_rsrc, v_rsrc);
             }
             if (active && !(causal && k0 > mw0 + 63)) {  // otherwise every key of the stage lies after every query of the wave
 #pragma unroll 1
@@ -662,13 +663,13 @@ __global__ __launch_bounds__(AP_THREADS, 1) void kept_attention_pipe_kernel(Attn
     using EvenT = std::integral_constant<bool, false>;
     using OddT = std::integral_constant<bool, true>;
     auto hot_stage = [&](int t) {
-        bool more; int k0, nbuf, n_next; const char* sk; const char* sv; u32x4 kd, vd;
-        stage_head(t, more, k0, nbuf, n_next, sk, sv, kd, vd);
+        bool more; int k0, nbuf; const char* sk; const char* sv; u32x4 kd, vd;
+        stage_head(t, more, k0, nbuf, sk, sv, kd, vd);
 #pragma unroll
         for (int c = 0; c < NCH; ++c) kf[c] = k_frag(sk, sub0, c);
         // the next stage's sixteen loads ride on the stage's first group, one per slot, so that they have the other seven
         // groups' time to land before the stage's closing wait
-        auto ride = [&](int n) { stage_load_one(n, nbuf, n_next, kd, vd); };
+        auto ride = [&](int n) { stage_load_one(n, nbuf, kd, vd); };
         auto no_ride = [&](int) {};
         group(OddT{}, sk, sv, sub0, false, ride);   // ODD(4t - 1): logits of a(4t), product of a(4t-1), exponentials of b(4t-1)
 #pragma unroll
@@ -745,17 +746,22 @@ __global__ __launch_bounds__(AP_THREADS, 1) void kept_attention_pipe_kernel(Attn
     }
 }
 
-template <int KS>
-static int launch_pipe(AttnParams p, hipStream_t st) {
+template <int KS, bool SAME_ROWS>
+static int launch_pipe_rows(AttnParams p, hipStream_t st) {
     static std::once_flag once;
     static hipError_t attr_err = hipSuccess;
     std::call_once(once, [] {
-        attr_err = hipFuncSetAttribute(reinterpret_cast<const void*>(&kept_attention_pipe_kernel<KS>), hipFuncAttributeMaxDynamicSharedMemorySize, ap_lds(KS));
+        attr_err = hipFuncSetAttribute(reinterpret_cast<const void*>(&kept_attention_pipe_kernel<KS, SAME_ROWS>), hipFuncAttributeMaxDynamicSharedMemorySize, ap_lds(KS));
     });
     if (attr_err != hipSuccess) return (int)attr_err;
     p.n_qblocks = (p.M + 256 / KS - 1) / (256 / KS);
-    hipLaunchKernelGGL(kept_attention_pipe_kernel<KS>, dim3((unsigned)(p.H * p.n_qblocks)), dim3(AP_THREADS), ap_lds(KS), st, p);
+    hipLaunchKernelGGL((kept_attention_pipe_kernel<KS, SAME_ROWS>), dim3((unsigned)(p.H * p.n_qblocks)), dim3(AP_THREADS), ap_lds(KS), st, p);
     return (int)hipGetLastError();
+}
+
+template <int KS>
+static int launch_pipe(const AttnParams& p, hipStream_t st) {
+    return !p.v_compact && p.v_ts == p.k_ts ? launch_pipe_rows<KS, true>(p, st) : launch_pipe_rows<KS, false>(p, st);
 }
 
 template <int D, int KS>
@@ -775,45 +781,55 @@ static int launch_waves(AttnParams p, hipStream_t st) {
 }
 
 // How many waves share queries, by the number n of 256-query blocks (one workgroup per CU, so up to 256 run at once):
-//   d = 128  1 keeps the hot stream's pace (9856 kept, 32 heads: 751 / 852 / 1279 us for 1 / 2 / 4); fewer blocks than CUs are
+//   d = 128  1 keeps the hot stream's pace (9856 kept, 32 heads: 741 / 833 / 1217 us for 1 / 2 / 4); fewer blocks than CUs are
 //            cut in two or four, under the causal mask, where most blocks are short, up to n = 200: n = 32 (256 kept, 32
-//            heads) 23 / 20 / 18 us, n = 64 39 / 28 / 24, n = 144 62 / 46 / 59, n = 192 61 / 53 / 68, n = 416 118 / 137 / 194;
-//            full attention n = 160 72 / 95 / 104, n = 192 85 / 109 / 122
-//   d = 64   4 up to n = 480: n = 48 27 / 20.5 / 18, n = 192 69 / 47 / 46, n = 320 full 182 / 193 / 168, n = 432 208 / 208 / 198;
-//            n = 816 456 / 547 / 544, full 961 / 1080 / 1043
+//            heads) 21 / 17 / 15 us, n = 64 38 / 27 / 21, n = 144 62 / 45 / 58, n = 192 53 / 45 / 57, n = 416 113 / 133 / 184;
+//            full attention n = 96 45 / 33 / 46, n = 160 68 / 91 / 96, n = 192 81 / 106 / 110
+//   d = 64   n = 48 24 / 17 / 15, n = 192 63 / 43 / 40, n = 320 full 178 / 162 / 163, n = 432 204 / 178 / 191, n = 816 422 / 445 /
+//            509, full 938 / 925 / 1009
 static int launch_attn(AttnParams p, int d, hipStream_t st) {
     p.heads_per_xcd = p.H % NUM_XCD == 0 ? p.H / NUM_XCD : 0;
     const long long n = (long long)p.H * ((p.M + 255) / 256);
-    if (d == 64) return n <= 480 ? launch_waves<64, 4>(p, st) : launch_waves<64, 1>(p, st);
+    if (d == 64) {
+        if (n <= 300) return launch_waves<64, 4>(p, st);
+        return n <= 640 ? launch_waves<64, 2>(p, st) : launch_waves<64, 1>(p, st);
+    }
     if (n <= 64) return launch_pipe<4>(p, st);
     if (n <= ((p.flags & LEMO_CAUSAL) ? 200 : 128)) return launch_pipe<2>(p, st);
     return launch_pipe<1>(p, st);
 }
 
-// V [S,H_kv,d] element strides v_ts, v_hs; workspace holds V^T of the kept rows: H_kv * d * Mpad bf16
+// V [S,H_kv,d] element strides v_ts, v_hs; the workspace (H_kv * M * d bf16 and more) is used only when one head of V spans
+// more than 32-bit offsets reach
 int launch_kept_attention(const void* Q, const void* K, const void* V, long long S, int H, int H_kv, int d, long long q_ts, long long q_hs,
                           long long k_ts, long long k_hs, long long v_ts, long long v_hs, const int* idx, long long M, float c2,
                           unsigned flags, void* O, long long o_ts, long long o_hs, void* workspace, hipStream_t st) {
     if (M == 0) return 0;
-    const int Mpad = (int)((M + AT_MPAD - 1) / AT_MPAD) * AT_MPAD;
-    uint16_t* Vt = static_cast<uint16_t*>(workspace);
-    hipLaunchKernelGGL(gather_vt_kernel, dim3((unsigned)(Mpad / 64), (unsigned)H_kv), dim3(256), 0, st, static_cast<const uint16_t*>(V), v_ts, v_hs,
-                       idx, (int)M, Mpad, d, Vt);
-    int rc = (int)hipGetLastError();
-    if (rc) return rc;
     AttnParams p{};
     p.Q = static_cast<const uint16_t*>(Q);
     p.K = static_cast<const uint16_t*>(K);
-    p.Vt = Vt;
+    p.V = static_cast<const uint16_t*>(V);
     p.idx = idx;
     p.O = static_cast<uint16_t*>(O);
     p.M = (int)M;
-    p.Mpad = Mpad;
     p.H = H;
     p.H_kv = H_kv;
-    p.q_ts = q_ts; p.q_hs = q_hs; p.k_ts = k_ts; p.k_hs = k_hs; p.o_ts = o_ts; p.o_hs = o_hs;
+    p.q_ts = q_ts; p.q_hs = q_hs; p.k_ts = k_ts; p.k_hs = k_hs; p.v_ts = v_ts; p.v_hs = v_hs; p.o_ts = o_ts; p.o_hs = o_hs;
     p.q_bytes = (unsigned)(((S - 1) * q_ts + (long long)(H - 1) * q_hs + d) * 2);
     p.k_bytes = (unsigned)(((S - 1) * k_ts + (long long)(H_kv - 1) * k_hs + d) * 2);
+    if (v_ts > ((1ll << 32) - 1 - d * 2) / 2 / S || v_ts >= (1 << 30)) {
+        const int rows = 256 / (d / 8);  // kept rows per workgroup
+        hipLaunchKernelGGL(gather_v_kernel, dim3((unsigned)((M + rows - 1) / rows), (unsigned)H_kv), dim3(256), 0, st, p.V, v_ts, v_hs, idx, (int)M, d,
+                           static_cast<uint16_t*>(workspace));
+        const int rc = (int)hipGetLastError();
+        if (rc) return rc;
+        p.V = static_cast<const uint16_t*>(workspace);
+        p.v_compact = 1;
+        p.v_ts = d;
+        p.v_hs = M * d;
+        S = M;
+    }
+    p.v_bytes = (unsigned)(((S - 1) * p.v_ts + d) * 2);
     p.c2 = c2;
     p.flags = flags;
     return launch_attn(p, d, st);

@@ -984,6 +984,25 @@ def test_kept_attention_larger_blocks(lemo, M, H, Hkv, causal):
     assert_attention_close(wl.to_bf16_bits(O), want, wl.as_numpy(V)[idx])
 
 
+@pytest.mark.parametrize("v_stride", [2 * 256 + 64, 3_700_000])
+@pytest.mark.parametrize("d", [64, 128])
+def test_kept_attention_value_strides(lemo, d, v_stride):
+    """V with a token stride of its own (its rows then do not lie like K's), and one so long that a head of V spans more than
+    32-bit offsets reach, where the kept rows are copied into the workspace first: the same bits as from a packed V."""
+    say(f"[attention] V stride {v_stride} d={d}")
+    S, H, Hkv, M = 600, 4, 2, 333
+    Q, K = wl.tiny_qk(S, H, Hkv, d, "bf16", seed=S + d, heavy=3)
+    V = torch.from_numpy(np.random.default_rng(d).standard_normal((S, Hkv, d)).astype(np.float32)).to(torch.bfloat16).cuda()
+    idx = torch.from_numpy(np.sort(np.random.default_rng(M).permutation(S)[:M]).astype(np.int32)).cuda()
+    far = torch.empty((S - 1) * v_stride + Hkv * d, dtype=torch.bfloat16, device="cuda").as_strided((S, Hkv, d), (v_stride, d, 1))
+    far.copy_(V)
+    for flags in (lemo.CAUSAL, 0):
+        want = lemo.lemo_kept_attention(Q.cuda(), K.cuda(), V, idx, flags=flags)
+        got = lemo.lemo_kept_attention(Q.cuda(), K.cuda(), far, idx, flags=flags)
+        torch.cuda.synchronize()
+        assert torch.equal(got, want)
+
+
 @pytest.mark.parametrize("dominant", [500, 840, 30])
 def test_kept_attention_reference_overflow_is_repaired(lemo, dominant):
     """With 128-wide heads the attention kernel freezes the reference of its exponentials in the stages of keys that need
