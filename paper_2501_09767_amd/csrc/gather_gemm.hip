@@ -484,8 +484,10 @@ static int launch_t256(const GgParams& p, hipStream_t st) {
 // Weight gradients (GG_TN): both operands pass the transposing read, which the 128 x 128 tile pays twice as often; it
 // takes over where the large tiles leave half the CUs idle (N = 4096, C = 1024, 700 tokens: 28 / 14.5 us; N = 11008, C =
 // 4096, 9856 tokens: 862 / 1317).
-// binary32: the products are bound by MFMA issue at any tile size, so only the fill counts and the 256 x 256 tile has
-// nothing to offer (M = 1500, N = 11008, K = 4096: 1852 / 1187 / 1147 us; M = 2000, N = 3072, K = 768: 203 / 97 / 103).
+// binary32: the products are bound by MFMA issue at any tile size, so only the fill counts: 128 x 128, or 32 x 32 tiles
+// with the contraction split over four waves (M = 200, N = K = 768: 51 / 11.6 us, M = 500, N = 3072, K = 768: 54 / 32, M =
+// 600, N = 4096, K = 1024: 70 / 57; dW of 700 tokens, 4096 x 1024: 56 / 81; M = 1500, N = 11008, K = 4096: 1188 / 1159,
+// which 256 x 256 tiles took 1852 for).
 struct GgPlan { int cols256; GgTile rest; };
 static GgPlan gg_plan(long long M, int N, int K, int layout, lemo_dtype_t dt) {
     auto tiles = [&](int b, int n) { return (double)((M + b - 1) / b) * (double)((n + b - 1) / b); };

@@ -50,7 +50,7 @@ __device__ __forceinline__ bool gg_tile(int b, int tiles_m, int tiles_n, int gro
     return true;
 }
 
-enum GgTile { GG_T128, GG_T64 };  // output tiles of gather_gemm_small.hip
+enum GgTile { GG_T128, GG_T64 };  // output tiles of gather_gemm_small.hip: 128 x 128; 64 x 64 (binary32: 32 x 32)
 int launch_gather_gemm_small(const GgParams& p, lemo_dtype_t dt, bool add, int layout, GgTile tile, hipStream_t st);
 
 }  // namespace lemo

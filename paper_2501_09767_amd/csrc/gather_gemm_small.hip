@@ -1,12 +1,13 @@
 // The selective-load GEMM (and its in-place-add and gradient forms, see gather_gemm.hip) on smaller output tiles, for
 // products whose 256 x 256 tiles do not fill the chip's 256 CUs or leave a nearly empty last round.
 //
-// One wave always computes a 64 x 64 block (2 x 2 MFMA tiles) from slabs of 128 bytes of the contraction; two shapes:
+// A wave computes a 64 x 64 block (2 x 2 MFMA tiles) from slabs of 128 bytes of the contraction; two shapes:
 //   GW = 4  the four waves of a workgroup share a slab: 128 x 128 output tile, two workgroups per CU (70 KB of LDS each).
 //           Bound by LDS: 32 KB written and 64 KB read per slab are 768 of its cycles against 512 of MFMAs.
 //   GW = 1  every wave has its own slabs: 64 x 64 output tile, the four waves take every fourth slab of the contraction
 //           each and their partial tiles are added, in wave order, through LDS at the end.  No barrier in the main loop.
-//           Bound by the latency of the loads: 128 KB per CU are in flight, all its LDS holds.
+//           Bound by the latency of the loads: 128 KB per CU are in flight, all its LDS holds.  binary32, whose MFMAs
+//           take 16 times as long, is bound by those instead and takes 32 x 32 blocks, for four times the workgroups.
 // Slabs arrive by LDS-direct loads, two per group in flight, and the registers are the third buffer: the MFMA fragments
 // of the next slab are read during the first MFMAs of the current one, which frees its LDS stage for the slab after next.
 // Measured beside this (M = 256, N = K = 4096 with 64 x 64 tiles: 17.5 us; M = 9856, N = 11008, K = 4096 with 128 x 128
@@ -21,33 +22,36 @@ namespace lemo {
 
 constexpr int SG_THREADS = 256;
 constexpr int SG_KB = 128;          // bytes of the contraction per slab
-constexpr int SG_EP = 64 * 4 + 16;  // LDS pitch of a row of 64 floats in the epilogue
 
-template <int GW, int ESZ> struct SgGeo {
+// WT = MFMA tiles per wave and direction
+template <int GW, int ESZ, int WT> struct SgGeo {
     static constexpr int W = GW == 4 ? 2 : 1;       // waves of a group per output direction
-    static constexpr int BM = 64 * W, BN = 64 * W;  // output tile
+    static constexpr int WB = 32 * WT;              // rows and columns of a wave's block
+    static constexpr int BM = WB * W, BN = WB * W;  // output tile
     static constexpr int GROUPS = 4 / GW;           // the slabs are dealt out to the groups in turn
-    static constexpr int OPER = 64 * W * SG_KB;     // bytes of one operand's slab
+    static constexpr int OPER = WB * W * SG_KB;     // bytes of one operand's slab
     static constexpr int STAGE = 2 * OPER;
     static constexpr int NLD = OPER / (GW * 1024);  // LDS-direct loads per thread, operand and slab
     static constexpr int TOK = GROUPS * 2 * STAGE;  // (GG_TN) token rings: per wave 4 slabs of 64 indices
-    static constexpr int EPI = 4 * 64 * SG_EP;      // epilogue: a 64 x 64 block of floats per wave
+    static constexpr int EP = WB * 4 + 16;          // epilogue: LDS pitch of a row of a wave's block of floats
+    static constexpr int EPI = 4 * WB * EP;
     static constexpr int LDS = TOK + 4096 > EPI ? TOK + 4096 : EPI;
     static constexpr int KROWS = SG_KB / ESZ;       // contraction-major slab: rows,
-    static constexpr int PIECES = 4 * W * ESZ;      // 16-byte pieces per row
+    static constexpr int PIECES = 2 * WT * W * ESZ;      // 16-byte pieces per row
     // position of 16-byte piece p of row r (the loads fill consecutive LDS bytes, so conflicts are avoided by exchanging
     // pieces inside a row).  Rows along the contraction, 128 bytes: p ^ (r / 2 % 8) spreads one piece of 16 rows over all
     // banks.  Contraction-major rows: the transposing read (16 bit) takes 4 rows x 4 pieces at a time; of binary32 rows, which
     // are read element by element, the two half-waves take rows 4 apart, 8 pieces each.
     __device__ static constexpr int swz(int r) { return (r >> 1) & 7; }
-    __device__ static constexpr int kswz(int r) { return ESZ == 4 ? ((r >> 2) & 1) << 3 : GW == 4 ? (r & 3) << 2 : ((r >> 1) & 1) << 2; }
+    __device__ static constexpr int kswz(int r) { return WT == 1 ? 0 : ESZ == 4 ? ((r >> 2) & 1) << 3 : GW == 4 ? (r & 3) << 2 : ((r >> 1) & 1) << 2; }
 };
 
-template <typename T, bool ADD, int LAYOUT, int GW>
+template <typename T, bool ADD, int LAYOUT, int GW, int WT>
 __global__ __launch_bounds__(SG_THREADS, GW == 4 ? 2 : 1) void gather_gemm_small_kernel(GgParams p) {
     constexpr bool A_KMAJOR = LAYOUT == GG_TN, B_KMAJOR = LAYOUT != GG_NT;
     constexpr int ESZ = (int)sizeof(T);
-    using G = SgGeo<GW, ESZ>;
+    static_assert(ESZ == 4 || WT == 2, "the 16-bit transposing read is laid out for 64 x 64 blocks");
+    using G = SgGeo<GW, ESZ, WT>;
     constexpr int GROUPS = G::GROUPS, NLD = G::NLD;
     extern __shared__ __attribute__((aligned(16))) char smem[];
 
@@ -152,15 +156,15 @@ __global__ __launch_bounds__(SG_THREADS, GW == 4 ? 2 : 1) void gather_gemm_small
         __builtin_amdgcn_sched_barrier(0);
     };
 
-    // fragment (32-row subtile i of the wave's 64 rows, chunk c of the slab) of an operand
+    // fragment (32-row subtile i of the wave's rows, chunk c of the slab) of an operand
     const int trow = 8 * half + ((l32 & 15) >> 2);
     auto frag = [&](const char* region, bool kmajor, int w, int i, int c) {
         if (!kmajor) {
-            const int row = w * 64 + i * 32 + l32;
+            const int row = (w * WT + i) * 32 + l32;
             return *reinterpret_cast<const u32x4*>(region + row * SG_KB + (((2 * c + half) ^ G::swz(row)) << 4));
         }
         if constexpr (ESZ == 4) {  // binary32: an MFMA takes one element per lane, rows 8c + 4 * half + {0..3} of its own column
-            const int col = w * 64 + i * 32 + l32, row = 8 * c + 4 * half;
+            const int col = (w * WT + i) * 32 + l32, row = 8 * c + 4 * half;
             const char* at = region + row * (G::PIECES * 16) + (((col >> 2) ^ G::kswz(row)) << 4) + (col & 3) * 4;
             u32x4 v;
 #pragma unroll
@@ -178,12 +182,12 @@ __global__ __launch_bounds__(SG_THREADS, GW == 4 ? 2 : 1) void gather_gemm_small
     auto a_frag = [&](int st, int i, int c) { return frag(stages + st * G::STAGE, A_KMAJOR, wm, i, c); };
     auto b_frag = [&](int st, int i, int c) { return frag(stages + st * G::STAGE + G::OPER, B_KMAJOR, wn, i, c); };
 
-    f32x16 acc[2][2];
+    f32x16 acc[WT][WT];
 #pragma unroll
-    for (int i = 0; i < 2; ++i)
+    for (int i = 0; i < WT; ++i)
 #pragma unroll
-        for (int j = 0; j < 2; ++j) acc[i][j] = f32x16{0};
-    u32x4 fa[2][4][2], fb[2][4][2];  // fragments of two slabs
+        for (int j = 0; j < WT; ++j) acc[i][j] = f32x16{0};
+    u32x4 fa[2][4][WT], fb[2][4][WT];  // fragments of two slabs
 
     const int nit = (nk + GROUPS - 1) / GROUPS;  // slabs per group; the last may lie past the end (zeros)
     issue_tokens(0);
@@ -207,7 +211,7 @@ __global__ __launch_bounds__(SG_THREADS, GW == 4 ? 2 : 1) void gather_gemm_small
 #pragma unroll
     for (int c = 0; c < 4; ++c)
 #pragma unroll
-        for (int i = 0; i < 2; ++i) {
+        for (int i = 0; i < WT; ++i) {
             fa[0][c][i] = a_frag(0, i, c);
             fb[0][c][i] = b_frag(0, i, c);
         }
@@ -225,33 +229,36 @@ __global__ __launch_bounds__(SG_THREADS, GW == 4 ? 2 : 1) void gather_gemm_small
     // Slab `it` of the group (it & 1 == PAR), its fragments in set PAR; slab it+1 has been asked for into stage PAR^1,
     // slab it+2 into stage PAR.  First half of the MFMAs: read slab it+1's fragments; then, every wave of the group
     // having read them, the second half: ask for slab it+3 into the same stage.
+    constexpr int NMMA = 4 * WT * WT;
     auto step = [&](int it, auto par_tag) {
         constexpr int PAR = decltype(par_tag)::value, NXT = PAR ^ 1;
         __builtin_amdgcn_s_waitcnt(vmcnt_imm(BATCH));
         group_barrier();
         const Slab s = slab_of(it + 3);
 #pragma unroll
-        for (int q = 0; q < 16; ++q) {  // MFMA q of the slab: chunk q / 4
-            const int c = q >> 2, i = (q >> 1) & 1, j = q & 1;
+        for (int q = 0; q < NMMA; ++q) {  // MFMA q of the slab: chunk q / (WT * WT)
+            const int c = q / (WT * WT), i = q / WT % WT, j = q % WT;
             __builtin_amdgcn_sched_barrier(0);
             mma_chunk<T>(acc[i][j], fa[PAR][c][i], fb[PAR][c][j]);
-            if (q < 8) {
-                const int cc = q >> 1, ii = q & 1;
-                fa[NXT][cc][ii] = a_frag(NXT, ii, cc);
-                fb[NXT][cc][ii] = b_frag(NXT, ii, cc);
+            if (q < NMMA / 2) {
+#pragma unroll
+                for (int f = q * 4 * WT / (NMMA / 2); f < (q + 1) * 4 * WT / (NMMA / 2); ++f) {
+                    fa[NXT][f / WT][f % WT] = a_frag(NXT, f % WT, f / WT);
+                    fb[NXT][f / WT][f % WT] = b_frag(NXT, f % WT, f / WT);
+                }
             }
-            if (q == 8) {
+            if (q == NMMA / 2) {
                 read_tokens(it + 3);
                 __builtin_amdgcn_s_waitcnt(LGKMCNT0);
                 group_barrier();
             }
-            if (q >= 8) {
+            if (q >= NMMA / 2) {
 #pragma unroll
-                for (int k = (q - 8) * 2 * NLD / 8; k < (q - 7) * 2 * NLD / 8; ++k) {
+                for (int k = (q - NMMA / 2) * 2 * NLD / (NMMA / 2); k < (q + 1 - NMMA / 2) * 2 * NLD / (NMMA / 2); ++k) {
                     if (k < NLD) load_a(s, k);
                     else load_b(s, k - NLD);
                 }
-                if (q == 15) issue_tokens(it + 5);
+                if (q == NMMA - 1) issue_tokens(it + 5);
             }
         }
         __builtin_amdgcn_sched_barrier(0);
@@ -267,14 +274,15 @@ __global__ __launch_bounds__(SG_THREADS, GW == 4 ? 2 : 1) void gather_gemm_small
     __builtin_amdgcn_s_waitcnt(vmcnt_imm(0));  // requests past the end write (zeros) to the stages, too
     __syncthreads();
 
-    // Epilogue.  Every wave lays its 64 x 64 block out in LDS as binary32; rows are then put together (GW = 1: the four
-    // partial blocks are added in wave order, each wave finishing 16 rows; GW = 4: each wave its own 64 rows), eight
+    // Epilogue.  Every wave lays its block out in LDS as binary32; rows are then put together (GW = 1: the four
+    // partial blocks are added in wave order, each wave finishing a quarter of the rows; GW = 4: each wave its own block), eight
     // consecutive columns of a row per lane, and stored in whole 16-byte pieces.
-    constexpr int PARTS = GROUPS, PASSES = 64 / PARTS / 8;
-    const int piece = lane & 7, rsub = lane >> 3;
-    const int row0 = group * (64 / PARTS);
-    const int ncol = n0 + wn * 64 + piece * 8;
-    const char* first = smem + wg * 64 * SG_EP;  // + part * GW blocks
+    constexpr int PARTS = GROUPS, ROWS = G::WB / PARTS;                       // rows a wave finishes
+    constexpr int LPR = G::WB / 8, RPP = 64 / LPR, PASSES = (ROWS + RPP - 1) / RPP;  // lanes per row, rows per pass
+    const int piece = lane % LPR, rsub = lane / LPR;
+    const int row0 = group * ROWS;
+    const int ncol = n0 + wn * G::WB + piece * 8;
+    const char* first = smem + wg * G::WB * G::EP;  // + part * GW blocks
     constexpr int NV = 8 * ESZ / 16;  // 16-byte pieces of a lane's 8 columns
     const bool vec = p.ldy % (16 / ESZ) == 0 && (reinterpret_cast<uintptr_t>(p.Y) & 15u) == 0 && ncol + 8 <= p.N;
     float bv[8];
@@ -291,9 +299,9 @@ __global__ __launch_bounds__(SG_THREADS, GW == 4 ? 2 : 1) void gather_gemm_small
     u32x4 old[PASSES][NV];
 #pragma unroll
     for (int q = 0; q < PASSES; ++q) {
-        const long long m = m0 + wm * 64 + row0 + q * 8 + rsub;
+        const long long m = m0 + wm * G::WB + row0 + q * RPP + rsub;
         orow[q] = ADD && p.oidx ? (long long)p.oidx[min(m, p.M - 1)] : m;
-        if (m >= p.M || ncol >= p.N || (ADD && (orow[q] < 0 || orow[q] >= p.out_rows))) orow[q] = -1;
+        if (m >= p.M || ncol >= p.N || q * RPP + rsub >= ROWS || (ADD && (orow[q] < 0 || orow[q] >= p.out_rows))) orow[q] = -1;
     }
     if constexpr (ADD) {
         const __amdgpu_buffer_rsrc_t y_rsrc = __builtin_amdgcn_make_buffer_rsrc(p.Y, 0, (int)p.y_bytes, 0x00020000);
@@ -305,30 +313,30 @@ __global__ __launch_bounds__(SG_THREADS, GW == 4 ? 2 : 1) void gather_gemm_small
                 old[q][v] = __builtin_amdgcn_raw_buffer_load_b128(y_rsrc, (int)off, 0, 0);
             }
     }
-    char* mine = smem + wave * 64 * SG_EP;
+    char* mine = smem + wave * G::WB * G::EP;
 #pragma unroll
-    for (int i = 0; i < 2; ++i)
+    for (int i = 0; i < WT; ++i)
 #pragma unroll
-        for (int j = 0; j < 2; ++j)
+        for (int j = 0; j < WT; ++j)
 #pragma unroll
             for (int r = 0; r < 16; ++r)
-                *reinterpret_cast<float*>(mine + (i * 32 + acc_row(r, lane)) * SG_EP + (j * 32 + l32) * 4) = acc[i][j][r];
+                *reinterpret_cast<float*>(mine + (i * 32 + acc_row(r, lane)) * G::EP + (j * 32 + l32) * 4) = acc[i][j][r];
     if constexpr (PARTS > 1) __syncthreads();  // (one group: a wave reads back its own block only)
 #pragma unroll
     for (int q = 0; q < PASSES; ++q) {
+        if (orow[q] < 0) continue;
         float v[8];
-        const char* at = first + (row0 + q * 8 + rsub) * SG_EP + piece * 32;
+        const char* at = first + (row0 + q * RPP + rsub) * G::EP + piece * 32;
 #pragma unroll
         for (int part = 0; part < PARTS; ++part) {
-            const f32x4 lo = *reinterpret_cast<const f32x4*>(at + part * GW * 64 * SG_EP);
-            const f32x4 hi = *reinterpret_cast<const f32x4*>(at + part * GW * 64 * SG_EP + 16);
+            const f32x4 lo = *reinterpret_cast<const f32x4*>(at + part * GW * G::WB * G::EP);
+            const f32x4 hi = *reinterpret_cast<const f32x4*>(at + part * GW * G::WB * G::EP + 16);
 #pragma unroll
             for (int e = 0; e < 4; ++e) {
                 v[e] = part ? v[e] + lo[e] : lo[e];
                 v[e + 4] = part ? v[e + 4] + hi[e] : hi[e];
             }
         }
-        if (orow[q] < 0) continue;
 #pragma unroll
         for (int e = 0; e < 8; ++e) v[e] += bv[e];
         T* dst = static_cast<T*>(p.Y) + orow[q] * p.ldy + ncol;
@@ -366,36 +374,34 @@ __global__ __launch_bounds__(SG_THREADS, GW == 4 ? 2 : 1) void gather_gemm_small
     }
 }
 
-template <typename T, bool ADD, int LAYOUT, int GW>
+template <typename T, bool ADD, int LAYOUT, int GW, int WT>
 static int launch_small(GgParams p, hipStream_t st) {
-    using G = SgGeo<GW, (int)sizeof(T)>;
+    using G = SgGeo<GW, (int)sizeof(T), WT>;
     static std::once_flag once;
     static hipError_t attr_err = hipSuccess;
     std::call_once(once, [] {
-        attr_err = hipFuncSetAttribute(reinterpret_cast<const void*>(&gather_gemm_small_kernel<T, ADD, LAYOUT, GW>),
+        attr_err = hipFuncSetAttribute(reinterpret_cast<const void*>(&gather_gemm_small_kernel<T, ADD, LAYOUT, GW, WT>),
                                        hipFuncAttributeMaxDynamicSharedMemorySize, G::LDS);
     });
     if (attr_err != hipSuccess) return (int)attr_err;
     p.tiles_m = (int)((p.M + G::BM - 1) / G::BM);
     p.tiles_n = (p.N + G::BN - 1) / G::BN;
     const int per_xcd = (p.tiles_m * p.tiles_n + NUM_XCD - 1) / NUM_XCD;
-    hipLaunchKernelGGL((gather_gemm_small_kernel<T, ADD, LAYOUT, GW>), dim3((unsigned)(per_xcd * NUM_XCD)), dim3(SG_THREADS), G::LDS, st, p);
+    hipLaunchKernelGGL((gather_gemm_small_kernel<T, ADD, LAYOUT, GW, WT>), dim3((unsigned)(per_xcd * NUM_XCD)), dim3(SG_THREADS), G::LDS, st, p);
     return (int)hipGetLastError();
 }
 
-template <int GW>
-static int launch_small_form(const GgParams& p, lemo_dtype_t dt, bool add, int layout, hipStream_t st) {
-    if (dt == LEMO_F32) {
-        if (layout == GG_TN) return launch_small<float, false, GG_TN, GW>(p, st);
-        return add ? launch_small<float, true, GG_NT, GW>(p, st) : launch_small<float, false, GG_NT, GW>(p, st);
-    }
-    if (layout == GG_NN) return launch_small<bf16_t, true, GG_NN, GW>(p, st);
-    if (layout == GG_TN) return launch_small<bf16_t, false, GG_TN, GW>(p, st);
-    return add ? launch_small<bf16_t, true, GG_NT, GW>(p, st) : launch_small<bf16_t, false, GG_NT, GW>(p, st);
+template <typename T, int GW, int WT>
+static int launch_small_form(const GgParams& p, bool add, int layout, hipStream_t st) {
+    if (layout == GG_TN) return launch_small<T, false, GG_TN, GW, WT>(p, st);
+    if constexpr (sizeof(T) == 2)
+        if (layout == GG_NN) return launch_small<T, true, GG_NN, GW, WT>(p, st);
+    return add ? launch_small<T, true, GG_NT, GW, WT>(p, st) : launch_small<T, false, GG_NT, GW, WT>(p, st);
 }
 
 int launch_gather_gemm_small(const GgParams& p, lemo_dtype_t dt, bool add, int layout, GgTile tile, hipStream_t st) {
-    return tile == GG_T128 ? launch_small_form<4>(p, dt, add, layout, st) : launch_small_form<1>(p, dt, add, layout, st);
+    if (dt == LEMO_F32) return tile == GG_T128 ? launch_small_form<float, 4, 2>(p, add, layout, st) : launch_small_form<float, 1, 1>(p, add, layout, st);
+    return tile == GG_T128 ? launch_small_form<bf16_t, 4, 2>(p, add, layout, st) : launch_small_form<bf16_t, 1, 2>(p, add, layout, st);
 }
 
 }  // namespace lemo
