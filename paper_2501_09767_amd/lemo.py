@@ -118,7 +118,9 @@ def _ptr(t: Optional[torch.Tensor]):
 
 
 def _stream():
-    return ctypes.c_void_p(torch.cuda.current_stream().cuda_stream)
+    # the current stream of the current device, without the Stream object that torch.cuda.current_stream() builds around it
+    # (0.3 us instead of 2.9, of about 9 us that a call of a small layer takes on the host)
+    return ctypes.c_void_p(torch._C._cuda_getCurrentRawStream(torch.cuda.current_device()))
 
 
 def _check(rc: int, what: str):
