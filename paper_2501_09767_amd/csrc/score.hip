@@ -208,7 +208,8 @@ __global__ __launch_bounds__(SC_THREADS, (Geo<T, D, NRT, KS>::MIN_WG)) void rows
     if (causal) qb = p.n_query_blocks - 1 - qb;  // late query blocks see the most keys: start them first
     const int g = (int)(((long long)h * p.H_kv) / p.H);
     const int tid = threadIdx.x, lane = tid & 63, half = lane >> 5, l32 = lane & 31;
-    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    // (KS = 1: not made a scalar -- the hot stream then comes out 1 % slower, 22000 tokens, 32 heads, full: 3640 / 3600 us)
+    const int wave = KS > 1 ? __builtin_amdgcn_readfirstlane(tid >> 6) : tid >> 6;
     const T* Qb = static_cast<const T*>(p.Q);
     const T* Kb = static_cast<const T*>(p.K);
     const long long q_off = (long long)h * p.q_hs, k_off = (long long)g * p.k_hs;
@@ -233,7 +234,7 @@ __global__ __launch_bounds__(SC_THREADS, (Geo<T, D, NRT, KS>::MIN_WG)) void rows
     const int k_row_bytes = (int)p.k_ts * (int)sizeof(T);           // host guarantees < 2^24
     int st_voff[G::NLOAD];
     stage_offsets<G>(st_voff, k_row_bytes, tid);
-    const unsigned lds_w = lds_offset_of(smem) + (unsigned)wave * 1024u;
+    const unsigned lds_w = lds_offset_of(smem) + (unsigned)__builtin_amdgcn_readfirstlane(wave) * 1024u;
 
     float lse[NRT];       // the result: lse2 of query qw0 + qt*32 + l32
     bool frozen = true;   // wave-uniform (in fact workgroup-uniform): which pass this is
@@ -459,7 +460,7 @@ __global__ __launch_bounds__(SC_THREADS, (Geo<T, D, NRT, KS>::MIN_WG)) void cols
 
     const int g = (int)(((long long)h * p.H_kv) / p.H);
     const int tid = threadIdx.x, lane = tid & 63, half = lane >> 5, l32 = lane & 31;
-    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int wave = KS > 1 ? __builtin_amdgcn_readfirstlane(tid >> 6) : tid >> 6;
     const T* Qb = static_cast<const T*>(p.Q);
     const T* Kb = static_cast<const T*>(p.K);
     const long long q_off = (long long)h * p.q_hs, k_off = (long long)g * p.k_hs;
@@ -487,7 +488,7 @@ __global__ __launch_bounds__(SC_THREADS, (Geo<T, D, NRT, KS>::MIN_WG)) void cols
     const int q_row_bytes = (int)p.q_ts * (int)sizeof(T);           // host guarantees < 2^24
     int st_voff[G::NLOAD];
     stage_offsets<G>(st_voff, q_row_bytes, tid);
-    const unsigned lds_w = lds_offset_of(smem) + (unsigned)wave * 1024u;
+    const unsigned lds_w = lds_offset_of(smem) + (unsigned)__builtin_amdgcn_readfirstlane(wave) * 1024u;
     float pre_l = 0.f;
     // row statistics of a stage: thread tid < TILE owns row tid; beyond the end +inf, so that p = exp2(-inf) = 0
     auto fetch_l = [&](int t) { return tid < G::TILE ? lse[min(t * G::TILE + tid, S - 1)] : 0.f; };
