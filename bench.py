@@ -34,9 +34,9 @@ PEAK_HBM_GBS = 8000.0       # MI355X HBM3E, published
 # The figures belong to the kernel sources they were measured on: "sources" is sources_digest() at that time, and the
 # bench reports traffic as null when the sources have changed since.
 MEASURED_TRAFFIC_BYTES = {
-    "sources": "c7e7cdca3b2de7e5",
-    "C5:rowstats": 2084561862, "C5:colsum": 2093587592, "C5:head_mean_select": 8641864,
-    "C5:gather_gemm": 1687025269, "C5:scatter": 242876820,
+    "sources": "de94920522445631",
+    "C5:rowstats": 2528996761, "C5:colsum": 2723617382, "C5:head_mean_select": 8641945,
+    "C5:gather_gemm": 1687094886, "C5:scatter": 242886246,
 }
 
 
