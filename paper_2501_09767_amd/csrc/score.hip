@@ -179,8 +179,8 @@ __device__ __forceinline__ void rowstat_update(const f32x16& raw, float c2, floa
     for (int c = 0; c < 8; ++c) rowstat_slice<8>(c, raw, c2, m, st);
     rowstat_finish(st, m, l);
 }
-// The same sum against a FROZEN reference m (no maximum search, no rescaling): exact for any finite m as long as
-// nothing overflows, which the caller checks at the end.  Slice c of NS covers elements [c*16/NS, (c+1)*16/NS).
+// The same sum against a FROZEN reference m (no maximum search, no rescaling): exact for any finite m that no logit exceeds
+// by too much, which the caller checks before it rescales the sum.  Slice c of NS covers elements [c*16/NS, (c+1)*16/NS).
 template <int NS>
 __device__ __forceinline__ void rowstat_frozen_slice(int c, const f32x16& raw, float c2, float neg_m, float& s0, float& s1) {
     const int lo = c * 16 / NS, hi = (c + 1) * 16 / NS;
@@ -193,10 +193,16 @@ __device__ __forceinline__ void rowstat_frozen_slice(int c, const f32x16& raw, f
 
 // First pass, frozen reference: the running maximum is tracked through the first stage (and through every masked
 // tile); from then on unmasked tiles add exp2(s*c2 - m) against the maximum frozen at that point, which saves the
-// maximum search and the rescale.  Should a later logit exceed the frozen reference by more than the binary32
-// exponent range the sum overflows and lse2 comes out non-finite.  A workgroup that finds such a row among its own
+// maximum search and the rescale.  Should a later logit exceed the frozen reference by too much, the sum overflows, or
+// grows so large that the factor which brings it to a later or another lane's reference would underflow (the exponential
+// flushes results below 2^-126 to zero) and drop it: sums of FROZEN_LIMIT and more are therefore made infinite before they
+// are rescaled, and lse2 comes out non-finite.  A workgroup that finds such a row among its own
 // (normally none does) goes through its keys a second time with the running maximum everywhere, before it stores
 // anything: no second launch, no extra traffic when there is nothing to repair.
+// The limit: what a flushed factor drops of a smaller sum is below 2^(90-126) of a total that is at least 1 (the largest
+// reference is some key's own logit), far under a binary32 rounding for all partial sums of a row together.
+constexpr float FROZEN_LIMIT = 0x1p90f;
+__device__ __forceinline__ float frozen_sum(float l) { return l < FROZEN_LIMIT ? l : INFINITY; }
 template <typename T, int D, int NRT, int KS>
 __global__ __launch_bounds__(SC_THREADS, (Geo<T, D, NRT, KS>::MIN_WG)) void rowstats_kernel(ScoreParams p) {
     using G = Geo<T, D, NRT, KS>;
@@ -337,6 +343,8 @@ __global__ __launch_bounds__(SC_THREADS, (Geo<T, D, NRT, KS>::MIN_WG)) void rows
                 }
             }
         } else if (!skip) {
+#pragma unroll
+            for (int qt = 0; qt < NRT; ++qt) l[qt] = frozen_sum(l[qt]);
             rowstat_update(carry, c2, m[NRT - 1], l[NRT - 1]);  // drain the pipeline before the masked tiles
 #pragma unroll
             for (int r = 0; r < 16; ++r) carry[r] = -INFINITY;
@@ -368,6 +376,8 @@ __global__ __launch_bounds__(SC_THREADS, (Geo<T, D, NRT, KS>::MIN_WG)) void rows
         }
         stage_settle();
     }
+#pragma unroll
+    for (int qt = 0; qt < NRT; ++qt) l[qt] = frozen_sum(l[qt]);
     rowstat_update(carry, c2, m[NRT - 1], l[NRT - 1]);
 
     // the two half-waves hold disjoint key rows of the same queries: merge, then lse2 = m + log2(l)

@@ -196,6 +196,29 @@ def test_score_reference_overflow_is_repaired(lemo, dominant):
             assert want[dominant] > 5  # the dominant key really collects the later queries
 
 
+@pytest.mark.parametrize("H,d,dtype", [(2, 128, "bf16"), (64, 128, "bf16"), (220, 128, "bf16"), (2, 64, "bf16"), (100, 64, "bf16"), (350, 64, "bf16"),
+                                       (2, 128, "f32"), (2, 64, "f32"), (66, 64, "f32")])
+@pytest.mark.parametrize("first,second", [(5, 296), (70, 300), (296, 690)])
+def test_score_two_keys_far_above_the_reference(lemo, first, second, H, d, dtype):
+    """Two keys 127.2 base-2 units above all others, met in different half-waves, shares or stages of the same rows: a sum
+    over one of them against a reference near 0 is still finite, but the factor that would bring it to the other's reference
+    underflows.  Rows that see both must split evenly between them.  The head counts give four, two and one waves per row
+    (bf16) and one and two resident subtiles (fp32, d = 64); all heads are the same."""
+    say(f"[score] two dominant keys {first}, {second}, H={H} d={d} {dtype}")
+    S = 700
+    q, k = np.zeros((S, 2, d), dtype=np.float32), np.zeros((S, 2, d), dtype=np.float32)
+    q[:, :, 0] = 16.0
+    k[[first, second], :, 0] = 16.0
+    Q, K = (torch.from_numpy(x).to(torch.bfloat16 if dtype == "bf16" else torch.float32) for x in (q, k))
+    scale = 127.2 / 256.0 * math.log(2.0)
+    for flags in (3, 0):
+        _, col, dg = run_score(lemo, Q[:, :1].expand(S, H, d).contiguous(), K, 256, flags, scale=scale)
+        _, wcol, wdg = oracle.score(wl.as_numpy(Q), wl.as_numpy(K), flags=flags, scale=scale, per_head=True)
+        np.testing.assert_allclose(wcol[0, second], (S - second) / 2 if flags & 1 else S / 2, rtol=1e-4)
+        assert_scores_close(col.ravel(), np.broadcast_to(wcol[:1], col.shape).ravel(), "colsum_per_head")
+        assert_scores_close(dg.ravel(), np.broadcast_to(wdg[:1], dg.shape).ravel(), "diag_per_head")
+
+
 @pytest.mark.parametrize("S,H,Hkv,d", [(700, 70, 35, 128), (333, 330, 110, 128), (700, 104, 52, 64), (300, 520, 130, 64)])
 def test_score_larger_blocks(lemo, S, H, Hkv, d):
     """Launches with more 256-row blocks share rows between two waves (first and third case) or none; the other scoring
