@@ -71,7 +71,8 @@ template <typename T, int D, int NRT_, int KS_> struct Geo {
     static constexpr int ROWS_PER_LOAD = SC_THREADS / CPR; // rows covered by one load of the whole workgroup
     static constexpr int STAGE_BYTES = TILE * STRIDE;
     static constexpr int MERGE_BYTES = KS > 1 ? SC_WAVES * RES * 16 : 0;  // two floats per half-wave and resident row
-    static constexpr int LDS_ROWSTATS = 2 * STAGE_BYTES + MERGE_BYTES;
+    static constexpr int REF_BYTES = KS > 1 ? SC_WAVES * RES * (int)sizeof(float) : 0;  // a share's maximum of the first stage per row
+    static constexpr int LDS_ROWSTATS = 2 * STAGE_BYTES + MERGE_BYTES + REF_BYTES;
     static constexpr int LDS_COLSUM = 2 * STAGE_BYTES + 2 * TILE * (int)sizeof(float) + MERGE_BYTES;
     static constexpr int MIN_WG = (ROWB * NRT > 512 || NRT > 2 || SC_WAVES > 4) ? 1 : ROWB > 128 ? 2 : 3;  // workgroups per CU the register budget is set for
     static_assert(TILE * CPR % SC_THREADS == 0, "tile must split evenly over the workgroup");
@@ -193,7 +194,9 @@ __device__ __forceinline__ void rowstat_frozen_slice(int c, const f32x16& raw, f
 
 // First pass, frozen reference: the running maximum is tracked through the first stage (and through every masked
 // tile); from then on unmasked tiles add exp2(s*c2 - m) against the maximum frozen at that point, which saves the
-// maximum search and the rescale.  Should a later logit exceed the frozen reference by too much, the sum overflows, or
+// maximum search and the rescale.  Waves that share rows freeze the maximum of the whole first stage, not of the 32 or 64
+// keys of their own share (of which the last tile is still in the carry: a share of one tile would have no reference at
+// all): a lower reference is overtaken more often, and against one far above every logit the exponentials are flushed.  Should a later logit exceed the frozen reference by too much, the sum overflows, or
 // grows so large that the factor which brings it to a later or another lane's reference would underflow (the exponential
 // flushes results below 2^-126 to zero) and drop it: sums of FROZEN_LIMIT and more are therefore made infinite before they
 // are rescaled, and lse2 comes out non-finite.  A workgroup that finds such a row among its own
@@ -242,6 +245,7 @@ __global__ __launch_bounds__(SC_THREADS, (Geo<T, D, NRT, KS>::MIN_WG)) void rows
     stage_offsets<G>(st_voff, k_row_bytes, tid);
     const unsigned lds_w = lds_offset_of(smem) + (unsigned)__builtin_amdgcn_readfirstlane(wave) * 1024u;
 
+    float* const refs = reinterpret_cast<float*>(smem + 2 * G::STAGE_BYTES + G::MERGE_BYTES);  // [wave][RES]
     float lse[NRT];       // the result: lse2 of query qw0 + qt*32 + l32
     bool frozen = true;   // wave-uniform (in fact workgroup-uniform): which pass this is
     for (;;) {
@@ -262,6 +266,18 @@ __global__ __launch_bounds__(SC_THREADS, (Geo<T, D, NRT, KS>::MIN_WG)) void rows
         const bool more = t + 1 < nstage;
         const u32x4 next_desc = stage_desc<G>(k_head, k_row_bytes, (t + 1) * G::TILE, S, more);
         const unsigned next_lds = lds_w + ((t + 1) & 1) * G::STAGE_BYTES;
+        if constexpr (KS > 1) {
+            if (t == 1) {  // the shares' common reference (none: no share met a key of the first stage it may use)
+#pragma unroll
+                for (int qt = 0; qt < NRT; ++qt) {
+                    float top = -INFINITY;
+#pragma unroll
+                    for (int w = 0; w < KS; ++w) top = fmaxf(top, refs[(wave - part + w) * G::RES + qt * 32 + l32]);
+                    l[qt] *= __builtin_amdgcn_exp2f(m[qt] - (top == -INFINITY ? 0.f : top));
+                    m[qt] = top;
+                }
+            }
+        }
         const int k0 = t * G::TILE;
         // wave-uniform classification of this share of keys against the wave's queries [qw0, qw0+RES-1]
         const int ka = k0 + sub0 * 32, kz = ka + G::SHARE * 32 - 1;  // keys of this wave's share
@@ -372,6 +388,15 @@ __global__ __launch_bounds__(SC_THREADS, (Geo<T, D, NRT, KS>::MIN_WG)) void rows
                     }
                     rowstat_update(acc, c2, m[qt], l[qt]);
                 }
+            }
+        }
+        if constexpr (KS > 1) {
+            if (t == 0 && more) {
+                rowstat_update(carry, c2, m[NRT - 1], l[NRT - 1]);  // the last tile counts as well
+#pragma unroll
+                for (int r = 0; r < 16; ++r) carry[r] = -INFINITY;
+#pragma unroll
+                for (int qt = 0; qt < NRT; ++qt) refs[wave * G::RES + qt * 32 + l32] = fmaxf(m[qt], __shfl_xor(m[qt], 32));
             }
         }
         stage_settle();

@@ -219,6 +219,24 @@ def test_score_two_keys_far_above_the_reference(lemo, first, second, H, d, dtype
         assert_scores_close(dg.ravel(), np.broadcast_to(wdg[:1], dg.shape).ravel(), "diag_per_head")
 
 
+@pytest.mark.parametrize("H,d,dtype", [(2, 128, "bf16"), (64, 128, "bf16"), (220, 128, "bf16"), (2, 64, "bf16"), (2, 128, "f32"), (2, 64, "f32"), (66, 64, "f32")])
+def test_score_all_logits_far_below_zero(lemo, H, d, dtype):
+    """Every logit at -125 or -127 base-2 units: exponentials taken against 0 instead of a key's own logit would come out
+    denormal, and are flushed, for half of the keys."""
+    say(f"[score] all logits far below zero, H={H} d={d} {dtype}")
+    S = 700
+    q, k = np.zeros((S, 2, d), dtype=np.float32), np.zeros((S, 2, d), dtype=np.float32)
+    q[:, :, 0] = 16.0
+    k[:, :, 0] = -16.0
+    k[1::2, :, 0] = -16.25
+    Q, K = (torch.from_numpy(x).to(torch.bfloat16 if dtype == "bf16" else torch.float32) for x in (q, k))
+    scale = 125.0 / 256.0 * math.log(2.0)
+    for flags in (3, 0):
+        _, col, _ = run_score(lemo, Q[:, :1].expand(S, H, d).contiguous(), K, 256, flags, scale=scale)
+        _, wcol, _ = oracle.score(wl.as_numpy(Q), wl.as_numpy(K), flags=flags, scale=scale, per_head=True)
+        assert_scores_close(col.ravel(), np.broadcast_to(wcol[:1], col.shape).ravel(), "colsum_per_head")
+
+
 @pytest.mark.parametrize("S,H,Hkv,d", [(700, 70, 35, 128), (333, 330, 110, 128), (700, 104, 52, 64), (300, 520, 130, 64)])
 def test_score_larger_blocks(lemo, S, H, Hkv, d):
     """Launches with more 256-row blocks share rows between two waves (first and third case) or none; the other scoring
