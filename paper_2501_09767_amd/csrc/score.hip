@@ -205,6 +205,15 @@ __device__ __forceinline__ void rowstat_frozen_slice(int c, const f32x16& raw, f
 // The limit: what a flushed factor drops of a smaller sum is below 2^(90-126) of a total that is at least 1 (the largest
 // reference is some key's own logit), far under a binary32 rounding for all partial sums of a row together.
 constexpr float FROZEN_LIMIT = 0x1p90f;
+// m + log2(l), rounded once.  v_log_f32 cuts off rather than rounds (mean error half a unit in its last place: -2.3e-7 for l
+// of 16 to 64), which every column sum of the row would see; one step of Newton's method gives what it leaves out.
+__device__ __forceinline__ float add_log2(float m, float l) {
+    const float y = __builtin_amdgcn_logf(l), s = m + y;
+    if (!isfinite(s)) return s;
+    const float rest = (fmaf(l, __builtin_amdgcn_exp2f(-y), -1.f)) * 1.44269504f;  // log2(l) - y
+    const float mm = s - y, lost = (m - mm) + (y - (s - mm));                      // m + y - s
+    return s + (lost + rest);
+}
 __device__ __forceinline__ float frozen_sum(float l) { return l < FROZEN_LIMIT ? l : INFINITY; }
 template <typename T, int D, int NRT, int KS>
 __global__ __launch_bounds__(SC_THREADS, (Geo<T, D, NRT, KS>::MIN_WG)) void rowstats_kernel(ScoreParams p) {
@@ -288,12 +297,14 @@ __global__ __launch_bounds__(SC_THREADS, (Geo<T, D, NRT, KS>::MIN_WG)) void rows
         if (more && !hot) stage_load<G>(st_voff, next_desc, next_lds);  // (the hot path spreads them over its tiles)
         if (hot) {
             // pipelined, frozen reference: exp/sum of the previous tile between the MFMAs of tile (ks, qt)
-            // (the sum of a query is kept in two halves, l and l2, that the exponentials are added to directly)
-            float nm[NRT], l2[NRT];
+            // (the sum of a query is kept in two halves, l1 and l2, that the exponentials are added to directly; shared
+            // rows begin each stage's sum at zero, since terms below 2^-24 of what they are added to are lost)
+            float nm[NRT], l1[NRT], l2[NRT];
 #pragma unroll
             for (int q = 0; q < NRT; ++q) {
                 m[q] = m[q] == -INFINITY ? 0.f : m[q];  // nothing seen yet: take 0 as the reference
                 nm[q] = -m[q];
+                l1[q] = KS > 1 ? 0.f : l[q];
                 l2[q] = 0.f;
             }
             u32x4 kf[G::NCH];
@@ -309,7 +320,7 @@ __global__ __launch_bounds__(SC_THREADS, (Geo<T, D, NRT, KS>::MIN_WG)) void rows
                     slot_fence();
 #pragma unroll
                     for (int c = 0; c < G::NCH; ++c) {
-                        rowstat_frozen_slice<G::NCH>(c, prev, c2, nm[pq], l[pq], l2[pq]);
+                        rowstat_frozen_slice<G::NCH>(c, prev, c2, nm[pq], l1[pq], l2[pq]);
                         mma_chunk<T>(acc, kf[c], qf[qt][c]);  // acc[key row][query col]
                         if (c == 1) stage_load_slot<G>(st_voff, next_desc, next_lds, ks * NRT + qt, G::SHARE * NRT);
                         if (qt == NRT - 1 && ks + 1 < G::SHARE)
@@ -325,7 +336,7 @@ __global__ __launch_bounds__(SC_THREADS, (Geo<T, D, NRT, KS>::MIN_WG)) void rows
                 }
             }
 #pragma unroll
-            for (int q = 0; q < NRT; ++q) l[q] += l2[q];
+            for (int q = 0; q < NRT; ++q) l[q] = KS > 1 ? l[q] + (l1[q] + l2[q]) : l1[q] + l2[q];
         } else if (clean) {
             // pipelined, running maximum: the statistics update of the previous tile is issued slice by slice
             // between the MFMAs of tile (ks, qt); fragments of the next key subtile are read during the last chain
@@ -435,7 +446,7 @@ __global__ __launch_bounds__(SC_THREADS, (Geo<T, D, NRT, KS>::MIN_WG)) void rows
     bool bad = false;
 #pragma unroll
     for (int qt = 0; qt < NRT; ++qt) {
-        lse[qt] = m[qt] + __builtin_amdgcn_logf(l[qt]);
+        lse[qt] = KS > 1 ? add_log2(m[qt], l[qt]) : m[qt] + __builtin_amdgcn_logf(l[qt]);
         bad |= qw0 + qt * 32 + l32 < S && !isfinite(lse[qt]);
     }
     // every wave is past its last read of the stages here as well, so a second pass may refill them
@@ -559,6 +570,12 @@ __global__ __launch_bounds__(SC_THREADS, (Geo<T, D, NRT, KS>::MIN_WG)) void cols
             // (qs, kt); fragments and row statistics of the next query subtile are read during the last chain
             u32x4 qf[G::NCH];
             float nl[16];
+            float s1[NRT], s2[NRT];  // as in sweep 1: shared rows sum stage by stage
+#pragma unroll
+            for (int kt = 0; kt < NRT; ++kt) {
+                s1[kt] = KS > 1 ? 0.f : col[kt];
+                s2[kt] = KS > 1 ? 0.f : col2[kt];
+            }
             read_frags<G>(qf, sbuf, sub0, l32, half);
             read_nl(nl, lbuf, sub0, half);
 #pragma unroll
@@ -573,8 +590,8 @@ __global__ __launch_bounds__(SC_THREADS, (Geo<T, D, NRT, KS>::MIN_WG)) void cols
                     slot_fence();
 #pragma unroll
                     for (int c = 0; c < G::NCH; ++c) {
-                        if (kt == 0) colsum_slice<G::NCH>(c, prev, carry_nl, c2, col[pk], col2[pk]);  // the carried tile has its own rows
-                        else colsum_slice<G::NCH>(c, prev, nl, c2, col[pk], col2[pk]);
+                        if (kt == 0) colsum_slice<G::NCH>(c, prev, carry_nl, c2, s1[pk], s2[pk]);  // the carried tile has its own rows
+                        else colsum_slice<G::NCH>(c, prev, nl, c2, s1[pk], s2[pk]);
                         mma_chunk<T>(acc, qf[c], kf[kt][c]);  // acc[query row][key col]
                         if (c == 1) stage_load_slot<G>(st_voff, next_desc, next_lds, qs * NRT + kt, G::SHARE * NRT);
                         if (kt == NRT - 1 && qs + 1 < G::SHARE) {
@@ -597,6 +614,11 @@ __global__ __launch_bounds__(SC_THREADS, (Geo<T, D, NRT, KS>::MIN_WG)) void cols
 #pragma unroll
                     for (int r = 0; r < 16; ++r) nl[r] = nn[r];
                 }
+            }
+#pragma unroll
+            for (int kt = 0; kt < NRT; ++kt) {
+                col[kt] = KS > 1 ? col[kt] + s1[kt] : s1[kt];
+                col2[kt] = KS > 1 ? col2[kt] + s2[kt] : s2[kt];
             }
         } else if (!skip) {
             col[NRT - 1] += colsum_tile(carry, carry_nl, c2);  // drain the pipeline before the masked tiles

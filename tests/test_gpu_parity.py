@@ -237,6 +237,33 @@ def test_score_all_logits_far_below_zero(lemo, H, d, dtype):
         assert_scores_close(col.ravel(), np.broadcast_to(wcol[:1], col.shape).ravel(), "colsum_per_head")
 
 
+@pytest.mark.parametrize("S,H,Hkv,d,dtype,flags", [(1000, 32, 8, 128, "bf16", 3), (3000, 32, 8, 128, "bf16", 3), (2000, 12, 12, 64, "bf16", 0),
+                                                   (4500, 32, 8, 64, "bf16", 0), (1024, 4, 4, 64, "f32", 3), (1200, 8, 8, 128, "f32", 3)])
+def test_score_sums_have_no_bias(lemo, S, H, Hkv, d, dtype, flags):
+    """Head sums of the column sums against 64 bits.  Logits, normalisers and probabilities are binary32 roundings to
+    nearest, which cancel over the rows and heads of a column; what does not cancel (sums too long for their small terms, a
+    logarithm that is cut off) has to stay below half a unit in the last place, 2^-24.  Launches whose rows are shared by
+    four and by two waves, where long sums and a cut-off logarithm gave 2e-7 to 5e-7."""
+    say(f"[score] bias S={S} H={H}/{Hkv} d={d} {dtype} flags={flags}")
+    gen = torch.Generator().manual_seed(S + d)
+    dt = torch.bfloat16 if dtype == "bf16" else torch.float32
+    Q, K = (1.28 * torch.randn(S, n, d, generator=gen) for n in (H, Hkv))
+    K[torch.rand(S, generator=gen) < 0.01] *= 4
+    Q, K = Q.to(dt), K.to(dt)
+    _, col, _ = run_score(lemo, Q, K, 512, flags)
+    want = torch.zeros(S, dtype=torch.float64, device="cuda")
+    later = torch.ones((S, S), dtype=torch.bool, device="cuda").triu(1)
+    for h in range(H):
+        x = Q[:, h].cuda().double() @ K[:, h * Hkv // H].cuda().double().t().contiguous() / math.sqrt(d)
+        if flags & 1:
+            x.masked_fill_(later, -math.inf)
+        want += torch.softmax(x, dim=1).sum(0)
+    got = torch.from_numpy(col).double().sum(0).cuda()
+    err = float((got - want).norm() / want.norm())
+    say(f"    {err:.2e}")
+    assert err <= 2.0 ** -24
+
+
 @pytest.mark.parametrize("S,H,Hkv,d", [(700, 70, 35, 128), (333, 330, 110, 128), (700, 104, 52, 64), (300, 520, 130, 64)])
 def test_score_larger_blocks(lemo, S, H, Hkv, d):
     """Launches with more 256-row blocks share rows between two waves (first and third case) or none; the other scoring
