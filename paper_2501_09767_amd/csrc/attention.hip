@@ -385,6 +385,7 @@ constexpr int AP_TILE = 128 * 256;         // bytes of a K tile and of a V tile 
 constexpr int AP_STAGE = 2 * AP_TILE;
 constexpr int ap_lds(int ks) { return ks == 1 ? 2 * AP_STAGE : share_lds<2, 128>(4); }  // (the shares take more than the stages)
 static_assert(share_lds<2, 128>(4) >= 2 * AP_STAGE && share_lds<2, 128>(4) <= 160 * 1024, "");
+constexpr float AP_FROZEN_LIMIT = 0x1p100f;  // a flushed factor (below 2^-126) drops less than 2^-26 of a smaller normaliser
 constexpr int AP_NLD = 8;                  // 16-byte loads per thread, tile and stage
 
 __device__ __forceinline__ void ap_fence() { __builtin_amdgcn_sched_barrier(0); }
@@ -704,6 +705,10 @@ __global__ __launch_bounds__(AP_THREADS, 1) void kept_attention_pipe_kernel(Attn
         consume(h1, 15, 1);
 #pragma unroll
         for (int i = 0; i < 8; ++i) mma_chunk<T>(o[1][i & 3], vf[(i & 3) * 2 + (i >> 2)], pb[1][i >> 2]);
+        // the masked stages may move the reference, and the factor of a far move underflows: what is too large to be scaled
+        // by it is marked for the check below
+#pragma unroll
+        for (int qs = 0; qs < 2; ++qs) la[qs] = la[qs] + lb[qs] < AP_FROZEN_LIMIT ? la[qs] : INFINITY;
     }
     for (int t = t_hot; t < nstage; ++t) slow_stage(t);
 
@@ -715,7 +720,7 @@ __global__ __launch_bounds__(AP_THREADS, 1) void kept_attention_pipe_kernel(Attn
         const float l = la[qs] + lb[qs];
         ltot[qs] = l + __shfl_xor(l, 32);
         o_ref[qs] = mrun[qs];
-        bad |= !(ltot[qs] < 0x1p100f);
+        bad |= !(ltot[qs] < AP_FROZEN_LIMIT);
     }
     if (!frozen || !__syncthreads_or(bad)) break;
     frozen = false;

@@ -1052,6 +1052,28 @@ def test_kept_attention_larger_blocks(lemo, M, H, Hkv, causal):
     assert_attention_close(wl.to_bf16_bits(O), want, wl.as_numpy(V)[idx])
 
 
+@pytest.mark.parametrize("H", [2, 36, 80])
+@pytest.mark.parametrize("first,second", [(5, 300), (296, 690), (300, 420)])
+def test_kept_attention_two_keys_far_above_the_reference(lemo, first, second, H):
+    """128-wide heads, two keys 127.2 base-2 units above all others, met in different stages or shares: the sum over the first
+    is still finite, but the factor that would bring it to the second's reference underflows.  Queries that see both get the
+    mean of their values.  The head counts give four, two and one waves per query; all heads are the same."""
+    say(f"[attention] two dominant keys {first}, {second}, H={H}")
+    M, d = 700, 128
+    q, k, v = (np.zeros((M, 2, d), dtype=np.float32) for _ in range(3))
+    q[:, :, 0] = 16.0
+    k[[first, second], :, 0] = 16.0
+    v[first], v[second] = 1.0, 0.5
+    Q, K, V = (torch.from_numpy(x).to(torch.bfloat16) for x in (q, k, v))
+    scale = 127.2 / 256.0 * math.log(2.0)
+    for flags in (lemo.CAUSAL, 0):
+        O = lemo.lemo_kept_attention(Q[:, :1].expand(M, H, d).contiguous().cuda(), K.cuda(), V.cuda(), None, flags=flags, scale=scale)
+        torch.cuda.synchronize()
+        want = oracle.kept_attention(wl.as_numpy(Q), wl.as_numpy(K), wl.as_numpy(V), np.arange(M, dtype=np.int32), flags=flags, scale=scale)
+        assert widen(want)[-1, 0, 0] == 0.75
+        assert_attention_close(wl.to_bf16_bits(O), np.broadcast_to(want[:, :1], (M, H, d)), wl.as_numpy(V))
+
+
 @pytest.mark.parametrize("v_stride", [2 * 256 + 64, 3_700_000])
 @pytest.mark.parametrize("d", [64, 128])
 def test_kept_attention_value_strides(lemo, d, v_stride):
