@@ -338,7 +338,8 @@ int lemo_gather_gemm_dw(const void* dY, int64_t ldy, const void* X, int64_t S, i
  *     row m belongs to token kept_idx[m]; lemo_gather_gemm_add with out_idx = kept_idx puts the block's
  *     projection back into the residual stream;
  *   workspace: lemo_kept_attention_workspace_bytes(M,H_kv,d) bytes, 256-byte aligned (written only when a
- *     head of V spans 4 GiB or more: the kept rows of V, 2 bytes per kept element).
+ *     head of V spans 4 GiB or more or O lies in V's storage: the kept rows of V, 2 bytes per kept element).
+ *   O may lie in V's storage, but may not overlap Q, K, kept_idx or the workspace (blocks store O while others still read).
  *
  * Supported: LEMO_BF16, d in {64,128}; Q and K each spanning less than 4 GiB.  The probabilities are
  * rounded to bf16 for the second product and the normaliser is summed in binary32 from the unrounded

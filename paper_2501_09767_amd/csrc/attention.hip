@@ -71,7 +71,7 @@ struct AttnParams {
     int n_qblocks, heads_per_xcd;
 };
 
-// The kept rows of V, compact: [H_kv, M, D].  Only for a V that 32-bit offsets do not reach across.
+// The kept rows of V, compact: [H_kv, M, D].  Only for a V that cannot be read in place (see launch_kept_attention).
 __global__ __launch_bounds__(256) void gather_v_kernel(const uint16_t* __restrict__ V, long long v_ts, long long v_hs, const int* __restrict__ idx,
                                                        int M, int D, uint16_t* __restrict__ out) {
     const int lpr = D / 8, m = blockIdx.x * (256 / lpr) + threadIdx.x / lpr, g = blockIdx.y, c0 = threadIdx.x % lpr * 8;
@@ -805,7 +805,7 @@ static int launch_attn(AttnParams p, int d, hipStream_t st) {
 }
 
 // V [S,H_kv,d] element strides v_ts, v_hs; the workspace (H_kv * M * d bf16 and more) is used only when one head of V spans
-// more than 32-bit offsets reach
+// more than 32-bit offsets reach, or when O may lie in V's storage: workgroups that are done store while others still read V
 int launch_kept_attention(const void* Q, const void* K, const void* V, long long S, int H, int H_kv, int d, long long q_ts, long long q_hs,
                           long long k_ts, long long k_hs, long long v_ts, long long v_hs, const int* idx, long long M, float c2,
                           unsigned flags, void* O, long long o_ts, long long o_hs, void* workspace, hipStream_t st) {
@@ -822,7 +822,8 @@ int launch_kept_attention(const void* Q, const void* K, const void* V, long long
     p.q_ts = q_ts; p.q_hs = q_hs; p.k_ts = k_ts; p.k_hs = k_hs; p.v_ts = v_ts; p.v_hs = v_hs; p.o_ts = o_ts; p.o_hs = o_hs;
     p.q_bytes = (unsigned)(((S - 1) * q_ts + (long long)(H - 1) * q_hs + d) * 2);
     p.k_bytes = (unsigned)(((S - 1) * k_ts + (long long)(H_kv - 1) * k_hs + d) * 2);
-    if (v_ts > ((1ll << 32) - 1 - d * 2) / 2 / S || v_ts >= (1 << 30)) {
+    const bool v_far = v_ts > ((1ll << 32) - 1 - d * 2) / 2 / S || v_ts >= (1 << 30);
+    if (v_far || spans_meet(V, ((S - 1) * v_ts + (H_kv - 1) * v_hs + d) * 2, O, ((M - 1) * o_ts + (H - 1) * o_hs + d) * 2)) {
         const int rows = 256 / (d / 8);  // kept rows per workgroup
         hipLaunchKernelGGL(gather_v_kernel, dim3((unsigned)((M + rows - 1) / rows), (unsigned)H_kv), dim3(256), 0, st, p.V, v_ts, v_hs, idx, (int)M, d,
                            static_cast<uint16_t*>(workspace));

@@ -108,6 +108,12 @@ __device__ __forceinline__ void decode_block(int heads_per_xcd, int H, int nblk,
     }
 }
 
+// ---- host: do [a, a + a_bytes) and [b, b + b_bytes) share a byte? -----------------------------------
+inline bool spans_meet(const void* a, long long a_bytes, const void* b, long long b_bytes) {
+    const uintptr_t x = reinterpret_cast<uintptr_t>(a), y = reinterpret_cast<uintptr_t>(b);
+    return x < y + (uintptr_t)b_bytes && y < x + (uintptr_t)a_bytes;
+}
+
 // ---- parameter blocks -----------------------------------------------------------------------------
 struct ScoreParams {
     const void* Q;

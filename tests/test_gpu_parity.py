@@ -1074,6 +1074,23 @@ def test_kept_attention_two_keys_far_above_the_reference(lemo, first, second, H)
         assert_attention_close(wl.to_bf16_bits(O), np.broadcast_to(want[:, :1], (M, H, d)), wl.as_numpy(V))
 
 
+@pytest.mark.parametrize("H,d", [(4, 128), (60, 128), (110, 128), (4, 64), (200, 64)])
+def test_kept_attention_into_the_values(lemo, H, d):
+    """The result written over the storage of V: the same bits as into a buffer of its own."""
+    say(f"[attention] O in V's storage, H={H} d={d}")
+    S, M = 600, 555
+    Q, K = wl.tiny_qk(S, H, H, d, "bf16", seed=S + H, heavy=3)
+    V = torch.from_numpy(np.random.default_rng(d).standard_normal((S, H, d)).astype(np.float32)).to(torch.bfloat16).cuda()
+    idx = torch.from_numpy(np.sort(np.random.default_rng(M).permutation(S)[:M]).astype(np.int32)).cuda()
+    for flags in (lemo.CAUSAL, 0):
+        want = lemo.lemo_kept_attention(Q.cuda(), K.cuda(), V, idx, flags=flags)
+        both = V.clone()
+        got = lemo.lemo_kept_attention(Q.cuda(), K.cuda(), both, idx, flags=flags, O=both[:M])
+        torch.cuda.synchronize()
+        assert torch.equal(got, want)
+        assert torch.equal(both[M:], V[M:])
+
+
 @pytest.mark.parametrize("v_stride", [2 * 256 + 64, 3_700_000])
 @pytest.mark.parametrize("d", [64, 128])
 def test_kept_attention_value_strides(lemo, d, v_stride):
