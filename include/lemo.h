@@ -262,7 +262,8 @@ int lemo_select_threshold(const float* token_blocks, int64_t S, int32_t b, float
  * binary32 accumulation, one rounding at the store.  The result for output row m depends only on
  * the values of X row kept_idx[m], so running on a materialised compact copy gives identical bits.
  * Supported: C % 8 == 0 (bf16) / C % 4 == 0 (fp32).  X and W follow the 16-byte rule; Y only needs
- * element alignment and any ldy >= N (4-byte aligned bf16 rows are stored two columns at a time).
+ * element alignment and any ldy >= N (rows that are 16-byte aligned are stored 16 bytes at a time).  Y may not overlap X, W
+ * or bias (blocks of Y are stored while others still read).
  */
 int lemo_gather_gemm(const void* X, int64_t S, int64_t ldx, const int32_t* kept_idx, int64_t M,
                      const void* W, int64_t ldw, const void* bias, void* Y, int64_t ldy, int32_t C,
@@ -312,8 +313,10 @@ int lemo_gather_gemm_add(const void* X, int64_t S, int64_t ldx, const int32_t* k
  * N % 8 == 0; dY, W follow the 16-byte rule; row pitches below 8 MiB; dY and dX spanning less than 4 GiB, W less than
  * 2 GiB.  lemo_gather_gemm_dw: C % 8 == 0 and N % 8 == 0 (bf16) / % 4 (fp32); bf16 needs no workspace
  * (lemo_gather_gemm_dw_workspace_bytes reports 0, `workspace` may be NULL) with dY spanning less than 2 GiB and X less than
- * 4 GiB; fp32 goes through transposed copies of both operands in the workspace (256-byte aligned device memory of the
- * reported size; M below 2M tokens and N * M * 4 below 4 GiB).
+ * 4 GiB; fp32 needs a workspace (256-byte aligned device memory of the reported size; M below 2M tokens and N * M * 4 below
+ * 4 GiB), into which both operands are copied transposed where they span more (dY 2 GiB, X 4 GiB, a pitch 8 MiB) or dW lies
+ * in the storage of one of them; otherwise fp32 reads them where they lie, too, and leaves the workspace alone.
+ * dX may not overlap dY or W; a bf16 dW may not overlap dY or X; no result may overlap an index list or the workspace.
  */
 int lemo_gather_gemm_dx(const void* dY, int64_t ldy, int64_t M, const void* W, int64_t ldw, void* dX, int64_t lddx,
                         int64_t S_out, const int32_t* out_idx, int32_t C, int32_t N, lemo_dtype_t dt, void* stream);

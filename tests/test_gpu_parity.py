@@ -779,6 +779,25 @@ def test_gather_gemm_tiles_exact(lemo, form, M, N, K, dtype):
     assert torch.equal(got[:, :N], want.float().to(dt))
 
 
+@pytest.mark.parametrize("M,N,C", [(300, 260, 132), (77, 1024, 640)])
+@pytest.mark.parametrize("over", ["dY", "X"])
+def test_gather_gemm_dw_f32_over_an_operand(lemo, M, N, C, over):
+    """binary32 weight gradient written over the storage of one of its operands (whole numbers: exact in any order)."""
+    say(f"[gemm] fp32 dW over {over} M={M} N={N} C={C}")
+    gen = torch.Generator().manual_seed(M)
+    S = M + 9
+    need = {"dY": (M, N), "X": (S, C)}
+    idx = torch.randperm(S, generator=gen)[:M].int().cuda()
+    flat = {n: torch.zeros(max(r * c, N * C)).cuda() for n, (r, c) in need.items()}
+    for n, (r, c) in need.items():
+        flat[n][:r * c] = torch.randint(-3, 4, (r * c,), generator=gen).float().cuda()
+    dY, X = (flat[n][:r * c].view(r, c) for n, (r, c) in need.items())
+    want = dY.double().t().contiguous() @ X[idx.long()].double()
+    dW = lemo.lemo_gather_gemm_dw(dY, X, idx, dW=flat[over][:N * C].view(N, C))
+    torch.cuda.synchronize()
+    assert torch.equal(dW.double(), want)
+
+
 def test_gather_gemm_add_as_backward_of_the_selective_load(lemo):
     """Backward of Y = X[idx] W^T with respect to X: dX[idx[m],:] += dY[m,:] W.  With the weight's transpose stored as a
     [C,N] matrix this is the same call (compact rows in, indexed rows out); bit-exact against the oracle on a dyadic grid."""
