@@ -68,7 +68,8 @@ struct AttnParams {
     unsigned q_bytes, k_bytes, v_bytes;            // spans of Q, of K, of one head of V (32-bit buffer offsets)
     float c2;
     unsigned flags;
-    int n_qblocks, heads_per_xcd;
+    int n_qblocks;
+    HeadOrder order;
 };
 
 // The kept rows of V, compact: [H_kv, M, D].  Only for a V that cannot be read in place (see launch_kept_attention).
@@ -156,7 +157,7 @@ __global__ __launch_bounds__(AT_THREADS, 1) void kept_attention_kernel(AttnParam
 
     int h, qb;
     const bool causal = (p.flags & LEMO_CAUSAL) != 0;
-    decode_block(p.heads_per_xcd, p.H, causal ? 0 : p.n_qblocks, h, qb);  // causal: late query blocks (most keys) first
+    decode_block(p.order, p.H, p.n_qblocks, h, qb);  // causal: late query blocks (most keys) first
     if (causal) qb = p.n_qblocks - 1 - qb;
     const int g = (int)(((long long)h * p.H_kv) / p.H);
     const int tid = threadIdx.x, lane = tid & 63, half = lane >> 5, l32 = lane & 31;
@@ -411,7 +412,7 @@ __global__ __launch_bounds__(AP_THREADS, 1) void kept_attention_pipe_kernel(Attn
 
     int h, qb;
     const bool causal = (p.flags & LEMO_CAUSAL) != 0;
-    decode_block(p.heads_per_xcd, p.H, causal ? 0 : p.n_qblocks, h, qb);  // causal: late query blocks (most keys) first
+    decode_block(p.order, p.H, p.n_qblocks, h, qb);  // causal: late query blocks (most keys) first
     if (causal) qb = p.n_qblocks - 1 - qb;
     const int g = (int)(((long long)h * p.H_kv) / p.H);
     const int tid = threadIdx.x, lane = tid & 63, half = lane >> 5, l32 = lane & 31;
@@ -760,6 +761,11 @@ static int launch_pipe_rows(AttnParams p, hipStream_t st) {
     });
     if (attr_err != hipSuccess) return (int)attr_err;
     p.n_qblocks = (p.M + 256 / KS - 1) / (256 / KS);
+    // more than 8 heads on a die: about as many blocks together as it has CUs (us with 2 / 4 / 8 / 16 heads together, 128 / 8
+    // heads, 1000, 1638, 3277 and 6553 kept tokens in blocks of 256: 79 / 73 / 66 / 68, 150 / 144 / 148 / 151, 418 / 430 / 441 /
+    // 436, 1462 / 1435 / 1451 / 1446; head by head 82, 158, 428, 1444)
+    p.order = head_order(p.H, (p.flags & LEMO_CAUSAL) != 0,
+                         p.H % NUM_XCD != 0 || p.H <= 8 * NUM_XCD ? 8 : p.n_qblocks > 16 ? 4 : 32 / p.n_qblocks);
     hipLaunchKernelGGL((kept_attention_pipe_kernel<KS, SAME_ROWS>), dim3((unsigned)(p.H * p.n_qblocks)), dim3(AP_THREADS), ap_lds(KS), st, p);
     return (int)hipGetLastError();
 }
@@ -781,6 +787,7 @@ static int launch_waves(AttnParams p, hipStream_t st) {
     if (attr_err != hipSuccess) return (int)attr_err;
     constexpr int BQ = AT_WAVES / KS * 32 * AT_NQ;
     p.n_qblocks = (p.M + BQ - 1) / BQ;
+    p.order = head_order(p.H, (p.flags & LEMO_CAUSAL) != 0, 64);  // (the more heads together the better: figures at head_order)
     hipLaunchKernelGGL((kept_attention_kernel<D, KS>), dim3((unsigned)(p.H * p.n_qblocks)), dim3(AT_THREADS), LDS, st, p);
     return (int)hipGetLastError();
 }
@@ -793,7 +800,6 @@ static int launch_waves(AttnParams p, hipStream_t st) {
 //   d = 64   n = 48 24 / 17 / 15, n = 192 63 / 43 / 40, n = 320 full 178 / 162 / 163, n = 432 204 / 178 / 191, n = 816 422 / 445 /
 //            509, full 938 / 925 / 1009
 static int launch_attn(AttnParams p, int d, hipStream_t st) {
-    p.heads_per_xcd = p.H % NUM_XCD == 0 ? p.H / NUM_XCD : 0;
     const long long n = (long long)p.H * ((p.M + 255) / 256);
     if (d == 64) {
         if (n <= 300) return launch_waves<64, 4>(p, st);

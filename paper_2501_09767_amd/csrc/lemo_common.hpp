@@ -91,21 +91,34 @@ __device__ __forceinline__ uint32_t pack_bf16x2_hw(float lo, float hi) {
 }
 
 // ---- workgroups of per-head kernels ---------------------------------------------------------------
-// Block index -> (head, block rank); ranks are walked for all heads at once, so that the longest blocks of EVERY head
-// start first and the launch ends on short ones.  Workgroup b runs on die b % 8; when the heads divide evenly a die gets a
-// contiguous range of them (the query heads of one GQA group share the die's L2 with their KV head), otherwise
-// (heads_per_xcd = 0) blocks are dealt out over all dies.  nblk > 0 (blocks of equal length): head by head on each die.  Head by head instead, a sweep of the score took: 8192 tokens, 32
-// heads 310 us against 280, 16384 tokens 1096 against 1036; and a 12-head layer left two dies idle.
-__device__ __forceinline__ void decode_block(int heads_per_xcd, int H, int nblk, int& h, int& rank) {
-    const int b = blockIdx.x;
-    if (heads_per_xcd > 0) {
-        const int w = b / NUM_XCD, inner = nblk > 0 ? nblk : heads_per_xcd, outer = w / inner;
-        rank = nblk > 0 ? w - outer * inner : outer;
-        h = b % NUM_XCD * heads_per_xcd + (nblk > 0 ? outer : w - outer * inner);
-    } else {
-        rank = b / H;
-        h = b - rank * H;
+// Block index -> (head, block rank).  Workgroup b runs on die b % 8; when the heads divide evenly a die gets a contiguous
+// range of them (the query heads of one GQA group share the die's L2 with their KV head), otherwise (per_xcd = 0) blocks are
+// dealt out over all dies: with 12 heads, two dies would be idle.  The heads are cut into groups as even as can be; the
+// nblk blocks of a group's heads are walked rank by rank, so that the longest blocks of all of them start first and the
+// group ends on short ones; then comes the next group.
+struct HeadOrder { int per_xcd, groups; };
+// Groups: blocks of equal length (no causal mask) gain nothing from the order and go head by head (dealt out: 8 at a time),
+// which keeps the rows that a die streams in its L2.  Under the mask up to `limit` heads of a die are walked together.
+// Score, 16384 tokens, 128 heads, us with 1 / 2 / 4 / 8 / 16 heads of a die together: causal 8293 / 7937 / 7815 / 7802 /
+// 8395, full 14793 / 14832 / 15022 / 15462 / 16676; 8192 tokens, 32 heads, causal 616 / 573 / 541.  Attention, 3277 kept
+// tokens, 128 / 8 heads of 64, causal: 277 / 273 / 260 / 248 / 239; 128-wide heads: see its launch.
+inline HeadOrder head_order(int H, bool causal, int limit) {
+    const int per_xcd = H % NUM_XCD == 0 ? H / NUM_XCD : 0;
+    const int heads = per_xcd ? per_xcd : H, together = (causal ? limit : 1) * (per_xcd ? 1 : NUM_XCD);
+    return {per_xcd, heads < (1 << 15) ? (heads + together - 1) / together : 1};  // (the products of decode_block fit 32 bits)
+}
+__device__ __forceinline__ void decode_block(HeadOrder o, int H, int nblk, int& h, int& rank) {
+    const bool dealt = o.per_xcd == 0;
+    const int x = dealt ? 0 : blockIdx.x % NUM_XCD, w = dealt ? blockIdx.x : blockIdx.x / NUM_XCD, heads = dealt ? H : o.per_xcd;
+    int first = 0, width = heads;
+    if (o.groups > 1) {  // group g holds heads [g * heads / groups, (g + 1) * heads / groups)
+        const int g = ((w / nblk + 1) * o.groups - 1) / heads;
+        first = g * heads / o.groups;
+        width = (g + 1) * heads / o.groups - first;
     }
+    const int r = w - first * nblk;
+    rank = r / width;
+    h = x * o.per_xcd + first + (r - rank * width);
 }
 
 // ---- host: do [a, a + a_bytes) and [b, b + b_bytes) share a byte? -----------------------------------
@@ -122,7 +135,7 @@ struct ScoreParams {
     long long q_ts, q_hs, k_ts, k_hs;  // element strides
     float c2;                          // scale * log2(e): logits are handled in base-2 units
     int n_query_blocks;                // blocks per head (of queries: sweep 1, of keys: sweep 2)
-    int heads_per_xcd;                 // 0: the heads do not divide over the dies
+    HeadOrder order;
     unsigned flags;
     float* lse2;    // [H,S] base-2 log-sum-exp of every query row
     float* colsum;  // [H,S]

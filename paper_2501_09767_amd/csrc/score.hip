@@ -221,7 +221,7 @@ __global__ __launch_bounds__(SC_THREADS, (Geo<T, D, NRT, KS>::MIN_WG)) void rows
     extern __shared__ __attribute__((aligned(16))) char smem[];
 
     int h, qb;
-    decode_block(p.heads_per_xcd, p.H, 0, h, qb);
+    decode_block(p.order, p.H, p.n_query_blocks, h, qb);
     const bool causal = (p.flags & LEMO_CAUSAL) != 0;
     if (causal) qb = p.n_query_blocks - 1 - qb;  // late query blocks see the most keys: start them first
     const int g = (int)(((long long)h * p.H_kv) / p.H);
@@ -497,7 +497,7 @@ __global__ __launch_bounds__(SC_THREADS, (Geo<T, D, NRT, KS>::MIN_WG)) void cols
     float* const sLbase = reinterpret_cast<float*>(smem + 2 * G::STAGE_BYTES);
 
     int h, kb;
-    decode_block(p.heads_per_xcd, p.H, 0, h, kb);
+    decode_block(p.order, p.H, p.n_query_blocks, h, kb);
     const bool causal = (p.flags & LEMO_CAUSAL) != 0;
     const int S = p.S;
     const float c2 = p.c2;
@@ -757,7 +757,7 @@ static int launch_sweeps_ks(const ScoreParams& p, long long n, int which, hipStr
 // workgroup per CU (d = 128, n = 192: 175 / 208, n = 768: 1173 / 1255).
 int launch_score(const ScoreParams& p_in, lemo_dtype_t dt, int d, int which, hipStream_t st) {
     ScoreParams p = p_in;
-    p.heads_per_xcd = p.H % NUM_XCD == 0 ? p.H / NUM_XCD : 0;
+    p.order = head_order(p.H, (p.flags & LEMO_CAUSAL) != 0, 8);
     int rc = 0;
     const long long blocks256 = (long long)p.H * ((p.S + 255) / 256);
     if (which & 3) {
