@@ -744,8 +744,19 @@ static int launch_sweeps(const ScoreParams& p_in, int which, hipStream_t st) {
 //            n = 128 (1000, 32 heads) 22 / 15 / 14, n = 704 (5500, 32 heads) 134 / 136 / 161
 //   d = 64   the vector work per logit weighs twice as much against the loads: n = 2048 (32K tokens, 16 heads) 1.26 / 1.34 /
 //            1.50 ms, n = 756 (16000, 12 heads) 289 / 254 / 292 us, n = 240 (5000, 12 heads) 70 / 48 / 43, n = 96 30 / 19 / 16.5
+// Without a causal mask all blocks are equally long, and a launch takes as many rounds of 1/KS as its KS n blocks fill the 256
+// CUs: shares win only where they leave less of the last round empty, i.e. where 2 n fills an odd number of half rounds
+// (rowstats, full attention, us for KS = 1 / 2 / 4; d = 128: n = 32 14 / 11 / 10, n = 128 21 / 16.4 / 18.4, n = 192 28.8 / 31.3 /
+// 32.3, n = 256 39.5 / 42.4 / 50.7, n = 384 89.5 / 86.2 / 99.8, n = 448 107 / 122 / 133, n = 512 129 / 144 / 170, n = 576 199 / 194 /
+// 213, n = 896 399 / 411 / 485; d = 64: n = 192 23.7 / 24.7 / 22.6, n = 256 30.4 / 30.9 / 35.9, n = 384 66 / 59 / 68, n = 512 88 / 97 /
+// 110, n = 640 123 / 118 / 135, n = 768 190 / 204 / 232, n = 896 272 / 270 / 307).
 template <typename T, int D, int NRT>
 static int launch_sweeps_ks(const ScoreParams& p, long long n, int which, hipStream_t st) {
+    if (!(p.flags & LEMO_CAUSAL)) {
+        if (n <= 64 || (D == 64 && n > 128 && n <= 192)) return launch_sweeps<T, D, NRT, 4>(p, which, st);
+        if ((2 * n + 255) / 256 % 2 == 1 && n <= (D > 64 ? 640 : 1024)) return launch_sweeps<T, D, NRT, 2>(p, which, st);
+        return launch_sweeps<T, D, NRT, 1>(p, which, st);
+    }
     if (n <= (D > 64 ? 128 : 256)) return launch_sweeps<T, D, NRT, 4>(p, which, st);
     if (n <= (D > 64 ? 640 : 1024)) return launch_sweeps<T, D, NRT, 2>(p, which, st);
     return launch_sweeps<T, D, NRT, 1>(p, which, st);
