@@ -280,6 +280,19 @@ def test_score_larger_blocks(lemo, S, H, Hkv, d):
         assert_scores_close(got, want, "scores")
 
 
+@pytest.mark.parametrize("S,H,Hkv,d", [(300, 104, 52, 64), (530, 70, 10, 64), (300, 100, 25, 128)])
+def test_score_larger_blocks_f32(lemo, S, H, Hkv, d):
+    """binary32 launches of more than 192 blocks (two resident subtiles per wave at d = 64)."""
+    say(f"[score] fp32 larger blocks S={S} H={H}/{Hkv} d={d}")
+    Q, K = wl.tiny_qk(S, H, Hkv, d, "f32", seed=S + H + d, heavy=4)
+    for flags in (3, 0):
+        got, col, dg = run_score(lemo, Q, K, 128, flags)
+        want, wcol, wdg = oracle.score(wl.as_numpy(Q), wl.as_numpy(K), flags=flags, per_head=True)
+        assert_scores_close(col.ravel(), wcol.ravel(), "colsum_per_head")
+        assert_scores_close(dg.ravel(), wdg.ravel(), "diag_per_head")
+        assert_scores_close(got, want, "scores")
+
+
 def test_score_config_C2_full(lemo):
     """Llama2-7B-shaped layer, S=4096, all 32 heads, against the full oracle."""
     cfg = wl.CONFIGS["C2"]
@@ -779,6 +792,59 @@ def test_gather_gemm_tiles_exact(lemo, form, M, N, K, dtype):
     assert torch.equal(got[:, :N], want.float().to(dt))
 
 
+@pytest.mark.parametrize("far", ["dY", "X"])
+def test_gather_gemm_dw_f32_beyond_32_bit_offsets(lemo, far):
+    """binary32 weight gradient of operands whose row pitch is 8 MiB and more, which goes through transposed copies in the
+    workspace (whole numbers: exact in any order)."""
+    say(f"[gemm] fp32 dW, {far} with a long pitch")
+    gen = torch.Generator().manual_seed(3)
+    M, N, C, S, pitch = 37, 260, 132, 41, (1 << 21) + 4
+    whole = lambda r, c: torch.randint(-3, 4, (r, c), generator=gen).float().cuda()
+    idx = torch.randperm(S, generator=gen)[:M].int().cuda()
+    dY, X = whole(M, N), whole(S, C)
+    want = dY.double().t().contiguous() @ X[idx.long()].double()
+    if far == "dY":
+        long_ = torch.empty((M - 1) * pitch + N, device="cuda").as_strided((M, N), (pitch, 1))
+        dY = long_.copy_(dY)
+    else:
+        long_ = torch.empty((S - 1) * pitch + C, device="cuda").as_strided((S, C), (pitch, 1))
+        X = long_.copy_(X)
+    dW = lemo.lemo_gather_gemm_dw(dY, X, idx)
+    torch.cuda.synchronize()
+    assert torch.equal(dW.double(), want)
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+@pytest.mark.parametrize("listed", [True, False])
+def test_gather_gemm_more_rows_than_a_launch_holds(lemo, listed, dtype):
+    """More than 2^24 rows are taken in turns: row lists or plain rows on either side, forward and in-place add (small whole
+    numbers: exact)."""
+    say(f"[gemm] 2^24 rows and more, listed={listed} {dtype}")
+    dt = torch.bfloat16 if dtype == "bf16" else torch.float32
+    M, N, C = (1 << 24) + 700, 8, 8
+    gen = torch.Generator(device="cuda").manual_seed(1)
+    S = 1 << 16 if listed else M
+    X = torch.randint(-2, 3, (S, C), generator=gen, device="cuda").to(dt)
+    W = torch.randint(-2, 3, (N, C), generator=gen, device="cuda").to(dt)
+    idx = torch.randint(0, S, (M,), generator=gen, device="cuda", dtype=torch.int32) if listed else None
+    picked = X[idx.long()] if listed else X
+    want = sum(picked[:, c:c + 1].float() * W[:, c].float() for c in range(C))  # |entries| <= 32
+    Y = lemo.lemo_gather_gemm(X, idx, W)
+    torch.cuda.synchronize()
+    assert torch.equal(Y, want.to(dt))
+    del Y
+    R = torch.randint(-2, 3, (M, N), generator=gen, device="cuda").to(dt)
+    out = torch.randperm(M, generator=gen, device="cuda").int() if listed else None
+    total = R.float()
+    if listed:
+        total[out.long()] += want
+    else:
+        total += want
+    lemo.lemo_gather_gemm_add(X, idx, W, R, out)
+    torch.cuda.synchronize()
+    assert torch.equal(R, total.to(dt))
+
+
 @pytest.mark.parametrize("M,N,C", [(300, 260, 132), (77, 1024, 640)])
 @pytest.mark.parametrize("over", ["dY", "X"])
 def test_gather_gemm_dw_f32_over_an_operand(lemo, M, N, C, over):
@@ -1108,6 +1174,43 @@ def test_kept_attention_into_the_values(lemo, H, d):
         torch.cuda.synchronize()
         assert torch.equal(got, want)
         assert torch.equal(both[M:], V[M:])
+
+
+@pytest.mark.parametrize("causal", [True, False])
+@pytest.mark.parametrize("M,H,Hkv", [(300, 200, 50), (257, 403, 13), (290, 330, 33)])
+def test_kept_attention_64_wide_larger_blocks(lemo, M, H, Hkv, causal):
+    """64-wide heads in launches of 400 and of more than 640 blocks, where two waves or none share queries (the other tests run
+    with four); head counts that divide over the dies and that do not."""
+    say(f"[attention] 64-wide, larger blocks M={M} H={H}/{Hkv} causal={causal}")
+    S, d = M + 11, 64
+    Q, K = wl.tiny_qk(S, H, Hkv, d, "bf16", seed=M + H, heavy=3)
+    V = torch.from_numpy(np.random.default_rng(M).standard_normal((S, Hkv, d)).astype(np.float32)).to(torch.bfloat16)
+    idx = np.sort(np.random.default_rng(M + 1).permutation(S)[:M]).astype(np.int32)
+    flags = lemo.CAUSAL if causal else 0
+    O = lemo.lemo_kept_attention(Q.cuda(), K.cuda(), V.cuda(), torch.from_numpy(idx).cuda(), flags=flags)
+    torch.cuda.synchronize()
+    want = oracle.kept_attention(wl.as_numpy(Q), wl.as_numpy(K), wl.as_numpy(V), idx, flags=flags)
+    assert_attention_close(wl.to_bf16_bits(O), want, wl.as_numpy(V)[idx])
+
+
+@pytest.mark.parametrize("v_stride", [2 * 256 + 64, 3_700_000])
+@pytest.mark.parametrize("H", [60, 110])
+def test_kept_attention_value_strides_larger_blocks(lemo, H, v_stride):
+    """V with a token stride of its own, and one beyond 32-bit offsets, where two waves or none share queries."""
+    say(f"[attention] V stride {v_stride} H={H}")
+    S, Hkv, M, d = 600, 2, 333, 128
+    Q, K = wl.tiny_qk(S, H, Hkv, d, "bf16", seed=S + H, heavy=3)
+    V = torch.from_numpy(np.random.default_rng(H).standard_normal((S, Hkv, d)).astype(np.float32)).to(torch.bfloat16).cuda()
+    idx = torch.from_numpy(np.sort(np.random.default_rng(M).permutation(S)[:M]).astype(np.int32)).cuda()
+    far = torch.empty((S - 1) * v_stride + Hkv * d, dtype=torch.bfloat16, device="cuda").as_strided((S, Hkv, d), (v_stride, d, 1))
+    far.copy_(V)
+    for flags in (lemo.CAUSAL, 0):
+        want = lemo.lemo_kept_attention(Q.cuda(), K.cuda(), V, idx, flags=flags)
+        got = lemo.lemo_kept_attention(Q.cuda(), K.cuda(), far, idx, flags=flags)
+        torch.cuda.synchronize()
+        assert torch.equal(got, want)
+        ref = oracle.kept_attention(wl.as_numpy(Q), wl.as_numpy(K), wl.as_numpy(V.cpu()), idx.cpu().numpy(), flags=flags)
+        assert_attention_close(wl.to_bf16_bits(got), ref, wl.as_numpy(V.cpu()))
 
 
 @pytest.mark.parametrize("v_stride", [2 * 256 + 64, 3_700_000])
