@@ -42,13 +42,13 @@ constexpr int AT_NQ = LEMO_AT_NQ;                   // 32-query subtiles per wav
 constexpr int AT_KT = 128;                          // keys per LDS stage
 typedef __attribute__((ext_vector_type(4))) short s16x4;
 
-template <int D> struct AGeo {
-    static constexpr int ROWB = D * 2;            // bytes per head row (bf16)
+struct AGeo {  // of the 64-wide kernel
+    static constexpr int D = 64, ROWB = D * 2;            // bytes per head row (bf16)
     static constexpr int NCH = ROWB / 32;         // MFMA chunks per K / Q row
     static constexpr int CPR = ROWB / 16;         // 16-byte pieces per K row
     static constexpr int KSTRIDE = ROWB + 16;     // LDS pitch of a K row
     static constexpr int VSTRIDE = ROWB;          // V rows are unpadded: piece p of row r sits at p ^ vswz(r), so that the 4 rows x 4
-    __device__ static constexpr int vswz(int r) { return D == 64 ? ((r >> 1) & 1) << 2 : (r & 3) << 2; }  // pieces of a transposing read fill all banks
+    __device__ static constexpr int vswz(int r) { return ((r >> 1) & 1) << 2; }  // pieces of a transposing read fill all banks
     static constexpr int NDV = D / 32;            // 32-row tiles of the value dimension
     static constexpr int NLK = AT_KT * CPR / AT_THREADS;  // K loads per thread and stage
     static constexpr int K_RPL = AT_THREADS / CPR;        // K rows covered by one load of the workgroup
@@ -65,7 +65,7 @@ struct AttnParams {
     int M, H, H_kv;
     int v_compact;       // V holds the kept rows only (row n belongs to kept token n)
     long long q_ts, q_hs, k_ts, k_hs, v_ts, v_hs, o_ts, o_hs;  // element strides
-    unsigned q_bytes, k_bytes, v_bytes;            // spans of Q, of K, of one head of V (32-bit buffer offsets)
+    unsigned k_bytes, v_bytes;                     // spans of K, of one head of V (32-bit buffer offsets)
     float c2;
     unsigned flags;
     int n_qblocks;
@@ -149,9 +149,9 @@ __device__ __forceinline__ void finish_shares(const f32x16 (&o)[NQ][D / 32], con
     }
 }
 
-template <int D, int KS>
+template <int KS>
 __global__ __launch_bounds__(AT_THREADS, 1) void kept_attention_kernel(AttnParams p) {
-    using G = AGeo<D>;
+    using G = AGeo;
     using T = bf16_t;
     extern __shared__ __attribute__((aligned(16))) char smem[];
 
@@ -325,7 +325,7 @@ __global__ __launch_bounds__(AT_THREADS, 1) void kept_attention_kernel(AttnParam
 #pragma unroll
         for (int qs = 0; qs < AT_NQ; ++qs) lrun[qs] += __shfl_xor(lrun[qs], 32);
         __syncthreads();
-        finish_shares<KS, AT_NQ, D>(o, mrun, lrun, smem, AT_WAVES, wave, lane, mw0, h, p);
+        finish_shares<KS, AT_NQ, G::D>(o, mrun, lrun, smem, AT_WAVES, wave, lane, mw0, h, p);
         return;
     }
     // normalise and store: lane (query l32, half) holds value rows 8*(r/4) + 4*half + r%4 of every 32-row tile
@@ -775,20 +775,20 @@ static int launch_pipe(const AttnParams& p, hipStream_t st) {
     return !p.v_compact && p.v_ts == p.k_ts ? launch_pipe_rows<KS, true>(p, st) : launch_pipe_rows<KS, false>(p, st);
 }
 
-template <int D, int KS>
+template <int KS>
 static int launch_waves(AttnParams p, hipStream_t st) {
-    using G = AGeo<D>;
-    constexpr int LDS = KS > 1 && share_lds<AT_NQ, D>(AT_WAVES) > G::LDS ? share_lds<AT_NQ, D>(AT_WAVES) : G::LDS;
+    using G = AGeo;
+    constexpr int LDS = KS > 1 && share_lds<AT_NQ, G::D>(AT_WAVES) > G::LDS ? share_lds<AT_NQ, G::D>(AT_WAVES) : G::LDS;
     static std::once_flag once;
     static hipError_t attr_err = hipSuccess;
     std::call_once(once, [] {
-        attr_err = hipFuncSetAttribute(reinterpret_cast<const void*>(&kept_attention_kernel<D, KS>), hipFuncAttributeMaxDynamicSharedMemorySize, LDS);
+        attr_err = hipFuncSetAttribute(reinterpret_cast<const void*>(&kept_attention_kernel<KS>), hipFuncAttributeMaxDynamicSharedMemorySize, LDS);
     });
     if (attr_err != hipSuccess) return (int)attr_err;
     constexpr int BQ = AT_WAVES / KS * 32 * AT_NQ;
     p.n_qblocks = (p.M + BQ - 1) / BQ;
     p.order = head_order(p.H, (p.flags & LEMO_CAUSAL) != 0, 64);  // (the more heads together the better: figures at head_order)
-    hipLaunchKernelGGL((kept_attention_kernel<D, KS>), dim3((unsigned)(p.H * p.n_qblocks)), dim3(AT_THREADS), LDS, st, p);
+    hipLaunchKernelGGL((kept_attention_kernel<KS>), dim3((unsigned)(p.H * p.n_qblocks)), dim3(AT_THREADS), LDS, st, p);
     return (int)hipGetLastError();
 }
 
@@ -802,8 +802,8 @@ static int launch_waves(AttnParams p, hipStream_t st) {
 static int launch_attn(AttnParams p, int d, hipStream_t st) {
     const long long n = (long long)p.H * ((p.M + 255) / 256);
     if (d == 64) {
-        if (n <= 300) return launch_waves<64, 4>(p, st);
-        return n <= 640 ? launch_waves<64, 2>(p, st) : launch_waves<64, 1>(p, st);
+        if (n <= 300) return launch_waves<4>(p, st);
+        return n <= 640 ? launch_waves<2>(p, st) : launch_waves<1>(p, st);
     }
     if (n <= 64) return launch_pipe<4>(p, st);
     if (n <= ((p.flags & LEMO_CAUSAL) ? 200 : 128)) return launch_pipe<2>(p, st);
@@ -826,7 +826,6 @@ int launch_kept_attention(const void* Q, const void* K, const void* V, long long
     p.H = H;
     p.H_kv = H_kv;
     p.q_ts = q_ts; p.q_hs = q_hs; p.k_ts = k_ts; p.k_hs = k_hs; p.v_ts = v_ts; p.v_hs = v_hs; p.o_ts = o_ts; p.o_hs = o_hs;
-    p.q_bytes = (unsigned)(((S - 1) * q_ts + (long long)(H - 1) * q_hs + d) * 2);
     p.k_bytes = (unsigned)(((S - 1) * k_ts + (long long)(H_kv - 1) * k_hs + d) * 2);
     const bool v_far = v_ts > ((1ll << 32) - 1 - d * 2) / 2 / S || v_ts >= (1 << 30);
     if (v_far || spans_meet(V, ((S - 1) * v_ts + (H_kv - 1) * v_hs + d) * 2, O, ((M - 1) * o_ts + (H - 1) * o_hs + d) * 2)) {

@@ -35,24 +35,19 @@ constexpr int GG_KPITCH = 512 + 32;      // LDS pitch of such a row (256 columns
                                          // quads one 16-lane group reads fall into 32 distinct banks
 static_assert(GG_KROWS * GG_KPITCH <= GG_BM * GG_STRIDE, "a contraction-major slab must fit the operand's LDS region");
 
-// exchange with the neighbouring lane (l ^ 1) inside a quad: DPP quad_perm [1,0,3,2]
-__device__ __forceinline__ float swap_with_neighbour(float v) {
-    return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0xB1, 0xF, 0xF, true));
-}
-
 // ADD = false: Y[m,:] = result row m.
 // ADD = true:  Y is the residual stream [out_rows, N]; result row m is ADDED in place to row oidx[m] (row m when
 //              oidx is null) -- the zero padding and the residual addition of Sec. 4.4 in one step, one rounding.
 // GG_TN: `w_bytes_all` is the span of the whole B tensor (its rows are picked by idx); unused otherwise.
-template <typename T, bool ADD, int LAYOUT>
-__global__ __launch_bounds__(GG_THREADS, 1) void gather_gemm_kernel(const T* __restrict__ X, long long ldx,
+template <bool ADD, int LAYOUT>
+__global__ __launch_bounds__(GG_THREADS, 1) void gather_gemm_kernel(const bf16_t* __restrict__ X, long long ldx,
                                                                     const int* __restrict__ idx, long long M,
-                                                                    const T* __restrict__ W, long long ldw,
-                                                                    const T* __restrict__ bias, T* __restrict__ Y,
+                                                                    const bf16_t* __restrict__ W, long long ldw,
+                                                                    const bf16_t* __restrict__ bias, bf16_t* __restrict__ Y,
                                                                     long long ldy, int C, int N, int tiles_m, int tiles_n,
                                                                     unsigned x_bytes, const int* __restrict__ oidx,
                                                                     long long out_rows, unsigned r_bytes, unsigned w_bytes_all) {
-    static_assert(sizeof(T) == 2, "built for 16-bit elements");
+    using T = bf16_t;  // (binary32: gather_gemm_small.hip)
     constexpr bool A_KMAJOR = LAYOUT == GG_TN, B_KMAJOR = LAYOUT != GG_NT;
     extern __shared__ __attribute__((aligned(16))) char smem[];
 
@@ -456,13 +451,13 @@ static int launch_t256(const GgParams& p, hipStream_t st) {
     static std::once_flag once;
     static hipError_t attr_err = hipSuccess;
     std::call_once(once, [] {
-        attr_err = hipFuncSetAttribute(reinterpret_cast<const void*>(&gather_gemm_kernel<bf16_t, ADD, LAYOUT>),
+        attr_err = hipFuncSetAttribute(reinterpret_cast<const void*>(&gather_gemm_kernel<ADD, LAYOUT>),
                                        hipFuncAttributeMaxDynamicSharedMemorySize, GG_LDS);
     });
     if (attr_err != hipSuccess) return (int)attr_err;
     const int tiles_m = (int)((p.M + GG_BM - 1) / GG_BM), tiles_n = (p.N + GG_BN - 1) / GG_BN;
     const int per_xcd = (tiles_m * tiles_n + NUM_XCD - 1) / NUM_XCD;
-    hipLaunchKernelGGL((gather_gemm_kernel<bf16_t, ADD, LAYOUT>), dim3((unsigned)(per_xcd * NUM_XCD)), dim3(GG_THREADS), GG_LDS, st,
+    hipLaunchKernelGGL((gather_gemm_kernel<ADD, LAYOUT>), dim3((unsigned)(per_xcd * NUM_XCD)), dim3(GG_THREADS), GG_LDS, st,
                        static_cast<const bf16_t*>(p.A), p.lda, p.idx, p.M, static_cast<const bf16_t*>(p.B), p.ldb,
                        static_cast<const bf16_t*>(p.bias), static_cast<bf16_t*>(p.Y), p.ldy, p.K, p.N, tiles_m, tiles_n, p.a_bytes, p.oidx,
                        p.out_rows, p.y_bytes, p.b_bytes);

@@ -458,7 +458,7 @@ int lemo_gather_gemm_dw(const void* dY, int64_t ldy, const void* X, int64_t S, i
     const bool apart = !spans_meet(dW, dw_bytes, dY, ((M - 1) * ldy + N) * esz) && !spans_meet(dW, dw_bytes, X, ((S - 1) * ldx + C) * esz);
     if (apart && dw_direct(ldy, S, ldx, M, C, N, dt))
         return hip_rc(launch_gather_gemm_dw_direct(dY, ldy, X, S, ldx, kept_idx, M, dW, lddw, C, N, dt, static_cast<hipStream_t>(stream)));
-    return hip_rc(launch_gather_gemm_dw(dY, ldy, X, S, ldx, kept_idx, M, dW, lddw, C, N, dt, workspace, static_cast<hipStream_t>(stream)));
+    return hip_rc(launch_gather_gemm_dw(dY, ldy, X, S, ldx, kept_idx, M, dW, lddw, C, N, workspace, static_cast<hipStream_t>(stream)));
 }
 
 int lemo_scatter_grad(const void* G, int64_t ldg, const int32_t* kept_idx, int64_t M, void* dX, int64_t lddx, int64_t S,

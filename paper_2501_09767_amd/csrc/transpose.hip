@@ -1,18 +1,18 @@
-// Weight gradient of the selective-load GEMM (backward of the selective load of Sec. 4.4):
+// Weight gradient of the selective-load GEMM (backward of the selective load of Sec. 4.4) in binary32, for the operands that
+// the GEMM kernels cannot read where they lie (beyond their 32-bit offsets, or with dW in the storage of one of them):
 //   dW[n,c] = sum_m dY[m,n] * X[idx[m],c]
-// The contraction runs over the kept tokens, i.e. over the ROW index of both operands, while the MFMA wants each operand
-// contiguous along the contraction.  Both operands are therefore first written transposed into the workspace -- dY^T
-// [N, Mpad] and X[idx]^T [C, Mpad], the gather folded into that pass (the kept rows are read in place, no compact copy of
-// X in its original orientation is made) -- and the product is then the forward kernel's  A . B^T  with A = dY^T, B = X^T.
+// The contraction runs over the kept tokens, i.e. over the ROW index of both operands.  Both are first written transposed
+// into the workspace -- dY^T [N, Mpad] and X[idx]^T [C, Mpad], the gather folded into that pass -- and the product is then
+// the forward kernel's  A . B^T  with A = dY^T, B = X^T.
 #include "lemo_common.hpp"
 
 namespace lemo {
 
 // out[c][m] = in[row(m)][c] for m < M (row(m) = idx[m], or m without a list), zero for M <= m < Mpad.  Bits are moved,
-// never interpreted: U is an unsigned integer of the element's size.
-template <typename U>
-__global__ __launch_bounds__(256) void gather_transpose_kernel(const U* __restrict__ in, long long ld_in, const int* __restrict__ idx, int M,
-                                                               int ncols, U* __restrict__ out, long long ld_out) {
+// never interpreted.
+__global__ __launch_bounds__(256) void gather_transpose_kernel(const uint32_t* __restrict__ in, long long ld_in, const int* __restrict__ idx, int M,
+                                                               int ncols, uint32_t* __restrict__ out, long long ld_out) {
+    using U = uint32_t;
     constexpr int EPV = 16 / (int)sizeof(U);  // elements per 16 bytes
     constexpr int TC = 16 * EPV;              // columns of `in` per tile
     constexpr int PPC = 64 / EPV;             // 16-byte pieces per output row segment of 64 tokens
@@ -46,11 +46,10 @@ __global__ __launch_bounds__(256) void gather_transpose_kernel(const U* __restri
     }
 }
 
-template <typename U>
 static int launch_transpose(const void* in, long long ld_in, const int* idx, long long M, long long Mpad, int ncols, void* out, hipStream_t st) {
-    constexpr int TC = 16 * (16 / (int)sizeof(U));
-    hipLaunchKernelGGL((gather_transpose_kernel<U>), dim3((unsigned)(Mpad / 64), (unsigned)((ncols + TC - 1) / TC)), dim3(256), 0, st,
-                       static_cast<const U*>(in), ld_in, idx, (int)M, ncols, static_cast<U*>(out), Mpad);
+    constexpr int TC = 16 * 4;
+    hipLaunchKernelGGL(gather_transpose_kernel, dim3((unsigned)(Mpad / 64), (unsigned)((ncols + TC - 1) / TC)), dim3(256), 0, st,
+                       static_cast<const uint32_t*>(in), ld_in, idx, (int)M, ncols, static_cast<uint32_t*>(out), Mpad);
     return (int)hipGetLastError();
 }
 
@@ -70,18 +69,16 @@ int launch_zero_matrix(void* p, long long pitch, int row_elems, int rows, lemo_d
 }
 
 int launch_gather_gemm_dw(const void* dY, long long ldy, const void* X, long long S, long long ldx, const int* idx, long long M, void* dW,
-                          long long lddw, int C, int N, lemo_dtype_t dt, void* workspace, hipStream_t st) {
+                          long long lddw, int C, int N, void* workspace, hipStream_t st) {
     const long long Mpad = (M + 63) / 64 * 64;
-    const size_t esz = dt == LEMO_BF16 ? 2 : 4;
     char* dYt = static_cast<char*>(workspace);
-    char* Xt = dYt + (((size_t)N * (size_t)Mpad * esz + 255) / 256) * 256;
-    int rc = dt == LEMO_BF16 ? launch_transpose<uint16_t>(dY, ldy, nullptr, M, Mpad, N, dYt, st)
-                             : launch_transpose<uint32_t>(dY, ldy, nullptr, M, Mpad, N, dYt, st);
+    char* Xt = dYt + (((size_t)N * (size_t)Mpad * 4 + 255) / 256) * 256;
+    int rc = launch_transpose(dY, ldy, nullptr, M, Mpad, N, dYt, st);
     if (rc) return rc;
-    rc = dt == LEMO_BF16 ? launch_transpose<uint16_t>(X, ldx, idx, M, Mpad, C, Xt, st) : launch_transpose<uint32_t>(X, ldx, idx, M, Mpad, C, Xt, st);
+    rc = launch_transpose(X, ldx, idx, M, Mpad, C, Xt, st);
     if (rc) return rc;
     // dW [N, C] = dY^T [N, Mpad] . (X^T [C, Mpad])^T : the forward kernel with the padded token axis as contraction
-    return launch_gather_gemm(dYt, N, Mpad, nullptr, N, Xt, Mpad, nullptr, dW, lddw, (int)Mpad, C, dt, st);
+    return launch_gather_gemm(dYt, N, Mpad, nullptr, N, Xt, Mpad, nullptr, dW, lddw, (int)Mpad, C, LEMO_F32, st);
 }
 
 }  // namespace lemo
