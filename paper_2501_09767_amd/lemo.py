@@ -117,10 +117,16 @@ def _ptr(t: Optional[torch.Tensor]):
     return None if t is None else ctypes.c_void_p(t.data_ptr())
 
 
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+
+
 def _stream():
     # the current stream of the current device, without the Stream object that torch.cuda.current_stream() builds around it
-    # (0.3 us instead of 2.9, of about 9 us that a call of a small layer takes on the host)
-    return ctypes.c_void_p(torch._C._cuda_getCurrentRawStream(torch.cuda.current_device()))
+    # (0.3 us instead of 2.9, of about 9 us that a call of a small layer takes on the host); the function is not part of
+    # torch's public interface, so a torch without it takes the public way
+    if _raw_stream is None:
+        return ctypes.c_void_p(torch.cuda.current_stream().cuda_stream)
+    return ctypes.c_void_p(_raw_stream(torch.cuda.current_device()))
 
 
 def _check(rc: int, what: str):
