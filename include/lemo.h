@@ -95,10 +95,9 @@ int lemo_score_workspace_bytes(int64_t S, int32_t H, int32_t H_kv, int32_t d, le
  *     diag^h[j]   = P^h[j][j]
  *     scores[j]   = (1/H) * sum_h ( colsum^h[j] - [EXCLUDE_SELF] diag^h[j] )      (Eq. 1, head mean of Eq. 2)
  *
- * The key axis is processed one segment of L tokens at a time against tiles of queries; results do
- * not depend on L beyond binary32 summation order.  Two sweeps over Q K^T are made (row
- * log-sum-exp, then column sums); both run on the matrix cores (bf16 inputs) or in true binary32
- * (fp32 inputs), accumulate in binary32, and keep probabilities in binary32.
+ * Blocks of queries and of keys are worked on without regard to segments; results do not depend on L.  Two
+ * sweeps over Q K^T are made (row log-sum-exp, then column sums); both run on the matrix cores (bf16 inputs)
+ * or in true binary32 (fp32 inputs), accumulate in binary32, and keep probabilities in binary32.
  *
  *   Q  [S, H, d]     element (i,h,c) at Q[i*q_tok_stride + h*q_head_stride + c]   (d contiguous)
  *   K  [S, H_kv, d]  likewise with the k_ strides

@@ -3,8 +3,8 @@
 //
 //   O[m,h,:] = sum_n softmax_n(scale * <Q[idx[m],h], K[idx[n],g]>) V[idx[n],g,:]        g = floor(h * H_kv / H)
 //
-// A workgroup owns 256 kept queries of one head (8 waves x 32), their rows gathered through idx into MFMA fragments that
-// stay in registers, and walks the kept keys in stages of 128 through two LDS stages.  Both products are computed
+// A workgroup owns 256 kept queries of one head, or a half or a quarter of that where waves share queries, their rows gathered
+// through idx into MFMA fragments that stay in registers, and walks the kept keys in stages of 128 through two LDS stages.  Both products are computed
 // transposed so that a lane owns one QUERY column throughout:
 //   S^T = K Q^T       acc[key row][query col]: the 16 logits a lane holds belong to one query -> the online softmax is
 //                     an in-register chain; the two half-waves (which hold the other 16 keys of the same query) agree
@@ -28,7 +28,7 @@
 
 namespace lemo {
 
-// Eight waves per workgroup (two per SIMD: while one wave does its softmax arithmetic the other has the matrix core),
+// 64-wide heads.  Eight waves per workgroup (two per SIMD: while one wave does its softmax arithmetic the other has the matrix core),
 // each keeping ONE 32-query subtile: 64 accumulator registers for O^T, everything within 256 registers.  One workgroup
 // per CU with two LDS stages of 128 keys: a barrier every four tiles, and a stage of K and V^T is shared by 256 queries.
 #ifndef LEMO_AT_THREADS
@@ -168,7 +168,7 @@ __global__ __launch_bounds__(AT_THREADS, 1) void kept_attention_kernel(AttnParam
     const int m0 = qb * AT_BQ, mw0 = m0 + wave / KS * 32 * AT_NQ;
     const int sub0 = wave % KS * SHARE;
 
-    // resident operand: this wave's 64 queries (rows gathered through idx), as MFMA B fragments
+    // resident operand: this wave's 32 queries (rows gathered through idx), as MFMA B fragments
     u32x4 qf[AT_NQ][G::NCH];
 #pragma unroll
     for (int qs = 0; qs < AT_NQ; ++qs) {
@@ -400,8 +400,8 @@ __device__ __forceinline__ void ap_settle() {
 }
 
 // KS: waves that share queries (see finish_shares).  SAME_ROWS: K and V have the same token stride and are picked by the
-// same list, so a V row's offset is its K row's plus a constant (8 registers less, which is what keeps the hot stream from
-// spilling); otherwise it has registers of its own.
+// same list, so a V row's offset is its K row's plus a constant (8 registers less; 1 to 2 % at every size, e.g. 9856 kept tokens,
+// 32 heads 750 us against 761, without the mask 1380 / 1398, 1500 tokens 39.3 / 40.2); otherwise it has registers of its own.
 template <int KS, bool SAME_ROWS>
 __global__ __launch_bounds__(AP_THREADS, 1) void kept_attention_pipe_kernel(AttnParams p) {
     using T = bf16_t;

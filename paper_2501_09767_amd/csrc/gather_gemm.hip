@@ -469,20 +469,25 @@ static int launch_t256(const GgParams& p, hipStream_t st) {
 // The large tile is the fastest per flop but comes in rounds of 256, one per CU, and a round lasts as long for one tile
 // as for (nearly) all: with few tiles, or just past a full round, smaller ones win although they move more bytes per
 // flop.  The choice is the least of these times, in us, for a contraction of k slabs of 128 bytes; the constants are
-// fits to M = 64 ... 9856, N = 256 ... 14336, K = 256 ... 11008 (within a fifth of what was measured):
+// fits to M = 64 ... 9856, N = 256 ... 14336, K = 256 ... 11008, in a stream of other work (within a fourth of what was
+// measured; with the operands in the caches already, the smaller tiles take up to 40 % less than this):
 //   256 x 256  6 + k (1.5 per full round + 1.5 for a last one over half full, 1.15 otherwise)
 //   128 x 128  4 + (k + 3) (0.6 up to 256 tiles -- one per CU --, then n/512 + 0.25, at least 0.95)
 //   64 x 64    4 + (2 + 0.25 k) per 256 tiles
 //   256 x 256 for the columns that fill whole rounds, 128 x 128 for the rest: the sum (the launches follow each other)
 // e.g. M = 256, N = K = 4096: 80 / 32 / 17.5 us; M = 256, N = 11008, K = 4096: 82 / 45 / 58; M = 1500, N = K = 4096: 85 /
-// 59 / 97; M = 3280, N = 11008, K = 4096: 282 / 292 / 565, and 9856 rows of it 705 / 815 / 1610.
+// 59 / 97; M = 3280, N = 11008, K = 4096: 282 / 292 / 565, and 9856 rows of it 705 / 815 / 1610.  Between 256 x 256 and
+// 128 x 128 the line is known to a fifth: M = 2000, N = 4096, K = 11008 takes the large tiles, 191 / 176 / 270.
 // Weight gradients (GG_TN): both operands pass the transposing read, which the 128 x 128 tile pays twice as often; it
-// takes over where the large tiles leave half the CUs idle (N = 4096, C = 1024, 700 tokens: 28 / 14.5 us; N = 11008, C =
-// 4096, 9856 tokens: 862 / 1317).
+// takes over where the large tiles leave half the CUs idle (256 x 256 / 128 x 128, N = 4096: C = 1024, 64 large tiles, 700
+// tokens 28 / 14.5 us; 4000 tokens, C = 2048, 128 tiles 113 / 78, C = 2304, 144 tiles 113 / 107, C = 3072, 192 tiles 115 / 112,
+// C = 4096, 256 tiles 133 / 145; N = 11008, C = 4096, 9856 tokens: 862 / 1317).
 // binary32: the products are bound by MFMA issue at any tile size, so only the fill counts: 128 x 128, or 32 x 32 tiles
-// with the contraction split over four waves (M = 200, N = K = 768: 51 / 11.6 us, M = 500, N = 3072, K = 768: 54 / 32, M =
-// 600, N = 4096, K = 1024: 70 / 57; dW of 700 tokens, 4096 x 1024: 56 / 81; M = 1500, N = 11008, K = 4096: 1188 / 1159,
-// which 256 x 256 tiles took 1852 for).
+// with the contraction split over four waves, up to 192 of the former (M = 200, N = K = 768: 51 / 11.6 us; 96 tiles, M = 500,
+// N = 3072, K = 768: 54 / 32; 160, M = 640, N = 4096, K = 1024: 69 / 59; 192, M = 768: 69.5 / 68.6; 256, M = 1024: 71 / 87; dW of 700
+// tokens, 4096 x 1024, 256 tiles: 54 / 81).  Past 256 a second round that is nearly empty would favour the small tiles again
+// (288 tiles, M = 1500, N = 3072, K = 768: 97 / 80); with more rounds the two are alike (1032 tiles, M = 1500, N = 11008, K = 4096:
+// 1193 / 1201, which 256 x 256 tiles took 1852 for).
 struct GgPlan { int cols256; GgTile rest; };
 static GgPlan gg_plan(long long M, int N, int K, int layout, lemo_dtype_t dt) {
     auto tiles = [&](int b, int n) { return (double)((M + b - 1) / b) * (double)((n + b - 1) / b); };

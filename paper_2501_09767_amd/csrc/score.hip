@@ -3,10 +3,10 @@
 // Column sums of softmax(Q K^T) need every row's FINAL normaliser, so Q K^T is swept twice and the
 // S x S matrix is never stored (memory linear in S, as Sec. 4.3 requires of the scoring kernel):
 //
-//   sweep 1  rowstats_kernel   per (head, 256-query block): keys stream through LDS, the block's
+//   sweep 1  rowstats_kernel   per (head, block of 256 queries or a part of that): keys stream through LDS, the block's
 //                              queries stay in registers; an online max/sum per query gives the
 //                              base-2 log-sum-exp  lse2[h][i].
-//   sweep 2  colsum_kernel     per (head, <=256-key block of one segment): the block's keys stay in
+//   sweep 2  colsum_kernel     per (head, block of 256 keys or a part of that): the block's keys stay in
 //                              registers, queries stream through LDS; p = exp2(s*c2 - lse2[i]) is
 //                              added into per-lane column accumulators -- each column is owned by one
 //                              workgroup, so there are no atomics and the result is deterministic.
@@ -192,19 +192,12 @@ __device__ __forceinline__ void rowstat_frozen_slice(int c, const f32x16& raw, f
     }
 }
 
-// First pass, frozen reference: the running maximum is tracked through the first stage (and through every masked
-// tile); from then on unmasked tiles add exp2(s*c2 - m) against the maximum frozen at that point, which saves the
-// maximum search and the rescale.  Waves that share rows freeze the maximum of the whole first stage, not of the 32 or 64
-// keys of their own share (of which the last tile is still in the carry: a share of one tile would have no reference at
-// all): a lower reference is overtaken more often, and against one far above every logit the exponentials are flushed.  Should a later logit exceed the frozen reference by too much, the sum overflows, or
-// grows so large that the factor which brings it to a later or another lane's reference would underflow (the exponential
-// flushes results below 2^-126 to zero) and drop it: sums of FROZEN_LIMIT and more are therefore made infinite before they
-// are rescaled, and lse2 comes out non-finite.  A workgroup that finds such a row among its own
-// (normally none does) goes through its keys a second time with the running maximum everywhere, before it stores
-// anything: no second launch, no extra traffic when there is nothing to repair.
-// The limit: what a flushed factor drops of a smaller sum is below 2^(90-126) of a total that is at least 1 (the largest
-// reference is some key's own logit), far under a binary32 rounding for all partial sums of a row together.
+// What a sum against a frozen reference may reach before it is rescaled.  A later or another lane's reference brings it down by
+// a factor that underflows 126 base-2 units on (the exponential flushes results below 2^-126 to zero); what that drops of a
+// smaller sum is below 2^(90-126) of a total that is at least 1 (the largest reference is some key's own logit), far under
+// a binary32 rounding for all partial sums of a row together.
 constexpr float FROZEN_LIMIT = 0x1p90f;
+__device__ __forceinline__ float frozen_sum(float l) { return l < FROZEN_LIMIT ? l : INFINITY; }
 // m + log2(l), rounded once.  v_log_f32 cuts off rather than rounds (mean error half a unit in its last place: -2.3e-7 for l
 // of 16 to 64), which every column sum of the row would see; one step of Newton's method gives what it leaves out.
 __device__ __forceinline__ float add_log2(float m, float l) {
@@ -214,7 +207,16 @@ __device__ __forceinline__ float add_log2(float m, float l) {
     const float mm = s - y, lost = (m - mm) + (y - (s - mm));                      // m + y - s
     return s + (lost + rest);
 }
-__device__ __forceinline__ float frozen_sum(float l) { return l < FROZEN_LIMIT ? l : INFINITY; }
+
+// First pass, frozen reference: the running maximum is tracked through the first stage (and through every masked
+// tile); from then on unmasked tiles add exp2(s*c2 - m) against the maximum frozen at that point, which saves the
+// maximum search and the rescale.  Waves that share rows freeze the maximum of the whole first stage, not of the 32 or 64
+// keys of their own share (of which the last tile is still in the carry: a share of one tile would have no reference at
+// all): a lower reference is overtaken more often, and against one far above every logit the exponentials are flushed.
+// Should a later logit exceed the frozen reference by too much, the sum overflows or passes FROZEN_LIMIT; it is then made
+// infinite before it is rescaled, and lse2 comes out non-finite.  A workgroup that finds such a row among its own
+// (normally none does) goes through its keys a second time with the running maximum everywhere, before it stores
+// anything: no second launch, no extra traffic when there is nothing to repair.
 template <typename T, int D, int NRT, int KS>
 __global__ __launch_bounds__(SC_THREADS, (Geo<T, D, NRT, KS>::MIN_WG)) void rowstats_kernel(ScoreParams p) {
     using G = Geo<T, D, NRT, KS>;
