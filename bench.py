@@ -34,13 +34,13 @@ PEAK_HBM_GBS = 8000.0       # MI355X HBM3E, published
 # The figures belong to the kernel sources they were measured on: "sources" is sources_digest() at that time, and the
 # bench reports traffic as null when the sources have changed since.
 MEASURED_TRAFFIC_BYTES = {
-    "sources": "de94920522445631",
-    "C5:rowstats": 2528996761, "C5:colsum": 2723617382, "C5:head_mean_select": 8641945,
-    "C5:gather_gemm": 1687094886, "C5:scatter": 242886246,
+    "sources": "3691ae75f3f4331f",
+    "C5:rowstats": 2536736973, "C5:colsum": 2663310746, "C5:head_mean_select": 8641126,
+    "C5:gather_gemm": 1687128678, "C5:scatter": 242886042,
 }
 
 
-HOT_PATH_SOURCES = ("lemo_common.hpp", "score.hip", "select.hip", "gather_gemm.hip", "scatter.hip")
+HOT_PATH_SOURCES = ("lemo_common.hpp", "score.hip", "select.hip", "gather_gemm.hpp", "gather_gemm.hip", "gather_gemm_small.hip", "scatter.hip")
 
 
 def sources_digest() -> str:
