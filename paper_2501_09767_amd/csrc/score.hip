@@ -197,7 +197,7 @@ __device__ __forceinline__ void rowstat_frozen_slice(int c, const f32x16& raw, f
 // smaller sum is below 2^(90-126) of a total that is at least 1 (the largest reference is some key's own logit), far under
 // a binary32 rounding for all partial sums of a row together.
 constexpr float FROZEN_LIMIT = 0x1p90f;
-__device__ __forceinline__ float frozen_sum(float l) { return l < FROZEN_LIMIT ? l : INFINITY; }
+__device__ __forceinline__ float frozen_sum(float l) { return l >= FROZEN_LIMIT ? INFINITY : l; }  // (NaN stays)
 // m + log2(l), rounded once.  v_log_f32 cuts off rather than rounds (mean error half a unit in its last place: -2.3e-7 for l
 // of 16 to 64), which every column sum of the row would see; one step of Newton's method gives what it leaves out.
 __device__ __forceinline__ float add_log2(float m, float l) {

@@ -219,6 +219,29 @@ def test_score_two_keys_far_above_the_reference(lemo, first, second, H, d, dtype
         assert_scores_close(dg.ravel(), np.broadcast_to(wdg[:1], dg.shape).ravel(), "diag_per_head")
 
 
+@pytest.mark.parametrize("H,d,dtype", [(2, 128, "bf16"), (64, 128, "bf16"), (220, 128, "bf16"), (2, 64, "bf16"), (350, 64, "bf16"), (2, 128, "f32"), (66, 64, "f32")])
+@pytest.mark.parametrize("row", [3, 350, 699])
+def test_score_nan_stays_visible(lemo, row, H, d, dtype):
+    """A query that is not a number makes the columns it reads not a number, and no others; a key that is not a number does so
+    to every row that reads it, and so to every column."""
+    say(f"[score] NaN query and key {row}, H={H} d={d} {dtype}")
+    S = 700
+    Q, K = wl.tiny_qk(S, H, 2, d, dtype, seed=row + H, heavy=4)
+    for flags in (3, 0):
+        _, want, _ = run_score(lemo, Q, K, 256, flags)
+        bad = Q.clone()
+        bad[row] = float("nan")
+        _, got, _ = run_score(lemo, bad, K, 256, flags)
+        last = row if flags & 1 else S - 1
+        assert np.isnan(got[:, :last + 1]).all()
+        # the other rows of the query's block go through the repair pass with it: one rounding of lse2 (2^-19 base-2 units below 32)
+        np.testing.assert_allclose(got[:, last + 1:], want[:, last + 1:], rtol=2.0 ** -19, atol=1e-12)
+        bad = K.clone()
+        bad[row] = float("nan")
+        _, got, _ = run_score(lemo, Q, bad, 256, flags)
+        assert np.isnan(got).all()
+
+
 @pytest.mark.parametrize("H,d,dtype", [(2, 128, "bf16"), (64, 128, "bf16"), (220, 128, "bf16"), (2, 64, "bf16"), (2, 128, "f32"), (2, 64, "f32"), (66, 64, "f32")])
 def test_score_all_logits_far_below_zero(lemo, H, d, dtype):
     """Every logit at -125 or -127 base-2 units: exponentials taken against 0 instead of a key's own logit would come out
