@@ -1,4 +1,4 @@
-// What the two selective-load GEMM kernels (256 x 256 tiles: gather_gemm.hip; smaller ones: gather_gemm_small.hip) share.
+// What the two selective-load GEMM kernels (256 x 256 tiles: gather_gemm_large.hip; smaller ones: gather_gemm_small.hip) share.
 #pragma once
 #include <type_traits>
 
@@ -51,6 +51,7 @@ __device__ __forceinline__ bool gg_tile(int b, int tiles_m, int tiles_n, int gro
 }
 
 enum GgTile { GG_T128, GG_T64 };  // output tiles of gather_gemm_small.hip: 128 x 128; 64 x 64 (binary32: 32 x 32)
+int launch_gather_gemm_large(const GgParams& p, bool add, int layout, hipStream_t st);  // 256 x 256 tiles, bf16: gather_gemm_large.hip
 int launch_gather_gemm_small(const GgParams& p, lemo_dtype_t dt, bool add, int layout, GgTile tile, hipStream_t st);
 
 }  // namespace lemo

@@ -65,7 +65,8 @@ __device__ __forceinline__ u32x4 raw_rsrc(const void* base, long long bytes) {
 }
 // s_waitcnt immediates that wait on one counter only (gfx9 layout: vmcnt in bits 3:0 and 15:14, lgkmcnt in 11:8)
 constexpr int vmcnt_imm(int n) { return (n & 15) | ((n >> 4) << 14) | 0x0F70; }
-constexpr int LGKMCNT0 = 0xC07F;
+constexpr int lgkmcnt_imm(int n) { return n << 8 | 0xC07F; }
+constexpr int LGKMCNT0 = lgkmcnt_imm(0);
 // LDS byte offset of a pointer into the workgroup's LDS
 __device__ __forceinline__ unsigned lds_offset_of(const void* p) { return (unsigned)reinterpret_cast<unsigned long long>(p); }
 

@@ -1,0 +1,143 @@
+"""Host model of the loads and LDS positions of the selective-load GEMM on 256 x 256 tiles (CPU only).
+
+Every operand's slab is two regions of 128 rows (contraction-major: 64 rows of half the tile's columns) in one of two stages.
+Unit u of a region (16 bytes) goes to its LDS bytes [16 u, 16 u + 16), and the lane that asks for it chooses which piece of
+which row that is.  This restates the kernel's formulas and its order of loads and reads, and checks that every request the
+range check lets through stays inside its operand, that the fragment reads find the piece they want, and that no region is
+read before its load was waited for or loaded again before its reads were."""
+import pytest
+
+KB, THREADS, NLD, TA, TB = 128, 512, 2, 4, 2
+
+
+def kswz(r):
+    return ((r & 3) | ((r >> 3) & 1) << 2) << 1
+
+
+def unit(i, tid):
+    """(row, byte) of unit i * THREADS + tid: rows along the contraction, contraction-major rows."""
+    krow = tid >> 4
+    return ((i * (THREADS // 8) + (tid >> 3), ((tid & 7) ^ ((tid >> 4) & 7)) * 16),
+            (i * (THREADS // 16) + krow, ((tid & 15) ^ kswz(krow)) * 16))
+
+
+def test_fragments_find_their_pieces():
+    along, across = {}, {}
+    for i in range(NLD):
+        for tid in range(THREADS):
+            along[i * THREADS + tid], across[i * THREADS + tid] = unit(i, tid)
+    assert sorted(along.values()) == [(r, 16 * p) for r in range(128) for p in range(8)]
+    assert sorted(across.values()) == [(r, 16 * p) for r in range(64) for p in range(16)]
+    for t in range(8):                                       # 16-row tiles of a region
+        for c in range(2):
+            banks = {}
+            for lane in range(64):
+                l16, quad = lane & 15, lane >> 4
+                at = t * 16 * KB + l16 * KB + (((4 * c + quad) ^ ((l16 >> 1) & 7)) << 4)
+                assert along[at // 16] == (t * 16 + l16, (4 * c + quad) * 16)
+                banks.setdefault(quad, set()).add(at // 16 % 16)
+                trow = 8 * quad + (l16 >> 2)
+                for step in (0, 4):                          # the two transposing reads: four columns of row `trow`
+                    at = trow * 256 + (lane & 1) * 8 + c * 32 * 256 + (((t * 2 + ((lane & 3) >> 1)) ^ kswz(trow)) << 4) + step * 256
+                    col = t * 16 + (lane & 3) * 4
+                    assert across[at // 16] == (c * 32 + trow + step, col * 2 // 16 * 16) and at % 16 == col * 2 % 16
+            assert all(len(b) == 16 for b in banks.values())
+
+
+def requests(layout, M, N, K, S, lda, ldb, idx):
+    """(operand, base, size, offset checked, scalar offset, row, byte in the row, wanted)"""
+    kbytes, nk = K * 2, -(-K // 64)
+    a_rows = K if layout == "tn" else S
+    a_bytes, b_bytes = ((a_rows - 1) * lda + (M if layout == "tn" else K)) * 2, ((S - 1) * ldb + N) * 2
+    for m0 in range(0, M, 256):
+        for n0 in range(0, N, 256):
+            for kt in list(range(nk)) + [nk, nk + 1]:        # the loop asks for two slabs past the end
+                live = kt < nk
+                for r in range(2):
+                    for i in range(NLD):
+                        for tid in (0, 1, 7, 8, 130, 511):
+                            (row, kpos), (krow, kcol) = unit(i, tid)
+                            row += r * 128
+                            in_k = kpos < kbytes - kt * KB
+                            k = kt * 64 + krow
+                            if layout == "tn":
+                                off = kt * 64 * lda * 2 if live else 0
+                                yield ("A", m0 * 2 + off, ((K - 1) * lda + M - m0) * 2 - off if live else 0, krow * lda * 2 + r * 256 + kcol, 0, k,
+                                       m0 * 2 + r * 256 + kcol, k < K)
+                                tok = idx[k] * ldb * 2 if k < K else b_bytes
+                                yield ("B", 0, b_bytes, tok if tok == b_bytes else tok + n0 * 2 + r * 256 + kcol, 0, idx[k] if k < K else 0,
+                                       n0 * 2 + r * 256 + kcol, k < K)
+                                continue
+                            m = min(m0 + row, M - 1)
+                            a_row = idx[m] if layout == "nt" else m
+                            yield "A", 0, a_bytes, a_row * lda * 2 + kpos if in_k else a_bytes, kt * KB, a_row, kt * KB + kpos, in_k
+                            if layout == "nt":
+                                size = (min(256, N - n0) - 1) * ldb * 2 + kbytes
+                                yield ("B", n0 * ldb * 2, size, row * ldb * 2 + kpos if in_k else size, kt * KB, n0 + row, kt * KB + kpos,
+                                       in_k and n0 + row < N)
+                            else:
+                                off = kt * 64 * ldb * 2 if live else 0
+                                yield ("B", n0 * 2 + off, ((K - 1) * ldb + N - n0) * 2 - off if live else 0, krow * ldb * 2 + r * 256 + kcol, 0, k,
+                                       n0 * 2 + r * 256 + kcol, k < K)
+
+
+@pytest.mark.parametrize("layout,M,N,K,pad", [("nt", 300, 270, 72, 0), ("nt", 1, 1, 8, 8), ("nt", 257, 513, 200, 16), ("nn", 260, 264, 72, 0),
+                                              ("nn", 300, 512, 200, 8), ("tn", 264, 520, 65, 0), ("tn", 256, 264, 131, 8), ("tn", 8, 8, 1, 0)])
+def test_no_request_leaves_its_operand(layout, M, N, K, pad):
+    S = (K if layout == "tn" else M) + (0 if layout == "nn" else 9)
+    idx = [(7 * r + 3) % S for r in range(K if layout == "tn" else M)]
+    lda, ldb = (M if layout == "tn" else K) + pad, (K if layout == "nt" else N) + pad
+    width = {"A": M if layout == "tn" else K, "B": K if layout == "nt" else N}
+    total = {"A": (((K if layout == "tn" else S) - 1) * lda + width["A"]) * 2, "B": (({"nt": N, "nn": K, "tn": S}[layout] - 1) * ldb + width["B"]) * 2}
+    for op, base, size, voff, soff, row, byte, wanted in requests(layout, M, N, K, S, lda, ldb, idx):
+        if voff + 16 <= size:                                # the hardware lets it through
+            assert 0 <= base + voff + soff <= total[op] - 16, (op, base, size, voff, soff)
+        if wanted and byte + 16 <= width[op] * 2:
+            assert voff + 16 <= size and base + voff + soff == row * (lda if op == "A" else ldb) * 2 + byte, (op, row, byte)
+        if not wanted:
+            assert voff >= size, (op, row, byte)             # arrives as zeros
+
+
+@pytest.mark.parametrize("nk", [1, 2, 3, 6])
+@pytest.mark.parametrize("tn", [False, True])
+def test_regions_are_waited_for_and_free(nk, tn):
+    """One wave's order of loads, waits and reads; a barrier makes what every wave has waited for true of all of them."""
+    events = []                                              # loads in issue order: (region, slab), one entry per load
+    place = lambda reg, kt: (reg, kt & 1)                    # where a region of a slab lies
+    landed, holds, unread = 0, {}, {}
+
+    def load(reg, kt):
+        p = place(reg, kt)
+        assert not unread.get(p), (reg, kt, "overwrites fragments still to be read")
+        for _ in range(NLD):
+            events.append((p, kt))
+        holds[p], unread[p] = kt, True
+
+    def read(reg, kt, published):
+        p = place(reg, kt)
+        assert holds[p] == kt and max(n for n, e in enumerate(events) if e == (p, kt)) < published, (reg, kt)
+
+    for reg, kt in [("B0", 0), ("A0", 0), ("B1", 0), ("A1", 0), ("B1", 1), ("A0", 1), ("B0", 1)]:
+        load(reg, kt)
+    published = len(events) - 5 * NLD
+    late = []                                                # read in the quarter before: awaited by the next barrier but one
+    for reg in ("B0", "A0"):
+        read(reg, 0, published)
+        unread[place(reg, 0)] = False                        # (all fragments awaited before the loop)
+    for kt in range(nk):
+        F, L = ("B0", "B1") if kt % 2 == 0 else ("B1", "B0")
+        published = len(events) - 3 * NLD
+        for q1, q2, loads in (((L, kt), ("A1", kt), [("A1", kt + 1), (F, kt + 2)]), ((L, kt + 1), ("A0", kt + 1), [("A0", kt + 2), (L, kt + 2)])):
+            done, late = late, []
+            for p in done:
+                unread[p] = False
+            if tn and q2[0] == "A0":
+                events.append(("tokens", kt + 4))
+            for reg, s in loads:
+                load(reg, s)
+            read(*q1, published)
+            read(*q2, published)
+            # at the next barrier the first quarter's reads are awaited, the second's only at the one after
+            unread[place(*q1)] = False
+            late = [place(*q2)]
+            published = len(events) - 3 * NLD

@@ -815,6 +815,16 @@ def test_gather_gemm_tiles_exact(lemo, form, M, N, K, dtype):
     assert torch.equal(got[:, :N], want.float().to(dt))
 
 
+@pytest.mark.parametrize("form,M,N,K", [
+    # one piece of a slab, a whole slab and a piece more, an odd and an even number of slabs; ragged rows and columns
+    ("nt", 4000, 4090, 8), ("nt", 4000, 4090, 64), ("nt", 3841, 4096, 72), ("nt", 4000, 4090, 128), ("nt", 4000, 4090, 136), ("nt", 3585, 4353, 1000),
+    ("add", 4001, 4088, 56), ("add", 3841, 4097, 200), ("dx", 3841, 4104, 8), ("dx", 4000, 4088, 64), ("dx", 3841, 4096, 328),
+    ("dw", 4104, 4088, 1), ("dw", 4104, 4096, 63), ("dw", 3848, 4360, 64), ("dw", 4096, 4096, 65), ("dw", 4104, 4088, 129), ("dw", 3848, 4104, 327)])
+def test_gather_gemm_large_tiles_exact(lemo, form, M, N, K):
+    """256 x 256 tiles over contractions of few slabs, where the loads run ahead of the last one from the start."""
+    test_gather_gemm_tiles_exact(lemo, form, M, N, K, "bf16")
+
+
 @pytest.mark.parametrize("far", ["dY", "X"])
 def test_gather_gemm_dw_f32_beyond_32_bit_offsets(lemo, far):
     """binary32 weight gradient of operands whose row pitch is 8 MiB and more, which goes through transposed copies in the
