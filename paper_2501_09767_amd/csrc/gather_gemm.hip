@@ -8,57 +8,65 @@
 
 namespace lemo {
 
-// Which tiles a product is cut into: the first `cols256` columns into 256 x 256 tiles, the others into `rest` tiles.
+// Which tiles a product is cut into: the first `head_cols` columns into `head` tiles, the others into `rest` tiles.
 //
-// The large tile is the fastest per flop but comes in rounds of 256, one per CU, and a round lasts as long for one tile
-// as for (nearly) all: with few tiles, or just past a full round, smaller ones win although they move more bytes per
-// flop.  The choice is the least of these times, in us, for a contraction of k slabs of 128 bytes; the constants are
-// fits to M = 64 ... 9856, N = 256 ... 14336, K = 256 ... 11008, in a stream of other work (within a fourth of what was
-// measured; with the operands in the caches already, the smaller tiles take up to 40 % less than this):
-//   256 x 256  6 + k (1.5 per full round + 1.5 for a last one over half full, 1.15 otherwise)
-//   128 x 128  4 + (k + 3) (0.6 up to 256 tiles -- one per CU --, then n/512 + 0.25, at least 0.95)
-//   64 x 64    4 + (2 + 0.25 k) per 256 tiles
-//   256 x 256 for the columns that fill whole rounds, 128 x 128 for the rest: the sum (the launches follow each other)
-// e.g. M = 256, N = K = 4096: 80 / 32 / 17.5 us; M = 256, N = 11008, K = 4096: 82 / 45 / 58; M = 1500, N = K = 4096: 85 /
-// 59 / 97; M = 3280, N = 11008, K = 4096: 282 / 292 / 565, and 9856 rows of it 705 / 815 / 1610.  Between 256 x 256 and
-// 128 x 128 the line is known to a fifth: M = 2000, N = 4096, K = 11008 takes the large tiles, 191 / 176 / 270.
-// Weight gradients (GG_TN): both operands pass the transposing read, which the 128 x 128 tile pays twice as often; it
-// takes over where the large tiles leave half the CUs idle (256 x 256 / 128 x 128, N = 4096: C = 1024, 64 large tiles, 700
-// tokens 28 / 14.5 us; 4000 tokens, C = 2048, 128 tiles 113 / 78, C = 2304, 144 tiles 113 / 107, C = 3072, 192 tiles 115 / 112,
-// C = 4096, 256 tiles 133 / 145; N = 11008, C = 4096, 9856 tokens: 862 / 1317).
+// The larger the tile the faster per flop, but tiles come in rounds of 256, one per CU, and a round lasts nearly as long for one
+// tile as for all: with few tiles, or just past a full round, smaller ones win although they move more bytes per flop.
+// The time of n tiles of a kind over k slabs of 64 elements of the contraction, in us, is taken as
+//   a + full (b k + e) + (c + d f) k + e f          full whole rounds, the last one filled to f (nothing if f = 0)
+// with a the launch, b a slab in a full round, c ... c + d in the last one (c: if it is the first, if there are rounds before), e
+// what a round costs besides (loads before, stores after).  Fitted to the four kinds over M = 64 ... 5000 with the widths and contractions of layers of 256 to 4096 (N or K up to
+// 14336), 143 products X W^T, 66 input and 66 weight gradients, operands from HBM: each kind within 4 to 13 % (rms); the
+// kind chosen costs 0.1 % over the best one on average, 6 % at worst.
+// e.g. us for 256 x 256 / 256 x 128 / 128 x 128 / 64 x 64:  M = 200, N = K = 4096  75 / 50 / 35 / 20;   M = 504, N = 11008,
+// K = 4096  79 / 57 / 69 / 103;   M = 1504, N = K = 4096  79 / 57 / 73 / 96;   M = 3280, N = K = 4096  87 / 101 / 129 / 194.
+// Products that fill whole rounds with one of the two large kinds may take another for the columns behind them (the launches
+// follow each other, so the times add).
 // binary32: the products are bound by MFMA issue at any tile size, so only the fill counts: 128 x 128, or 32 x 32 tiles
 // with the contraction split over four waves, up to 192 of the former (M = 200, N = K = 768: 51 / 11.6 us; 96 tiles, M = 500,
 // N = 3072, K = 768: 54 / 32; 160, M = 640, N = 4096, K = 1024: 69 / 59; 192, M = 768: 69.5 / 68.6; 256, M = 1024: 71 / 87; dW of 700
 // tokens, 4096 x 1024, 256 tiles: 54 / 81).  Past 256 a second round that is nearly empty would favour the small tiles again
 // (288 tiles, M = 1500, N = 3072, K = 768: 97 / 80); with more rounds the two are alike (1032 tiles, M = 1500, N = 11008, K = 4096:
 // 1193 / 1201, which 256 x 256 tiles took 1852 for).
-struct GgPlan { int cols256; GgTile rest; };
+struct GgPlan { int head_cols; GgTile head, rest; };
+struct GgFit { int rows, cols; double a, b, c[2], d, e; };
 static GgPlan gg_plan(long long M, int N, int K, int layout, lemo_dtype_t dt) {
-    auto tiles = [&](int b, int n) { return (double)((M + b - 1) / b) * (double)((n + b - 1) / b); };
-    const double n256 = tiles(256, N), n128 = tiles(128, N), n64 = tiles(64, N);
-    if (dt == LEMO_F32) return {0, n128 <= 192 ? GG_T64 : GG_T128};
+    // in the order of GgTile
+    static constexpr GgFit along[4] = {{256, 256, 6.8, 1.48, {1.02, 0.99}, 0.30, 2.3}, {256, 128, 4.2, 0.87, {0.64, 0.59}, 0.22, 3.8},
+                                       {128, 128, 1.7, 0.54, {0.48, 0.43}, 0.09, 3.2}, {64, 64, 2.4, 0.21, {0.24, 0.225}, 0.02, 2.9}};
+    static constexpr GgFit across[4] = {{256, 256, 5.6, 1.51, {1.16, 1.16}, 0.14, 7.1}, {256, 128, 5.0, 0.94, {0.75, 0.75}, 0.13, 5.0},
+                                        {128, 128, 3.2, 0.59, {0.56, 0.56}, 0.02, 3.6}, {64, 64, 4.4, 0.18, {0.17, 0.17}, 0.30, 4.2}};
+    if (dt == LEMO_F32) {
+        const double n128 = (double)((M + 127) / 128) * (double)(((long long)N + 127) / 128);
+        return {0, GG_T128, n128 <= 192 ? GG_T64 : GG_T128};
+    }
+    const GgFit* fits = layout == GG_TN ? across : along;
     const double k = K / 64.;
-    auto t256 = [&](double n) {
-        const double full = (double)(long long)(n / 256), rem = n - 256 * full;
-        return 6 + k * (1.5 * full + (rem == 0 ? 0. : rem <= 128 ? 1.15 : 1.5));
+    auto time = [&](const GgFit& f, long long cols) {
+        const double n = (double)((M + f.rows - 1) / f.rows) * (double)((cols + f.cols - 1) / f.cols);
+        const double full = (double)(long long)(n / 256), part = n / 256 - full;
+        return f.a + full * (f.b * k + f.e) + (part == 0 ? 0. : (f.c[full > 0] + f.d * part) * k + f.e * part);
     };
-    auto t128 = [&](double n) { return 4 + (k + 3) * (n <= 256 ? 0.6 : n / 512 + 0.25 > 0.95 ? n / 512 + 0.25 : 0.95); };
-    auto t64 = [&](double n) { return 4 + (2 + 0.25 * k) * (double)((long long)(n + 255) / 256); };
-    if (layout == GG_TN) {
-        if (n256 > 128) return {N, GG_T128};
-        return {0, t64(n64) < t128(n128) ? GG_T64 : GG_T128};
+    GgPlan best{0, GG_T256, GG_T256};
+    double least = time(fits[0], N);
+    for (int t = 1; t < 4; ++t)
+        if (time(fits[t], N) < least) { least = time(fits[t], N); best.rest = (GgTile)t; }
+    for (int h = 0; h < 2; ++h) {
+        const long long tm = (M + 255) / 256, rounds = tm * ((N + fits[h].cols - 1) / fits[h].cols) / 256;
+        const long long cols = rounds * 256 / tm * fits[h].cols;  // columns whose tiles fit whole rounds
+        if (cols <= 0 || cols >= N) continue;
+        for (int t = h + 1; t < 4; ++t) {
+            const double both = time(fits[h], cols) + time(fits[t], N - cols);
+            if (both < least) { least = both; best = {(int)cols, (GgTile)h, (GgTile)t}; }
+        }
     }
-    GgPlan best{N, GG_T128};
-    double t = t256(n256);
-    const long long tm = (M + 255) / 256, rounds = (long long)n256 / 256;
-    const long long cols = rounds * 256 / tm * 256;  // columns whose tiles fit whole rounds
-    if (rounds > 0 && cols > 0 && cols < N) {
-        const double mixed = t256((double)tm * (double)(cols / 256)) + t128(tiles(128, N - (int)cols));
-        if (mixed < t) { t = mixed; best = {(int)cols, GG_T128}; }
-    }
-    if (t128(n128) < t) { t = t128(n128); best = {0, GG_T128}; }
-    if (t64(n64) < t) best = {0, GG_T64};
     return best;
+}
+
+static int launch_tiles(const GgParams& p, lemo_dtype_t dt, bool add, int layout, GgTile tile, hipStream_t st) {
+    if (dt == LEMO_F32 || tile == GG_T64) return launch_gather_gemm_small(p, dt, add, layout, tile, st);
+    if (tile == GG_T256) return launch_gather_gemm_large(p, add, layout, st);
+    return launch_gather_gemm_mid(p, add, layout, tile, st);
 }
 
 template <bool ADD, int LAYOUT>
@@ -83,23 +91,22 @@ static int launch_gg(const GgParams& p, lemo_dtype_t dt, hipStream_t st) {
         return 0;
     }
     const GgPlan plan = gg_plan(p.M, p.N, p.K, LAYOUT, dt);
-    if (plan.cols256 >= p.N) return launch_gather_gemm_large(p, ADD, LAYOUT, st);  // (never binary32)
     GgParams rest = p;
-    if (plan.cols256 > 0) {
+    if (plan.head_cols > 0) {  // (never binary32)
         GgParams head = p;
-        head.N = plan.cols256;
-        const int rc = launch_gather_gemm_large(head, ADD, LAYOUT, st);
+        head.N = plan.head_cols;
+        const int rc = launch_tiles(head, dt, ADD, LAYOUT, plan.head, st);
         if (rc) return rc;
-        // the same product on the columns behind: bases move by cols256 columns, the output's span shrinks by as much
-        // (bf16, and not GG_TN, whose b_bytes would move as well)
-        const long long c = plan.cols256;
-        rest.N -= plan.cols256;
+        // the same product on the columns behind: bases move by head_cols columns, the spans that begin there shrink by as much
+        const long long c = plan.head_cols;
+        rest.N -= plan.head_cols;
         rest.B = static_cast<const bf16_t*>(p.B) + (LAYOUT == GG_NT ? c * p.ldb : c);
         rest.Y = static_cast<bf16_t*>(p.Y) + c;
         if (p.bias) rest.bias = static_cast<const bf16_t*>(p.bias) + c;
+        if (LAYOUT == GG_TN) rest.b_bytes -= (unsigned)c * 2u;
         if (ADD) rest.y_bytes -= (unsigned)c * 2u;
     }
-    return launch_gather_gemm_small(rest, dt, ADD, LAYOUT, plan.rest, st);
+    return launch_tiles(rest, dt, ADD, LAYOUT, plan.rest, st);
 }
 
 static unsigned span_bytes(long long rows, long long ld, long long cols, lemo_dtype_t dt) {  // host checked: fits 32 bits

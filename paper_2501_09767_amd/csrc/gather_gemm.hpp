@@ -1,4 +1,5 @@
-// What the two selective-load GEMM kernels (256 x 256 tiles: gather_gemm_large.hip; smaller ones: gather_gemm_small.hip) share.
+// What the selective-load GEMM kernels share: gather_gemm_large.hip (256 x 256 tiles), gather_gemm_mid.hip (256 x 128 and
+// 128 x 128), gather_gemm_small.hip (64 x 64; all of binary32).
 #pragma once
 #include <type_traits>
 
@@ -50,8 +51,10 @@ __device__ __forceinline__ bool gg_tile(int b, int tiles_m, int tiles_n, int gro
     return true;
 }
 
-enum GgTile { GG_T128, GG_T64 };  // output tiles of gather_gemm_small.hip: 128 x 128; 64 x 64 (binary32: 32 x 32)
-int launch_gather_gemm_large(const GgParams& p, bool add, int layout, hipStream_t st);  // 256 x 256 tiles, bf16: gather_gemm_large.hip
+// Output tiles.  binary32 knows GG_T128 and GG_T64 only, both in gather_gemm_small.hip, the latter 32 x 32.
+enum GgTile { GG_T256, GG_T256x128, GG_T128, GG_T64 };
+int launch_gather_gemm_large(const GgParams& p, bool add, int layout, hipStream_t st);               // GG_T256, bf16
+int launch_gather_gemm_mid(const GgParams& p, bool add, int layout, GgTile tile, hipStream_t st);    // GG_T256x128, GG_T128, bf16
 int launch_gather_gemm_small(const GgParams& p, lemo_dtype_t dt, bool add, int layout, GgTile tile, hipStream_t st);
 
 }  // namespace lemo

@@ -23,32 +23,26 @@
 // ahead of the wait, in the barriers' place (793).
 #include <mutex>
 
-#include "gather_gemm.hpp"
+#include "gather_gemm_regions.hpp"
 
 namespace lemo {
 
 constexpr int LG_BM = 256, LG_BN = 256;
-constexpr int LG_KB = 128;               // bytes of the contraction per slab
-constexpr int LG_KROWS = LG_KB / 2;      // rows of a contraction-major slab
-constexpr int LG_REGION = 128 * LG_KB;   // one operand's half of a slab: 128 rows of 128 bytes, or 64 contraction rows of 256 bytes
-constexpr int LG_STAGE = 2 * LG_REGION;  // rows (columns of the output) 0-127, 128-255
+constexpr int LG_STAGE = 2 * RG_BYTES;   // regions: rows (columns of the output) 0-127, 128-255
 constexpr int LG_OPER = 2 * LG_STAGE;    // two stages of A, then two of B: 64 KB, the reach of an LDS read's immediate offset
-constexpr int LG_TOK = 2 * LG_OPER;     // (GG_TN) token rings: per wave 4 slabs of 64 indices
+constexpr int LG_TOK = 2 * LG_OPER;      // (GG_TN) token rings
 constexpr int LG_EP = LG_BN * 2 + 16;    // epilogue: LDS pitch of a row of bf16, ...
 constexpr int LG_EPF = LG_BN * 4 + 16;   // ... of binary32 (128 rows at a time)
-
-constexpr int LG_WAVES = 8, LG_THREADS = 64 * LG_WAVES, LG_WN = 4;  // waves, along the columns
+constexpr int LG_WN = 4;                 // waves along the columns
 constexpr int LG_TA = 4, LG_TB = 2;      // 16-row tiles of a wave per half of A, of B
-constexpr int LG_NLD = LG_REGION / (16 * LG_THREADS);  // loads per thread and region
-constexpr int LG_LDS_LOOP = LG_TOK + LG_WAVES * 1024;
 constexpr int LG_LDS_EPI = LG_BM * LG_EP > 128 * LG_EPF ? LG_BM * LG_EP : 128 * LG_EPF;
-constexpr int LG_LDS = LG_LDS_LOOP > LG_LDS_EPI ? LG_LDS_LOOP : LG_LDS_EPI;
+constexpr int LG_LDS = LG_TOK + RG_TOK > LG_LDS_EPI ? LG_TOK + RG_TOK : LG_LDS_EPI;
 static_assert(LG_LDS <= 160 * 1024, "a workgroup's LDS");
 
 template <bool ADD, int LAYOUT>
-__global__ __launch_bounds__(LG_THREADS, 1) void gather_gemm_large_kernel(GgParams p) {
+__global__ __launch_bounds__(RG_THREADS, 1) void gather_gemm_large_kernel(GgParams p) {
     constexpr bool A_KMAJOR = LAYOUT == GG_TN, B_KMAJOR = LAYOUT != GG_NT;
-    constexpr int TA = LG_TA, TB = LG_TB, NL = LG_NLD, T = LG_THREADS;
+    constexpr int TA = LG_TA, TB = LG_TB, NL = RG_NLD;
     extern __shared__ __attribute__((aligned(16))) char smem[];
 
     int tm, tn;
@@ -58,114 +52,14 @@ __global__ __launch_bounds__(LG_THREADS, 1) void gather_gemm_large_kernel(GgPara
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int wm = wave / LG_WN, wn = wave % LG_WN;
-    const bf16_t* A = static_cast<const bf16_t*>(p.A);
-    const bf16_t* B = static_cast<const bf16_t*>(p.B);
-    const unsigned lda_bytes = (unsigned)p.lda * 2, ldb_bytes = (unsigned)p.ldb * 2;  // host: both < 2^23
-    const int K = p.K, kbytes = K * 2;
-    const int nk = (K + LG_KROWS - 1) / LG_KROWS;
-
-    // Loads.  Unit u = i * T + tid of a region is its LDS bytes [16 u, 16 u + 16); the lane asks for the piece that belongs there.
-    // Rows along the contraction, 8 pieces: piece p of row r at p ^ (r / 2 % 8), so that one piece of 16 rows meets all banks.
-    // Contraction-major rows, 16 pieces of 8 columns: at p ^ kswz(r); a half-wave of a transposing read takes rows 0-3 and 8-11
-    // (+ 4, + 16), two pieces each.  The hardware range check sees the per-thread offset only: rows past an operand's end fail it
-    // (or are clamped to the last one, A), pieces past the end of the contraction are given an offset at the descriptor's size in
-    // both operands and arrive as zeros; the scalar offset moves along a row.
-    auto kswz = [](int r) { return ((r & 3) | ((r >> 3) & 1) << 2) << 1; };
-    const int kpos = ((tid & 7) ^ ((tid >> 4) & 7)) * 16;
-    const int krow = tid >> 4, kcol = ((tid & 15) ^ kswz(krow)) * 16;
-    unsigned a_voff[2][NL], b_voff[2][NL];
-#pragma unroll
-    for (int r = 0; r < 2; ++r)
-#pragma unroll
-        for (int i = 0; i < NL; ++i) {
-            const int row = r * 128 + i * (T / 8) + (tid >> 3), kr = i * (T / 16) + krow;
-            if constexpr (A_KMAJOR) {
-                a_voff[r][i] = kr * lda_bytes + r * 256 + kcol;
-            } else {
-                const long long m = min(m0 + row, p.M - 1);
-                const unsigned tok = p.idx ? (unsigned)p.idx[m] : (unsigned)m;
-                a_voff[r][i] = tok * lda_bytes + kpos;
-            }
-            if constexpr (LAYOUT == GG_NT) b_voff[r][i] = row * ldb_bytes + kpos;
-            else if constexpr (LAYOUT == GG_NN) b_voff[r][i] = kr * ldb_bytes + r * 256 + kcol;
-            else b_voff[r][i] = (unsigned)n0 * 2 + r * 256 + kcol;
-        }
-    // (GG_NT) this tile's rows of B
-    const int b_rows = min(LG_BN, p.N - n0);
-    const unsigned bn_bytes = (b_rows - 1) * ldb_bytes + kbytes;
-    // contraction-major operand: from the slab's first row (and the tile's first column) to the operand's end, which refuses
-    // the rows past it (host: the operand spans < 2^31 bytes)
-    auto kmajor_rsrc = [&](const bf16_t* col0, unsigned ld_bytes, unsigned cols, int kt) {
-        const bool live = kt < nk;
-        const unsigned off = live ? (unsigned)(kt * LG_KROWS) * ld_bytes : 0u;
-        const unsigned size = live ? (unsigned)(K - 1) * ld_bytes + cols * 2 - off : 0u;
-        return raw_rsrc(reinterpret_cast<const char*>(col0) + off, size);
-    };
+    const int l16 = lane & 15, quad = lane >> 4;
+    using Loads = RgLoads<LAYOUT, 2, 2>;
+    using Slab = typename Loads::Slab;
+    Loads ld(p, m0, n0, tid, smem + LG_TOK + wave * 1024);
+    const int nk = ld.nk;
     const unsigned lds0 = __builtin_amdgcn_readfirstlane(lds_offset_of(smem) + wave * 1024);
-    const unsigned lds_tok = __builtin_amdgcn_readfirstlane(lds_offset_of(smem) + LG_TOK + wave * 1024);
-    const u32x4 idx_rsrc = raw_rsrc(p.idx, p.idx ? (long long)K * 4 : 0);
-    auto issue_tokens = [&](int kt) {  // indices of slab kt into the wave's ring
-        if constexpr (LAYOUT == GG_TN) lds_direct_b32(idx_rsrc, lds_tok + (kt & 3) * 256, kt * (LG_KROWS * 4) + lane * 4);
-    };
-    struct Slab { u32x4 a, b; int soff; unsigned stage; bool in_k; };
-    auto slab_of = [&](int kt) {
-        Slab s;
-        s.soff = kt * LG_KB;
-        s.in_k = kpos < kbytes - s.soff;
-        s.stage = lds0 + (kt & 1) * LG_STAGE;
-        s.a = A_KMAJOR ? kmajor_rsrc(A + m0, lda_bytes, (unsigned)(p.M - m0), kt) : raw_rsrc(A, p.a_bytes);
-        s.b = LAYOUT == GG_NN ? kmajor_rsrc(B + n0, ldb_bytes, (unsigned)(p.N - n0), kt)
-                              : raw_rsrc(LAYOUT == GG_NT ? B + (long long)n0 * p.ldb : B, LAYOUT == GG_NT ? bn_bytes : p.b_bytes);
-#pragma unroll
-        for (int e = 0; e < 4; ++e) {  // uniform values; the assembly wants them in scalar registers
-            s.a[e] = __builtin_amdgcn_readfirstlane(s.a[e]);
-            s.b[e] = __builtin_amdgcn_readfirstlane(s.b[e]);
-        }
-        return s;
-    };
-    unsigned tok[LAYOUT == GG_TN ? NL : 1];
-    auto read_tokens = [&](int kt) {  // the rows of B of slab kt
-        if constexpr (LAYOUT == GG_TN) {
-#pragma unroll
-            for (int i = 0; i < NL; ++i) {
-                const int kr = i * (T / 16) + krow, k = kt * LG_KROWS + kr;
-                const unsigned row = p.idx ? *reinterpret_cast<const unsigned*>(smem + LG_TOK + wave * 1024 + (kt & 3) * 256 + kr * 4) : (unsigned)k;
-                tok[i] = k < K ? row * ldb_bytes : p.b_bytes;  // (a row past the end: at or past the descriptor's size with any column)
-            }
-        }
-    };
-    auto load_a = [&](const Slab& s, int r, int i) {
-        const unsigned dst = s.stage + r * LG_REGION + i * (T * 16);
-        if constexpr (A_KMAJOR) lds_direct_b128(s.a, dst, (int)a_voff[r][i]);
-        else lds_direct_b128(s.a, dst, (int)(s.in_k ? a_voff[r][i] : p.a_bytes), s.soff);
-    };
-    auto load_b = [&](const Slab& s, int r, int i) {
-        const unsigned dst = s.stage + LG_OPER + r * LG_REGION + i * (T * 16);
-        if constexpr (LAYOUT == GG_TN) lds_direct_b128(s.b, dst, (int)(tok[i] == p.b_bytes ? tok[i] : tok[i] + b_voff[r][i]));
-        else if constexpr (LAYOUT == GG_NN) lds_direct_b128(s.b, dst, (int)b_voff[r][i]);
-        else lds_direct_b128(s.b, dst, (int)(s.in_k ? b_voff[r][i] : bn_bytes), s.soff);
-    };
-    auto barrier = [&]() {
-        asm volatile("" ::: "memory");
-        __builtin_amdgcn_sched_barrier(0);
-        __builtin_amdgcn_s_barrier();
-        asm volatile("" ::: "memory");
-        __builtin_amdgcn_sched_barrier(0);
-    };
-
-    // fragment (16-row tile t of a region, chunk c of the slab); the transposing read: see gather_gemm.hpp
-    const int l16 = lane & 15, quad = lane >> 4;  // MFMA operands: lane holds row l16 of a 16-row tile, elements 8 quad .. + 7 of a chunk of 32
-    const int swz = (l16 >> 1) & 7;
-    const int trow = 8 * quad + (l16 >> 2);  // this lane's row of a transposing read
-    const int tr_base = trow * 256 + (lane & 1) * 8, tr_piece = (lane & 3) >> 1, tr_swz = kswz(trow);
-    auto frag = [&](const char* region, bool kmajor, int t, int c) {
-        if (!kmajor) return *reinterpret_cast<const u32x4*>(region + t * 16 * LG_KB + l16 * LG_KB + (((4 * c + quad) ^ swz) << 4));
-        const char* at = region + tr_base + c * 32 * 256 + (((t * 2 + tr_piece) ^ tr_swz) << 4);
-        const s16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((s16x4 __attribute__((address_space(3)))*)(at));
-        const s16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((s16x4 __attribute__((address_space(3)))*)(at + 4 * 256));
-        const uint2 l2 = __builtin_bit_cast(uint2, lo), h2 = __builtin_bit_cast(uint2, hi);
-        return u32x4{l2.x, l2.y, h2.x, h2.y};
-    };
+    auto load_a = [&](const Slab& s, int kt, int r, int i) { ld.load_a(s, r, i, lds0 + (kt & 1) * LG_STAGE + r * RG_BYTES); };
+    auto load_b = [&](const Slab& s, int kt, int r, int i) { ld.load_b(s, r, i, lds0 + LG_OPER + (kt & 1) * LG_STAGE + r * RG_BYTES); };
 
     f32x4 acc[2][TA][2][TB];  // [half of A][tile][half of B][tile]
 #pragma unroll
@@ -178,8 +72,8 @@ __global__ __launch_bounds__(LG_THREADS, 1) void gather_gemm_large_kernel(GgPara
                 for (int j = 0; j < TB; ++j) acc[a][i][b][j] = f32x4{0.f, 0.f, 0.f, 0.f};
     // fragments: the current half of A, both halves of B
     u32x4 fa[2][TA], fb[2][2][TB];
-    auto read_a = [&](int st, int r, int c, int i) { fa[c][i] = frag(smem + st * LG_STAGE + r * LG_REGION, A_KMAJOR, wm * TA + i, c); };
-    auto read_b = [&](int st, int r, int c, int j) { fb[r][c][j] = frag(smem + LG_OPER + st * LG_STAGE + r * LG_REGION, B_KMAJOR, wn * TB + j, c); };
+    auto read_a = [&](int st, int r, int c, int i) { fa[c][i] = rg_fragment(smem + st * LG_STAGE + r * RG_BYTES, A_KMAJOR, wm * TA + i, c, lane); };
+    auto read_b = [&](int st, int r, int c, int j) { fb[r][c][j] = rg_fragment(smem + LG_OPER + st * LG_STAGE + r * RG_BYTES, B_KMAJOR, wn * TB + j, c, lane); };
 
     constexpr int NM = 2 * TA * TB;  // MFMAs of a quarter
     // One quarter of a slab: the MFMAs of (half AH of A) x (half BH of B), `mem(q, c, i, j)` behind MFMA q, which is of chunk c
@@ -191,42 +85,41 @@ __global__ __launch_bounds__(LG_THREADS, 1) void gather_gemm_large_kernel(GgPara
             const int c = q / (TA * TB), w = q % (TA * TB), u = by_columns ? w / TA : w / TB, v = by_columns ? w % TA : w % TB;
             const int back = by_columns ? TA - 1 - v : TB - 1 - v, t = u & 1 ? back : v, i = by_columns ? t : u, j = by_columns ? u : t;
             __builtin_amdgcn_sched_barrier(0);
-            // (the operands exchanged: a lane holds one row of the output, four consecutive columns of it)
-            acc[AH][i][BH][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, fb[BH][c][j]), __builtin_bit_cast(bf16x8, fa[c][i]), acc[AH][i][BH][j], 0, 0, 0);
+            rg_mma(acc[AH][i][BH][j], fa[c][i], fb[BH][c][j]);
             mem(q, c, i, j);
             __builtin_amdgcn_sched_barrier(0);
         }
     };
     using I0 = std::integral_constant<int, 0>;
     using I1 = std::integral_constant<int, 1>;
-    auto load_region = [&](const Slab& s, bool a, int r) {
+    auto load_region = [&](const Slab& s, int kt, bool a, int r) {
 #pragma unroll
         for (int i = 0; i < NL; ++i) {
-            if (a) load_a(s, r, i); else load_b(s, r, i);
+            if (a) load_a(s, kt, r, i); else load_b(s, kt, r, i);
         }
     };
 
     // What would have been asked for in the halves before: {B 0} {A 0, B 1} of slab 0, {A 1 of 0, B 1 of 1}, {A 0, B 0 of 1}
     if constexpr (LAYOUT == GG_TN) {
-        for (int kt = 0; kt < 4; ++kt) issue_tokens(kt);
+        for (int kt = 0; kt < 4; ++kt) ld.issue_tokens(kt, lane);
         __builtin_amdgcn_s_waitcnt(vmcnt_imm(0));
         asm volatile("" ::: "memory");
     }
     {
-        const Slab s0 = slab_of(0), s1 = slab_of(1);
-        read_tokens(0);
-        load_region(s0, false, 0);
-        load_region(s0, true, 0);
-        load_region(s0, false, 1);
-        load_region(s0, true, 1);
-        read_tokens(1);
-        load_region(s1, false, 1);
-        load_region(s1, true, 0);
-        load_region(s1, false, 0);
-        read_tokens(2);
+        const Slab s0 = ld.slab(0), s1 = ld.slab(1);
+        ld.read_tokens(0);
+        load_region(s0, 0, false, 0);
+        load_region(s0, 0, true, 0);
+        load_region(s0, 0, false, 1);
+        load_region(s0, 0, true, 1);
+        ld.read_tokens(1);
+        load_region(s1, 1, false, 1);
+        load_region(s1, 1, true, 0);
+        load_region(s1, 1, false, 0);
+        ld.read_tokens(2);
     }
     __builtin_amdgcn_s_waitcnt(vmcnt_imm(5 * NL));
-    barrier();
+    rg_barrier();
 #pragma unroll
     for (int c = 0; c < 2; ++c) {
 #pragma unroll
@@ -239,7 +132,7 @@ __global__ __launch_bounds__(LG_THREADS, 1) void gather_gemm_large_kernel(GgPara
 
     // Waves of one SIMD do not take turns: one of them goes first (X W^T 752 -> 742 us at 8192^3, the gradients no change)
     if constexpr (LAYOUT == GG_NT)
-        if (wave < LG_WAVES / 2) __builtin_amdgcn_s_setprio(1);
+        if (wave < RG_WAVES / 2) __builtin_amdgcn_s_setprio(1);
     // Slab kt, kt & 1 == PAR.  Halves of a slab begin with a barrier, before which every wave has seen to it that the regions
     // read in this half have landed (its own part: all loads but the last IN_FLIGHT, which complete in order) and that it
     // has read what this half's loads overwrite: all but the fragments read in the quarter before.
@@ -250,27 +143,27 @@ __global__ __launch_bounds__(LG_THREADS, 1) void gather_gemm_large_kernel(GgPara
         using IL = std::integral_constant<int, L>;
         __builtin_amdgcn_s_waitcnt(vmcnt_imm(IN_FLIGHT));
         __builtin_amdgcn_s_waitcnt(lgkmcnt_imm(A_KMAJOR ? 15 : 2 * TA));
-        barrier();
-        const Slab s1 = slab_of(kt + 1), s2 = slab_of(kt + 2);
+        rg_barrier();
+        const Slab s1 = ld.slab(kt + 1), s2 = ld.slab(kt + 2);
         quarter(I0{}, IF{}, false, [&](int q, int c, int i, int j) {
             if (q < 2 * TB) read_b(PAR, L, q / TB, q % TB);
             if (q < 2 * NL) {
-                if (q < NL) load_a(s1, 1, q); else load_b(s2, F, q - NL);
+                if (q < NL) load_a(s1, PAR ^ 1, 1, q); else load_b(s2, PAR, F, q - NL);
             }
         });
         quarter(I0{}, IL{}, false, [&](int q, int c, int i, int j) {
             if (q % TB == TB - 1) read_a(PAR, 1, c, i);
         });
         __builtin_amdgcn_s_waitcnt(vmcnt_imm(IN_FLIGHT));
-        barrier();
-        if constexpr (LAYOUT == GG_TN) issue_tokens(kt + 4);
+        rg_barrier();
+        ld.issue_tokens(kt + 4, lane);
         quarter(I1{}, IL{}, true, [&](int q, int c, int i, int j) {
             if (q % TA == TA - 1) read_b(PAR ^ 1, L, c, j);
             if (q < 2 * NL) {
-                if (q < NL) load_a(s2, 0, q); else load_b(s2, L, q - NL);
+                if (q < NL) load_a(s2, PAR, 0, q); else load_b(s2, PAR, L, q - NL);
             }
         });
-        if constexpr (LAYOUT == GG_TN) read_tokens(kt + 3);
+        ld.read_tokens(kt + 3);
         quarter(I1{}, IF{}, false, [&](int q, int c, int i, int j) {
             if (q % TB == TB - 1) read_a(PAR ^ 1, 0, c, i);
         });
@@ -308,7 +201,7 @@ __global__ __launch_bounds__(LG_THREADS, 1) void gather_gemm_large_kernel(GgPara
                 }
     }
     if constexpr (ADD) {
-        constexpr int ROWS = 128 / LG_WAVES, PASSES = ROWS / 2;  // rows a wave finishes per half of the tile
+        constexpr int ROWS = 128 / RG_WAVES, PASSES = ROWS / 2;  // rows a wave finishes per half of the tile
         const bool col_vec = vec_ok && ncol + 8 <= p.N;
         const __amdgpu_buffer_rsrc_t y_rsrc = __builtin_amdgcn_make_buffer_rsrc(p.Y, 0, (int)p.y_bytes, 0x00020000);
         const unsigned NONE = p.y_bytes, ldy_bytes = (unsigned)p.ldy * 2;
@@ -372,7 +265,7 @@ __global__ __launch_bounds__(LG_THREADS, 1) void gather_gemm_large_kernel(GgPara
                             make_uint2(pack_bf16x2_hw(v[0], v[1]), pack_bf16x2_hw(v[2], v[3]));
                     }
         __syncthreads();
-        constexpr int ROWS = LG_BM / LG_WAVES;
+        constexpr int ROWS = LG_BM / RG_WAVES;
 #pragma unroll 4
         for (int q = 0; q < ROWS / 2; ++q) {
             const int row = wave * ROWS + q * 2 + rsub;
@@ -402,7 +295,7 @@ static int launch_large(GgParams p, hipStream_t st) {
     p.tiles_m = (int)((p.M + LG_BM - 1) / LG_BM);
     p.tiles_n = (p.N + LG_BN - 1) / LG_BN;
     const int per_xcd = (p.tiles_m * p.tiles_n + NUM_XCD - 1) / NUM_XCD;
-    hipLaunchKernelGGL((gather_gemm_large_kernel<ADD, LAYOUT>), dim3((unsigned)(per_xcd * NUM_XCD)), dim3(LG_THREADS), LG_LDS, st, p);
+    hipLaunchKernelGGL((gather_gemm_large_kernel<ADD, LAYOUT>), dim3((unsigned)(per_xcd * NUM_XCD)), dim3(RG_THREADS), LG_LDS, st, p);
     return (int)hipGetLastError();
 }
 

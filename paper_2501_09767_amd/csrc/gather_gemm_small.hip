@@ -1,22 +1,19 @@
-// The selective-load GEMM (and its in-place-add and gradient forms, see gather_gemm.hip) on smaller output tiles, for
-// products whose 256 x 256 tiles do not fill the chip's 256 CUs or leave a nearly empty last round.
+// The selective-load GEMM (and its in-place-add and gradient forms, see gather_gemm.hip) on 64 x 64 output tiles (bf16, for
+// products of few tiles) and, in binary32, on 128 x 128 and 32 x 32 ones.
 //
-// A wave computes a 64 x 64 block (2 x 2 MFMA tiles) from slabs of 128 bytes of the contraction; two shapes:
-//   GW = 4  the four waves of a workgroup share a slab: 128 x 128 output tile, two workgroups per CU (70 KB of LDS each).
-//           1.09 PFLOP/s with the chip full of them: the matrix cores are busy 61 % of the cycles (256 x 256 tiles: 68-71 %)
-//           at 1.67 GHz, LDS reads take 33 %, and filling LDS through registers instead takes the same time (823 us
-//           against 815 at the size below), so it is the clock and the issue of two waves per SIMD that hold it.
+// A wave computes a block of 32 x 32 MFMA tiles from slabs of 128 bytes of the contraction; two shapes:
 //   GW = 1  every wave has its own slabs: 64 x 64 output tile, the four waves take every fourth slab of the contraction
 //           each and their partial tiles are added, in wave order, through LDS at the end.  No barrier in the main loop.
-//           Bound by the latency of the loads: 128 KB per CU are in flight, all its LDS holds.  binary32, whose MFMAs
-//           take 16 times as long, is bound by those instead and takes 32 x 32 blocks, for four times the workgroups.
+//           Bound by the latency of the loads: 128 KB per CU are in flight, all its LDS holds (M = 256, N = K = 4096: 17.5 us with
+//           the operands in the caches, 20.8 from HBM).  binary32, whose MFMAs take 16 times as long, is bound by those instead
+//           and takes 32 x 32 blocks, for four times the workgroups.
+//   GW = 4  (binary32) the four waves of a workgroup share a slab: 128 x 128 output tile, 64 x 64 per wave, two workgroups per
+//           CU (70 KB of LDS each).
 // Slabs arrive by LDS-direct loads, two per group in flight, and the registers are the third buffer: the MFMA fragments
 // of the next slab are read during the first MFMAs of the current one, which frees its LDS stage for the slab after next.
-// Measured beside this (M = 256, N = K = 4096 with 64 x 64 tiles: 17.5 us; M = 9856, N = 11008, K = 4096 with 128 x 128
-// tiles: 815 us): a ring of four half-slabs with the loads spread over all MFMAs 21.6 / 1033 us (64-byte row segments
-// halve what an L2 delivers), a ring of two slabs without the registers' lookahead 19.1 / 863 us; the contraction of a
-// 128 x 128 tile split over two groups of four waves, one workgroup per CU, is no faster than one group (M = 256, N = 11008,
-// K = 4096: 45.8 / 45.9 us).
+// Measured beside this (M = 256, N = K = 4096 with 64 x 64 tiles, 17.5 us): a ring of four half-slabs with the loads spread over all
+// MFMAs 21.6 (64-byte row segments halve what an L2 delivers), a ring of two slabs without the registers' lookahead 19.1;
+// 16 x 16 x 32 MFMAs, which pay in the larger tiles, change nothing here (20.6 / 20.9 from HBM).
 #include <mutex>
 
 #include "gather_gemm.hpp"
@@ -46,14 +43,14 @@ template <int GW, int ESZ, int WT> struct SgGeo {
     // banks.  Contraction-major rows: the transposing read (16 bit) takes 4 rows x 4 pieces at a time; of binary32 rows, which
     // are read element by element, the two half-waves take rows 4 apart, 8 pieces each.
     __device__ static constexpr int swz(int r) { return (r >> 1) & 7; }
-    __device__ static constexpr int kswz(int r) { return WT == 1 ? 0 : ESZ == 4 ? ((r >> 2) & 1) << 3 : GW == 4 ? (r & 3) << 2 : ((r >> 1) & 1) << 2; }
+    __device__ static constexpr int kswz(int r) { return WT == 1 ? 0 : ESZ == 4 ? ((r >> 2) & 1) << 3 : ((r >> 1) & 1) << 2; }
 };
 
 template <typename T, bool ADD, int LAYOUT, int GW, int WT>
 __global__ __launch_bounds__(SG_THREADS, GW == 4 ? 2 : 1) void gather_gemm_small_kernel(GgParams p) {
     constexpr bool A_KMAJOR = LAYOUT == GG_TN, B_KMAJOR = LAYOUT != GG_NT;
     constexpr int ESZ = (int)sizeof(T);
-    static_assert(ESZ == 4 || WT == 2, "the 16-bit transposing read is laid out for 64 x 64 blocks");
+    static_assert(ESZ == 4 || (WT == 2 && GW == 1), "the 16-bit transposing read is laid out for 64 x 64 tiles");
     using G = SgGeo<GW, ESZ, WT>;
     constexpr int GROUPS = G::GROUPS, NLD = G::NLD;
     extern __shared__ __attribute__((aligned(16))) char smem[];
@@ -403,8 +400,8 @@ static int launch_small_form(const GgParams& p, bool add, int layout, hipStream_
 }
 
 int launch_gather_gemm_small(const GgParams& p, lemo_dtype_t dt, bool add, int layout, GgTile tile, hipStream_t st) {
-    if (dt == LEMO_F32) return tile == GG_T128 ? launch_small_form<float, 4, 2>(p, add, layout, st) : launch_small_form<float, 1, 1>(p, add, layout, st);
-    return tile == GG_T128 ? launch_small_form<bf16_t, 4, 2>(p, add, layout, st) : launch_small_form<bf16_t, 1, 2>(p, add, layout, st);
+    if (dt == LEMO_BF16) return launch_small_form<bf16_t, 1, 2>(p, add, layout, st);
+    return tile == GG_T128 ? launch_small_form<float, 4, 2>(p, add, layout, st) : launch_small_form<float, 1, 1>(p, add, layout, st);
 }
 
 }  // namespace lemo

@@ -1,10 +1,12 @@
-"""Host model of the loads and LDS positions of the selective-load GEMM on 256 x 256 tiles (CPU only).
+"""Host model of the loads and LDS positions of the selective-load GEMM on 256 x 256, 256 x 128 and 128 x 128 tiles (CPU only).
 
-Every operand's slab is two regions of 128 rows (contraction-major: 64 rows of half the tile's columns) in one of two stages.
+An operand's slab comes in regions of 128 rows (contraction-major: 64 rows of 128 columns); a 256-wide tile has two of them.
 Unit u of a region (16 bytes) goes to its LDS bytes [16 u, 16 u + 16), and the lane that asks for it chooses which piece of
 which row that is.  This restates the kernel's formulas and its order of loads and reads, and checks that every request the
 range check lets through stays inside its operand, that the fragment reads find the piece they want, and that no region is
 read before its load was waited for or loaded again before its reads were."""
+import itertools
+
 import pytest
 
 KB, THREADS, NLD, TA, TB = 128, 512, 2, 4, 2
@@ -44,52 +46,51 @@ def test_fragments_find_their_pieces():
             assert all(len(b) == 16 for b in banks.values())
 
 
-def requests(layout, M, N, K, S, lda, ldb, idx):
+def requests(layout, bm, bn, M, N, K, S, lda, ldb, idx):
     """(operand, base, size, offset checked, scalar offset, row, byte in the row, wanted)"""
     kbytes, nk = K * 2, -(-K // 64)
     a_rows = K if layout == "tn" else S
     a_bytes, b_bytes = ((a_rows - 1) * lda + (M if layout == "tn" else K)) * 2, ((S - 1) * ldb + N) * 2
-    for m0 in range(0, M, 256):
-        for n0 in range(0, N, 256):
-            for kt in list(range(nk)) + [nk, nk + 1]:        # the loop asks for two slabs past the end
-                live = kt < nk
-                for r in range(2):
-                    for i in range(NLD):
-                        for tid in (0, 1, 7, 8, 130, 511):
-                            (row, kpos), (krow, kcol) = unit(i, tid)
-                            row += r * 128
-                            in_k = kpos < kbytes - kt * KB
-                            k = kt * 64 + krow
-                            if layout == "tn":
-                                off = kt * 64 * lda * 2 if live else 0
-                                yield ("A", m0 * 2 + off, ((K - 1) * lda + M - m0) * 2 - off if live else 0, krow * lda * 2 + r * 256 + kcol, 0, k,
-                                       m0 * 2 + r * 256 + kcol, k < K)
-                                tok = idx[k] * ldb * 2 if k < K else b_bytes
-                                yield ("B", 0, b_bytes, tok if tok == b_bytes else tok + n0 * 2 + r * 256 + kcol, 0, idx[k] if k < K else 0,
-                                       n0 * 2 + r * 256 + kcol, k < K)
-                                continue
-                            m = min(m0 + row, M - 1)
-                            a_row = idx[m] if layout == "nt" else m
-                            yield "A", 0, a_bytes, a_row * lda * 2 + kpos if in_k else a_bytes, kt * KB, a_row, kt * KB + kpos, in_k
-                            if layout == "nt":
-                                size = (min(256, N - n0) - 1) * ldb * 2 + kbytes
-                                yield ("B", n0 * ldb * 2, size, row * ldb * 2 + kpos if in_k else size, kt * KB, n0 + row, kt * KB + kpos,
-                                       in_k and n0 + row < N)
-                            else:
-                                off = kt * 64 * ldb * 2 if live else 0
-                                yield ("B", n0 * 2 + off, ((K - 1) * ldb + N - n0) * 2 - off if live else 0, krow * ldb * 2 + r * 256 + kcol, 0, k,
-                                       n0 * 2 + r * 256 + kcol, k < K)
+    for m0, n0 in itertools.product(range(0, M, bm), range(0, N, bn)):
+        for kt in list(range(nk)) + [nk, nk + 3]:            # the loops ask for up to four slabs past the end
+            live = kt < nk
+            for i, tid in itertools.product(range(NLD), (0, 1, 7, 8, 130, 511)):
+                (row, kpos), (krow, kcol) = unit(i, tid)
+                in_k, k = kpos < kbytes - kt * KB, kt * 64 + krow
+                for r in range(bm // 128):
+                    if layout == "tn":
+                        off = kt * 64 * lda * 2 if live else 0
+                        yield ("A", m0 * 2 + off, ((K - 1) * lda + M - m0) * 2 - off if live else 0, krow * lda * 2 + r * 256 + kcol, 0, k,
+                               m0 * 2 + r * 256 + kcol, k < K)
+                    else:
+                        m = min(m0 + r * 128 + row, M - 1)
+                        a_row = idx[m] if layout == "nt" else m
+                        yield "A", 0, a_bytes, a_row * lda * 2 + kpos if in_k else a_bytes, kt * KB, a_row, kt * KB + kpos, in_k
+                for r in range(bn // 128):
+                    if layout == "tn":
+                        tok = idx[k] * ldb * 2 if k < K else b_bytes
+                        yield ("B", 0, b_bytes, tok if tok == b_bytes else tok + n0 * 2 + r * 256 + kcol, 0, idx[k] if k < K else 0,
+                               n0 * 2 + r * 256 + kcol, k < K)
+                    elif layout == "nt":
+                        size = (min(bn, N - n0) - 1) * ldb * 2 + kbytes
+                        yield ("B", n0 * ldb * 2, size, (r * 128 + row) * ldb * 2 + kpos if in_k else size, kt * KB, n0 + r * 128 + row, kt * KB + kpos,
+                               in_k and n0 + r * 128 + row < N)
+                    else:
+                        off = kt * 64 * ldb * 2 if live else 0
+                        yield ("B", n0 * 2 + off, ((K - 1) * ldb + N - n0) * 2 - off if live else 0, krow * ldb * 2 + r * 256 + kcol, 0, k,
+                               n0 * 2 + r * 256 + kcol, k < K)
 
 
 @pytest.mark.parametrize("layout,M,N,K,pad", [("nt", 300, 270, 72, 0), ("nt", 1, 1, 8, 8), ("nt", 257, 513, 200, 16), ("nn", 260, 264, 72, 0),
                                               ("nn", 300, 512, 200, 8), ("tn", 264, 520, 65, 0), ("tn", 256, 264, 131, 8), ("tn", 8, 8, 1, 0)])
-def test_no_request_leaves_its_operand(layout, M, N, K, pad):
+@pytest.mark.parametrize("bm,bn", [(256, 256), (256, 128), (128, 128)])
+def test_no_request_leaves_its_operand(layout, M, N, K, pad, bm, bn):
     S = (K if layout == "tn" else M) + (0 if layout == "nn" else 9)
     idx = [(7 * r + 3) % S for r in range(K if layout == "tn" else M)]
     lda, ldb = (M if layout == "tn" else K) + pad, (K if layout == "nt" else N) + pad
     width = {"A": M if layout == "tn" else K, "B": K if layout == "nt" else N}
     total = {"A": (((K if layout == "tn" else S) - 1) * lda + width["A"]) * 2, "B": (({"nt": N, "nn": K, "tn": S}[layout] - 1) * ldb + width["B"]) * 2}
-    for op, base, size, voff, soff, row, byte, wanted in requests(layout, M, N, K, S, lda, ldb, idx):
+    for op, base, size, voff, soff, row, byte, wanted in requests(layout, bm, bn, M, N, K, S, lda, ldb, idx):
         if voff + 16 <= size:                                # the hardware lets it through
             assert 0 <= base + voff + soff <= total[op] - 16, (op, base, size, voff, soff)
         if wanted and byte + 16 <= width[op] * 2:
@@ -101,7 +102,7 @@ def test_no_request_leaves_its_operand(layout, M, N, K, pad):
 @pytest.mark.parametrize("nk", [1, 2, 3, 6])
 @pytest.mark.parametrize("tn", [False, True])
 def test_regions_are_waited_for_and_free(nk, tn):
-    """One wave's order of loads, waits and reads; a barrier makes what every wave has waited for true of all of them."""
+    """256 x 256 tiles.  One wave's order of loads, waits and reads; a barrier makes what every wave has waited for true of all of them."""
     events = []                                              # loads in issue order: (region, slab), one entry per load
     place = lambda reg, kt: (reg, kt & 1)                    # where a region of a slab lies
     landed, holds, unread = 0, {}, {}
@@ -141,3 +142,39 @@ def test_regions_are_waited_for_and_free(nk, tn):
             unread[place(*q1)] = False
             late = [place(*q2)]
             published = len(events) - 3 * NLD
+
+
+@pytest.mark.parametrize("nk", [1, 2, 3, 4, 5, 9])
+@pytest.mark.parametrize("ra,stages", [(1, 4), (2, 3)])
+@pytest.mark.parametrize("tn", [False, True])
+def test_ring_is_waited_for_and_free(nk, ra, stages, tn):
+    """256 x 128 and 128 x 128 tiles: slabs in a ring of stages, and the kept rows' indices in a ring of four entries."""
+    batch, ahead = NLD * (ra + 1) + tn, stages - 1
+    events, holds, unread, entry = [], {}, {}, {}
+
+    def done(what, outstanding):                              # loads complete in issue order
+        return max(n for n, e in enumerate(events) if e == what) < len(events) - outstanding
+
+    def load(kt):
+        assert not unread.get(kt % stages), (kt, "overwrites fragments still to be read")
+        if tn:
+            assert entry[kt % 4] == kt, (kt, "indices of another slab")
+        events.extend([("slab", kt)] * (NLD * (ra + 1)))
+        holds[kt % stages], unread[kt % stages] = kt, True
+        if tn:
+            events.append(("idx", kt + ahead))
+            entry[(kt + ahead) % 4] = kt + ahead
+
+    if tn:
+        entry = {n: n for n in range(4)}                      # waited for before the first rows
+    for kt in range(stages):
+        load(kt)
+    assert done(("slab", 0), (stages - 1) * batch)
+    unread[0] = False                                         # slab 0's fragments are read
+    for kt in range(nk):
+        outstanding = (stages - 2) * batch
+        assert done(("slab", kt + 1), outstanding) and holds[(kt + 1) % stages] == kt + 1
+        if tn and ("idx", kt + stages) in events:
+            assert done(("idx", kt + stages), outstanding)
+        load(kt + stages)
+        unread[(kt + 1) % stages] = False                     # read during this step, awaited before the next barrier

@@ -825,6 +825,21 @@ def test_gather_gemm_large_tiles_exact(lemo, form, M, N, K):
     test_gather_gemm_tiles_exact(lemo, form, M, N, K, "bf16")
 
 
+@pytest.mark.parametrize("form,M,N,K", [
+    # 256 x 128 tiles: one slab and a piece of the next, as many slabs as the ring holds, one more; ragged rows and columns
+    ("nt", 3300, 2300, 64), ("nt", 3297, 2305, 72), ("nt", 2305, 3070, 136), ("nt", 3300, 2303, 200), ("add", 2305, 3071, 264), ("dx", 3300, 2312, 72),
+    ("dx", 2305, 3064, 200), ("dw", 2304, 3064, 129), ("dw", 2312, 3064, 191), ("dw", 2304, 3072, 300),
+    # 128 x 128 tiles, likewise
+    ("nt", 700, 1300, 8), ("nt", 1025, 1290, 64), ("nt", 897, 1153, 72), ("nt", 1000, 1153, 264), ("nt", 1000, 1280, 328), ("add", 897, 1281, 264),
+    ("add", 1000, 1100, 56), ("dx", 897, 1288, 200), ("dx", 1000, 1096, 8), ("dx", 1025, 1288, 328), ("dw", 1032, 1288, 65), ("dw", 904, 1160, 1),
+    ("dw", 1032, 1288, 257), ("dw", 904, 1160, 321),
+    # whole rounds of large tiles, smaller ones on the columns behind
+    ("nt", 1796, 8329, 264), ("dx", 2827, 5376, 264), ("nt", 2323, 8071, 1032), ("dw", 2056, 7232, 264), ("dw", 2064, 7192, 520), ("dw", 2312, 8208, 1032)])
+def test_gather_gemm_mid_tiles_exact(lemo, form, M, N, K):
+    """256 x 128 and 128 x 128 tiles at their edges, and products cut into two kinds of tiles."""
+    test_gather_gemm_tiles_exact(lemo, form, M, N, K, "bf16")
+
+
 @pytest.mark.parametrize("far", ["dY", "X"])
 def test_gather_gemm_dw_f32_beyond_32_bit_offsets(lemo, far):
     """binary32 weight gradient of operands whose row pitch is 8 MiB and more, which goes through transposed copies in the
