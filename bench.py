@@ -40,7 +40,7 @@ MEASURED_TRAFFIC_BYTES = {
 }
 
 
-HOT_PATH_SOURCES = ("lemo_common.hpp", "score.hip", "select.hip", "gather_gemm.hpp", "gather_gemm.hip", "gather_gemm_large.hip", "gather_gemm_mid.hip", "gather_gemm_regions.hpp", "gather_gemm_small.hip", "scatter.hip")
+HOT_PATH_SOURCES = ("lemo_common.hpp", "score.hip", "score_sweeps.hpp", "select.hip", "gather_gemm.hpp", "gather_gemm.hip", "gather_gemm_large.hip", "gather_gemm_mid.hip", "gather_gemm_regions.hpp", "gather_gemm_small.hip", "scatter.hip")
 
 
 def sources_digest() -> str:

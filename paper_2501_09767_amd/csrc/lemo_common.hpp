@@ -35,6 +35,7 @@ template <> __device__ __forceinline__ void mma_chunk<float>(f32x16& acc, const 
     acc = __builtin_amdgcn_mfma_f32_32x32x2f32(__uint_as_float(a.w), __uint_as_float(b.w), acc, 0, 0, 0);
 }
 
+
 // Accumulator layout of the 32x32 MFMAs (checked on hardware): register r of lane l is the element in
 //   row = 8*(r/4) + 4*(l/32) + (r%4)   (A-operand row),   col = l % 32   (B-operand row).
 __device__ __forceinline__ int acc_row(int r, int lane) { return 8 * (r >> 2) + 4 * (lane >> 5) + (r & 3); }
@@ -89,6 +90,37 @@ __device__ __forceinline__ uint32_t pack_bf16x2_hw(float lo, float hi) {
     typedef __attribute__((ext_vector_type(2))) __bf16 bf16x2_t;
     const f32x2_t v = {lo, hi};
     return __builtin_bit_cast(uint32_t, __builtin_convertvector(v, bf16x2_t));
+}
+
+// ---- binary32 products on the bf16 matrix cores ---------------------------------------------------
+// A binary32 value is the exact sum of three bf16 ones, each the rest rounded to nearest (below 2^-110 the last ones fall out of
+// bf16's range).  Six of the nine products of two such sums are formed, the smallest first; the other three amount to at most
+// 2^-26 of a product, with either sign, and the 32 x 32 x 16 MFMA adds 16 products per rounding of the sum where the binary32 one
+// adds 2.  8 times the rate for 6 products; splitting 8 values takes 44 instructions.  (Cut off instead of rounded, the rests have
+// their value's sign: scores were then up to twice as far from 64 bits.)  Infinities do not survive this (infinity times a zero
+// part): a result that is not finite has to be formed again with mma_chunk<float>.
+struct Split8 { u32x4 part[3]; };  // 8 values in three parts, as MFMA operands
+__device__ __forceinline__ Split8 split_f32(const u32x4& lo, const u32x4& hi) {
+    Split8 s;
+    float v[8];
+#pragma unroll
+    for (int e = 0; e < 4; ++e) { v[e] = __uint_as_float(lo[e]); v[e + 4] = __uint_as_float(hi[e]); }
+#pragma unroll
+    for (int part = 0; part < 3; ++part)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            const uint32_t both = pack_bf16x2_hw(v[2 * e], v[2 * e + 1]);
+            s.part[part][e] = both;
+            if (part == 2) continue;
+            v[2 * e] -= bf16lo_to_f32(both);
+            v[2 * e + 1] -= bf16hi_to_f32(both);
+        }
+    return s;
+}
+constexpr int SPLIT_TERMS = 6;
+__device__ __forceinline__ void mma_split(f32x16& acc, const Split8& a, const Split8& b, int term) {
+    constexpr int ap[SPLIT_TERMS] = {2, 0, 1, 1, 0, 0}, bp[SPLIT_TERMS] = {0, 2, 1, 0, 1, 0};
+    mma_chunk<bf16_t>(acc, a.part[ap[term]], b.part[bp[term]]);
 }
 
 // ---- workgroups of per-head kernels ---------------------------------------------------------------

@@ -167,6 +167,42 @@ def test_score_steps_compose_to_the_full_call(lemo):
             assert abs(float(lse2[h, i]) - want) < 1e-4 * max(1.0, abs(want))
 
 
+@pytest.mark.parametrize("what,S,H,d,causal", [
+    (what, *shape) for what in ("lowest key", "inf query", "nan query")
+    for shape in ((40, 1, 64, True), (333, 3, 64, True), (333, 2, 64, False), (3000, 20, 64, True), (65, 2, 128, True), (200, 2, 128, False))] + [
+    # (whole stages: the zeros that fill up a ragged one are not a number times infinity, and were not before the split either)
+    ("-inf key", 256, 3, 64, True), ("-inf key", 384, 2, 64, False), ("-inf key", 3072, 20, 64, True), ("-inf key", 128, 2, 128, True), ("-inf key", 256, 2, 128, False)])
+def test_score_fp32_not_finite(lemo, what, S, H, d, causal):
+    """binary32 scores come from split products, which an infinity (or a value that rounds to one) does not survive: such sums are
+    formed again from whole ones.  A key at minus infinity, or at the lowest finite value, is one nobody looks at; a query that is
+    not a number, or infinite, spoils its own row only."""
+    say(f"[score] fp32 {what} S={S} H={H} d={d} causal={causal}")
+    gen = torch.Generator().manual_seed(S + d)
+    Q, K = (torch.randn((S, H, d), generator=gen) for _ in range(2))
+    at = [S // 3, S // 2 + 1]
+    if "key" in what:
+        Q[..., 5] = Q[..., 5].abs() + 0.5
+        K[at, :, 5] = -math.inf if what == "-inf key" else torch.finfo(torch.float32).min
+    else:
+        Q[at, :, 7] = math.inf if what == "inf query" else math.nan
+    scores = torch.empty(S, device="cuda")
+    col, dg = (torch.empty((H, S), device="cuda") for _ in range(2))
+    lemo.lemo_score_segments(Q.cuda(), K.cuda(), 128, lemo.CAUSAL if causal else 0, scores=scores, colsum_per_head=col, diag_per_head=dg)
+    torch.cuda.synchronize()
+    x = torch.einsum("ihd,jhd->hij", Q.double(), K.double()) / math.sqrt(d)
+    if "key" in what:
+        x[:, :, at] = -math.inf
+    if causal:
+        x.masked_fill_(torch.ones(S, S, dtype=torch.bool).triu(1), -math.inf)
+    p = torch.softmax(x, dim=2)
+    if "query" in what:
+        p[:, at] = math.nan
+        if causal:  # a key behind a query takes nothing from it
+            p.masked_fill_(torch.ones(S, S, dtype=torch.bool).triu(1), 0.0)
+    for got, want in ((col, p.sum(1)), (dg, p.diagonal(dim1=1, dim2=2)), (scores, p.sum(1).mean(0))):
+        np.testing.assert_allclose(got.cpu().numpy(), want.numpy(), rtol=2e-3, atol=1e-6, equal_nan=True)
+
+
 @pytest.mark.parametrize("dominant", [450, 690, 3])
 def test_score_reference_overflow_is_repaired(lemo, dominant):
     """Sweep 1 freezes its reference maximum after the first stage of keys; a key far later whose logit exceeds that
