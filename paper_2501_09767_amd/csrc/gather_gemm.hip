@@ -22,12 +22,11 @@ namespace lemo {
 // K = 4096  79 / 57 / 69 / 103;   M = 1504, N = K = 4096  79 / 57 / 73 / 96;   M = 3280, N = K = 4096  87 / 101 / 129 / 194.
 // Products that fill whole rounds with one of the two large kinds may take another for the columns behind them (the launches
 // follow each other, so the times add).
-// binary32: the products are bound by MFMA issue at any tile size, so only the fill counts: 128 x 128, or 32 x 32 tiles
-// with the contraction split over four waves, up to 192 of the former (M = 200, N = K = 768: 51 / 11.6 us; 96 tiles, M = 500,
-// N = 3072, K = 768: 54 / 32; 160, M = 640, N = 4096, K = 1024: 69 / 59; 192, M = 768: 69.5 / 68.6; 256, M = 1024: 71 / 87; dW of 700
-// tokens, 4096 x 1024, 256 tiles: 54 / 81).  Past 256 a second round that is nearly empty would favour the small tiles again
-// (288 tiles, M = 1500, N = 3072, K = 768: 97 / 80); with more rounds the two are alike (1032 tiles, M = 1500, N = 11008, K = 4096:
-// 1193 / 1201, which 256 x 256 tiles took 1852 for).
+// binary32: 128 x 128 tiles, or 32 x 32 ones with the contraction split over four waves up to 192 of the former (us, 128 x 128 /
+// 32 x 32: M = 200, N = K = 768 32 / 7.8; 96 tiles, M = 500, N = 3072, K = 768 33 / 29; 160, M = 640, N = 4096, K = 1024 43 / 56; 192,
+// M = 700, N = K = 4096 159 / 203; 256, M = 1024, N = 4096, K = 1024 53 / 88).  By time the line would lie at 128; but the four partial
+// sums of the small tiles are nearer to 64 bits (2.9e-7 against 4.9e-7), so what they served before the large ones became
+// faster they still serve.
 struct GgPlan { int head_cols; GgTile head, rest; };
 struct GgFit { int rows, cols; double a, b, c[2], d, e; };
 static GgPlan gg_plan(long long M, int N, int K, int layout, lemo_dtype_t dt) {

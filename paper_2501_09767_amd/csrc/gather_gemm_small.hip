@@ -6,9 +6,13 @@
 //           each and their partial tiles are added, in wave order, through LDS at the end.  No barrier in the main loop.
 //           Bound by the latency of the loads: 128 KB per CU are in flight, all its LDS holds (M = 256, N = K = 4096: 17.5 us with
 //           the operands in the caches, 20.8 from HBM).  binary32, whose MFMAs take 16 times as long, is bound by those instead
-//           and takes 32 x 32 blocks, for four times the workgroups.
+//           and takes 32 x 32 blocks, for four times the workgroups (splitting an operand for one tile costs as much as it saves).
 //   GW = 4  (binary32) the four waves of a workgroup share a slab: 128 x 128 output tile, 64 x 64 per wave, two workgroups per
-//           CU (70 KB of LDS each).
+//           CU (70 KB of LDS each).  The products are three-part splits on the bf16 matrix cores (lemo_common.hpp); a slab costs a
+//           wave 352 instructions of splitting beside 1536 cycles of MFMAs, 2240 cycles where binary32 MFMAs took 4096 (and are
+//           still what a sum that is not finite is formed from again).  us, before / now: 1500 x 11008 x 4096 1209 / 783 (2.02 rounds
+//           run as 3), 1024 x 4096 x 1024 70 / 53, 10000 x 768 x 3072 381 / 250, weight gradient 8192 x 2048 of 300 tokens 96 / 70;
+//           error against 64 bits 1.1e-6 / 1.0e-6, 5.7e-7 / 4.9e-7, 9.9e-7 / 8.6e-7, 3.1e-7 / 2.6e-7.
 // Slabs arrive by LDS-direct loads, two per group in flight, and the registers are the third buffer: the MFMA fragments
 // of the next slab are read during the first MFMAs of the current one, which frees its LDS stage for the slab after next.
 // Measured beside this (M = 256, N = K = 4096 with 64 x 64 tiles, 17.5 us): a ring of four half-slabs with the loads spread over all
@@ -183,10 +187,22 @@ __global__ __launch_bounds__(SG_THREADS, GW == 4 ? 2 : 1) void gather_gemm_small
     auto b_frag = [&](int st, int i, int c) { return frag(stages + st * G::STAGE + G::OPER, B_KMAJOR, wn, i, c); };
 
     f32x16 acc[WT][WT];
+    auto clear = [&]() {
 #pragma unroll
-    for (int i = 0; i < WT; ++i)
+        for (int i = 0; i < WT; ++i)
 #pragma unroll
-        for (int j = 0; j < WT; ++j) acc[i][j] = f32x16{0};
+            for (int j = 0; j < WT; ++j) acc[i][j] = f32x16{0};
+    };
+    clear();
+    auto drain = [&]() {
+        __builtin_amdgcn_s_waitcnt(vmcnt_imm(0));  // requests past the end write (zeros) to the stages, too
+        __syncthreads();
+    };
+    using I0 = std::integral_constant<int, 0>;
+    using I1 = std::integral_constant<int, 1>;
+
+    // The product from the operands' own MFMAs.
+    auto product = [&]() {
     u32x4 fa[2][4][WT], fb[2][4][WT];  // fragments of two slabs
 
     const int nit = (nk + GROUPS - 1) / GROUPS;  // slabs per group; the last may lie past the end (zeros)
@@ -263,16 +279,106 @@ __global__ __launch_bounds__(SG_THREADS, GW == 4 ? 2 : 1) void gather_gemm_small
         }
         __builtin_amdgcn_sched_barrier(0);
     };
-    using I0 = std::integral_constant<int, 0>;
-    using I1 = std::integral_constant<int, 1>;
     int it = 0;
     for (; it + 1 < nit; it += 2) {
         step(it, I0{});
         step(it + 1, I1{});
     }
     if (it < nit) step(it, I0{});
-    __builtin_amdgcn_s_waitcnt(vmcnt_imm(0));  // requests past the end write (zeros) to the stages, too
-    __syncthreads();
+    drain();
+    };
+
+    // The product from three-part splits (binary32, GW = 4).  A slab is two operand chunks of 16 elements; during the 24 MFMAs of one
+    // chunk the next one's four operand tiles are split, pair by pair, and the one after that is read.  So slab it has left LDS when
+    // its MFMAs begin: its stage is asked for again at once, with one barrier per slab, and has a slab's time to fill.
+    auto split_product = [&]() {
+        u32x4 raw[4][2];   // A's tiles, B's tiles
+        Split8 part[2][4];
+        auto read_raw = [&](int st, int c16, int o) {
+#pragma unroll
+            for (int e = 0; e < 2; ++e) raw[o][e] = o < 2 ? a_frag(st, o, 2 * c16 + e) : b_frag(st, o - 2, 2 * c16 + e);
+        };
+        auto half_slab = [&](auto set_tag, int st, int c16, auto mem) {
+            constexpr int SET = decltype(set_tag)::value;
+#pragma unroll
+            for (int q = 0; q < 4 * SPLIT_TERMS; ++q) {
+                const int i = q % 4 / 2, j = i ? 1 - q % 2 : q % 2;
+                __builtin_amdgcn_sched_barrier(0);
+                mma_split(acc[i][j], part[SET][i], part[SET][2 + j], q / 4);
+#pragma unroll
+                for (int pr = q * 16 / (4 * SPLIT_TERMS); pr < (q + 1) * 16 / (4 * SPLIT_TERMS); ++pr) {
+                    split_pair(part[SET ^ 1][pr / 4], pr % 4, raw[pr / 4][pr % 4 / 2]);
+                    if (pr % 4 == 3) read_raw(st, c16, pr / 4);
+                }
+                mem(q);
+            }
+            __builtin_amdgcn_sched_barrier(0);
+        };
+        issue_tokens(0);
+        issue_tokens(1);
+        if constexpr (LAYOUT == GG_TN) {
+            __builtin_amdgcn_s_waitcnt(vmcnt_imm(0));
+            asm volatile("" ::: "memory");
+        }
+#pragma unroll
+        for (int it = 0; it < 2; ++it) {
+            const Slab s = slab_of(it);
+            read_tokens(it);
+#pragma unroll
+            for (int i = 0; i < NLD; ++i) load_a(s, i);
+#pragma unroll
+            for (int i = 0; i < NLD; ++i) load_b(s, i);
+            issue_tokens(it + 2);
+        }
+        __builtin_amdgcn_s_waitcnt(vmcnt_imm(BATCH));
+        group_barrier();
+#pragma unroll
+        for (int o = 0; o < 4; ++o) {
+            read_raw(0, 0, o);
+            part[0][o] = split_f32(raw[o][0], raw[o][1]);
+            read_raw(0, 1, o);
+        }
+        auto step = [&](int it, auto par_tag) {
+            constexpr int PAR = decltype(par_tag)::value, NXT = PAR ^ 1;
+            __builtin_amdgcn_s_waitcnt(vmcnt_imm(0));
+            __builtin_amdgcn_s_waitcnt(LGKMCNT0);
+            group_barrier();
+            const Slab s = slab_of(it + 2);
+            read_tokens(it + 2);
+            half_slab(I0{}, NXT, 0, [&](int q) {
+                if (q % 3 == 1) {
+                    if (q / 3 < NLD) load_a(s, q / 3);
+                    else load_b(s, q / 3 - NLD);
+                }
+            });
+            issue_tokens(it + 4);
+            half_slab(I1{}, NXT, 1, [&](int) {});
+        };
+        int it = 0;
+        for (; it + 1 < nk; it += 2) {
+            step(it, I0{});
+            step(it + 1, I1{});
+        }
+        if (it < nk) step(it, I0{});
+        drain();
+    };
+    if constexpr (ESZ == 4 && GW == 4) {
+        static_assert(WT == 2 && 2 * NLD == 8, "four operand tiles, a load per three MFMAs");
+        split_product();
+        float probe = 0.f;  // not a number if any sum is infinite or not a number: an infinity does not survive the split
+#pragma unroll
+        for (int i = 0; i < WT; ++i)
+#pragma unroll
+            for (int j = 0; j < WT; ++j)
+#pragma unroll
+                for (int r = 0; r < 16; ++r) probe = fmaf(acc[i][j][r], 0.f, probe);
+        if (__syncthreads_or(!(probe == 0.f))) {
+            clear();
+            product();
+        }
+    } else {
+        product();
+    }
 
     // Epilogue.  Every wave lays its block out in LDS as binary32; rows are then put together (GW = 1: the four
     // partial blocks are added in wave order, each wave finishing a quarter of the rows; GW = 4: each wave its own block), eight

@@ -100,21 +100,20 @@ __device__ __forceinline__ uint32_t pack_bf16x2_hw(float lo, float hi) {
 // their value's sign: scores were then up to twice as far from 64 bits.)  Infinities do not survive this (infinity times a zero
 // part): a result that is not finite has to be formed again with mma_chunk<float>.
 struct Split8 { u32x4 part[3]; };  // 8 values in three parts, as MFMA operands
+__device__ __forceinline__ void split_pair(Split8& s, int e, const u32x4& from) {  // values 2e and 2e + 1, elements 2 (e % 2) of `from` on
+    float v0 = __uint_as_float(from[e % 2 * 2]), v1 = __uint_as_float(from[e % 2 * 2 + 1]);
+#pragma unroll
+    for (int part = 0; part < 3; ++part) {
+        const uint32_t both = pack_bf16x2_hw(v0, v1);
+        s.part[part][e] = both;
+        v0 -= bf16lo_to_f32(both);
+        v1 -= bf16hi_to_f32(both);
+    }
+}
 __device__ __forceinline__ Split8 split_f32(const u32x4& lo, const u32x4& hi) {
     Split8 s;
-    float v[8];
 #pragma unroll
-    for (int e = 0; e < 4; ++e) { v[e] = __uint_as_float(lo[e]); v[e + 4] = __uint_as_float(hi[e]); }
-#pragma unroll
-    for (int part = 0; part < 3; ++part)
-#pragma unroll
-        for (int e = 0; e < 4; ++e) {
-            const uint32_t both = pack_bf16x2_hw(v[2 * e], v[2 * e + 1]);
-            s.part[part][e] = both;
-            if (part == 2) continue;
-            v[2 * e] -= bf16lo_to_f32(both);
-            v[2 * e + 1] -= bf16hi_to_f32(both);
-        }
+    for (int e = 0; e < 4; ++e) split_pair(s, e, e < 2 ? lo : hi);
     return s;
 }
 constexpr int SPLIT_TERMS = 6;

@@ -12,8 +12,8 @@
 //                              workgroup, so there are no atomics and the result is deterministic.
 //   reduce   head_mean_kernel  scores[j] = (1/H) sum_h (colsum - [exclude self] diag), fixed order.
 //
-// Both sweeps compute 32x32 logit tiles with MFMA (bf16: 32x32x16; fp32: 32x32x2, a true binary32
-// contraction).  The product is oriented so that the axis being reduced runs along the accumulator
+// Both sweeps compute 32x32 logit tiles with MFMA (bf16: 32x32x16; fp32: score_f32.hip, three-part
+// splits on the same instruction).  The product is oriented so that the axis being reduced runs along the accumulator
 // REGISTERS of a lane and the axis being kept runs along LANES: sweep 1 computes K.Q^T (lane = query),
 // sweep 2 computes Q.K^T (lane = key).  Row and column statistics are then plain in-register chains
 // with one cross-lane step at the very end.

@@ -876,6 +876,42 @@ def test_gather_gemm_mid_tiles_exact(lemo, form, M, N, K):
     test_gather_gemm_tiles_exact(lemo, form, M, N, K, "bf16")
 
 
+@pytest.mark.parametrize("what", ["plain", "inf", "nan", "lowest", "tiny"])
+@pytest.mark.parametrize("form,M,N,K", [("nt", 1700, 1931, 132), ("nt", 1537, 2049, 1000), ("add", 1600, 2050, 36), ("dw", 1924, 2060, 331)])
+def test_gather_gemm_fp32_split(lemo, form, M, N, K, what):
+    """binary32 products of many tiles come from three-part splits.  Within a random walk of one rounding per term of the sum; an
+    infinity, a value that rounds to one in the parts, or something that is not a number gives what the whole operands give."""
+    say(f"[gemm] fp32 split {form} M={M} N={N} K={K} {what}")
+    gen = torch.Generator().manual_seed(M + K)
+    A, B = (torch.randn((K, n) if form == "dw" else (n, K), generator=gen) for n in (M, N))
+    if what == "tiny":
+        A *= 1e-30
+    value = {"inf": math.inf, "nan": math.nan, "lowest": torch.finfo(torch.float32).min}.get(what)
+    if value is not None:
+        (A.t() if form == "dw" else A)[M // 2, K - 1] = value
+        (B.t() if form == "dw" else B)[:, K - 1].clamp_(min=0.125)
+        if what == "lowest":
+            (B.t() if form == "dw" else B)[:, K - 1].clamp_(max=0.5)
+    A, B = A.cuda(), B.cuda()
+    idx = torch.arange(K if form == "dw" else M, dtype=torch.int32, device="cuda")
+    want = (A.t().contiguous().double() if form == "dw" else A.double()) @ (B.double() if form == "dw" else B.double().t().contiguous())
+    if form == "dw":
+        got = lemo.lemo_gather_gemm_dw(A, B, idx)
+    elif form == "add":
+        got = lemo.lemo_gather_gemm_add(A, None, B, torch.zeros((M, N), device="cuda"), idx)
+    else:
+        got = lemo.lemo_gather_gemm(A, idx, B)
+    torch.cuda.synchronize()
+    assert torch.equal(got.isnan(), want.isnan()) and torch.equal(got.isinf(), want.isinf())
+    if what in ("plain", "tiny"):
+        assert (got.double() - want).norm() <= 2.0 ** -24 * math.sqrt(K) * want.norm()
+    else:
+        rest = torch.ones(M, dtype=torch.bool, device="cuda")
+        rest[M // 2] = False
+        assert (got.double() - want)[rest].norm() <= 2.0 ** -24 * math.sqrt(K) * want[rest].norm()
+        np.testing.assert_allclose(got[M // 2].cpu().numpy(), want[M // 2].cpu().numpy(), rtol=1e-5)
+
+
 @pytest.mark.parametrize("far", ["dY", "X"])
 def test_gather_gemm_dw_f32_beyond_32_bit_offsets(lemo, far):
     """binary32 weight gradient of operands whose row pitch is 8 MiB and more, which goes through transposed copies in the
