@@ -14,6 +14,7 @@ ROOT = os.path.dirname(HERE)
 CSRC = os.path.join(HERE, "csrc")
 OBJDIR = os.path.join(ROOT, "_build")
 LIB = os.path.join(HERE, "liblemo_hip.so")
+NATIVE = os.path.join(HERE, "lemo_native.so")  # the binding's native marshalling, linked against LIB
 SOURCES = ["lemo_api.hip", "score.hip", "score_f32.hip", "score_blocks.hip", "attention.hip", "select.hip", "gather_gemm.hip", "gather_gemm_large.hip", "gather_gemm_mid.hip", "gather_gemm_small.hip", "transpose.hip", "scatter.hip", "probe.hip"]
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 # packed-fp32 code generation is switched off on purpose: the compiler must not form v_pk_*_f32 instructions from scalar float code
@@ -40,6 +41,28 @@ def _compile(src: str, extra) -> str:
     return obj
 
 
+def build_native() -> str:
+    """csrc/native.cpp as a CPython extension beside the library (host compiler, torch's headers)."""
+    import sysconfig
+
+    import torch
+    from torch.utils import cpp_extension
+
+    tmp = NATIVE + f".tmp{os.getpid()}"
+    libs = cpp_extension.library_paths()
+    cmd = [os.environ.get("CXX", "g++"), "-O2", "-std=c++17", "-fPIC", "-shared", "-Wall", f"-D_GLIBCXX_USE_CXX11_ABI={int(torch.compiled_with_cxx11_abi())}",
+           "-I" + os.path.join(ROOT, "include"), "-I" + sysconfig.get_paths()["include"], *("-isystem" + p for p in cpp_extension.include_paths()),
+           os.path.join(CSRC, "native.cpp"), "-o", tmp, "-L" + HERE, "-l:liblemo_hip.so", "-Wl,-rpath,$ORIGIN",
+           *("-L" + p for p in libs), *("-Wl,-rpath," + p for p in libs), "-lc10", "-ltorch_cpu", "-ltorch_python"]
+    r = subprocess.run(cmd, capture_output=True, text=True)
+    if r.returncode != 0:
+        raise RuntimeError("building the native binding failed:\n" + r.stderr)
+    if r.stderr.strip():
+        print(r.stderr, file=sys.stderr)
+    os.replace(tmp, NATIVE)
+    return NATIVE
+
+
 def build_library(extra_flags=(), verbose: bool = True) -> str:
     os.makedirs(OBJDIR, exist_ok=True)
     with ThreadPoolExecutor(max_workers=min(8, len(SOURCES))) as ex:
@@ -49,8 +72,9 @@ def build_library(extra_flags=(), verbose: bool = True) -> str:
     if r.returncode != 0:
         raise RuntimeError("link failed:\n" + r.stderr)
     os.replace(tmp, LIB)
+    native = build_native()
     if verbose:
-        print("built", LIB)
+        print("built", LIB, native)
     return LIB
 
 

@@ -8,6 +8,8 @@ been built the import of this module fails.
 from __future__ import annotations
 
 import ctypes
+import importlib.machinery
+import importlib.util
 import os
 from typing import Optional
 
@@ -19,6 +21,7 @@ SCATTER_ACCUMULATE, SCATTER_ZERO_PAD = 0, 1
 
 _HERE = os.path.dirname(os.path.abspath(__file__))
 LIB_PATH = os.path.join(_HERE, "liblemo_hip.so")
+NATIVE_PATH = os.path.join(_HERE, "lemo_native.so")
 
 EXPORTS = ("lemo_strerror", "lemo_keep_k", "lemo_kept_count", "lemo_score_workspace_bytes",
            "lemo_score_segments", "lemo_score_segments_static", "lemo_score_rowstats", "lemo_score_colsums", "lemo_score_head_mean",
@@ -129,6 +132,23 @@ def _stream():
     return ctypes.c_void_p(_raw_stream(torch.cuda.current_device()))
 
 
+def _load_native():
+    # csrc/native.cpp: the calls that a layer makes over and over, in the plain case, without the steps in Python below; anything
+    # else it leaves to them (it answers None and has done nothing).  backward of a small binary32 layer, three calls: 22 us
+    # enqueued from Python, 12 so.
+    if not os.path.exists(NATIVE_PATH):
+        raise ImportError(f"{NATIVE_PATH} is missing: build it first (python -m paper_2501_09767_amd.build).")
+    loader = importlib.machinery.ExtensionFileLoader("lemo_native", NATIVE_PATH)
+    module = importlib.util.module_from_spec(importlib.util.spec_from_file_location("lemo_native", NATIVE_PATH, loader=loader))
+    loader.exec_module(module)
+    if _raw_stream is not None:
+        module.set_stream_source(torch.cuda.current_device, _raw_stream)
+    return module
+
+
+_native = _load_native()
+
+
 def _check(rc: int, what: str):
     if rc != 0:
         raise LemoError(rc, what)
@@ -157,6 +177,10 @@ def lemo_score_segments(Q: torch.Tensor, K: torch.Tensor, L: int, flags: int = C
                         colsum_per_head: Optional[torch.Tensor] = None, diag_per_head: Optional[torch.Tensor] = None,
                         workspace: Optional[torch.Tensor] = None) -> torch.Tensor:
     """Q [S,H,d], K [S,H_kv,d] (last dim contiguous) -> scores [S] float32."""
+    rc = _native.score_segments(Q, K, L, flags, scale, scores, colsum_per_head, diag_per_head, workspace)
+    if rc is not None:
+        _check(rc, "lemo_score_segments")
+        return scores
     _dev(Q, K, scores, colsum_per_head, diag_per_head, workspace)
     if Q.dim() != 3 or K.dim() != 3 or Q.stride(2) != 1 or K.stride(2) != 1:
         raise ValueError("Q must be [S,H,d] and K [S,H_kv,d] with head_dim contiguous")
@@ -328,6 +352,10 @@ def lemo_select_threshold(token_blocks: torch.Tensor, S: int, b: int, threshold,
 
 def lemo_select_topk(scores: torch.Tensor, L: int, k: int, kept_idx: Optional[torch.Tensor] = None) -> torch.Tensor:
     """scores [S] float32 -> kept_idx [M] int32, ascending."""
+    rc = _native.select_topk(scores, L, k, kept_idx)
+    if rc is not None:
+        _check(rc, "lemo_select_topk")
+        return kept_idx
     _dev(scores, kept_idx)
     if scores.dtype != torch.float32 or scores.dim() != 1 or not scores.is_contiguous():
         raise ValueError("scores must be contiguous float32 [S]")
@@ -386,6 +414,10 @@ def lemo_gather_gemm(X: torch.Tensor, kept_idx: Optional[torch.Tensor], W: torch
                      bias: Optional[torch.Tensor] = None, Y: Optional[torch.Tensor] = None,
                      M: Optional[int] = None) -> torch.Tensor:
     """Y[m,:] = X[kept_idx[m],:] @ W.T (+ bias).  X [S,C], W [N,C], rows contiguous."""
+    rc = _native.gather_gemm(X, kept_idx, W, bias, Y, M)
+    if rc is not None:
+        _check(rc, "lemo_gather_gemm")
+        return Y
     _dev(X, kept_idx, W, bias, Y)
     if X.dim() != 2 or W.dim() != 2 or X.stride(1) != 1 or W.stride(1) != 1 or X.shape[1] != W.shape[1] or _dt(X) != _dt(W):
         raise ValueError("X must be [S,C], W [N,C], same dtype, rows contiguous")
@@ -412,6 +444,10 @@ def lemo_gather_gemm_add(X: torch.Tensor, kept_idx: Optional[torch.Tensor], W: t
                          out_idx: Optional[torch.Tensor], bias: Optional[torch.Tensor] = None,
                          M: Optional[int] = None) -> torch.Tensor:
     """In place: R[out_idx[m],:] += X[kept_idx[m],:] @ W.T (+ bias).  X [S,C], W [N,C], R [S_out,N], rows contiguous."""
+    rc = _native.gather_gemm_add(X, kept_idx, W, R, out_idx, bias, M)
+    if rc is not None:
+        _check(rc, "lemo_gather_gemm_add")
+        return R
     _dev(X, kept_idx, W, bias, R, out_idx)
     if X.dim() != 2 or W.dim() != 2 or X.stride(1) != 1 or W.stride(1) != 1 or X.shape[1] != W.shape[1] or _dt(X) != _dt(W):
         raise ValueError("X must be [S,C], W [N,C], same dtype, rows contiguous")
@@ -446,6 +482,10 @@ def lemo_kept_attention(Q: torch.Tensor, K: torch.Tensor, V: torch.Tensor, kept_
                         scale: float = 0.0, O: Optional[torch.Tensor] = None, workspace: Optional[torch.Tensor] = None,
                         M: Optional[int] = None) -> torch.Tensor:
     """Attention over the kept rows of Q [S,H,d], K, V [S,H_kv,d] -> compact O [M,H,d]."""
+    rc = _native.kept_attention(Q, K, V, kept_idx, flags, scale, O, workspace, M)
+    if rc is not None:
+        _check(rc, "lemo_kept_attention")
+        return O
     a = _qk_args(Q, K)
     _dev(V, kept_idx, O, workspace)
     S, H, Hkv, d = a[2], a[3], a[4], a[5]
@@ -471,6 +511,10 @@ def lemo_kept_attention(Q: torch.Tensor, K: torch.Tensor, V: torch.Tensor, kept_
 
 def lemo_gather_gemm_dx(dY: torch.Tensor, W: torch.Tensor, dX: torch.Tensor, out_idx: Optional[torch.Tensor]) -> torch.Tensor:
     """In place: dX[out_idx[m],:] += dY[m,:] @ W.  dY [M,N], W [N,C] (as stored for the forward), dX [S_out,C]."""
+    rc = _native.gather_gemm_dx(dY, W, dX, out_idx)
+    if rc is not None:
+        _check(rc, "lemo_gather_gemm_dx")
+        return dX
     _dev(dY, W, dX, out_idx)
     if dY.dim() != 2 or W.dim() != 2 or dX.dim() != 2 or _dt(dY) != _dt(W) or _dt(dX) != _dt(W) or W.stride(1) != 1 or dX.stride(1) != 1 \
             or dY.shape[1] != W.shape[0] or dX.shape[1] != W.shape[1] or (dY.shape[0] > 0 and dY.stride(1) != 1):
@@ -493,6 +537,10 @@ def lemo_gather_gemm_dw_workspace_bytes(M: int, C: int, N: int, dtype: int) -> i
 def lemo_gather_gemm_dw(dY: torch.Tensor, X: torch.Tensor, kept_idx: Optional[torch.Tensor], dW: Optional[torch.Tensor] = None,
                         workspace: Optional[torch.Tensor] = None) -> torch.Tensor:
     """dW[n,c] = sum_m dY[m,n] * X[kept_idx[m],c].  dY [M,N], X [S,C] -> dW [N,C]."""
+    rc = _native.gather_gemm_dw(dY, X, kept_idx, dW, workspace)
+    if rc is not None:
+        _check(rc, "lemo_gather_gemm_dw")
+        return dW
     _dev(dY, X, kept_idx, dW, workspace)
     if dY.dim() != 2 or X.dim() != 2 or _dt(dY) != _dt(X) or X.stride(1) != 1 or (dY.shape[0] > 0 and dY.stride(1) != 1):
         raise ValueError("dY must be [M,N] and X [S,C], same dtype, rows contiguous")
@@ -516,6 +564,10 @@ def lemo_gather_gemm_dw(dY: torch.Tensor, X: torch.Tensor, kept_idx: Optional[to
 
 def lemo_scatter_grad(G: torch.Tensor, kept_idx: torch.Tensor, dX: torch.Tensor, mode: int = SCATTER_ACCUMULATE) -> torch.Tensor:
     """In place: dX[kept_idx[m],:] += G[m,:] (ACCUMULATE) or dX = zero-padded G (ZERO_PAD)."""
+    rc = _native.scatter_grad(G, kept_idx, dX, mode)
+    if rc is not None:
+        _check(rc, "lemo_scatter_grad")
+        return dX
     _dev(G, kept_idx, dX)
     if G.dim() != 2 or dX.dim() != 2 or G.shape[1] != dX.shape[1] or dX.stride(1) != 1 or (G.shape[0] > 0 and G.stride(1) != 1):
         raise ValueError("G must be [M,C] and dX [S,C], rows contiguous")
