@@ -15,7 +15,7 @@ CSRC = os.path.join(HERE, "csrc")
 OBJDIR = os.path.join(ROOT, "_build")
 LIB = os.path.join(HERE, "liblemo_hip.so")
 NATIVE = os.path.join(HERE, "lemo_native.so")  # the binding's native marshalling, linked against LIB
-SOURCES = ["lemo_api.hip", "score.hip", "score_f32.hip", "score_blocks.hip", "attention.hip", "select.hip", "gather_gemm.hip", "gather_gemm_large.hip", "gather_gemm_mid.hip", "gather_gemm_small.hip", "transpose.hip", "scatter.hip", "probe.hip"]
+SOURCES = ["lemo_api.hip", "score.hip", "score_f32.hip", "score_blocks.hip", "score_blocks_few.hip", "attention.hip", "select.hip", "gather_gemm.hip", "gather_gemm_large.hip", "gather_gemm_mid.hip", "gather_gemm_small.hip", "transpose.hip", "scatter.hip", "probe.hip"]
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 # packed-fp32 code generation is switched off on purpose: the compiler must not form v_pk_*_f32 instructions from scalar float code
 FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-Wall", "-Wno-unused-command-line-argument",
@@ -23,10 +23,10 @@ FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-Wall", "-Wno-u
          "-I" + os.path.join(ROOT, "include"), "-I" + CSRC]
 
 
-# Per-file flags.  attention.hip: its 64-queries-per-wave kernel may use the whole register file (one wave per SIMD), and
-# for such a kernel the compiler would otherwise give every MFMA its result in the accumulation registers, with a copy
-# around each use by vector arithmetic; this makes MFMAs write ordinary vector registers.
-FILE_FLAGS = {"attention.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form"]}
+# Per-file flags.  attention.hip (its 64-queries-per-wave kernel) and score_blocks_few.hip may use the whole register file
+# (one wave per SIMD), and for such a kernel the compiler would otherwise give every MFMA its result in the accumulation
+# registers, with a copy around each use by vector arithmetic; this makes MFMAs write ordinary vector registers.
+FILE_FLAGS = {"attention.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form"], "score_blocks_few.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form"]}
 
 
 def _compile(src: str, extra) -> str:

@@ -187,7 +187,7 @@ struct BlockParams {
     float* tilemax;     // [nt32, nt32] maxima of the 32 x 32 tiles
     int nt32;           // ceil(S / 32)
     int nt;             // rectangles per side
-    int nsp;            // super-patches per side
+    int count, per_xcd; // rectangles, of them on a die
 };
 
 // kernel launchers (defined next to their kernels; return hipError_t as int)

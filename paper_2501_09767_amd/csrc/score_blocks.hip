@@ -10,8 +10,9 @@
 // each block column.
 //
 // Unlike the two sweeps of the token-wise score there is no operand that stays resident across the inner loop (every
-// head brings its own Q and K rows), so the kernel leans on the caches: the 256 workgroups in flight form a 16 x 16
-// super-patch of rectangles (32 operand tiles for 256 rectangles), and each die works on a 4 x 8 sub-patch of it.
+// head brings its own Q and K rows), so the kernel leans on the caches: each die works on a 4 x 8 patch of rectangles
+// (score_blocks.hpp; with the dies' patches cut from 16 x 16 ones, most of them past a causal diagonal or the end, some dies
+// had twice the others' share: 5000 tokens, 32 heads 247 us, now 183; 3000 tokens 122, now 86).
 // Per head a workgroup moves 64 KB from L2 into LDS and 192 KB from LDS into registers for 4.2 MFLOP, so the head loop
 // is one software pipeline three heads deep: head h in registers (MFMA fragments, refilled in place as soon as an
 // MFMA has used them), head h + 1 complete in one LDS stage, head h + 2 arriving in the other through LDS-direct
@@ -19,11 +20,11 @@
 #include <mutex>
 #include <type_traits>
 
-#include "lemo_common.hpp"
+#include "score_blocks.hpp"
 
 namespace lemo {
 
-constexpr int SB_PATCH = 16;  // super-patch edge, in rectangles
+constexpr int SB_CUS = 256;  // compute units
 
 template <typename T, int D> struct BGeo {
     static constexpr int ROWB = D * (int)sizeof(T);  // bytes per head row
@@ -62,21 +63,10 @@ __global__ __launch_bounds__((BGeo<T, D>::THREADS), 1) void tilemax_kernel(Block
 
     // rectangle of this workgroup
     const bool causal = (p.flags & LEMO_CAUSAL) != 0;
-    const int sp_id = blockIdx.x / (SB_PATCH * SB_PATCH), loc = blockIdx.x % (SB_PATCH * SB_PATCH);
-    int spm, spn;
-    if (causal) {  // super-patches on and below the diagonal, row by row
-        spm = (int)((sqrtf(8.f * (float)sp_id + 1.f) - 1.f) * 0.5f);
-        while ((spm + 1) * (spm + 2) / 2 <= sp_id) ++spm;
-        while (spm * (spm + 1) / 2 > sp_id) --spm;
-        spn = sp_id - spm * (spm + 1) / 2;
-    } else {
-        spm = sp_id / p.nsp;
-        spn = sp_id - spm * p.nsp;
-    }
-    const int x = loc % NUM_XCD, w = loc / NUM_XCD;  // die, and the workgroup's slot on it
-    const int tq = spm * SB_PATCH + (x >> 1) * 4 + (w & 3);
-    const int tk = spn * SB_PATCH + (x & 1) * 8 + (w >> 2);
-    if (tq >= p.nt || tk >= p.nt || (causal && tk > tq)) return;  // outside the matrix, or wholly above the diagonal
+    const int id = blockIdx.x % NUM_XCD * p.per_xcd + blockIdx.x / NUM_XCD;
+    if (blockIdx.x / NUM_XCD >= p.per_xcd || id >= p.count) return;
+    int tq, tk;
+    sb_rectangle(id, p.nt, causal, tq, tk);
 
     const int S = p.S;
     const int q0 = tq * G::TT, k0 = tk * G::TT;
@@ -299,8 +289,21 @@ template <typename T, int D, int MODE>
 static int launch_tilemax_t(BlockParams p, hipStream_t st) {
     using G = BGeo<T, D>;
     p.nt = (p.S + G::TT - 1) / G::TT;
-    p.nsp = (p.nt + SB_PATCH - 1) / SB_PATCH;
-    const long long nsp_total = (p.flags & LEMO_CAUSAL) ? (long long)p.nsp * (p.nsp + 1) / 2 : (long long)p.nsp * p.nsp;
+    const long long total = (p.flags & LEMO_CAUSAL) ? (long long)p.nt * (p.nt + 1) / 2 : (long long)p.nt * p.nt;
+    if (total > INT32_MAX - NUM_XCD) return (int)hipErrorInvalidConfiguration;
+    p.count = (int)total;
+    // One workgroup per CU is one round of 256 rectangles, and a round takes the same time however many there are.  What a last
+    // round has goes to tilemax_few_kernel as quarters if those fit one round of that kernel (two workgroups per CU at
+    // D = 64).  us per call, one kernel / so divided; 32 heads, D = 128, causal: 36 rectangles 42.5 / 23.0, 300 85.6 / 68.0, 528
+    // 130 / 114, 820 183 / 168, 2080 403 / 394; 16 heads, D = 64: 36 (12 heads) 18.5 / 13.7, 136 23.0 / 22.1 (alike: the
+    // line), 300 38.8 / 32.0, 528 55.4 / 48.4.  Beyond it, at 128: 325 86.7 / 85.0, 136 43.5 / 56.0.
+    int rest = 0;
+    if constexpr (G::TT == 128 && sizeof(T) == 2) {
+        rest = p.count % SB_CUS;
+        if (rest > (D == 128 ? SB_CUS / 4 : SB_CUS / 2)) rest = 0;
+        p.count -= rest;
+    }
+    p.per_xcd = (p.count + NUM_XCD - 1) / NUM_XCD;
     static std::once_flag once;
     static hipError_t attr_err = hipSuccess;
     std::call_once(once, [] {
@@ -308,8 +311,10 @@ static int launch_tilemax_t(BlockParams p, hipStream_t st) {
                                        hipFuncAttributeMaxDynamicSharedMemorySize, G::LDS);
     });
     if (attr_err != hipSuccess) return (int)attr_err;
-    hipLaunchKernelGGL((tilemax_kernel<T, D, MODE>), dim3((unsigned)(nsp_total * SB_PATCH * SB_PATCH)), dim3(G::THREADS), G::LDS, st, p);
-    return (int)hipGetLastError();
+    if (p.count > 0) hipLaunchKernelGGL((tilemax_kernel<T, D, MODE>), dim3((unsigned)(p.per_xcd * NUM_XCD)), dim3(G::THREADS), G::LDS, st, p);
+    const hipError_t err = hipGetLastError();
+    if (err != hipSuccess || rest == 0) return (int)err;
+    return launch_tilemax_few(p, D, MODE, p.count, rest, st);
 }
 
 // mode 0: probabilities (lse2 must hold the row statistics); mode 1: positive logits

@@ -1,0 +1,175 @@
+// The head sums and tile maxima of score_blocks.hip for few rectangles (bf16): short sequences, and the last round of longer ones.
+//
+// A workgroup owns a 64 x 64 quarter of a rectangle and its four waves share out the heads, every fourth each: a wave forms the
+// whole quarter for its heads from operands of its own (32 KB of LDS at D = 128, filled by LDS-direct loads while the head before
+// is worked on from registers; no barrier in the loop), and the four partial sums meet in LDS at the end.  A quarter then takes a
+// quarter of the steps, where tilemax_kernel walks all heads one after the other: that one needs half the bytes per
+// flop and keeps two waves on a SIMD (32 heads, D = 128: 256 rectangles in 39 us, 64 as quarters in 19), but with few rectangles its
+// time is one walk of all heads whatever their number.
+// What bounds it: the latency of a step (one wave per SIMD: 4 us for the launch, then 2 us per step of loads, 32 reads of LDS,
+// 32 MFMAs and 64 exponentials per lane, overlapped only in parts).
+#include <mutex>
+#include <type_traits>
+
+#include "score_blocks.hpp"
+
+namespace lemo {
+
+template <int D> struct FGeo {
+    static constexpr int ROWB = D * 2, NCH = ROWB / 32, CPR = ROWB / 16;
+    static constexpr int OPER = 64 * ROWB;            // one operand's 64 rows
+    static constexpr int NLD = OPER / 1024, RPI = 1024 / ROWB;  // loads per operand and head, rows of one
+    static constexpr int PERIOD = D == 128 ? 4 : 2;   // of the loads' exchange of pieces
+    static constexpr int BUF = 2 * OPER + 256;        // a wave's: Q rows, K rows, row statistics
+    static constexpr int SUMS = 4 * 4 * 16 * 64 * 4;  // partial sums: [wave][tile][register][lane]
+    static constexpr int LDS = 4 * BUF > SUMS ? 4 * BUF : SUMS;
+    __device__ static constexpr int swz(int row) { return CPR >= 16 ? (row & 15) : ((row >> 1) & (CPR - 1)); }
+};
+
+// MODE as in tilemax_kernel.  The quarters of the rectangles first .. first + rest - 1.
+template <int D, int MODE>
+__global__ __launch_bounds__(256, 1) void tilemax_few_kernel(BlockParams p, int first, int rest) {
+    using G = FGeo<D>;
+    extern __shared__ __attribute__((aligned(16))) char smem[];
+    const bool causal = (p.flags & LEMO_CAUSAL) != 0;
+    const int per_xcd = (4 * rest + NUM_XCD - 1) / NUM_XCD;  // a die takes neighbouring quarters
+    const int id = blockIdx.x % NUM_XCD * per_xcd + blockIdx.x / NUM_XCD;
+    if (blockIdx.x / NUM_XCD >= per_xcd || id >= 4 * rest) return;
+    int tq, tk;
+    sb_rectangle(first + id / 4, p.nt, causal, tq, tk);
+    tq = 2 * tq + (id >> 1 & 1);
+    tk = 2 * tk + (id & 1);
+    if (tq * 64 >= p.S || tk * 64 >= p.S || (causal && tk > tq)) return;
+    const int S = p.S, q0 = tq * 64, k0 = tk * 64;
+    const int lane = threadIdx.x & 63, half = lane >> 5, l32 = lane & 31;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const float c2 = p.c2;
+    const bf16_t* Qb = static_cast<const bf16_t*>(p.Q);
+    const bf16_t* Kb = static_cast<const bf16_t*>(p.K);
+    const unsigned group = (unsigned)(p.H / p.H_kv);
+
+    // load i of an operand fills 1 KB of consecutive LDS bytes: rows i * RPI + lane / CPR, position lane % CPR, which holds piece
+    // (lane % CPR) ^ swz(row); range-checked, rows past the end arrive as zeros
+    const int q_row_bytes = (int)p.q_ts * 2, k_row_bytes = (int)p.k_ts * 2;  // host: < 2^24
+    int q_off[G::PERIOD], k_off[G::PERIOD];
+#pragma unroll
+    for (int i = 0; i < G::PERIOD; ++i) {
+        const int row = lane / G::CPR, piece = (lane % G::CPR) ^ G::swz(i * G::RPI + row);
+        q_off[i] = row * q_row_bytes + piece * 16;
+        k_off[i] = row * k_row_bytes + piece * 16;
+    }
+    char* const buf = smem + wave * G::BUF;
+    const unsigned lds = __builtin_amdgcn_readfirstlane(lds_offset_of(buf));
+    const int l_off = min(q0 + lane, S - 1) * 4;  // rows past the end reuse the last row's statistics (left out at the end)
+    auto issue = [&](int h) {
+        const char* qh = reinterpret_cast<const char*>(Qb + (long long)h * p.q_hs) + (long long)q0 * q_row_bytes;
+        const char* kh = reinterpret_cast<const char*>(Kb + (long long)((unsigned)h / group) * p.k_hs) + (long long)k0 * k_row_bytes;
+        const u32x4 qd = raw_rsrc(qh, (long long)(S - q0 - 1) * q_row_bytes + G::ROWB), kd = raw_rsrc(kh, (long long)(S - k0 - 1) * k_row_bytes + G::ROWB);
+#pragma unroll
+        for (int i = 0; i < G::NLD; ++i) lds_direct_b128(qd, lds + i * 1024, q_off[i % G::PERIOD] + i * G::RPI * q_row_bytes);
+#pragma unroll
+        for (int i = 0; i < G::NLD; ++i) lds_direct_b128(kd, lds + G::OPER + i * 1024, k_off[i % G::PERIOD] + i * G::RPI * k_row_bytes);
+        if (MODE == 0) lds_direct_b32(raw_rsrc(p.lse2 + (size_t)h * S, (long long)S * 4), lds + 2 * G::OPER, l_off);
+    };
+
+    f32x16 sum[2][2];  // [query subtile][key subtile], of this wave's heads
+#pragma unroll
+    for (int t = 0; t < 4; ++t) sum[t >> 1][t & 1] = f32x16{0};
+    if (wave < p.H) issue(wave);
+    for (int h = wave; h < p.H; h += 4) {
+        __builtin_amdgcn_s_waitcnt(vmcnt_imm(0));
+        asm volatile("" ::: "memory");
+        u32x4 qf[2][G::NCH], kf[2][G::NCH];
+        float nl[2][16];  // row statistics of the lane's rows 8 gq + 4 half + {0..3}, negated
+#pragma unroll
+        for (int s = 0; s < 2; ++s) {
+            const char* row = buf + (s * 32 + l32) * G::ROWB;
+#pragma unroll
+            for (int c = 0; c < G::NCH; ++c) {
+                qf[s][c] = *reinterpret_cast<const u32x4*>(row + (((2 * c + half) ^ G::swz(l32)) << 4));
+                kf[s][c] = *reinterpret_cast<const u32x4*>(row + G::OPER + (((2 * c + half) ^ G::swz(l32)) << 4));
+            }
+            if (MODE == 0) {
+#pragma unroll
+                for (int gq = 0; gq < 4; ++gq) {
+                    const f32x4 v = *reinterpret_cast<const f32x4*>(buf + 2 * G::OPER + (s * 32 + gq * 8 + half * 4) * 4);
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) nl[s][gq * 4 + e] = -v[e];
+                }
+            }
+        }
+        // the buffer is the wave's own: once its reads have returned, the next head may land in it
+        __builtin_amdgcn_s_waitcnt(LGKMCNT0);
+        asm volatile("" ::: "memory");
+        if (h + 4 < p.H) issue(h + 4);
+        f32x16 prev = {0};
+        auto add = [&](int t, int r) {  // element r of tile t
+            f32x16& s = sum[t >> 1][t & 1];
+            if (MODE == 0) s[r] += __builtin_amdgcn_exp2f(fmaf(prev[r], c2, nl[t >> 1][r]));
+            else s[r] += fmaxf(prev[r], 0.f);
+        };
+#pragma unroll
+        for (int t = 0; t < 4; ++t) {  // the tile before is added between this one's MFMAs
+            f32x16 acc = {0};
+#pragma unroll
+            for (int c = 0; c < G::NCH; ++c) {
+                __builtin_amdgcn_sched_barrier(0);
+                mma_chunk<bf16_t>(acc, qf[t >> 1][c], kf[t & 1][c]);  // acc[query row][key col]
+                if (t > 0) {
+#pragma unroll
+                    for (int r = c * 16 / G::NCH; r < (c + 1) * 16 / G::NCH; ++r) add(t - 1, r);
+                }
+            }
+            __builtin_amdgcn_sched_barrier(0);
+            prev = acc;
+        }
+#pragma unroll
+        for (int r = 0; r < 16; ++r) add(3, r);
+    }
+
+    // wave w puts tile w together: the partial sums in wave order, then the maximum over the pairs that are admitted
+    float* const sums = reinterpret_cast<float*>(smem);
+    __syncthreads();  // every wave is done with its buffer
+#pragma unroll
+    for (int t = 0; t < 4; ++t)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) sums[((wave * 4 + t) * 16 + r) * 64 + lane] = sum[t >> 1][t & 1][r];
+    __syncthreads();
+    const bool excl = (p.flags & LEMO_EXCLUDE_SELF) != 0;
+    const int i0 = q0 + (wave >> 1) * 32, j0 = k0 + (wave & 1) * 32, j = j0 + l32;
+    float m = 0.f;
+#pragma unroll
+    for (int r = 0; r < 16; ++r) {
+        float v = 0.f;
+#pragma unroll
+        for (int w = 0; w < 4; ++w) v += sums[((w * 4 + wave) * 16 + r) * 64 + lane];
+        const int i = i0 + acc_row(r, lane);
+        const bool ok = (i < S) & (j < S) & (!causal | (j <= i)) & (!excl | (i != j));
+        m = fmaxf(m, ok ? v : 0.f);
+    }
+#pragma unroll
+    for (int sh = 32; sh >= 1; sh >>= 1) m = fmaxf(m, __shfl_xor(m, sh));
+    const int ti = i0 / 32, tj = j0 / 32;
+    if (lane == 0 && ti < p.nt32 && tj < p.nt32) p.tilemax[(size_t)ti * p.nt32 + tj] = m * p.out_scale;
+}
+
+template <int D, int MODE>
+static int launch_few(const BlockParams& p, int first, int rest, hipStream_t st) {
+    using G = FGeo<D>;
+    static std::once_flag once;
+    static hipError_t attr_err = hipSuccess;
+    std::call_once(once, [] {
+        attr_err = hipFuncSetAttribute(reinterpret_cast<const void*>(&tilemax_few_kernel<D, MODE>), hipFuncAttributeMaxDynamicSharedMemorySize, G::LDS);
+    });
+    if (attr_err != hipSuccess) return (int)attr_err;
+    const int per_xcd = (4 * rest + NUM_XCD - 1) / NUM_XCD;
+    hipLaunchKernelGGL((tilemax_few_kernel<D, MODE>), dim3((unsigned)(per_xcd * NUM_XCD)), dim3(256), G::LDS, st, p, first, rest);
+    return (int)hipGetLastError();
+}
+
+int launch_tilemax_few(const BlockParams& p, int d, int mode, int first, int rest, hipStream_t st) {
+    if (d == 128) return mode ? launch_few<128, 1>(p, first, rest, st) : launch_few<128, 0>(p, first, rest, st);
+    return mode ? launch_few<64, 1>(p, first, rest, st) : launch_few<64, 0>(p, first, rest, st);
+}
+
+}  // namespace lemo

@@ -519,6 +519,23 @@ def test_score_blocks_small_shapes(lemo, S, H, Hkv, d, dtype, b, flags, mode):
     assert_blocks_close(tb.cpu().numpy(), want_tb, "token blocks", atol)
 
 
+@pytest.mark.parametrize("S,H,Hkv,d,flags", [
+    (1, 1, 1, 128, 0), (65, 2, 1, 64, 3),                           # one row; one row past a quarter; fewer heads than waves
+    (1024, 4, 4, 128, 2), (1025, 5, 5, 128, 2),                     # 64 rectangles, all as quarters; 81, none
+    (1280, 6, 2, 128, 1), (1281, 3, 3, 128, 3),                     # the same under a causal mask: 55 and 66
+    (1408, 9, 3, 64, 0), (1920, 4, 1, 64, 1), (1921, 4, 2, 64, 1),  # 121, 120 (quarters), 136
+    (2850, 7, 7, 128, 3), (2060, 3, 1, 64, 0)])                     # a round of whole rectangles and 20 (33) in quarters
+def test_score_blocks_few_rectangles(lemo, S, H, Hkv, d, flags):
+    for mode in (0, 1):
+        say(f"[blocks few] S={S} H={H}/{Hkv} d={d} flags={flags} mode={mode}")
+        Q, K = wl.tiny_qk(S, H, Hkv, d, "bf16", seed=S + d)
+        sb, tb = lemo.lemo_score_blocks(Q.cuda(), K.cuda(), 32, flags=flags, mode=mode)
+        torch.cuda.synchronize()
+        want_sb, want_tb = oracle.score_blocks(wl.as_numpy(Q), wl.as_numpy(K), 32, flags=flags, mode=mode)
+        assert_blocks_close(sb.cpu().numpy(), want_sb, "score blocks", 1e-6 if mode == 0 else 1e-5)
+        assert_blocks_close(tb.cpu().numpy(), want_tb, "token blocks", 1e-6 if mode == 0 else 1e-5)
+
+
 def test_score_blocks_options_and_determinism(lemo):
     say("[blocks] options")
     Q, K = wl.tiny_qk(700, 4, 2, 128, "bf16", seed=5)
