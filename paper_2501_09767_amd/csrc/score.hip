@@ -65,10 +65,12 @@ __global__ __launch_bounds__(SC_THREADS, (Geo<T, D, NRT, KS>::MIN_WG)) void rows
 
     // resident operand: this wave's queries as MFMA B fragments
     u32x4 qf[NRT][G::NCH];
+    if constexpr (KS == 1) {
 #pragma unroll
-    for (int qt = 0; qt < NRT; ++qt)
+        for (int qt = 0; qt < NRT; ++qt)
 #pragma unroll
-        for (int c = 0; c < G::NCH; ++c) qf[qt][c] = load_piece(Qb, p.q_ts, q_off, qw0 + qt * 32 + l32, S, c * 32 + half * 16);
+            for (int c = 0; c < G::NCH; ++c) qf[qt][c] = load_piece(Qb, p.q_ts, q_off, qw0 + qt * 32 + l32, S, c * 32 + half * 16);
+    }
 
     // key stages [0, nstage): under a causal mask only keys up to the block's last query matter
     const int q_last = min(q0 + G::BLOCK, S) - 1;
@@ -79,6 +81,16 @@ __global__ __launch_bounds__(SC_THREADS, (Geo<T, D, NRT, KS>::MIN_WG)) void rows
     int st_voff[G::NLOAD];
     stage_offsets<G>(st_voff, k_row_bytes, tid);
     const unsigned lds_w = lds_offset_of(smem) + (unsigned)__builtin_amdgcn_readfirstlane(wave) * 1024u;
+
+    if constexpr (KS > 1) {  // the queries pass through the second stage, while the first stage of keys arrives
+        load_resident<G>(reinterpret_cast<const char*>(Qb + q_off), (int)p.q_ts * (int)sizeof(T), q0, S, lds_w + G::STAGE_BYTES, tid);
+        stage_load<G>(st_voff, stage_desc<G>(k_head, k_row_bytes, 0, S, true), lds_w);
+        stage_settle();
+        __syncthreads();
+#pragma unroll
+        for (int qt = 0; qt < NRT; ++qt) read_frags<G>(qf[qt], smem + G::STAGE_BYTES, (qw0 - q0) / 32 + qt, l32, half);
+        stage_settle();
+    }
 
     float* const refs = reinterpret_cast<float*>(smem + 2 * G::STAGE_BYTES + G::MERGE_BYTES);  // [wave][RES]
     float lse[NRT];       // the result: lse2 of query qw0 + qt*32 + l32
@@ -94,8 +106,10 @@ __global__ __launch_bounds__(SC_THREADS, (Geo<T, D, NRT, KS>::MIN_WG)) void rows
 #pragma unroll
     for (int r = 0; r < 16; ++r) carry[r] = -INFINITY;
 
-    stage_load<G>(st_voff, stage_desc<G>(k_head, k_row_bytes, 0, S, true), lds_w);
-    stage_settle();
+    if (KS == 1 || !frozen) {
+        stage_load<G>(st_voff, stage_desc<G>(k_head, k_row_bytes, 0, S, true), lds_w);
+        stage_settle();
+    }
     for (int t = 0; t < nstage; ++t) {
         __syncthreads();  // stage t is complete; every wave is done reading stage t-1
         const bool more = t + 1 < nstage;
@@ -316,10 +330,12 @@ __global__ __launch_bounds__(SC_THREADS, (Geo<T, D, NRT, KS>::MIN_WG)) void cols
 
     // resident operand: this wave's keys as MFMA B fragments (zero beyond the block's end)
     u32x4 kf[NRT][G::NCH];
+    if constexpr (KS == 1) {
 #pragma unroll
-    for (int kt = 0; kt < NRT; ++kt)
+        for (int kt = 0; kt < NRT; ++kt)
 #pragma unroll
-        for (int c = 0; c < G::NCH; ++c) kf[kt][c] = load_piece(Kb, p.k_ts, k_off, kw0 + kt * 32 + l32, kend, c * 32 + half * 16);
+            for (int c = 0; c < G::NCH; ++c) kf[kt][c] = load_piece(Kb, p.k_ts, k_off, kw0 + kt * 32 + l32, kend, c * 32 + half * 16);
+    }
 
     float col[NRT], col2[NRT], dg[NRT];  // column kw0 + kt*32 + l32 (its sum kept in two halves, col and col2)
 #pragma unroll
@@ -346,10 +362,18 @@ __global__ __launch_bounds__(SC_THREADS, (Geo<T, D, NRT, KS>::MIN_WG)) void cols
 #pragma unroll
     for (int r = 0; r < 16; ++r) carry_nl[r] = -INFINITY;
 
+    if constexpr (KS > 1)  // the keys pass through the second stage
+        load_resident<G>(reinterpret_cast<const char*>(Kb + k_off), (int)p.k_ts * (int)sizeof(T), key0, S, lds_w + G::STAGE_BYTES, tid);
     stage_load<G>(st_voff, stage_desc<G>(q_head, q_row_bytes, t_hi * G::TILE, S, true), lds_w);
     pre_l = fetch_l(t_hi);
     if (tid < G::TILE) sLbase[tid] = fix_l(t_hi, pre_l);
     stage_settle();
+    if constexpr (KS > 1) {
+        __syncthreads();
+#pragma unroll
+        for (int kt = 0; kt < NRT; ++kt) read_frags<G>(kf[kt], smem + G::STAGE_BYTES, (kw0 - key0) / 32 + kt, l32, half);
+        stage_settle();
+    }
     int buf = 0;
     for (int t = t_hi; t >= t_lo; --t, buf ^= 1) {
         __syncthreads();

@@ -8,8 +8,8 @@
 // What bounds it: issue.  A 32 x 32 tile of 64 elements (d = 64) is 768 cycles of MFMAs, 176 instructions of splitting over the NRT
 // tiles that use them, and the fma, exp2 and add of each logit; one subtile per barrier leaves the rest uncovered (about 1700
 // cycles a tile on a full chip).  Measured, both sweeps and the head mean, us, before (binary32 MFMAs) / now, causal:
-//   d = 64    1024 tokens, 4 heads 32.8 / 28.6;  3000, 4: 91.7 / 65.6;  1024, 12: 39.1 / 30.7;  5000, 16: 476 / 318
-//   d = 128   1000 tokens, 32 heads 117 / 80;  2500, 32: 473 / 345;  1500, 16, no mask: 220 / 154
+//   d = 64    1024 tokens, 4 heads 32.8 / 28.1;  3000, 4: 91.7 / 65.2;  1024, 12: 39.1 / 29.6;  5000, 16: 478 / 307
+//   d = 128   1000 tokens, 32 heads 117 / 76;  2500, 32: 475 / 329;  1500, 16, no mask: 220 / 151
 // and as far from 64 bits (per-head column sums, 60 draws each: 6.6e-8 before, 6.9e-8 now for 1024 tokens of 4 heads, 8.3e-8 / 8.0e-8 for 300 of
 // 12, 7.85e-8 / 7.87e-8 for 1000 of 16 heads of 128; single draws spread by a third).
 // Tried (5000 tokens, 16 heads, d = 64): two waves per row with two subtiles each 580 us, whole rows 397, one resident subtile
@@ -22,14 +22,15 @@
 
 namespace lemo {
 
-// One 32-row subtile as MFMA operand: resident (split once, zero beyond `nrows`) and streamed (from a stage).  Lane half h of operand
+// One 32-row subtile as MFMA operand: resident (split once, from the block's rows in a stage) and streamed.  Lane half h of operand
 // chunk c holds the 16 bytes h of the row's 32-byte chunks 2c and 2c + 1.
 template <typename G> struct Resident32 {
     Split8 f[G::NCH / 2];
-    __device__ __forceinline__ void load(const float* base, long long tok_stride, long long head_off, int row, int nrows, int half) {
+    __device__ __forceinline__ void read(const char* sbuf, int sub, int l32, int half) {
+        u32x4 raw[G::NCH];
+        read_frags<G>(raw, sbuf, sub, l32, half);
 #pragma unroll
-        for (int c = 0; c < G::NCH / 2; ++c)
-            f[c] = split_f32(load_piece(base, tok_stride, head_off, row, nrows, c * 64 + half * 16), load_piece(base, tok_stride, head_off, row, nrows, c * 64 + 32 + half * 16));
+        for (int c = 0; c < G::NCH / 2; ++c) f[c] = split_f32(raw[2 * c], raw[2 * c + 1]);
     }
 };
 template <typename G> struct Streamed32 {
@@ -86,10 +87,6 @@ __global__ __launch_bounds__(SC_THREADS, (Geo<float, D, NRT, KS>::MIN_WG)) void 
     const int part = wave % KS;               // this wave's subtile of a stage
     const int qw0 = q0 + wave / KS * G::RES;  // first query of this wave
 
-    Resident32<G> qf[NRT];
-#pragma unroll
-    for (int qt = 0; qt < NRT; ++qt) qf[qt].load(Qb, p.q_ts, q_off, qw0 + qt * 32 + l32, S, half);
-
     // key stages [0, nstage): under a causal mask only keys up to the block's last query matter
     const int q_last = min(q0 + G::BLOCK, S) - 1;
     const int nstage = (causal ? q_last : S - 1) / G::TILE + 1;
@@ -98,6 +95,16 @@ __global__ __launch_bounds__(SC_THREADS, (Geo<float, D, NRT, KS>::MIN_WG)) void 
     int st_voff[G::NLOAD];
     stage_offsets<G>(st_voff, k_row_bytes, tid);
     const unsigned lds_w = lds_offset_of(smem) + (unsigned)wave * 1024u;
+
+    // the queries pass through the second stage, while the first stage of keys arrives
+    Resident32<G> qf[NRT];
+    load_resident<G>(reinterpret_cast<const char*>(Qb + q_off), (int)p.q_ts * 4, q0, S, lds_w + G::STAGE_BYTES, tid);
+    stage_load<G>(st_voff, stage_desc<G>(k_head, k_row_bytes, 0, S, true), lds_w);
+    stage_settle();
+    __syncthreads();
+#pragma unroll
+    for (int qt = 0; qt < NRT; ++qt) qf[qt].read(smem + G::STAGE_BYTES, (qw0 - q0) / 32 + qt, l32, half);
+    stage_settle();
 
     float2* const shares = reinterpret_cast<float2*>(smem + 2 * G::STAGE_BYTES);                // [wave][half][RES]
     float* const refs = reinterpret_cast<float*>(smem + 2 * G::STAGE_BYTES + G::MERGE_BYTES);  // [wave][RES]
@@ -111,8 +118,10 @@ __global__ __launch_bounds__(SC_THREADS, (Geo<float, D, NRT, KS>::MIN_WG)) void 
 #pragma unroll
     for (int r = 0; r < 16; ++r) carry[r] = -INFINITY;
 
-    stage_load<G>(st_voff, stage_desc<G>(k_head, k_row_bytes, 0, S, true), lds_w);
-    stage_settle();
+    if (!frozen) {
+        stage_load<G>(st_voff, stage_desc<G>(k_head, k_row_bytes, 0, S, true), lds_w);
+        stage_settle();
+    }
     for (int t = 0; t < nstage; ++t) {
         __syncthreads();  // stage t is complete; every wave is done reading stage t-1
         const bool more = t + 1 < nstage;
@@ -262,10 +271,6 @@ __global__ __launch_bounds__(SC_THREADS, (Geo<float, D, NRT, KS>::MIN_WG)) void 
     const int part = wave % KS;                 // this wave's subtile of a stage
     const int kw0 = key0 + wave / KS * G::RES;  // first key of this wave
 
-    Resident32<G> kf[NRT];  // zero beyond the block's end
-#pragma unroll
-    for (int kt = 0; kt < NRT; ++kt) kf[kt].load(Kb, p.k_ts, k_off, kw0 + kt * 32 + l32, kend, half);
-
     // query stages run from the end of the sequence DOWN to the first stage that can see this block
     const int t_hi = (S - 1) / G::TILE;
     const int t_lo = causal ? key0 / G::TILE : 0;
@@ -278,6 +283,16 @@ __global__ __launch_bounds__(SC_THREADS, (Geo<float, D, NRT, KS>::MIN_WG)) void 
     auto fetch_l = [&](int t) { return tid < G::TILE ? lse[min(t * G::TILE + tid, S - 1)] : 0.f; };
     auto fix_l = [&](int t, float v) { return t * G::TILE + tid < S ? -v : -INFINITY; };  // stored negated: p = exp2(s*c2 + nl)
 
+    // the keys pass through the second stage, while the first stage of queries arrives
+    Resident32<G> kf[NRT];
+    load_resident<G>(reinterpret_cast<const char*>(Kb + k_off), (int)p.k_ts * 4, key0, S, lds_w + G::STAGE_BYTES, tid);
+    stage_load<G>(st_voff, stage_desc<G>(q_head, q_row_bytes, t_hi * G::TILE, S, true), lds_w);
+    stage_settle();
+    __syncthreads();
+#pragma unroll
+    for (int kt = 0; kt < NRT; ++kt) kf[kt].read(smem + G::STAGE_BYTES, (kw0 - key0) / 32 + kt, l32, half);
+    stage_settle();
+
     float col[NRT], dg[NRT];  // column kw0 + kt*32 + l32
     bool whole = false;       // workgroup-uniform: which pass this is
     for (;;) {
@@ -289,7 +304,7 @@ __global__ __launch_bounds__(SC_THREADS, (Geo<float, D, NRT, KS>::MIN_WG)) void 
 #pragma unroll
     for (int r = 0; r < 16; ++r) carry_nl[r] = -INFINITY;
 
-    stage_load<G>(st_voff, stage_desc<G>(q_head, q_row_bytes, t_hi * G::TILE, S, true), lds_w);
+    if (whole) stage_load<G>(st_voff, stage_desc<G>(q_head, q_row_bytes, t_hi * G::TILE, S, true), lds_w);
     pre_l = fetch_l(t_hi);
     if (tid < G::TILE) sLbase[tid] = fix_l(t_hi, pre_l);
     stage_settle();

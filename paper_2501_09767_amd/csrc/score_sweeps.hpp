@@ -53,6 +53,7 @@ template <typename T, int D, int NRT_, int KS_> struct Geo {
     static constexpr int LDS_COLSUM = 2 * STAGE_BYTES + 2 * TILE * (int)sizeof(float) + MERGE_BYTES;
     static constexpr int MIN_WG = (ROWB * NRT > 512 || NRT > 2 || SC_WAVES > 4) ? 1 : ROWB > 128 ? 2 : 3;  // workgroups per CU the register budget is set for
     static_assert(TILE * CPR % SC_THREADS == 0, "tile must split evenly over the workgroup");
+    static_assert(KS == 1 || (BLOCK <= TILE && NLOAD * BLOCK % TILE == 0), "shared rows are loaded through one stage");
     static_assert(SC_WAVES % KS == 0 && NSUB % KS == 0, "the shares must be whole subtiles");
 };
 
@@ -95,6 +96,19 @@ __device__ __forceinline__ void stage_load_slot(const int (&voff)[G::NLOAD], u32
 #pragma unroll
     for (int i = 0; i < G::NLOAD; ++i)
         if (i >= ti * G::NLOAD / nslots && i < (ti + 1) * G::NLOAD / nslots) lds_direct_b128(rsrc, lds_stage + i * (SC_THREADS * 16), voff[i]);
+}
+// A wave's resident fragments (row `row0` of the block on), from the block's rows in an LDS stage of the same layout.  For waves
+// that share rows: loaded straight from memory, 32 bytes of each of 32 rows at a time and by every sharer, the block's rows
+// are 4096 line accesses of a CU (two workgroups, d = 128: 1.8 us of the 4.3 between the start and the first stage), as
+// LDS-direct loads a quarter of that or less.  Both sweeps and the head mean, us before / now: bf16 d = 128 1000 tokens, 32 heads 29.2 /
+// 25.9, 2048 60.1 / 57.4, 4096 174 / 171; d = 64 2048 tokens, 16 heads 35.1 / 33.2; binary32 d = 64 5000 tokens, 16 heads 318 / 307.
+template <typename G>
+__device__ __forceinline__ void load_resident(const char* head, int row_bytes, int first, int nrows, unsigned lds_stage, int tid) {
+    int voff[G::NLOAD];
+    stage_offsets<G>(voff, row_bytes, tid);
+    const u32x4 desc = stage_desc<G>(head, row_bytes, first, nrows, true);
+#pragma unroll
+    for (int i = 0; i < G::NLOAD * G::BLOCK / G::TILE; ++i) lds_direct_b128(desc, lds_stage + i * (SC_THREADS * 16), voff[i]);
 }
 // before the barrier that ends a stage: this wave's loads of the next stage have landed, its reads of this one returned
 __device__ __forceinline__ void stage_settle() {
