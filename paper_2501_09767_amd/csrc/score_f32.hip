@@ -10,8 +10,9 @@
 // cycles a tile on a full chip).  Measured, both sweeps and the head mean, us, before (binary32 MFMAs) / now, causal:
 //   d = 64    1024 tokens, 4 heads 32.8 / 28.1;  3000, 4: 91.7 / 65.2;  1024, 12: 39.1 / 29.6;  5000, 16: 478 / 307
 //   d = 128   1000 tokens, 32 heads 117 / 76;  2500, 32: 475 / 329;  1500, 16, no mask: 220 / 151
-// and as far from 64 bits (per-head column sums, 60 draws each: 6.6e-8 before, 6.9e-8 now for 1024 tokens of 4 heads, 8.3e-8 / 8.0e-8 for 300 of
-// 12, 7.85e-8 / 7.87e-8 for 1000 of 16 heads of 128; single draws spread by a third).
+// and no further from 64 bits (scores, relative 2-norm, mean of 12 to 60 draws, before / now: 1024 tokens, 4 heads of 64 4.60e-8 /
+// 4.52e-8; 300, 12 6.4e-8 / 5.7e-8; 3000, 4 5.08e-8 / 5.08e-8; 5000, 16 6.4e-8 / 6.3e-8; 1024, 12, no mask 6.4e-8 / 5.9e-8; 1000,
+// 16 heads of 128 6.3e-8 / 5.8e-8; 2500, 32 8.4e-8 / 8.7e-8; 700, 16, no mask 7.0e-8 / 6.0e-8; single draws spread by a third).
 // Tried (5000 tokens, 16 heads, d = 64): two waves per row with two subtiles each 580 us, whole rows 397, one resident subtile
 // per wave 341.
 //
@@ -47,14 +48,18 @@ template <typename G> struct Streamed32 {
         raw[0][0] = piece(0);
         raw[0][1] = piece(1);
     }
-    // MFMA q of a tile (streamed rows x resident columns); the subtile's first tile splits the operand on its way
+    // MFMA q of a tile (streamed rows x resident columns); the subtile's first tile splits the operand on its way.  The products of the
+    // leading parts come last: what the others round is then a rounding of sums
+    // 2^-8 as large (chunk by chunk: 4.9e-8 from 64 bits instead of 4.5e-8 at 1024 tokens, 4 heads, same time).
     __device__ __forceinline__ void mma(int q, f32x16& acc, const Resident32<G>& r, bool first) {
-        const int c = q / SPLIT_TERMS;
-        if (first && q % SPLIT_TERMS == 0) {
+        constexpr int LOW = SPLIT_TERMS - 1, LEAD = G::NCH / 2 * LOW;
+        if (q >= LEAD) return mma_split(acc, f[q - LEAD], r.f[q - LEAD], LOW);
+        const int c = q / LOW;
+        if (first && q % LOW == 0) {
             f[c] = split_f32(raw[c & 1][0], raw[c & 1][1]);
             if (c + 1 < G::NCH / 2) { raw[(c + 1) & 1][0] = piece(2 * c + 2); raw[(c + 1) & 1][1] = piece(2 * c + 3); }
         }
-        mma_split(acc, f[c], r.f[c], q % SPLIT_TERMS);
+        mma_split(acc, f[c], r.f[c], q % LOW);
     }
     // the same tile from binary32 MFMAs, the resident operand read again
     __device__ __forceinline__ void mma_whole(f32x16& acc, const float* base, long long tok_stride, long long head_off, int at, int nrows) const {
