@@ -187,13 +187,10 @@ __global__ __launch_bounds__(SG_THREADS, GW == 4 ? 2 : 1) void gather_gemm_small
     auto b_frag = [&](int st, int i, int c) { return frag(stages + st * G::STAGE + G::OPER, B_KMAJOR, wn, i, c); };
 
     f32x16 acc[WT][WT];
-    auto clear = [&]() {
 #pragma unroll
-        for (int i = 0; i < WT; ++i)
+    for (int i = 0; i < WT; ++i)
 #pragma unroll
-            for (int j = 0; j < WT; ++j) acc[i][j] = f32x16{0};
-    };
-    clear();
+        for (int j = 0; j < WT; ++j) acc[i][j] = f32x16{0};
     auto drain = [&]() {
         __builtin_amdgcn_s_waitcnt(vmcnt_imm(0));  // requests past the end write (zeros) to the stages, too
         __syncthreads();
@@ -362,6 +359,75 @@ __global__ __launch_bounds__(SG_THREADS, GW == 4 ? 2 : 1) void gather_gemm_small
         if (it < nk) step(it, I0{});
         drain();
     };
+    // Sums that the splits do not give, formed again from the operands' own MFMAs: those that are not finite.  Sum by sum, so that no
+    // row depends on its neighbours.
+    auto form_again = [&]() {
+        // f(stage) for every slab, the next one on its way
+        auto each_slab = [&](auto f) {
+            issue_tokens(0);
+            issue_tokens(1);
+            auto load = [&](int kt) {
+                const Slab s = slab_of(kt);
+                read_tokens(kt);
+#pragma unroll
+                for (int i = 0; i < NLD; ++i) load_a(s, i);
+#pragma unroll
+                for (int i = 0; i < NLD; ++i) load_b(s, i);
+                issue_tokens(kt + 2);
+            };
+            auto landed = [&]() {
+                __builtin_amdgcn_s_waitcnt(vmcnt_imm(0));
+                __builtin_amdgcn_s_waitcnt(LGKMCNT0);
+                group_barrier();
+            };
+            if constexpr (LAYOUT == GG_TN) landed();
+            load(0);
+#pragma unroll 1
+            for (int kt = 0; kt < nk; ++kt) {
+                landed();  // and everyone has read the slab before, into whose stage the next one comes
+                load(kt + 1);
+                f(kt & 1);
+            }
+            drain();
+        };
+        unsigned again[WT][WT];  // bit r: acc[i][j][r]
+        bool any = false;
+#pragma unroll
+        for (int i = 0; i < WT; ++i)
+#pragma unroll
+            for (int j = 0; j < WT; ++j) {
+                again[i][j] = 0;
+#pragma unroll
+                for (int r = 0; r < 16; ++r)
+                    if (!isfinite(acc[i][j][r]) && m0 + (wm * WT + i) * 32 + acc_row(r, lane) < p.M && n0 + (wn * WT + j) * 32 + l32 < p.N) again[i][j] |= 1u << r;
+                any |= again[i][j] != 0;
+            }
+        if (!__syncthreads_or(any)) return;
+        f32x16 sum[WT][WT];
+        bool tile[WT][WT];  // of the wave
+#pragma unroll
+        for (int i = 0; i < WT; ++i)
+#pragma unroll
+            for (int j = 0; j < WT; ++j) {
+                sum[i][j] = f32x16{0};
+                tile[i][j] = __ballot(again[i][j] != 0) != 0;
+            }
+        each_slab([&](int st) {
+#pragma unroll
+            for (int c = 0; c < 4; ++c)
+#pragma unroll
+                for (int i = 0; i < WT; ++i)
+#pragma unroll
+                    for (int j = 0; j < WT; ++j)
+                        if (tile[i][j]) mma_chunk<T>(sum[i][j], a_frag(st, i, c), b_frag(st, j, c));
+        });
+#pragma unroll
+        for (int i = 0; i < WT; ++i)
+#pragma unroll
+            for (int j = 0; j < WT; ++j)
+#pragma unroll
+                for (int r = 0; r < 16; ++r) acc[i][j][r] = again[i][j] >> r & 1 ? sum[i][j][r] : acc[i][j][r];
+    };
     if constexpr (ESZ == 4 && GW == 4) {
         static_assert(WT == 2 && 2 * NLD == 8, "four operand tiles, a load per three MFMAs");
         split_product();
@@ -372,10 +438,7 @@ __global__ __launch_bounds__(SG_THREADS, GW == 4 ? 2 : 1) void gather_gemm_small
             for (int j = 0; j < WT; ++j)
 #pragma unroll
                 for (int r = 0; r < 16; ++r) probe = fmaf(acc[i][j][r], 0.f, probe);
-        if (__syncthreads_or(!(probe == 0.f))) {
-            clear();
-            product();
-        }
+        if (__syncthreads_or(!(probe == 0.f))) form_again();
     } else {
         product();
     }

@@ -929,6 +929,34 @@ def test_gather_gemm_fp32_split(lemo, form, M, N, K, what):
         np.testing.assert_allclose(got[M // 2].cpu().numpy(), want[M // 2].cpu().numpy(), rtol=1e-5)
 
 
+@pytest.mark.parametrize("value", [math.inf, math.nan, torch.finfo(torch.float32).max])
+@pytest.mark.parametrize("form", ["nt", "add", "dw"])
+def test_gather_gemm_fp32_rows_do_not_depend_on_their_neighbours(lemo, form, value):
+    """One row whose sums splits do not give (ragged tiles, so that what lies past the result is formed as well): the other rows
+    keep their bits, and the row is the one that the same product gives among other rows."""
+    say(f"[gemm] fp32 {form}, one row with {value}")
+    M, N, K = 1700, 1932, 132
+    gen = torch.Generator(device="cuda").manual_seed(5)
+    A, B = torch.randn((M, K), generator=gen, device="cuda"), torch.randn((N, K), generator=gen, device="cuda")
+    B[:, 7] = B[:, 7].abs() + 0.25
+
+    def product(a):
+        if form == "dw":
+            return lemo.lemo_gather_gemm_dw(a.t().contiguous(), B.t().contiguous(), None)
+        if form == "add":
+            return lemo.lemo_gather_gemm_add(a, None, B, torch.zeros((M, N), device="cuda"), None)
+        return lemo.lemo_gather_gemm(a, None, B)
+    plain, bad = product(A), A.clone()
+    bad[[40, 1699], 7] = value
+    got = product(bad)
+    A[40, 7] = value
+    alone = product(A)
+    rest = torch.ones(M, dtype=torch.bool, device="cuda")
+    rest[[40, 1699]] = False
+    assert torch.equal(got[rest], plain[rest])
+    assert torch.equal(got[40].view(torch.int32), alone[40].view(torch.int32)) and torch.equal(alone[1699], plain[1699])
+
+
 @pytest.mark.parametrize("far", ["dY", "X"])
 def test_gather_gemm_dw_f32_beyond_32_bit_offsets(lemo, far):
     """binary32 weight gradient of operands whose row pitch is 8 MiB and more, which goes through transposed copies in the
