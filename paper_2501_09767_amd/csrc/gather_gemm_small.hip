@@ -9,10 +9,13 @@
 //           and takes 32 x 32 blocks, for four times the workgroups (splitting an operand for one tile costs as much as it saves).
 //   GW = 4  (binary32) the four waves of a workgroup share a slab: 128 x 128 output tile, 64 x 64 per wave, two workgroups per
 //           CU (70 KB of LDS each).  The products are three-part splits on the bf16 matrix cores (lemo_common.hpp); a slab costs a
-//           wave 352 instructions of splitting beside 1536 cycles of MFMAs, 2240 cycles where binary32 MFMAs took 4096 (and are
-//           still what a sum that is not finite is formed from again).  us, before / now: 1500 x 11008 x 4096 1209 / 783 (2.02 rounds
-//           run as 3), 1024 x 4096 x 1024 70 / 53, 10000 x 768 x 3072 381 / 250, weight gradient 8192 x 2048 of 300 tokens 96 / 70;
-//           error against 64 bits 1.1e-6 / 1.0e-6, 5.7e-7 / 4.9e-7, 9.9e-7 / 8.6e-7, 3.1e-7 / 2.6e-7.
+//           wave 352 instructions of splitting and 16 for the largest operands beside 1536 cycles of MFMAs, 2240 cycles where binary32
+//           MFMAs took 4096.  Sums that the splits may not give are formed again from those (form_again).  us, binary32
+//           MFMAs / now: 1500 x 11008 x 4096 1188 / 784 (2.02 rounds run as 3), 1024 x 4096 x 1024 71 / 54, 10000 x 768 x 3072 359 /
+//           249, weight gradient 8192 x 2048 of 300 tokens 95 / 78; error against 64 bits 1.1e-6 / 1.0e-6, 5.7e-7 / 4.9e-7, 9.9e-7 /
+//           8.6e-7, 3.1e-7 / 2.6e-7.  The first product without the largest operands 770, with the smallest as well, which would spare
+//           form_again its look for them, 825; with many sums of exactly zero (whole numbers, which the chip multiplies faster)
+//           617, with that look 815; one row of small values 1283, all rows 2350, not a number throughout 2218.
 // Slabs arrive by LDS-direct loads, two per group in flight, and the registers are the third buffer: the MFMA fragments
 // of the next slab are read during the first MFMAs of the current one, which frees its LDS stage for the slab after next.
 // Measured beside this (M = 256, N = K = 4096 with 64 x 64 tiles, 17.5 us): a ring of four half-slabs with the loads spread over all
@@ -183,14 +186,16 @@ __global__ __launch_bounds__(SG_THREADS, GW == 4 ? 2 : 1) void gather_gemm_small
         return u32x4{l2.x, l2.y, h2.x, h2.y};
     };
     char* const stages = smem + group * 2 * G::STAGE;
-    auto a_frag = [&](int st, int i, int c) { return frag(stages + st * G::STAGE, A_KMAJOR, wm, i, c); };
-    auto b_frag = [&](int st, int i, int c) { return frag(stages + st * G::STAGE + G::OPER, B_KMAJOR, wn, i, c); };
+    // (GW = 4: the tiles of one of two waves with the same rows, or columns, are exchanged, so that tile 0 of both waves is all of them)
+    auto a_frag = [&](int st, int i, int c) { return frag(stages + st * G::STAGE, A_KMAJOR, wm, i ^ wn, c); };
+    auto b_frag = [&](int st, int i, int c) { return frag(stages + st * G::STAGE + G::OPER, B_KMAJOR, wn, i ^ wm, c); };
 
     f32x16 acc[WT][WT];
 #pragma unroll
     for (int i = 0; i < WT; ++i)
 #pragma unroll
         for (int j = 0; j < WT; ++j) acc[i][j] = f32x16{0};
+    float most[2] = {0.f, 0.f};  // (splits) largest magnitude in the lane's row of tile 0 of the wave's rows, of its columns
     auto drain = [&]() {
         __builtin_amdgcn_s_waitcnt(vmcnt_imm(0));  // requests past the end write (zeros) to the stages, too
         __syncthreads();
@@ -305,6 +310,7 @@ __global__ __launch_bounds__(SG_THREADS, GW == 4 ? 2 : 1) void gather_gemm_small
 #pragma unroll
                 for (int pr = q * 16 / (4 * SPLIT_TERMS); pr < (q + 1) * 16 / (4 * SPLIT_TERMS); ++pr) {
                     split_pair(part[SET ^ 1][pr / 4], pr % 4, raw[pr / 4][pr % 4 / 2]);
+                    if (pr / 4 % 2 == 0) most_of_pair(most[pr / 8], pr % 4, raw[pr / 4][pr % 4 / 2]);
                     if (pr % 4 == 3) read_raw(st, c16, pr / 4);
                 }
                 mem(q);
@@ -333,6 +339,10 @@ __global__ __launch_bounds__(SG_THREADS, GW == 4 ? 2 : 1) void gather_gemm_small
         for (int o = 0; o < 4; ++o) {
             read_raw(0, 0, o);
             part[0][o] = split_f32(raw[o][0], raw[o][1]);
+            if (o % 2 == 0) {
+#pragma unroll
+                for (int e = 0; e < 4; ++e) most_of_pair(most[o / 2], e, raw[o][e / 2]);
+            }
             read_raw(0, 1, o);
         }
         auto step = [&](int it, auto par_tag) {
@@ -359,8 +369,10 @@ __global__ __launch_bounds__(SG_THREADS, GW == 4 ? 2 : 1) void gather_gemm_small
         if (it < nk) step(it, I0{});
         drain();
     };
-    // Sums that the splits do not give, formed again from the operands' own MFMAs: those that are not finite.  Sum by sum, so that no
-    // row depends on its neighbours.
+    // Sums that the splits do not give, formed again from the operands' own MFMAs: those that are not finite, and small ones of a row
+    // and a column of which one has values too small to be split (they lose up to 2^-134 each, so a sum above `slight` times the
+    // largest operand does not feel it).  Sum by sum, so that no row depends on its neighbours.
+    const float slight = 0x1p-103f * (float)K;
     auto form_again = [&]() {
         // f(stage) for every slab, the next one on its way
         auto each_slab = [&](auto f) {
@@ -390,19 +402,56 @@ __global__ __launch_bounds__(SG_THREADS, GW == 4 ? 2 : 1) void gather_gemm_small
             }
             drain();
         };
+        unsigned* const of_rows = reinterpret_cast<unsigned*>(smem);  // [half-wave][128], of what a lane knows about tile 0
+        unsigned* const of_cols = of_rows + 256;
+        auto exchange = [&](unsigned row, unsigned col) {
+            of_rows[half * 128 + (wm * WT + wn) * 32 + l32] = row;
+            of_cols[half * 128 + (wn * WT + wm) * 32 + l32] = col;
+            __syncthreads();
+        };
         unsigned again[WT][WT];  // bit r: acc[i][j][r]
-        bool any = false;
+        // drops the sums that are not in f(what the lanes know about the sum's row, its column; the sum); false if none is left
+        auto keep = [&](auto f) {
+            bool any = false;
+#pragma unroll
+            for (int i = 0; i < WT; ++i)
+#pragma unroll
+                for (int j = 0; j < WT; ++j) {
+                    const int col = (wn * WT + (j ^ wm)) * 32 + l32;
+#pragma unroll
+                    for (int r = 0; r < 16; ++r) {
+                        const int row = (wm * WT + (i ^ wn)) * 32 + acc_row(r, lane);
+                        if (!f(of_rows[row], of_rows[128 + row], of_cols[col], of_cols[128 + col], fabsf(acc[i][j][r])) || m0 + row >= p.M || n0 + col >= p.N)
+                            again[i][j] &= ~(1u << r);
+                    }
+                    any |= again[i][j] != 0;
+                }
+            return __syncthreads_or(any) != 0;
+        };
 #pragma unroll
         for (int i = 0; i < WT; ++i)
 #pragma unroll
-            for (int j = 0; j < WT; ++j) {
-                again[i][j] = 0;
+            for (int j = 0; j < WT; ++j) again[i][j] = 0xffffu;
+        exchange(__float_as_uint(most[0]), __float_as_uint(most[1]));
+        if (!keep([&](unsigned r0, unsigned r1, unsigned c0, unsigned c1, float v) {
+                const float r = fmaxf(__uint_as_float(r0), __uint_as_float(r1)), c = fmaxf(__uint_as_float(c0), __uint_as_float(c1));
+                return !(v < INFINITY) | ((v < slight * fmaxf(r, c)) & (r > 0.f) & (c > 0.f));
+            }))
+            return;
+        unsigned least[2] = {0xffffffffu, 0xffffffffu};  // smallest magnitude but zero, bits * 2 - 1
+        each_slab([&](int st) {
 #pragma unroll
-                for (int r = 0; r < 16; ++r)
-                    if (!isfinite(acc[i][j][r]) && m0 + (wm * WT + i) * 32 + acc_row(r, lane) < p.M && n0 + (wn * WT + j) * 32 + l32 < p.N) again[i][j] |= 1u << r;
-                any |= again[i][j] != 0;
-            }
-        if (!__syncthreads_or(any)) return;
+            for (int c = 0; c < 4; ++c)
+#pragma unroll
+                for (int o = 0; o < 2; ++o) {
+                    const u32x4 v = o ? b_frag(st, 0, c) : a_frag(st, 0, c);
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) least[o] = min(least[o], (v[e] << 1) - 1);
+                }
+        });
+        exchange(least[0], least[1]);
+        if (!keep([&](unsigned r0, unsigned r1, unsigned c0, unsigned c1, float v) { return !(v < INFINITY) | (min(min(r0, r1), min(c0, c1)) < SPLIT_WHOLE * 2 - 1); }))
+            return;
         f32x16 sum[WT][WT];
         bool tile[WT][WT];  // of the wave
 #pragma unroll
@@ -431,14 +480,18 @@ __global__ __launch_bounds__(SG_THREADS, GW == 4 ? 2 : 1) void gather_gemm_small
     if constexpr (ESZ == 4 && GW == 4) {
         static_assert(WT == 2 && 2 * NLD == 8, "four operand tiles, a load per three MFMAs");
         split_product();
-        float probe = 0.f;  // not a number if any sum is infinite or not a number: an infinity does not survive the split
+        // (an infinity does not survive the split: the sum is then not a number)
+        float probe = 0.f, low = INFINITY;
 #pragma unroll
         for (int i = 0; i < WT; ++i)
 #pragma unroll
             for (int j = 0; j < WT; ++j)
 #pragma unroll
-                for (int r = 0; r < 16; ++r) probe = fmaf(acc[i][j][r], 0.f, probe);
-        if (__syncthreads_or(!(probe == 0.f))) form_again();
+                for (int r = 0; r < 16; ++r) {
+                    probe = fmaf(acc[i][j][r], 0.f, probe);
+                    low = fminf(low, fabsf(acc[i][j][r]));
+                }
+        if (__syncthreads_or(!(probe == 0.f) | (low < slight * 0x1p20f) | (fmaxf(most[0], most[1]) >= 0x1p20f))) form_again();
     } else {
         product();
     }
@@ -489,7 +542,7 @@ __global__ __launch_bounds__(SG_THREADS, GW == 4 ? 2 : 1) void gather_gemm_small
         for (int j = 0; j < WT; ++j)
 #pragma unroll
             for (int r = 0; r < 16; ++r)
-                *reinterpret_cast<float*>(mine + (i * 32 + acc_row(r, lane)) * G::EP + (j * 32 + l32) * 4) = acc[i][j][r];
+                *reinterpret_cast<float*>(mine + ((i ^ wn) * 32 + acc_row(r, lane)) * G::EP + ((j ^ wm) * 32 + l32) * 4) = acc[i][j][r];
     if constexpr (PARTS > 1) __syncthreads();  // (one group: a wave reads back its own block only)
 #pragma unroll
     for (int q = 0; q < PASSES; ++q) {

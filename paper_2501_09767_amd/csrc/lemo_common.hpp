@@ -93,12 +93,11 @@ __device__ __forceinline__ uint32_t pack_bf16x2_hw(float lo, float hi) {
 }
 
 // ---- binary32 products on the bf16 matrix cores ---------------------------------------------------
-// A binary32 value is the exact sum of three bf16 ones, each the rest rounded to nearest (below 2^-110 the last ones fall out of
-// bf16's range).  Six of the nine products of two such sums are formed, the smallest first; the other three amount to at most
+// A binary32 value is the exact sum of three bf16 ones, each the rest rounded to nearest (below 2^-110 it may not be: SPLIT_WHOLE).  Six of the nine products of two such sums are formed, the smallest first; the other three amount to at most
 // 2^-26 of a product, with either sign, and the 32 x 32 x 16 MFMA adds 16 products per rounding of the sum where the binary32 one
 // adds 2.  8 times the rate for 6 products; splitting 8 values takes 44 instructions.  (Cut off instead of rounded, the rests have
 // their value's sign: scores were then up to twice as far from 64 bits.)  Infinities do not survive this (infinity times a zero
-// part): a result that is not finite has to be formed again with mma_chunk<float>.
+// part).  Results that are not finite, or that feel what small values lose, have to be formed again with mma_chunk<float>.
 struct Split8 { u32x4 part[3]; };  // 8 values in three parts, as MFMA operands
 __device__ __forceinline__ void split_pair(Split8& s, int e, const u32x4& from) {  // values 2e and 2e + 1, elements 2 (e % 2) of `from` on
     float v0 = __uint_as_float(from[e % 2 * 2]), v1 = __uint_as_float(from[e % 2 * 2 + 1]);
@@ -115,6 +114,13 @@ __device__ __forceinline__ Split8 split_f32(const u32x4& lo, const u32x4& hi) {
 #pragma unroll
     for (int e = 0; e < 4; ++e) split_pair(s, e, e < 2 ? lo : hi);
     return s;
+}
+// Bits of 2^-110: below it a value's last part may fall below bf16's smallest number, 2^-133 (the matrix cores take denormal
+// numbers as they are), and up to 2^-134 of the value is lost.
+constexpr unsigned SPLIT_WHOLE = 17u << 23;
+// largest magnitude of the values that split_pair takes (NaN is passed over)
+__device__ __forceinline__ void most_of_pair(float& most, int e, const u32x4& from) {
+    asm("v_max3_f32 %0, %0, |%1|, |%2|" : "+v"(most) : "v"(from[e % 2 * 2]), "v"(from[e % 2 * 2 + 1]));
 }
 constexpr int SPLIT_TERMS = 6;
 __device__ __forceinline__ void mma_split(f32x16& acc, const Split8& a, const Split8& b, int term) {

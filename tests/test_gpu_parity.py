@@ -957,6 +957,45 @@ def test_gather_gemm_fp32_rows_do_not_depend_on_their_neighbours(lemo, form, val
     assert torch.equal(got[40].view(torch.int32), alone[40].view(torch.int32)) and torch.equal(alone[1699], plain[1699])
 
 
+@pytest.mark.parametrize("which", ["all", "columns", "two rows", "one operand"])
+@pytest.mark.parametrize("small,large", [(1e-34, 1.0), (1e-36, 1.0), (1e-37, 1e35), (1e-41, 1e35)])  # (ordinary rows stay below binary32's largest number)
+@pytest.mark.parametrize("form,M,N,K", [("nt", 1700, 1932, 132), ("add", 1600, 2052, 36), ("dw", 1924, 2060, 330)])
+def test_gather_gemm_fp32_split_keeps_small_operands(lemo, form, M, N, K, small, large, which):
+    """Operands that bf16 parts cannot hold (below 2^-110, down to denormal ones), on either side, in some rows only, or one in each row
+    beside ordinary ones: the binary32 product's error, a random walk of one rounding per term."""
+    say(f"[gemm] fp32 {form} M={M} N={N} K={K} operands of {small}, {which}")
+    gen = torch.Generator(device="cuda").manual_seed(M + K)
+    A, B = (torch.randn((n, K), generator=gen, device="cuda", dtype=torch.float64) for n in (M, N))
+    few = torch.zeros(M, dtype=torch.bool, device="cuda")
+    few[[40, M - 1]] = which == "two rows"
+    plain = A.float()
+    if which == "all":
+        A *= small
+        B *= large
+    elif which == "columns":
+        B *= small
+        A *= large
+    elif which == "two rows":
+        A[few] *= small
+        B *= large
+    else:
+        A[:, 5] *= small
+    A, B = A.float(), B.float()
+
+    def product(a):
+        if form == "dw":
+            return lemo.lemo_gather_gemm_dw(a.t().contiguous(), B.t().contiguous(), None)
+        if form == "add":
+            return lemo.lemo_gather_gemm_add(a, None, B, torch.zeros((M, N), device="cuda"), None)
+        return lemo.lemo_gather_gemm(a, None, B)
+    got = product(A)
+    want = A.double() @ B.double().t().contiguous()
+    for rows in (few, ~few):
+        assert (got.double() - want)[rows].norm() <= 2.0 ** -24 * math.sqrt(K) * want[rows].norm()
+    if which == "two rows":  # and the others are what they are among ordinary rows
+        assert torch.equal(got[~few], product(plain)[~few])
+
+
 @pytest.mark.parametrize("far", ["dY", "X"])
 def test_gather_gemm_dw_f32_beyond_32_bit_offsets(lemo, far):
     """binary32 weight gradient of operands whose row pitch is 8 MiB and more, which goes through transposed copies in the
