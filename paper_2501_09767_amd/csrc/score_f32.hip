@@ -16,24 +16,62 @@
 // Tried (5000 tokens, 16 heads, d = 64): two waves per row with two subtiles each 580 us, whole rows 397, one resident subtile
 // per wave 341.
 //
-// A sum that is not finite -- an infinity does not survive the split -- is formed again from binary32 MFMAs before anything is stored.
+// A sum that is not finite -- an infinity does not survive the split -- is formed again from binary32 MFMAs before anything is stored;
+// blocks whose logits would feel what small values lose to the split (needs_whole) take those at once.
 #include <mutex>
 
 #include "score_sweeps.hpp"
 
 namespace lemo {
 
+// smallest magnitude but zero (as bits * 2 - 1) and largest (NaN is passed over)
+struct Extent {
+    unsigned least = 0xffffffffu;
+    float most = 0.f;
+    __device__ __forceinline__ void take(const u32x4& v) {
+#pragma unroll
+        for (int e = 0; e < 4; ++e) least = min(least, (v[e] << 1) - 1);
+        most_of_pair(most, 0, v);
+        most_of_pair(most, 1, v);
+    }
+    __device__ __forceinline__ bool small() const { return least < SPLIT_WHOLE * 2 - 1; }
+};
 // One 32-row subtile as MFMA operand: resident (split once, from the block's rows in a stage) and streamed.  Lane half h of operand
 // chunk c holds the 16 bytes h of the row's 32-byte chunks 2c and 2c + 1.
 template <typename G> struct Resident32 {
     Split8 f[G::NCH / 2];
-    __device__ __forceinline__ void read(const char* sbuf, int sub, int l32, int half) {
+    __device__ __forceinline__ void read(const char* sbuf, int sub, int l32, int half, Extent& extent) {
         u32x4 raw[G::NCH];
         read_frags<G>(raw, sbuf, sub, l32, half);
+#pragma unroll
+        for (int c = 0; c < G::NCH; ++c) extent.take(raw[c]);
 #pragma unroll
         for (int c = 0; c < G::NCH / 2; ++c) f[c] = split_f32(raw[2 * c], raw[2 * c + 1]);
     }
 };
+// Does the block need whole operands from the start?  A value below 2^-110 loses up to 2^-134 to the split, and a logit feels
+// that if the other operand is beyond `limit` (logits of base 2: c2 * D * 2^-134 * limit = 2^-32).  The resident rows are at hand; only
+// if they have such values are the streamed rows [first, last) looked through.  `flags`: a word of LDS per wave.  Both sweeps and the
+// head mean, us without / with it: 1024 tokens, 4 heads of 64 28.7 / 28.9; 1000, 32 heads of 128 75.6 / 76.6; 2500, 32 331 / 333.
+template <typename G, int D>
+__device__ __forceinline__ bool needs_whole(const Extent& resident, float c2, const float* base, long long tok_stride, long long head_off, int first,
+                                            int last, int tid, int wave, int* flags) {
+    const float limit = 0x1p102f / (c2 * (float)D);
+    bool look = __any(resident.small() | (resident.most > limit));
+    if constexpr (G::KS < SC_WAVES) {  // (otherwise all waves hold the same rows; __syncthreads_or took 0.4 us of each sweep)
+        if (tid % WAVE == 0) flags[wave] = look;
+        __syncthreads();
+#pragma unroll
+        for (int w = 0; w < SC_WAVES; ++w) look |= flags[w] != 0;
+    }
+    if (!look) return false;
+    Extent streamed;
+#pragma unroll 1
+    for (int row = first + tid / G::CPR; row < last; row += G::ROWS_PER_LOAD) streamed.take(load_piece(base, tok_stride, head_off, row, last, tid % G::CPR * 16));
+    const bool small = __syncthreads_or(resident.small()), large = __syncthreads_or(resident.most > limit);
+    const bool other_small = __syncthreads_or(streamed.small()), other_large = __syncthreads_or(streamed.most > limit);
+    return (small & other_large) | (large & other_small);
+}
 template <typename G> struct Streamed32 {
     static constexpr int NM = G::NCH / 2 * SPLIT_TERMS;  // MFMAs per tile
     const char* row;   // (the pieces of a row are exchanged)
@@ -103,18 +141,20 @@ __global__ __launch_bounds__(SC_THREADS, (Geo<float, D, NRT, KS>::MIN_WG)) void 
 
     // the queries pass through the second stage, while the first stage of keys arrives
     Resident32<G> qf[NRT];
+    Extent extent;
     load_resident<G>(reinterpret_cast<const char*>(Qb + q_off), (int)p.q_ts * 4, q0, S, lds_w + G::STAGE_BYTES, tid);
     stage_load<G>(st_voff, stage_desc<G>(k_head, k_row_bytes, 0, S, true), lds_w);
     stage_settle();
     __syncthreads();
 #pragma unroll
-    for (int qt = 0; qt < NRT; ++qt) qf[qt].read(smem + G::STAGE_BYTES, (qw0 - q0) / 32 + qt, l32, half);
+    for (int qt = 0; qt < NRT; ++qt) qf[qt].read(smem + G::STAGE_BYTES, (qw0 - q0) / 32 + qt, l32, half, extent);
     stage_settle();
 
     float2* const shares = reinterpret_cast<float2*>(smem + 2 * G::STAGE_BYTES);                // [wave][half][RES]
     float* const refs = reinterpret_cast<float*>(smem + 2 * G::STAGE_BYTES + G::MERGE_BYTES);  // [wave][RES]
     float lse[NRT];       // the result: lse2 of query qw0 + qt*32 + l32
-    bool frozen = true;   // workgroup-uniform: which pass this is
+    // workgroup-uniform: which pass this is
+    bool frozen = !needs_whole<G, D>(extent, c2, Kb, p.k_ts, k_off, 0, causal ? q_last + 1 : S, tid, wave, reinterpret_cast<int*>(shares));
     for (;;) {
     float m[NRT], l[NRT];  // statistics of the queries qw0 + qt*32 + l32 this lane keeps
 #pragma unroll
@@ -290,16 +330,19 @@ __global__ __launch_bounds__(SC_THREADS, (Geo<float, D, NRT, KS>::MIN_WG)) void 
 
     // the keys pass through the second stage, while the first stage of queries arrives
     Resident32<G> kf[NRT];
+    Extent extent;
     load_resident<G>(reinterpret_cast<const char*>(Kb + k_off), (int)p.k_ts * 4, key0, S, lds_w + G::STAGE_BYTES, tid);
     stage_load<G>(st_voff, stage_desc<G>(q_head, q_row_bytes, t_hi * G::TILE, S, true), lds_w);
     stage_settle();
     __syncthreads();
 #pragma unroll
-    for (int kt = 0; kt < NRT; ++kt) kf[kt].read(smem + G::STAGE_BYTES, (kw0 - key0) / 32 + kt, l32, half);
+    for (int kt = 0; kt < NRT; ++kt) kf[kt].read(smem + G::STAGE_BYTES, (kw0 - key0) / 32 + kt, l32, half, extent);
     stage_settle();
 
     float col[NRT], dg[NRT];  // column kw0 + kt*32 + l32
-    bool whole = false;       // workgroup-uniform: which pass this is
+    float2* const shares = reinterpret_cast<float2*>(smem + 2 * G::STAGE_BYTES + 2 * G::TILE * (int)sizeof(float));  // [wave][RES]
+    // workgroup-uniform: which pass this is
+    bool whole = needs_whole<G, D>(extent, c2, Qb, p.q_ts, q_off, t_lo * G::TILE, S, tid, wave, reinterpret_cast<int*>(shares));
     for (;;) {
     float pre_l = 0.f;
 #pragma unroll
@@ -404,7 +447,6 @@ __global__ __launch_bounds__(SC_THREADS, (Geo<float, D, NRT, KS>::MIN_WG)) void 
     whole = true;
     }
 
-    float2* const shares = reinterpret_cast<float2*>(smem + 2 * G::STAGE_BYTES + 2 * G::TILE * (int)sizeof(float));  // [wave][RES]
 #pragma unroll
     for (int kt = 0; kt < NRT; ++kt) {
         col[kt] += __shfl_xor(col[kt], 32);

@@ -203,6 +203,40 @@ def test_score_fp32_not_finite(lemo, what, S, H, d, causal):
         np.testing.assert_allclose(got.cpu().numpy(), want.numpy(), rtol=2e-3, atol=1e-6, equal_nan=True)
 
 
+@pytest.mark.parametrize("small", ["Q", "K", "some of Q", "some of K"])
+@pytest.mark.parametrize("by", [1e-37, 1e-41])
+@pytest.mark.parametrize("S,H,d,causal", [(40, 1, 64, True), (333, 3, 64, True), (333, 2, 64, False), (1500, 34, 64, True), (65, 2, 128, True), (200, 2, 128, False)])
+def test_score_fp32_small_operands(lemo, S, H, d, causal, by, small):
+    """Values below 2^-110 do not fit the parts of a split; against very large ones on the other side the logits are ordinary.
+    binary32 logits within 16 (2^-24 of them each, times the roundings of a sum of d) leave the column sums 2^-20."""
+    say(f"[score] fp32 {small} times {by}, S={S} H={H} d={d} causal={causal}")
+    gen = torch.Generator().manual_seed(S + d)
+    Q, K = (torch.randn((S, H, d), generator=gen, dtype=torch.float64) for _ in range(2))
+    tiny, huge = (Q, K) if "Q" in small else (K, Q)
+    if "some" in small:  # one element of a few rows, the one that meets large values
+        tiny[..., 9] = 0.0
+        tiny[::7, :, 9] = 5.0 * by
+        huge[..., 9] = torch.randn((S, H), generator=gen, dtype=torch.float64) * 1e36
+        if by < 1e-40:
+            tiny[::7, :, 9] *= 8e3
+            huge[..., 9] *= 10
+    else:
+        tiny *= by
+        huge *= 1e37
+        if by < 1e-40:
+            huge *= 5
+            tiny *= 1e3
+    Q, K = Q.float(), K.float()
+    _, col, dg = run_score(lemo, Q, K, 128, 1 if causal else 0)
+    x = torch.einsum("ihd,jhd->hij", Q.double(), K.double()) / math.sqrt(d)
+    assert 0.3 < x.abs().max() < 24
+    if causal:
+        x.masked_fill_(torch.ones(S, S, dtype=torch.bool).triu(1), -math.inf)
+    p = torch.softmax(x, dim=2)
+    for got, want in ((col, p.sum(1).numpy()), (dg, p.diagonal(dim1=1, dim2=2).numpy())):
+        assert np.linalg.norm(got - want) <= 2.0 ** -20 * np.linalg.norm(want)
+
+
 @pytest.mark.parametrize("dominant", [450, 690, 3])
 def test_score_reference_overflow_is_repaired(lemo, dominant):
     """Sweep 1 freezes its reference maximum after the first stage of keys; a key far later whose logit exceeds that
