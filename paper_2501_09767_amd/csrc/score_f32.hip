@@ -439,9 +439,9 @@ __global__ __launch_bounds__(SC_THREADS, (Geo<float, D, NRT, KS>::MIN_WG)) void 
         stage_settle();
     }
     col[NRT - 1] += colsum_tile(carry, carry_nl, c2);
-    bool bad = false;
+    bool bad = false;  // (the zeros that fill up the last block aside: a normaliser far below 0 takes them past all limits)
 #pragma unroll
-    for (int kt = 0; kt < NRT; ++kt) bad |= !isfinite(col[kt]);
+    for (int kt = 0; kt < NRT; ++kt) bad |= kw0 + kt * 32 + l32 < kend && !isfinite(col[kt]);
     // (every wave is past its last read of the stages)
     if (whole || !__syncthreads_or(bad)) break;
     whole = true;

@@ -237,6 +237,26 @@ def test_score_fp32_small_operands(lemo, S, H, d, causal, by, small):
         assert np.linalg.norm(got - want) <= 2.0 ** -20 * np.linalg.norm(want)
 
 
+@pytest.mark.parametrize("H,d", [(2, 64), (200, 64), (2, 128)])
+def test_score_fp32_what_fills_the_last_block_is_not_looked_at(lemo, H, d):
+    """Every logit near -350: against the normaliser, the zeros that fill up the last block of keys overflow, which must not send
+    the block's real keys through binary32 MFMAs.  The last 20 keys repeat the first 20, in products that cancel: what binary32 rounds
+    of those shows in the sums (3e-3), and both sets have to come from the same products (sums of another order: 1e-6)."""
+    say(f"[score] fp32 last block, H={H} d={d}")
+    S = 148
+    gen = torch.Generator().manual_seed(d)
+    Q, K = (torch.randn((S, H, d), generator=gen) for _ in range(2))
+    Q[..., 0] = 1000.0 + 100.0 * Q[..., 0]
+    Q[..., 1] = Q[..., 0]
+    K[..., 0] = 1000.0 + 100.0 * K[..., 0]
+    K[..., 1] = -K[..., 0]
+    Q[..., 2], K[..., 2] = 100.0, -3.5 * math.sqrt(d)
+    K[128:] = K[:20]
+    _, col, _ = run_score(lemo, Q, K, 128, 0)
+    assert np.isfinite(col).all()
+    np.testing.assert_allclose(col[:, 128:], col[:, :20], rtol=1e-6)
+
+
 @pytest.mark.parametrize("dominant", [450, 690, 3])
 def test_score_reference_overflow_is_repaired(lemo, dominant):
     """Sweep 1 freezes its reference maximum after the first stage of keys; a key far later whose logit exceeds that
