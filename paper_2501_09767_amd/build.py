@@ -51,6 +51,7 @@ def build_native() -> str:
     tmp = NATIVE + f".tmp{os.getpid()}"
     libs = cpp_extension.library_paths()
     cmd = [os.environ.get("CXX", "g++"), "-O2", "-std=c++17", "-fPIC", "-shared", "-Wall", f"-D_GLIBCXX_USE_CXX11_ABI={int(torch.compiled_with_cxx11_abi())}",
+           f'-DLEMO_TORCH_VERSION="{torch.__version__}"',
            "-I" + os.path.join(ROOT, "include"), "-I" + sysconfig.get_paths()["include"], *("-isystem" + p for p in cpp_extension.include_paths()),
            os.path.join(CSRC, "native.cpp"), "-o", tmp, "-L" + HERE, "-l:liblemo_hip.so", "-Wl,-rpath,$ORIGIN",
            *("-L" + p for p in libs), *("-Wl,-rpath," + p for p in libs), "-lc10", "-ltorch_cpu", "-ltorch_python"]

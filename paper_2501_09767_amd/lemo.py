@@ -1,4 +1,5 @@
-"""Thin binding over the C-ABI HIP library (include/lemo.h).  Argument marshalling only.
+"""Thin binding over the C-ABI HIP library (include/lemo.h).  Argument marshalling only, of the most frequent calls in native code
+(csrc/native.cpp) where they are plain.
 
 Every function takes torch tensors that live on the GPU, passes their ``data_ptr()`` and the current
 HIP stream to the library call of the same name, and raises ``LemoError`` on a negative return code.
@@ -11,6 +12,7 @@ import ctypes
 import importlib.machinery
 import importlib.util
 import os
+import warnings
 from typing import Optional
 
 import torch
@@ -132,15 +134,26 @@ def _stream():
     return ctypes.c_void_p(_raw_stream(torch.cuda.current_device()))
 
 
+class _NoNative:
+    """In the place of the native module: every call goes the long way."""
+
+    def __getattr__(self, name):
+        return lambda *args: None
+
+
 def _load_native():
     # csrc/native.cpp: the calls that a layer makes over and over, in the plain case, without the steps in Python below; anything
     # else it leaves to them (it answers None and has done nothing).  backward of a small binary32 layer, three calls: 22 us
-    # enqueued from Python, 12 so.
-    if not os.path.exists(NATIVE_PATH):
-        raise ImportError(f"{NATIVE_PATH} is missing: build it first (python -m paper_2501_09767_amd.build).")
-    loader = importlib.machinery.ExtensionFileLoader("lemo_native", NATIVE_PATH)
-    module = importlib.util.module_from_spec(importlib.util.spec_from_file_location("lemo_native", NATIVE_PATH, loader=loader))
-    loader.exec_module(module)
+    # enqueued from Python, 9.6 so.  It is bound to the torch it was built with; the steps in Python need liblemo_hip.so alone.
+    try:
+        loader = importlib.machinery.ExtensionFileLoader("lemo_native", NATIVE_PATH)
+        module = importlib.util.module_from_spec(importlib.util.spec_from_file_location("lemo_native", NATIVE_PATH, loader=loader))
+        loader.exec_module(module)
+        if module.torch_version != torch.__version__:
+            raise ImportError(f"built with torch {module.torch_version}, not {torch.__version__}")
+    except ImportError as e:
+        warnings.warn(f"{NATIVE_PATH} is not used ({e}): calls are marshalled in Python.  python -m paper_2501_09767_amd.build makes it.", RuntimeWarning)
+        return _NoNative()
     if _raw_stream is not None:
         module.set_stream_source(torch.cuda.current_device, _raw_stream)
     return module

@@ -1,4 +1,9 @@
 """The binding's native marshalling takes the plain case of a call only, and then does what the steps in Python do."""
+import os
+import shutil
+import subprocess
+import sys
+
 import numpy as np
 import pytest
 import torch
@@ -24,6 +29,42 @@ def test_what_is_not_plain_is_left_to_python():
         lemo.lemo_gather_gemm(t, None, t, Y=t)
     with pytest.raises(TypeError):
         lemo._native.set_stream_source(1)
+
+
+@pytest.mark.parametrize("native", ["missing", "no library", "of another torch"])
+def test_binding_without_its_native_part(tmp_path, native):
+    """The steps in Python need the HIP library and nothing else: where the native part cannot be used, they are taken."""
+    home = os.path.dirname(lemo.__file__)
+    package = tmp_path / "paper_2501_09767_amd"
+    package.mkdir()
+    for name in ("__init__.py", "lemo.py", "liblemo_hip.so", "lemo_native.so"):
+        shutil.copy(os.path.join(home, name), package / name)
+    if native == "missing":
+        (package / "lemo_native.so").unlink()
+    elif native == "no library":
+        (package / "lemo_native.so").write_bytes(b"not an object file")
+    code = """
+import warnings
+import torch
+if %r: torch.__version__ = type(torch.__version__)("1.13.1+cu117")
+with warnings.catch_warnings(record=True) as said:
+    warnings.simplefilter("always")
+    from paper_2501_09767_amd import lemo
+assert any("lemo_native.so" in str(w.message) for w in said), said
+assert lemo._native.gather_gemm(None, None, None, None, None, None) is None
+assert lemo.lemo_kept_count(1000, 128, 64) == 500
+t = torch.ones(8, 8)
+for f in (lambda: lemo.lemo_gather_gemm(t, None, t, Y=t), lambda: lemo.lemo_score_segments(t, t, 8), lambda: lemo.lemo_select_topk(t, 8, 4), lambda: lemo.lemo_scatter_grad(t, t, t),
+          lambda: lemo.lemo_gather_gemm_add(t, None, t, t, None), lambda: lemo.lemo_gather_gemm_dx(t, t, t, None), lambda: lemo.lemo_gather_gemm_dw(t, t, None)):
+    try:
+        f()
+    except ValueError as e:
+        assert "GPU" in str(e), e
+    else:
+        raise AssertionError("not refused")
+""" % (native == "of another torch")
+    r = subprocess.run([sys.executable, "-c", code], cwd=tmp_path, capture_output=True, text=True, env={**os.environ, "PYTHONPATH": str(tmp_path)})
+    assert r.returncode == 0, r.stderr
 
 
 def calls():
