@@ -158,7 +158,7 @@ PyObject* kept_attention(PyObject* const* a) {  // Q K V kept_idx flags scale O 
     const lemo_dtype_t dt = dtype(Q);
     need(K.size(0) == S && K.size(2) == d && K.scalar_type() == Q.scalar_type() && V.sizes() == K.sizes() && V.scalar_type() == K.scalar_type());
     const int64_t M = a[8] != Py_None ? whole(a[8]) : kept ? kept->numel() : S;
-    need(M > 0 && O.scalar_type() == Q.scalar_type() && O.size(0) >= M && O.size(1) == H && O.size(2) == d);
+    need(M > 0 && (!kept || kept->numel() >= M) && O.scalar_type() == Q.scalar_type() && O.size(0) >= M && O.size(1) == H && O.size(2) == d);
     const Bytes ws = workspace(a[7]);
     const int32_t flags = whole32(a[4]), h = size32(H), hkv = size32(K.size(1)), dd = size32(d);
     const float scale = real(a[5]);
@@ -177,7 +177,7 @@ PyObject* gather_gemm(PyObject* const* a) {  // X kept_idx W bias Y M
     const int64_t S = X.size(0), C = X.size(1), N = W.size(0);
     need(W.size(1) == C && W.scalar_type() == X.scalar_type());
     const int64_t M = a[5] != Py_None ? whole(a[5]) : kept ? kept->numel() : S;
-    need(M > 0 && Y.scalar_type() == X.scalar_type() && Y.size(0) >= M && Y.size(1) == N);
+    need(M > 0 && (!kept || kept->numel() >= M) && Y.scalar_type() == X.scalar_type() && Y.size(0) >= M && Y.size(1) == N);
     const void* b = bias_of(a[3], X, N);
     const int32_t* ki = rows(kept);
     const int32_t c = size32(C), n = size32(N);

@@ -439,7 +439,10 @@ def lemo_gather_gemm(X: torch.Tensor, kept_idx: Optional[torch.Tensor], W: torch
     if kept_idx is not None:
         if kept_idx.dtype != torch.int32 or kept_idx.dim() != 1 or not kept_idx.is_contiguous():
             raise ValueError("kept_idx must be contiguous int32 [M]")
-        M = kept_idx.numel() if M is None else M
+        if M is None:
+            M = kept_idx.numel()
+        elif kept_idx.numel() < M:
+            raise ValueError("kept_idx is shorter than M")
     elif M is None:
         M = S
     if bias is not None and (bias.dtype != X.dtype or tuple(bias.shape) != (N,) or not bias.is_contiguous()):
@@ -507,7 +510,10 @@ def lemo_kept_attention(Q: torch.Tensor, K: torch.Tensor, V: torch.Tensor, kept_
     if kept_idx is not None:
         if kept_idx.dtype != torch.int32 or kept_idx.dim() != 1 or not kept_idx.is_contiguous():
             raise ValueError("kept_idx must be contiguous int32 [M]")
-        M = kept_idx.numel() if M is None else M
+        if M is None:
+            M = kept_idx.numel()
+        elif kept_idx.numel() < M:
+            raise ValueError("kept_idx is shorter than M")
     elif M is None:
         M = S
     if O is None:

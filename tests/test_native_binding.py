@@ -122,6 +122,27 @@ def test_same_bits_either_way(monkeypatch, name):
     assert taken == [0, 0] and torch.equal(fast, slow) and torch.equal(other, slow)
 
 
+def more_rows_than_listed(o):
+    """M beyond the end of the list of rows, with room for the result (and so for the reads, if a call went through)."""
+    listed = torch.zeros(o["S"], dtype=torch.int32, device="cuda")[:o["M"]]
+    M, new = o["M"] + 1, lambda *s: torch.zeros(*s, dtype=torch.bfloat16, device="cuda")
+    H, d = o["Q"].shape[1:]
+    return [lambda: lemo.lemo_gather_gemm(o["X"], listed, o["W"], None, new(M, o["N"]), M), lambda: lemo.lemo_gather_gemm(o["X"], listed, o["W"], M=M),
+            lambda: lemo.lemo_gather_gemm_add(o["X"], listed, o["W"], new(o["S"], o["N"]), None, None, M),
+            lambda: lemo.lemo_kept_attention(o["Q"], o["K"], o["K"], listed, 1, 0.0, new(M, H, d), o["ws"], M), lambda: lemo.lemo_kept_attention(o["Q"], o["K"], o["K"], listed, M=M)]
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("native", [True, False])
+def test_more_rows_than_listed_are_refused(monkeypatch, native):
+    _, o = calls()
+    if not native:
+        monkeypatch.setattr(lemo, "_native", Refusing())
+    for f in more_rows_than_listed(o):
+        with pytest.raises(ValueError, match="shorter than M"):
+            f()
+
+
 @pytest.mark.gpu
 def test_same_refusals_either_way(monkeypatch):
     _, o = calls()
