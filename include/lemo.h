@@ -30,8 +30,9 @@
  *     the stream has finished; two calls in flight at once need two workspaces.
  *   - The calls only launch kernels (no allocation, no memset, no host synchronisation), so a stream
  *     that carries them may be captured into a HIP graph -- once each entry point has been called
- *     for its dtype and head size outside a capture: the first such call raises the dynamic-LDS
- *     limit of its kernels (hipFuncSetAttribute), which is not a stream operation.
+ *     for its dtype and head size outside a capture, at any size but none (M == 0): the first such
+ *     call raises the dynamic-LDS limits of all the kernels that calls of that dtype and head size
+ *     may take (hipFuncSetAttribute), which is not a stream operation.
  */
 #ifndef LEMO_H
 #define LEMO_H

@@ -21,7 +21,6 @@
 // 9856, all with 32 heads.)
 // P is rounded to bf16 for the second product (as in every flash-attention kernel); the normaliser is summed from the
 // unrounded values.
-#include <mutex>
 #include <type_traits>
 
 #include "lemo_common.hpp"
@@ -752,14 +751,26 @@ __global__ __launch_bounds__(AP_THREADS, 1) void kept_attention_pipe_kernel(Attn
     }
 }
 
+constexpr int at_lds(int ks) { return ks > 1 && share_lds<AT_NQ, AGeo::D>(AT_WAVES) > AGeo::LDS ? share_lds<AT_NQ, AGeo::D>(AT_WAVES) : AGeo::LDS; }
+
+static int prepare_attn(int d) {
+    if (d == 64) {
+        static const int err = raise_lds_limits({{reinterpret_cast<const void*>(&kept_attention_kernel<1>), at_lds(1)},
+                                                 {reinterpret_cast<const void*>(&kept_attention_kernel<2>), at_lds(2)},
+                                                 {reinterpret_cast<const void*>(&kept_attention_kernel<4>), at_lds(4)}});
+        return err;
+    }
+    static const int err = raise_lds_limits({{reinterpret_cast<const void*>(&kept_attention_pipe_kernel<1, false>), ap_lds(1)},
+                                             {reinterpret_cast<const void*>(&kept_attention_pipe_kernel<2, false>), ap_lds(2)},
+                                             {reinterpret_cast<const void*>(&kept_attention_pipe_kernel<4, false>), ap_lds(4)},
+                                             {reinterpret_cast<const void*>(&kept_attention_pipe_kernel<1, true>), ap_lds(1)},
+                                             {reinterpret_cast<const void*>(&kept_attention_pipe_kernel<2, true>), ap_lds(2)},
+                                             {reinterpret_cast<const void*>(&kept_attention_pipe_kernel<4, true>), ap_lds(4)}});
+    return err;
+}
+
 template <int KS, bool SAME_ROWS>
 static int launch_pipe_rows(AttnParams p, hipStream_t st) {
-    static std::once_flag once;
-    static hipError_t attr_err = hipSuccess;
-    std::call_once(once, [] {
-        attr_err = hipFuncSetAttribute(reinterpret_cast<const void*>(&kept_attention_pipe_kernel<KS, SAME_ROWS>), hipFuncAttributeMaxDynamicSharedMemorySize, ap_lds(KS));
-    });
-    if (attr_err != hipSuccess) return (int)attr_err;
     p.n_qblocks = (p.M + 256 / KS - 1) / (256 / KS);
     // more than 8 heads on a die: about as many blocks together as it has CUs (us with 2 / 4 / 8 / 16 heads together, 128 / 8
     // heads, 1000, 1638, 3277 and 6553 kept tokens in blocks of 256: 79 / 73 / 66 / 68, 150 / 144 / 148 / 151, 418 / 430 / 441 /
@@ -777,18 +788,10 @@ static int launch_pipe(const AttnParams& p, hipStream_t st) {
 
 template <int KS>
 static int launch_waves(AttnParams p, hipStream_t st) {
-    using G = AGeo;
-    constexpr int LDS = KS > 1 && share_lds<AT_NQ, G::D>(AT_WAVES) > G::LDS ? share_lds<AT_NQ, G::D>(AT_WAVES) : G::LDS;
-    static std::once_flag once;
-    static hipError_t attr_err = hipSuccess;
-    std::call_once(once, [] {
-        attr_err = hipFuncSetAttribute(reinterpret_cast<const void*>(&kept_attention_kernel<KS>), hipFuncAttributeMaxDynamicSharedMemorySize, LDS);
-    });
-    if (attr_err != hipSuccess) return (int)attr_err;
     constexpr int BQ = AT_WAVES / KS * 32 * AT_NQ;
     p.n_qblocks = (p.M + BQ - 1) / BQ;
     p.order = head_order(p.H, (p.flags & LEMO_CAUSAL) != 0, 64);  // (the more heads together the better: figures at head_order)
-    hipLaunchKernelGGL((kept_attention_kernel<KS>), dim3((unsigned)(p.H * p.n_qblocks)), dim3(AT_THREADS), LDS, st, p);
+    hipLaunchKernelGGL((kept_attention_kernel<KS>), dim3((unsigned)(p.H * p.n_qblocks)), dim3(AT_THREADS), at_lds(KS), st, p);
     return (int)hipGetLastError();
 }
 
@@ -816,6 +819,8 @@ int launch_kept_attention(const void* Q, const void* K, const void* V, long long
                           long long k_ts, long long k_hs, long long v_ts, long long v_hs, const int* idx, long long M, float c2,
                           unsigned flags, void* O, long long o_ts, long long o_hs, void* workspace, hipStream_t st) {
     if (M == 0) return 0;
+    const int unready = prepare_attn(d);
+    if (unready) return unready;
     AttnParams p{};
     p.Q = static_cast<const uint16_t*>(Q);
     p.K = static_cast<const uint16_t*>(K);

@@ -68,6 +68,13 @@ static int launch_tiles(const GgParams& p, lemo_dtype_t dt, bool add, int layout
     return launch_gather_gemm_mid(p, add, layout, tile, st);
 }
 
+static int prepare_tiles(lemo_dtype_t dt, bool add, int layout) {
+    int rc = prepare_gather_gemm_small(dt, add, layout);
+    if (rc == 0 && dt == LEMO_BF16) rc = prepare_gather_gemm_mid(add, layout);
+    if (rc == 0 && dt == LEMO_BF16) rc = prepare_gather_gemm_large(add, layout);
+    return rc;
+}
+
 template <bool ADD, int LAYOUT>
 static int launch_gg(const GgParams& p, lemo_dtype_t dt, hipStream_t st) {
     constexpr long long ROWS = 1ll << 24;  // a launch holds 2^32 threads: more rows than this are taken in turns
@@ -89,6 +96,8 @@ static int launch_gg(const GgParams& p, lemo_dtype_t dt, hipStream_t st) {
         }
         return 0;
     }
+    const int unready = prepare_tiles(dt, ADD, LAYOUT);
+    if (unready) return unready;
     const GgPlan plan = gg_plan(p.M, p.N, p.K, LAYOUT, dt);
     GgParams rest = p;
     if (plan.head_cols > 0) {  // (never binary32)
@@ -133,6 +142,11 @@ int launch_gather_gemm_dx(const void* dY, long long ldy, long long M, const void
     if (M == 0) return 0;
     return launch_gg<true, GG_NN>({dY, W, nullptr, dX, nullptr, oidx, ldy, ldw, lddx, M, out_rows, /*contraction*/ N, /*columns*/ C, 0, 0,
                                    span_bytes(M, ldy, N, LEMO_BF16), 0, span_bytes(out_rows, lddx, C, LEMO_BF16)}, LEMO_BF16, st);
+}
+
+int prepare_gather_gemm_dw(lemo_dtype_t dt) {  // binary32 may also take transposed copies, as rows along the contraction
+    const int rc = prepare_tiles(dt, false, GG_TN);
+    return rc || dt == LEMO_BF16 ? rc : prepare_tiles(dt, false, GG_NT);
 }
 
 // Weight gradient dW[n, c] = sum_m dY[m, n] X[idx[m], c], both operands read as they are stored (contraction-major),

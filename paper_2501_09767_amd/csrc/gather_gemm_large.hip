@@ -21,8 +21,6 @@
 //   weight grad.   8192 x 8192 x 8192: 800 / 987;   9856 x 11008 x 4096: 688 / 869;   3280 x 11008 x 4096: 278 / 357
 // Tried: four waves of 128 x 128 in this scheme (the compiler moves the 256 accumulators about: 987); counters in LDS, written
 // ahead of the wait, in the barriers' place (793).
-#include <mutex>
-
 #include "gather_gemm_regions.hpp"
 
 namespace lemo {
@@ -285,18 +283,24 @@ __global__ __launch_bounds__(RG_THREADS, 1) void gather_gemm_large_kernel(GgPara
 }
 
 template <bool ADD, int LAYOUT>
+static int prepare_large() {
+    static const int err = raise_lds_limits({{reinterpret_cast<const void*>(&gather_gemm_large_kernel<ADD, LAYOUT>), LG_LDS}});
+    return err;
+}
+
+template <bool ADD, int LAYOUT>
 static int launch_large(GgParams p, hipStream_t st) {
-    static std::once_flag once;
-    static hipError_t attr_err = hipSuccess;
-    std::call_once(once, [] {
-        attr_err = hipFuncSetAttribute(reinterpret_cast<const void*>(&gather_gemm_large_kernel<ADD, LAYOUT>), hipFuncAttributeMaxDynamicSharedMemorySize, LG_LDS);
-    });
-    if (attr_err != hipSuccess) return (int)attr_err;
     p.tiles_m = (int)((p.M + LG_BM - 1) / LG_BM);
     p.tiles_n = (p.N + LG_BN - 1) / LG_BN;
     const int per_xcd = (p.tiles_m * p.tiles_n + NUM_XCD - 1) / NUM_XCD;
     hipLaunchKernelGGL((gather_gemm_large_kernel<ADD, LAYOUT>), dim3((unsigned)(per_xcd * NUM_XCD)), dim3(RG_THREADS), LG_LDS, st, p);
     return (int)hipGetLastError();
+}
+
+int prepare_gather_gemm_large(bool add, int layout) {
+    if (layout == GG_TN) return prepare_large<false, GG_TN>();
+    if (layout == GG_NN) return prepare_large<true, GG_NN>();
+    return add ? prepare_large<true, GG_NT>() : prepare_large<false, GG_NT>();
 }
 
 int launch_gather_gemm_large(const GgParams& p, bool add, int layout, hipStream_t st) {

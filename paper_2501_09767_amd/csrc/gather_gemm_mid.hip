@@ -13,8 +13,6 @@
 //   256 x 128  M = 1504: N = K = 4096 55 / 63, N = 4096, K = 11008 149 / 165 (input gradient 149 / 165, weight gradient 159 / 189);
 //              M = 3280, N = K = 4096: 101 / 119
 //   128 x 128  M = 256, N = 11008, K = 4096: 41.5 / 44.4;  M = N = 256 x 4096: 38 / 41;  M = 768, N = 3072, K = 768: 9.4 / 10.7
-#include <mutex>
-
 #include "gather_gemm_regions.hpp"
 
 namespace lemo {
@@ -191,15 +189,16 @@ __global__ __launch_bounds__(RG_THREADS, 1) void gather_gemm_mid_kernel(GgParams
     }
 }
 
+template <bool ADD, int LAYOUT>
+static int prepare_mid() {
+    static const int err = raise_lds_limits({{reinterpret_cast<const void*>(&gather_gemm_mid_kernel<ADD, LAYOUT, 1>), MdGeo<1>::LDS},
+                                             {reinterpret_cast<const void*>(&gather_gemm_mid_kernel<ADD, LAYOUT, 2>), MdGeo<2>::LDS}});
+    return err;
+}
+
 template <bool ADD, int LAYOUT, int RA>
 static int launch_mid(GgParams p, hipStream_t st) {
     using G = MdGeo<RA>;
-    static std::once_flag once;
-    static hipError_t attr_err = hipSuccess;
-    std::call_once(once, [] {
-        attr_err = hipFuncSetAttribute(reinterpret_cast<const void*>(&gather_gemm_mid_kernel<ADD, LAYOUT, RA>), hipFuncAttributeMaxDynamicSharedMemorySize, G::LDS);
-    });
-    if (attr_err != hipSuccess) return (int)attr_err;
     p.tiles_m = (int)((p.M + G::BM - 1) / G::BM);
     p.tiles_n = (p.N + G::BN - 1) / G::BN;
     const int per_xcd = (p.tiles_m * p.tiles_n + NUM_XCD - 1) / NUM_XCD;
@@ -212,6 +211,13 @@ static int launch_mid_form(const GgParams& p, bool add, int layout, hipStream_t 
     if (layout == GG_NN) return launch_mid<true, GG_NN, RA>(p, st);
     return add ? launch_mid<true, GG_NT, RA>(p, st) : launch_mid<false, GG_NT, RA>(p, st);
 }
+
+int prepare_gather_gemm_mid(bool add, int layout) {
+    if (layout == GG_TN) return prepare_mid<false, GG_TN>();
+    if (layout == GG_NN) return prepare_mid<true, GG_NN>();
+    return add ? prepare_mid<true, GG_NT>() : prepare_mid<false, GG_NT>();
+}
+
 int launch_gather_gemm_mid(const GgParams& p, bool add, int layout, GgTile tile, hipStream_t st) {
     return tile == GG_T128 ? launch_mid_form<1>(p, add, layout, st) : launch_mid_form<2>(p, add, layout, st);
 }

@@ -21,8 +21,6 @@
 // Measured beside this (M = 256, N = K = 4096 with 64 x 64 tiles, 17.5 us): a ring of four half-slabs with the loads spread over all
 // MFMAs 21.6 (64-byte row segments halve what an L2 delivers), a ring of two slabs without the registers' lookahead 19.1;
 // 16 x 16 x 32 MFMAs, which pay in the larger tiles, change nothing here (20.6 / 20.9 from HBM).
-#include <mutex>
-
 #include "gather_gemm.hpp"
 
 namespace lemo {
@@ -596,16 +594,26 @@ __global__ __launch_bounds__(SG_THREADS, GW == 4 ? 2 : 1) void gather_gemm_small
     }
 }
 
+template <typename T, bool ADD, int LAYOUT>
+static int prepare_small() {
+    auto limit = [](auto gw, auto wt) {
+        constexpr int GW = decltype(gw)::value, WT = decltype(wt)::value;
+        return LdsLimit{reinterpret_cast<const void*>(&gather_gemm_small_kernel<T, ADD, LAYOUT, GW, WT>), SgGeo<GW, (int)sizeof(T), WT>::LDS};
+    };
+    using I1 = std::integral_constant<int, 1>;
+    using I2 = std::integral_constant<int, 2>;
+    if constexpr (sizeof(T) == 2) {
+        static const int err = raise_lds_limits({limit(I1{}, I2{})});
+        return err;
+    } else {
+        static const int err = raise_lds_limits({limit(I1{}, I1{}), limit(std::integral_constant<int, 4>{}, I2{})});
+        return err;
+    }
+}
+
 template <typename T, bool ADD, int LAYOUT, int GW, int WT>
 static int launch_small(GgParams p, hipStream_t st) {
     using G = SgGeo<GW, (int)sizeof(T), WT>;
-    static std::once_flag once;
-    static hipError_t attr_err = hipSuccess;
-    std::call_once(once, [] {
-        attr_err = hipFuncSetAttribute(reinterpret_cast<const void*>(&gather_gemm_small_kernel<T, ADD, LAYOUT, GW, WT>),
-                                       hipFuncAttributeMaxDynamicSharedMemorySize, G::LDS);
-    });
-    if (attr_err != hipSuccess) return (int)attr_err;
     p.tiles_m = (int)((p.M + G::BM - 1) / G::BM);
     p.tiles_n = (p.N + G::BN - 1) / G::BN;
     const int per_xcd = (p.tiles_m * p.tiles_n + NUM_XCD - 1) / NUM_XCD;
@@ -619,6 +627,18 @@ static int launch_small_form(const GgParams& p, bool add, int layout, hipStream_
     if constexpr (sizeof(T) == 2)
         if (layout == GG_NN) return launch_small<T, true, GG_NN, GW, WT>(p, st);
     return add ? launch_small<T, true, GG_NT, GW, WT>(p, st) : launch_small<T, false, GG_NT, GW, WT>(p, st);
+}
+
+template <typename T>
+static int prepare_small_form(bool add, int layout) {
+    if (layout == GG_TN) return prepare_small<T, false, GG_TN>();
+    if constexpr (sizeof(T) == 2)
+        if (layout == GG_NN) return prepare_small<T, true, GG_NN>();
+    return add ? prepare_small<T, true, GG_NT>() : prepare_small<T, false, GG_NT>();
+}
+
+int prepare_gather_gemm_small(lemo_dtype_t dt, bool add, int layout) {
+    return dt == LEMO_BF16 ? prepare_small_form<bf16_t>(add, layout) : prepare_small_form<float>(add, layout);
 }
 
 int launch_gather_gemm_small(const GgParams& p, lemo_dtype_t dt, bool add, int layout, GgTile tile, hipStream_t st) {

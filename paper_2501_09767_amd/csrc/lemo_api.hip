@@ -452,6 +452,7 @@ int lemo_gather_gemm_dw(const void* dY, int64_t ldy, const void* X, int64_t S, i
     if (Mpad * esz >= (1 << 23) || (int64_t)N * Mpad * esz >= ((int64_t)1 << 32)) return LEMO_ERR_UNSUPPORTED;  // limits of the GEMM on the transposed operands
     const int64_t tiles = (((int64_t)N + 255) / 256) * (((int64_t)C + 255) / 256);
     if (tiles >= (int64_t)1 << 28) return LEMO_ERR_UNSUPPORTED;
+    if (prepare_gather_gemm_dw(dt) != 0) return LEMO_ERR_HIP;
     // binary32 reads its operands where they lie as well; the workspace is for operands beyond the 32-bit offsets, and for
     // results that may lie in an operand's storage (workgroups that are done store while others still read)
     const int64_t dw_bytes = ((int64_t)(N - 1) * lddw + C) * esz;

@@ -4,6 +4,8 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <initializer_list>
+
 #include "lemo.h"
 
 namespace lemo {
@@ -165,6 +167,24 @@ inline bool spans_meet(const void* a, long long a_bytes, const void* b, long lon
     return x < y + (uintptr_t)b_bytes && y < x + (uintptr_t)a_bytes;
 }
 
+// ---- host: dynamic-LDS limits -------------------------------------------------------------------------
+// The limit of a kernel is raised once, which a stream capture cannot hold, and which kernel a call takes depends on its sizes: so
+// an entry point raises the limits of all the kernels that calls of one type and head size may take in the first of them
+// (prepare_...; function-local statics, safe between threads).
+struct LdsLimit { const void* kernel; int bytes; };
+inline int raise_lds_limits(std::initializer_list<LdsLimit> kernels) {
+    for (const LdsLimit& k : kernels) {
+        const hipError_t err = hipFuncSetAttribute(k.kernel, hipFuncAttributeMaxDynamicSharedMemorySize, k.bytes);
+        if (err != hipSuccess) return (int)err;
+    }
+    return 0;
+}
+template <typename... F> int first_error(F... prepare) {
+    int rc = 0;
+    ((rc = rc ? rc : prepare()), ...);
+    return rc;
+}
+
 // ---- parameter blocks -----------------------------------------------------------------------------
 struct ScoreParams {
     const void* Q;
@@ -198,6 +218,7 @@ struct BlockParams {
 
 // kernel launchers (defined next to their kernels; return hipError_t as int)
 int launch_score(const ScoreParams& p, lemo_dtype_t dt, int d, int which, hipStream_t st);  // which: 1 row stats | 2 column sums | 4 head mean
+int prepare_score(lemo_dtype_t dt, int d);  // (launch_score does so itself)
 int launch_score_blocks(const BlockParams& p, lemo_dtype_t dt, int d, int mode, int b, float* score_blocks, float* token_blocks,
                         hipStream_t st);  // mode 0: probabilities (p.lse2 filled), 1: positive logits
 int launch_select(const float* scores, int S, int L, int k, int* kept, hipStream_t st);
@@ -210,6 +231,7 @@ int launch_select_threshold(const float* token_blocks, int S, int b, float t_hos
                             hipStream_t st);
 int launch_gather_gemm_dw(const void* dY, long long ldy, const void* X, long long S, long long ldx, const int* idx, long long M, void* dW,
                           long long lddw, int C, int N, void* workspace, hipStream_t st);
+int prepare_gather_gemm_dw(lemo_dtype_t dt);
 int launch_zero_matrix(void* p, long long pitch, int row_elems, int rows, lemo_dtype_t dt, hipStream_t st);  // pitch in elements
 int launch_kept_attention(const void* Q, const void* K, const void* V, long long S, int H, int H_kv, int d, long long q_ts, long long q_hs,
                           long long k_ts, long long k_hs, long long v_ts, long long v_hs, const int* idx, long long M, float c2,

@@ -22,7 +22,7 @@
 // so the two must run at the same time.  Tiles that need no masking go through a software pipeline:
 // while the MFMA chain of tile n runs, the exp/sum work of tile n-1 (kept in a "carry" accumulator)
 // is issued between the MFMAs; the instruction order is pinned with scheduling-group barriers.
-#include <mutex>
+#include <type_traits>
 
 #include "score_sweeps.hpp"
 
@@ -539,22 +539,25 @@ __global__ __launch_bounds__(HM_THREADS) void head_mean_kernel(const float* __re
     scores[j] = acc / (float)H;
 }
 
+template <typename T, int D, int NRT>
+static int prepare_sweeps() {
+    auto limits = [](auto ks) {
+        constexpr int KS = decltype(ks)::value;
+        using G = Geo<T, D, NRT, KS>;
+        return raise_lds_limits({{reinterpret_cast<const void*>(&rowstats_kernel<T, D, NRT, KS>), G::LDS_ROWSTATS},
+                                 {reinterpret_cast<const void*>(&colsum_kernel<T, D, NRT, KS>), G::LDS_COLSUM}});
+    };
+    static const int err = first_error([&] { return limits(std::integral_constant<int, 1>{}); }, [&] { return limits(std::integral_constant<int, 2>{}); },
+                                       [&] { return limits(std::integral_constant<int, 4>{}); });
+    return err;
+}
+
 // which: bit 0 = sweep 1 (row statistics), bit 1 = sweep 2 (column sums)
 template <typename T, int D, int NRT, int KS>
 static int launch_sweeps(const ScoreParams& p_in, int which, hipStream_t st) {
     using G = Geo<T, D, NRT, KS>;
     ScoreParams p = p_in;
     p.n_query_blocks = (p.S + G::BLOCK - 1) / G::BLOCK;
-    static std::once_flag once;
-    static hipError_t attr_err = hipSuccess;
-    std::call_once(once, [] {  // the kernels use more dynamic LDS than the default limit
-        const void* ks[2] = {reinterpret_cast<const void*>(&rowstats_kernel<T, D, NRT, KS>),
-                             reinterpret_cast<const void*>(&colsum_kernel<T, D, NRT, KS>)};
-        const int bytes[2] = {G::LDS_ROWSTATS, G::LDS_COLSUM};
-        for (int i = 0; i < 2 && attr_err == hipSuccess; ++i)
-            attr_err = hipFuncSetAttribute(ks[i], hipFuncAttributeMaxDynamicSharedMemorySize, bytes[i]);
-    });
-    if (attr_err != hipSuccess) return (int)attr_err;
     const unsigned grid = (unsigned)(p.H * p.n_query_blocks);  // as many key blocks
     if (which & 1) hipLaunchKernelGGL((rowstats_kernel<T, D, NRT, KS>), dim3(grid), dim3(SC_THREADS), G::LDS_ROWSTATS, st, p);
     if (which & 2) hipLaunchKernelGGL((colsum_kernel<T, D, NRT, KS>), dim3(grid), dim3(SC_THREADS), G::LDS_COLSUM, st, p);
@@ -586,12 +589,19 @@ static int launch_sweeps_ks(const ScoreParams& p, long long n, int which, hipStr
     return launch_sweeps<T, D, NRT, 1>(p, which, st);
 }
 
+int prepare_score(lemo_dtype_t dt, int d) {
+    if (dt == LEMO_F32) return prepare_sweeps_f32(d);
+    return d == 128 ? prepare_sweeps<bf16_t, 128, LEMO_NRT_BF16_128>() : prepare_sweeps<bf16_t, 64, 2>();
+}
+
 int launch_score(const ScoreParams& p_in, lemo_dtype_t dt, int d, int which, hipStream_t st) {
     ScoreParams p = p_in;
     p.order = head_order(p.H, (p.flags & LEMO_CAUSAL) != 0, 8);
     int rc = 0;
     const long long blocks256 = (long long)p.H * ((p.S + 255) / 256);
     if (which & 3) {
+        rc = prepare_score(dt, d);
+        if (rc) return rc;
         if (dt == LEMO_BF16 && d == 128) rc = launch_sweeps_ks<bf16_t, 128, LEMO_NRT_BF16_128>(p, blocks256, which, st);
         else if (dt == LEMO_BF16 && d == 64) rc = launch_sweeps_ks<bf16_t, 64, 2>(p, blocks256, which, st);
         else if (dt == LEMO_F32 && (d == 64 || d == 128)) rc = launch_sweeps_f32(p, d, which, st);

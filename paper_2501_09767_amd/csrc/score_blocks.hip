@@ -17,7 +17,6 @@
 // is one software pipeline three heads deep: head h in registers (MFMA fragments, refilled in place as soon as an
 // MFMA has used them), head h + 1 complete in one LDS stage, head h + 2 arriving in the other through LDS-direct
 // loads, one barrier per head.
-#include <mutex>
 #include <type_traits>
 
 #include "score_blocks.hpp"
@@ -285,6 +284,13 @@ __global__ __launch_bounds__(256) void block_reduce_kernel(const float* __restri
     if (tid == 0) token_blocks[n] = part[0];
 }
 
+template <typename T, int D>
+static int prepare_tilemax() {
+    static const int err = raise_lds_limits({{reinterpret_cast<const void*>(&tilemax_kernel<T, D, 0>), BGeo<T, D>::LDS},
+                                             {reinterpret_cast<const void*>(&tilemax_kernel<T, D, 1>), BGeo<T, D>::LDS}});
+    return err;
+}
+
 template <typename T, int D, int MODE>
 static int launch_tilemax_t(BlockParams p, hipStream_t st) {
     using G = BGeo<T, D>;
@@ -304,13 +310,6 @@ static int launch_tilemax_t(BlockParams p, hipStream_t st) {
         p.count -= rest;
     }
     p.per_xcd = (p.count + NUM_XCD - 1) / NUM_XCD;
-    static std::once_flag once;
-    static hipError_t attr_err = hipSuccess;
-    std::call_once(once, [] {
-        attr_err = hipFuncSetAttribute(reinterpret_cast<const void*>(&tilemax_kernel<T, D, MODE>),
-                                       hipFuncAttributeMaxDynamicSharedMemorySize, G::LDS);
-    });
-    if (attr_err != hipSuccess) return (int)attr_err;
     if (p.count > 0) hipLaunchKernelGGL((tilemax_kernel<T, D, MODE>), dim3((unsigned)(p.per_xcd * NUM_XCD)), dim3(G::THREADS), G::LDS, st, p);
     const hipError_t err = hipGetLastError();
     if (err != hipSuccess || rest == 0) return (int)err;
@@ -322,7 +321,11 @@ int launch_score_blocks(const BlockParams& p_in, lemo_dtype_t dt, int d, int mod
                         hipStream_t st) {
     BlockParams p = p_in;
     p.nt32 = (p.S + 31) / 32;
-    int rc;
+    int rc = prepare_score(dt, d);
+    if (rc) return rc;
+    if (dt == LEMO_BF16) rc = first_error(d == 128 ? prepare_tilemax<bf16_t, 128> : prepare_tilemax<bf16_t, 64>, [=] { return prepare_tilemax_few(d); });
+    else rc = d == 128 ? prepare_tilemax<float, 128>() : prepare_tilemax<float, 64>();
+    if (rc) return rc;
     if (dt == LEMO_BF16 && d == 128) rc = mode ? launch_tilemax_t<bf16_t, 128, 1>(p, st) : launch_tilemax_t<bf16_t, 128, 0>(p, st);
     else if (dt == LEMO_BF16 && d == 64) rc = mode ? launch_tilemax_t<bf16_t, 64, 1>(p, st) : launch_tilemax_t<bf16_t, 64, 0>(p, st);
     else if (dt == LEMO_F32 && d == 128) rc = mode ? launch_tilemax_t<float, 128, 1>(p, st) : launch_tilemax_t<float, 128, 0>(p, st);

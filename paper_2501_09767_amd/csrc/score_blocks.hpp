@@ -33,6 +33,7 @@ __host__ __device__ inline void sb_rectangle(int id, int nt, bool causal, int& t
 }
 
 // Rectangles first .. first + rest - 1 of that order as 64 x 64 quarters (bf16): score_blocks_few.hip
+int prepare_tilemax_few(int d);
 int launch_tilemax_few(const BlockParams& p, int d, int mode, int first, int rest, hipStream_t st);
 
 }  // namespace lemo

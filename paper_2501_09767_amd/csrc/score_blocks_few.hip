@@ -8,7 +8,6 @@
 // time is one walk of all heads whatever their number.
 // What bounds it: the latency of a step (one wave per SIMD: 4 us for the launch, then 2 us per step of loads, 32 reads of LDS,
 // 32 MFMAs and 64 exponentials per lane, overlapped only in parts).
-#include <mutex>
 #include <type_traits>
 
 #include "score_blocks.hpp"
@@ -153,15 +152,17 @@ __global__ __launch_bounds__(256, 1) void tilemax_few_kernel(BlockParams p, int 
     if (lane == 0 && ti < p.nt32 && tj < p.nt32) p.tilemax[(size_t)ti * p.nt32 + tj] = m * p.out_scale;
 }
 
+template <int D>
+static int prepare_few() {
+    static const int err = raise_lds_limits({{reinterpret_cast<const void*>(&tilemax_few_kernel<D, 0>), FGeo<D>::LDS},
+                                             {reinterpret_cast<const void*>(&tilemax_few_kernel<D, 1>), FGeo<D>::LDS}});
+    return err;
+}
+int prepare_tilemax_few(int d) { return d == 128 ? prepare_few<128>() : prepare_few<64>(); }
+
 template <int D, int MODE>
 static int launch_few(const BlockParams& p, int first, int rest, hipStream_t st) {
     using G = FGeo<D>;
-    static std::once_flag once;
-    static hipError_t attr_err = hipSuccess;
-    std::call_once(once, [] {
-        attr_err = hipFuncSetAttribute(reinterpret_cast<const void*>(&tilemax_few_kernel<D, MODE>), hipFuncAttributeMaxDynamicSharedMemorySize, G::LDS);
-    });
-    if (attr_err != hipSuccess) return (int)attr_err;
     const int per_xcd = (4 * rest + NUM_XCD - 1) / NUM_XCD;
     hipLaunchKernelGGL((tilemax_few_kernel<D, MODE>), dim3((unsigned)(per_xcd * NUM_XCD)), dim3(256), G::LDS, st, p, first, rest);
     return (int)hipGetLastError();

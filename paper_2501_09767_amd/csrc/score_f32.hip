@@ -18,8 +18,6 @@
 //
 // A sum that is not finite -- an infinity does not survive the split -- is formed again from binary32 MFMAs before anything is stored;
 // blocks whose logits would feel what small values lose to the split (needs_whole) take those at once.
-#include <mutex>
-
 #include "score_sweeps.hpp"
 
 namespace lemo {
@@ -472,23 +470,25 @@ __global__ __launch_bounds__(SC_THREADS, (Geo<float, D, NRT, KS>::MIN_WG)) void 
 }
 
 template <int D, int NRT, int KS>
+static int prepare_f32() {
+    using G = Geo<float, D, NRT, KS>;
+    static const int err = raise_lds_limits({{reinterpret_cast<const void*>(&rowstats_f32_kernel<D, NRT, KS>), G::LDS_ROWSTATS},
+                                             {reinterpret_cast<const void*>(&colsum_f32_kernel<D, NRT, KS>), G::LDS_COLSUM}});
+    return err;
+}
+
+template <int D, int NRT, int KS>
 static int launch_f32(const ScoreParams& p_in, int which, hipStream_t st) {
     using G = Geo<float, D, NRT, KS>;
     ScoreParams p = p_in;
     p.n_query_blocks = (p.S + G::BLOCK - 1) / G::BLOCK;
-    static std::once_flag once;
-    static hipError_t attr_err = hipSuccess;
-    std::call_once(once, [] {  // the kernels use more dynamic LDS than the default limit
-        attr_err = hipFuncSetAttribute(reinterpret_cast<const void*>(&rowstats_f32_kernel<D, NRT, KS>), hipFuncAttributeMaxDynamicSharedMemorySize, G::LDS_ROWSTATS);
-        if (attr_err == hipSuccess)
-            attr_err = hipFuncSetAttribute(reinterpret_cast<const void*>(&colsum_f32_kernel<D, NRT, KS>), hipFuncAttributeMaxDynamicSharedMemorySize, G::LDS_COLSUM);
-    });
-    if (attr_err != hipSuccess) return (int)attr_err;
     const unsigned grid = (unsigned)(p.H * p.n_query_blocks);  // as many key blocks
     if (which & 1) hipLaunchKernelGGL((rowstats_f32_kernel<D, NRT, KS>), dim3(grid), dim3(SC_THREADS), G::LDS_ROWSTATS, st, p);
     if (which & 2) hipLaunchKernelGGL((colsum_f32_kernel<D, NRT, KS>), dim3(grid), dim3(SC_THREADS), G::LDS_COLSUM, st, p);
     return (int)hipGetLastError();
 }
+
+int prepare_sweeps_f32(int d) { return d == 128 ? prepare_f32<128, 1, 2>() : first_error(prepare_f32<64, 1, 4>, prepare_f32<64, 2, 4>); }
 
 int launch_sweeps_f32(const ScoreParams& p, int d, int which, hipStream_t st) {
     const long long blocks256 = (long long)p.H * ((p.S + 255) / 256);

@@ -221,6 +221,7 @@ __device__ __forceinline__ void read_nl(float (&nl)[16], const float* lbuf, int 
     }
 }
 
+int prepare_sweeps_f32(int d);
 int launch_sweeps_f32(const ScoreParams& p, int d, int which, hipStream_t st);  // score_f32.hip
 
 }  // namespace lemo
