@@ -37,7 +37,6 @@ template <> __device__ __forceinline__ void mma_chunk<float>(f32x16& acc, const 
     acc = __builtin_amdgcn_mfma_f32_32x32x2f32(__uint_as_float(a.w), __uint_as_float(b.w), acc, 0, 0, 0);
 }
 
-
 // Accumulator layout of the 32x32 MFMAs (checked on hardware): register r of lane l is the element in
 //   row = 8*(r/4) + 4*(l/32) + (r%4)   (A-operand row),   col = l % 32   (B-operand row).
 __device__ __forceinline__ int acc_row(int r, int lane) { return 8 * (r >> 2) + 4 * (lane >> 5) + (r & 3); }

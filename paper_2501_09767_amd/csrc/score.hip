@@ -41,9 +41,9 @@ namespace lemo {
 // infinite before it is rescaled, and lse2 comes out non-finite.  A workgroup that finds such a row among its own
 // (normally none does) goes through its keys a second time with the running maximum everywhere, before it stores
 // anything: no second launch, no extra traffic when there is nothing to repair.
-template <typename T, int D, int NRT, int KS>
-__global__ __launch_bounds__(SC_THREADS, (Geo<T, D, NRT, KS>::MIN_WG)) void rowstats_kernel(ScoreParams p) {
-    using G = Geo<T, D, NRT, KS>;
+template <int D, int NRT, int KS>
+__global__ __launch_bounds__(SC_THREADS, (Geo<bf16_t, D, NRT, KS>::MIN_WG)) void rowstats_kernel(ScoreParams p) {
+    using G = Geo<bf16_t, D, NRT, KS>;
     extern __shared__ __attribute__((aligned(16))) char smem[];
 
     int h, qb;
@@ -54,8 +54,8 @@ __global__ __launch_bounds__(SC_THREADS, (Geo<T, D, NRT, KS>::MIN_WG)) void rows
     const int tid = threadIdx.x, lane = tid & 63, half = lane >> 5, l32 = lane & 31;
     // (KS = 1: not made a scalar -- the hot stream then comes out 1 % slower, 22000 tokens, 32 heads, full: 3640 / 3600 us)
     const int wave = KS > 1 ? __builtin_amdgcn_readfirstlane(tid >> 6) : tid >> 6;
-    const T* Qb = static_cast<const T*>(p.Q);
-    const T* Kb = static_cast<const T*>(p.K);
+    const bf16_t* Qb = static_cast<const bf16_t*>(p.Q);
+    const bf16_t* Kb = static_cast<const bf16_t*>(p.K);
     const long long q_off = (long long)h * p.q_hs, k_off = (long long)g * p.k_hs;
     const int S = p.S;
     const float c2 = p.c2;
@@ -77,13 +77,13 @@ __global__ __launch_bounds__(SC_THREADS, (Geo<T, D, NRT, KS>::MIN_WG)) void rows
     const int nstage = (causal ? q_last : S - 1) / G::TILE + 1;
 
     const char* k_head = reinterpret_cast<const char*>(Kb + k_off);  // wave-uniform
-    const int k_row_bytes = (int)p.k_ts * (int)sizeof(T);           // host guarantees < 2^24
+    const int k_row_bytes = (int)p.k_ts * (int)sizeof(bf16_t);           // host guarantees < 2^24
     int st_voff[G::NLOAD];
     stage_offsets<G>(st_voff, k_row_bytes, tid);
     const unsigned lds_w = lds_offset_of(smem) + (unsigned)__builtin_amdgcn_readfirstlane(wave) * 1024u;
 
     if constexpr (KS > 1) {  // the queries pass through the second stage, while the first stage of keys arrives
-        load_resident<G>(reinterpret_cast<const char*>(Qb + q_off), (int)p.q_ts * (int)sizeof(T), q0, S, lds_w + G::STAGE_BYTES, tid);
+        load_resident<G>(reinterpret_cast<const char*>(Qb + q_off), (int)p.q_ts * (int)sizeof(bf16_t), q0, S, lds_w + G::STAGE_BYTES, tid);
         stage_load<G>(st_voff, stage_desc<G>(k_head, k_row_bytes, 0, S, true), lds_w);
         stage_settle();
         __syncthreads();
@@ -161,7 +161,7 @@ __global__ __launch_bounds__(SC_THREADS, (Geo<T, D, NRT, KS>::MIN_WG)) void rows
 #pragma unroll
                     for (int c = 0; c < G::NCH; ++c) {
                         rowstat_frozen_slice<G::NCH>(c, prev, c2, nm[pq], l1[pq], l2[pq]);
-                        mma_chunk<T>(acc, kf[c], qf[qt][c]);  // acc[key row][query col]
+                        mma_chunk<bf16_t>(acc, kf[c], qf[qt][c]);  // acc[key row][query col]
                         if (c == 1) stage_load_slot<G>(st_voff, next_desc, next_lds, ks * NRT + qt, G::SHARE * NRT);
                         if (qt == NRT - 1 && ks + 1 < G::SHARE)
                             kn[c] = *reinterpret_cast<const u32x4*>(&sbuf[G::frag((sub0 + ks + 1) * 32 + l32, c, half)]);
@@ -195,7 +195,7 @@ __global__ __launch_bounds__(SC_THREADS, (Geo<T, D, NRT, KS>::MIN_WG)) void rows
 #pragma unroll
                     for (int c = 0; c < G::NCH; ++c) {
                         rowstat_slice<G::NCH>(c, prev, c2, m[pq], st);
-                        mma_chunk<T>(acc, kf[c], qf[qt][c]);
+                        mma_chunk<bf16_t>(acc, kf[c], qf[qt][c]);
                         if (qt == NRT - 1 && ks + 1 < G::SHARE)
                             kn[c] = *reinterpret_cast<const u32x4*>(&sbuf[G::frag((sub0 + ks + 1) * 32 + l32, c, half)]);
                         slot_fence();
@@ -226,7 +226,7 @@ __global__ __launch_bounds__(SC_THREADS, (Geo<T, D, NRT, KS>::MIN_WG)) void rows
                     if (causal && kmin > qmin + 31) continue;  // every key lies after every query
                     f32x16 acc = {0};
 #pragma unroll
-                    for (int c = 0; c < G::NCH; ++c) mma_chunk<T>(acc, kf[c], qf[qt][c]);
+                    for (int c = 0; c < G::NCH; ++c) mma_chunk<bf16_t>(acc, kf[c], qf[qt][c]);
                     const bool all_allowed = causal ? (kmin + 31 <= qmin) : (kmin + 31 < S);
                     if (!all_allowed) {
                         // key j may be used by query i iff j <= lim(i): i itself under the causal mask, S-1 otherwise
@@ -304,9 +304,9 @@ __global__ __launch_bounds__(SC_THREADS, (Geo<T, D, NRT, KS>::MIN_WG)) void rows
 // Sweep 2: column sums (and the diagonal) of the probabilities, one key block per workgroup.
 // ------------------------------------------------------------------------------------------------
 
-template <typename T, int D, int NRT, int KS>
-__global__ __launch_bounds__(SC_THREADS, (Geo<T, D, NRT, KS>::MIN_WG)) void colsum_kernel(ScoreParams p) {
-    using G = Geo<T, D, NRT, KS>;
+template <int D, int NRT, int KS>
+__global__ __launch_bounds__(SC_THREADS, (Geo<bf16_t, D, NRT, KS>::MIN_WG)) void colsum_kernel(ScoreParams p) {
+    using G = Geo<bf16_t, D, NRT, KS>;
     extern __shared__ __attribute__((aligned(16))) char smem[];
     float* const sLbase = reinterpret_cast<float*>(smem + 2 * G::STAGE_BYTES);
 
@@ -321,8 +321,8 @@ __global__ __launch_bounds__(SC_THREADS, (Geo<T, D, NRT, KS>::MIN_WG)) void cols
     const int g = (int)(((long long)h * p.H_kv) / p.H);
     const int tid = threadIdx.x, lane = tid & 63, half = lane >> 5, l32 = lane & 31;
     const int wave = KS > 1 ? __builtin_amdgcn_readfirstlane(tid >> 6) : tid >> 6;
-    const T* Qb = static_cast<const T*>(p.Q);
-    const T* Kb = static_cast<const T*>(p.K);
+    const bf16_t* Qb = static_cast<const bf16_t*>(p.Q);
+    const bf16_t* Kb = static_cast<const bf16_t*>(p.K);
     const long long q_off = (long long)h * p.q_hs, k_off = (long long)g * p.k_hs;
     const float* lse = p.lse2 + (size_t)h * S;
     const int part = wave % KS, sub0 = part * G::SHARE;  // this wave's share of a stage: subtiles [sub0, sub0 + SHARE)
@@ -347,7 +347,7 @@ __global__ __launch_bounds__(SC_THREADS, (Geo<T, D, NRT, KS>::MIN_WG)) void cols
     const int t_lo = causal ? key0 / G::TILE : 0;
 
     const char* q_head = reinterpret_cast<const char*>(Qb + q_off);  // wave-uniform
-    const int q_row_bytes = (int)p.q_ts * (int)sizeof(T);           // host guarantees < 2^24
+    const int q_row_bytes = (int)p.q_ts * (int)sizeof(bf16_t);           // host guarantees < 2^24
     int st_voff[G::NLOAD];
     stage_offsets<G>(st_voff, q_row_bytes, tid);
     const unsigned lds_w = lds_offset_of(smem) + (unsigned)__builtin_amdgcn_readfirstlane(wave) * 1024u;
@@ -363,7 +363,7 @@ __global__ __launch_bounds__(SC_THREADS, (Geo<T, D, NRT, KS>::MIN_WG)) void cols
     for (int r = 0; r < 16; ++r) carry_nl[r] = -INFINITY;
 
     if constexpr (KS > 1)  // the keys pass through the second stage
-        load_resident<G>(reinterpret_cast<const char*>(Kb + k_off), (int)p.k_ts * (int)sizeof(T), key0, S, lds_w + G::STAGE_BYTES, tid);
+        load_resident<G>(reinterpret_cast<const char*>(Kb + k_off), (int)p.k_ts * (int)sizeof(bf16_t), key0, S, lds_w + G::STAGE_BYTES, tid);
     stage_load<G>(st_voff, stage_desc<G>(q_head, q_row_bytes, t_hi * G::TILE, S, true), lds_w);
     pre_l = fetch_l(t_hi);
     if (tid < G::TILE) sLbase[tid] = fix_l(t_hi, pre_l);
@@ -416,7 +416,7 @@ __global__ __launch_bounds__(SC_THREADS, (Geo<T, D, NRT, KS>::MIN_WG)) void cols
                     for (int c = 0; c < G::NCH; ++c) {
                         if (kt == 0) colsum_slice<G::NCH>(c, prev, carry_nl, c2, s1[pk], s2[pk]);  // the carried tile has its own rows
                         else colsum_slice<G::NCH>(c, prev, nl, c2, s1[pk], s2[pk]);
-                        mma_chunk<T>(acc, qf[c], kf[kt][c]);  // acc[query row][key col]
+                        mma_chunk<bf16_t>(acc, qf[c], kf[kt][c]);  // acc[query row][key col]
                         if (c == 1) stage_load_slot<G>(st_voff, next_desc, next_lds, qs * NRT + kt, G::SHARE * NRT);
                         if (kt == NRT - 1 && qs + 1 < G::SHARE) {
                             qn[c] = *reinterpret_cast<const u32x4*>(&sbuf[G::frag((sub0 + qs + 1) * 32 + l32, c, half)]);
@@ -461,7 +461,7 @@ __global__ __launch_bounds__(SC_THREADS, (Geo<T, D, NRT, KS>::MIN_WG)) void cols
                     if (causal && qmin + 31 < kmin) continue;  // every query lies before every key
                     f32x16 acc = {0};
 #pragma unroll
-                    for (int c = 0; c < G::NCH; ++c) mma_chunk<T>(acc, qf[c], kf[kt][c]);
+                    for (int c = 0; c < G::NCH; ++c) mma_chunk<bf16_t>(acc, qf[c], kf[kt][c]);
                     if (qmin > kmin + 31 || qmin + 31 < kmin) {  // off the diagonal: nothing to mask, no self term
                         col[kt] += colsum_tile(acc, nl, c2);
                     } else {
@@ -539,13 +539,13 @@ __global__ __launch_bounds__(HM_THREADS) void head_mean_kernel(const float* __re
     scores[j] = acc / (float)H;
 }
 
-template <typename T, int D, int NRT>
+template <int D, int NRT>
 static int prepare_sweeps() {
     auto limits = [](auto ks) {
         constexpr int KS = decltype(ks)::value;
-        using G = Geo<T, D, NRT, KS>;
-        return raise_lds_limits({{reinterpret_cast<const void*>(&rowstats_kernel<T, D, NRT, KS>), G::LDS_ROWSTATS},
-                                 {reinterpret_cast<const void*>(&colsum_kernel<T, D, NRT, KS>), G::LDS_COLSUM}});
+        using G = Geo<bf16_t, D, NRT, KS>;
+        return raise_lds_limits({{reinterpret_cast<const void*>(&rowstats_kernel<D, NRT, KS>), G::LDS_ROWSTATS},
+                                 {reinterpret_cast<const void*>(&colsum_kernel<D, NRT, KS>), G::LDS_COLSUM}});
     };
     static const int err = first_error([&] { return limits(std::integral_constant<int, 1>{}); }, [&] { return limits(std::integral_constant<int, 2>{}); },
                                        [&] { return limits(std::integral_constant<int, 4>{}); });
@@ -553,14 +553,14 @@ static int prepare_sweeps() {
 }
 
 // which: bit 0 = sweep 1 (row statistics), bit 1 = sweep 2 (column sums)
-template <typename T, int D, int NRT, int KS>
+template <int D, int NRT, int KS>
 static int launch_sweeps(const ScoreParams& p_in, int which, hipStream_t st) {
-    using G = Geo<T, D, NRT, KS>;
+    using G = Geo<bf16_t, D, NRT, KS>;
     ScoreParams p = p_in;
     p.n_query_blocks = (p.S + G::BLOCK - 1) / G::BLOCK;
     const unsigned grid = (unsigned)(p.H * p.n_query_blocks);  // as many key blocks
-    if (which & 1) hipLaunchKernelGGL((rowstats_kernel<T, D, NRT, KS>), dim3(grid), dim3(SC_THREADS), G::LDS_ROWSTATS, st, p);
-    if (which & 2) hipLaunchKernelGGL((colsum_kernel<T, D, NRT, KS>), dim3(grid), dim3(SC_THREADS), G::LDS_COLSUM, st, p);
+    if (which & 1) hipLaunchKernelGGL((rowstats_kernel<D, NRT, KS>), dim3(grid), dim3(SC_THREADS), G::LDS_ROWSTATS, st, p);
+    if (which & 2) hipLaunchKernelGGL((colsum_kernel<D, NRT, KS>), dim3(grid), dim3(SC_THREADS), G::LDS_COLSUM, st, p);
     return (int)hipGetLastError();
 }
 
@@ -577,21 +577,21 @@ static int launch_sweeps(const ScoreParams& p_in, int which, hipStream_t st) {
 // 32.3, n = 256 39.5 / 42.4 / 50.7, n = 384 89.5 / 86.2 / 99.8, n = 448 107 / 122 / 133, n = 512 129 / 144 / 170, n = 576 199 / 194 /
 // 213, n = 896 399 / 411 / 485; d = 64: n = 192 23.7 / 24.7 / 22.6, n = 256 30.4 / 30.9 / 35.9, n = 384 66 / 59 / 68, n = 512 88 / 97 /
 // 110, n = 640 123 / 118 / 135, n = 768 190 / 204 / 232, n = 896 272 / 270 / 307).
-template <typename T, int D, int NRT>
+template <int D, int NRT>
 static int launch_sweeps_ks(const ScoreParams& p, long long n, int which, hipStream_t st) {
     if (!(p.flags & LEMO_CAUSAL)) {
-        if (n <= 64 || (D == 64 && n > 128 && n <= 192)) return launch_sweeps<T, D, NRT, 4>(p, which, st);
-        if ((2 * n + 255) / 256 % 2 == 1 && n <= (D > 64 ? 640 : 1024)) return launch_sweeps<T, D, NRT, 2>(p, which, st);
-        return launch_sweeps<T, D, NRT, 1>(p, which, st);
+        if (n <= 64 || (D == 64 && n > 128 && n <= 192)) return launch_sweeps<D, NRT, 4>(p, which, st);
+        if ((2 * n + 255) / 256 % 2 == 1 && n <= (D > 64 ? 640 : 1024)) return launch_sweeps<D, NRT, 2>(p, which, st);
+        return launch_sweeps<D, NRT, 1>(p, which, st);
     }
-    if (n <= (D > 64 ? 128 : 256)) return launch_sweeps<T, D, NRT, 4>(p, which, st);
-    if (n <= (D > 64 ? 640 : 1024)) return launch_sweeps<T, D, NRT, 2>(p, which, st);
-    return launch_sweeps<T, D, NRT, 1>(p, which, st);
+    if (n <= (D > 64 ? 128 : 256)) return launch_sweeps<D, NRT, 4>(p, which, st);
+    if (n <= (D > 64 ? 640 : 1024)) return launch_sweeps<D, NRT, 2>(p, which, st);
+    return launch_sweeps<D, NRT, 1>(p, which, st);
 }
 
 int prepare_score(lemo_dtype_t dt, int d) {
     if (dt == LEMO_F32) return prepare_sweeps_f32(d);
-    return d == 128 ? prepare_sweeps<bf16_t, 128, LEMO_NRT_BF16_128>() : prepare_sweeps<bf16_t, 64, 2>();
+    return d == 128 ? prepare_sweeps<128, LEMO_NRT_BF16_128>() : prepare_sweeps<64, 2>();
 }
 
 int launch_score(const ScoreParams& p_in, lemo_dtype_t dt, int d, int which, hipStream_t st) {
@@ -602,8 +602,8 @@ int launch_score(const ScoreParams& p_in, lemo_dtype_t dt, int d, int which, hip
     if (which & 3) {
         rc = prepare_score(dt, d);
         if (rc) return rc;
-        if (dt == LEMO_BF16 && d == 128) rc = launch_sweeps_ks<bf16_t, 128, LEMO_NRT_BF16_128>(p, blocks256, which, st);
-        else if (dt == LEMO_BF16 && d == 64) rc = launch_sweeps_ks<bf16_t, 64, 2>(p, blocks256, which, st);
+        if (dt == LEMO_BF16 && d == 128) rc = launch_sweeps_ks<128, LEMO_NRT_BF16_128>(p, blocks256, which, st);
+        else if (dt == LEMO_BF16 && d == 64) rc = launch_sweeps_ks<64, 2>(p, blocks256, which, st);
         else if (dt == LEMO_F32 && (d == 64 || d == 128)) rc = launch_sweeps_f32(p, d, which, st);
         else return (int)hipErrorInvalidValue;
         if (rc) return rc;
