@@ -82,7 +82,8 @@ def requests(layout, bm, bn, M, N, K, S, lda, ldb, idx):
 
 
 @pytest.mark.parametrize("layout,M,N,K,pad", [("nt", 300, 270, 72, 0), ("nt", 1, 1, 8, 8), ("nt", 257, 513, 200, 16), ("nn", 260, 264, 72, 0),
-                                              ("nn", 300, 512, 200, 8), ("tn", 264, 520, 65, 0), ("tn", 256, 264, 131, 8), ("tn", 8, 8, 1, 0)])
+                                              ("nn", 300, 512, 200, 8), ("tn", 264, 520, 65, 0), ("tn", 256, 264, 131, 8), ("tn", 8, 8, 1, 0), ("nt", 130, 40, 1000, 0), ("nt", 517, 300, 256, 8),
+                                              ("nt", 513, 257, 1000, 0), ("nt", 1, 2, 8, 0), ("nt", 300, 512, 4096, 0), ("nt", 256, 256, 64, 24)])
 @pytest.mark.parametrize("bm,bn", [(256, 256), (256, 128), (128, 128)])
 def test_no_request_leaves_its_operand(layout, M, N, K, pad, bm, bn):
     S = (K if layout == "tn" else M) + (0 if layout == "nn" else 9)
@@ -102,24 +103,38 @@ def test_no_request_leaves_its_operand(layout, M, N, K, pad, bm, bn):
 @pytest.mark.parametrize("nk", [1, 2, 3, 6])
 @pytest.mark.parametrize("tn", [False, True])
 def test_regions_are_waited_for_and_free(nk, tn):
-    """256 x 256 tiles.  One wave's order of loads, waits and reads; a barrier makes what every wave has waited for true of all of them."""
+    """256 x 256 tiles.  One wave's order of loads, waits and reads; a barrier makes what every wave has waited for true of all of them.
+    Weight gradient: the kept rows' indices of a slab come through a ring of four entries (the wave's own) into registers, from
+    which the loads of B take them."""
     events = []                                              # loads in issue order: (region, slab), one entry per load
     place = lambda reg, kt: (reg, kt & 1)                    # where a region of a slab lies
-    landed, holds, unread = 0, {}, {}
+    holds, unread = {}, {}
+    entry, tokens = {n: n for n in range(4)}, None           # (the first four entries are waited for before anything else)
 
     def load(reg, kt):
         p = place(reg, kt)
         assert not unread.get(p), (reg, kt, "overwrites fragments still to be read")
+        if tn and reg[0] == "B":
+            assert tokens == kt, (reg, kt, "rows of another slab")
         for _ in range(NLD):
             events.append((p, kt))
         holds[p], unread[p] = kt, True
 
+    def landed(what, published):
+        return max(n for n, e in enumerate(events) if e == what) < published
+
     def read(reg, kt, published):
         p = place(reg, kt)
-        assert holds[p] == kt and max(n for n, e in enumerate(events) if e == (p, kt)) < published, (reg, kt)
+        assert holds[p] == kt and landed((p, kt), published), (reg, kt)
 
-    for reg, kt in [("B0", 0), ("A0", 0), ("B1", 0), ("A1", 0), ("B1", 1), ("A0", 1), ("B0", 1)]:
-        load(reg, kt)
+    def read_tokens(kt, published):
+        nonlocal tokens
+        if tn:
+            assert entry[kt % 4] == kt and (kt < 4 or landed(("tokens", kt), published)), (kt, "indices")
+            tokens = kt
+
+    for step in (0, ("B0", 0), ("A0", 0), ("B1", 0), ("A1", 0), 1, ("B1", 1), ("A0", 1), ("B0", 1), 2):
+        load(*step) if isinstance(step, tuple) else read_tokens(step, 0)
     published = len(events) - 5 * NLD
     late = []                                                # read in the quarter before: awaited by the next barrier but one
     for reg in ("B0", "A0"):
@@ -133,10 +148,14 @@ def test_regions_are_waited_for_and_free(nk, tn):
             for p in done:
                 unread[p] = False
             if tn and q2[0] == "A0":
+                assert entry[kt % 4] == kt                   # (its indices were read three slabs ago)
                 events.append(("tokens", kt + 4))
+                entry[kt % 4] = kt + 4
             for reg, s in loads:
                 load(reg, s)
             read(*q1, published)
+            if q2[0] == "A0":
+                read_tokens(kt + 3, published)
             read(*q2, published)
             # at the next barrier the first quarter's reads are awaited, the second's only at the one after
             unread[place(*q1)] = False

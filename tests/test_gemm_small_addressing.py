@@ -1,4 +1,4 @@
-"""Host model of the loads and LDS positions of the selective-load GEMM on 128 x 128, 64 x 64 and 32 x 32 tiles (CPU only).
+"""Host model of the loads and LDS positions of the selective-load GEMM on 64 x 64 tiles (bf16), 128 x 128 and 32 x 32 ones (binary32) (CPU only).
 
 The kernel fills its slabs with LDS-direct loads: unit u of an operand's slab (16 bytes) goes to LDS bytes [16 u, 16 u + 16),
 and the lane that asks for it chooses which piece of which row that is.  The range check of the buffer descriptor sees the
@@ -29,10 +29,10 @@ class Geo:
             return 0
         if self.esz == 4:
             return ((r >> 2) & 1) << 3
-        return (r & 3) << 2 if self.gw == 4 else ((r >> 1) & 1) << 2
+        return ((r >> 1) & 1) << 2
 
 
-SHAPES = [(4, 2, 2), (1, 2, 2), (4, 4, 2), (1, 4, 1)]
+SHAPES = [(1, 2, 2), (4, 4, 2), (1, 4, 1)]
 
 
 @pytest.mark.parametrize("gw,esz,wt", SHAPES)
@@ -137,3 +137,42 @@ def test_no_request_leaves_its_operand(gw, esz, wt, layout, M, N, K, pad):
             assert voff + 16 <= size and base + voff + soff == row * pitch[op] + byte, (op, row, byte)
         if not wanted:
             assert voff >= size, (op, row, byte)          # arrives as zeros
+
+
+def test_every_row_and_column_is_measured_once():
+    """128 x 128 tiles, binary32: a wave follows the largest operand of its tile 0 of the rows and of the columns; wave (m, n) takes its
+    row tiles in the order n, 1 - n and its column tiles in the order m, 1 - m."""
+    waves = [(m, n) for m in range(2) for n in range(2)]
+    assert sorted((m * 2 + (0 ^ n)) * 32 for m, n in waves) == sorted((n * 2 + (0 ^ m)) * 32 for m, n in waves) == [0, 32, 64, 96]
+    sums = sorted(((m * 2 + (i ^ n)) * 32, (n * 2 + (j ^ m)) * 32) for m, n in waves for i in range(2) for j in range(2))
+    assert sums == [(r, c) for r in range(0, 128, 32) for c in range(0, 128, 32)]
+
+
+@pytest.mark.parametrize("nk", [1, 2, 3, 6])
+def test_second_look_waits_for_its_slabs(nk):
+    """128 x 128 tiles, binary32: the pass over all slabs that forms sums again keeps one slab on its way behind the one it reads; the
+    indices of the kept rows (weight gradient) come two slabs ahead, into a ring of four entries."""
+    stage, entry, on_the_way, reading = {}, {}, [], None
+
+    def issue_tokens(kt):
+        entry[kt % 4] = kt
+        on_the_way.append(("tokens", kt))
+
+    def load(kt):
+        assert entry[kt % 4] == kt and ("tokens", kt) not in on_the_way
+        assert reading is None or reading % 2 != kt % 2       # what is read at the same time lies in the other stage
+        stage[kt % 2] = kt
+        on_the_way.append(("slab", kt))
+        issue_tokens(kt + 2)
+
+    issue_tokens(0)
+    issue_tokens(1)
+    on_the_way.clear()                                        # waited for, then everyone's barrier
+    load(0)
+    for kt in range(nk):
+        on_the_way.clear()
+        reading = None                                        # everyone has read the slab before
+        assert stage[kt % 2] == kt
+        reading = kt
+        load(kt + 1)
+        assert stage[kt % 2] == kt and ("slab", kt) not in on_the_way
