@@ -15,7 +15,8 @@
 //           249, weight gradient 8192 x 2048 of 300 tokens 95 / 78; error against 64 bits 1.1e-6 / 1.0e-6, 5.7e-7 / 4.9e-7, 9.9e-7 /
 //           8.6e-7, 3.1e-7 / 2.6e-7.  The first product without the largest operands 770, with the smallest as well, which would spare
 //           form_again its look for them, 825; with many sums of exactly zero (whole numbers, which the chip multiplies faster)
-//           617, with that look 815; one row of small values 1283, all rows 2350, not a number throughout 2218.
+//           617, with that look 815; one row of small values 1283, all rows 2350, not a number throughout 2218.  Sums of one or two
+//           products are nearer to 64 bits from binary32 MFMAs, and take those.
 // Slabs arrive by LDS-direct loads, two per group in flight, and the registers are the third buffer: the MFMA fragments
 // of the next slab are read during the first MFMAs of the current one, which frees its LDS stage for the slab after next.
 // Measured beside this (M = 256, N = K = 4096 with 64 x 64 tiles, 17.5 us): a ring of four half-slabs with the loads spread over all
@@ -27,6 +28,8 @@ namespace lemo {
 
 constexpr int SG_THREADS = 256;
 constexpr int SG_KB = 128;          // bytes of the contraction per slab
+
+constexpr int SPLIT_LEAST = 3;      // terms of a sum from which splits are no further from 64 bits than binary32 MFMAs
 
 // WT = MFMA tiles per wave and direction
 template <int GW, int ESZ, int WT> struct SgGeo {
@@ -51,7 +54,8 @@ template <int GW, int ESZ, int WT> struct SgGeo {
     __device__ static constexpr int kswz(int r) { return WT == 1 ? 0 : ESZ == 4 ? ((r >> 2) & 1) << 3 : ((r >> 1) & 1) << 2; }
 };
 
-template <typename T, bool ADD, int LAYOUT, int GW, int WT>
+// SPLIT: products from three-part splits
+template <typename T, bool ADD, int LAYOUT, int GW, int WT, bool SPLIT>
 __global__ __launch_bounds__(SG_THREADS, GW == 4 ? 2 : 1) void gather_gemm_small_kernel(GgParams p) {
     constexpr bool A_KMAJOR = LAYOUT == GG_TN, B_KMAJOR = LAYOUT != GG_NT;
     constexpr int ESZ = (int)sizeof(T);
@@ -288,7 +292,7 @@ __global__ __launch_bounds__(SG_THREADS, GW == 4 ? 2 : 1) void gather_gemm_small
     drain();
     };
 
-    // The product from three-part splits (binary32, GW = 4).  A slab is two operand chunks of 16 elements; during the 24 MFMAs of one
+    // (SPLIT) The product from three-part splits.  A slab is two operand chunks of 16 elements; during the 24 MFMAs of one
     // chunk the next one's four operand tiles are split, pair by pair, and the one after that is read.  So slab it has left LDS when
     // its MFMAs begin: its stage is asked for again at once, with one barrier per slab, and has a slab's time to fill.
     auto split_product = [&]() {
@@ -475,8 +479,8 @@ __global__ __launch_bounds__(SG_THREADS, GW == 4 ? 2 : 1) void gather_gemm_small
 #pragma unroll
                 for (int r = 0; r < 16; ++r) acc[i][j][r] = again[i][j] >> r & 1 ? sum[i][j][r] : acc[i][j][r];
     };
-    if constexpr (ESZ == 4 && GW == 4) {
-        static_assert(WT == 2 && 2 * NLD == 8, "four operand tiles, a load per three MFMAs");
+    if constexpr (SPLIT) {
+        static_assert(ESZ == 4 && GW == 4 && WT == 2 && 2 * NLD == 8, "four operand tiles, a load per three MFMAs");
         split_product();
         // (an infinity does not survive the split: the sum is then not a number)
         float probe = 0.f, low = INFINITY;
@@ -596,37 +600,37 @@ __global__ __launch_bounds__(SG_THREADS, GW == 4 ? 2 : 1) void gather_gemm_small
 
 template <typename T, bool ADD, int LAYOUT>
 static int prepare_small() {
-    auto limit = [](auto gw, auto wt) {
-        constexpr int GW = decltype(gw)::value, WT = decltype(wt)::value;
-        return LdsLimit{reinterpret_cast<const void*>(&gather_gemm_small_kernel<T, ADD, LAYOUT, GW, WT>), SgGeo<GW, (int)sizeof(T), WT>::LDS};
-    };
-    using I1 = std::integral_constant<int, 1>;
-    using I2 = std::integral_constant<int, 2>;
-    if constexpr (sizeof(T) == 2) {
-        static const int err = raise_lds_limits({limit(I1{}, I2{})});
+    constexpr int ESZ = (int)sizeof(T);
+    if constexpr (ESZ == 2) {
+        static const int err = raise_lds_limits({{reinterpret_cast<const void*>(&gather_gemm_small_kernel<T, ADD, LAYOUT, 1, 2, false>), SgGeo<1, ESZ, 2>::LDS}});
         return err;
     } else {
-        static const int err = raise_lds_limits({limit(I1{}, I1{}), limit(std::integral_constant<int, 4>{}, I2{})});
+        static const int err = raise_lds_limits({{reinterpret_cast<const void*>(&gather_gemm_small_kernel<T, ADD, LAYOUT, 1, 1, false>), SgGeo<1, ESZ, 1>::LDS},
+                                                 {reinterpret_cast<const void*>(&gather_gemm_small_kernel<T, ADD, LAYOUT, 4, 2, true>), SgGeo<4, ESZ, 2>::LDS}});
+        if constexpr (LAYOUT == GG_TN) {
+            static const int few = raise_lds_limits({{reinterpret_cast<const void*>(&gather_gemm_small_kernel<T, ADD, LAYOUT, 4, 2, false>), SgGeo<4, ESZ, 2>::LDS}});
+            if (few) return few;
+        }
         return err;
     }
 }
 
-template <typename T, bool ADD, int LAYOUT, int GW, int WT>
+template <typename T, bool ADD, int LAYOUT, int GW, int WT, bool SPLIT = false>
 static int launch_small(GgParams p, hipStream_t st) {
     using G = SgGeo<GW, (int)sizeof(T), WT>;
     p.tiles_m = (int)((p.M + G::BM - 1) / G::BM);
     p.tiles_n = (p.N + G::BN - 1) / G::BN;
     const int per_xcd = (p.tiles_m * p.tiles_n + NUM_XCD - 1) / NUM_XCD;
-    hipLaunchKernelGGL((gather_gemm_small_kernel<T, ADD, LAYOUT, GW, WT>), dim3((unsigned)(per_xcd * NUM_XCD)), dim3(SG_THREADS), G::LDS, st, p);
+    hipLaunchKernelGGL((gather_gemm_small_kernel<T, ADD, LAYOUT, GW, WT, SPLIT>), dim3((unsigned)(per_xcd * NUM_XCD)), dim3(SG_THREADS), G::LDS, st, p);
     return (int)hipGetLastError();
 }
 
-template <typename T, int GW, int WT>
+template <typename T, int GW, int WT, bool SPLIT = false>
 static int launch_small_form(const GgParams& p, bool add, int layout, hipStream_t st) {
-    if (layout == GG_TN) return launch_small<T, false, GG_TN, GW, WT>(p, st);
+    if (layout == GG_TN) return launch_small<T, false, GG_TN, GW, WT, SPLIT>(p, st);
     if constexpr (sizeof(T) == 2)
         if (layout == GG_NN) return launch_small<T, true, GG_NN, GW, WT>(p, st);
-    return add ? launch_small<T, true, GG_NT, GW, WT>(p, st) : launch_small<T, false, GG_NT, GW, WT>(p, st);
+    return add ? launch_small<T, true, GG_NT, GW, WT, SPLIT>(p, st) : launch_small<T, false, GG_NT, GW, WT, SPLIT>(p, st);
 }
 
 template <typename T>
@@ -643,7 +647,11 @@ int prepare_gather_gemm_small(lemo_dtype_t dt, bool add, int layout) {
 
 int launch_gather_gemm_small(const GgParams& p, lemo_dtype_t dt, bool add, int layout, GgTile tile, hipStream_t st) {
     if (dt == LEMO_BF16) return launch_small_form<bf16_t, 1, 2>(p, add, layout, st);
-    return tile == GG_T128 ? launch_small_form<float, 4, 2>(p, add, layout, st) : launch_small_form<float, 1, 1>(p, add, layout, st);
+    if (tile != GG_T128) return launch_small_form<float, 1, 1>(p, add, layout, st);
+    // sums of one or two products (only a weight gradient has them, the other forms contract over 4 at least) from binary32 MFMAs:
+    // error 2.5e-8 and 3.1e-8 against 3.5e-8 and 3.4e-8 of splits, 8192 x 8192 83 us against 69
+    if (layout == GG_TN && p.K < SPLIT_LEAST) return launch_small<float, false, GG_TN, 4, 2>(p, st);
+    return launch_small_form<float, 4, 2, true>(p, add, layout, st);
 }
 
 }  // namespace lemo

@@ -1050,6 +1050,21 @@ def test_gather_gemm_fp32_split_keeps_small_operands(lemo, form, M, N, K, small,
         assert torch.equal(got[~few], product(plain)[~few])
 
 
+@pytest.mark.parametrize("M", [1, 2, 3, 4])
+def test_gather_gemm_dw_fp32_of_few_tokens(lemo, M):
+    """Sums of few products, in many tiles: no further from 64 bits (2-norm) than a chain of fused binary32 operations, one rounding per
+    product, within the one percent that two sets of 4 million roundings may differ by."""
+    say(f"[gemm] fp32 dW of {M} tokens")
+    gen = torch.Generator(device="cuda").manual_seed(M)
+    dY, X = (torch.randn((M, 2048), generator=gen, device="cuda") for _ in range(2))
+    got = lemo.lemo_gather_gemm_dw(dY, X, torch.arange(M, dtype=torch.int32, device="cuda"))
+    want = sum(dY[m].double()[:, None] * X[m].double() for m in range(M))
+    chain = torch.zeros_like(got)
+    for m in range(M):  # binary32, fused: one rounding per product
+        chain = (chain.double() + dY[m].double()[:, None] * X[m].double()).float()
+    assert (got.double() - want).norm() <= 1.01 * (chain.double() - want).norm()
+
+
 @pytest.mark.parametrize("far", ["dY", "X"])
 def test_gather_gemm_dw_f32_beyond_32_bit_offsets(lemo, far):
     """binary32 weight gradient of operands whose row pitch is 8 MiB and more, which goes through transposed copies in the

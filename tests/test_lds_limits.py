@@ -79,7 +79,7 @@ def gemm_dx(lib, dt, _):
 
 
 def gemm_dw(lib, dt, _):
-    for N, C, M in PRODUCTS:
+    for N, C, M in PRODUCTS + [(4096, 4096, 2)]:
         N = (N + 7) // 8 * 8
         for dW in (FAR, P) if dt == F32 else (FAR,):  # apart from the operands, and over one of them
             yield lib.lemo_gather_gemm_dw, (P, N, 1 << 45, M, C, None, M, dW, C, C, N, dt, P, 1 << 40, None)
