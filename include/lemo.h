@@ -97,8 +97,11 @@ int lemo_score_workspace_bytes(int64_t S, int32_t H, int32_t H_kv, int32_t d, le
  *     scores[j]   = (1/H) * sum_h ( colsum^h[j] - [EXCLUDE_SELF] diag^h[j] )      (Eq. 1, head mean of Eq. 2)
  *
  * Blocks of queries and of keys are worked on without regard to segments; results do not depend on L.  Two
- * sweeps over Q K^T are made (row log-sum-exp, then column sums); both run on the matrix cores (bf16 inputs)
- * or in true binary32 (fp32 inputs), accumulate in binary32, and keep probabilities in binary32.
+ * sweeps over Q K^T are made (row log-sum-exp, then column sums) on the matrix cores; both accumulate in binary32
+ * and keep probabilities in binary32.  fp32 inputs are split into three bf16 parts whose products, but for the
+ * smallest (2^-24 of a product at most), are added in binary32: measured no further from 64 bits than binary32
+ * products.  Where parts cannot hold what a logit feels (values that are not finite, or below 2^-110 against
+ * very large ones) the products are binary32 ones.
  *
  *   Q  [S, H, d]     element (i,h,c) at Q[i*q_tok_stride + h*q_head_stride + c]   (d contiguous)
  *   K  [S, H_kv, d]  likewise with the k_ strides
@@ -261,6 +264,9 @@ int lemo_select_threshold(const float* token_blocks, int64_t S, int32_t b, float
  *
  * binary32 accumulation, one rounding at the store.  The result for output row m depends only on
  * the values of X row kept_idx[m], so running on a materialised compact copy gives identical bits.
+ * fp32: products of many output tiles come from three bf16 parts of each operand as in the scores;
+ * a sum that is not finite, or that would feel what parts lose of values below 2^-110, is formed
+ * from binary32 products, by itself.
  * Supported: C % 8 == 0 (bf16) / C % 4 == 0 (fp32).  X and W follow the 16-byte rule; Y only needs
  * element alignment and any ldy >= N (rows that are 16-byte aligned are stored 16 bytes at a time).  Y may not overlap X, W
  * or bias (blocks of Y are stored while others still read).

@@ -2,8 +2,8 @@
 // straight from the [S,C] input inside the A-tile load -- a kept row is C contiguous elements, so the
 // indexed load is as coalesced as a dense one and no compacted copy of X ever exists.
 //
-// This file holds the launches and the choice of the output tiles; the kernels are gather_gemm_large.hip (256 x 256, bf16)
-// and gather_gemm_small.hip.
+// This file holds the launches and the choice of the output tiles; the kernels are gather_gemm_large.hip (256 x 256, bf16),
+// gather_gemm_mid.hip (256 x 128 and 128 x 128, bf16) and gather_gemm_small.hip (64 x 64; binary32).
 #include "gather_gemm.hpp"
 
 namespace lemo {

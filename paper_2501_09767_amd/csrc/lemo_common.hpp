@@ -94,11 +94,13 @@ __device__ __forceinline__ uint32_t pack_bf16x2_hw(float lo, float hi) {
 }
 
 // ---- binary32 products on the bf16 matrix cores ---------------------------------------------------
-// A binary32 value is the exact sum of three bf16 ones, each the rest rounded to nearest (below 2^-110 it may not be: SPLIT_WHOLE).  Six of the nine products of two such sums are formed, the smallest first; the other three amount to at most
-// 2^-26 of a product, with either sign, and the 32 x 32 x 16 MFMA adds 16 products per rounding of the sum where the binary32 one
-// adds 2.  8 times the rate for 6 products; splitting 8 values takes 44 instructions.  (Cut off instead of rounded, the rests have
-// their value's sign: scores were then up to twice as far from 64 bits.)  Infinities do not survive this (infinity times a zero
-// part).  Results that are not finite, or that feel what small values lose, have to be formed again with mma_chunk<float>.
+// A binary32 value is the exact sum of three bf16 ones, each the rest rounded to nearest (below 2^-110 it may not be: SPLIT_WHOLE).
+// Six of the nine products of two such sums are formed, the smallest first; the other three amount to at most 2^-24 of a product
+// (a = b = 1.0038986), 2^-27.5 of it in the mean square over mantissas, with either sign, and the 32 x 32 x 16 MFMA adds 16
+// products per rounding of the sum where the binary32 one adds 2.  16 times the rate for 6 products; splitting 8 values takes 44
+// instructions.  (Cut off instead of rounded, the rests have their value's sign: scores were then up to twice as far from 64 bits.)
+// Infinities do not survive this (infinity times a zero part).  Results that are not finite, or that feel what small values lose,
+// have to be formed again with mma_chunk<float>.
 struct Split8 { u32x4 part[3]; };  // 8 values in three parts, as MFMA operands
 __device__ __forceinline__ void split_pair(Split8& s, int e, const u32x4& from) {  // values 2e and 2e + 1, elements 2 (e % 2) of `from` on
     float v0 = __uint_as_float(from[e % 2 * 2]), v1 = __uint_as_float(from[e % 2 * 2 + 1]);

@@ -10,9 +10,12 @@
 // cycles a tile on a full chip).  Measured, both sweeps and the head mean, us, before (binary32 MFMAs) / now, causal:
 //   d = 64    1024 tokens, 4 heads 32.8 / 28.1;  3000, 4: 91.7 / 65.2;  1024, 12: 39.1 / 29.6;  5000, 16: 478 / 307
 //   d = 128   1000 tokens, 32 heads 117 / 76;  2500, 32: 475 / 329;  1500, 16, no mask: 220 / 151
-// and no further from 64 bits (scores, relative 2-norm, mean of 12 to 60 draws, before / now: 1024 tokens, 4 heads of 64 4.60e-8 /
-// 4.52e-8; 300, 12 6.4e-8 / 5.7e-8; 3000, 4 5.08e-8 / 5.08e-8; 5000, 16 6.4e-8 / 6.3e-8; 1024, 12, no mask 6.4e-8 / 5.9e-8; 1000,
-// 16 heads of 128 6.3e-8 / 5.8e-8; 2500, 32 8.4e-8 / 8.7e-8; 700, 16, no mask 7.0e-8 / 6.0e-8; single draws spread by a third).
+// and as far from 64 bits within what draws of this number tell apart (scores, relative 2-norm, binary32 MFMAs / now, mean of 24 to
+// 200 draws and of the paired differences with their standard error):
+//   d = 64    1024 tokens, 4 heads 4.99e-8 / 4.63e-8 (-3.5 +- 1.3 e-9);  3000, 4 5.03e-8 / 4.86e-8 (-1.7 +- 1.0);  300, 12 6.22e-8 / 5.86e-8
+//             (-3.6 +- 1.8);  5000, 16 6.33e-8 / 6.30e-8 (-0.2 +- 1.8);  1024, 12, no mask 6.44e-8 / 6.21e-8 (-2.3 +- 1.6)
+//   d = 128   1000 tokens, 16 heads 6.57e-8 / 6.56e-8 (-0.1 +- 1.9);  2500, 32 8.85e-8 / 8.54e-8 (-3.1 +- 1.9);  5000, 32 8.63e-8 / 8.78e-8
+//             (+1.5 +- 3.0);  700, 16, no mask 6.27e-8 / 6.13e-8 (-1.4 +- 1.8)
 // Tried (5000 tokens, 16 heads, d = 64): two waves per row with two subtiles each 580 us, whole rows 397, one resident subtile
 // per wave 341.
 //
