@@ -23,8 +23,8 @@ namespace lemo {
 // Products that fill whole rounds with one of the two large kinds may take another for the columns behind them (the launches
 // follow each other, so the times add).
 // binary32: 128 x 128 tiles, or 32 x 32 ones with the contraction split over four waves up to 192 of the former (us, 128 x 128 /
-// 32 x 32: M = 200, N = K = 768 32 / 7.8; 96 tiles, M = 500, N = 3072, K = 768 33 / 29; 160, M = 640, N = 4096, K = 1024 43 / 56; 192,
-// M = 700, N = K = 4096 159 / 203; 256, M = 1024, N = 4096, K = 1024 53 / 88).  By time the line would lie at 128; but the four partial
+// 32 x 32: M = 200, N = K = 768 33 / 7.3; 96 tiles, M = 500, N = 3072, K = 768 36 / 32; 160, M = 640, N = 4096, K = 1024 45 / 60; 192,
+// M = 700, N = K = 4096 158 / 204; 256, M = 1024, N = 4096, K = 1024 52 / 85).  By time the line would lie at 128; but the four partial
 // sums of the small tiles are nearer to 64 bits (2.9e-7 against 4.9e-7), so what they served before the large ones became
 // faster they still serve.
 struct GgPlan { int head_cols; GgTile head, rest; };
