@@ -15,7 +15,7 @@ CSRC = os.path.join(HERE, "csrc")
 OBJDIR = os.path.join(ROOT, "_build")
 LIB = os.path.join(HERE, "liblemo_hip.so")
 NATIVE = os.path.join(HERE, "lemo_native.so")  # the binding's native marshalling, linked against LIB
-SOURCES = ["lemo_api.hip", "score.hip", "score_f32.hip", "score_blocks.hip", "score_blocks_few.hip", "attention.hip", "select.hip", "gather_gemm.hip", "gather_gemm_large.hip", "gather_gemm_mid.hip", "gather_gemm_small.hip", "transpose.hip", "scatter.hip", "probe.hip"]
+SOURCES = ["lemo_api.hip", "score.hip", "score_f32.hip", "score_blocks.hip", "score_blocks_few.hip", "score_blocks_slabs.hip", "attention.hip", "select.hip", "gather_gemm.hip", "gather_gemm_large.hip", "gather_gemm_mid.hip", "gather_gemm_small.hip", "transpose.hip", "scatter.hip", "probe.hip"]
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 # packed-fp32 code generation is switched off on purpose: the compiler must not form v_pk_*_f32 instructions from scalar float code
 FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-Wall", "-Wno-unused-command-line-argument",

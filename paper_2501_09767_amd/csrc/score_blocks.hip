@@ -298,20 +298,29 @@ static int launch_tilemax_t(BlockParams p, hipStream_t st) {
     const long long total = (p.flags & LEMO_CAUSAL) ? (long long)p.nt * (p.nt + 1) / 2 : (long long)p.nt * p.nt;
     if (total > INT32_MAX - NUM_XCD) return (int)hipErrorInvalidConfiguration;
     p.count = (int)total;
-    // One workgroup per CU is one round of 256 rectangles, and a round takes the same time however many there are.  What a last
-    // round has goes to tilemax_few_kernel as quarters if those fit one round of that kernel (two workgroups per CU at
-    // D = 64).  us per call, one kernel / so divided; 32 heads, D = 128, causal: 36 rectangles 42.5 / 23.0, 300 85.6 / 68.0, 528
-    // 130 / 114, 820 183 / 168, 2080 403 / 394; 16 heads, D = 64: 36 (12 heads) 18.5 / 13.7, 136 23.0 / 22.1 (alike: the
-    // line), 300 38.8 / 32.0, 528 55.4 / 48.4.  Beyond it, at 128: 325 86.7 / 85.0, 136 43.5 / 56.0.
+    // bf16.  More than 256 rectangles go to tilemax_slab_kernel, which has 512 at a time; up to 256, one per CU, this kernel's eight
+    // waves per rectangle are faster.  A round takes nearly as long for a few rectangles as for all: what is left of the last 256 goes
+    // to tilemax_few_kernel as quarters if it is little, or all there is.  us per call, this kernel / slabs / slabs (or none)
+    // and the rest as quarters, causal; 32 heads, D = 128: 36 rectangles 45 / 51 / 25, 120 45.5 / 51 / 43.5, 136 45 / 51 / 58,
+    // 253 52 / 54 / 77, 276 88 / 72 / 74, 325 89 / 76 / 91, 496 97 / 86 / 130, 528 134 / 118 / 106, 561 135 / 118 / 111, 666 141 / 125 /
+    // 144, 1081 224 / 190 / 180; 16 heads, D = 64: 36 24 / 25 / 16, 120 24.4 / 25.8 / 18.0, 171 24.9 / 25.8 / 23.6, 253 25.1 / 26.1 / 28.1,
+    // 276 41.5 / 35.3 / 35.6, 378 41 / 35 / 40, 528 60 / 51 / 47, 561 59 / 50 / 46, 666 59 / 50 / 56, 1275 95 / 77 / 88.
     int rest = 0;
+    bool slabs = false;
     if constexpr (G::TT == 128 && sizeof(T) == 2) {
         rest = p.count % SB_CUS;
-        if (rest > (D == 128 ? SB_CUS / 4 : SB_CUS / 2)) rest = 0;
+        if (rest > (p.count < SB_CUS ? SB_CUS / 2 : SB_CUS / 4)) rest = 0;
         p.count -= rest;
+        slabs = p.count > SB_CUS;
     }
     p.per_xcd = (p.count + NUM_XCD - 1) / NUM_XCD;
-    if (p.count > 0) hipLaunchKernelGGL((tilemax_kernel<T, D, MODE>), dim3((unsigned)(p.per_xcd * NUM_XCD)), dim3(G::THREADS), G::LDS, st, p);
-    const hipError_t err = hipGetLastError();
+    hipError_t err = hipSuccess;
+    if (slabs) {
+        err = (hipError_t)launch_tilemax_slabs(p, D, MODE, st);
+    } else if (p.count > 0) {
+        hipLaunchKernelGGL((tilemax_kernel<T, D, MODE>), dim3((unsigned)(p.per_xcd * NUM_XCD)), dim3(G::THREADS), G::LDS, st, p);
+        err = hipGetLastError();
+    }
     if (err != hipSuccess || rest == 0) return (int)err;
     return launch_tilemax_few(p, D, MODE, p.count, rest, st);
 }
@@ -323,7 +332,8 @@ int launch_score_blocks(const BlockParams& p_in, lemo_dtype_t dt, int d, int mod
     p.nt32 = (p.S + 31) / 32;
     int rc = prepare_score(dt, d);
     if (rc) return rc;
-    if (dt == LEMO_BF16) rc = first_error(d == 128 ? prepare_tilemax<bf16_t, 128> : prepare_tilemax<bf16_t, 64>, [=] { return prepare_tilemax_few(d); });
+    if (dt == LEMO_BF16) rc = first_error(d == 128 ? prepare_tilemax<bf16_t, 128> : prepare_tilemax<bf16_t, 64>, [=] { return prepare_tilemax_few(d); },
+                                              [=] { return prepare_tilemax_slabs(d); });
     else rc = d == 128 ? prepare_tilemax<float, 128>() : prepare_tilemax<float, 64>();
     if (rc) return rc;
     if (dt == LEMO_BF16 && d == 128) rc = mode ? launch_tilemax_t<bf16_t, 128, 1>(p, st) : launch_tilemax_t<bf16_t, 128, 0>(p, st);

@@ -1,4 +1,4 @@
-// The 128 x 128 rectangles of the block-wise scores and the order in which both kernels walk them.
+// The 128 x 128 rectangles of the block-wise scores and the order in which the kernels walk them.
 #pragma once
 #include "lemo_common.hpp"
 
@@ -32,6 +32,9 @@ __host__ __device__ inline void sb_rectangle(int id, int nt, bool causal, int& t
     tq = r0 + 1 + t + id;
 }
 
+// The first p.count rectangles of that order (bf16): score_blocks_slabs.hip
+int prepare_tilemax_slabs(int d);
+int launch_tilemax_slabs(const BlockParams& p, int d, int mode, hipStream_t st);
 // Rectangles first .. first + rest - 1 of that order as 64 x 64 quarters (bf16): score_blocks_few.hip
 int prepare_tilemax_few(int d);
 int launch_tilemax_few(const BlockParams& p, int d, int mode, int first, int rest, hipStream_t st);

@@ -590,6 +590,22 @@ def test_score_blocks_few_rectangles(lemo, S, H, Hkv, d, flags):
         assert_blocks_close(tb.cpu().numpy(), want_tb, "token blocks", 1e-6 if mode == 0 else 1e-5)
 
 
+@pytest.mark.parametrize("S,H,Hkv,d,flags", [
+    (3073, 1, 1, 128, 3), (3195, 2, 1, 128, 1), (3200, 3, 3, 128, 2 | 1), (2177, 4, 2, 128, 0), (2304, 5, 5, 128, 2),  # 325 (causal), 324 rectangles
+    (3073, 1, 1, 64, 1), (3130, 2, 2, 64, 3), (2290, 3, 1, 64, 0), (2200, 4, 4, 64, 2), (3199, 9, 9, 64, 3),
+    (4110, 2, 1, 128, 3), (4110, 1, 1, 64, 1)])                     # 512 and 49 in quarters
+def test_score_blocks_many_rectangles(lemo, S, H, Hkv, d, flags):
+    """More than 256 rectangles: heads around the depth of the slab kernel's pipeline, ragged last rows and columns."""
+    for mode in (0, 1):
+        say(f"[blocks many] S={S} H={H}/{Hkv} d={d} flags={flags} mode={mode}")
+        Q, K = wl.tiny_qk(S, H, Hkv, d, "bf16", seed=S + d + H)
+        sb, tb = lemo.lemo_score_blocks(Q.cuda(), K.cuda(), 32, flags=flags, mode=mode)
+        torch.cuda.synchronize()
+        want_sb, want_tb = oracle.score_blocks(wl.as_numpy(Q), wl.as_numpy(K), 32, flags=flags, mode=mode)
+        assert_blocks_close(sb.cpu().numpy(), want_sb, "score blocks", 1e-6 if mode == 0 else 1e-5)
+        assert_blocks_close(tb.cpu().numpy(), want_tb, "token blocks", 1e-6 if mode == 0 else 1e-5)
+
+
 def test_score_blocks_options_and_determinism(lemo):
     say("[blocks] options")
     Q, K = wl.tiny_qk(700, 4, 2, 128, "bf16", seed=5)
