@@ -46,8 +46,9 @@ __global__ __launch_bounds__(256, 2) void tilemax_slab_kernel(BlockParams p) {
     const unsigned group = (unsigned)(p.H / p.H_kv);
 
     // Unit u = i * 256 + tid of a slab is its LDS bytes [16 u, 16 u + 16): row u / 8 (queries, then keys), position u % 8, which
-    // holds piece (u % 8) ^ (row / 2 % 8), so that one piece of 16 rows meets all banks.  The descriptor ends with the last row, so that rows past the end (larger per-thread offsets) arrive as zeros; the scalar offset moves along a row and
-    // counts against the descriptor's size as well.
+    // holds piece (u % 8) ^ (row / 2 % 8), so that one piece of 16 rows meets all banks.  The descriptor ends with the
+    // last row, so that rows past the end (larger per-thread offsets) arrive as zeros; the scalar offset moves along a row and counts
+    // against the descriptor's size as well.
     const unsigned q_row_bytes = (unsigned)p.q_ts * 2u, k_row_bytes = (unsigned)p.k_ts * 2u;  // host: < 2^24
     unsigned voff[G::NLOAD];
 #pragma unroll
