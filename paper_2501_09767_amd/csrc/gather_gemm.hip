@@ -3,7 +3,7 @@
 // indexed load is as coalesced as a dense one and no compacted copy of X ever exists.
 //
 // This file holds the launches and the choice of the output tiles; the kernels are gather_gemm_large.hip (256 x 256, bf16),
-// gather_gemm_mid.hip (256 x 128 and 128 x 128, bf16) and gather_gemm_small.hip (64 x 64; binary32).
+// gather_gemm_mid.hip (256, 192, 128 or 64 x 128, bf16) and gather_gemm_small.hip (64 x 64; binary32).
 #include "gather_gemm.hpp"
 
 namespace lemo {
@@ -15,12 +15,16 @@ namespace lemo {
 // The time of n tiles of a kind over k slabs of 64 elements of the contraction, in us, is taken as
 //   a + full (b k + e) + (c + d f) k + e f          full whole rounds, the last one filled to f (nothing if f = 0)
 // with a the launch, b a slab in a full round, c ... c + d in the last one (c: if it is the first, if there are rounds before), e
-// what a round costs besides (loads before, stores after).  Fitted to the four kinds over M = 64 ... 5000 with the widths and contractions of layers of 256 to 4096 (N or K up to
-// 14336), 143 products X W^T, 66 input and 66 weight gradients, operands from HBM: each kind within 4 to 13 % (rms); the
-// kind chosen costs 0.1 % over the best one on average, 6 % at worst.
-// e.g. us for 256 x 256 / 256 x 128 / 128 x 128 / 64 x 64:  M = 200, N = K = 4096  75 / 50 / 35 / 20;   M = 504, N = 11008,
-// K = 4096  79 / 57 / 69 / 103;   M = 1504, N = K = 4096  79 / 57 / 73 / 96;   M = 3280, N = K = 4096  87 / 101 / 129 / 194.
-// Products that fill whole rounds with one of the two large kinds may take another for the columns behind them (the launches
+// what a round costs besides (loads before, stores after).  `along` is fitted to the six kinds over M = 50 ... 9000 with the widths and
+// contractions of layers of 768 to 4096 (N or K up to 14336), 197 products X W^T and 114 input gradients, operands from HBM: each
+// kind within 4 to 9 % (rms), the kind chosen costs 0.1 % over the best one on average, 14 % at worst.  `across` is fitted to 66 weight
+// gradients of layers of 256 to 4096, M = 64 ... 5000; its kinds are those whose rows are whole contraction-major regions.
+// e.g. us for 256 x 256 / 256 x 128 / 192 x 128 / 128 x 128 / 64 x 128 / 64 x 64:  M = 100, N = K = 4096  - / 46 / 42 / 35 / 28 / 15;
+// M = 128, N = 11008, K = 4096  73 / 46 / 43 / 42 / 32 / 42;   M = 504, N = 11008, K = 4096  79 / 56 / 80 / 76 / 83 / 106;
+// M = 1500, N = K = 4096  81 / 56 / 50 / 76 / - / 97;   M = 3280, N = K = 4096  93 / 110 / 131 / 136 / - / 196;   input gradient M = 1500,
+// 4096 columns, contraction 11008  203 / 153 / 134 / 195 / - / 251.  The two kinds between (192 x 128: M = 1500 above is 256 tiles of
+// it; 64 x 128: half of 128 x 128's time where those leave half of the CUs without one) are the best ones by 3.5 % on average.
+// Products that fill whole rounds with one of the larger kinds may take another for the columns behind them (the launches
 // follow each other, so the times add).
 // binary32: 128 x 128 tiles, or 32 x 32 ones with the contraction split over four waves up to 192 of the former (us, 128 x 128 /
 // 32 x 32: M = 200, N = K = 768 33 / 7.3; 96 tiles, M = 500, N = 3072, K = 768 36 / 32; 160, M = 640, N = 4096, K = 1024 45 / 60; 192,
@@ -28,18 +32,19 @@ namespace lemo {
 // sums of the small tiles are nearer to 64 bits (2.9e-7 against 4.9e-7), so what they served before the large ones became
 // faster they still serve.
 struct GgPlan { int head_cols; GgTile head, rest; };
-struct GgFit { int rows, cols; double a, b, c[2], d, e; };
+struct GgFit { GgTile tile; int rows, cols; double a, b, c[2], d, e; };
 static GgPlan gg_plan(long long M, int N, int K, int layout, lemo_dtype_t dt) {
-    // in the order of GgTile
-    static constexpr GgFit along[4] = {{256, 256, 6.8, 1.48, {1.02, 0.99}, 0.30, 2.3}, {256, 128, 4.2, 0.87, {0.64, 0.59}, 0.22, 3.8},
-                                       {128, 128, 1.7, 0.54, {0.48, 0.43}, 0.09, 3.2}, {64, 64, 2.4, 0.21, {0.24, 0.225}, 0.02, 2.9}};
-    static constexpr GgFit across[4] = {{256, 256, 5.6, 1.51, {1.16, 1.16}, 0.14, 7.1}, {256, 128, 5.0, 0.94, {0.75, 0.75}, 0.13, 5.0},
-                                        {128, 128, 3.2, 0.59, {0.56, 0.56}, 0.02, 3.6}, {64, 64, 4.4, 0.18, {0.17, 0.17}, 0.30, 4.2}};
+    static constexpr GgFit along[] = {{GG_T256, 256, 256, 4.7, 1.525, {1.06, 1.008}, 0.333, 4.4}, {GG_T256x128, 256, 128, 4.0, 0.863, {0.647, 0.658}, 0.203, 2.6},
+                                      {GG_T192x128, 192, 128, 3.3, 0.701, {0.554, 0.531}, 0.145, 2.9}, {GG_T128, 128, 128, 2.8, 0.534, {0.474, 0.472}, 0.067, 2.5},
+                                      {GG_T64x128, 64, 128, 2.3, 0.374, {0.373, 0.362}, 0.064, 1.8}, {GG_T64, 64, 64, 3.1, 0.198, {0.215, 0.227}, 0.029, 2.8}};
+    static constexpr GgFit across[] = {{GG_T256, 256, 256, 5.6, 1.51, {1.16, 1.16}, 0.14, 7.1}, {GG_T256x128, 256, 128, 5.0, 0.94, {0.75, 0.75}, 0.13, 5.0},
+                                       {GG_T128, 128, 128, 3.2, 0.59, {0.56, 0.56}, 0.02, 3.6}, {GG_T64, 64, 64, 4.4, 0.18, {0.17, 0.17}, 0.30, 4.2}};
     if (dt == LEMO_F32) {
         const double n128 = (double)((M + 127) / 128) * (double)(((long long)N + 127) / 128);
         return {0, GG_T128, n128 <= 192 ? GG_T64 : GG_T128};
     }
     const GgFit* fits = layout == GG_TN ? across : along;
+    const int kinds = layout == GG_TN ? 4 : 6, heads = kinds / 2;  // heads: the kinds that may come before another one
     const double k = K / 64.;
     auto time = [&](const GgFit& f, long long cols) {
         const double n = (double)((M + f.rows - 1) / f.rows) * (double)((cols + f.cols - 1) / f.cols);
@@ -48,15 +53,15 @@ static GgPlan gg_plan(long long M, int N, int K, int layout, lemo_dtype_t dt) {
     };
     GgPlan best{0, GG_T256, GG_T256};
     double least = time(fits[0], N);
-    for (int t = 1; t < 4; ++t)
-        if (time(fits[t], N) < least) { least = time(fits[t], N); best.rest = (GgTile)t; }
-    for (int h = 0; h < 2; ++h) {
-        const long long tm = (M + 255) / 256, rounds = tm * ((N + fits[h].cols - 1) / fits[h].cols) / 256;
+    for (int t = 1; t < kinds; ++t)
+        if (time(fits[t], N) < least) { least = time(fits[t], N); best.rest = fits[t].tile; }
+    for (int h = 0; h < heads; ++h) {
+        const long long tm = (M + fits[h].rows - 1) / fits[h].rows, rounds = tm * ((N + fits[h].cols - 1) / fits[h].cols) / 256;
         const long long cols = rounds * 256 / tm * fits[h].cols;  // columns whose tiles fit whole rounds
         if (cols <= 0 || cols >= N) continue;
-        for (int t = h + 1; t < 4; ++t) {
+        for (int t = h + 1; t < kinds; ++t) {
             const double both = time(fits[h], cols) + time(fits[t], N - cols);
-            if (both < least) { least = both; best = {(int)cols, (GgTile)h, (GgTile)t}; }
+            if (both < least) { least = both; best = {(int)cols, fits[h].tile, fits[t].tile}; }
         }
     }
     return best;

@@ -1,5 +1,5 @@
-// What the selective-load GEMM kernels share: gather_gemm_large.hip (256 x 256 tiles), gather_gemm_mid.hip (256 x 128 and
-// 128 x 128), gather_gemm_small.hip (64 x 64; all of binary32).
+// What the selective-load GEMM kernels share: gather_gemm_large.hip (256 x 256 tiles), gather_gemm_mid.hip (256, 192,
+// 128 or 64 x 128), gather_gemm_small.hip (64 x 64; all of binary32).
 #pragma once
 #include <type_traits>
 
@@ -52,12 +52,12 @@ __device__ __forceinline__ bool gg_tile(int b, int tiles_m, int tiles_n, int gro
 }
 
 // Output tiles.  binary32 knows GG_T128 and GG_T64 only, both in gather_gemm_small.hip, the latter 32 x 32.
-enum GgTile { GG_T256, GG_T256x128, GG_T128, GG_T64 };
+enum GgTile { GG_T256, GG_T256x128, GG_T192x128, GG_T128, GG_T64x128, GG_T64 };
 int prepare_gather_gemm_large(bool add, int layout);
 int prepare_gather_gemm_mid(bool add, int layout);
 int prepare_gather_gemm_small(lemo_dtype_t dt, bool add, int layout);
 int launch_gather_gemm_large(const GgParams& p, bool add, int layout, hipStream_t st);               // GG_T256, bf16
-int launch_gather_gemm_mid(const GgParams& p, bool add, int layout, GgTile tile, hipStream_t st);    // GG_T256x128, GG_T128, bf16
+int launch_gather_gemm_mid(const GgParams& p, bool add, int layout, GgTile tile, hipStream_t st);    // the kinds of 128 columns, bf16
 int launch_gather_gemm_small(const GgParams& p, lemo_dtype_t dt, bool add, int layout, GgTile tile, hipStream_t st);
 
 }  // namespace lemo

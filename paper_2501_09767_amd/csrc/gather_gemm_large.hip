@@ -51,13 +51,13 @@ __global__ __launch_bounds__(RG_THREADS, 1) void gather_gemm_large_kernel(GgPara
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int wm = wave / LG_WN, wn = wave % LG_WN;
     const int l16 = lane & 15, quad = lane >> 4;
-    using Loads = RgLoads<LAYOUT, 2, 2>;
+    using Loads = RgLoads<LAYOUT, 4, 4>;
     using Slab = typename Loads::Slab;
     Loads ld(p, m0, n0, tid, smem + LG_TOK + wave * 1024);
     const int nk = ld.nk;
     const unsigned lds0 = __builtin_amdgcn_readfirstlane(lds_offset_of(smem) + wave * 1024);
-    auto load_a = [&](const Slab& s, int kt, int r, int i) { ld.load_a(s, r, i, lds0 + (kt & 1) * LG_STAGE + r * RG_BYTES); };
-    auto load_b = [&](const Slab& s, int kt, int r, int i) { ld.load_b(s, r, i, lds0 + LG_OPER + (kt & 1) * LG_STAGE + r * RG_BYTES); };
+    auto load_a = [&](const Slab& s, int kt, int r, int i) { ld.load_a(s, 2 * r + i, lds0 + (kt & 1) * LG_STAGE); };
+    auto load_b = [&](const Slab& s, int kt, int r, int i) { ld.load_b(s, 2 * r + i, lds0 + LG_OPER + (kt & 1) * LG_STAGE); };
 
     f32x4 acc[2][TA][2][TB];  // [half of A][tile][half of B][tile]
 #pragma unroll

@@ -1,72 +1,76 @@
-// The selective-load GEMM (and its in-place-add and gradient forms, see gather_gemm.hip) on 256 x 128 and 128 x 128 output
-// tiles, bf16, for products that leave most CUs without a 256 x 256 tile or its last round nearly empty.
+// The selective-load GEMM (and its in-place-add and gradient forms, see gather_gemm.hip) on output tiles of 256, 192, 128 or 64
+// rows x 128 columns, bf16, for products that leave most CUs without a 256 x 256 tile or its last round nearly empty.
 //
-// One workgroup of eight waves per CU, in a 4 x 2 grid: a wave computes 32 x 64 of every 128 x 128 region.  Slabs of 128 bytes of
-// the contraction pass through a ring of 3 (256 x 128) or 4 stages, filled by LDS-direct loads; the fragments of the next slab are
+// One workgroup of eight waves per CU, in a 4 x 2 grid: a wave computes a quarter of the rows x 64 columns.  Slabs of 128 bytes of
+// the contraction pass through a ring of 4 stages (256 x 128: 3), filled by LDS-direct loads; the fragments of the next slab are
 // read during the MFMAs of the current one, so the registers are one stage more, and a slab needs one barrier: the next slab has
 // landed, and everyone has the current one in registers, so its stage can be asked for again.
 //
 // What bounds it: LDS (a slab of 256 x 128 takes 896 cycles of it for 1024 of MFMAs, of 128 x 128 640 for 512) and what the barrier
-// costs; with weights that come from HBM, the latency of the loads (M = 256, N = 11008, K = 4096: 30 us with W in the caches, 41
-// without, whether the loads are spread or not, and 50 with a ninth wave that touches the slabs ahead).
-// Measured, operands from HBM, us (two workgroups of four waves per CU on 128 x 128 tiles, 64 x 64 per wave, were before):
-//   256 x 128  M = 1504: N = K = 4096 55 / 63, N = 4096, K = 11008 149 / 165 (input gradient 149 / 165, weight gradient 159 / 189);
-//              M = 3280, N = K = 4096: 101 / 119
-//   128 x 128  M = 256, N = 11008, K = 4096: 41.5 / 44.4;  M = N = 256 x 4096: 38 / 41;  M = 768, N = 3072, K = 768: 9.4 / 10.7
+// costs; with weights that come from HBM, what a CU gets: 55 to 60 GB/s of rows of both operands, however many stages
+// are in flight (3 or 4 alike; loads spread or not; tiles starting at different slabs alike; a ninth wave that touches the slabs ahead 50 us
+// against 41, M = 256, N = 11008, K = 4096), so that fewer rows per tile on more CUs win there.
+// Measured, operands from HBM, us (the kind before it in brackets):
+//   256 x 128  M = 1504: N = 4096, K = 11008 149;  weight gradient 159;  M = 3280, N = K = 4096: 101
+//   192 x 128  M = 1500: N = K = 4096 50 (256 x 128: 56), input gradient of 11008 x 4096 134 (153);  M = 522, N = 8192, K = 2048 25.7 (27.6)
+//   128 x 128  M = 256, N = 11008, K = 4096: 42;  M = 768, N = 3072, K = 768: 9.4
+//   64 x 128   M = 128, N = 11008, K = 4096: 32 (128 x 128: 42);  M = 500, N = K = 4096 30 (37);  M = 408, N = 3072, K = 768 8.0 (9.7)
+// (128 x 64 does as well as 64 x 128, 128 x 96 gains 7 % where 64 x 128 loses; neither fits contraction-major regions.)
 #include "gather_gemm_regions.hpp"
 
 namespace lemo {
 
-template <int RA> struct MdGeo {                           // RA: regions of A's rows
-    static constexpr int BM = 128 * RA, BN = 128;
-    static constexpr int NS = RA == 1 ? 4 : 3;             // stages
-    static constexpr int STAGE = (RA + 1) * RG_BYTES;      // A's regions, then B's
+template <int LAYOUT, int UA> struct MdGeo {               // UA: the tile's rows / 64
+    static constexpr int BM = 64 * UA, BN = 128;
+    static constexpr int A_BYTES = BM * RG_KB, STAGE = A_BYTES + RG_BYTES;  // A's rows, then B's region
+    static constexpr int TOKENS = LAYOUT == GG_TN ? RG_TOK : 0;
+    static constexpr int NS = UA == 4 ? 3 : 4;             // stages
     static constexpr int TOK = NS * STAGE;                 // (GG_TN) token rings
     static constexpr int EP = BN * 4 + 16;                 // epilogue: LDS pitch of a row of floats
-    static constexpr int LDS_LOOP = TOK + RG_TOK, LDS_EPI = BM * EP;
+    static constexpr int LDS_LOOP = TOK + TOKENS, LDS_EPI = BM * EP;
     static constexpr int LDS = LDS_LOOP > LDS_EPI ? LDS_LOOP : LDS_EPI;
     static_assert(LDS <= 160 * 1024, "a workgroup's LDS");
 };
 
-template <bool ADD, int LAYOUT, int RA>
+template <bool ADD, int LAYOUT, int UA>
 __global__ __launch_bounds__(RG_THREADS, 1) void gather_gemm_mid_kernel(GgParams p) {
-    using G = MdGeo<RA>;
+    using G = MdGeo<LAYOUT, UA>;
     constexpr bool A_KMAJOR = LAYOUT == GG_TN, B_KMAJOR = LAYOUT != GG_NT;
-    constexpr int TA = 2, TB = 4, NL = RG_NLD, NS = G::NS;  // 16-row tiles of a wave per region of A, of B
+    constexpr int TA = UA, TB = 4, NS = G::NS;  // 16-row tiles of a wave of A, of B
     extern __shared__ __attribute__((aligned(16))) char smem[];
     int tm, tn;
-    if (!gg_tile(blockIdx.x, p.tiles_m, p.tiles_n, 8 / RA, tm, tn)) return;
+    if (!gg_tile(blockIdx.x, p.tiles_m, p.tiles_n, UA <= 2 ? 16 / UA : 4, tm, tn)) return;
     const long long m0 = (long long)tm * G::BM;
     const int n0 = tn * G::BN;
     const int tid = threadIdx.x, lane = tid & 63, l16 = lane & 15, quad = lane >> 4;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int wm = wave >> 1, wn = wave & 1;
-    using Loads = RgLoads<LAYOUT, RA, 1>;
+    // 16-row tile i of the wave, among the tile's: contraction-major rows come in regions of 128, of which a wave takes 32
+    auto a_tile = [&](int i) { return A_KMAJOR ? i / 2 * 8 + wm * 2 + i % 2 : wm * TA + i; };
+    using Loads = RgLoads<LAYOUT, UA, 2>;
     Loads ld(p, m0, n0, tid, smem + G::TOK + wave * 1024);
     const int nk = ld.nk;
     const unsigned lds0 = __builtin_amdgcn_readfirstlane(lds_offset_of(smem) + wave * 1024);
-    constexpr int LOADS = NL * (RA + 1), BATCH = LOADS + (LAYOUT == GG_TN ? 1 : 0);
+    constexpr int LOADS = UA + 2, BATCH = LOADS + (LAYOUT == GG_TN ? 1 : 0);
     constexpr int AHEAD = NS - 1;  // (GG_TN) the indices of a slab are asked for this many slabs ahead of its rows
     auto load = [&](const typename Loads::Slab& s, unsigned stage, int k) {  // load k of a slab
-        if (k < NL * RA) ld.load_a(s, k / NL, k % NL, stage + (k / NL) * RG_BYTES);
-        else ld.load_b(s, 0, k - NL * RA, stage + RA * RG_BYTES);
+        if (k < UA) ld.load_a(s, k, stage);
+        else ld.load_b(s, k - UA, stage + G::A_BYTES);
     };
 
-    f32x4 acc[RA][TA][TB];
+    f32x4 acc[TA][TB];
 #pragma unroll
-    for (int a = 0; a < RA; ++a)
+    for (int i = 0; i < TA; ++i)
 #pragma unroll
-        for (int i = 0; i < TA; ++i)
-#pragma unroll
-            for (int j = 0; j < TB; ++j) acc[a][i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
-    u32x4 fa[2][RA][2][TA], fb[2][2][TB];  // fragments of two slabs
-    constexpr int NF = 2 * (RA * TA + TB);
+        for (int j = 0; j < TB; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+    u32x4 fa[2][2][TA], fb[2][2][TB];  // fragments of two slabs
+    constexpr int NF = 2 * (TA + TB);
     auto read = [&](auto set_tag, const char* stage, int f) {  // fragment f of a slab: B's, then A's
         constexpr int SET = decltype(set_tag)::value;
-        if (f < 2 * TB) { fb[SET][f / TB][f % TB] = rg_fragment(stage + RA * RG_BYTES, B_KMAJOR, wn * TB + f % TB, f / TB, lane); return; }
+        if (f < 2 * TB) { fb[SET][f / TB][f % TB] = rg_fragment(stage + G::A_BYTES, B_KMAJOR, wn * TB + f % TB, f / TB, lane); return; }
         f -= 2 * TB;
-        const int a = f / (2 * TA), c = f / TA % 2, i = f % TA;
-        fa[SET][a][c][i] = rg_fragment(stage + a * RG_BYTES, A_KMAJOR, wm * TA + i, c, lane);
+        const int c = f / TA, t = a_tile(f % TA);
+        fa[SET][c][f % TA] = A_KMAJOR ? rg_fragment(stage + t / 8 * RG_BYTES, true, t % 8, c, lane) : rg_fragment(stage, false, t, c, lane);
     };
 
     if constexpr (LAYOUT == GG_TN) {
@@ -92,7 +96,7 @@ __global__ __launch_bounds__(RG_THREADS, 1) void gather_gemm_mid_kernel(GgParams
 #pragma unroll
     for (int f = 0; f < NF; ++f) read(std::integral_constant<int, 0>{}, smem, f);
 
-    constexpr int NM = 2 * RA * TA * TB;
+    constexpr int NM = 2 * TA * TB;
     int st = 0;  // stage of slab kt
     // Slab kt (kt & 1 == PAR), its fragments in set PAR.  Behind the barrier slab kt + 1 has landed (all batches but the last
     // NS - 2) and stage st is free; the source order is the issue order, neighbouring MFMAs share a fragment.
@@ -108,9 +112,9 @@ __global__ __launch_bounds__(RG_THREADS, 1) void gather_gemm_mid_kernel(GgParams
         if constexpr (LAYOUT == GG_TN) ld.read_tokens(kt + NS);
 #pragma unroll
         for (int q = 0; q < NM; ++q) {
-            const int a = q / (2 * TA * TB), c = q / (TA * TB) % 2, w = q % (TA * TB), i = w / TB, j = i & 1 ? TB - 1 - w % TB : w % TB;
+            const int c = q / (TA * TB), w = q % (TA * TB), i = w / TB, j = i & 1 ? TB - 1 - w % TB : w % TB;
             __builtin_amdgcn_sched_barrier(0);
-            rg_mma(acc[a][i][j], fa[PAR][a][c][i], fb[PAR][c][j]);
+            rg_mma(acc[i][j], fa[PAR][c][i], fb[PAR][c][j]);
 #pragma unroll
             for (int f = q * NF / (NM * 3 / 4); f < (q + 1) * NF / (NM * 3 / 4); ++f)
                 if (f < NF) read(std::integral_constant<int, PAR ^ 1>{}, next, f);
@@ -159,12 +163,10 @@ __global__ __launch_bounds__(RG_THREADS, 1) void gather_gemm_mid_kernel(GgParams
         }
     }
 #pragma unroll
-    for (int a = 0; a < RA; ++a)
+    for (int i = 0; i < TA; ++i)
 #pragma unroll
-        for (int i = 0; i < TA; ++i)
-#pragma unroll
-            for (int j = 0; j < TB; ++j)
-                *reinterpret_cast<f32x4*>(smem + (a * 128 + (wm * TA + i) * 16 + l16) * G::EP + ((wn * TB + j) * 16 + 4 * quad) * 4) = acc[a][i][j];
+        for (int j = 0; j < TB; ++j)
+            *reinterpret_cast<f32x4*>(smem + (a_tile(i) * 16 + l16) * G::EP + ((wn * TB + j) * 16 + 4 * quad) * 4) = acc[i][j];
     __syncthreads();
 #pragma unroll
     for (int q = 0; q < PASSES; ++q) {
@@ -189,27 +191,35 @@ __global__ __launch_bounds__(RG_THREADS, 1) void gather_gemm_mid_kernel(GgParams
     }
 }
 
+template <bool ADD, int LAYOUT, int UA> constexpr LdsLimit mid_limit() {
+    return {reinterpret_cast<const void*>(&gather_gemm_mid_kernel<ADD, LAYOUT, UA>), MdGeo<LAYOUT, UA>::LDS};
+}
 template <bool ADD, int LAYOUT>
 static int prepare_mid() {
-    static const int err = raise_lds_limits({{reinterpret_cast<const void*>(&gather_gemm_mid_kernel<ADD, LAYOUT, 1>), MdGeo<1>::LDS},
-                                             {reinterpret_cast<const void*>(&gather_gemm_mid_kernel<ADD, LAYOUT, 2>), MdGeo<2>::LDS}});
+    static const int err = [] {
+        if constexpr (LAYOUT == GG_TN) return raise_lds_limits({mid_limit<ADD, LAYOUT, 2>(), mid_limit<ADD, LAYOUT, 4>()});
+        else return raise_lds_limits({mid_limit<ADD, LAYOUT, 1>(), mid_limit<ADD, LAYOUT, 2>(), mid_limit<ADD, LAYOUT, 3>(), mid_limit<ADD, LAYOUT, 4>()});
+    }();
     return err;
 }
 
-template <bool ADD, int LAYOUT, int RA>
+template <bool ADD, int LAYOUT, int UA>
 static int launch_mid(GgParams p, hipStream_t st) {
-    using G = MdGeo<RA>;
+    using G = MdGeo<LAYOUT, UA>;
     p.tiles_m = (int)((p.M + G::BM - 1) / G::BM);
     p.tiles_n = (p.N + G::BN - 1) / G::BN;
     const int per_xcd = (p.tiles_m * p.tiles_n + NUM_XCD - 1) / NUM_XCD;
-    hipLaunchKernelGGL((gather_gemm_mid_kernel<ADD, LAYOUT, RA>), dim3((unsigned)(per_xcd * NUM_XCD)), dim3(RG_THREADS), G::LDS, st, p);
+    hipLaunchKernelGGL((gather_gemm_mid_kernel<ADD, LAYOUT, UA>), dim3((unsigned)(per_xcd * NUM_XCD)), dim3(RG_THREADS), G::LDS, st, p);
     return (int)hipGetLastError();
 }
-template <int RA>
+template <int UA>
 static int launch_mid_form(const GgParams& p, bool add, int layout, hipStream_t st) {
-    if (layout == GG_TN) return launch_mid<false, GG_TN, RA>(p, st);
-    if (layout == GG_NN) return launch_mid<true, GG_NN, RA>(p, st);
-    return add ? launch_mid<true, GG_NT, RA>(p, st) : launch_mid<false, GG_NT, RA>(p, st);
+    if (layout == GG_TN) {
+        if constexpr (UA % 2 == 0) return launch_mid<false, GG_TN, UA>(p, st);
+        else return (int)hipErrorInvalidValue;  // (its plans know whole regions of rows only)
+    }
+    if (layout == GG_NN) return launch_mid<true, GG_NN, UA>(p, st);
+    return add ? launch_mid<true, GG_NT, UA>(p, st) : launch_mid<false, GG_NT, UA>(p, st);
 }
 
 int prepare_gather_gemm_mid(bool add, int layout) {
@@ -219,7 +229,12 @@ int prepare_gather_gemm_mid(bool add, int layout) {
 }
 
 int launch_gather_gemm_mid(const GgParams& p, bool add, int layout, GgTile tile, hipStream_t st) {
-    return tile == GG_T128 ? launch_mid_form<1>(p, add, layout, st) : launch_mid_form<2>(p, add, layout, st);
+    switch (tile) {
+        case GG_T256x128: return launch_mid_form<4>(p, add, layout, st);
+        case GG_T192x128: return launch_mid_form<3>(p, add, layout, st);
+        case GG_T128: return launch_mid_form<2>(p, add, layout, st);
+        default: return launch_mid_form<1>(p, add, layout, st);
+    }
 }
 
 }  // namespace lemo

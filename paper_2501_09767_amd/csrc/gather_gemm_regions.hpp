@@ -20,13 +20,15 @@ constexpr int RG_TOK = RG_WAVES * 1024;               // (GG_TN) token rings: pe
 // size in both operands and arrive as zeros; the scalar offset moves along a row.
 __device__ __forceinline__ constexpr int rg_kswz(int r) { return ((r & 3) | ((r >> 3) & 1) << 2) << 1; }
 
-template <int LAYOUT, int RA, int RB> struct RgLoads {  // RA, RB: regions of the tile's A rows, B rows
+// Load u of an operand: rows (columns) 64 u .. + 63; contraction-major, half u % 2 of the contraction rows of region u / 2.
+template <int LAYOUT, int UA, int UB> struct RgLoads {  // the tile's rows of A, of B, / 64
+    static_assert((LAYOUT != GG_TN || UA % 2 == 0) && (LAYOUT == GG_NT || UB % 2 == 0), "contraction-major operands come in whole regions");
     static constexpr bool A_KMAJOR = LAYOUT == GG_TN, B_KMAJOR = LAYOUT != GG_NT;
     const bf16_t *a_base, *b_base;
     const int* idx;
     unsigned lda_bytes, ldb_bytes, a_size, b_size, a_cols, b_cols;
     int K, nk, kpos, krow;
-    unsigned a_voff[RA][RG_NLD], b_voff[RB][RG_NLD], tok[LAYOUT == GG_TN ? RG_NLD : 1];
+    unsigned a_voff[UA], b_voff[UB], tok[LAYOUT == GG_TN ? RG_NLD : 1];
     const char* ring;
     unsigned lds_ring;
     u32x4 idx_rsrc;
@@ -42,28 +44,24 @@ template <int LAYOUT, int RA, int RB> struct RgLoads {  // RA, RB: regions of th
         krow = tid >> 4;
         const int kcol = ((tid & 15) ^ rg_kswz(krow)) * 16;
 #pragma unroll
-        for (int r = 0; r < RA; ++r)
-#pragma unroll
-            for (int i = 0; i < RG_NLD; ++i) {
-                if constexpr (A_KMAJOR) {
-                    a_voff[r][i] = (i * (RG_THREADS / 16) + krow) * lda_bytes + r * 256 + kcol;
-                } else {
-                    const long long m = min(m0 + r * 128 + i * (RG_THREADS / 8) + (tid >> 3), p.M - 1);
-                    a_voff[r][i] = (p.idx ? (unsigned)p.idx[m] : (unsigned)m) * lda_bytes + kpos;
-                }
+        for (int u = 0; u < UA; ++u) {
+            if constexpr (A_KMAJOR) {
+                a_voff[u] = (u % 2 * (RG_THREADS / 16) + krow) * lda_bytes + u / 2 * 256 + kcol;
+            } else {
+                const long long m = min(m0 + u * (RG_THREADS / 8) + (tid >> 3), p.M - 1);
+                a_voff[u] = (p.idx ? (unsigned)p.idx[m] : (unsigned)m) * lda_bytes + kpos;
             }
+        }
 #pragma unroll
-        for (int r = 0; r < RB; ++r)
-#pragma unroll
-            for (int i = 0; i < RG_NLD; ++i) {
-                if constexpr (LAYOUT == GG_NT) b_voff[r][i] = (r * 128 + i * (RG_THREADS / 8) + (tid >> 3)) * ldb_bytes + kpos;
-                else if constexpr (LAYOUT == GG_NN) b_voff[r][i] = (i * (RG_THREADS / 16) + krow) * ldb_bytes + r * 256 + kcol;
-                else b_voff[r][i] = (unsigned)n0 * 2 + r * 256 + kcol;  // + the token's row, per slab
-            }
+        for (int u = 0; u < UB; ++u) {
+            if constexpr (LAYOUT == GG_NT) b_voff[u] = (u * (RG_THREADS / 8) + (tid >> 3)) * ldb_bytes + kpos;
+            else if constexpr (LAYOUT == GG_NN) b_voff[u] = (u % 2 * (RG_THREADS / 16) + krow) * ldb_bytes + u / 2 * 256 + kcol;
+            else b_voff[u] = (unsigned)n0 * 2 + u / 2 * 256 + kcol;  // + the token's row, per slab
+        }
         a_base = static_cast<const bf16_t*>(p.A) + (A_KMAJOR ? m0 : 0ll);
         b_base = static_cast<const bf16_t*>(p.B) + (LAYOUT == GG_NT ? (long long)n0 * p.ldb : LAYOUT == GG_NN ? (long long)n0 : 0ll);
         a_size = p.a_bytes;
-        b_size = LAYOUT == GG_NT ? (min(128 * RB, p.N - n0) - 1) * ldb_bytes + K * 2 : p.b_bytes;  // GG_NT: this tile's rows of B
+        b_size = LAYOUT == GG_NT ? (min(64 * UB, p.N - n0) - 1) * ldb_bytes + K * 2 : p.b_bytes;  // GG_NT: this tile's rows of B
         a_cols = (unsigned)(p.M - m0);
         b_cols = (unsigned)(p.N - n0);
         ring = token_ring;
@@ -92,15 +90,15 @@ template <int LAYOUT, int RA, int RB> struct RgLoads {  // RA, RB: regions of th
         }
         return s;
     }
-    // load i of region r; lds: the region + 1024 * wave
-    __device__ __forceinline__ void load_a(const Slab& s, int r, int i, unsigned lds) const {
-        if constexpr (A_KMAJOR) lds_direct_b128(s.a, lds + i * (RG_THREADS * 16), (int)a_voff[r][i]);
-        else lds_direct_b128(s.a, lds + i * (RG_THREADS * 16), (int)(s.in_k ? a_voff[r][i] : a_size), s.soff);
+    // load u; lds: the operand's first region + 1024 * wave
+    __device__ __forceinline__ void load_a(const Slab& s, int u, unsigned lds) const {
+        if constexpr (A_KMAJOR) lds_direct_b128(s.a, lds + u * (RG_THREADS * 16), (int)a_voff[u]);
+        else lds_direct_b128(s.a, lds + u * (RG_THREADS * 16), (int)(s.in_k ? a_voff[u] : a_size), s.soff);
     }
-    __device__ __forceinline__ void load_b(const Slab& s, int r, int i, unsigned lds) const {
-        if constexpr (LAYOUT == GG_TN) lds_direct_b128(s.b, lds + i * (RG_THREADS * 16), (int)(tok[i] == b_size ? tok[i] : tok[i] + b_voff[r][i]));
-        else if constexpr (LAYOUT == GG_NN) lds_direct_b128(s.b, lds + i * (RG_THREADS * 16), (int)b_voff[r][i]);
-        else lds_direct_b128(s.b, lds + i * (RG_THREADS * 16), (int)(s.in_k ? b_voff[r][i] : b_size), s.soff);
+    __device__ __forceinline__ void load_b(const Slab& s, int u, unsigned lds) const {
+        if constexpr (LAYOUT == GG_TN) lds_direct_b128(s.b, lds + u * (RG_THREADS * 16), (int)(tok[u % 2] == b_size ? tok[u % 2] : tok[u % 2] + b_voff[u]));
+        else if constexpr (LAYOUT == GG_NN) lds_direct_b128(s.b, lds + u * (RG_THREADS * 16), (int)b_voff[u]);
+        else lds_direct_b128(s.b, lds + u * (RG_THREADS * 16), (int)(s.in_k ? b_voff[u] : b_size), s.soff);
     }
     // (GG_TN) indices of slab kt into the wave's ring; the rows of B of slab kt, which load_b then takes
     __device__ __forceinline__ void issue_tokens(int kt, int lane) const {

@@ -57,7 +57,9 @@ def requests(layout, bm, bn, M, N, K, S, lda, ldb, idx):
             for i, tid in itertools.product(range(NLD), (0, 1, 7, 8, 130, 511)):
                 (row, kpos), (krow, kcol) = unit(i, tid)
                 in_k, k = kpos < kbytes - kt * KB, kt * 64 + krow
-                for r in range(bm // 128):
+                for r in range(-(-bm // 128)):
+                    if r * 2 + i >= bm // 64:                # the kinds of 64 and 192 rows end with half a region
+                        continue
                     if layout == "tn":
                         off = kt * 64 * lda * 2 if live else 0
                         yield ("A", m0 * 2 + off, ((K - 1) * lda + M - m0) * 2 - off if live else 0, krow * lda * 2 + r * 256 + kcol, 0, k,
@@ -84,7 +86,7 @@ def requests(layout, bm, bn, M, N, K, S, lda, ldb, idx):
 @pytest.mark.parametrize("layout,M,N,K,pad", [("nt", 300, 270, 72, 0), ("nt", 1, 1, 8, 8), ("nt", 257, 513, 200, 16), ("nn", 260, 264, 72, 0),
                                               ("nn", 300, 512, 200, 8), ("tn", 264, 520, 65, 0), ("tn", 256, 264, 131, 8), ("tn", 8, 8, 1, 0), ("nt", 130, 40, 1000, 0), ("nt", 517, 300, 256, 8),
                                               ("nt", 513, 257, 1000, 0), ("nt", 1, 2, 8, 0), ("nt", 300, 512, 4096, 0), ("nt", 256, 256, 64, 24)])
-@pytest.mark.parametrize("bm,bn", [(256, 256), (256, 128), (128, 128)])
+@pytest.mark.parametrize("bm,bn", [(256, 256), (256, 128), (128, 128), (192, 128), (64, 128)])
 def test_no_request_leaves_its_operand(layout, M, N, K, pad, bm, bn):
     S = (K if layout == "tn" else M) + (0 if layout == "nn" else 9)
     idx = [(7 * r + 3) % S for r in range(K if layout == "tn" else M)]

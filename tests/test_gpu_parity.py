@@ -963,6 +963,23 @@ def test_gather_gemm_mid_tiles_exact(lemo, form, M, N, K):
     test_gather_gemm_tiles_exact(lemo, form, M, N, K, "bf16")
 
 
+@pytest.mark.parametrize("form,M,N,K", [
+    # 192 x 128: less than a slab, one, a piece more, as many as the ring holds (4), more; ragged rows and columns
+    ("nt", 2419, 1869, 8), ("add", 1861, 2992, 64), ("dx", 1515, 3064, 72), ("add", 2454, 1785, 136), ("nt", 766, 6761, 200), ("dx", 766, 6760, 200),
+    ("dx", 798, 5920, 264), ("nt", 1584, 2512, 328), ("add", 418, 8391, 392),
+    # 64 x 128
+    ("nt", 241, 1165, 8), ("dx", 344, 3544, 64), ("add", 111, 10601, 72), ("nt", 203, 5656, 136), ("dx", 1102, 912, 200), ("nt", 554, 2921, 264),
+    ("add", 72, 3280, 328), ("dx", 1673, 856, 392), ("nt", 211, 7184, 456),
+    # 128 x 128
+    ("nt", 2142, 1229, 8), ("add", 1519, 2520, 64), ("dx", 2037, 1816, 72), ("nt", 2073, 1264, 136), ("dx", 1133, 3264, 200), ("add", 2259, 1461, 264),
+    ("nt", 1913, 1552, 328),
+    # 64 x 64
+    ("nt", 122, 2200, 1000), ("dx", 61, 4000, 1000), ("add", 200, 1003, 2056)])
+def test_gather_gemm_tiles_of_128_columns_exact(lemo, form, M, N, K):
+    """The kinds of tiles that small and middle-sized products take, from one slab to more than the ring of stages holds."""
+    test_gather_gemm_tiles_exact(lemo, form, M, N, K, "bf16")
+
+
 @pytest.mark.parametrize("what", ["plain", "inf", "nan", "lowest", "tiny"])
 @pytest.mark.parametrize("form,M,N,K", [("nt", 1700, 1931, 132), ("nt", 1537, 2049, 1000), ("add", 1600, 2050, 36), ("dw", 1924, 2060, 331)])
 def test_gather_gemm_fp32_split(lemo, form, M, N, K, what):
