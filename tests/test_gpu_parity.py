@@ -515,6 +515,28 @@ def test_select_all_equal_and_extremes(lemo):
         np.testing.assert_array_equal(got, oracle.select_topk(ext, 128, k))
 
 
+@pytest.mark.parametrize("alike", [1, 2, 63, 64, 65, 300, 1000])
+@pytest.mark.parametrize("low", [2, 300, 1 << 21])
+def test_select_many_alike_in_the_leading_digits(lemo, alike, low):
+    """`alike` scores share their leading 11 bits and differ (or not) within the `low` smallest steps behind them: the select's ends by
+    rank (up to 64 candidates), by later digits, and where all that are alike are kept."""
+    say(f"[select digits] alike={alike} low={low}")
+    rng = np.random.default_rng(alike + low)
+    L = 1024
+    scores = (rng.random(3 * L - 100) * 4 + 4).astype(np.float32)  # (4 .. 8, in other bins than 1 .. 1.25 below)
+    scores[rng.random(scores.size) < 0.3] *= np.float32(-1)
+    for s in range(0, scores.size, L):
+        n = min(L, scores.size - s)
+        where = s + rng.permutation(n)[:min(alike, n)]
+        scores[where] = (np.uint32(0x3f800000) + rng.integers(0, low, where.size).astype(np.uint32)).view(np.float32)
+    above = int((scores[:L] > 2).sum())
+    for k in {1, above, above + 1, above + (alike + 1) // 2, above + alike, L}:
+        if not 1 <= k <= L:
+            continue
+        got = lemo.lemo_select_topk(torch.from_numpy(scores).cuda(), L, k).cpu().numpy()
+        np.testing.assert_array_equal(got, oracle.select_topk(scores, L, k))
+
+
 @pytest.mark.parametrize("S,H,L,k,flags", [(1024, 4, 128, 64, 3), (1000, 3, 128, 64, 1), (7, 1, 4, 3, 2), (8192, 32, 512, 205, 3), (32768, 32, 1024, 308, 3),
                                            (20000, 9, 8192, 3000, 0), (32768, 8, 32768, 9831, 3), (513, 17, 512, 205, 3), (70000, 2, 20000, 7000, 2)])
 def test_head_mean_and_select_in_one_launch(lemo, S, H, L, k, flags):
