@@ -300,7 +300,7 @@ static int launch_tilemax_t(BlockParams p, hipStream_t st) {
     p.count = (int)total;
     // bf16.  More than 256 rectangles go to tilemax_slab_kernel, which has 512 at a time; up to 256, one per CU, this kernel's eight
     // waves per rectangle are faster.  A round takes nearly as long for a few rectangles as for all: what is left of the last 256 goes
-    // to tilemax_few_kernel as quarters if it is little, or all there is.  us per call, this kernel / slabs / slabs (or none)
+    // to tilemax_few_kernel as quarters or smaller if it is little, or all there is.  us per call (the rest always as quarters), this kernel / slabs / slabs (or none)
     // and the rest as quarters, causal; 32 heads, D = 128: 36 rectangles 45 / 51 / 25, 120 45.5 / 51 / 43.5, 136 45 / 51 / 58,
     // 253 52 / 54 / 77, 276 88 / 72 / 74, 325 89 / 76 / 91, 496 97 / 86 / 130, 528 134 / 118 / 106, 561 135 / 118 / 111, 666 141 / 125 /
     // 144, 1081 224 / 190 / 180; 16 heads, D = 64: 36 24 / 25 / 16, 120 24.4 / 25.8 / 18.0, 171 24.9 / 25.8 / 23.6, 253 25.1 / 26.1 / 28.1,

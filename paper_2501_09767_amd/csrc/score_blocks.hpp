@@ -35,7 +35,7 @@ __host__ __device__ inline void sb_rectangle(int id, int nt, bool causal, int& t
 // The first p.count rectangles of that order (bf16): score_blocks_slabs.hip
 int prepare_tilemax_slabs(int d);
 int launch_tilemax_slabs(const BlockParams& p, int d, int mode, hipStream_t st);
-// Rectangles first .. first + rest - 1 of that order as 64 x 64 quarters (bf16): score_blocks_few.hip
+// Rectangles first .. first + rest - 1 of that order as 64 x 64 quarters or 32 x 32 pieces (bf16): score_blocks_few.hip
 int prepare_tilemax_few(int d);
 int launch_tilemax_few(const BlockParams& p, int d, int mode, int first, int rest, hipStream_t st);
 
