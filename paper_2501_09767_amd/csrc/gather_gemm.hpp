@@ -51,7 +51,7 @@ __device__ __forceinline__ bool gg_tile(int b, int tiles_m, int tiles_n, int gro
     return true;
 }
 
-// Output tiles.  binary32 knows GG_T128 and GG_T64 only, both in gather_gemm_small.hip, the latter 32 x 32.
+// Output tiles.  binary32 knows GG_T128 and GG_T64 only, both in gather_gemm_small.hip, the latter 32 x 32 or 16 x 16.
 enum GgTile { GG_T256, GG_T256x128, GG_T192x128, GG_T128, GG_T64x128, GG_T64 };
 int prepare_gather_gemm_large(bool add, int layout);
 int prepare_gather_gemm_mid(bool add, int layout);

@@ -1,12 +1,12 @@
 // The selective-load GEMM (and its in-place-add and gradient forms, see gather_gemm.hip) on 64 x 64 output tiles (bf16, for
-// products of few tiles) and, in binary32, on 128 x 128 and 32 x 32 ones.
+// products of few tiles) and, in binary32, on 128 x 128, 32 x 32 and 16 x 16 ones.
 //
 // A wave computes a block of 32 x 32 MFMA tiles from slabs of 128 bytes of the contraction; two shapes:
 //   GW = 1  every wave has its own slabs: 64 x 64 output tile, the four waves take every fourth slab of the contraction
 //           each and their partial tiles are added, in wave order, through LDS at the end.  No barrier in the main loop.
 //           Bound by the latency of the loads: 128 KB per CU are in flight, all its LDS holds (M = 256, N = K = 4096: 17.5 us with
 //           the operands in the caches, 20.8 from HBM).  binary32, whose MFMAs take 16 times as long, is bound by those instead
-//           and takes 32 x 32 blocks, for four times the workgroups (splitting an operand for one tile costs as much as it saves).
+//           and takes 32 x 32 or 16 x 16 blocks, for four times the workgroups or 16 (splitting an operand for one tile costs as much as it saves).
 //   GW = 4  (binary32) the four waves of a workgroup share a slab: 128 x 128 output tile, 64 x 64 per wave, two workgroups per
 //           CU (70 KB of LDS each).  The products are three-part splits on the bf16 matrix cores (lemo_common.hpp); a slab costs a
 //           wave 352 instructions of splitting and 16 for the largest operands beside 1536 cycles of MFMAs, 2240 cycles where binary32
@@ -31,10 +31,10 @@ constexpr int SG_KB = 128;          // bytes of the contraction per slab
 
 constexpr int SPLIT_LEAST = 3;      // terms of a sum from which splits are no further from 64 bits than binary32 MFMAs
 
-// WT = MFMA tiles per wave and direction
-template <int GW, int ESZ, int WT> struct SgGeo {
+// WT = MFMA tiles per wave and direction, of E x E
+template <int GW, int ESZ, int WT, int E = 32> struct SgGeo {
     static constexpr int W = GW == 4 ? 2 : 1;       // waves of a group per output direction
-    static constexpr int WB = 32 * WT;              // rows and columns of a wave's block
+    static constexpr int WB = E * WT;               // rows and columns of a wave's block
     static constexpr int BM = WB * W, BN = WB * W;  // output tile
     static constexpr int GROUPS = 4 / GW;           // the slabs are dealt out to the groups in turn
     static constexpr int OPER = WB * W * SG_KB;     // bytes of one operand's slab
@@ -45,7 +45,9 @@ template <int GW, int ESZ, int WT> struct SgGeo {
     static constexpr int EPI = 4 * WB * EP;
     static constexpr int LDS = TOK + 4096 > EPI ? TOK + 4096 : EPI;
     static constexpr int KROWS = SG_KB / ESZ;       // contraction-major slab: rows,
-    static constexpr int PIECES = 2 * WT * W * ESZ;      // 16-byte pieces per row
+    static constexpr int PIECES = WB * W * ESZ / 16;     // 16-byte pieces per row
+    static constexpr int CHUNK = E == 16 ? 64 : 32;      // bytes of the contraction of one fragment; its MFMA tile per lane: rows,
+    static constexpr int CHUNKS = SG_KB / CHUNK, REGS = E * E / 64;  // registers
     // position of 16-byte piece p of row r (the loads fill consecutive LDS bytes, so conflicts are avoided by exchanging
     // pieces inside a row).  Rows along the contraction, 128 bytes: p ^ (r / 2 % 8) spreads one piece of 16 rows over all
     // banks.  Contraction-major rows: the transposing read (16 bit) takes 4 rows x 4 pieces at a time; of binary32 rows, which
@@ -55,12 +57,14 @@ template <int GW, int ESZ, int WT> struct SgGeo {
 };
 
 // SPLIT: products from three-part splits
-template <typename T, bool ADD, int LAYOUT, int GW, int WT, bool SPLIT>
+template <typename T, bool ADD, int LAYOUT, int GW, int WT, bool SPLIT, int E = 32>
 __global__ __launch_bounds__(SG_THREADS, GW == 4 ? 2 : 1) void gather_gemm_small_kernel(GgParams p) {
     constexpr bool A_KMAJOR = LAYOUT == GG_TN, B_KMAJOR = LAYOUT != GG_NT;
     constexpr int ESZ = (int)sizeof(T);
     static_assert(ESZ == 4 || (WT == 2 && GW == 1), "the 16-bit transposing read is laid out for 64 x 64 tiles");
-    using G = SgGeo<GW, ESZ, WT>;
+    static_assert(E == 32 || (ESZ == 4 && GW == 1 && WT == 1 && !SPLIT), "16 x 16 tiles: small binary32 products");
+    using G = SgGeo<GW, ESZ, WT, E>;
+    using Tile = std::conditional_t<E == 16, f32x4, f32x16>;
     constexpr int GROUPS = G::GROUPS, NLD = G::NLD;
     extern __shared__ __attribute__((aligned(16))) char smem[];
 
@@ -165,19 +169,21 @@ __global__ __launch_bounds__(SG_THREADS, GW == 4 ? 2 : 1) void gather_gemm_small
         __builtin_amdgcn_sched_barrier(0);
     };
 
-    // fragment (32-row subtile i of the wave's rows, chunk c of the slab) of an operand
+    // fragment (subtile i of the wave's rows, chunk c of the slab) of an operand.  E = 16: lane q * 16 + r has row r and a quarter of the chunk's
+    // 16 elements, 4 q .. + 3 of rows along the contraction, q, 4 + q, ... (other banks) of contraction-major ones
+    const int lrow = lane % E, part = lane / E;
     const int trow = 8 * half + ((l32 & 15) >> 2);
     auto frag = [&](const char* region, bool kmajor, int w, int i, int c) {
         if (!kmajor) {
-            const int row = (w * WT + i) * 32 + l32;
-            return *reinterpret_cast<const u32x4*>(region + row * SG_KB + (((2 * c + half) ^ G::swz(row)) << 4));
+            const int row = (w * WT + i) * E + lrow;
+            return *reinterpret_cast<const u32x4*>(region + row * SG_KB + (((G::CHUNK / 16 * c + part) ^ G::swz(row)) << 4));
         }
         if constexpr (ESZ == 4) {  // binary32: an MFMA takes one element per lane, rows 8c + 4 * half + {0..3} of its own column
-            const int col = (w * WT + i) * 32 + l32, row = 8 * c + 4 * half;
+            const int col = (w * WT + i) * E + lrow, row = E == 16 ? 16 * c + part : 8 * c + 4 * half;
             const char* at = region + row * (G::PIECES * 16) + (((col >> 2) ^ G::kswz(row)) << 4) + (col & 3) * 4;
             u32x4 v;
 #pragma unroll
-            for (int e = 0; e < 4; ++e) v[e] = *reinterpret_cast<const unsigned*>(at + e * G::PIECES * 16);
+            for (int e = 0; e < 4; ++e) v[e] = *reinterpret_cast<const unsigned*>(at + e * (E == 16 ? 4 : 1) * G::PIECES * 16);
             return v;
         }
         const int piece = (w * 8 + i * 4 + (l32 >> 4) * 2 + ((l32 & 3) >> 1)) ^ G::kswz(trow);
@@ -192,11 +198,19 @@ __global__ __launch_bounds__(SG_THREADS, GW == 4 ? 2 : 1) void gather_gemm_small
     auto a_frag = [&](int st, int i, int c) { return frag(stages + st * G::STAGE, A_KMAJOR, wm, i ^ wn, c); };
     auto b_frag = [&](int st, int i, int c) { return frag(stages + st * G::STAGE + G::OPER, B_KMAJOR, wn, i ^ wm, c); };
 
-    f32x16 acc[WT][WT];
+    Tile acc[WT][WT];
 #pragma unroll
     for (int i = 0; i < WT; ++i)
 #pragma unroll
-        for (int j = 0; j < WT; ++j) acc[i][j] = f32x16{0};
+        for (int j = 0; j < WT; ++j) acc[i][j] = Tile{0};
+    auto mma = [&](Tile& d, const u32x4& a, const u32x4& b) {
+        if constexpr (E == 16) {
+#pragma unroll
+            for (int e = 0; e < 4; ++e) d = __builtin_amdgcn_mfma_f32_16x16x4f32(__uint_as_float(a[e]), __uint_as_float(b[e]), d, 0, 0, 0);
+        } else {
+            mma_chunk<T>(d, a, b);
+        }
+    };
     float most[2] = {0.f, 0.f};  // (splits) largest magnitude in the lane's row of tile 0 of the wave's rows, of its columns
     auto drain = [&]() {
         __builtin_amdgcn_s_waitcnt(vmcnt_imm(0));  // requests past the end write (zeros) to the stages, too
@@ -207,7 +221,7 @@ __global__ __launch_bounds__(SG_THREADS, GW == 4 ? 2 : 1) void gather_gemm_small
 
     // The product from the operands' own MFMAs.
     auto product = [&]() {
-    u32x4 fa[2][4][WT], fb[2][4][WT];  // fragments of two slabs
+    u32x4 fa[2][G::CHUNKS][WT], fb[2][G::CHUNKS][WT];  // fragments of two slabs
 
     const int nit = (nk + GROUPS - 1) / GROUPS;  // slabs per group; the last may lie past the end (zeros)
     issue_tokens(0);
@@ -229,7 +243,7 @@ __global__ __launch_bounds__(SG_THREADS, GW == 4 ? 2 : 1) void gather_gemm_small
     __builtin_amdgcn_s_waitcnt(vmcnt_imm(BATCH));  // slab 0 (and the indices of slab 2)
     group_barrier();
 #pragma unroll
-    for (int c = 0; c < 4; ++c)
+    for (int c = 0; c < G::CHUNKS; ++c)
 #pragma unroll
         for (int i = 0; i < WT; ++i) {
             fa[0][c][i] = a_frag(0, i, c);
@@ -249,7 +263,7 @@ __global__ __launch_bounds__(SG_THREADS, GW == 4 ? 2 : 1) void gather_gemm_small
     // Slab `it` of the group (it & 1 == PAR), its fragments in set PAR; slab it+1 has been asked for into stage PAR^1,
     // slab it+2 into stage PAR.  First half of the MFMAs: read slab it+1's fragments; then, every wave of the group
     // having read them, the second half: ask for slab it+3 into the same stage.
-    constexpr int NMMA = 4 * WT * WT;
+    constexpr int NMMA = G::CHUNKS * WT * WT;
     auto step = [&](int it, auto par_tag) {
         constexpr int PAR = decltype(par_tag)::value, NXT = PAR ^ 1;
         __builtin_amdgcn_s_waitcnt(vmcnt_imm(BATCH));
@@ -259,10 +273,10 @@ __global__ __launch_bounds__(SG_THREADS, GW == 4 ? 2 : 1) void gather_gemm_small
         for (int q = 0; q < NMMA; ++q) {  // MFMA q of the slab: chunk q / (WT * WT)
             const int c = q / (WT * WT), i = q / WT % WT, j = q % WT;
             __builtin_amdgcn_sched_barrier(0);
-            mma_chunk<T>(acc[i][j], fa[PAR][c][i], fb[PAR][c][j]);
+            mma(acc[i][j], fa[PAR][c][i], fb[PAR][c][j]);
             if (q < NMMA / 2) {
 #pragma unroll
-                for (int f = q * 4 * WT / (NMMA / 2); f < (q + 1) * 4 * WT / (NMMA / 2); ++f) {
+                for (int f = q * G::CHUNKS * WT / (NMMA / 2); f < (q + 1) * G::CHUNKS * WT / (NMMA / 2); ++f) {
                     fa[NXT][f / WT][f % WT] = a_frag(NXT, f % WT, f / WT);
                     fb[NXT][f / WT][f % WT] = b_frag(NXT, f % WT, f / WT);
                 }
@@ -295,7 +309,7 @@ __global__ __launch_bounds__(SG_THREADS, GW == 4 ? 2 : 1) void gather_gemm_small
     // (SPLIT) The product from three-part splits.  A slab is two operand chunks of 16 elements; during the 24 MFMAs of one
     // chunk the next one's four operand tiles are split, pair by pair, and the one after that is read.  So slab it has left LDS when
     // its MFMAs begin: its stage is asked for again at once, with one barrier per slab, and has a slab's time to fill.
-    auto split_product = [&]() {
+    auto split_product = [&](auto& acc) {
         u32x4 raw[4][2];   // A's tiles, B's tiles
         Split8 part[2][4];
         auto read_raw = [&](int st, int c16, int o) {
@@ -375,7 +389,7 @@ __global__ __launch_bounds__(SG_THREADS, GW == 4 ? 2 : 1) void gather_gemm_small
     // and a column of which one has values too small to be split (they lose up to 2^-134 each, so a sum above `slight` times the
     // largest operand does not feel it).  Sum by sum, so that no row depends on its neighbours.
     const float slight = 0x1p-103f * (float)K;
-    auto form_again = [&]() {
+    auto form_again = [&](auto& acc) {
         // f(stage) for every slab, the next one on its way
         auto each_slab = [&](auto f) {
             issue_tokens(0);
@@ -481,7 +495,7 @@ __global__ __launch_bounds__(SG_THREADS, GW == 4 ? 2 : 1) void gather_gemm_small
     };
     if constexpr (SPLIT) {
         static_assert(ESZ == 4 && GW == 4 && WT == 2 && 2 * NLD == 8, "four operand tiles, a load per three MFMAs");
-        split_product();
+        split_product(acc);
         // (an infinity does not survive the split: the sum is then not a number)
         float probe = 0.f, low = INFINITY;
 #pragma unroll
@@ -493,7 +507,7 @@ __global__ __launch_bounds__(SG_THREADS, GW == 4 ? 2 : 1) void gather_gemm_small
                     probe = fmaf(acc[i][j][r], 0.f, probe);
                     low = fminf(low, fabsf(acc[i][j][r]));
                 }
-        if (__syncthreads_or(!(probe == 0.f) | (low < slight * 0x1p20f) | (fmaxf(most[0], most[1]) >= 0x1p20f))) form_again();
+        if (__syncthreads_or(!(probe == 0.f) | (low < slight * 0x1p20f) | (fmaxf(most[0], most[1]) >= 0x1p20f))) form_again(acc);
     } else {
         product();
     }
@@ -543,8 +557,8 @@ __global__ __launch_bounds__(SG_THREADS, GW == 4 ? 2 : 1) void gather_gemm_small
 #pragma unroll
         for (int j = 0; j < WT; ++j)
 #pragma unroll
-            for (int r = 0; r < 16; ++r)
-                *reinterpret_cast<float*>(mine + ((i ^ wn) * 32 + acc_row(r, lane)) * G::EP + ((j ^ wm) * 32 + l32) * 4) = acc[i][j][r];
+            for (int r = 0; r < G::REGS; ++r)
+                *reinterpret_cast<float*>(mine + ((i ^ wn) * E + (E == 16 ? 4 * part + r : acc_row(r, lane))) * G::EP + ((j ^ wm) * E + lrow) * 4) = acc[i][j][r];
     if constexpr (PARTS > 1) __syncthreads();  // (one group: a wave reads back its own block only)
 #pragma unroll
     for (int q = 0; q < PASSES; ++q) {
@@ -615,22 +629,22 @@ static int prepare_small() {
     }
 }
 
-template <typename T, bool ADD, int LAYOUT, int GW, int WT, bool SPLIT = false>
+template <typename T, bool ADD, int LAYOUT, int GW, int WT, bool SPLIT = false, int E = 32>
 static int launch_small(GgParams p, hipStream_t st) {
-    using G = SgGeo<GW, (int)sizeof(T), WT>;
+    using G = SgGeo<GW, (int)sizeof(T), WT, E>;
     p.tiles_m = (int)((p.M + G::BM - 1) / G::BM);
     p.tiles_n = (p.N + G::BN - 1) / G::BN;
     const int per_xcd = (p.tiles_m * p.tiles_n + NUM_XCD - 1) / NUM_XCD;
-    hipLaunchKernelGGL((gather_gemm_small_kernel<T, ADD, LAYOUT, GW, WT, SPLIT>), dim3((unsigned)(per_xcd * NUM_XCD)), dim3(SG_THREADS), G::LDS, st, p);
+    hipLaunchKernelGGL((gather_gemm_small_kernel<T, ADD, LAYOUT, GW, WT, SPLIT, E>), dim3((unsigned)(per_xcd * NUM_XCD)), dim3(SG_THREADS), G::LDS, st, p);
     return (int)hipGetLastError();
 }
 
-template <typename T, int GW, int WT, bool SPLIT = false>
+template <typename T, int GW, int WT, bool SPLIT = false, int E = 32>
 static int launch_small_form(const GgParams& p, bool add, int layout, hipStream_t st) {
-    if (layout == GG_TN) return launch_small<T, false, GG_TN, GW, WT, SPLIT>(p, st);
+    if (layout == GG_TN) return launch_small<T, false, GG_TN, GW, WT, SPLIT, E>(p, st);
     if constexpr (sizeof(T) == 2)
         if (layout == GG_NN) return launch_small<T, true, GG_NN, GW, WT>(p, st);
-    return add ? launch_small<T, true, GG_NT, GW, WT, SPLIT>(p, st) : launch_small<T, false, GG_NT, GW, WT, SPLIT>(p, st);
+    return add ? launch_small<T, true, GG_NT, GW, WT, SPLIT, E>(p, st) : launch_small<T, false, GG_NT, GW, WT, SPLIT, E>(p, st);
 }
 
 template <typename T>
@@ -647,6 +661,12 @@ int prepare_gather_gemm_small(lemo_dtype_t dt, bool add, int layout) {
 
 int launch_gather_gemm_small(const GgParams& p, lemo_dtype_t dt, bool add, int layout, GgTile tile, hipStream_t st) {
     if (dt == LEMO_BF16) return launch_small_form<bf16_t, 1, 2>(p, add, layout, st);
+    // binary32 MFMAs bound these, so a CU's time is that of its tiles' areas: four 16 x 16 tiles for one of 32 x 32 spread them better over 256
+    // CUs until a CU would have more than three (two of 32 x 32 run side by side).  us, 32 x 32 / 16 x 16: weight gradient 256 x 256
+    // of 512 tokens 7.0 / 4.8, of 3000 21.6 / 11.8; M = 100, N = K = 256 4.7 / 3.5; 512, 256, 256 4.8 / 4.1; 256, 768, 3072 (768 tiles) 17.4 /
+    // 16.6; 800, 256, 256 (800) 4.9 / 5.9; 500, 768, 768 10.7 / 12.1.  Errors against 64 bits alike (2.07e-7, 4.93e-7, 1.5e-7, ...).
+    const long long n16 = (p.M + 15) / 16 * ((p.N + 15ll) / 16);
+    if (tile != GG_T128 && n16 <= 768) return launch_small_form<float, 1, 1, false, 16>(p, add, layout, st);
     if (tile != GG_T128) return launch_small_form<float, 1, 1>(p, add, layout, st);
     // sums of one or two products (only a weight gradient has them, the other forms contract over 4 at least) from binary32 MFMAs:
     // error 2.5e-8 and 3.1e-8 against 3.5e-8 and 3.4e-8 of splits, 8192 x 8192 83 us against 69

@@ -973,6 +973,16 @@ def test_gather_gemm_large_tiles_exact(lemo, form, M, N, K):
 
 
 @pytest.mark.parametrize("form,M,N,K", [
+    # binary32, 16 x 16 tiles: one tile and less, fewer slabs than waves, a wave's share and more; ragged; 768 of them
+    ("nt", 1, 1, 4), ("nt", 16, 16, 32), ("nt", 17, 15, 36), ("add", 15, 33, 128), ("add", 100, 129, 132), ("nt", 384, 512, 260), ("add", 33, 770, 516),
+    ("dw", 4, 4, 1), ("dw", 16, 16, 31), ("dw", 36, 20, 33), ("dw", 100, 132, 129), ("dw", 256, 256, 600), ("dw", 512, 384, 257),
+    # 32 x 32 tiles
+    ("nt", 385, 512, 36), ("nt", 500, 451, 260), ("add", 1000, 385, 516), ("dw", 516, 388, 33), ("dw", 500, 1000, 131)])
+def test_gather_gemm_small_fp32_tiles_exact(lemo, form, M, N, K):
+    test_gather_gemm_tiles_exact(lemo, form, M, N, K, "f32")
+
+
+@pytest.mark.parametrize("form,M,N,K", [
     # 256 x 128 tiles: one slab and a piece of the next, as many slabs as the ring holds, one more; ragged rows and columns
     ("nt", 3300, 2300, 64), ("nt", 3297, 2305, 72), ("nt", 2305, 3070, 136), ("nt", 3300, 2303, 200), ("add", 2305, 3071, 264), ("dx", 3300, 2312, 72),
     ("dx", 2305, 3064, 200), ("dw", 2304, 3064, 129), ("dw", 2312, 3064, 191), ("dw", 2304, 3072, 300),
