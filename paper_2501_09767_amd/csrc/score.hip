@@ -41,9 +41,9 @@ namespace lemo {
 // infinite before it is rescaled, and lse2 comes out non-finite.  A workgroup that finds such a row among its own
 // (normally none does) goes through its keys a second time with the running maximum everywhere, before it stores
 // anything: no second launch, no extra traffic when there is nothing to repair.
-template <int D, int NRT, int KS>
-__global__ __launch_bounds__(SC_THREADS, (Geo<bf16_t, D, NRT, KS>::MIN_WG)) void rowstats_kernel(ScoreParams p) {
-    using G = Geo<bf16_t, D, NRT, KS>;
+template <int D, int NRT, int KS, int WAVES>
+__global__ __launch_bounds__(64 * WAVES, (Geo<bf16_t, D, NRT, KS, WAVES>::MIN_WG)) void rowstats_kernel(ScoreParams p) {
+    using G = Geo<bf16_t, D, NRT, KS, WAVES>;
     extern __shared__ __attribute__((aligned(16))) char smem[];
 
     int h, qb;
@@ -93,7 +93,9 @@ __global__ __launch_bounds__(SC_THREADS, (Geo<bf16_t, D, NRT, KS>::MIN_WG)) void
     }
 
     float* const refs = reinterpret_cast<float*>(smem + 2 * G::STAGE_BYTES + G::MERGE_BYTES);  // [wave][RES]
-    float lse[NRT];       // the result: lse2 of query qw0 + qt*32 + l32
+    static_assert(KS == 1 || G::RES == WAVE, "a lane finishes one of the shared rows");
+    constexpr int NR = KS > 1 ? 1 : NRT;
+    float lse[NR];        // the result: lse2 of query qw0 + qt*32 + l32 (KS > 1: qw0 + lane)
     bool frozen = true;   // wave-uniform (in fact workgroup-uniform): which pass this is
     for (;;) {
     float m[NRT], l[NRT];  // statistics of the queries qw0 + qt*32 + l32 this lane keeps
@@ -264,39 +266,35 @@ __global__ __launch_bounds__(SC_THREADS, (Geo<bf16_t, D, NRT, KS>::MIN_WG)) void
         for (int qt = 0; qt < NRT; ++qt) shares[(wave * 2 + half) * G::RES + qt * 32 + l32] = make_float2(m[qt], l[qt]);
         __syncthreads();
     }
+    bool bad = false;
 #pragma unroll
-    for (int qt = 0; qt < NRT; ++qt) {
+    for (int qt = 0; qt < NR; ++qt) {
         constexpr int N = KS > 1 ? 2 * KS : 2;
         float2 v[N];
         if constexpr (KS > 1) {
 #pragma unroll
-            for (int w = 0; w < N; ++w) v[w] = shares[((wave - part) * 2 + w) * G::RES + qt * 32 + l32];  // the same order in every wave
+            for (int w = 0; w < N; ++w) v[w] = shares[((wave - part) * 2 + w) * G::RES + lane];  // the same order in every wave
         } else {
             v[0] = make_float2(m[qt], l[qt]);
             v[1] = make_float2(__shfl_xor(m[qt], 32), __shfl_xor(l[qt], 32));
         }
-        m[qt] = v[0].x;
+        float top = v[0].x, sum = 0.f;
 #pragma unroll
-        for (int w = 1; w < N; ++w) m[qt] = fmaxf(m[qt], v[w].x);
-        const float ms = m[qt] == -INFINITY ? 0.f : m[qt];
-        l[qt] = 0.f;
+        for (int w = 1; w < N; ++w) top = fmaxf(top, v[w].x);
+        const float ms = top == -INFINITY ? 0.f : top;
 #pragma unroll
-        for (int w = 0; w < N; ++w) l[qt] += v[w].y * __builtin_amdgcn_exp2f(v[w].x - ms);
+        for (int w = 0; w < N; ++w) sum += v[w].y * __builtin_amdgcn_exp2f(v[w].x - ms);
+        lse[qt] = KS > 1 ? add_log2(top, sum) : top + __builtin_amdgcn_logf(sum);
+        bad |= qw0 + (KS > 1 ? lane : qt * 32 + l32) < S && !isfinite(lse[qt]);
     }
-    bool bad = false;
-#pragma unroll
-    for (int qt = 0; qt < NRT; ++qt) {
-        lse[qt] = KS > 1 ? add_log2(m[qt], l[qt]) : m[qt] + __builtin_amdgcn_logf(l[qt]);
-        bad |= qw0 + qt * 32 + l32 < S && !isfinite(lse[qt]);
-    }
-    // every wave is past its last read of the stages here as well, so a second pass may refill them
-    if (!frozen || !__syncthreads_or(bad)) break;
+    // every wave is past its last read of the stages here as well, so a second pass may refill them (KS = WAVES: all waves have the same rows)
+    if (!frozen || !(KS == WAVES ? __any(bad) : __syncthreads_or(bad))) break;
     frozen = false;
     }
 #pragma unroll
-    for (int qt = 0; qt < NRT; ++qt) {
-        const int q = qw0 + qt * 32 + l32;
-        if (half == 0 && part == 0 && q < S) p.lse2[(size_t)h * S + q] = lse[qt];
+    for (int qt = 0; qt < NR; ++qt) {
+        const int q = qw0 + (KS > 1 ? lane : qt * 32 + l32);
+        if ((KS > 1 || half == 0) && part == 0 && q < S) p.lse2[(size_t)h * S + q] = lse[qt];
     }
 }
 
@@ -304,9 +302,9 @@ __global__ __launch_bounds__(SC_THREADS, (Geo<bf16_t, D, NRT, KS>::MIN_WG)) void
 // Sweep 2: column sums (and the diagonal) of the probabilities, one key block per workgroup.
 // ------------------------------------------------------------------------------------------------
 
-template <int D, int NRT, int KS>
-__global__ __launch_bounds__(SC_THREADS, (Geo<bf16_t, D, NRT, KS>::MIN_WG)) void colsum_kernel(ScoreParams p) {
-    using G = Geo<bf16_t, D, NRT, KS>;
+template <int D, int NRT, int KS, int WAVES>
+__global__ __launch_bounds__(64 * WAVES, (Geo<bf16_t, D, NRT, KS, WAVES>::MIN_WG)) void colsum_kernel(ScoreParams p) {
+    using G = Geo<bf16_t, D, NRT, KS, WAVES>;
     extern __shared__ __attribute__((aligned(16))) char smem[];
     float* const sLbase = reinterpret_cast<float*>(smem + 2 * G::STAGE_BYTES);
 
@@ -387,7 +385,9 @@ __global__ __launch_bounds__(SC_THREADS, (Geo<bf16_t, D, NRT, KS>::MIN_WG)) void
         const bool skip = causal && iz < kw0;                        // every query lies before every key
         const char* sbuf = smem + buf * G::STAGE_BYTES;
         const float* lbuf = sLbase + buf * G::TILE;
-        const bool hot = !on_diag && !skip;
+        // (eight waves: no subtile past the end is touched, so that their longer stages meet no more zeros in the place of queries)
+        bool hot = !on_diag && !skip;
+        if constexpr (WAVES > 4) hot = hot && ia + (G::SHARE - 1) * 32 < S;
         if (more && !hot) stage_load<G>(st_voff, next_desc, next_lds);  // (the hot path spreads them over its tiles)
         if (hot) {
             // pipelined: exp/sum of the previous tile is issued slice by slice between the MFMAs of tile
@@ -459,6 +459,8 @@ __global__ __launch_bounds__(SC_THREADS, (Geo<bf16_t, D, NRT, KS>::MIN_WG)) void
                     // this 32x32 tile: queries [qmin, qmin+31] against keys [kmin, kmin+31] (wave-uniform tests)
                     const int qmin = ia + qs * 32, kmin = kw0 + kt * 32;
                     if (causal && qmin + 31 < kmin) continue;  // every query lies before every key
+                    if constexpr (WAVES > 4)
+                        if (qmin >= S) continue;
                     f32x16 acc = {0};
 #pragma unroll
                     for (int c = 0; c < G::NCH; ++c) mma_chunk<bf16_t>(acc, qf[c], kf[kt][c]);
@@ -539,28 +541,32 @@ __global__ __launch_bounds__(HM_THREADS) void head_mean_kernel(const float* __re
     scores[j] = acc / (float)H;
 }
 
+template <int D, int NRT, int KS, int WAVES>
+static int limits_of() {
+    using G = Geo<bf16_t, D, NRT, KS, WAVES>;
+    return raise_lds_limits({{reinterpret_cast<const void*>(&rowstats_kernel<D, NRT, KS, WAVES>), G::LDS_ROWSTATS},
+                             {reinterpret_cast<const void*>(&colsum_kernel<D, NRT, KS, WAVES>), G::LDS_COLSUM}});
+}
 template <int D, int NRT>
 static int prepare_sweeps() {
-    auto limits = [](auto ks) {
-        constexpr int KS = decltype(ks)::value;
-        using G = Geo<bf16_t, D, NRT, KS>;
-        return raise_lds_limits({{reinterpret_cast<const void*>(&rowstats_kernel<D, NRT, KS>), G::LDS_ROWSTATS},
-                                 {reinterpret_cast<const void*>(&colsum_kernel<D, NRT, KS>), G::LDS_COLSUM}});
-    };
-    static const int err = first_error([&] { return limits(std::integral_constant<int, 1>{}); }, [&] { return limits(std::integral_constant<int, 2>{}); },
-                                       [&] { return limits(std::integral_constant<int, 4>{}); });
+    static const int err = [] {
+        const int rc = first_error(limits_of<D, NRT, 1, 4>, limits_of<D, NRT, 2, 4>, limits_of<D, NRT, 4, 4>, limits_of<D, NRT, 1, 8>, limits_of<D, NRT, 4, 8>,
+                                   limits_of<D, NRT, 8, 8>);
+        if constexpr (D == 128) return rc ? rc : limits_of<D, NRT, 2, 8>();
+        return rc;
+    }();
     return err;
 }
 
 // which: bit 0 = sweep 1 (row statistics), bit 1 = sweep 2 (column sums)
-template <int D, int NRT, int KS>
+template <int D, int NRT, int KS, int WAVES>
 static int launch_sweeps(const ScoreParams& p_in, int which, hipStream_t st) {
-    using G = Geo<bf16_t, D, NRT, KS>;
+    using G = Geo<bf16_t, D, NRT, KS, WAVES>;
     ScoreParams p = p_in;
     p.n_query_blocks = (p.S + G::BLOCK - 1) / G::BLOCK;
     const unsigned grid = (unsigned)(p.H * p.n_query_blocks);  // as many key blocks
-    if (which & 1) hipLaunchKernelGGL((rowstats_kernel<D, NRT, KS>), dim3(grid), dim3(SC_THREADS), G::LDS_ROWSTATS, st, p);
-    if (which & 2) hipLaunchKernelGGL((colsum_kernel<D, NRT, KS>), dim3(grid), dim3(SC_THREADS), G::LDS_COLSUM, st, p);
+    if (which & 1) hipLaunchKernelGGL((rowstats_kernel<D, NRT, KS, WAVES>), dim3(grid), dim3(G::THREADS), G::LDS_ROWSTATS, st, p);
+    if (which & 2) hipLaunchKernelGGL((colsum_kernel<D, NRT, KS, WAVES>), dim3(grid), dim3(G::THREADS), G::LDS_COLSUM, st, p);
     return (int)hipGetLastError();
 }
 
@@ -577,16 +583,38 @@ static int launch_sweeps(const ScoreParams& p_in, int which, hipStream_t st) {
 // 32.3, n = 256 39.5 / 42.4 / 50.7, n = 384 89.5 / 86.2 / 99.8, n = 448 107 / 122 / 133, n = 512 129 / 144 / 170, n = 576 199 / 194 /
 // 213, n = 896 399 / 411 / 485; d = 64: n = 192 23.7 / 24.7 / 22.6, n = 256 30.4 / 30.9 / 35.9, n = 384 66 / 59 / 68, n = 512 88 / 97 /
 // 110, n = 640 123 / 118 / 135, n = 768 190 / 204 / 232, n = 896 272 / 270 / 307).
+//
+// Workgroups of eight waves have a CU each, stages of 256 rows (half the barriers, and the loads of 256 rows serve all eight) and blocks of
+// 512 / KS rows.  Under the mask a launch is as long as its longest block or as all of them over 256 CUs, which are alike for blocks
+// of about n / 2 rows; without it, as many rounds as its n KS / 2 workgroups fill the CUs.  us a sweep, four waves with the KS above / eight:
+//   d = 128, causal  KS = 8: n = 48 (1500 tokens) 12.7 / 11.0, 64 (512) 7.0 / 6.7, 96 (3000) 25 / 19, (700) 9.4 / 10.6, 128 (1000) 11.1 / 13.4, (2048)
+//                    19.1 / 18.2, (8192) 63 / 51;  KS = 4: n = 144 34 / 28, 160 (1280) 17.5 / 15.2, 192 (6000) 63 / 51, 256 27.2 / 26.8, 288 30 / 35;
+//                    KS = 2: n = 384 48 / 48, 448 62 / 57.5, 512 80 / 76, 640 114 / 117;  KS = 1: n = 768 161 / 166, 896 207 / 196, 1024 267 / 256, 1152
+//                    320 / 338, 4096 3780 / 3770
+//   d = 64, causal   KS = 8: n = 48 (1024) 9.0 / 7.7, (3000) 20 / 15, 80 (5000) 30 / 23, 96 (1500) 11.5 / 11.0, 128 (2048) 14.4 / 14.8, (4096) 25 / 22;
+//                    KS = 4: n = 192 41 / 40, 256 32 / 34;  KS = 1: n = 1024 347 / 334, 1504 685 / 761
+//   d = 128, full    KS = 8: n = 64 (1000) 10.5 / 9.6;  KS = 4: n = 96 12.3 / 11.4, 128 25.6 / 22;  KS = 2: n = 192 53 / 46, 256 41 / 37;  KS = 1: n = 384 84 / 82, 512
+//                    126 / 122, 640 212 / 262, 1024 489 / 475
+//   d = 64, full     KS = 8: n = 48 (3000) 20 / 15.5;  KS = 4: n = 96 16 / 14, 128 35 / 28;  KS = 2: n = 192 35 / 37;  KS = 1: n = 512 174 / 161, 384 103 / 117
 template <int D, int NRT>
 static int launch_sweeps_ks(const ScoreParams& p, long long n, int which, hipStream_t st) {
-    if (!(p.flags & LEMO_CAUSAL)) {
-        if (n <= 64 || (D == 64 && n > 128 && n <= 192)) return launch_sweeps<D, NRT, 4>(p, which, st);
-        if ((2 * n + 255) / 256 % 2 == 1 && n <= (D > 64 ? 640 : 1024)) return launch_sweeps<D, NRT, 2>(p, which, st);
-        return launch_sweeps<D, NRT, 1>(p, which, st);
+    const bool causal = (p.flags & LEMO_CAUSAL) != 0;
+    if (p.S >= 512) {
+        const int longest = D == 128 ? 64 : 80;  // blocks of 64 rows for any length; beyond it, where the longest one decides
+        if (n <= (causal ? longest : 64) || (causal && n <= 128 && p.S >= (D == 128 ? 1500 : 3000))) return launch_sweeps<D, NRT, 8, 8>(p, which, st);
+        if (causal ? D == 128 && n > 128 && n <= 256 && p.S >= 1024 : n <= 128) return launch_sweeps<D, NRT, 4, 8>(p, which, st);
+        if constexpr (D == 128)
+            if (causal ? n > 400 && n <= 512 && p.S >= 1024 : n <= 256) return launch_sweeps<D, NRT, 2, 8>(p, which, st);
+        if (p.S >= 2048 && ((n >= 896 && n <= 1024) || (!causal && n >= 448 && n <= 512))) return launch_sweeps<D, NRT, 1, 8>(p, which, st);
     }
-    if (n <= (D > 64 ? 128 : 256)) return launch_sweeps<D, NRT, 4>(p, which, st);
-    if (n <= (D > 64 ? 640 : 1024)) return launch_sweeps<D, NRT, 2>(p, which, st);
-    return launch_sweeps<D, NRT, 1>(p, which, st);
+    if (!causal) {
+        if (n <= 64 || (D == 64 && n > 128 && n <= 192)) return launch_sweeps<D, NRT, 4, 4>(p, which, st);
+        if ((2 * n + 255) / 256 % 2 == 1 && n <= (D > 64 ? 640 : 1024)) return launch_sweeps<D, NRT, 2, 4>(p, which, st);
+        return launch_sweeps<D, NRT, 1, 4>(p, which, st);
+    }
+    if (n <= (D > 64 ? 128 : 256)) return launch_sweeps<D, NRT, 4, 4>(p, which, st);
+    if (n <= (D > 64 ? 640 : 1024)) return launch_sweeps<D, NRT, 2, 4>(p, which, st);
+    return launch_sweeps<D, NRT, 1, 4>(p, which, st);
 }
 
 int prepare_score(lemo_dtype_t dt, int d) {

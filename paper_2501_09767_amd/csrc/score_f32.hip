@@ -2,7 +2,7 @@
 //
 // The logits come from three-part splits on the bf16 matrix cores (split_f32, mma_split in lemo_common.hpp): 6 MFMAs of 32 x 32 x 16
 // where binary32 MFMAs take 16 times the cycles for 16 elements.  The resident operand is split once; a wave splits its streamed
-// subtile once per stage, between the MFMAs that use it.  All waves of a workgroup share resident rows (KS = 4, d = 128: 2), so
+// subtile once per stage, between the MFMAs that use it.  The waves of a workgroup share resident rows (KS = 4, d = 128: 2; of eight waves twice as many), so
 // that no two of them split the same rows and a stage is one subtile per wave; the statistics are those of score.hip's shared rows.
 //
 // What bounds it: issue.  A 32 x 32 tile of 64 elements (d = 64) is 768 cycles of MFMAs, 176 instructions of splitting over the NRT
@@ -59,11 +59,11 @@ __device__ __forceinline__ bool needs_whole(const Extent& resident, float c2, co
                                             int last, int tid, int wave, int* flags) {
     const float limit = 0x1p102f / (c2 * (float)D);
     bool look = __any(resident.small() | (resident.most > limit));
-    if constexpr (G::KS < SC_WAVES) {  // (otherwise all waves hold the same rows; __syncthreads_or took 0.4 us of each sweep)
+    if constexpr (G::KS < G::WAVES) {  // (otherwise all waves hold the same rows; __syncthreads_or took 0.4 us of each sweep)
         if (tid % WAVE == 0) flags[wave] = look;
         __syncthreads();
 #pragma unroll
-        for (int w = 0; w < SC_WAVES; ++w) look |= flags[w] != 0;
+        for (int w = 0; w < G::WAVES; ++w) look |= flags[w] != 0;
     }
     if (!look) return false;
     Extent streamed;
@@ -108,9 +108,9 @@ template <typename G> struct Streamed32 {
 };
 
 // Sweep 1 (see rowstats_kernel): lse2 of every query row.
-template <int D, int NRT, int KS>
-__global__ __launch_bounds__(SC_THREADS, (Geo<float, D, NRT, KS>::MIN_WG)) void rowstats_f32_kernel(ScoreParams p) {
-    using G = Geo<float, D, NRT, KS>;
+template <int D, int NRT, int KS, int WAVES>
+__global__ __launch_bounds__(64 * WAVES, (Geo<float, D, NRT, KS, WAVES>::MIN_WG)) void rowstats_f32_kernel(ScoreParams p) {
+    using G = Geo<float, D, NRT, KS, WAVES>;
     static_assert(KS > 1 && G::SHARE == 1, "one subtile per wave and stage");
     constexpr int NM = Streamed32<G>::NM;
     extern __shared__ __attribute__((aligned(16))) char smem[];
@@ -153,7 +153,8 @@ __global__ __launch_bounds__(SC_THREADS, (Geo<float, D, NRT, KS>::MIN_WG)) void 
 
     float2* const shares = reinterpret_cast<float2*>(smem + 2 * G::STAGE_BYTES);                // [wave][half][RES]
     float* const refs = reinterpret_cast<float*>(smem + 2 * G::STAGE_BYTES + G::MERGE_BYTES);  // [wave][RES]
-    float lse[NRT];       // the result: lse2 of query qw0 + qt*32 + l32
+    float lse;            // the result: lse2 of query qw0 + lane % RES
+    const int lq = lane % G::RES;
     // workgroup-uniform: which pass this is
     bool frozen = !needs_whole<G, D>(extent, c2, Kb, p.k_ts, k_off, 0, causal ? q_last + 1 : S, tid, wave, reinterpret_cast<int*>(shares));
     for (;;) {
@@ -264,37 +265,29 @@ __global__ __launch_bounds__(SC_THREADS, (Geo<float, D, NRT, KS>::MIN_WG)) void 
 #pragma unroll
     for (int qt = 0; qt < NRT; ++qt) shares[(wave * 2 + half) * G::RES + qt * 32 + l32] = make_float2(m[qt], l[qt]);
     __syncthreads();
-    bool bad = false;
+    float2 v[2 * KS];
 #pragma unroll
-    for (int qt = 0; qt < NRT; ++qt) {
-        float2 v[2 * KS];
+    for (int w = 0; w < 2 * KS; ++w) v[w] = shares[((wave - part) * 2 + w) * G::RES + lq];  // the same order in every wave
+    float top = v[0].x, sum = 0.f;
 #pragma unroll
-        for (int w = 0; w < 2 * KS; ++w) v[w] = shares[((wave - part) * 2 + w) * G::RES + qt * 32 + l32];  // the same order in every wave
-        m[qt] = v[0].x;
+    for (int w = 1; w < 2 * KS; ++w) top = fmaxf(top, v[w].x);
+    const float ms = top == -INFINITY ? 0.f : top;
 #pragma unroll
-        for (int w = 1; w < 2 * KS; ++w) m[qt] = fmaxf(m[qt], v[w].x);
-        const float ms = m[qt] == -INFINITY ? 0.f : m[qt];
-        l[qt] = 0.f;
-#pragma unroll
-        for (int w = 0; w < 2 * KS; ++w) l[qt] += v[w].y * __builtin_amdgcn_exp2f(v[w].x - ms);
-        lse[qt] = add_log2(m[qt], l[qt]);
-        bad |= qw0 + qt * 32 + l32 < S && !isfinite(lse[qt]);
-    }
-    // every wave is past its last read of the stages here as well, so a second pass may refill them
-    if (!frozen || !__syncthreads_or(bad)) break;
+    for (int w = 0; w < 2 * KS; ++w) sum += v[w].y * __builtin_amdgcn_exp2f(v[w].x - ms);
+    lse = add_log2(top, sum);
+    const bool bad = qw0 + lq < S && !isfinite(lse);
+    // every wave is past its last read of the stages here as well, so a second pass may refill them (KS = WAVES: all waves have the same rows)
+    if (!frozen || !(KS == WAVES ? __any(bad) : __syncthreads_or(bad))) break;
     frozen = false;
     }
-#pragma unroll
-    for (int qt = 0; qt < NRT; ++qt) {
-        const int q = qw0 + qt * 32 + l32;
-        if (half == 0 && part == 0 && q < S) p.lse2[(size_t)h * S + q] = lse[qt];
-    }
+    const int q = qw0 + lq;
+    if (lane < G::RES && part == 0 && q < S) p.lse2[(size_t)h * S + q] = lse;
 }
 
 // Sweep 2 (see colsum_kernel): column sums (and the diagonal) of the probabilities, one key block per workgroup.
-template <int D, int NRT, int KS>
-__global__ __launch_bounds__(SC_THREADS, (Geo<float, D, NRT, KS>::MIN_WG)) void colsum_f32_kernel(ScoreParams p) {
-    using G = Geo<float, D, NRT, KS>;
+template <int D, int NRT, int KS, int WAVES>
+__global__ __launch_bounds__(64 * WAVES, (Geo<float, D, NRT, KS, WAVES>::MIN_WG)) void colsum_f32_kernel(ScoreParams p) {
+    using G = Geo<float, D, NRT, KS, WAVES>;
     constexpr int NM = Streamed32<G>::NM;
     extern __shared__ __attribute__((aligned(16))) char smem[];
     float* const sLbase = reinterpret_cast<float*>(smem + 2 * G::STAGE_BYTES);
@@ -366,7 +359,7 @@ __global__ __launch_bounds__(SC_THREADS, (Geo<float, D, NRT, KS>::MIN_WG)) void 
         if (more) pre_l = fetch_l(t - 1);
         const int qmin = t * G::TILE + part * 32;                            // this wave's subtile: queries [qmin, qmin + 31]
         const bool on_diag = qmin <= kw0 + G::RES - 1 && qmin + 31 >= kw0;  // they meet the diagonal band of this wave
-        const bool skip = causal && qmin + 31 < kw0;                        // every query lies before every key
+        const bool skip = (causal && qmin + 31 < kw0) || qmin >= S;         // every query lies before every key, or past the end
         const char* sbuf = smem + buf * G::STAGE_BYTES;
         const float* lbuf = sLbase + buf * G::TILE;
         const bool hot = !on_diag && !skip && !whole;
@@ -472,31 +465,38 @@ __global__ __launch_bounds__(SC_THREADS, (Geo<float, D, NRT, KS>::MIN_WG)) void 
     }
 }
 
-template <int D, int NRT, int KS>
+template <int D, int NRT, int KS, int WAVES>
 static int prepare_f32() {
-    using G = Geo<float, D, NRT, KS>;
-    static const int err = raise_lds_limits({{reinterpret_cast<const void*>(&rowstats_f32_kernel<D, NRT, KS>), G::LDS_ROWSTATS},
-                                             {reinterpret_cast<const void*>(&colsum_f32_kernel<D, NRT, KS>), G::LDS_COLSUM}});
+    using G = Geo<float, D, NRT, KS, WAVES>;
+    static const int err = raise_lds_limits({{reinterpret_cast<const void*>(&rowstats_f32_kernel<D, NRT, KS, WAVES>), G::LDS_ROWSTATS},
+                                             {reinterpret_cast<const void*>(&colsum_f32_kernel<D, NRT, KS, WAVES>), G::LDS_COLSUM}});
     return err;
 }
 
-template <int D, int NRT, int KS>
+template <int D, int NRT, int KS, int WAVES>
 static int launch_f32(const ScoreParams& p_in, int which, hipStream_t st) {
-    using G = Geo<float, D, NRT, KS>;
+    using G = Geo<float, D, NRT, KS, WAVES>;
     ScoreParams p = p_in;
     p.n_query_blocks = (p.S + G::BLOCK - 1) / G::BLOCK;
     const unsigned grid = (unsigned)(p.H * p.n_query_blocks);  // as many key blocks
-    if (which & 1) hipLaunchKernelGGL((rowstats_f32_kernel<D, NRT, KS>), dim3(grid), dim3(SC_THREADS), G::LDS_ROWSTATS, st, p);
-    if (which & 2) hipLaunchKernelGGL((colsum_f32_kernel<D, NRT, KS>), dim3(grid), dim3(SC_THREADS), G::LDS_COLSUM, st, p);
+    if (which & 1) hipLaunchKernelGGL((rowstats_f32_kernel<D, NRT, KS, WAVES>), dim3(grid), dim3(G::THREADS), G::LDS_ROWSTATS, st, p);
+    if (which & 2) hipLaunchKernelGGL((colsum_f32_kernel<D, NRT, KS, WAVES>), dim3(grid), dim3(G::THREADS), G::LDS_COLSUM, st, p);
     return (int)hipGetLastError();
 }
 
-int prepare_sweeps_f32(int d) { return d == 128 ? prepare_f32<128, 1, 2>() : first_error(prepare_f32<64, 1, 4>, prepare_f32<64, 2, 4>); }
+int prepare_sweeps_f32(int d) { return d == 128 ? first_error(prepare_f32<128, 1, 2, 4>, prepare_f32<128, 1, 4, 8>) : first_error(prepare_f32<64, 1, 4, 4>, prepare_f32<64, 2, 4, 4>, prepare_f32<64, 1, 8, 8>); }
 
 int launch_sweeps_f32(const ScoreParams& p, int d, int which, hipStream_t st) {
     const long long blocks256 = (long long)p.H * ((p.S + 255) / 256);
-    if (d == 128) return launch_f32<128, 1, 2>(p, which, st);
-    return blocks256 <= 192 ? launch_f32<64, 1, 4>(p, which, st) : launch_f32<64, 2, 4>(p, which, st);
+    // Eight waves, twice the sharers of a row and twice the rows of a stage, one workgroup per CU: where the CUs then have at most one, or
+    // the longest block decides.  us a sweep, four / eight: d = 64 1024 tokens, 4 heads 13.2 / 11.6, 500, 16 9.0 / 8.7, 300, 4 7.6 / 8.2, 3000, 4
+    // 32 / 25, 4000, 4 41 / 38, 1024, 12 13.5 / 16, full 2000, 4 22.5 / 19.4, 2500, 4 37 / 41.5; d = 128 500, 16 19 / 17.5, 1000, 16 33 / 28.5,
+    // 2000, 12 62 / 52, 1000, 32 38 / 39, full 700, 16 24.6 / 23.5.
+    const bool causal = (p.flags & LEMO_CAUSAL) != 0;
+    if (d == 128 && p.S >= 384 && (blocks256 <= 64 || (causal && blocks256 <= 128 && p.S >= 1500))) return launch_f32<128, 1, 4, 8>(p, which, st);
+    if (d == 64 && p.S >= 384 && (blocks256 <= 32 || (causal && blocks256 <= 64 && p.S >= 3000))) return launch_f32<64, 1, 8, 8>(p, which, st);
+    if (d == 128) return launch_f32<128, 1, 2, 4>(p, which, st);
+    return blocks256 <= 192 ? launch_f32<64, 1, 4, 4>(p, which, st) : launch_f32<64, 2, 4, 4>(p, which, st);
 }
 
 }  // namespace lemo

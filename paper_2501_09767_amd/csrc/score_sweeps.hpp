@@ -28,10 +28,11 @@ constexpr int SC_THREADS = 64 * SC_WAVES;
 // KS = waves that share resident rows: KS consecutive waves hold the same rows and take every stage's streamed subtiles
 // in shares; their statistics are put together through LDS at the end.  A block is then 1/KS as many rows and takes 1/KS
 // as long, at KS times the loads into LDS per flop.
-template <typename T, int D, int NRT_, int KS_> struct Geo {
-    static constexpr int NRT = NRT_, KS = KS_;
+// More than four waves: one workgroup per CU where there are few, a stage has as many more rows.
+template <typename T, int D, int NRT_, int KS_, int WAVES_ = SC_WAVES> struct Geo {
+    static constexpr int NRT = NRT_, KS = KS_, WAVES = WAVES_, THREADS = 64 * WAVES;
     static constexpr int RES = 32 * NRT;             // resident rows per wave
-    static constexpr int BLOCK = SC_WAVES / KS * RES; // resident rows per workgroup
+    static constexpr int BLOCK = WAVES / KS * RES; // resident rows per workgroup
     static constexpr int ROWB = D * (int)sizeof(T);  // bytes per head row
     static constexpr int NCH = ROWB / 32;            // MFMA chunks per row
     static constexpr int CPR = ROWB / 16;            // 16-byte pieces per row
@@ -41,20 +42,20 @@ template <typename T, int D, int NRT_, int KS_> struct Geo {
     __device__ static constexpr int swz(int row) { return CPR >= 16 ? (row & 15) : ((row >> 1) & (CPR - 1)); }
     // byte offset inside a stage of the fragment piece (chunk c, half) of row `row`
     __device__ static constexpr int frag(int row, int c, int half) { return row * ROWB + (((2 * c + half) ^ swz(row)) << 4); }
-    static constexpr int TILE = ROWB > 256 ? 64 : 128; // streamed rows per LDS stage (two stages; long enough to hide a global load)
+    static constexpr int TILE = (ROWB > 256 ? 64 : 128) * WAVES / SC_WAVES;  // streamed rows per LDS stage (two stages; long enough to hide a global load)
     static constexpr int NSUB = TILE / 32;           // 32-row MFMA subtiles per stage
     static constexpr int SHARE = NSUB / KS;          // of them, those a wave takes
-    static constexpr int NLOAD = TILE * CPR / SC_THREADS;  // 16-byte global loads per thread per stage
-    static constexpr int ROWS_PER_LOAD = SC_THREADS / CPR; // rows covered by one load of the whole workgroup
+    static constexpr int NLOAD = TILE * CPR / THREADS;  // 16-byte global loads per thread per stage
+    static constexpr int ROWS_PER_LOAD = THREADS / CPR; // rows covered by one load of the whole workgroup
     static constexpr int STAGE_BYTES = TILE * STRIDE;
-    static constexpr int MERGE_BYTES = KS > 1 ? SC_WAVES * RES * 16 : 0;  // two floats per half-wave and resident row
-    static constexpr int REF_BYTES = KS > 1 ? SC_WAVES * RES * (int)sizeof(float) : 0;  // a share's maximum of the first stage per row
+    static constexpr int MERGE_BYTES = KS > 1 ? WAVES * RES * 16 : 0;  // two floats per half-wave and resident row
+    static constexpr int REF_BYTES = KS > 1 ? WAVES * RES * (int)sizeof(float) : 0;  // a share's maximum of the first stage per row
     static constexpr int LDS_ROWSTATS = 2 * STAGE_BYTES + MERGE_BYTES + REF_BYTES;
     static constexpr int LDS_COLSUM = 2 * STAGE_BYTES + 2 * TILE * (int)sizeof(float) + MERGE_BYTES;
-    static constexpr int MIN_WG = (ROWB * NRT > 512 || NRT > 2 || SC_WAVES > 4) ? 1 : ROWB > 128 ? 2 : 3;  // workgroups per CU the register budget is set for
-    static_assert(TILE * CPR % SC_THREADS == 0, "tile must split evenly over the workgroup");
+    static constexpr int MIN_WG = WAVES > 4 ? 2 : (ROWB * NRT > 512 || NRT > 2) ? 1 : ROWB > 128 ? 2 : 3;  // waves per SIMD the register budget is set for
+    static_assert(TILE * CPR % THREADS == 0, "tile must split evenly over the workgroup");
     static_assert(KS == 1 || (BLOCK <= TILE && NLOAD * BLOCK % TILE == 0), "shared rows are loaded through one stage");
-    static_assert(SC_WAVES % KS == 0 && NSUB % KS == 0, "the shares must be whole subtiles");
+    static_assert(WAVES % KS == 0 && NSUB % KS == 0, "the shares must be whole subtiles");
 };
 
 // 16 bytes at byte offset `byte_off` of row `row` of a [rows, heads, D] tensor, zero beyond `nrows`
@@ -65,7 +66,7 @@ __device__ __forceinline__ u32x4 load_piece(const T* base, long long tok_stride,
     return v;
 }
 
-// Stage loads: LDS-direct (no staging registers, no LDS write instructions).  Unit u = i * SC_THREADS + tid of a stage is
+// Stage loads: LDS-direct (no staging registers, no LDS write instructions).  Unit u = i * THREADS + tid of a stage is
 // its LDS bytes [16u, 16u + 16) = row u / CPR, position u % CPR; the lane fetches the piece that belongs there.  The
 // loads go through a buffer descriptor rebuilt per stage (wave-uniform base = first row of the stage, size = bytes up to
 // the end of the last valid row), so pieces of rows beyond the end of the tensor arrive as zeros.
@@ -73,7 +74,7 @@ template <typename G>
 __device__ __forceinline__ void stage_offsets(int (&voff)[G::NLOAD], int row_bytes, int tid) {
 #pragma unroll
     for (int i = 0; i < G::NLOAD; ++i) {
-        const int u = i * SC_THREADS + tid, row = u / G::CPR, piece = (u % G::CPR) ^ G::swz(row);
+        const int u = i * G::THREADS + tid, row = u / G::CPR, piece = (u % G::CPR) ^ G::swz(row);
         voff[i] = row * row_bytes + piece * 16;
     }
 }
@@ -87,7 +88,7 @@ __device__ __forceinline__ u32x4 stage_desc(const char* head, int row_bytes, int
 template <typename G>
 __device__ __forceinline__ void stage_load(const int (&voff)[G::NLOAD], u32x4 rsrc, unsigned lds_stage) {
 #pragma unroll
-    for (int i = 0; i < G::NLOAD; ++i) lds_direct_b128(rsrc, lds_stage + i * (SC_THREADS * 16), voff[i]);
+    for (int i = 0; i < G::NLOAD; ++i) lds_direct_b128(rsrc, lds_stage + i * (G::THREADS * 16), voff[i]);
 }
 // the share of pipeline slot `ti` of `nslots`: issued one slot at a time, the loads do not queue up behind each other
 // in the CU's vector-memory pipe (16 cycles per 1 KB instruction) while the wave stands still
@@ -95,7 +96,7 @@ template <typename G>
 __device__ __forceinline__ void stage_load_slot(const int (&voff)[G::NLOAD], u32x4 rsrc, unsigned lds_stage, int ti, int nslots) {
 #pragma unroll
     for (int i = 0; i < G::NLOAD; ++i)
-        if (i >= ti * G::NLOAD / nslots && i < (ti + 1) * G::NLOAD / nslots) lds_direct_b128(rsrc, lds_stage + i * (SC_THREADS * 16), voff[i]);
+        if (i >= ti * G::NLOAD / nslots && i < (ti + 1) * G::NLOAD / nslots) lds_direct_b128(rsrc, lds_stage + i * (G::THREADS * 16), voff[i]);
 }
 // A wave's resident fragments (row `row0` of the block on), from the block's rows in an LDS stage of the same layout.  For waves
 // that share rows: loaded straight from memory, 32 bytes of each of 32 rows at a time and by every sharer, the block's rows
@@ -108,7 +109,7 @@ __device__ __forceinline__ void load_resident(const char* head, int row_bytes, i
     stage_offsets<G>(voff, row_bytes, tid);
     const u32x4 desc = stage_desc<G>(head, row_bytes, first, nrows, true);
 #pragma unroll
-    for (int i = 0; i < G::NLOAD * G::BLOCK / G::TILE; ++i) lds_direct_b128(desc, lds_stage + i * (SC_THREADS * 16), voff[i]);
+    for (int i = 0; i < G::NLOAD * G::BLOCK / G::TILE; ++i) lds_direct_b128(desc, lds_stage + i * (G::THREADS * 16), voff[i]);
 }
 // before the barrier that ends a stage: this wave's loads of the next stage have landed, its reads of this one returned
 __device__ __forceinline__ void stage_settle() {

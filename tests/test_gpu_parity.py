@@ -393,6 +393,39 @@ def test_score_larger_blocks(lemo, S, H, Hkv, d):
         assert_scores_close(got, want, "scores")
 
 
+@pytest.mark.parametrize("S,H,Hkv,d,flags,dtype", [
+    # blocks of 64, 128, 256 and 512 rows on eight waves: just past the shortest, ragged, whole 128 rows but not whole stages of 256
+    (513, 3, 1, 128, 3, "bf16"), (1501, 20, 5, 128, 1, "bf16"), (640, 5, 5, 128, 0, "bf16"), (1152, 33, 11, 128, 3, "bf16"), (1040, 33, 33, 128, 1, "bf16"),
+    (640, 40, 8, 128, 2, "bf16"), (777, 40, 40, 128, 0, "bf16"), (1152, 90, 30, 128, 3, "bf16"), (1030, 84, 84, 128, 3, "bf16"), (640, 70, 70, 128, 2, "bf16"),
+    (777, 60, 20, 128, 0, "bf16"), (2176, 100, 25, 128, 3, "bf16"), (2050, 100, 100, 128, 1, "bf16"), (2176, 50, 50, 128, 0, "bf16"),
+    (515, 4, 4, 64, 3, "bf16"), (3001, 10, 5, 64, 3, "bf16"), (640, 40, 40, 64, 2, "bf16"), (600, 40, 8, 64, 0, "bf16"), (2176, 100, 50, 64, 3, "bf16"), (2049, 50, 50, 64, 0, "bf16"),
+    (640, 5, 5, 64, 3, "f32"), (390, 5, 1, 64, 2, "f32"), (3001, 4, 4, 64, 3, "f32"), (385, 7, 7, 128, 0, "f32"), (1501, 20, 4, 128, 3, "f32")])
+@pytest.mark.parametrize("gone", [False, True])
+def test_score_workgroups_of_eight_waves(lemo, S, H, Hkv, d, flags, dtype, gone):
+    """Column sums and diagonals against 64 bits: a key whose logits overtake the frozen reference of sweep 1, or (whole 128 rows: no
+    zeros in the place of a query meet it) one at minus infinity that nobody looks at."""
+    if gone and S % 128:
+        pytest.skip("zeros fill up the last rows")
+    say(f"[score] eight waves S={S} H={H}/{Hkv} d={d} flags={flags} {dtype} gone={gone}")
+    Q, K = wl.tiny_qk(S, H, Hkv, d, dtype, seed=S + H + d, heavy=4)
+    at = S // 2 + 40
+    if gone:
+        Q[..., 5] = Q[..., 5].abs() + 0.5
+        K[at, :, 5] = -math.inf
+    else:
+        K[at, 0] = K[at, 0] * 40
+    _, col, dg = run_score(lemo, Q, K, 128, flags)
+    q, k = Q.cuda().double(), K.cuda().double()
+    later = torch.ones((S, S), dtype=torch.bool, device="cuda").triu(1)
+    for h in range(H):
+        x = q[:, h] @ k[:, h * Hkv // H].t().contiguous() / math.sqrt(d)
+        if flags & 1:
+            x.masked_fill_(later, -math.inf)
+        pr = torch.softmax(x, dim=1)
+        assert_scores_close(col[h], pr.sum(0).cpu().numpy(), f"colsum of head {h}")
+        assert_scores_close(dg[h], pr.diagonal().cpu().numpy(), f"diagonal of head {h}")
+
+
 @pytest.mark.parametrize("S,H,Hkv,d", [(300, 104, 52, 64), (530, 70, 10, 64), (300, 100, 25, 128)])
 def test_score_larger_blocks_f32(lemo, S, H, Hkv, d):
     """binary32 launches of more than 192 blocks (two resident subtiles per wave at d = 64)."""
