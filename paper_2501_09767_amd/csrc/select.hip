@@ -248,33 +248,32 @@ __global__ __launch_bounds__(256) void block_mean_kernel(const float* __restrict
 
 // One workgroup.  Phase 1: start[n] = number of kept tokens in blocks before n (prefix sum over the kept blocks'
 // lengths, carried from chunk to chunk of 1024 blocks).  Phase 2: every token of a kept block writes its own index.
+// The scan is one inside the wavefronts and a pass over their totals (us, twenty barriers of a scan through LDS / now: 64 blocks of 64
+// 3.7 / 2.4, 1024 of 32 8.7 / 7.4).
 constexpr int THR_THREADS = 1024;
 __global__ __launch_bounds__(THR_THREADS) void select_threshold_kernel(const float* __restrict__ token_blocks, int S, int b, int nb,
                                                                        float t_host, const float* __restrict__ t_dev,
                                                                        int* __restrict__ kept, int* __restrict__ kept_count) {
     extern __shared__ int start[];  // [nb]; -1 marks a dropped block
-    __shared__ int scan[THR_THREADS];
-    __shared__ int base;
-    const int tid = threadIdx.x;
+    __shared__ int wave_total[THR_THREADS / WAVE];
+    const int tid = threadIdx.x, wave = tid / WAVE;
     const float T = t_dev ? t_dev[0] : t_host;
-    if (tid == 0) base = 0;
-    __syncthreads();
+    int base = 0;
     for (int n0 = 0; n0 < nb; n0 += THR_THREADS) {
         const int n = n0 + tid;
         int len = 0;
         if (n < nb && token_blocks[n] >= T) len = min(b, S - n * b);
-        scan[tid] = len;
+        const int incl = (int)wave_inclusive_scan((uint32_t)len);
+        if (tid % WAVE == WAVE - 1) wave_total[wave] = incl;
         __syncthreads();
-        for (int off = 1; off < THR_THREADS; off <<= 1) {
-            const int v = tid >= off ? scan[tid - off] : 0;
-            __syncthreads();
-            scan[tid] += v;
-            __syncthreads();
+        int before = base;
+#pragma unroll
+        for (int w = 0; w < THR_THREADS / WAVE; ++w) {
+            if (w < wave) before += wave_total[w];
+            base += wave_total[w];
         }
-        if (n < nb) start[n] = len ? base + scan[tid] - len : -1;
-        __syncthreads();
-        if (tid == 0) base += scan[THR_THREADS - 1];
-        __syncthreads();
+        if (n < nb) start[n] = len ? before + incl - len : -1;
+        __syncthreads();  // (the totals have been read; behind the last chunk: the starts are complete)
     }
     if (tid == 0) kept_count[0] = base;
     for (int j = tid; j < S; j += THR_THREADS) {
