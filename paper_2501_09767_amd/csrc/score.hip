@@ -562,6 +562,7 @@ static int prepare_sweeps() {
 template <int D, int NRT, int KS, int WAVES>
 static int launch_sweeps(const ScoreParams& p_in, int which, hipStream_t st) {
     using G = Geo<bf16_t, D, NRT, KS, WAVES>;
+    static_assert(G::LONGEST_PITCH >= (PITCH_END - 8) * 2, "a stage reaches all its rows at every pitch");
     ScoreParams p = p_in;
     p.n_query_blocks = (p.S + G::BLOCK - 1) / G::BLOCK;
     const unsigned grid = (unsigned)(p.H * p.n_query_blocks);  // as many key blocks

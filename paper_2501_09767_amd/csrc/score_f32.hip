@@ -476,6 +476,7 @@ static int prepare_f32() {
 template <int D, int NRT, int KS, int WAVES>
 static int launch_f32(const ScoreParams& p_in, int which, hipStream_t st) {
     using G = Geo<float, D, NRT, KS, WAVES>;
+    static_assert(G::LONGEST_PITCH >= (PITCH_END - 4) * 4 || (D == 64 && WAVES == 8), "a stage reaches all its rows at every pitch");
     ScoreParams p = p_in;
     p.n_query_blocks = (p.S + G::BLOCK - 1) / G::BLOCK;
     const unsigned grid = (unsigned)(p.H * p.n_query_blocks);  // as many key blocks
@@ -494,7 +495,9 @@ int launch_sweeps_f32(const ScoreParams& p, int d, int which, hipStream_t st) {
     // 2000, 12 62 / 52, 1000, 32 38 / 39, full 700, 16 24.6 / 23.5.
     const bool causal = (p.flags & LEMO_CAUSAL) != 0;
     if (d == 128 && p.S >= 384 && (blocks256 <= 64 || (causal && blocks256 <= 128 && p.S >= 1500))) return launch_f32<128, 1, 4, 8>(p, which, st);
-    if (d == 64 && p.S >= 384 && (blocks256 <= 32 || (causal && blocks256 <= 64 && p.S >= 3000))) return launch_f32<64, 1, 8, 8>(p, which, st);
+    // (d = 64: their 256 rows of a stage must be within reach, up to 8.4 MB of pitch)
+    const bool reach = (p.q_ts > p.k_ts ? p.q_ts : p.k_ts) * 4 <= Geo<float, 64, 1, 8, 8>::LONGEST_PITCH;
+    if (d == 64 && reach && p.S >= 384 && (blocks256 <= 32 || (causal && blocks256 <= 64 && p.S >= 3000))) return launch_f32<64, 1, 8, 8>(p, which, st);
     if (d == 128) return launch_f32<128, 1, 2, 4>(p, which, st);
     return blocks256 <= 192 ? launch_f32<64, 1, 4, 4>(p, which, st) : launch_f32<64, 2, 4, 4>(p, which, st);
 }

@@ -48,6 +48,8 @@ template <typename T, int D, int NRT_, int KS_, int WAVES_ = SC_WAVES> struct Ge
     static constexpr int NLOAD = TILE * CPR / THREADS;  // 16-byte global loads per thread per stage
     static constexpr int ROWS_PER_LOAD = THREADS / CPR; // rows covered by one load of the whole workgroup
     static constexpr int STAGE_BYTES = TILE * STRIDE;
+    // Longest pitch of a streamed token, in bytes: stage_offsets and stage_desc have 31 bits, and a row beyond arrives as zeros
+    static constexpr long long LONGEST_PITCH = (0x7fffffffLL - ROWB) / (TILE - 1);
     static constexpr int MERGE_BYTES = KS > 1 ? WAVES * RES * 16 : 0;  // two floats per half-wave and resident row
     static constexpr int REF_BYTES = KS > 1 ? WAVES * RES * (int)sizeof(float) : 0;  // a share's maximum of the first stage per row
     static constexpr int LDS_ROWSTATS = 2 * STAGE_BYTES + MERGE_BYTES + REF_BYTES;
@@ -57,6 +59,8 @@ template <typename T, int D, int NRT_, int KS_, int WAVES_ = SC_WAVES> struct Ge
     static_assert(KS == 1 || (BLOCK <= TILE && NLOAD * BLOCK % TILE == 0), "shared rows are loaded through one stage");
     static_assert(WAVES % KS == 0 && NSUB % KS == 0, "the shares must be whole subtiles");
 };
+
+constexpr long long PITCH_END = 1 << 22;  // token pitches are below this many elements, whole 16-byte pieces (host: check_qk)
 
 // 16 bytes at byte offset `byte_off` of row `row` of a [rows, heads, D] tensor, zero beyond `nrows`
 template <typename T>

@@ -426,6 +426,25 @@ def test_score_workgroups_of_eight_waves(lemo, S, H, Hkv, d, flags, dtype, gone)
         assert_scores_close(dg[h], pr.diagonal().cpu().numpy(), f"diagonal of head {h}")
 
 
+@pytest.mark.parametrize("S,d,dtype", [(400, 64, "f32"), (400, 128, "f32"), (520, 64, "bf16"), (520, 128, "bf16")])
+def test_score_longest_pitch(lemo, S, d, dtype):
+    """Tokens as far apart as the entry point takes them: every row of a stage arrives."""
+    say(f"[score] longest pitch S={S} d={d} {dtype}")
+    H, Hkv = 4, 2
+    Q, K = wl.tiny_qk(S, H, Hkv, d, dtype, seed=S + d, heavy=4)
+    pitch = (1 << 22) - 16 // Q.element_size()
+    wide = torch.empty((S - 1) * pitch + 2 * H * d, dtype=Q.dtype, device="cuda")
+    Qw = wide.as_strided((S, H, d), (pitch, d, 1)).copy_(Q)
+    Kw = wide.as_strided((S, Hkv, d), (pitch, d, 1), H * d).copy_(K)
+    for flags in (0, 3):
+        want, want_col, want_dg = run_score(lemo, Q, K, 128, flags)
+        for a, b in ((Qw, K), (Q, Kw), (Qw, Kw)):
+            got, col, dg = run_score(lemo, a, b, 128, flags)
+            assert_scores_close(got, want, "scores")
+            assert_scores_close(col, want_col, "column sums")
+            assert_scores_close(dg, want_dg, "diagonals")
+
+
 @pytest.mark.parametrize("S,H,Hkv,d", [(300, 104, 52, 64), (530, 70, 10, 64), (300, 100, 25, 128)])
 def test_score_larger_blocks_f32(lemo, S, H, Hkv, d):
     """binary32 launches of more than 192 blocks (two resident subtiles per wave at d = 64)."""

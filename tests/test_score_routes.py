@@ -1,0 +1,118 @@
+"""Which kernels the scoring sweeps take, and what these can reach (CPU only).  The library is run against a HIP runtime that only
+notes what is asked of it."""
+import ctypes
+import json
+import os
+import re
+import subprocess
+import sys
+
+import pytest
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+LIB = os.path.join(ROOT, "paper_2501_09767_amd", "liblemo_hip.so")
+
+RUNTIME = r"""
+#include <stddef.h>
+#include <string.h>
+typedef struct { unsigned x, y, z; } dim3;
+static struct { const void* kernel; const char* name; } known[4096];
+static int n_known;
+static dim3 grid, block;
+static size_t lds;
+static void* stream;
+const char* launched[64];
+int threads[64], blocks[64], n_launched;
+void** __hipRegisterFatBinary(const void* data) { (void)data; return (void**)known; }
+void __hipUnregisterFatBinary(void** m) { (void)m; }
+void __hipRegisterFunction(void** m, const void* f, char* a, const char* name, unsigned n, void* t, void* b, dim3* bd, dim3* gd, int* w) {
+    (void)m; (void)a; (void)n; (void)t; (void)b; (void)bd; (void)gd; (void)w;
+    if (n_known < 4096) { known[n_known].kernel = f; known[n_known++].name = strdup(name); }
+}
+int __hipPushCallConfiguration(dim3 g, dim3 b, size_t l, void* s) { grid = g; block = b; lds = l; stream = s; return 0; }
+int __hipPopCallConfiguration(dim3* g, dim3* b, size_t* l, void** s) { *g = grid; *b = block; *l = lds; *s = stream; return 0; }
+int hipFuncSetAttribute(const void* f, int what, int bytes) { (void)f; (void)what; (void)bytes; return 0; }
+int hipGetLastError(void) { return 0; }
+int hipLaunchKernel(const void* f, dim3 g, dim3 b, void** args, size_t l, void* s) {
+    (void)args; (void)l; (void)s;
+    for (int i = 0; i < n_known && n_launched < 64; ++i)
+        if (known[i].kernel == f) { launched[n_launched] = known[i].name; blocks[n_launched] = (int)g.x; threads[n_launched++] = (int)b.x; }
+    return 0;
+}
+"""
+P = 1 << 20  # in the place of device addresses: nothing is read
+F32, BF16 = 0, 1
+CAUSAL = 1
+LONGEST = {F32: (1 << 22) - 4, BF16: (1 << 22) - 8}  # token pitch, elements
+
+
+def run(runtime):
+    """In a process of its own: calls from standard input, the kernels each of them launched to standard output."""
+    hip = ctypes.CDLL(runtime, mode=ctypes.RTLD_GLOBAL)
+    lib = ctypes.CDLL(LIB)
+    kinds = {"p": ctypes.c_void_p, "i": ctypes.c_int32, "l": ctypes.c_int64, "f": ctypes.c_float}
+    lib.lemo_score_rowstats.argtypes = [kinds[k] for k in "ppliiiillllfipp"]
+    lib.lemo_score_colsums.argtypes = [kinds[k] for k in "ppliiiillllfiipppp"]
+    seen = ctypes.c_int.in_dll(hip, "n_launched")
+    names, threads = (ctypes.c_char_p * 64).in_dll(hip, "launched"), (ctypes.c_int * 64).in_dll(hip, "threads")
+    out = []
+    for dt, d, S, H, flags, q_pitch, k_pitch in json.load(sys.stdin):
+        seen.value = 0
+        assert lib.lemo_score_rowstats(P, P, S, H, H, d, dt, q_pitch, d, k_pitch, d, 0, flags, P, None) == 0
+        assert lib.lemo_score_colsums(P, P, S, H, H, d, dt, q_pitch, d, k_pitch, d, 0, 128, flags, P, P, P, None) == 0
+        out.append([(names[i].decode(), threads[i]) for i in range(seen.value)])
+    json.dump(out, sys.stdout)
+
+
+@pytest.fixture(scope="module")
+def routes(tmp_path_factory):
+    """calls (type, head size, tokens, heads, flags, pitch of Q, of K) -> per call the (D, NRT, KS, WAVES, binary32) of its sweeps"""
+    source = tmp_path_factory.mktemp("runtime") / "runtime.c"
+    runtime = source.with_suffix(".so")
+    source.write_text(RUNTIME)
+    subprocess.run(["gcc", "-O1", "-shared", "-fPIC", str(source), "-o", str(runtime)], check=True)
+
+    def ask(calls):
+        r = subprocess.run([sys.executable, __file__, str(runtime)], input=json.dumps(calls), capture_output=True, text=True)
+        assert r.returncode == 0, r.stdout + r.stderr
+        out = []
+        for launches in json.loads(r.stdout):
+            assert len(launches) == 2
+            kinds = []
+            for sweep, (name, threads) in zip(("rowstats", "colsum"), launches):
+                m = re.search(sweep + r"(_f32)?_kernelILi(\d+)ELi(\d+)ELi(\d+)ELi(\d+)E", name)
+                assert m, name
+                kinds.append((*(int(m[i]) for i in range(2, 6)), m[1] is not None))
+                assert threads == 64 * kinds[-1][3]
+            out.append(kinds)
+        return out
+    return ask
+
+
+def sizes():
+    """Tokens and heads over the ranges of all rules that choose a kernel."""
+    tokens = (300, 384, 500, 512, 700, 1024, 1500, 2048, 3000, 4096, 5000, 8192, 12345, 14336, 16384, 32768)
+    return [(S, H) for S in tokens for H in (1, 2, 3, 4, 5, 7, 8, 9, 11, 12, 14, 16, 20, 24, 28, 32, 40, 64, 128)]
+
+
+@pytest.mark.parametrize("dt,d", [(dt, d) for dt in (F32, BF16) for d in (64, 128)])
+def test_stages_are_within_reach_at_every_pitch(routes, dt, d):
+    """The offset of a row in a stage and the size of the stage's descriptor have 31 bits: rows beyond would arrive as zeros."""
+    size = 4 if dt == F32 else 2
+    calls, longest = [], 0
+    for S, H in sizes():
+        for flags in (0, CAUSAL):
+            for q, k in ((LONGEST[dt], LONGEST[dt]), (d, LONGEST[dt]), (LONGEST[dt], d), (1 << 20, 1 << 20)):
+                calls.append((dt, d, S, H, flags, q, k))
+    for call, kinds in zip(calls, routes(calls)):
+        for D, nrt, ks, waves, f32 in kinds:
+            assert D == d and f32 == (dt == F32)
+            rows, row_bytes = (64 if d * size > 256 else 128) * waves // 4, max(call[5:]) * size
+            reach = (rows - 1) * row_bytes + d * size
+            assert reach <= 0x7fffffff, (call, kinds)
+            longest = max(longest, reach)
+    assert longest > 1 << 30
+
+
+if __name__ == "__main__":
+    run(sys.argv[1])
