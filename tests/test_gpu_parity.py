@@ -351,7 +351,8 @@ def test_score_all_logits_far_below_zero(lemo, H, d, dtype):
 
 
 @pytest.mark.parametrize("S,H,Hkv,d,dtype,flags", [(1000, 32, 8, 128, "bf16", 3), (3000, 32, 8, 128, "bf16", 3), (2000, 12, 12, 64, "bf16", 0),
-                                                   (4500, 32, 8, 64, "bf16", 0), (1024, 4, 4, 64, "f32", 3), (1200, 8, 8, 128, "f32", 3)])
+                                                   (4500, 32, 8, 64, "bf16", 0), (1024, 4, 4, 64, "f32", 3), (1200, 8, 8, 128, "f32", 3),
+                                                   (14336, 16, 4, 64, "bf16", 3)])
 def test_score_sums_have_no_bias(lemo, S, H, Hkv, d, dtype, flags):
     """Head sums of the column sums against 64 bits.  Logits, normalisers and probabilities are binary32 roundings to
     nearest, which cancel over the rows and heads of a column; what does not cancel (sums too long for their small terms, a

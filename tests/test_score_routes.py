@@ -114,5 +114,20 @@ def test_stages_are_within_reach_at_every_pitch(routes, dt, d):
     assert longest > 1 << 30
 
 
+@pytest.mark.parametrize("d,most", [(64, 1024), (128, 640)])
+def test_shared_rows_stay_shared(routes, d, most):
+    """Waves that share rows add up stage by stage and round the row statistics once: column sums of 14336 tokens, 16 heads of 64 are
+    7e-8 from 64 bits where waves with rows of their own are 1.2e-6 off.  Launches that were small enough for the former keep them."""
+    calls = [(BF16, d, S, H, flags, H * d, H * d) for S, H in sizes() for flags in (0, CAUSAL)]
+    shared = 0
+    for call, kinds in zip(calls, routes(calls)):
+        S, H, flags = call[2:5]
+        n = H * ((S + 255) // 256)                            # blocks of 256 rows
+        if n <= most and (flags & CAUSAL or n <= 64 or (2 * n + 255) // 256 % 2 == 1):
+            shared += 1
+            assert all(k[2] > 1 for k in kinds), (call, n, kinds)
+    assert shared > 200
+
+
 if __name__ == "__main__":
     run(sys.argv[1])
