@@ -586,29 +586,32 @@ static int launch_sweeps(const ScoreParams& p_in, int which, hipStream_t st) {
 // 110, n = 640 123 / 118 / 135, n = 768 190 / 204 / 232, n = 896 272 / 270 / 307).
 //
 // Workgroups of eight waves have a CU each, stages of 256 rows (half the barriers, and the loads of 256 rows serve all eight) and blocks of
-// 512 / KS rows.  Under the mask a launch is as long as its longest block or as all of them over 256 CUs, which are alike for blocks
-// of about n / 2 rows; without it, as many rounds as its n KS / 2 workgroups fill the CUs.  us a sweep, four waves with the KS above / eight:
-//   d = 128, causal  KS = 8: n = 48 (1500 tokens) 12.7 / 11.0, 64 (512) 7.0 / 6.7, 96 (3000) 25 / 19, (700) 9.4 / 10.6, 128 (1000) 11.1 / 13.4, (2048)
-//                    19.1 / 18.2, (8192) 63 / 51;  KS = 4: n = 144 34 / 28, 160 (1280) 17.5 / 15.2, 192 (6000) 63 / 51, 256 27.2 / 26.8, 288 30 / 35;
-//                    KS = 2: n = 384 48 / 48, 448 62 / 57.5, 512 80 / 76, 640 114 / 117;  KS = 1: n = 768 161 / 166, 896 207 / 196, 1024 267 / 256, 1152
-//                    320 / 338, 4096 3780 / 3770
-//   d = 64, causal   KS = 8: n = 48 (1024) 9.0 / 7.7, (3000) 20 / 15, 80 (5000) 30 / 23, 96 (1500) 11.5 / 11.0, 128 (2048) 14.4 / 14.8, (4096) 25 / 22;
-//                    KS = 4: n = 192 41 / 40, 256 32 / 34;  KS = 1: n = 1504 685 / 761
-//   d = 128, full    KS = 8: n = 64 (1000) 10.5 / 9.6;  KS = 4: n = 96 12.3 / 11.4, 128 25.6 / 22;  KS = 2: n = 192 53 / 46, 256 41 / 37;  KS = 1: n = 384 84 / 82, 512
-//                    126 / 122, 640 212 / 262, 1024 489 / 475
-//   d = 64, full     KS = 8: n = 48 (3000) 20 / 15.5;  KS = 4: n = 96 16 / 14, 128 35 / 28;  KS = 2: n = 192 35 / 37;  KS = 1: n = 512 174 / 161, 384 103 / 117
+// 512 / KS rows.  Under the mask a launch is as long as its longest block or as all of them over 256 CUs: many heads of few tokens are
+// better off with the smaller blocks that two workgroups per CU take in turn.  Without a mask it takes as many rounds as its workgroups fill the CUs, and
+// 513 to 640 tokens end in a stage that is half empty.  Both sweeps, time with eight waves / with four and the KS above, n = 256-row blocks:
+//   d = 128, causal  KS = 8: n = 64 (512 tokens, 32 heads) 0.96, (16384, 1) 0.70, 96 (6000, 4) 0.79, (2000, 12) 0.93, (1500, 16) 0.97, 112 (1949, 14)
+//                    0.94, (1792, 16) 1.01, 120 (1500, 20) 1.13, 128 (8192, 4) 0.85, (2048, 16) 1.02;  KS = 4: n = 160 (1280, 32) 0.86, 192 (1500, 32) 0.94, 216
+//                    (1323, 36) 1.11, 256 (4096, 16) 0.90, (2048, 32) 1.00, (1024, 64) 1.20;  KS = 2: n = 432 (2304, 48) 1.00, 448 (7168, 16) 0.93, (1846, 56) 1.08, 512 (8192, 16)
+//                    0.96, (2048, 64) 1.04;  KS = 1: n = 896 (7168, 32) 0.95, 980 (12345, 20) 0.98, 1024 (8192, 32) 0.98, (4096, 64) 1.04, 1008 (5376, 48: 528 workgroups) 1.04
+//   d = 64, causal   KS = 8: n = 64 (16384, 1) 0.71, (2048, 8) 0.80, 80 (1000, 20) 1.01, 112 (3584, 8) 0.84, 128 (4096, 8) 0.92, (2048, 16) 1.03;  KS = 4: n = 256 1.06
+//   d = 128, full    KS = 8: n = 64 (16384, 1) 0.75, (1000, 16) 0.90, 60 (640, 20) 1.06, (641, 20) 0.93;  KS = 4: n = 96 (1500, 16) 0.87, (640, 32) 1.08, 128 (4096, 8)
+//                    0.87, (512, 64) 1.02;  KS = 2: n = 192 (3000, 16) 0.86, (640, 64) 1.06, 256 (4096, 16) 0.94;  KS = 1: n = 448 (7168, 16) 0.95, 512 (4096, 32) 0.95, 896 (7168, 32)
+//                    0.95, 1024 (8192, 32) 0.97, 1008 (2304, 112: 560 workgroups) 1.29, (6254, 40: 520) 1.35
+//   d = 64, full     KS = 8: n = 64 (16384, 1) 0.71, (1000, 16) 0.90, 60 (640, 20) 1.07;  KS = 4: n = 96 (3000, 8) 0.83, (640, 32) 1.09, 128 (4096, 8) 0.81;  KS = 1: n = 448
+//                    (7168, 16) 0.93, 512 (8192, 16) 0.97, 1024 (8192, 32) 1.00, 1008 (2304, 112) 1.38
+// Where rows are not shared either way only: whole rows add up less exactly.  Column sums of 16 heads of 64, relative 2-norm from 64 bits with
+// KS = 2 / 1: 14336 tokens 7.4e-8 / 1.2e-6, 16384 7.1e-8 / 1.3e-6, 14336 without a mask 9.8e-8 / 4.0e-6.
 template <int D, int NRT>
 static int launch_sweeps_ks(const ScoreParams& p, long long n, int which, hipStream_t st) {
     const bool causal = (p.flags & LEMO_CAUSAL) != 0;
-    if (p.S >= 512) {
+    if (p.S >= 512 && (causal || p.S == 512 || p.S > 640)) {
         const int longest = D == 128 ? 64 : 80;  // blocks of 64 rows for any length; beyond it, where the longest one decides
-        if (n <= (causal ? longest : 64) || (causal && n <= 128 && p.S >= (D == 128 ? 1500 : 3000))) return launch_sweeps<D, NRT, 8, 8>(p, which, st);
-        if (causal ? D == 128 && n > 128 && n <= 256 && p.S >= 1024 : n <= 128) return launch_sweeps<D, NRT, 4, 8>(p, which, st);
+        if (n <= (causal ? longest : 64) || (causal && n <= 128 && (D == 128 ? p.H <= 14 : p.S >= 3000))) return launch_sweeps<D, NRT, 8, 8>(p, which, st);
+        if (causal ? D == 128 && n > 128 && n <= 256 && p.H <= 32 : n <= 128) return launch_sweeps<D, NRT, 4, 8>(p, which, st);
         if constexpr (D == 128)
-            if (causal ? n > 400 && n <= 512 && p.S >= 1024 : n <= 256) return launch_sweeps<D, NRT, 2, 8>(p, which, st);
-        // (where rows are not shared either way: whole rows add up less exactly.  Column sums of 16 heads of 64, relative 2-norm from 64 bits with
-        // KS = 2 / 1: 14336 tokens 7.4e-8 / 1.2e-6, 16384 7.1e-8 / 1.3e-6, 14336 without a mask 9.8e-8 / 4.0e-6)
-        if (p.S >= 2048 && ((D == 128 && n >= 896 && n <= 1024) || (!causal && n >= 448 && n <= 512))) return launch_sweeps<D, NRT, 1, 8>(p, which, st);
+            if (causal ? n > 400 && n <= 512 && p.H <= 48 : n <= 256) return launch_sweeps<D, NRT, 2, 8>(p, which, st);
+        const long long n512 = (long long)p.H * ((p.S + 511) / 512);  // workgroups with KS = 1
+        if (p.S >= 2048 && ((D == 128 && n >= 896 && n512 <= 512 && (!causal || p.H <= 48)) || (!causal && n >= 448 && n512 <= 256))) return launch_sweeps<D, NRT, 1, 8>(p, which, st);
     }
     if (!causal) {
         if (n <= 64 || (D == 64 && n > 128 && n <= 192)) return launch_sweeps<D, NRT, 4, 4>(p, which, st);

@@ -490,14 +490,14 @@ int prepare_sweeps_f32(int d) { return d == 128 ? first_error(prepare_f32<128, 1
 int launch_sweeps_f32(const ScoreParams& p, int d, int which, hipStream_t st) {
     const long long blocks256 = (long long)p.H * ((p.S + 255) / 256);
     // Eight waves, twice the sharers of a row and twice the rows of a stage, one workgroup per CU: where the CUs then have at most one, or
-    // the longest block decides.  us a sweep, four / eight: d = 64 1024 tokens, 4 heads 13.2 / 11.6, 500, 16 9.0 / 8.7, 300, 4 7.6 / 8.2, 3000, 4
-    // 32 / 25, 4000, 4 41 / 38, 1024, 12 13.5 / 16, full 2000, 4 22.5 / 19.4, 2500, 4 37 / 41.5; d = 128 500, 16 19 / 17.5, 1000, 16 33 / 28.5,
-    // 2000, 12 62 / 52, 1000, 32 38 / 39, full 700, 16 24.6 / 23.5.
+    // the longest block decides.  us a sweep, four / eight: d = 64 1024 tokens, 4 heads 13.2 / 11.6, 500, 16 9.0 / 8.7, 400, 4 8.8 / 8.6, 384, 4 (a stage and a
+    // half) 7.5 / 8.2, 300, 4 7.6 / 8.2, 3000, 4 32 / 25, 4000, 4 41 / 38, 1024, 12 13.5 / 16, full 2000, 4 22.5 / 19.4, 2500, 4 37 / 41.5; d = 128 400, 8 17.7 / 17.8,
+    // 500, 16 19 / 17.5, 1000, 16 33 / 28.5, 2000, 12 62 / 52, 1000, 32 38 / 39, full 700, 16 24.6 / 23.5.
     const bool causal = (p.flags & LEMO_CAUSAL) != 0;
     if (d == 128 && p.S >= 384 && (blocks256 <= 64 || (causal && blocks256 <= 128 && p.S >= 1500))) return launch_f32<128, 1, 4, 8>(p, which, st);
     // (d = 64: their 256 rows of a stage must be within reach, up to 8.4 MB of pitch)
     const bool reach = (p.q_ts > p.k_ts ? p.q_ts : p.k_ts) * 4 <= Geo<float, 64, 1, 8, 8>::LONGEST_PITCH;
-    if (d == 64 && reach && p.S >= 384 && (blocks256 <= 32 || (causal && blocks256 <= 64 && p.S >= 3000))) return launch_f32<64, 1, 8, 8>(p, which, st);
+    if (d == 64 && reach && p.S > 384 && (blocks256 <= 32 || (causal && blocks256 <= 64 && p.S >= 3000))) return launch_f32<64, 1, 8, 8>(p, which, st);
     if (d == 128) return launch_f32<128, 1, 2, 4>(p, which, st);
     return blocks256 <= 192 ? launch_f32<64, 1, 4, 4>(p, which, st) : launch_f32<64, 2, 4, 4>(p, which, st);
 }

@@ -129,5 +129,22 @@ def test_shared_rows_stay_shared(routes, d, most):
     assert shared > 200
 
 
+@pytest.mark.parametrize("dt,d,S,H,causal,ks,waves", [
+    # many heads of few tokens under the mask
+    (BF16, 128, 1500, 20, 1, 4, 4), (BF16, 128, 2048, 16, 1, 4, 4), (BF16, 128, 1024, 64, 1, 2, 4), (BF16, 128, 1323, 36, 1, 2, 4), (BF16, 128, 2048, 64, 1, 2, 4),
+    (BF16, 128, 1846, 56, 1, 2, 4), (BF16, 128, 4096, 64, 1, 1, 4),
+    # a last round that blocks of 512 rows would leave nearly empty
+    (BF16, 128, 5376, 48, 1, 1, 4), (BF16, 128, 2304, 112, 0, 1, 4), (BF16, 128, 6254, 40, 0, 1, 4), (BF16, 64, 5376, 48, 0, 1, 4), (BF16, 64, 5376, 24, 0, 1, 4),
+    # a last stage that is half empty
+    (BF16, 128, 640, 16, 0, 4, 4), (BF16, 64, 513, 20, 0, 4, 4), (BF16, 64, 640, 32, 0, 2, 4), (BF16, 128, 640, 64, 0, 1, 4), (F32, 64, 384, 4, 0, 4, 4), (F32, 64, 384, 4, 1, 4, 4),
+    # and where eight waves are the faster ones
+    (BF16, 128, 512, 16, 0, 8, 8), (BF16, 128, 641, 16, 0, 8, 8), (BF16, 128, 513, 16, 1, 8, 8), (BF16, 128, 1949, 14, 1, 8, 8), (BF16, 128, 1500, 32, 1, 4, 8),
+    (BF16, 128, 4096, 32, 1, 2, 8), (BF16, 128, 8192, 32, 1, 1, 8), (BF16, 128, 8192, 32, 0, 1, 8), (BF16, 64, 8192, 16, 0, 1, 8), (F32, 64, 385, 4, 1, 8, 8)])
+def test_eight_waves_only_where_they_are_faster(routes, dt, d, S, H, causal, ks, waves):
+    """Calls on either side of the rules' lines, each with the kernel that was measured to be the faster one."""
+    for _, _, k, w, _ in routes([(dt, d, S, H, causal, H * d, H * d)])[0]:
+        assert (k, w) == (ks, waves)
+
+
 if __name__ == "__main__":
     run(sys.argv[1])
