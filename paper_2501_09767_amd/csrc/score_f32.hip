@@ -451,12 +451,9 @@ __global__ __launch_bounds__(64 * WAVES, (Geo<float, D, NRT, KS, WAVES>::MIN_WG)
     if (part != 0) return;
 #pragma unroll
     for (int kt = 0; kt < NRT; ++kt) {
-#pragma unroll
-        for (int w = 1; w < KS; ++w) {
-            const float2 v = shares[(wave + w) * G::RES + kt * 32 + l32];
-            col[kt] += v.x;
-            dg[kt] += v.y;
-        }
+        const float2 all = add_shares<G>(shares + wave * G::RES + kt * 32 + l32);
+        col[kt] = all.x;
+        dg[kt] = all.y;
         const int key = kw0 + kt * 32 + l32;
         if (half == 0 && key < kend) {
             p.colsum[(size_t)h * S + key] = col[kt];

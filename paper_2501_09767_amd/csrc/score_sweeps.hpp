@@ -226,6 +226,21 @@ __device__ __forceinline__ void read_nl(float (&nl)[16], const float* lbuf, int 
     }
 }
 
+// The sums of the KS waves that share a key, from the first one's entry on: in pairs, then in pairs of those, so that eight shares round the whole
+// sum once and not seven times.  Column sums, relative 2-norm from 64 bits, mean of 24 draws, one after the other /
+// in pairs: eight shares 3000 tokens, 4 heads of 64 6.4e-8 / 5.1e-8, 1500, 8 of 128 6.6e-8 / 5.8e-8; four 6000, 8 of 128 5.8e-8 / 5.6e-8.
+template <typename G>
+__device__ __forceinline__ float2 add_shares(const float2* share) {
+    float2 v[G::KS];
+#pragma unroll
+    for (int w = 0; w < G::KS; ++w) v[w] = share[w * G::RES];
+#pragma unroll
+    for (int step = 1; step < G::KS; step *= 2)
+#pragma unroll
+        for (int w = 0; w < G::KS; w += 2 * step) { v[w].x += v[w + step].x; v[w].y += v[w + step].y; }
+    return v[0];
+}
+
 int prepare_sweeps_f32(int d);
 int launch_sweeps_f32(const ScoreParams& p, int d, int which, hipStream_t st);  // score_f32.hip
 

@@ -378,6 +378,27 @@ def test_score_sums_have_no_bias(lemo, S, H, Hkv, d, dtype, flags):
     assert err <= 2.0 ** -24
 
 
+def test_score_shares_are_added_in_pairs(lemo):
+    """Column sums that eight waves share out, relative 2-norm from 64 bits, mean of 24 draws: 5.35e-8 with the shares added in pairs, 5.84e-8 with
+    one added after the other, which rounds nearly the whole sum seven times."""
+    S, H, d = 3000, 4, 64
+    say(f"[score] shares in pairs S={S} H={H} d={d}")
+    later, errs = torch.ones((S, S), dtype=torch.bool, device="cuda").triu(1), []
+    for seed in range(24):
+        gen = torch.Generator().manual_seed(seed)
+        Q, K = (1.28 * torch.randn(S, H, d, generator=gen) for _ in range(2))
+        K[torch.rand(S, generator=gen) < 0.01] *= 4
+        Q, K = Q.to(torch.bfloat16), K.to(torch.bfloat16)
+        _, col, _ = run_score(lemo, Q, K, 512, 1)
+        for h in range(H):
+            x = Q[:, h].cuda().double() @ K[:, h].cuda().double().t().contiguous() / math.sqrt(d)
+            want = torch.softmax(x.masked_fill_(later, -math.inf), dim=1).sum(0)
+            errs.append(float((torch.from_numpy(col[h]).cuda().double() - want).norm() / want.norm()))
+    err = sum(errs) / len(errs)
+    say(f"    {err:.2e}")
+    assert err <= 5.6e-8
+
+
 @pytest.mark.parametrize("S,H,Hkv,d", [(700, 70, 35, 128), (333, 330, 110, 128), (700, 104, 52, 64), (300, 520, 130, 64)])
 def test_score_larger_blocks(lemo, S, H, Hkv, d):
     """Launches with more 256-row blocks share rows between two waves (first and third case) or none; the other scoring
@@ -394,19 +415,22 @@ def test_score_larger_blocks(lemo, S, H, Hkv, d):
         assert_scores_close(got, want, "scores")
 
 
-@pytest.mark.parametrize("S,H,Hkv,d,flags,dtype", [
-    # blocks of 64, 128, 256 and 512 rows on eight waves: just past the shortest, ragged, whole 128 rows but not whole stages of 256
-    (513, 3, 1, 128, 3, "bf16"), (1501, 20, 5, 128, 1, "bf16"), (640, 5, 5, 128, 0, "bf16"), (1152, 33, 11, 128, 3, "bf16"), (1040, 33, 33, 128, 1, "bf16"),
-    (640, 40, 8, 128, 2, "bf16"), (777, 40, 40, 128, 0, "bf16"), (1152, 90, 30, 128, 3, "bf16"), (1030, 84, 84, 128, 3, "bf16"), (640, 70, 70, 128, 2, "bf16"),
-    (777, 60, 20, 128, 0, "bf16"), (2176, 100, 25, 128, 3, "bf16"), (2050, 100, 100, 128, 1, "bf16"), (2176, 50, 50, 128, 0, "bf16"),
-    (515, 4, 4, 64, 3, "bf16"), (3001, 10, 5, 64, 3, "bf16"), (640, 40, 40, 64, 2, "bf16"), (600, 40, 8, 64, 0, "bf16"), (2176, 100, 50, 64, 3, "bf16"), (2049, 50, 50, 64, 0, "bf16"),
-    (640, 5, 5, 64, 3, "f32"), (390, 5, 1, 64, 2, "f32"), (3001, 4, 4, 64, 3, "f32"), (385, 7, 7, 128, 0, "f32"), (1501, 20, 4, 128, 3, "f32")])
-@pytest.mark.parametrize("gone", [False, True])
+# Blocks of 64, 128, 256 and 512 rows on eight waves, causal and not: ragged, whole 32 rows but not 128, whole 128 rows but not whole stages of 256.
+EIGHT_WAVES = [
+    (513, 3, 1, 128, 3, "bf16"), (1501, 14, 7, 128, 1, "bf16"), (544, 4, 2, 128, 3, "bf16"), (777, 4, 4, 128, 2, "bf16"), (704, 5, 5, 128, 0, "bf16"), (512, 8, 8, 128, 0, "bf16"),
+    (1281, 26, 13, 128, 3, "bf16"), (1056, 30, 30, 128, 1, "bf16"), (1152, 30, 10, 128, 3, "bf16"), (777, 30, 30, 128, 0, "bf16"), (704, 40, 8, 128, 2, "bf16"),
+    (2177, 46, 23, 128, 3, "bf16"), (2208, 46, 46, 128, 1, "bf16"), (777, 60, 20, 128, 0, "bf16"), (704, 60, 20, 128, 0, "bf16"),
+    (4641, 48, 48, 128, 1, "bf16"), (4640, 48, 16, 128, 3, "bf16"), (2050, 50, 25, 128, 2, "bf16"), (2176, 50, 50, 128, 0, "bf16"), (2176, 100, 25, 128, 2, "bf16"),
+    (515, 4, 4, 64, 3, "bf16"), (3001, 10, 5, 64, 3, "bf16"), (1056, 8, 8, 64, 1, "bf16"), (672, 8, 8, 64, 0, "bf16"), (700, 40, 8, 64, 0, "bf16"), (704, 40, 40, 64, 2, "bf16"),
+    (2049, 50, 50, 64, 0, "bf16"), (2176, 50, 25, 64, 2, "bf16"),
+    (640, 5, 5, 64, 3, "f32"), (390, 5, 1, 64, 2, "f32"), (416, 5, 5, 64, 0, "f32"), (3001, 4, 4, 64, 3, "f32"),
+    (385, 7, 7, 128, 0, "f32"), (416, 7, 7, 128, 3, "f32"), (1501, 20, 4, 128, 3, "f32"), (1504, 20, 20, 128, 1, "f32")]
+
+
+@pytest.mark.parametrize("S,H,Hkv,d,flags,dtype,gone", [(*c, False) for c in EIGHT_WAVES] + [(*c, True) for c in EIGHT_WAVES if c[0] % 32 == 0])
 def test_score_workgroups_of_eight_waves(lemo, S, H, Hkv, d, flags, dtype, gone):
-    """Column sums and diagonals against 64 bits: a key whose logits overtake the frozen reference of sweep 1, or (whole 128 rows: no
+    """Column sums and diagonals against 64 bits: a key whose logits overtake the frozen reference of sweep 1, or (whole 32 rows: no
     zeros in the place of a query meet it) one at minus infinity that nobody looks at."""
-    if gone and S % 128:
-        pytest.skip("zeros fill up the last rows")
     say(f"[score] eight waves S={S} H={H}/{Hkv} d={d} flags={flags} {dtype} gone={gone}")
     Q, K = wl.tiny_qk(S, H, Hkv, d, dtype, seed=S + H + d, heavy=4)
     at = S // 2 + 40

@@ -146,5 +146,16 @@ def test_eight_waves_only_where_they_are_faster(routes, dt, d, S, H, causal, ks,
         assert (k, w) == (ks, waves)
 
 
+def test_the_shapes_of_the_eight_wave_tests_take_them(routes):
+    from test_gpu_parity import EIGHT_WAVES
+    calls = [(F32 if dt == "f32" else BF16, d, S, H, flags & CAUSAL, H * d, H * d) for S, H, _, d, flags, dt in EIGHT_WAVES]
+    taken = set()
+    for call, kinds in zip(calls, routes(calls)):
+        assert all(k[3] == 8 for k in kinds), (call, kinds)
+        taken.add((call[0], call[1], call[4], kinds[0][2]))
+    assert taken == {(BF16, 128, c, ks) for c in (0, 1) for ks in (8, 4, 2, 1)} | {(BF16, 64, 1, 8)} | {(BF16, 64, 0, ks) for ks in (8, 4, 1)} | \
+        {(F32, 64, c, 8) for c in (0, 1)} | {(F32, 128, c, 4) for c in (0, 1)}
+
+
 if __name__ == "__main__":
     run(sys.argv[1])
