@@ -300,16 +300,19 @@ static int launch_tilemax_t(BlockParams p, hipStream_t st) {
     p.count = (int)total;
     // bf16.  More than 256 rectangles go to tilemax_slab_kernel, which has 512 at a time; up to 256, one per CU, this kernel's eight
     // waves per rectangle are faster.  A round takes nearly as long for a few rectangles as for all: what is left of the last 256 goes
-    // to tilemax_few_kernel as quarters or smaller if it is little, or all there is.  us per call (the rest always as quarters), this kernel / slabs / slabs (or none)
-    // and the rest as quarters, causal; 32 heads, D = 128: 36 rectangles 45 / 51 / 25, 120 45.5 / 51 / 43.5, 136 45 / 51 / 58,
+    // to tilemax_few_kernel as quarters or smaller if it is little, or all there is.  us per call (the rest always as quarters), this kernel /
+    // slabs / slabs (or none) and the rest as quarters, causal; 32 heads, D = 128: 36 rectangles 45 / 51 / 25, 120 45.5 / 51 / 43.5, 136 45 / 51 / 58,
     // 253 52 / 54 / 77, 276 88 / 72 / 74, 325 89 / 76 / 91, 496 97 / 86 / 130, 528 134 / 118 / 106, 561 135 / 118 / 111, 666 141 / 125 /
     // 144, 1081 224 / 190 / 180; 16 heads, D = 64: 36 24 / 25 / 16, 120 24.4 / 25.8 / 18.0, 171 24.9 / 25.8 / 23.6, 253 25.1 / 26.1 / 28.1,
     // 276 41.5 / 35.3 / 35.6, 378 41 / 35 / 40, 528 60 / 51 / 47, 561 59 / 50 / 46, 666 59 / 50 / 56, 1275 95 / 77 / 88.
+    // 65 to 128 rectangles are two quarters to a CU (D = 128, whose LDS holds one at a time), which pays with the heads: this kernel /
+    // quarters, 120 rectangles of 128 1 head 9.7 / 12.8, 4 13.3 / 14.5, 16 25.9 / 26.7, 20 31.8 / 31.4, 32 42.6 / 40.4, 64 74.7 / 61.3; of 64 1 head 9.1 / 8.9,
+    // 16 21.8 / 15.9.
     int rest = 0;
     bool slabs = false;
     if constexpr (G::TT == 128 && sizeof(T) == 2) {
         rest = p.count % SB_CUS;
-        if (rest > (p.count < SB_CUS ? SB_CUS / 2 : SB_CUS / 4)) rest = 0;
+        if (rest > (p.count < SB_CUS && (D == 64 || p.H >= 20) ? SB_CUS / 2 : SB_CUS / 4)) rest = 0;
         p.count -= rest;
         slabs = p.count > SB_CUS;
     }

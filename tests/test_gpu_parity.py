@@ -677,6 +677,7 @@ def test_score_blocks_small_shapes(lemo, S, H, Hkv, d, dtype, b, flags, mode):
     (1024, 4, 4, 128, 2), (1025, 5, 5, 128, 2),                     # 64 rectangles, all as quarters; 81, none
     (1280, 6, 2, 128, 1), (1281, 3, 3, 128, 3),                     # the same under a causal mask: 55 and 66
     (1408, 9, 3, 64, 0), (1920, 4, 1, 64, 1), (1921, 4, 2, 64, 1),  # 121, 120 (quarters), 136
+    (1500, 20, 4, 128, 3),                                          # 78, as quarters from 20 heads on
     (2850, 7, 7, 128, 3), (2060, 3, 1, 64, 0),                      # a round of whole rectangles and 20 (33) in quarters
     (33, 8, 8, 128, 1), (500, 9, 3, 128, 3), (512, 17, 17, 128, 2), (544, 3, 3, 128, 2),  # in pieces: up to 16 (25: quarters) ...
     (610, 10, 5, 64, 0), (895, 16, 16, 64, 3), (4000, 1, 1, 128, 3)])                     # ... at D = 64 up to 32; 512 whole and 16

@@ -1,4 +1,4 @@
-"""Which kernels the scoring sweeps take, and what these can reach (CPU only).  The library is run against a HIP runtime that only
+"""Which kernels calls take, and what these can reach (CPU only).  The library is run against a HIP runtime that only
 notes what is asked of it."""
 import ctypes
 import json
@@ -50,23 +50,38 @@ def run(runtime):
     """In a process of its own: calls from standard input, the kernels each of them launched to standard output."""
     hip = ctypes.CDLL(runtime, mode=ctypes.RTLD_GLOBAL)
     lib = ctypes.CDLL(LIB)
-    kinds = {"p": ctypes.c_void_p, "i": ctypes.c_int32, "l": ctypes.c_int64, "f": ctypes.c_float}
-    lib.lemo_score_rowstats.argtypes = [kinds[k] for k in "ppliiiillllfipp"]
-    lib.lemo_score_colsums.argtypes = [kinds[k] for k in "ppliiiillllfiipppp"]
+    kinds = {"p": ctypes.c_void_p, "i": ctypes.c_int32, "l": ctypes.c_int64, "f": ctypes.c_float, "z": ctypes.c_size_t}
+    for fn, args in (("score_rowstats", "ppliiiillllfipp"), ("score_colsums", "ppliiiillllfiipppp"), ("score_blocks", "ppliiiillllfiiippppzp"),
+                     ("gather_gemm", "pllplplppliiip"), ("gather_gemm_dw", "plpllplpliiipzp")):
+        getattr(lib, "lemo_" + fn).argtypes = [kinds[k] for k in args]
     seen = ctypes.c_int.in_dll(hip, "n_launched")
     names, threads = (ctypes.c_char_p * 64).in_dll(hip, "launched"), (ctypes.c_int * 64).in_dll(hip, "threads")
+
+    def sweeps(dt, d, S, H, flags, q_pitch, k_pitch):
+        return lib.lemo_score_rowstats(P, P, S, H, H, d, dt, q_pitch, d, k_pitch, d, 0, flags, P, None) or \
+            lib.lemo_score_colsums(P, P, S, H, H, d, dt, q_pitch, d, k_pitch, d, 0, 128, flags, P, P, P, None)
+
+    def blocks(dt, d, S, H, flags):
+        return lib.lemo_score_blocks(P, P, S, H, H, d, dt, H * d, d, H * d, d, 0, 64, flags, 0, P, None, P, P, 1 << 40, None)
+
+    def gemm(dt, M, N, K):
+        return lib.lemo_gather_gemm(P, M, K, None, M, P, K, None, P, N, K, N, dt, None)
+
+    def gemm_dw(dt, M, N, K):  # [M, N] of K tokens
+        return lib.lemo_gather_gemm_dw(P, M, P, K, N, None, K, 1 << 50, N, N, M, dt, P, 1 << 40, None)
+
     out = []
-    for dt, d, S, H, flags, q_pitch, k_pitch in json.load(sys.stdin):
+    for entry, *args in json.load(sys.stdin):
         seen.value = 0
-        assert lib.lemo_score_rowstats(P, P, S, H, H, d, dt, q_pitch, d, k_pitch, d, 0, flags, P, None) == 0
-        assert lib.lemo_score_colsums(P, P, S, H, H, d, dt, q_pitch, d, k_pitch, d, 0, 128, flags, P, P, P, None) == 0
+        rc = {"sweeps": sweeps, "blocks": blocks, "gemm": gemm, "gemm_dw": gemm_dw}[entry](*args)
+        assert rc == 0, (entry, args, rc)
         out.append([(names[i].decode(), threads[i]) for i in range(seen.value)])
     json.dump(out, sys.stdout)
 
 
 @pytest.fixture(scope="module")
-def routes(tmp_path_factory):
-    """calls (type, head size, tokens, heads, flags, pitch of Q, of K) -> per call the (D, NRT, KS, WAVES, binary32) of its sweeps"""
+def launches(tmp_path_factory):
+    """calls (entry, arguments) -> per call the names of the kernels it launched and their workgroups' threads"""
     source = tmp_path_factory.mktemp("runtime") / "runtime.c"
     runtime = source.with_suffix(".so")
     source.write_text(RUNTIME)
@@ -75,11 +90,19 @@ def routes(tmp_path_factory):
     def ask(calls):
         r = subprocess.run([sys.executable, __file__, str(runtime)], input=json.dumps(calls), capture_output=True, text=True)
         assert r.returncode == 0, r.stdout + r.stderr
+        return json.loads(r.stdout)
+    return ask
+
+
+@pytest.fixture
+def routes(launches):
+    """calls (type, head size, tokens, heads, flags, pitch of Q, of K) -> per call the (D, NRT, KS, WAVES, binary32) of its sweeps"""
+    def ask(calls):
         out = []
-        for launches in json.loads(r.stdout):
-            assert len(launches) == 2
+        for made in launches([("sweeps", *c) for c in calls]):
+            assert len(made) == 2
             kinds = []
-            for sweep, (name, threads) in zip(("rowstats", "colsum"), launches):
+            for sweep, (name, threads) in zip(("rowstats", "colsum"), made):
                 m = re.search(sweep + r"(_f32)?_kernelILi(\d+)ELi(\d+)ELi(\d+)ELi(\d+)E", name)
                 assert m, name
                 kinds.append((*(int(m[i]) for i in range(2, 6)), m[1] is not None))
@@ -155,6 +178,17 @@ def test_the_shapes_of_the_eight_wave_tests_take_them(routes):
         taken.add((call[0], call[1], call[4], kinds[0][2]))
     assert taken == {(BF16, 128, c, ks) for c in (0, 1) for ks in (8, 4, 2, 1)} | {(BF16, 64, 1, 8)} | {(BF16, 64, 0, ks) for ks in (8, 4, 1)} | \
         {(F32, 64, c, 8) for c in (0, 1)} | {(F32, 128, c, 4) for c in (0, 1)}
+
+
+@pytest.mark.parametrize("d,S,H,causal,first", [
+    # 65 to 128 rectangles: quarters from 20 heads of 128 on, and for all of 64
+    (128, 1200, 1, 0, "tilemax_kernel"), (128, 1500, 4, 1, "tilemax_kernel"), (128, 1800, 16, 1, "tilemax_kernel"), (128, 1800, 20, 1, "tilemax_few_kernel"),
+    (128, 1200, 32, 0, "tilemax_few_kernel"), (64, 1800, 1, 1, "tilemax_few_kernel"), (64, 1408, 4, 0, "tilemax_few_kernel"),
+    # up to 64, and more than 128
+    (128, 1000, 1, 0, "tilemax_few_kernel"), (128, 1921, 32, 1, "tilemax_kernel"), (64, 1921, 4, 1, "tilemax_kernel")])
+def test_rectangles_in_quarters_only_where_they_are_faster(launches, d, S, H, causal, first):
+    names = [name for name, _ in launches([("blocks", BF16, d, S, H, causal)])[0]]
+    assert len(names) == 2 and re.match(r"_ZN4lemo\d+" + first, names[0]), names
 
 
 if __name__ == "__main__":
