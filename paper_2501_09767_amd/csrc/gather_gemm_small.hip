@@ -662,11 +662,12 @@ int prepare_gather_gemm_small(lemo_dtype_t dt, bool add, int layout) {
 int launch_gather_gemm_small(const GgParams& p, lemo_dtype_t dt, bool add, int layout, GgTile tile, hipStream_t st) {
     if (dt == LEMO_BF16) return launch_small_form<bf16_t, 1, 2>(p, add, layout, st);
     // binary32 MFMAs bound these, so a CU's time is that of its tiles' areas: four 16 x 16 tiles for one of 32 x 32 spread them better over 256
-    // CUs until a CU would have more than three (two of 32 x 32 run side by side).  us, 32 x 32 / 16 x 16: weight gradient 256 x 256
-    // of 512 tokens 7.0 / 4.8, of 3000 21.6 / 11.8; M = 100, N = K = 256 4.7 / 3.5; 512, 256, 256 4.8 / 4.1; 256, 768, 3072 (768 tiles) 17.4 /
-    // 16.6; 800, 256, 256 (800) 4.9 / 5.9; 500, 768, 768 10.7 / 12.1.  Errors against 64 bits alike (2.07e-7, 4.93e-7, 1.5e-7, ...).
+    // CUs until a CU would have more than two (of 32 x 32 two run side by side).  us, 32 x 32 / 16 x 16 tiles, contraction 64 / 1024:  256 x 256
+    // (256 tiles) 4.2 / 3.3, 8.1 / 4.8, its weight gradient 4.5 / 3.7, 9.3 / 5.7;  256 x 512 (512) 4.2 / 3.8, 8.3 / 6.3, 4.5 / 4.2, 9.5 / 8.0;  272 x 512 (544)
+    // 4.2 / 4.4, 8.3 / 7.7, 4.5 / 5.1, 9.5 / 10.4;  256 x 768 (768) 4.2 / 4.5, 8.4 / 8.1, 4.5 / 5.2, 9.5 / 11.1.  Errors against 64 bits alike (2.07e-7,
+    // 4.93e-7, 1.5e-7, ...).
     const long long n16 = (p.M + 15) / 16 * ((p.N + 15ll) / 16);
-    if (tile != GG_T128 && n16 <= 768) return launch_small_form<float, 1, 1, false, 16>(p, add, layout, st);
+    if (tile != GG_T128 && n16 <= 512) return launch_small_form<float, 1, 1, false, 16>(p, add, layout, st);
     if (tile != GG_T128) return launch_small_form<float, 1, 1>(p, add, layout, st);
     // sums of one or two products (only a weight gradient has them, the other forms contract over 4 at least) from binary32 MFMAs:
     // error 2.5e-8 and 3.1e-8 against 3.5e-8 and 3.4e-8 of splits, 8192 x 8192 83 us against 69

@@ -1051,10 +1051,11 @@ def test_gather_gemm_large_tiles_exact(lemo, form, M, N, K):
 
 
 @pytest.mark.parametrize("form,M,N,K", [
-    # binary32, 16 x 16 tiles: one tile and less, fewer slabs than waves, a wave's share and more; ragged; 768 of them
-    ("nt", 1, 1, 4), ("nt", 16, 16, 32), ("nt", 17, 15, 36), ("add", 15, 33, 128), ("add", 100, 129, 132), ("nt", 384, 512, 260), ("add", 33, 770, 516),
-    ("dw", 4, 4, 1), ("dw", 16, 16, 31), ("dw", 36, 20, 33), ("dw", 100, 132, 129), ("dw", 256, 256, 600), ("dw", 512, 384, 257),
+    # binary32, 16 x 16 tiles: one tile and less, fewer slabs than waves, a wave's share and more; ragged; 512 of them
+    ("nt", 1, 1, 4), ("nt", 16, 16, 32), ("nt", 17, 15, 36), ("add", 15, 33, 128), ("add", 100, 129, 132), ("nt", 256, 512, 260), ("add", 33, 770, 516),
+    ("dw", 4, 4, 1), ("dw", 16, 16, 31), ("dw", 36, 20, 33), ("dw", 100, 132, 129), ("dw", 256, 256, 600), ("dw", 512, 256, 257),
     # 32 x 32 tiles
+    ("nt", 257, 512, 260), ("dw", 260, 512, 257), ("nt", 384, 512, 260), ("dw", 512, 384, 257),
     ("nt", 385, 512, 36), ("nt", 500, 451, 260), ("add", 1000, 385, 516), ("dw", 516, 388, 33), ("dw", 500, 1000, 131)])
 def test_gather_gemm_small_fp32_tiles_exact(lemo, form, M, N, K):
     test_gather_gemm_tiles_exact(lemo, form, M, N, K, "f32")

@@ -191,5 +191,14 @@ def test_rectangles_in_quarters_only_where_they_are_faster(launches, d, S, H, ca
     assert len(names) == 2 and re.match(r"_ZN4lemo\d+" + first, names[0]), names
 
 
+@pytest.mark.parametrize("entry", ["gemm", "gemm_dw"])
+@pytest.mark.parametrize("M,N,edge", [(16, 16, 16), (256, 512, 16), (512, 256, 16), (260, 512, 32), (368, 512, 32), (256, 768, 32), (192, 1024, 32), (800, 256, 32)])
+def test_small_fp32_tiles(launches, entry, M, N, edge):
+    """16 x 16 tiles up to two per CU (512), 32 x 32 ones beyond."""
+    for K in (16, 1024):
+        names = [name for name, _ in launches([(entry, F32, M, N, K)])[0]]
+        assert len(names) == 1 and re.search(r"gather_gemm_small_kernelIfLb[01]ELi\dELi1ELi1ELb0ELi(\d+)E", names[0])[1] == str(edge), names
+
+
 if __name__ == "__main__":
     run(sys.argv[1])
