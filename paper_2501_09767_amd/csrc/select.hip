@@ -292,7 +292,7 @@ int launch_select_threshold(const float* token_blocks, int S, int b, float t_hos
     const int nb = (S + b - 1) / b;  // host checked: nb <= 16384
     static std::once_flag once;
     static hipError_t attr_err = hipSuccess;
-    std::call_once(once, [] {  // 16384 block offsets are 64 KB of dynamic LDS on top of the kernel's static 4 KB: above the default limit
+    std::call_once(once, [] {  // 16384 block offsets are 64 KB of dynamic LDS on top of the kernel's static 64 bytes: above the default limit
         attr_err = hipFuncSetAttribute(reinterpret_cast<const void*>(&select_threshold_kernel), hipFuncAttributeMaxDynamicSharedMemorySize, 16384 * 4);
     });
     if (attr_err != hipSuccess) return (int)attr_err;

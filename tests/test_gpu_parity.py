@@ -592,6 +592,22 @@ def test_select_all_equal_and_extremes(lemo):
         np.testing.assert_array_equal(got, oracle.select_topk(ext, 128, k))
 
 
+@pytest.mark.parametrize("L", [1, 2, 5, 31, 63, 64, 65])
+def test_select_short_segments(lemo, L):
+    """Segments that fit a wavefront, and the first that do not: every k, many equal, both zeros, the lowest, infinities, a ragged tail."""
+    say(f"[select short] L={L}")
+    rng = np.random.default_rng(L)
+    S = 7 * L + L // 2
+    for scores in (rng.integers(0, 4, S).astype(np.float32), rng.standard_normal(S).astype(np.float32), np.zeros(S, np.float32),
+                   rng.choice(np.array([0.0, -0.0, np.inf, -np.inf, np.finfo(np.float32).min, 1e-45], np.float32), S)):
+        for k in {1, 2, (L + 1) // 2, L - 1, L} & set(range(1, L + 1)):
+            got = lemo.lemo_select_topk(torch.from_numpy(scores).cuda(), L, k).cpu().numpy()
+            np.testing.assert_array_equal(got, oracle.select_topk(scores, L, k))
+            cols = torch.from_numpy(np.stack([scores, np.zeros_like(scores)])).cuda()
+            mean, kept = lemo.lemo_head_mean_select_topk(cols, torch.zeros_like(cols), L, k, flags=0)
+            np.testing.assert_array_equal(kept.cpu().numpy(), oracle.select_topk(mean.cpu().numpy(), L, k))
+
+
 @pytest.mark.parametrize("alike", [1, 2, 63, 64, 65, 300, 1000])
 @pytest.mark.parametrize("low", [2, 300, 1 << 21])
 def test_select_many_alike_in_the_leading_digits(lemo, alike, low):
