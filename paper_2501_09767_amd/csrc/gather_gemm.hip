@@ -15,17 +15,20 @@ namespace lemo {
 // The time of n tiles of a kind over k slabs of 64 elements of the contraction, in us, is taken as
 //   a + full (b k + e) + (c + d f) k + e f          full whole rounds, the last one filled to f (nothing if f = 0)
 // with a the launch, b a slab in a full round, c ... c + d in the last one (c: if it is the first, if there are rounds before), e
-// what a round costs besides (loads before, stores after).  `along` is fitted to the six kinds over M = 50 ... 9000 with the widths and
-// contractions of layers of 768 to 4096 (N or K up to 14336), 197 products X W^T and 114 input gradients, operands from HBM: each
-// kind within 4 to 9 % (rms), the kind chosen costs 0.1 % over the best one on average, 14 % at worst.  `across` is fitted to 66 weight
-// gradients of layers of 256 to 4096, M = 64 ... 5000; its kinds are those whose rows are whole contraction-major regions.
+// what a round costs besides (loads before, stores after).  `along` (X W^T) and `mixed` (input gradients, whose weights pass through the transposing read) are
+// fitted to the six kinds over M = 50 ... 12000 with the widths and contractions of layers of 256 to 4096 (N or K up to 14336), 1000 products
+// each, operands from HBM; the kind chosen costs 0.05 % over the best one on average, 5 % at worst (X W^T, M = 112, N = 256, K = 768: 64 x 64) and in one
+// input gradient 8 % (M = 575, N = 2048, K = 8192: 64 x 128).  `across` is fitted to 66 weight gradients of layers of 256 to 4096, M = 64 ... 5000; its kinds
+// are those whose rows are whole contraction-major regions.
 // e.g. us for 256 x 256 / 256 x 128 / 192 x 128 / 128 x 128 / 64 x 128 / 64 x 64:  M = 100, N = K = 4096  - / 46 / 42 / 35 / 28 / 15;
 // M = 128, N = 11008, K = 4096  73 / 46 / 43 / 42 / 32 / 42;   M = 504, N = 11008, K = 4096  79 / 56 / 80 / 76 / 83 / 106;
 // M = 1500, N = K = 4096  81 / 56 / 50 / 76 / - / 97;   M = 3280, N = K = 4096  93 / 110 / 131 / 136 / - / 196;   input gradient M = 1500,
-// 4096 columns, contraction 11008  203 / 153 / 134 / 195 / - / 251.  The two kinds between (192 x 128: M = 1500 above is 256 tiles of
-// it; 64 x 128: half of 128 x 128's time where those leave half of the CUs without one) are the best ones by 3.5 % on average.
-// Products that fill whole rounds with one of the larger kinds may take another for the columns behind them (the launches
-// follow each other, so the times add).
+// 4096 columns, contraction 11008  203 / 153 / 134 / 195 / - / 251;   M = 256, N = K = 256  9.6 / 7.7 / 6.9 / 5.7 / 4.8 / 5.7, its input gradient 13.3 / 9.3 / 8.2 / 6.6 /
+// 5.5 / 5.7;   M = 1000, N = K = 768  19.8 / 15.6 / 13.4 / 11.0 / 8.7 / 8.2, its input gradient 23.7 / 16.9 / 14.3 / 11.7 / 9.3 / 8.4.  The two kinds between
+// (192 x 128: M = 1500 above is 256 tiles of it; 64 x 128: half of 128 x 128's time where those leave half of the CUs without one) are the best ones by 5 % on average.
+// Products that fill whole rounds with one of the larger kinds may take another for the columns behind them.  The launches follow each
+// other and the times add, but for what the second one's start hides behind the first one's end: with 2 us for that, 46 products for which it matters cost
+// 0.6 % over the better choice on average (with none 1.3 %, with 5 1.2 %).
 // binary32: 128 x 128 tiles, or 32 x 32 ones with the contraction split over four waves up to 192 of the former (us, 128 x 128 /
 // 32 x 32: M = 200, N = K = 768 33 / 7.3; 96 tiles, M = 500, N = 3072, K = 768 36 / 32; 160, M = 640, N = 4096, K = 1024 45 / 60; 192,
 // M = 700, N = K = 4096 158 / 204; 256, M = 1024, N = 4096, K = 1024 52 / 85).  By time the line would lie at 128; but the four partial
@@ -34,17 +37,21 @@ namespace lemo {
 struct GgPlan { int head_cols; GgTile head, rest; };
 struct GgFit { GgTile tile; int rows, cols; double a, b, c[2], d, e; };
 static GgPlan gg_plan(long long M, int N, int K, int layout, lemo_dtype_t dt) {
-    static constexpr GgFit along[] = {{GG_T256, 256, 256, 4.7, 1.525, {1.06, 1.008}, 0.333, 4.4}, {GG_T256x128, 256, 128, 4.0, 0.863, {0.647, 0.658}, 0.203, 2.6},
-                                      {GG_T192x128, 192, 128, 3.3, 0.701, {0.554, 0.531}, 0.145, 2.9}, {GG_T128, 128, 128, 2.8, 0.534, {0.474, 0.472}, 0.067, 2.5},
-                                      {GG_T64x128, 64, 128, 2.3, 0.374, {0.373, 0.362}, 0.064, 1.8}, {GG_T64, 64, 64, 3.1, 0.198, {0.215, 0.227}, 0.029, 2.8}};
+    static constexpr GgFit along[] = {{GG_T256, 256, 256, 6.43, 1.405, {1.004, 0.998}, 0.347, 5.76}, {GG_T256x128, 256, 128, 4.76, 0.812, {0.735, 0.655}, 0.129, 5.19},
+                                      {GG_T192x128, 192, 128, 4.36, 0.673, {0.617, 0.573}, 0.091, 4.24}, {GG_T128, 128, 128, 3.62, 0.529, {0.498, 0.461}, 0.068, 3.01},
+                                      {GG_T64x128, 64, 128, 3.19, 0.388, {0.359, 0.307}, 0.040, 1.78}, {GG_T64, 64, 64, 4.59, 0.226, {0.223, 0.207}, 0.012, 1.27}};
+    static constexpr GgFit mixed[] = {{GG_T256, 256, 256, 8.34, 1.429, {0.919, 1.011}, 0.472, 11.79}, {GG_T256x128, 256, 128, 6.15, 0.819, {0.658, 0.701}, 0.178, 7.01},
+                                      {GG_T192x128, 192, 128, 4.82, 0.672, {0.583, 0.600}, 0.087, 6.43}, {GG_T128, 128, 128, 4.71, 0.534, {0.486, 0.542}, 0.040, 3.94},
+                                      {GG_T64x128, 64, 128, 3.86, 0.409, {0.404, 0.411}, 0.008, 2.24}, {GG_T64, 64, 64, 4.45, 0.272, {0.264, 0.156}, 0.017, 1.33}};
     static constexpr GgFit across[] = {{GG_T256, 256, 256, 5.6, 1.51, {1.16, 1.16}, 0.14, 7.1}, {GG_T256x128, 256, 128, 5.0, 0.94, {0.75, 0.75}, 0.13, 5.0},
                                        {GG_T128, 128, 128, 3.2, 0.59, {0.56, 0.56}, 0.02, 3.6}, {GG_T64, 64, 64, 4.4, 0.18, {0.17, 0.17}, 0.30, 4.2}};
     if (dt == LEMO_F32) {
         const double n128 = (double)((M + 127) / 128) * (double)(((long long)N + 127) / 128);
         return {0, GG_T128, n128 <= 192 ? GG_T64 : GG_T128};
     }
-    const GgFit* fits = layout == GG_TN ? across : along;
+    const GgFit* fits = layout == GG_TN ? across : layout == GG_NN ? mixed : along;
     const int kinds = layout == GG_TN ? 4 : 6, heads = kinds / 2;  // heads: the kinds that may come before another one
+    const double meets = layout == GG_TN ? 0. : 2.;                // the second launch starts as the first one ends
     const double k = K / 64.;
     auto time = [&](const GgFit& f, long long cols) {
         const double n = (double)((M + f.rows - 1) / f.rows) * (double)((cols + f.cols - 1) / f.cols);
@@ -60,7 +67,7 @@ static GgPlan gg_plan(long long M, int N, int K, int layout, lemo_dtype_t dt) {
         const long long cols = rounds * 256 / tm * fits[h].cols;  // columns whose tiles fit whole rounds
         if (cols <= 0 || cols >= N) continue;
         for (int t = h + 1; t < kinds; ++t) {
-            const double both = time(fits[h], cols) + time(fits[t], N - cols);
+            const double both = time(fits[h], cols) + time(fits[t], N - cols) - meets;
             if (both < least) { least = both; best = {(int)cols, fits[h].tile, fits[t].tile}; }
         }
     }

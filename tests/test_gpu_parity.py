@@ -1092,20 +1092,22 @@ def test_gather_gemm_mid_tiles_exact(lemo, form, M, N, K):
     test_gather_gemm_tiles_exact(lemo, form, M, N, K, "bf16")
 
 
-@pytest.mark.parametrize("form,M,N,K", [
-    # 192 x 128: less than a slab, one, a piece more, as many as the ring holds (4), more; ragged rows and columns
-    ("nt", 2419, 1869, 8), ("add", 1861, 2992, 64), ("dx", 1515, 3064, 72), ("add", 2454, 1785, 136), ("nt", 766, 6761, 200), ("dx", 766, 6760, 200),
-    ("dx", 798, 5920, 264), ("nt", 1584, 2512, 328), ("add", 418, 8391, 392),
-    # 64 x 128
-    ("nt", 241, 1165, 8), ("dx", 344, 3544, 64), ("add", 111, 10601, 72), ("nt", 203, 5656, 136), ("dx", 1102, 912, 200), ("nt", 554, 2921, 264),
-    ("add", 72, 3280, 328), ("dx", 1673, 856, 392), ("nt", 211, 7184, 456),
-    # 128 x 128
-    ("nt", 2142, 1229, 8), ("add", 1519, 2520, 64), ("dx", 2037, 1816, 72), ("nt", 2073, 1264, 136), ("dx", 1133, 3264, 200), ("add", 2259, 1461, 264),
-    ("nt", 1913, 1552, 328),
-    # 64 x 64
-    ("nt", 122, 2200, 1000), ("dx", 61, 4000, 1000), ("add", 200, 1003, 2056)])
-def test_gather_gemm_tiles_of_128_columns_exact(lemo, form, M, N, K):
-    """The kinds of tiles that small and middle-sized products take, from one slab to more than the ring of stages holds."""
+# bf16 products by the kind of tiles they take: less than a slab, one, a piece more, as many as the ring of stages holds, more; ragged rows and columns.
+TILE_KINDS = {
+    "256x256": [("nt", 898, 8257, 200), ("add", 933, 7731, 64), ("dx", 978, 8256, 264), ("dx", 1174, 6832, 328)],
+    "256x128": [("nt", 1199, 6095, 136), ("add", 642, 8369, 200), ("nt", 963, 5694, 264), ("add", 670, 8514, 328), ("dx", 1945, 3864, 136), ("dx", 983, 5656, 200),
+                ("dx", 1156, 4624, 264), ("dx", 992, 5480, 328)],
+    "192x128": [("nt", 563, 7776, 64), ("nt", 897, 4572, 72), ("add", 650, 5908, 136), ("add", 525, 7236, 200), ("add", 459, 8309, 264), ("nt", 3308, 1175, 328),
+                ("dx", 926, 9024, 64), ("dx", 2338, 1688, 136), ("dx", 474, 8424, 200), ("dx", 515, 6616, 264), ("dx", 514, 6816, 392)],
+    "128x128": [("nt", 1616, 1854, 8), ("add", 202, 8937, 64), ("nt", 2375, 796, 72), ("add", 205, 8390, 136), ("add", 2387, 775, 200), ("nt", 286, 6741, 328),
+                ("dx", 706, 8320, 8), ("dx", 1488, 2632, 72), ("dx", 200, 8672, 136), ("dx", 202, 8344, 264), ("dx", 201, 8520, 328)],
+    "64x128": [("nt", 91, 334, 8), ("add", 123, 115, 64), ("nt", 67, 109, 72), ("add", 71, 677, 200), ("add", 58, 114, 264), ("nt", 222, 107, 328), ("nt", 112, 337, 392),
+               ("dx", 86, 192, 8), ("dx", 117, 272, 64), ("dx", 53, 632, 136), ("dx", 58, 360, 200), ("dx", 77, 4584, 328), ("dx", 92, 7904, 392)],
+    "64x64": [("nt", 122, 2200, 1000), ("add", 200, 1003, 2056), ("dx", 1830, 168, 264), ("dx", 138, 400, 328), ("dx", 106, 696, 392), ("dx", 61, 4000, 1000)]}
+
+
+@pytest.mark.parametrize("form,M,N,K", [c for kind in TILE_KINDS.values() for c in kind])
+def test_gather_gemm_every_kind_of_tiles_exact(lemo, form, M, N, K):
     test_gather_gemm_tiles_exact(lemo, form, M, N, K, "bf16")
 
 

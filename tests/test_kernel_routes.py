@@ -52,7 +52,7 @@ def run(runtime):
     lib = ctypes.CDLL(LIB)
     kinds = {"p": ctypes.c_void_p, "i": ctypes.c_int32, "l": ctypes.c_int64, "f": ctypes.c_float, "z": ctypes.c_size_t}
     for fn, args in (("score_rowstats", "ppliiiillllfipp"), ("score_colsums", "ppliiiillllfiipppp"), ("score_blocks", "ppliiiillllfiiippppzp"),
-                     ("gather_gemm", "pllplplppliiip"), ("gather_gemm_dw", "plpllplpliiipzp")):
+                     ("gather_gemm", "pllplplppliiip"), ("gather_gemm_dx", "pllplpllpiiip"), ("gather_gemm_dw", "plpllplpliiipzp")):
         getattr(lib, "lemo_" + fn).argtypes = [kinds[k] for k in args]
     seen = ctypes.c_int.in_dll(hip, "n_launched")
     names, threads = (ctypes.c_char_p * 64).in_dll(hip, "launched"), (ctypes.c_int * 64).in_dll(hip, "threads")
@@ -67,13 +67,16 @@ def run(runtime):
     def gemm(dt, M, N, K):
         return lib.lemo_gather_gemm(P, M, K, None, M, P, K, None, P, N, K, N, dt, None)
 
+    def gemm_dx(dt, M, N, K):  # [M, N], contraction K
+        return lib.lemo_gather_gemm_dx(P, K, M, P, N, P, N, M, None, N, K, dt, None)
+
     def gemm_dw(dt, M, N, K):  # [M, N] of K tokens
         return lib.lemo_gather_gemm_dw(P, M, P, K, N, None, K, 1 << 50, N, N, M, dt, P, 1 << 40, None)
 
     out = []
     for entry, *args in json.load(sys.stdin):
         seen.value = 0
-        rc = {"sweeps": sweeps, "blocks": blocks, "gemm": gemm, "gemm_dw": gemm_dw}[entry](*args)
+        rc = {"sweeps": sweeps, "blocks": blocks, "gemm": gemm, "gemm_dx": gemm_dx, "gemm_dw": gemm_dw}[entry](*args)
         assert rc == 0, (entry, args, rc)
         out.append([(names[i].decode(), threads[i]) for i in range(seen.value)])
     json.dump(out, sys.stdout)
@@ -198,6 +201,27 @@ def test_small_fp32_tiles(launches, entry, M, N, edge):
     for K in (16, 1024):
         names = [name for name, _ in launches([(entry, F32, M, N, K)])[0]]
         assert len(names) == 1 and re.search(r"gather_gemm_small_kernelIfLb[01]ELi\dELi1ELi1ELb0ELi(\d+)E", names[0])[1] == str(edge), names
+
+
+@pytest.mark.parametrize("entry,M,N,K,tile", [
+    ("gemm_dx", 100, 512, 512, "64x64"), ("gemm_dx", 408, 512, 512, "64x64"), ("gemm_dx", 2000, 512, 512, "64x64"), ("gemm_dx", 3277, 512, 512, "64x128"),
+    ("gemm_dx", 256, 256, 256, "64x128"), ("gemm_dx", 256, 256, 768, "64x64"), ("gemm_dx", 2000, 768, 768, "64x128"),
+    ("gemm", 50, 256, 256, "64x128"), ("gemm", 5000, 256, 256, "64x128"), ("gemm", 408, 512, 512, "64x128"), ("gemm", 256, 256, 1024, "64x64"), ("gemm", 408, 3072, 768, "64x128")])
+def test_tiles_of_narrow_bf16_products(launches, entry, M, N, K, tile):
+    """64 x 64 tiles against 64 x 128 ones, which cost an input gradient more: the one that was measured to be faster."""
+    names = [name for name, _ in launches([(entry, BF16, M, N, K)])[0]]
+    assert len(names) == 1 and re.search({"64x64": "gather_gemm_small_kernel", "64x128": r"gather_gemm_mid_kernelILb[01]ELi\dELi1E"}[tile], names[0]), names
+
+
+def test_the_shapes_of_the_tile_tests_take_their_kinds(launches):
+    from test_gpu_parity import TILE_KINDS
+    kernel = {"256x256": "large_kernel", "256x128": r"mid_kernelILb[01]ELi\dELi4E", "192x128": r"mid_kernelILb[01]ELi\dELi3E", "128x128": r"mid_kernelILb[01]ELi\dELi2E",
+              "64x128": r"mid_kernelILb[01]ELi\dELi1E", "64x64": "small_kernel"}
+    entry = {"nt": "gemm", "add": "gemm", "dx": "gemm_dx"}   # (the in-place add takes the tiles of the plain product)
+    for kind, shapes in TILE_KINDS.items():
+        assert {entry[form] for form, *_ in shapes} == {"gemm", "gemm_dx"}
+        for shape, made in zip(shapes, launches([(entry[form], BF16, *size) for form, *size in shapes])):
+            assert len(made) == 1 and re.search(kernel[kind], made[0][0]), (kind, shape, made)
 
 
 if __name__ == "__main__":
