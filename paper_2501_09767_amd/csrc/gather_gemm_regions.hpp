@@ -15,9 +15,9 @@ constexpr int RG_TOK = RG_WAVES * 1024;               // (GG_TN) token rings: pe
 // The loads of one thread.  Unit u = i * 512 + tid of a region is its LDS bytes [16 u, 16 u + 16); the lane asks for the piece
 // that belongs there.  Rows along the contraction, 8 pieces: piece p of row r at p ^ (r / 2 % 8), so that one piece of 16 rows meets
 // all banks.  Contraction-major rows, 16 pieces of 8 columns: at p ^ kswz(r); a half-wave of a transposing read takes rows 0-3
-// and 8-11 (+ 4, + 16), two pieces each.  The hardware range check sees the per-thread offset only: rows past an operand's end
+// and 8-11 (+ 4, + 16), two pieces each.  The range check (raw_rsrc): rows past an operand's end
 // fail it (or are clamped to the last one, A), pieces past the end of the contraction are given an offset at the descriptor's
-// size in both operands and arrive as zeros; the scalar offset moves along a row.
+// size in both operands and arrive as zeros; the scalar offset moves along a row, whose valid pieces pass with it.
 __device__ __forceinline__ constexpr int rg_kswz(int r) { return ((r & 3) | ((r >> 3) & 1) << 2) << 1; }
 
 // Load u of an operand: rows (columns) 64 u .. + 63; contraction-major, half u % 2 of the contraction rows of region u / 2.

@@ -82,9 +82,9 @@ __global__ __launch_bounds__(SG_THREADS, GW == 4 ? 2 : 1) void gather_gemm_small
     const int K = p.K, kbytes = K * ESZ;  // (along-the-contraction operands: bytes of a row)
     const int nk = A_KMAJOR ? (K + G::KROWS - 1) / G::KROWS : (kbytes + SG_KB - 1) / SG_KB;
 
-    // Per-thread byte offsets of the loads.  The hardware range check sees the per-thread offset only: rows past an
+    // Per-thread byte offsets of the loads.  The range check (raw_rsrc): rows past an
     // operand's end fail it (or are clamped to the last one, A), pieces past the end of the contraction are given an
-    // offset at the descriptor's size in both operands and arrive as zeros; the scalar offset moves along a row.
+    // offset at the descriptor's size in both operands and arrive as zeros; the scalar offset moves along a row, whose valid pieces pass with it.
     auto kpos = [&](int i) { return ((gtid & 7) ^ G::swz(i * 8 * GW + (gtid >> 3))) * 16; };  // of piece i in a row's slab
     unsigned a_voff[NLD], b_voff[NLD];
 #pragma unroll

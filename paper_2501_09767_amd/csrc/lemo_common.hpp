@@ -55,7 +55,9 @@ __device__ __forceinline__ void lds_direct_b128(u32x4 rsrc, unsigned lds_off, in
 __device__ __forceinline__ void lds_direct_b32(u32x4 rsrc, unsigned lds_off, int voff, int soff = 0) {
     asm volatile("s_mov_b32 m0, %0\n\tbuffer_load_dword %1, %2, %3 offen lds" ::"s"(lds_off), "v"(voff), "s"(rsrc), "s"(soff) : "memory");
 }
-// raw buffer descriptor over [base, base + bytes): offsets at or past `bytes` read as zero
+// Raw buffer descriptor over [base, base + bytes).  The range check takes the per-thread and the scalar offset together, without wrapping at
+// 2^32 (seen on hardware: of 256 bytes, a scalar offset of 128 leaves the first eight 16-byte pieces; of none, none; at sizes and offsets just below 2^32
+// likewise).  What it refuses reaches no memory and arrives as zeros, in LDS as well.
 __device__ __forceinline__ u32x4 raw_rsrc(const void* base, long long bytes) {
     const unsigned long long a = reinterpret_cast<unsigned long long>(base);
     u32x4 r;

@@ -47,8 +47,7 @@ __global__ __launch_bounds__(256, 2) void tilemax_slab_kernel(BlockParams p) {
 
     // Unit u = i * 256 + tid of a slab is its LDS bytes [16 u, 16 u + 16): row u / 8 (queries, then keys), position u % 8, which
     // holds piece (u % 8) ^ (row / 2 % 8), so that one piece of 16 rows meets all banks.  The descriptor ends with the
-    // last row, so that rows past the end (larger per-thread offsets) arrive as zeros; the scalar offset moves along a row and counts
-    // against the descriptor's size as well.
+    // last row, so that rows past the end fail the range check (raw_rsrc) and arrive as zeros; the scalar offset moves along a row.
     const unsigned q_row_bytes = (unsigned)p.q_ts * 2u, k_row_bytes = (unsigned)p.k_ts * 2u;  // host: < 2^24
     unsigned voff[G::NLOAD];
 #pragma unroll
@@ -58,7 +57,7 @@ __global__ __launch_bounds__(256, 2) void tilemax_slab_kernel(BlockParams p) {
     }
     const unsigned l_voff = (unsigned)min(q0 + (tid & 127), S - 1) * 4u;  // rows past the end reuse the last row's (left out at the end)
     const unsigned lds0 = lds_offset_of(smem) + (unsigned)wave * 1024u, lds_l = lds_offset_of(smem) + G::LSE_BASE + (unsigned)(wave & 1) * 256u;
-    u32x4 aim_q, aim_k, aim_l;  // descriptors of the head whose slabs are asked for; past the last one of length zero
+    u32x4 aim_q, aim_k, aim_l;  // descriptors of the head whose slabs are asked for; past the last one of length zero: all is refused
     auto aim = [&](int hh) {
         const bool live = hh < p.H;
         const int h = min(hh, p.H - 1), g = (int)((unsigned)h / group);
@@ -113,7 +112,7 @@ __global__ __launch_bounds__(256, 2) void tilemax_slab_kernel(BlockParams p) {
     for (int n = 0; n <= G::NLOAD; ++n) issue_one(n, G::SLABS == 1 ? 1 : 0, G::SLABS == 1 ? 0 : 1, G::STAGE);
     aim(G::SLABS == 1 ? 2 : 1);
 
-    f32x4 acc[4][4], carry[4];  // carry: tiles (3, 1), (3, 0), (3, 3), (3, 2) of the head before
+    f32x4 acc[4][4], carry[4];  // carry: tiles (3, 2), (3, 3), (3, 0), (3, 1) of the head before
 #pragma unroll
     for (int t = 0; t < 4; ++t) carry[t] = f32x4{0.f, 0.f, 0.f, 0.f};
     unsigned st = 0;  // LDS offset of the ring stage whose slab is in the registers
@@ -175,7 +174,7 @@ __global__ __launch_bounds__(256, 2) void tilemax_slab_kernel(BlockParams p) {
     }
 #pragma unroll
     for (int m = 0; m < 16; ++m) add(3, (m / 4) ^ 2, carry[m / 4], m % 4);
-    __builtin_amdgcn_s_waitcnt(vmcnt_imm(0));  // (requests past the last head write nothing, but are on their way)
+    __builtin_amdgcn_s_waitcnt(vmcnt_imm(0));  // (requests past the last head, of length zero, still write zeros to LDS)
 
     // maximum of every 32 x 32 tile over the pairs that are admitted
     const bool excl = (p.flags & LEMO_EXCLUDE_SELF) != 0;

@@ -94,10 +94,10 @@ def test_no_request_leaves_its_operand(layout, M, N, K, pad, bm, bn):
     width = {"A": M if layout == "tn" else K, "B": K if layout == "nt" else N}
     total = {"A": (((K if layout == "tn" else S) - 1) * lda + width["A"]) * 2, "B": (({"nt": N, "nn": K, "tn": S}[layout] - 1) * ldb + width["B"]) * 2}
     for op, base, size, voff, soff, row, byte, wanted in requests(layout, bm, bn, M, N, K, S, lda, ldb, idx):
-        if voff + 16 <= size:                                # the hardware lets it through
+        if voff + soff + 16 <= size:                         # the hardware lets it through
             assert 0 <= base + voff + soff <= total[op] - 16, (op, base, size, voff, soff)
         if wanted and byte + 16 <= width[op] * 2:
-            assert voff + 16 <= size and base + voff + soff == row * (lda if op == "A" else ldb) * 2 + byte, (op, row, byte)
+            assert voff + soff + 16 <= size and base + voff + soff == row * (lda if op == "A" else ldb) * 2 + byte, (op, row, byte)
         if not wanted:
             assert voff >= size, (op, row, byte)             # arrives as zeros
 

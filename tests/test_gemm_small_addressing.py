@@ -1,8 +1,8 @@
 """Host model of the loads and LDS positions of the selective-load GEMM on 64 x 64 tiles (bf16), 128 x 128 and 32 x 32 ones (binary32) (CPU only).
 
 The kernel fills its slabs with LDS-direct loads: unit u of an operand's slab (16 bytes) goes to LDS bytes [16 u, 16 u + 16),
-and the lane that asks for it chooses which piece of which row that is.  The range check of the buffer descriptor sees the
-per-thread offset, not the scalar one.  This restates the kernel's formulas, in the three operand layouts, and checks that
+and the lane that asks for it chooses which piece of which row that is.  The range check of the buffer descriptor takes
+the per-thread and the scalar offset together.  This restates the kernel's formulas, in the three operand layouts, and checks that
 every request that passes the check stays inside its operand, that pieces past the end of the contraction are refused in at
 least one operand, and that the fragment reads find the piece they want where the loads put it."""
 import pytest
@@ -131,10 +131,10 @@ def test_no_request_leaves_its_operand(gw, esz, wt, layout, M, N, K, pad):
     total = {"A": ((a_rows - 1) * lda + (M if layout == "tn" else K)) * esz, "B": ((b_rows - 1) * ldb + (K if layout == "nt" else N)) * esz}
     pitch = {"A": lda * esz, "B": ldb * esz}
     for op, base, size, voff, soff, row, byte, wanted in requests(g, layout, M, N, K, S, lda, ldb, idx):
-        if voff + 16 <= size:                             # the hardware lets it through
+        if voff + soff + 16 <= size:                      # the hardware lets it through
             assert 0 <= base + voff + soff <= total[op] - 16, (op, base, size, voff, soff)
         if wanted and byte + 16 <= (M if op == "A" and layout == "tn" else K if op == "A" or layout == "nt" else N) * esz:
-            assert voff + 16 <= size and base + voff + soff == row * pitch[op] + byte, (op, row, byte)
+            assert voff + soff + 16 <= size and base + voff + soff == row * pitch[op] + byte, (op, row, byte)
         if not wanted:
             assert voff >= size, (op, row, byte)          # arrives as zeros
 

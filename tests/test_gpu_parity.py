@@ -724,6 +724,23 @@ def test_score_blocks_many_rectangles(lemo, S, H, Hkv, d, flags):
         assert_blocks_close(tb.cpu().numpy(), want_tb, "token blocks", 1e-6 if mode == 0 else 1e-5)
 
 
+@pytest.mark.parametrize("S,H,Hkv,d,flags", [(3199, 4, 2, 128, 3), (3130, 3, 3, 64, 1), (2290, 4, 1, 64, 2), (2200, 3, 3, 128, 0), (1000, 4, 2, 128, 3), (640, 3, 1, 64, 2)])
+def test_score_blocks_strided_views(lemo, S, H, Hkv, d, flags):
+    """A fused QKV buffer, and heads stored one after the other, with NaN in everything beside them: the bits of the packed tensors.  More than 256
+    rectangles (whose kernel moves a scalar offset along the row), and few."""
+    say(f"[blocks strided] S={S} H={H}/{Hkv} d={d} flags={flags}")
+    Q, K = (t.cuda() for t in wl.tiny_qk(S, H, Hkv, d, "bf16", seed=S + d))
+    want, want_tb = lemo.lemo_score_blocks(Q, K, 32, flags=flags)
+    fused = torch.full((S + 3, H + 2 * Hkv, d), math.nan, dtype=torch.bfloat16, device="cuda")
+    apart = torch.full((H + Hkv, S + 5, d), math.nan, dtype=torch.bfloat16, device="cuda")
+    views = []
+    for q, k in ((fused[:S, :H], fused[:S, H:H + Hkv]), (apart[:H, :S].transpose(0, 1), apart[H:, :S].transpose(0, 1))):
+        views.append((q.copy_(Q), k.copy_(K)))
+    for q, k in views + [(views[0][0], views[1][1]), (views[1][0], K)]:
+        got, got_tb = lemo.lemo_score_blocks(q, k, 32, flags=flags)
+        assert torch.equal(got, want) and torch.equal(got_tb, want_tb)
+
+
 def test_score_blocks_options_and_determinism(lemo):
     say("[blocks] options")
     Q, K = wl.tiny_qk(700, 4, 2, 128, "bf16", seed=5)
