@@ -23,9 +23,10 @@ namespace lemo {
 // e.g. us for 256 x 256 / 256 x 128 / 192 x 128 / 128 x 128 / 64 x 128 / 64 x 64:  M = 100, N = K = 4096  - / 46 / 42 / 35 / 28 / 15;
 // M = 128, N = 11008, K = 4096  73 / 46 / 43 / 42 / 32 / 42;   M = 504, N = 11008, K = 4096  79 / 56 / 80 / 76 / 83 / 106;
 // M = 1500, N = K = 4096  81 / 56 / 50 / 76 / - / 97;   M = 3280, N = K = 4096  93 / 110 / 131 / 136 / - / 196;   input gradient M = 1500,
-// 4096 columns, contraction 11008  203 / 153 / 134 / 195 / - / 251;   M = 256, N = K = 256  9.6 / 7.7 / 6.9 / 5.7 / 4.8 / 5.7, its input gradient 13.3 / 9.3 / 8.2 / 6.6 /
-// 5.5 / 5.7;   M = 1000, N = K = 768  19.8 / 15.6 / 13.4 / 11.0 / 8.7 / 8.2, its input gradient 23.7 / 16.9 / 14.3 / 11.7 / 9.3 / 8.4.  The two kinds between
-// (192 x 128: M = 1500 above is 256 tiles of it; 64 x 128: half of 128 x 128's time where those leave half of the CUs without one) are the best ones by 5 % on average.
+// 4096 columns, contraction 11008  203 / 153 / 134 / 195 / - / 251;   M = 256, N = K = 256  9.6 / 7.7 / 6.9 / 5.7 / 4.8 / 5.7, its input
+// gradient 13.3 / 9.3 / 8.2 / 6.6 / 5.5 / 5.7;   M = 1000, N = K = 768  19.8 / 15.6 / 13.4 / 11.0 / 8.7 / 8.2, its input gradient 23.7 / 16.9 /
+// 14.3 / 11.7 / 9.3 / 8.4.  The two kinds between (192 x 128: M = 1500 above is 256 tiles of it; 64 x 128: half of 128 x 128's time where those leave
+// half of the CUs without one) are worth 5 % on average.
 // Products that fill whole rounds with one of the larger kinds may take another for the columns behind them.  The launches follow each
 // other and the times add, but for what the second one's start hides behind the first one's end: with 2 us for that, 46 products for which it matters cost
 // 0.6 % over the better choice on average (with none 1.3 %, with 5 1.2 %).

@@ -15,7 +15,7 @@
 //   192 x 128  M = 1500: N = K = 4096 50 (256 x 128: 56), input gradient of 11008 x 4096 134 (153);  M = 522, N = 8192, K = 2048 25.7 (27.6)
 //   128 x 128  M = 256, N = 11008, K = 4096: 42;  M = 768, N = 3072, K = 768: 9.4
 //   64 x 128   M = 128, N = 11008, K = 4096: 32 (128 x 128: 42);  M = 500, N = K = 4096 30 (37);  M = 408, N = 3072, K = 768 8.0 (9.7)
-// (128 x 64 does as well as 64 x 128, 128 x 96 gains 7 % where 64 x 128 loses; neither fits contraction-major regions.)
+// (128 x 64 does as well as 64 x 128.  128 x 96 gained 7 % in X W^T where 64 x 128 loses, M = 256, N = 11008; it is not built: B's rows are loaded 64 at a time.)
 #include "gather_gemm_regions.hpp"
 
 namespace lemo {

@@ -588,16 +588,21 @@ static int launch_sweeps(const ScoreParams& p_in, int which, hipStream_t st) {
 // 512 / KS rows.  Under the mask a launch is as long as its longest block or as all of them over 256 CUs: many heads of few tokens are
 // better off with the smaller blocks that two workgroups per CU take in turn.  Without a mask it takes as many rounds as its workgroups fill the CUs, and
 // 513 to 640 tokens end in a stage that is half empty.  Both sweeps, time with eight waves / with four and the KS above, n = 256-row blocks:
-//   d = 128, causal  KS = 8: n = 64 (512 tokens, 32 heads) 0.96, (16384, 1) 0.70, 96 (6000, 4) 0.79, (2000, 12) 0.93, (1500, 16) 0.97, 112 (1949, 14)
-//                    0.94, (1792, 16) 1.01, 120 (1500, 20) 1.13, 128 (8192, 4) 0.85, (2048, 16) 1.02;  KS = 4: n = 160 (1280, 32) 0.86, 192 (1500, 32) 0.94, 216
-//                    (1323, 36) 1.11, 256 (4096, 16) 0.90, (2048, 32) 1.00, (1024, 64) 1.20;  KS = 2: n = 432 (2304, 48) 1.00, 448 (7168, 16) 0.93, (1846, 56) 1.08, 512 (8192, 16)
-//                    0.96, (2048, 64) 1.04;  KS = 1: n = 896 (7168, 32) 0.95, 980 (12345, 20) 0.98, 1024 (8192, 32) 0.98, (4096, 64) 1.04, 1008 (5376, 48: 528 workgroups) 1.04
-//   d = 64, causal   KS = 8: n = 64 (16384, 1) 0.71, (2048, 8) 0.80, 80 (1000, 20) 1.01, 112 (3584, 8) 0.84, 128 (4096, 8) 0.92, (2048, 16) 1.03;  KS = 4: n = 256 1.06
-//   d = 128, full    KS = 8: n = 64 (16384, 1) 0.75, (1000, 16) 0.90, 60 (640, 20) 1.06, (641, 20) 0.93;  KS = 4: n = 96 (1500, 16) 0.87, (640, 32) 1.08, 128 (4096, 8)
-//                    0.87, (512, 64) 1.02;  KS = 2: n = 192 (3000, 16) 0.86, (640, 64) 1.06, 256 (4096, 16) 0.94;  KS = 1: n = 448 (7168, 16) 0.95, 512 (4096, 32) 0.95, 896 (7168, 32)
-//                    0.95, 1024 (8192, 32) 0.97, 1008 (2304, 112: 560 workgroups) 1.29, (6254, 40: 520) 1.35
-//   d = 64, full     KS = 8: n = 64 (16384, 1) 0.71, (1000, 16) 0.90, 60 (640, 20) 1.07;  KS = 4: n = 96 (3000, 8) 0.83, (640, 32) 1.09, 128 (4096, 8) 0.81;  KS = 1: n = 448
-//                    (7168, 16) 0.93, 512 (8192, 16) 0.97, 1024 (8192, 32) 1.00, 1008 (2304, 112) 1.38
+//   d = 128, causal  KS = 8: n = 64 (512 tokens, 32 heads) 0.96, (16384, 1) 0.70, 96 (6000, 4) 0.79, (2000, 12) 0.93, (1500, 16) 0.97,
+//                    112 (1949, 14) 0.94, (1792, 16) 1.01, 120 (1500, 20) 1.13, 128 (8192, 4) 0.85, (2048, 16) 1.02
+//                    KS = 4: n = 160 (1280, 32) 0.86, 192 (1500, 32) 0.94, 216 (1323, 36) 1.11, 256 (4096, 16) 0.90, (2048, 32) 1.00, (1024, 64) 1.20
+//                    KS = 2: n = 432 (2304, 48) 1.00, 448 (7168, 16) 0.93, (1846, 56) 1.08, 512 (8192, 16) 0.96, (2048, 64) 1.04
+//                    KS = 1: n = 896 (7168, 32) 0.95, 980 (12345, 20) 0.98, 1024 (8192, 32) 0.98, (4096, 64) 1.04, 1008 (5376, 48: 528
+//                    workgroups) 1.04
+//   d = 64, causal   KS = 8: n = 64 (16384, 1) 0.71, (2048, 8) 0.80, 80 (1000, 20) 1.01, 112 (3584, 8) 0.84, 128 (4096, 8) 0.92, (2048, 16) 1.03
+//                    KS = 4: n = 256 1.06
+//   d = 128, full    KS = 8: n = 64 (16384, 1) 0.75, (1000, 16) 0.90, 60 (640, 20) 1.06, (641, 20) 0.93
+//                    KS = 4: n = 96 (1500, 16) 0.87, (640, 32) 1.08, 128 (4096, 8) 0.87, (512, 64) 1.02
+//                    KS = 2: n = 192 (3000, 16) 0.86, (640, 64) 1.06, 256 (4096, 16) 0.94
+//                    KS = 1: n = 448 (7168, 16) 0.95, 512 (4096, 32) 0.95, 896 (7168, 32) 0.95, 1024 (8192, 32) 0.97, 1008 (2304, 112: 560
+//                    workgroups) 1.29, (6254, 40: 520) 1.35
+//   d = 64, full     KS = 8: n = 64 (16384, 1) 0.71, (1000, 16) 0.90, 60 (640, 20) 1.07;  KS = 4: n = 96 (3000, 8) 0.83, (640, 32) 1.09, 128 (4096,
+//                    8) 0.81;  KS = 1: n = 448 (7168, 16) 0.93, 512 (8192, 16) 0.97, 1024 (8192, 32) 1.00, 1008 (2304, 112) 1.38
 // Where rows are not shared either way only: whole rows add up less exactly.  Column sums of 16 heads of 64, relative 2-norm from 64 bits with
 // KS = 2 / 1: 14336 tokens 7.4e-8 / 1.2e-6, 16384 7.1e-8 / 1.3e-6, 14336 without a mask 9.8e-8 / 4.0e-6.
 template <int D, int NRT>
@@ -610,7 +615,8 @@ static int launch_sweeps_ks(const ScoreParams& p, long long n, int which, hipStr
         if constexpr (D == 128)
             if (causal ? n > 400 && n <= 512 && p.H <= 48 : n <= 256) return launch_sweeps<D, NRT, 2, 8>(p, which, st);
         const long long n512 = (long long)p.H * ((p.S + 511) / 512);  // workgroups with KS = 1
-        if (p.S >= 2048 && ((D == 128 && n >= 896 && n512 <= 512 && (!causal || p.H <= 48)) || (!causal && n >= 448 && n512 <= 256))) return launch_sweeps<D, NRT, 1, 8>(p, which, st);
+        const bool full_rounds = (!causal && n >= 448 && n512 <= 256) || (D == 128 && n >= 896 && n512 <= 512 && (!causal || p.H <= 48));
+        if (p.S >= 2048 && full_rounds) return launch_sweeps<D, NRT, 1, 8>(p, which, st);
     }
     if (!causal) {
         if (n <= 64 || (D == 64 && n > 128 && n <= 192)) return launch_sweeps<D, NRT, 4, 4>(p, which, st);
@@ -624,7 +630,7 @@ static int launch_sweeps_ks(const ScoreParams& p, long long n, int which, hipStr
 
 int prepare_score(lemo_dtype_t dt, int d) {
     if (dt == LEMO_F32) return prepare_sweeps_f32(d);
-    return d == 128 ? prepare_sweeps<128, LEMO_NRT_BF16_128>() : prepare_sweeps<64, 2>();
+    return d == 128 ? prepare_sweeps<128, 2>() : prepare_sweeps<64, 2>();
 }
 
 int launch_score(const ScoreParams& p_in, lemo_dtype_t dt, int d, int which, hipStream_t st) {
@@ -635,7 +641,7 @@ int launch_score(const ScoreParams& p_in, lemo_dtype_t dt, int d, int which, hip
     if (which & 3) {
         rc = prepare_score(dt, d);
         if (rc) return rc;
-        if (dt == LEMO_BF16 && d == 128) rc = launch_sweeps_ks<128, LEMO_NRT_BF16_128>(p, blocks256, which, st);
+        if (dt == LEMO_BF16 && d == 128) rc = launch_sweeps_ks<128, 2>(p, blocks256, which, st);
         else if (dt == LEMO_BF16 && d == 64) rc = launch_sweeps_ks<64, 2>(p, blocks256, which, st);
         else if (dt == LEMO_F32 && (d == 64 || d == 128)) rc = launch_sweeps_f32(p, d, which, st);
         else return (int)hipErrorInvalidValue;

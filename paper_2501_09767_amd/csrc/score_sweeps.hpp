@@ -5,20 +5,9 @@
 
 namespace lemo {
 
-// resident subtiles per wave for bf16, d = 128 (2 or 4; see Geo)
-#ifndef LEMO_NRT_BF16_128
-#define LEMO_NRT_BF16_128 2
-#endif
-
-#ifndef LEMO_SC_WAVES
-#define LEMO_SC_WAVES 4
-#endif
-constexpr int SC_WAVES = LEMO_SC_WAVES;
-constexpr int SC_THREADS = 64 * SC_WAVES;
-
 // Geometry of one instantiation.  NRT = 32-row MFMA subtiles of the RESIDENT operand a wave keeps in registers:
 //   NRT = 2  64 resident rows per wave, 256 per workgroup, two workgroups per CU (two waves per SIMD)
-//   NRT = 4  128 resident rows per wave, 512 per workgroup, one workgroup per CU: every LDS fragment read feeds
+//   NRT = 4  (not built any more) 128 resident rows per wave, 512 per workgroup, one workgroup per CU: every LDS fragment read feeds
 //            four MFMA chains instead of two (half the LDS traffic per flop), but a SIMD then has no second wave
 //            to run while the first waits at a barrier or on LDS
 // Measured on the 32K-token bf16 d=128 layer: NRT = 2 4.20 / 4.25 ms (sweep 1 / sweep 2), NRT = 4 4.45 / 4.57 ms; with
@@ -28,8 +17,8 @@ constexpr int SC_THREADS = 64 * SC_WAVES;
 // KS = waves that share resident rows: KS consecutive waves hold the same rows and take every stage's streamed subtiles
 // in shares; their statistics are put together through LDS at the end.  A block is then 1/KS as many rows and takes 1/KS
 // as long, at KS times the loads into LDS per flop.
-// More than four waves: one workgroup per CU where there are few, a stage has as many more rows.
-template <typename T, int D, int NRT_, int KS_, int WAVES_ = SC_WAVES> struct Geo {
+// WAVES = 4, or 8: one workgroup per CU where there are few, and stages of twice the rows.
+template <typename T, int D, int NRT_, int KS_, int WAVES_> struct Geo {
     static constexpr int NRT = NRT_, KS = KS_, WAVES = WAVES_, THREADS = 64 * WAVES;
     static constexpr int RES = 32 * NRT;             // resident rows per wave
     static constexpr int BLOCK = WAVES / KS * RES; // resident rows per workgroup
@@ -42,7 +31,7 @@ template <typename T, int D, int NRT_, int KS_, int WAVES_ = SC_WAVES> struct Ge
     __device__ static constexpr int swz(int row) { return CPR >= 16 ? (row & 15) : ((row >> 1) & (CPR - 1)); }
     // byte offset inside a stage of the fragment piece (chunk c, half) of row `row`
     __device__ static constexpr int frag(int row, int c, int half) { return row * ROWB + (((2 * c + half) ^ swz(row)) << 4); }
-    static constexpr int TILE = (ROWB > 256 ? 64 : 128) * WAVES / SC_WAVES;  // streamed rows per LDS stage (two stages; long enough to hide a global load)
+    static constexpr int TILE = (ROWB > 256 ? 16 : 32) * WAVES;  // streamed rows per LDS stage (two stages; long enough to hide a global load)
     static constexpr int NSUB = TILE / 32;           // 32-row MFMA subtiles per stage
     static constexpr int SHARE = NSUB / KS;          // of them, those a wave takes
     static constexpr int NLOAD = TILE * CPR / THREADS;  // 16-byte global loads per thread per stage
