@@ -614,7 +614,7 @@ static int launch_sweeps_ks(const ScoreParams& p, long long n, int which, hipStr
         if (causal ? D == 128 && n > 128 && n <= 256 && p.H <= 32 : n <= 128) return launch_sweeps<D, NRT, 4, 8>(p, which, st);
         if constexpr (D == 128)
             if (causal ? n > 400 && n <= 512 && p.H <= 48 : n <= 256) return launch_sweeps<D, NRT, 2, 8>(p, which, st);
-        const long long n512 = (long long)p.H * ((p.S + 511) / 512);  // workgroups with KS = 1
+        const long long n512 = (long long)p.H * ((p.S + 511ll) / 512);  // workgroups with KS = 1
         const bool full_rounds = (!causal && n >= 448 && n512 <= 256) || (D == 128 && n >= 896 && n512 <= 512 && (!causal || p.H <= 48));
         if (p.S >= 2048 && full_rounds) return launch_sweeps<D, NRT, 1, 8>(p, which, st);
     }
