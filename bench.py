@@ -34,9 +34,9 @@ PEAK_HBM_GBS = 8000.0       # MI355X HBM3E, published
 # The figures belong to the kernel sources they were measured on: "sources" is sources_digest() at that time, and the
 # bench reports traffic as null when the sources have changed since.
 MEASURED_TRAFFIC_BYTES = {
-    "sources": "51a06949d9df6b7e",
-    "C5:rowstats": 2546066227, "C5:colsum": 2678766387, "C5:head_mean_select": 8641126,
-    "C5:gather_gemm": 1687706419, "C5:scatter": 242885837,
+    "sources": "5c0eed281a5de816",
+    "C5:rowstats": 2532561621, "C5:colsum": 2691222485, "C5:head_mean_select": 8639147,
+    "C5:gather_gemm": 1686875989, "C5:scatter": 242885973,
 }
 
 

@@ -1,4 +1,4 @@
-"""Host model of the loads and LDS positions of the selective-load GEMM on 256 x 256, 256 x 128 and 128 x 128 tiles (CPU only).
+"""Host model of the loads and LDS positions of the selective-load GEMM on tiles of 256 x 256 and of 256, 192, 128 or 64 x 128 (CPU only).
 
 An operand's slab comes in regions of 128 rows (contraction-major: 64 rows of 128 columns); a 256-wide tile has two of them.
 Unit u of a region (16 bytes) goes to its LDS bytes [16 u, 16 u + 16), and the lane that asks for it chooses which piece of
@@ -166,11 +166,10 @@ def test_regions_are_waited_for_and_free(nk, tn):
 
 
 @pytest.mark.parametrize("nk", [1, 2, 3, 4, 5, 9])
-@pytest.mark.parametrize("ra,stages", [(1, 4), (2, 3)])
-@pytest.mark.parametrize("tn", [False, True])
-def test_ring_is_waited_for_and_free(nk, ra, stages, tn):
-    """256 x 128 and 128 x 128 tiles: slabs in a ring of stages, and the kept rows' indices in a ring of four entries."""
-    batch, ahead = NLD * (ra + 1) + tn, stages - 1
+@pytest.mark.parametrize("ua,stages,tn", [(1, 4, False), (2, 4, False), (2, 4, True), (3, 4, False), (4, 3, False), (4, 3, True)])
+def test_ring_is_waited_for_and_free(nk, ua, stages, tn):
+    """Tiles of 64 ua x 128: slabs in a ring of stages, and the kept rows' indices in a ring of four entries."""
+    batch, ahead = ua + NLD + tn, stages - 1
     events, holds, unread, entry = [], {}, {}, {}
 
     def done(what, outstanding):                              # loads complete in issue order
@@ -180,7 +179,7 @@ def test_ring_is_waited_for_and_free(nk, ra, stages, tn):
         assert not unread.get(kt % stages), (kt, "overwrites fragments still to be read")
         if tn:
             assert entry[kt % 4] == kt, (kt, "indices of another slab")
-        events.extend([("slab", kt)] * (NLD * (ra + 1)))
+        events.extend([("slab", kt)] * (ua + NLD))
         holds[kt % stages], unread[kt % stages] = kt, True
         if tn:
             events.append(("idx", kt + ahead))
