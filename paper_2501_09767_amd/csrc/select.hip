@@ -90,10 +90,15 @@ __device__ __forceinline__ void select_from_keys(SelectLds<T>& lds, const uint32
         himask = 0xffffffffu << shift;
         if (shift == 0 || count == need) break;  // (all that share the known bits are kept)
         if (count <= WAVE) {  // every wave finds the pivot among the candidates by their ranks
-            for (int t = tid; t < len; t += T)
-                if ((keys[t] & himask) == prefix) lds.candidates[atomicAdd(&lds.n_candidates, 1u)] = keys[t];
-            __syncthreads();
-            const uint32_t mine = (uint32_t)lane < count ? lds.candidates[lane] : 0u;
+            uint32_t mine = 0u;
+            if (count == (uint32_t)len) {  // (a short segment, all in one digit: nothing to pick)
+                if (lane < len) mine = keys[lane];
+            } else {
+                for (int t = tid; t < len; t += T)
+                    if ((keys[t] & himask) == prefix) lds.candidates[atomicAdd(&lds.n_candidates, 1u)] = keys[t];
+                __syncthreads();
+                if ((uint32_t)lane < count) mine = lds.candidates[lane];
+            }
             uint32_t gt = 0u;
             for (uint32_t j = 0; j < count; j += 4)
 #pragma unroll
@@ -155,7 +160,8 @@ __device__ __forceinline__ int segment_keep(int len, int L, int k) {
 }
 
 // 512 threads, from segments of more than 2048 on 1024 (us with 256 / 512 / 1024: segments of 512 4.2 / 4.1 / 4.8, 1024 5.5 / 5.1 / 6.0, 8192
-// 17.7 / 10.3 / 7.7)
+// 17.7 / 10.3 / 7.7), up to 128 tokens 256 (32768 tokens, us with 256 / 512: segments of 16 4.4 / 6.6, all scores equal 5.0 / 7.7; 64 3.6 / 3.8, 4.5 / 5.4; 128 3.6 /
+// 3.6, 4.6 / 4.6; 256 4.0 / 4.0, 4.9 / 4.9)
 template <int T>
 __global__ __launch_bounds__(T) void select_topk_kernel(const float* __restrict__ scores, int S, int L, int k,
                                                                   int* __restrict__ kept) {
@@ -331,7 +337,8 @@ int launch_select(const float* scores, int S, int L, int k, int* kept, hipStream
     });
     if (attr_err != 0) return attr_err;
     const size_t lds = (size_t)Leff * sizeof(uint32_t);
-    if (Leff <= 2048) hipLaunchKernelGGL(select_topk_kernel<512>, dim3(nseg), dim3(512), lds, st, scores, S, L, k, kept);
+    if (Leff <= 128) hipLaunchKernelGGL(select_topk_kernel<256>, dim3(nseg), dim3(256), lds, st, scores, S, L, k, kept);
+    else if (Leff <= 2048) hipLaunchKernelGGL(select_topk_kernel<512>, dim3(nseg), dim3(512), lds, st, scores, S, L, k, kept);
     else hipLaunchKernelGGL(select_topk_kernel<1024>, dim3(nseg), dim3(1024), lds, st, scores, S, L, k, kept);
     return (int)hipGetLastError();
 }

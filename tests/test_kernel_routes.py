@@ -52,7 +52,7 @@ def run(runtime):
     lib = ctypes.CDLL(LIB)
     kinds = {"p": ctypes.c_void_p, "i": ctypes.c_int32, "l": ctypes.c_int64, "f": ctypes.c_float, "z": ctypes.c_size_t}
     for fn, args in (("score_rowstats", "ppliiiillllfipp"), ("score_colsums", "ppliiiillllfiipppp"), ("score_blocks", "ppliiiillllfiiippppzp"),
-                     ("gather_gemm", "pllplplppliiip"), ("gather_gemm_dx", "pllplpllpiiip"), ("gather_gemm_dw", "plpllplpliiipzp")):
+                     ("select_topk", "pliipp"), ("gather_gemm", "pllplplppliiip"), ("gather_gemm_dx", "pllplpllpiiip"), ("gather_gemm_dw", "plpllplpliiipzp")):
         getattr(lib, "lemo_" + fn).argtypes = [kinds[k] for k in args]
     seen = ctypes.c_int.in_dll(hip, "n_launched")
     names, threads = (ctypes.c_char_p * 64).in_dll(hip, "launched"), (ctypes.c_int * 64).in_dll(hip, "threads")
@@ -63,6 +63,9 @@ def run(runtime):
 
     def blocks(dt, d, S, H, flags):
         return lib.lemo_score_blocks(P, P, S, H, H, d, dt, H * d, d, H * d, d, 0, 64, flags, 0, P, None, P, P, 1 << 40, None)
+
+    def topk(S, L):
+        return lib.lemo_select_topk(P, S, L, max(1, L // 3), P, None)
 
     def gemm(dt, M, N, K):
         return lib.lemo_gather_gemm(P, M, K, None, M, P, K, None, P, N, K, N, dt, None)
@@ -76,7 +79,7 @@ def run(runtime):
     out = []
     for entry, *args in json.load(sys.stdin):
         seen.value = 0
-        rc = {"sweeps": sweeps, "blocks": blocks, "gemm": gemm, "gemm_dx": gemm_dx, "gemm_dw": gemm_dw}[entry](*args)
+        rc = {"sweeps": sweeps, "blocks": blocks, "topk": topk, "gemm": gemm, "gemm_dx": gemm_dx, "gemm_dw": gemm_dw}[entry](*args)
         assert rc == 0, (entry, args, rc)
         out.append([(names[i].decode(), threads[i]) for i in range(seen.value)])
     json.dump(out, sys.stdout)
@@ -192,6 +195,13 @@ def test_the_shapes_of_the_eight_wave_tests_take_them(routes):
 def test_rectangles_in_quarters_only_where_they_are_faster(launches, d, S, H, causal, first):
     names = [name for name, _ in launches([("blocks", BF16, d, S, H, causal)])[0]]
     assert len(names) == 2 and re.match(r"_ZN4lemo\d+" + first, names[0]), names
+
+
+@pytest.mark.parametrize("S,L,threads", [(32768, 16, 256), (32768, 128, 256), (32768, 129, 512), (100, 4096, 256), (4096, 2048, 512), (4096, 2049, 1024), (32768, 32768, 1024)])
+def test_threads_of_a_selection(launches, S, L, threads):
+    """Short segments on few threads: on 512, all scores equal, they were slower than with digits of 8 bits."""
+    (name, n), = launches([("topk", S, L)])[0]
+    assert "select_topk_kernel" in name and n == threads
 
 
 @pytest.mark.parametrize("entry", ["gemm", "gemm_dw"])
